@@ -7,11 +7,13 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
-SOURCES = ["engine.hip", "decode.hip", "enc_proj.hip", "probes.hip"]
+SOURCES = ["engine.hip", "decode.hip", "resident.hip", "enc_proj.hip", "probes.hip"]
 # the decode kernel is instantiated in one unit per (loop nest, row groups, weight storage),
 # all compiled from decode_inst.hip, so that the instances build in parallel
 INSTANCES = [(nest, rg, wt) for wt in ("f32", "bf16", "fp8", "bf16a", "fp8a", "fp4a") for nest in ("f", "l")
              for rg in (1, 2, 4)] + [("s", 1, wt) for wt in ("f32", "bf16", "fp8", "bf16a", "fp8a", "fp4a")]
+# the decode kernel with register-resident weights: one unit per (kind, bfloat16 mode, size class)
+RESIDENT = [(kind, bf, cls) for kind, bf in ((1, 0), (1, 1), (2, 1), (3, 0)) for cls in (0, 1, 2)]
 LIB = os.path.join(HERE, "librnnt_greedy.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 FLAGS = ((["-DRNNT_PROFILE"] if os.environ.get("RNNT_PROFILE") else []) +
@@ -56,6 +58,8 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
     jobs_ = [("decode_inst.hip", f"decode_{nest}{rg}_{wt}",
               [f"-DRNNT_INST_NEST={nest}", f"-DRNNT_INST_RG={rg}", f"-DRNNT_INST_WT={wt}"])
              for nest, rg, wt in INSTANCES]
+    jobs_ += [("resident_inst.hip", f"resident_{kind}_{bf}_{cls}",
+               [f"-DRNNT_RES_KIND={kind}", f"-DRNNT_RES_BF={bf}", f"-DRNNT_RES_CLS={cls}"]) for kind, bf, cls in RESIDENT]
     jobs_ += [(src, src.replace(".hip", ""), []) for src in SOURCES]
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, os.cpu_count() or 1))) as pool:
         objs = list(pool.map(compile_one, jobs_))

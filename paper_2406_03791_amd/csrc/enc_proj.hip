@@ -18,6 +18,27 @@ __device__ __forceinline__ float bf16_rne(float v)
     return __uint_as_float(u);
 }
 
+// What a decode call needs cleared before its decode kernel starts, done by the blocks of the
+// projection on the way (a kernel of its own would be one more launch in front of a decode of a
+// few hundred microseconds): the synchronisation words, and the output rows' fill (-1 and 0).
+__device__ __forceinline__ void init_call(const CallInit &ci, int b)
+{
+    const int nx = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x;
+    if (b == 0 && id == 0) {
+        for (int i = threadIdx.x; i < ci.n_form; i += blockDim.x) ci.form[i] = 0u;
+        if (threadIdx.x == 0 && ci.abort_flag) { *ci.abort_flag = 0u; *ci.status = 0; }
+    }
+    if (!ci.tokens) return;
+    const long long o = (long long)b * ci.cap;
+    for (int i = id * blockDim.x + threadIdx.x; i < ci.cap; i += nx * blockDim.x) {
+        ci.tokens[o + i] = -1;
+        if (ci.frames) ci.frames[o + i] = -1;
+        if (ci.logits) ci.logits[o + i] = 0.f;
+        if (ci.logps) ci.logps[o + i] = 0.f;
+        if (ci.durs) ci.durs[o + i] = -1;
+    }
+}
+
 // grid: (ceil(T/BM), ceil(J/BN), B); 256 threads = 4 waves in 2 x 2, each a (BM/2) x 64 tile.
 // BM = 128 reuses a loaded weight tile for twice the rows; BM = 64 wastes less on the tiles of an
 // utterance's last frames and spreads a small batch more evenly over the compute units (the
@@ -29,12 +50,13 @@ template <int BM>
 __global__ void __launch_bounds__(256)
 enc_proj_kernel(const float *__restrict__ x, const int *__restrict__ enc_len,
                 const float *__restrict__ w_enc, const float *__restrict__ b_enc,
-                float *__restrict__ proj, int T, int F, int J)
+                float *__restrict__ proj, int T, int F, int J, const CallInit ci)
 {
     constexpr int MI = BM / 64;     // 32-row MFMA tiles of a wave along M (its share of BM is 32 * MI rows)
     __shared__ float As[KT][BM + LDP];
     __shared__ float Bs[KT][BN + LDP];
     const int b = blockIdx.z;
+    init_call(ci, b);
     int len = enc_len[b];
     len = min(max(len, 0), T);
     const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
@@ -146,7 +168,7 @@ template <int BM>
 __global__ void __launch_bounds__(256)
 enc_proj_bf16_kernel(const float *__restrict__ x, const int *__restrict__ enc_len,
                      const float *__restrict__ w_enc, const float *__restrict__ b_enc,
-                     float *__restrict__ proj, int T, int F, int J)
+                     float *__restrict__ proj, int T, int F, int J, const CallInit ci)
 {
     constexpr int MI = BM / 64;
     constexpr int NA = BM / 32;          // float4 of A a thread stages per K tile (BM * 8 / 256)
@@ -154,6 +176,7 @@ enc_proj_bf16_kernel(const float *__restrict__ x, const int *__restrict__ enc_le
     __shared__ __align__(16) unsigned short As[BM][LDB];
     __shared__ __align__(16) unsigned short Bs[BN][LDB];
     const int b = blockIdx.z;
+    init_call(ci, b);
     int len = enc_len[b];
     len = min(max(len, 0), T);
     const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
@@ -247,7 +270,7 @@ enc_proj_bf16_kernel(const float *__restrict__ x, const int *__restrict__ enc_le
 
 hipError_t launch_encoder_projection(const float *enc_out, const int *enc_len, const float *w_enc,
                                      const float *b_enc, float *proj, int B, int T, int F, int J,
-                                     bool round_x, hipStream_t stream)
+                                     bool round_x, const CallInit &ci, hipStream_t stream)
 {
     // the smaller row tile while the larger one would give each compute unit only a few blocks
     const long long blocks128 = (long long)((T + 127) / 128) * ((J + BN - 1) / BN) * B;
@@ -257,18 +280,30 @@ hipError_t launch_encoder_projection(const float *enc_out, const int *enc_len, c
     if (small_tile) {
         if (round_x)
             hipLaunchKernelGGL((enc_proj_bf16_kernel<64>), grid, dim3(256), 0, stream, enc_out, enc_len, w_enc,
-                               b_enc, proj, T, F, J);
+                               b_enc, proj, T, F, J, ci);
         else
             hipLaunchKernelGGL((enc_proj_kernel<64>), grid, dim3(256), 0, stream, enc_out, enc_len, w_enc,
-                               b_enc, proj, T, F, J);
+                               b_enc, proj, T, F, J, ci);
     } else {
         if (round_x)
             hipLaunchKernelGGL((enc_proj_bf16_kernel<128>), grid, dim3(256), 0, stream, enc_out, enc_len, w_enc,
-                               b_enc, proj, T, F, J);
+                               b_enc, proj, T, F, J, ci);
         else
             hipLaunchKernelGGL((enc_proj_kernel<128>), grid, dim3(256), 0, stream, enc_out, enc_len, w_enc,
-                               b_enc, proj, T, F, J);
+                               b_enc, proj, T, F, J, ci);
     }
+    return hipGetLastError();
+}
+
+__global__ void reset_resident_kernel(unsigned *form, int n_form, unsigned *abort_flag)
+{
+    for (int i = threadIdx.x; i < n_form; i += blockDim.x) form[i] = 0u;
+    if (threadIdx.x == 0) *abort_flag = 0u;
+}
+
+hipError_t launch_reset_resident(unsigned *form, int n_form, unsigned *abort_flag, hipStream_t stream)
+{
+    hipLaunchKernelGGL(reset_resident_kernel, dim3(1), dim3(256), 0, stream, form, n_form, abort_flag);
     return hipGetLastError();
 }
 

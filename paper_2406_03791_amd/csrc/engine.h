@@ -95,12 +95,25 @@ struct DecodeParams {
 // (zero_stats); later launches add to them.
 hipError_t launch_decode(const DecodeParams &p, bool zero_status, bool zero_stats, hipStream_t stream);
 
+// What the projection kernel clears for the decode kernel behind it; nothing where NULL.
+struct CallInit {
+    unsigned *form = nullptr;       // meeting words of the resident decode kernel
+    int n_form = 0;
+    unsigned *abort_flag = nullptr;
+    int *status = nullptr;
+    int *tokens = nullptr, *frames = nullptr, *durs = nullptr;   // output rows [B, cap]
+    float *logits = nullptr, *logps = nullptr;
+    int cap = 0;
+};
+
 // Keeps the text of a failed HIP call for rnnt_status_string; returns RNNT_ERR_HIP.
 int hip_fail(hipError_t e, const char *what);
 
 hipError_t launch_encoder_projection(const float *enc_out, const int *enc_len, const float *w_enc,
                                      const float *b_enc, float *proj, int B, int T, int F, int J,
-                                     bool round_x, hipStream_t stream);
+                                     bool round_x, const CallInit &ci, hipStream_t stream);
+// Clears what a further launch of the resident decode kernel within a call needs cleared.
+hipError_t launch_reset_resident(unsigned *form, int n_form, unsigned *abort_flag, hipStream_t stream);
 // v[i] = nearest bfloat16 value of v[i] (ties to even), in place
 hipError_t launch_round_bf16(float *v, long long n, hipStream_t stream);
 // T0[v][u][g] = b_ih0[g*H+u] + b_hh0[g*H+u] + sum_e W_ih0[g*H+u][e] * emb[v][e]

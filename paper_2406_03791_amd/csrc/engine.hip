@@ -19,6 +19,8 @@
 
 #include "engine.h"
 #include "pack.h"
+#include "resident.h"
+#include "resident_pack.h"
 
 using namespace rnnt;
 
@@ -94,6 +96,9 @@ struct Workspace {
     unsigned *bar = nullptr, *abort_flag = nullptr;
     int *status = nullptr, *xcc = nullptr;
     long long *stats = nullptr;
+    // resident kernel: exchange buffers of all teams, meeting words
+    unsigned char *xbuf = nullptr;
+    unsigned *form = nullptr;
 };
 
 // Bytes of each part of the team workspace for a layout (everything but P).
@@ -145,6 +150,13 @@ struct rnnt_engine {
     DevBuf w_enc, b_enc, T0, bias_l, b_pred, b_out;
     DevBuf sc_hh, sc_ih, sc_pred, sc_out;   // e4m3 storage in the bfloat16 mode: power-of-two scale of every weight row
     DevBuf P, abort_flag, status;
+    // The decode kernel with register-resident weights runs the calls of a model that fits it
+    // (res.kind), unless rnnt_engine_configure asks for a team layout, lookahead or search limit:
+    // those are the streaming kernel's, whose layouts are made then (or at once for other models).
+    ResidentPlan res{};
+    DevBuf res_w, res_help, res_tail, res_xbuf, res_form, res_stats;
+    bool use_streaming = true;
+    bool own_layout = false;        // n_teams was configured
     // Team layouts, one per range of launch sizes in which the measured best arrangement (or
     // the rows per team, hence the prediction path) changes, in ascending order of for_B: a
     // launch of nb utterances runs in the first layout planned for at least nb.  An engine for
@@ -154,6 +166,7 @@ struct rnnt_engine {
     // layouts (and workspaces) the launches of the last call ran in: where its statistics are
     struct Used { const TeamConfig *t; Workspace ws; int nb; };   // nb: utterances of its latest launch
     std::vector<Used> last_used;
+    bool last_resident = false;     // the last call ran in the resident kernel
     Workspace last_ws;      // where the last call kept its status word
     int last_B = 0;
     void *scratch = nullptr;   // device address of the library's static scratch array on the engine's device
@@ -528,18 +541,123 @@ int check_call(rnnt_engine *e, const float *enc_out, const int32_t *enc_len, int
     return RNNT_OK;
 }
 
+// ---- resident decode kernel ---------------------------------------------------------------
+Workspace resident_workspace(const rnnt_engine *e)
+{
+    Workspace w;
+    w.P = e->P.as<float>(); w.abort_flag = e->abort_flag.as<unsigned>(); w.status = e->status.as<int>();
+    w.stats = e->res_stats.as<long long>(); w.xbuf = e->res_xbuf.as<unsigned char>(); w.form = e->res_form.as<unsigned>();
+    return w;
+}
+
+// Packs the weights for the resident kernel.  Synchronous.
+int make_resident(rnnt_engine *e)
+{
+    const ResidentPlan &pl = e->res;
+    auto put = [](DevBuf &dst, const void *src, size_t bytes) -> int {
+        HIP_TRY(dst.alloc(bytes));
+        HIP_TRY(hipMemcpy(dst.p, src, bytes, hipMemcpyHostToDevice));
+        return RNNT_OK;
+    };
+    const ResidentWeights rw{e->d.H, e->d.J, e->d.L, &e->w_hh, &e->w_ih, &e->w_pred, &e->w_out};
+    int rc;
+    {
+        const std::vector<uint32_t> w = pack_resident_main(pl, rw);
+        if ((rc = put(e->res_w, w.data(), w.size() * 4))) return rc;
+    }
+    if (pl.kind == kResident2Pair) {
+        const std::vector<uint32_t> w = pack_resident_helper(pl, rw);
+        if ((rc = put(e->res_help, w.data(), w.size() * 4))) return rc;
+    }
+    if (pl.n_tail) {
+        std::vector<float> t((size_t)pl.n_tail * res_row(pl.cls), 0.f);
+        for (int i = 0; i < pl.n_tail; ++i)
+            std::copy_n(e->w_out.data() + (size_t)(pl.nout_m + i) * e->d.J, e->d.J, t.data() + (size_t)i * res_row(pl.cls));
+        if ((rc = put(e->res_tail, t.data(), t.size() * 4))) return rc;
+    }
+    HIP_TRY(e->res_xbuf.alloc((size_t)resident_buf(pl.cls).bytes * pl.n_teams));
+    HIP_TRY(e->res_form.alloc((size_t)pl.n_xcd * 32 * sizeof(unsigned)));
+    HIP_TRY(e->res_stats.alloc((size_t)pl.n_teams * kStatStride * sizeof(long long)));
+    HIP_TRY(hipMemset(e->res_form.p, 0, (size_t)pl.n_xcd * 32 * sizeof(unsigned)));
+    HIP_TRY(hipMemset(e->res_stats.p, 0, (size_t)pl.n_teams * kStatStride * sizeof(long long)));
+    return RNNT_OK;
+}
+
+// Utterances a team decodes at a time and frames per utterance and joint step for a launch of nb.
+void resident_rows(const ResidentPlan &pl, int nb, int *slots, int *la)
+{
+    *slots = std::min(kResRows, (nb + pl.n_teams - 1) / pl.n_teams);
+    *la = *slots <= 2 ? 16 / *slots : kResSamples / *slots;
+    *la = std::min(*la, 16);
+}
+
+int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_t *enc_len, int32_t B, int32_t T, int32_t S,
+                 int32_t *tokens_out, int32_t *tok_len_out, int32_t cap, int32_t *frames_out, float *logit_out,
+                 int32_t *durs_out, hipStream_t stream, const Workspace *static_ws)
+{
+    const rnnt_model_desc &d = e->d;
+    const ResidentPlan &pl = e->res;
+    const Workspace ws = static_ws ? *static_ws : resident_workspace(e);
+    CallInit ci;
+    ci.form = ws.form; ci.n_form = pl.n_xcd * 32; ci.abort_flag = ws.abort_flag; ci.status = ws.status;
+    ci.tokens = tokens_out; ci.frames = frames_out; ci.durs = durs_out; ci.logits = logit_out; ci.logps = e->logp_out;
+    ci.cap = cap;
+    HIP_TRY(hipEventRecord(e->ev[0], stream));
+    HIP_TRY(launch_encoder_projection(enc_out, enc_len, e->w_enc.as<float>(), e->b_enc.as<float>(), ws.P, B, T, d.F, d.J,
+                                      is_bf16_arith(e->wt), ci, stream));
+    HIP_TRY(hipEventRecord(e->ev[1], stream));
+    e->last_B = B; e->last_used.clear(); e->last_ws = ws; e->last_resident = true;
+    const int launch_rows = kResList * pl.n_teams;
+    for (int off = 0; off < B; off += launch_rows) {
+        const int nb = std::min(launch_rows, B - off);
+        if (off > 0) HIP_TRY(launch_reset_resident(ws.form, pl.n_xcd * 32, ws.abort_flag, stream));
+        ResidentParams p{};
+        p.H = d.H; p.J = d.J; p.V1 = d.V1; p.NOUT = e->NOUT; p.blank = d.blank;
+        p.tdt = variant == kTdtLabelLooping;
+        p.D = p.tdt ? d.D : 0;
+        p.VT = e->multi_blank ? e->NOUT : d.V1;
+        for (int i = 0; i < kMaxDur; ++i) p.durations[i] = e->durations[i];
+        p.B = nb; p.T = T; p.S = S; p.cap = cap;
+        resident_rows(pl, nb, &p.slots, &p.la);
+        p.spin_limit = e->spin_limit;
+        p.pl = pl;
+        const long long oc = (long long)off * cap;
+        p.enc_len = enc_len + off; p.P = ws.P + (long long)off * T * d.J;
+        p.tokens = tokens_out + oc; p.tok_len = tok_len_out + off;
+        p.frames = frames_out ? frames_out + oc : nullptr;
+        p.logits = logit_out ? logit_out + oc : nullptr;
+        p.durs = durs_out ? durs_out + oc : nullptr;
+        p.logps = e->logp_out ? e->logp_out + oc : nullptr;
+        p.done = e->done ? e->done + off : nullptr;
+        p.w = e->res_w.as<float>(); p.w_help = e->res_help.as<float>(); p.w_tail = e->res_tail.as<float>();
+        p.T0 = e->T0.as<float>(); p.bias_l = e->bias_l.as<float>(); p.b_pred = e->b_pred.as<float>(); p.b_out = e->b_out.as<float>();
+        p.xbuf = ws.xbuf;
+        p.form = ws.form; p.abort_flag = ws.abort_flag; p.status = ws.status; p.stats = ws.stats;
+        p.zero_stats = off == 0;
+        p.count_rows = variant == kFrameLooping;
+        HIP_TRY(launch_resident(p, p.slots <= 4 ? 1 : 2, p.slots * p.la <= 16 ? 1 : 2, e->plain_launch, stream));
+    }
+    HIP_TRY(hipEventRecord(e->ev[2], stream));
+    e->timed = true;
+    return RNNT_OK;
+}
+
 int run_decode(rnnt_engine *e, int variant, const float *enc_out, const int32_t *enc_len, int32_t B,
                int32_t T, int32_t S, int32_t *tokens_out, int32_t *tok_len_out, int32_t cap,
                int32_t *frames_out, float *logit_out, int32_t *durs_out, hipStream_t stream,
                const Workspace *static_ws = nullptr)
 {
     const rnnt_model_desc &d = e->d;
+    if (!e->use_streaming)
+        return run_resident(e, variant, enc_out, enc_len, B, T, S, tokens_out, tok_len_out, cap, frames_out, logit_out,
+                            durs_out, stream, static_ws);
+    e->last_resident = false;
     const auto &cfgs = variant == kFrameLooping ? e->frame_cfgs : e->label_cfgs;
     // every launch reads the projected frames of the whole call from one buffer
     float *P = static_ws ? static_ws->P : e->P.as<float>();
     HIP_TRY(hipEventRecord(e->ev[0], stream));
     HIP_TRY(launch_encoder_projection(enc_out, enc_len, e->w_enc.as<float>(), e->b_enc.as<float>(),
-                                      P, B, T, d.F, d.J, is_bf16_arith(e->wt), stream));
+                                      P, B, T, d.F, d.J, is_bf16_arith(e->wt), CallInit(), stream));
     HIP_TRY(hipEventRecord(e->ev[1], stream));
     e->last_B = B;
     e->last_used.clear();
@@ -808,7 +926,13 @@ int rnnt_engine_create(const rnnt_model_desc *desc, int32_t max_B, int32_t max_T
     HIP_TRY(e->status.alloc(sizeof(int)));
     HIP_TRY(hipMemset(e->abort_flag.p, 0, sizeof(unsigned)));
     HIP_TRY(hipMemset(e->status.p, 0, sizeof(int)));
-    if ((rc = default_layouts(e))) return rc;
+    e->res = plan_resident(d.H, d.J, d.L, e->NOUT, is_bf16_arith(e->wt), prop.multiProcessorCount);
+    if (e->res.kind != kResidentNone) {
+        if ((rc = make_resident(e))) return rc;
+        e->use_streaming = false;
+    } else if ((rc = default_layouts(e))) {
+        return rc;
+    }
     for (auto &x : e->ev) HIP_TRY(hipEventCreate(&x));
     HIP_TRY(hipDeviceSynchronize());
     guard.e = nullptr;
@@ -879,6 +1003,19 @@ int rnnt_engine_configure(rnnt_engine *eng, int32_t n_teams, int32_t joint_group
     if (n_teams == 0 && joint_groups != 0) return RNNT_ERR_SHAPE;
     if (search_steps < -1) return RNNT_ERR_SHAPE;
     HIP_TRY(hipDeviceSynchronize());
+    if (eng->res.kind != kResidentNone) {
+        eng->own_layout = eng->own_layout || n_teams > 0;
+        const bool streaming = eng->own_layout || lookahead != 0 || search_steps != 0;
+        if (streaming && eng->label_cfgs.empty() && n_teams == 0) {
+            const int rc = default_layouts(eng);
+            if (rc) return rc;
+        }
+        eng->last_used.clear();
+        eng->last_ws = Workspace();
+        eng->last_resident = false;
+        eng->use_streaming = streaming;
+        if (!streaming) { eng->lookahead = 0; eng->search_steps = 0; return RNNT_OK; }
+    }
     if (n_teams > 0) {
         eng->last_used.clear();       // the workspaces the last call's statistics live in go away
         eng->last_ws = Workspace();
@@ -972,6 +1109,28 @@ int rnnt_label_looping_decode_noalloc(rnnt_engine *eng, const float *enc_out, co
     if (rc) return rc;
     if (eng->d.D != 0 && !eng->multi_blank) return RNNT_ERR_VARIANT;
     if (!eng->scratch) return RNNT_ERR_UNSUPPORTED;
+    if (!eng->use_streaming) {
+        if (B > kLaunchRows) return RNNT_ERR_SCRATCH;
+        const ResidentPlan &pl = eng->res;
+        size_t off = 0;
+        auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
+        const size_t o_P = take((size_t)B * T * eng->d.J * sizeof(float));
+        const size_t o_x = take((size_t)resident_buf(pl.cls).bytes * pl.n_teams);
+        const size_t o_f = take((size_t)pl.n_xcd * 32 * sizeof(unsigned));
+        const size_t o_s = take((size_t)pl.n_teams * kStatStride * sizeof(long long));
+        const size_t o_a = take(sizeof(unsigned)), o_st = take(sizeof(int));
+        if (off > (size_t)RNNT_NOALLOC_SCRATCH_BYTES) return RNNT_ERR_SCRATCH;
+        unsigned char *base = static_cast<unsigned char *>(eng->scratch);
+        Workspace ws;
+        ws.P = reinterpret_cast<float *>(base + o_P);
+        ws.xbuf = base + o_x;
+        ws.form = reinterpret_cast<unsigned *>(base + o_f);
+        ws.stats = reinterpret_cast<long long *>(base + o_s);
+        ws.abort_flag = reinterpret_cast<unsigned *>(base + o_a);
+        ws.status = reinterpret_cast<int *>(base + o_st);
+        return run_decode(eng, kLabelLooping, enc_out, enc_len, B, T, max_symbols, tokens_out, tok_len_out, cap, frames_out,
+                          logit_out, nullptr, static_cast<hipStream_t>(stream), &ws);
+    }
     // one launch only: the workspace is that of one layout
     if (B > eng->label_cfgs.back()->for_B) return RNNT_ERR_SCRATCH;
     // carve the call's workspace out of the static array, every part 256-byte aligned
@@ -1029,7 +1188,7 @@ int rnnt_encoder_projection(rnnt_engine *eng, const float *enc_out, const int32_
     if ((reinterpret_cast<uintptr_t>(enc_out) & 15u) != 0) return RNNT_ERR_SHAPE;
     HIP_TRY(launch_encoder_projection(enc_out, enc_len, eng->w_enc.as<float>(),
                                       eng->b_enc.as<float>(), proj_out, B, T, eng->d.F, eng->d.J,
-                                      is_bf16_arith(eng->wt), static_cast<hipStream_t>(stream)));
+                                      is_bf16_arith(eng->wt), CallInit(), static_cast<hipStream_t>(stream)));
     return RNNT_OK;
 }
 
@@ -1047,6 +1206,32 @@ int rnnt_engine_stats(rnnt_engine *eng, rnnt_stats *out)
     if (!eng || !out) return RNNT_ERR_NULL;
     HIP_TRY(hipDeviceSynchronize());
     std::memset(out, 0, sizeof(*out));
+    if (eng->last_resident) {
+        const ResidentPlan &pl = eng->res;
+        std::vector<long long> st((size_t)pl.n_teams * kStatStride);
+        HIP_TRY(hipMemcpy(st.data(), eng->last_ws.stats, st.size() * sizeof(long long), hipMemcpyDeviceToHost));
+        for (int i = 0; i < pl.n_teams; ++i) {
+            const long long *s = st.data() + (size_t)i * kStatStride;
+            out->pred_steps += s[kStatPred];
+            out->joint_steps += s[kStatJoint];
+            out->joint_samples += s[kStatSamples];
+            out->barrier_polls += s[kStatPolls];
+            out->max_pred_steps = std::max<int64_t>(out->max_pred_steps, s[kStatPred]);
+            out->max_joint_steps = std::max<int64_t>(out->max_joint_steps, s[kStatJoint]);
+        }
+        int slots, la;
+        resident_rows(pl, std::min(eng->last_B, kResList * pl.n_teams), &slots, &la);
+        out->n_teams = pl.n_teams;
+        out->team_size = res_team(pl.cls) * (pl.kind == kResident2Pair ? 2 : 1);
+        out->joint_groups = 1;
+        out->lookahead = la;
+        out->search_steps = 1;
+        if (eng->timed) {
+            HIP_TRY(hipEventElapsedTime(&out->projection_ms, eng->ev[0], eng->ev[1]));
+            HIP_TRY(hipEventElapsedTime(&out->decode_ms, eng->ev[1], eng->ev[2]));
+        }
+        return RNNT_OK;
+    }
     if (eng->last_used.empty()) return RNNT_OK;
     // a call of more utterances than one launch takes may have run in more than one layout:
     // the counts are sums over them, the longest chains the largest per-team sums
@@ -1096,6 +1281,14 @@ int rnnt_engine_phase_timers(rnnt_engine *eng, int32_t team, double *us_out, int
     if (!eng || !us_out) return RNNT_ERR_NULL;
 #ifdef RNNT_PROFILE
     // (of the layout the call's first launch ran in)
+    if (eng->last_resident) {
+        if (team < 0 || team >= eng->res.n_teams || n < 0) return RNNT_ERR_SHAPE;
+        HIP_TRY(hipDeviceSynchronize());
+        long long raw[kStatProf];
+        HIP_TRY(hipMemcpy(raw, eng->last_ws.stats + (size_t)team * kStatStride + kStatCount, sizeof raw, hipMemcpyDeviceToHost));
+        for (int i = 0; i < n; ++i) us_out[i] = i < kStatProf ? raw[i] * 0.01 : 0.0;   // 100 MHz clock
+        return RNNT_OK;
+    }
     if (eng->last_used.empty()) return RNNT_ERR_SHAPE;
     const TeamConfig *t = eng->last_used.front().t;
     if (team < 0 || team >= t->n_teams || n < 0) return RNNT_ERR_SHAPE;

@@ -1,0 +1,51 @@
+"""The decode kernel with register-resident weights at the edges of what it holds: the widest and
+narrowest layers of every size class and one unit beyond, output layers that just fill the column
+tiles, the tail columns and no longer, one and two layers, one utterance, teams whose list is longer
+than the rows they decode at a time, and more utterances than one launch takes.  Against the
+oracle, through the C ABI."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import synth
+from test_gpu_parity import check, pkg  # noqa: F401  (pkg: fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def model_inputs(H, J, V1, L, B, T, seed, durations=(), big_blanks=(), max_symbols=4):
+    dims = synth.ModelDims(F=32, E=24, H=H, L=L, J=J, V1=V1, durations=tuple(durations), big_blanks=tuple(big_blanks))
+    model = synth.make_model(dims, seed, weight_range=0.15, emb_gain=4.0, pred_gain=3.0, blank_bias=1.5)
+    x, ln = synth.make_inputs(seed, B, T, dims.F, 0, T)
+    variant = "tdt" if durations else "label"
+    return synth.Workload(f"resident {H}/{J}/{V1}/{L}", variant, model, x, ln, max_symbols)
+
+
+# (H, J, V1, L): widths of the size classes 128, 320 and 640 and their neighbours; output layers of
+# 32 columns per work-group (8, 16, 32 of them), with a full tail, and one more
+EDGES = [(4, 4, 3, 1), (128, 128, 256, 1), (132, 128, 257, 2), (128, 132, 264, 1), (320, 316, 512, 2), (316, 320, 528, 1),
+         (324, 320, 529, 1), (640, 640, 1024, 1), (640, 636, 1056, 2), (636, 640, 1057, 1), (644, 640, 40, 1), (160, 640, 33, 2)]
+
+
+@pytest.mark.parametrize("H,J,V1,L", EDGES)
+@pytest.mark.parametrize("bf16", [False, True])
+def test_edges_of_the_size_classes(pkg, H, J, V1, L, bf16):  # noqa: F811
+    w = model_inputs(H, J, V1, L, B=9, T=14, seed=H + J + V1)
+    eng = pkg.Engine(w.model, w.B, w.T, flags=pkg.RNNT_FLAG_BF16_ARITHMETIC if bf16 else 0)
+    for variant in ("label", "frame"):
+        check(pkg, w, variant, f"edge {H}/{J}/{V1}/{L} bf16={bf16}", engine=eng, bf16=bf16, logp=True)
+    one = dataclasses.replace(w, enc_out=w.enc_out[:1].copy(), enc_len=np.maximum(w.enc_len[:1], 3))
+    check(pkg, one, "label", f"edge {H}/{J}/{V1}/{L} bf16={bf16}, one utterance", engine=eng, bf16=bf16)
+    eng.close()
+
+
+@pytest.mark.parametrize("B", [2, 33, 70, 515])
+@pytest.mark.parametrize("extra", [{}, dict(durations=(0, 1, 3, 7)), dict(big_blanks=(2, 5))])
+def test_lists_longer_than_the_rows_in_work(pkg, B, extra):  # noqa: F811
+    """Every decoder with one row per team, a partly filled last row, rows that take over the next
+    utterance of the team's list, and (515 utterances on 4 teams) a second launch."""
+    w = model_inputs(324, 332, 530 if not extra else 520, 2, B=B, T=9, seed=B, **extra)
+    eng = pkg.Engine(w.model, w.B, w.T)
+    check(pkg, w, w.variant, f"list {B} {extra}", engine=eng, logp=True)
+    eng.close()
