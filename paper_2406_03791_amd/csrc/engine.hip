@@ -635,7 +635,7 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
         p.form = ws.form; p.abort_flag = ws.abort_flag; p.status = ws.status; p.stats = ws.stats;
         p.zero_stats = off == 0;
         p.count_rows = variant == kFrameLooping;
-        HIP_TRY(launch_resident(p, p.slots <= 4 ? 1 : 2, p.slots * p.la <= 16 ? 1 : 2, e->plain_launch, stream));
+        HIP_TRY(launch_resident(p, p.slots * p.la <= 16 ? 1 : 2, e->plain_launch, stream));
     }
     HIP_TRY(hipEventRecord(e->ev[2], stream));
     e->timed = true;

@@ -12,7 +12,7 @@ constexpr int kResThreads = 512;          // eight waves, two per SIMD: 256 regi
 constexpr int kResWaves = 8;
 constexpr int kResUnits = 20;             // LSTM units per work-group at most
 constexpr int kResSlots = 4;              // exchange slots per vector, used in turn
-constexpr int kResRows = 8;               // utterances a team decodes at the same time at most
+constexpr int kResRows = 4;               // utterances a team decodes at the same time at most
 constexpr int kResSamples = 32;           // (utterance, frame) pairs per joint step at most
 constexpr int kResList = 128;             // utterances a team takes per launch at most
 
@@ -29,12 +29,12 @@ RNNT_HD constexpr int res_piece_regs(bool bf) { return bf ? 2 : 4; }
 RNNT_HD constexpr int res_pieces(int cls) { return res_width(cls) / 4; }
 // LSTM stages: waves 0 .. 5 hold a sixth of K for units 0 .. 15, waves 6 and 7 an eighth per block for units 16 .. 19
 RNNT_HD constexpr int res_lstm_pieces(int cls) { return (res_pieces(cls) + 5) / 6; }
-// prediction-side projection: a group per pair of waves (half of K each), and an eighth of a fifth group
-RNNT_HD constexpr int res_pred_own(int cls) { return (res_pieces(cls) + 31) / 32; }
-RNNT_HD constexpr int res_pred_fifth(int cls) { return (res_pieces(cls) + 127) / 128; }
+// prediction-side projection: fifteen of a wave's blocks are five groups of columns times three slices of K, so
+// 24 slices in all
+RNNT_HD constexpr int res_pred_pieces(int cls) { return (res_pieces(cls) + 23) / 24; }
 // joint steps per wave: 16 K values each, every eighth one of the joint width
 RNNT_HD constexpr int res_joint_steps(int cls) { return res_row(cls) / 128; }
-// bytes of an activation row in LDS; rows of a row group start 64 bytes apart modulo the banks
+// bytes of an activation row in LDS; the rows start 64 bytes apart modulo the banks
 RNNT_HD constexpr int res_xrow(bool bf, int cls) { return res_width(cls) * (bf ? 2 : 4) + 64; }
 
 // Kinds of resident decoders (which weights sit where).
@@ -95,8 +95,8 @@ RNNT_HD constexpr ResidentBuf resident_buf(int cls)
     b.dur = b.key + recs * 8u;
     b.lse = b.dur + kResSlots * kResSamples * kMaxDur * 4u;
     b.hr[0] = b.lse + recs * 4u; b.hr[1] = b.hr[0] + vec; b.pre = b.hr[1] + vec;
-    // [layer][slot][rank][block of 16 (unit, row) pairs][lane]
-    b.bytes = b.pre + 2u * kResSlots * (unsigned)res_team(cls) * 10u * 64u * 4u;
+    // [layer][slot][rank][wave of the cells][lane]
+    b.bytes = b.pre + 2u * kResSlots * (unsigned)res_team(cls) * 5u * 64u * 4u;
     return b;
 }
 
@@ -104,39 +104,47 @@ RNNT_HD constexpr ResidentBuf resident_buf(int cls)
 // kResident2: both layers), input matrix of the second layer, prediction-side projection, joint
 // output.  The helpers of kResident2Pair hold the two recurrent matrices.
 RNNT_HD constexpr int res_lstm_regs(bool bf, int cls) { return res_lstm_pieces(cls) * res_piece_regs(bf); }
-RNNT_HD constexpr int res_pred_regs(bool bf, int cls) { return (res_pred_own(cls) + res_pred_fifth(cls)) * res_piece_regs(bf); }
+RNNT_HD constexpr int res_pred_regs(bool bf, int cls) { return res_pred_pieces(cls) * res_piece_regs(bf); }
 RNNT_HD constexpr int res_joint_regs(bool bf, int cls) { return res_joint_steps(cls) * 2 * res_piece_regs(bf); }
 RNNT_HD constexpr int res_main_regs(int kind, bool bf, int cls)
 {
     return (kind == kResident2 ? 3 : 1) * res_lstm_regs(bf, cls) + res_pred_regs(bf, cls) + res_joint_regs(bf, cls);
 }
 
-// LDS layout in bytes (dynamic part): frames of the joint step's samples (later the step's partial
-// sums), activation rows of the LSTM stages, q rows (before q arrives, partial sums of the input
-// stage), tail column, partial sums of the recurrent stages and of the projection.
-// rg: row groups, nmt: tiles of 16 samples.
-struct ResidentLds { int p, xh, q, tail, rec, g4, tpart, bytes; };
+// LDS layout in bytes (dynamic part): frames of the joint step's samples, activation rows of the LSTM
+// stages and partial sums of the projection (both done with when the joint step's partial sums take
+// their place; so rows that no utterance is in hold anything), q rows (zeros beyond the joint width: what
+// stands there is multiplied by zero weights), tail column, partial sums of the input stage and of the
+// recurrent stages.
+// nmt: tiles of 16 samples.
+struct ResidentLds { int p, part, xh, g4, q, tail, ih, rec, tpart, bytes; };
 constexpr int kResSumRow = 36;            // floats per sample row of the joint step's partial sums
-RNNT_HD constexpr ResidentLds resident_lds(int kind, bool bf, int cls, int rg, int nmt)
+RNNT_HD constexpr ResidentLds resident_lds(int kind, bool bf, int cls, int nmt)
 {
     ResidentLds l{};
-    const int p_frames = 16 * nmt * res_row(cls) * 4, p_sums = kResWaves * 16 * nmt * kResSumRow * 4;
-    const int stage = kResWaves * rg * 1024, q = 4 * rg * (res_row(cls) + 16) * 4;
+    const int frames = 16 * nmt * res_row(cls) * 4, sums = kResWaves * 16 * nmt * kResSumRow * 4;
+    const int stage = kResWaves * 1024, q = kResRows * (res_row(cls) + 16) * 4;
     l.p = 0;
-    l.xh = p_frames > p_sums ? p_frames : p_sums;
-    if (kind == kResident2Pair && l.xh < stage) l.xh = stage;         // (the helpers' partial sums)
-    l.q = l.xh + (kind == kResident1 ? 1 : 2) * 4 * rg * res_xrow(bf, cls);
-    l.tail = l.q + (q > stage ? q : stage);
-    l.rec = l.tail + res_row(cls) * 4;
-    l.g4 = l.rec + (kind == kResident2Pair ? 0 : stage);
-    l.tpart = l.g4 + 2 * kResWaves * rg * 16 * 4;
+    l.part = l.xh = frames;
+    if (kind == kResident2Pair && l.xh < stage) l.part = l.xh = stage;         // (the helpers' partial sums)
+    // (kResident2Pair: where the first layer's rows are large enough, the projection's sums take their place)
+    const int x_row = kResRows * res_xrow(bf, cls), proj = kResWaves * 60 * 16;
+    const bool over = kind == kResident2Pair && x_row >= proj;
+    l.g4 = over ? l.xh : l.xh + (kind == kResident1 ? 1 : 2) * x_row;
+    l.q = over ? l.xh + 2 * x_row : l.g4 + proj;
+    if (l.q < l.part + sums) l.q = l.part + sums;
+    l.tail = l.q + q;
+    l.ih = l.tail + res_row(cls) * 4;
+    l.rec = l.ih + (kind == kResident1 ? 0 : stage);
+    l.tpart = l.rec + (kind == kResident2Pair ? 0 : (kind == kResident2 ? 2 : 1) * stage);
     l.bytes = l.tpart + kResWaves * 2 * 16 * 4;
     return l;
 }
-static_assert(resident_lds(kResident2Pair, false, 0, 2, 2).bytes + 4096 <= 160 * 1024, "the largest layout and the control block fit the LDS");
+constexpr int kResCtl = 3840;             // bytes kept for the control block
+static_assert(resident_lds(kResident1, false, 0, 2).bytes + kResCtl <= 160 * 1024 && resident_lds(kResident2, true, 0, 2).bytes + kResCtl <= 160 * 1024 &&
+              resident_lds(kResident2Pair, false, 0, 2).bytes + kResCtl <= 160 * 1024, "the largest layouts and the control block fit the LDS");
 
-// rg: row groups (of four utterances) a team decodes at the same time, 1 or 2
 // nmt: tiles of 16 samples a joint step has, 1 or 2
-hipError_t launch_resident(const ResidentParams &p, int rg, int nmt, bool plain, hipStream_t stream);
+hipError_t launch_resident(const ResidentParams &p, int nmt, bool plain, hipStream_t stream);
 
 }  // namespace rnnt

@@ -34,6 +34,8 @@
 // everyone, which everyone sent after reading step n - 2; and it waits for that store before it
 // publishes step n + 1, so nobody can look for step n + 2's data in a slot that still holds old data.
 #pragma once
+#include <type_traits>
+
 #include "engine.h"
 #include "resident.h"
 
@@ -51,18 +53,21 @@ constexpr unsigned kStop = 0xfffffffeu;    // to the helpers: the team is done
 
 // Rows in work: every wave keeps a copy of its own and takes the same decisions from the same
 // results, so loop control needs no work-group barrier.
-struct RRows { int b[kResRows], len[kResRows], t[kResRows], n[kResRows], cnt[kResRows], active[kResRows]; };
+struct __align__(16) RRow { int t, len, n, cnt; };       // frame, frames, labels of this frame, labels; t >= len: idle
+struct RRows { RRow s[kResRows]; int b[kResRows], m[kResRows]; };   // utterance; t modulo the frames of a joint step
 
 struct RCtl {
     RRows rows[kResWaves];
     int s_k[kResSamples], s_d[kResSamples];        // results of a joint step
     float s_v[kResSamples], s_lp[kResSamples];
     int n_list, ok, st_clamped, st_overflow;
+    int dur[kMaxDur];
     int list_b[kResList], list_len[kResList];
     // this work-group's slices of the biases: second layer [unit][gate], projection, output and tail column
     float b1[kResUnits * 4], bp[20], bo[32], bt;
 };
 __shared__ RCtl rc;
+static_assert(sizeof(RCtl) <= kResCtl, "the control block has its place");
 
 // Phase timers (100 MHz wall clock), compiled in only for profiling builds.
 #ifdef RNNT_PROFILE
@@ -96,16 +101,28 @@ struct RCtx {
     int polls;
 };
 
-// stores that stay in the XCD's L2 / that go through to the memory side (sc1)
-__device__ __forceinline__ void put(const RCtx &x, unsigned off, unsigned imm, unsigned v)
+// A word for the team, and the mark into the slot that everyone has read (byte offsets `now` and `old` of
+// the slots): stores that stay in the XCD's L2, or go through to the memory side (sc1).
+__device__ __forceinline__ void put(const RCtx &x, unsigned off, unsigned now, unsigned old, unsigned v)
 {
-    if (x.local) __builtin_amdgcn_raw_buffer_store_b32(v, x.buf, (int)off, (int)imm, 0);
-    else __builtin_amdgcn_raw_buffer_store_b32(v, x.buf, (int)off, (int)imm, 16);
+    if (x.local) {
+        __builtin_amdgcn_raw_buffer_store_b32(v, x.buf, (int)off, (int)now, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(kMark, x.buf, (int)off, (int)old, 0);
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b32(v, x.buf, (int)off, (int)now, 16);
+        __builtin_amdgcn_raw_buffer_store_b32(kMark, x.buf, (int)off, (int)old, 16);
+    }
 }
-__device__ __forceinline__ void put2(const RCtx &x, unsigned off, unsigned imm, r2u v)
+__device__ __forceinline__ void put2(const RCtx &x, unsigned off, unsigned now, unsigned old, r2u v)
 {
-    if (x.local) __builtin_amdgcn_raw_buffer_store_b64(v, x.buf, (int)off, (int)imm, 0);
-    else __builtin_amdgcn_raw_buffer_store_b64(v, x.buf, (int)off, (int)imm, 16);
+    const r2u mark = {kMark, kMark};
+    if (x.local) {
+        __builtin_amdgcn_raw_buffer_store_b64(v, x.buf, (int)off, (int)now, 0);
+        __builtin_amdgcn_raw_buffer_store_b64(mark, x.buf, (int)off, (int)old, 0);
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b64(v, x.buf, (int)off, (int)now, 16);
+        __builtin_amdgcn_raw_buffer_store_b64(mark, x.buf, (int)off, (int)old, 16);
+    }
 }
 __device__ __forceinline__ void put_far(const RCtx &x, unsigned off, unsigned imm, unsigned v)
 {
@@ -192,27 +209,49 @@ template <> struct Piece<false> {
     static constexpr int N = 4, B = 16;
     float4 v;
     __device__ __forceinline__ void load(const unsigned char *p) { v = *reinterpret_cast<const float4 *>(p); }
+    // S, ID: the blocks form groups of 2^S that all take the operand of block ID of their group
+    template <int S = 0, int ID = 0>
     __device__ __forceinline__ void mfma(int e, const float *w, r4f &acc) const
     {
-        acc = __builtin_amdgcn_mfma_f32_4x4x1f32(e == 0 ? v.x : (e == 1 ? v.y : (e == 2 ? v.z : v.w)), w[e], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_4x4x1f32(e == 0 ? v.x : (e == 1 ? v.y : (e == 2 ? v.z : v.w)), w[e], acc, S, ID, 0);
     }
 };
 template <> struct Piece<true> {
     static constexpr int N = 1, B = 8;
     r4s v;
     __device__ __forceinline__ void load(const unsigned char *p) { v = *reinterpret_cast<const r4s *>(p); }
+    template <int S = 0, int ID = 0>
     __device__ __forceinline__ void mfma(int, const float *w, r4f &acc) const
     {
         struct P { float a, b; };
-        acc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(v, __builtin_bit_cast(r4s, P{w[0], w[1]}), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(v, __builtin_bit_cast(r4s, P{w[0], w[1]}), acc, S, ID, 0);
     }
 };
 
 template <int CTRL>
 __device__ __forceinline__ float dppf(float v)
 {
-    const int i = (int)__float_as_uint(v);
-    return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(i, i, CTRL, 0xf, 0xf, false));
+    return __uint_as_float((unsigned)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+// maximum over groups of 2, 4, 8 or 16 adjacent lanes (one instruction a step; fmaxf of a permuted value
+// takes three)
+template <int LANES>
+__device__ __forceinline__ float lane_max(float v)
+{
+    asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf" : "+v"(v));
+    if (LANES > 2) asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf" : "+v"(v));
+    if (LANES > 4) asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf" : "+v"(v));
+    if (LANES > 8) asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf" : "+v"(v));
+    return v;
+}
+template <int LANES>
+__device__ __forceinline__ float lane_sum(float v)
+{
+    v += dppf<0xB1>(v);
+    if (LANES > 2) v += dppf<0x4E>(v);
+    if (LANES > 4) v += dppf<0x141>(v);
+    if (LANES > 8) v += dppf<0x140>(v);
+    return v;
 }
 
 __device__ __forceinline__ void swap32(float &a, float &b)
@@ -226,78 +265,67 @@ __device__ __forceinline__ void swap16(float &a, float &b)
     a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
 }
 
-// Sum of a group's partial sums over the wave's 16 blocks: lane l gets the one of row l / 16,
-// column l % 4 (the same in the four blocks of a 16-lane row).
-__device__ __forceinline__ float sum_blocks(r4f v)
+// compile-time loop: f(std::integral_constant<int, I>) for I = LO .. HI - 1
+template <int LO, int HI, class F>
+__device__ __forceinline__ void static_for(F f)
 {
-    float a = v[0], b = v[1], c = v[2], d = v[3];
-    swap32(a, c); a += c;             // rows 0 and 2
-    swap32(b, d); b += d;             // rows 1 and 3
-    swap16(a, b); a += b;             // rows 0, 1, 2, 3 by 16-lane row
-    a += dppf<0x124>(a);              // row_ror 4
-    a += dppf<0x128>(a);              // row_ror 8
-    return a;
+    if constexpr (LO < HI) {
+        f(std::integral_constant<int, LO>());
+        static_for<LO + 1, HI>(f);
+    }
 }
 
 // One LSTM stage over the wave's part of K: partial sums of the work-group's units for all rows go to
-// LDS, [row group][wave][lane] with a lane's four rows.  x: the lane's first piece of row lane % 4 (waves
-// 0 .. 5: the same for all blocks, so a read is a broadcast), `step` bytes from piece to piece.  No
-// sums across lanes: the readers of the partial sums add six or eight of them (stage_sum).
-template <bool BF, int CLS, int RG>
-__device__ __forceinline__ void lstm_stage(const RegW<res_lstm_regs(BF, CLS)> &w, const unsigned char *x, int step, float *sums, int wave, int lane)
+// LDS, [row group][wave][lane] with a lane's four rows; the readers add six or eight of them
+// (stage_sum), so there are no sums across lanes.  The activation rows x are read once: lane 4 b + r
+// fetches another piece of row r for every block b, and the matrix instruction's broadcast hands each of
+// them to all blocks in turn (waves 6 and 7: to the four blocks of a slice of K).  Reading a piece
+// once per block instead kept the LDS as busy as the matrix cores: 2.8 against 1.9 us for eight rows.
+template <bool BF, int CLS>
+__device__ __forceinline__ void lstm_stage(const RegW<res_lstm_regs(BF, CLS)> &w, const unsigned char *x, int h4, float *sums, int wave, int lane)
 {
-    constexpr int N = res_lstm_pieces(CLS), PR = res_piece_regs(BF), XR = 4 * res_xrow(BF, CLS);
+    constexpr int N = res_lstm_pieces(CLS), N8 = res_pieces(CLS) / 8, PR = res_piece_regs(BF), XROW = res_xrow(BF, CLS);
     typedef Piece<BF> Pc;
-    constexpr int C = RG == 1 ? 2 : 1;  // chains of sums per row group
-    r4f acc[RG][C];
+    r4f acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    const int b = lane >> 2;
+    const unsigned char *xr = x + (lane & 3) * XROW;       // (pieces beyond the last have zero weights: the last will do)
+    if (wave < 6) {
+        constexpr int Q = (N + 15) / 16;
+        Pc q[Q];
 #pragma unroll
-    for (int rg = 0; rg < RG; ++rg)
+        for (int h = 0; h < Q; ++h) q[h].load(xr + min(wave * N + h * 16 + b, h4 - 1) * Pc::B);
+        static_for<0, N>([&](auto i_) {
+            constexpr int i = decltype(i_)::value;
 #pragma unroll
-        for (int i = 0; i < C; ++i) acc[rg][i] = (r4f){0.f, 0.f, 0.f, 0.f};
-    constexpr int D = BF ? 3 : (RG == 1 ? 2 : 1);         // pieces on their way ahead of the matrix instructions
-    constexpr int N8 = res_pieces(CLS) / 8;               // pieces of a block of waves 6 and 7
-    Pc q[D][RG];
+            for (int e = 0; e < Pc::N; ++e) q[i / 16].template mfma<4, i % 16>(e, &w.w[i * PR], acc[(i * Pc::N + e) & 1]);
+        });
+    } else {
+        constexpr int Q = (N8 + 3) / 4;
+        Pc q[2];
+        auto fetch = [&](int h) { q[h & 1].load(xr + min((h * 4 + (b & 3)) * 8 + (wave - 6) * 4 + (b >> 2), h4 - 1) * Pc::B); };
+        fetch(0);
+        static_for<0, Q>([&](auto h_) {
+            constexpr int h = decltype(h_)::value;
+            if constexpr (h + 1 < Q) fetch(h + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<h * 4, (h * 4 + 4 < N8 ? h * 4 + 4 : N8)>([&](auto i_) {
+                constexpr int i = decltype(i_)::value;
 #pragma unroll
-    for (int i = 0; i < D && i < N8; ++i)
-#pragma unroll
-        for (int rg = 0; rg < RG; ++rg) q[i][rg].load(x + i * step + rg * XR);
-    auto run = [&](int i, bool more) {
-        Pc v[RG];
-#pragma unroll
-        for (int rg = 0; rg < RG; ++rg) {
-            v[rg] = q[i % D][rg];
-            if (more) q[i % D][rg].load(x + (i + D) * step + rg * XR);
-        }
-#pragma unroll
-        for (int e = 0; e < Pc::N; ++e)
-#pragma unroll
-            for (int rg = 0; rg < RG; ++rg) v[rg].mfma(e, &w.w[i * PR], acc[rg][(i * Pc::N + e) % C]);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-#pragma unroll
-    for (int i = 0; i < N8; ++i) run(i, i + D < N8);
-    if (wave < 6) {                     // (uniform; a read beyond a block's pieces would leave the row)
-#pragma unroll
-        for (int i = N8; i < N8 + D && i < N; ++i)
-#pragma unroll
-            for (int rg = 0; rg < RG; ++rg) q[i % D][rg].load(x + i * step + rg * XR);
-#pragma unroll
-        for (int i = N8; i < N; ++i) run(i, i + D < N);
+                for (int e = 0; e < Pc::N; ++e) q[h & 1].template mfma<2, i % 4>(e, &w.w[i * PR], acc[(i * Pc::N + e) & 1]);
+            });
+        });
     }
-#pragma unroll
-    for (int rg = 0; rg < RG; ++rg)
-        *reinterpret_cast<r4f *>(sums + ((rg * kResWaves + wave) * 64 + lane) * 4) = C == 1 ? acc[rg][0] : acc[rg][0] + acc[rg][C - 1];
+    *reinterpret_cast<r4f *>(sums + (wave * 64 + lane) * 4) = acc[0] + acc[1];
 }
 
-// The stage's sum for lane `lane` of block `blk` of sixteen (unit, row) pairs: row group blk / 5, unit
-// 4 (blk % 5) + lane / 16, row lane / 4 % 4, gate lane % 4.
+// The stage's sum for lane `lane` of wave `blk` < 5: unit 4 blk + lane / 16, row lane / 4 % 4, gate lane % 4.
 __device__ __forceinline__ float stage_sum(const float *sums, int blk, int lane)
 {
-    const int rg = blk >= 5 ? 1 : 0, ub = blk - 5 * rg, uu = lane >> 4, row = (lane >> 2) & 3, j = lane & 3;
-    const float *s = sums + rg * kResWaves * 256 + row;
-    if (ub < 4) {
-        s += (4 * (ub * 4 + uu) + j) * 4;
-        return ((s[0] + s[256]) + (s[512] + s[768])) + (s[1024] + s[1280]);
+    const int uu = lane >> 4, row = (lane >> 2) & 3, j = lane & 3;
+    const float *s = sums + row;
+    if (blk < 4) {
+        s += (4 * (blk * 4 + uu) + j) * 4;
+        return (s[0] + (s[256] + s[512])) + (s[768] + (s[1024] + s[1280]));
     }
     s += 6 * 256 + (4 * uu + j) * 4;         // slices 64 floats apart
     return ((s[0] + s[64]) + (s[128] + s[192])) + ((s[256] + s[320]) + (s[384] + s[448]));
@@ -340,25 +368,26 @@ __device__ __forceinline__ void cell(float pre, int j, float c_old, float &c_new
 
 // Receives a vector of `rows` rows of n4 16-byte pieces each (rows row_bytes apart from byte `base`
 // of the exchange buffers on) and hands every piece to f(row, k4, words).
-template <int RG, int WIDTH, class F>
+template <int WIDTH, class F>
 __device__ __forceinline__ void receive_rows(const ResidentParams &p, RCtx &x, unsigned base, int rows, int n4, F f)
 {
-    constexpr int N = (4 * RG * (WIDTH / 4) + kResThreads - 1) / kResThreads;
+    constexpr int N = (kResRows * (WIDTH / 4) + kResThreads - 1) / kResThreads;
     unsigned off[N];
     r4u v[N];
     const unsigned tid = (unsigned)again(x.tid), last = (unsigned)(rows * n4 - 1);
     const unsigned inv = ((1u << 20) + (unsigned)n4 - 1u) / (unsigned)n4;   // idx / n4 for idx * n4 < 2^20, idx < 2^11
+    auto row_of = [&](unsigned idx) { return __umul24(idx, inv) >> 20; };
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         // (threads beyond the vector read its last piece along)
-        const unsigned idx = min(tid + (unsigned)(i * kResThreads), last), r = (idx * inv) >> 20;
-        off[i] = r * (WIDTH * 4u) + (idx - r * (unsigned)n4) * 16u;
+        const unsigned idx = min(tid + (unsigned)(i * kResThreads), last);
+        off[i] = __umul24(row_of(idx), WIDTH * 4u - (unsigned)n4 * 16u) + idx * 16u;
     }
     receive<N>(p, x, off, base, v);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        const unsigned r = off[i] / (WIDTH * 4u);
-        f((int)r, (int)((off[i] - r * (WIDTH * 4u)) >> 4), v[i]);
+        const unsigned idx = min(tid + (unsigned)(i * kResThreads), last), r = row_of(idx);
+        f((int)r, (int)(idx - __umul24(r, (unsigned)n4)), v[i]);
     }
 }
 
@@ -369,46 +398,29 @@ __device__ __forceinline__ void res_finish_row(const ResidentParams &p, int b, i
     if (p.done) __hip_atomic_store(p.done + b, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Loads the projected frames of the next joint step's samples into LDS, straight from memory.
-// Sample s's 16-byte piece k4 goes to position (k4 with its low four bits xored with s), so that
-// sixteen samples' pieces of the same k sit in different banks.  Wave v takes samples v, v + 4, ...
-// pidx: the frame row of sample `lane`, -1 for none.
-template <int ROW, int NMT>
-__device__ __forceinline__ void prefetch_frames(const ResidentParams &p, const RCtx &x, unsigned lds_p, int pidx)
+// Loads row `row` of the projected frames into sample s's place in LDS, straight from memory.  The
+// 16-byte piece k4 goes to position (k4 with its low four bits xored with s), so that sixteen samples'
+// pieces of the same k sit in different banks.  (The instruction's offset counts on both sides.)
+template <int ROW>
+__device__ __forceinline__ void load_frame(const ResidentParams &p, const RCtx &x, unsigned lds_p, int row, int s)
 {
-    const int lane = again(x.lane);
-    const int j4 = p.J >> 2;
-#pragma unroll
-    for (int i = 0; i < 16 * NMT / kResWaves; ++i) {
-        const int s = x.wave + i * kResWaves;
-        const int row = __builtin_amdgcn_readlane(pidx, s);
-        if (row >= 0) {
-            const char *src = reinterpret_cast<const char *>(p.P + (long long)row * p.J);
-            const int l16 = lane ^ (s & 15);
-            auto load = [&](int u) {
-                const unsigned m = lds_p + (unsigned)(s * ROW * 4 + u * 1024);
-                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2"
-                             :: "v"(l16 * 16 + u * 1024), "s"(__builtin_amdgcn_readfirstlane((int)m)), "s"(src) : "memory");
-            };
-            constexpr int U = ROW / 256;                  // whole runs of 64 pieces
-            if (j4 == ROW / 4) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) load(u);
-                if (ROW / 4 > 64 * U && lane < ROW / 4 - 64 * U) load(U);
-            } else {
-#pragma unroll
-                for (int u = 0; u < (ROW / 4 + 63) / 64; ++u)
-                    if (u * 64 + lane < ROW / 4 && u * 64 + l16 < j4) load(u);
-            }
-        }
-    }
+    const int lane = again(x.lane), j4 = p.J >> 2, k4 = lane ^ (s & 15);
+    const char *src = reinterpret_cast<const char *>(p.P + (long long)row * p.J);
+    const unsigned m = (unsigned)__builtin_amdgcn_readfirstlane((int)(lds_p + (unsigned)(s * ROW * 4)));
+    static_for<0, (ROW / 4 + 63) / 64>([&](auto u_) {
+        constexpr int u = decltype(u_)::value;
+        const char *from = src;
+        const unsigned to = m, off = (unsigned)k4 * 16u;
+        if (((u + 1) * 64 <= ROW / 4 || lane < ROW / 4 - u * 64) && (j4 == ROW / 4 || u * 64 + k4 < j4))
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 offset:%3"
+                         :: "v"(off), "s"(to), "s"(from), "n"(u * 1024) : "memory", "m0");
+    });
 }
 
 __device__ __forceinline__ int from_lane(int v, int lane) { return __builtin_amdgcn_ds_bpermute(lane << 2, v); }
 
-// KIND: ResidentKind; BF: bfloat16 mode; CLS: size class; RG: row groups (of 4 utterances) decoded
-// at a time; NMT: tiles of 16 samples of a joint step
-template <int KIND, bool BF, int CLS, int RG, int NMT>
+// KIND: ResidentKind; BF: bfloat16 mode; CLS: size class; NMT: tiles of 16 samples of a joint step
+template <int KIND, bool BF, int CLS, int NMT>
 __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const ResidentParams p)
 {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -416,14 +428,13 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     constexpr bool PAIR = KIND == kResident2Pair;
     constexpr int W = res_width(CLS), ROW = res_row(CLS), TS = res_team(CLS), XROW = res_xrow(BF, CLS);
     constexpr int NI = res_joint_steps(CLS), PR = res_piece_regs(BF), LREGS = res_lstm_regs(BF, CLS);
-    constexpr int NB = (5 * RG + kResWaves - 1) / kResWaves;     // blocks of 16 (unit, row) pairs a wave finishes at most
     typedef Piece<BF> Pc;
     constexpr int NREC = PAIR ? 0 : NL;          // recurrent matrices the chain's work-groups hold
     constexpr ResidentBuf bo = resident_buf(CLS);
-    constexpr ResidentLds lo = resident_lds(KIND, BF, CLS, RG, NMT);
+    constexpr ResidentLds lo = resident_lds(KIND, BF, CLS, NMT);
     constexpr unsigned VROW = W * 4u, VSLOT = kResRows * VROW;                      // h and q rows
     constexpr unsigned KSLOT = kResSamples * TS * 8u, DSLOT = kResSamples * kMaxDur * 4u;
-    constexpr unsigned PSLOT = TS * 10u * 64u * 4u;
+    constexpr unsigned PSLOT = TS * 5u * 64u * 4u;
 
     RCtx x;
     x.tid = threadIdx.x; x.lane = x.tid & 63;
@@ -454,9 +465,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     }
     if (x.tid == 0) { rc.ok = 1; rc.n_list = 0; rc.st_clamped = 0; rc.st_overflow = 0; }
     if (x.tid < kResSamples) { rc.s_k[x.tid] = p.blank; rc.s_d[x.tid] = 0; }
+    if (x.tid < kMaxDur) rc.dur[x.tid] = p.durations[x.tid];
     if (x.lane < kResRows) {
         RRows &w = rc.rows[x.wave];
-        w.b[x.lane] = 0; w.len[x.lane] = 0; w.t[x.lane] = 0; w.n[x.lane] = 0; w.cnt[x.lane] = 0; w.active[x.lane] = 0;
+        w.s[x.lane] = RRow{0, 0, 0, 0}; w.b[x.lane] = w.m[x.lane] = 0;
     }
     for (int i = x.tid * 16; i < lo.bytes; i += kResThreads * 16) *reinterpret_cast<r4u *>(lds + i) = (r4u){0, 0, 0, 0};
     // the marks have to be in memory before this work-group says that it is there
@@ -487,10 +499,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         const int same = !(mine && (side == 1) == helper && v != first);
         x.local = __syncthreads_and(same) != 0;
     };
-    const unsigned prelane = ((unsigned)x.rank * 10u * 64u + (unsigned)x.lane) * 4u;     // + 256 per block
-    // the lane's first piece of an activation row in the LSTM stages, and the distance of the following
-    const int lane_x = (x.lane & 3) * XROW + (x.wave < 6 ? x.wave * res_lstm_pieces(CLS) : (x.wave - 6) * 4 + (x.lane >> 4)) * Pc::B;
-    const int step_x = x.wave < 6 ? Pc::B : 8 * Pc::B;
+    const bool has_cells = x.wave < 5;          // finishes 16 (unit, row) pairs of the LSTM stages, see stage_sum
+    const unsigned prelane = (((unsigned)x.rank * 5u + (unsigned)x.wave) * 64u + (unsigned)x.lane) * 4u;
     const int h4 = p.H >> 2;
 
     if (PAIR && helper) {
@@ -504,23 +514,19 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         for (unsigned n = 1; go; ++n) {
 #pragma unroll
             for (int layer = 0; layer < 2; ++layer) {
-                unsigned char *xr = lds + lo.xh + layer * 4 * RG * XROW;
+                unsigned char *xr = lds + lo.xh + layer * kResRows * XROW;
                 float *sums = reinterpret_cast<float *>(lds + lo.p);
                 int seen = 0;
-                receive_rows<RG, W>(p, x, bo.hr[layer] + RES_SLOT(n) * VSLOT, p.slots, h4, [&](int r, int k4, r4u v) {
+                receive_rows<W>(p, x, bo.hr[layer] + RES_SLOT(n) * VSLOT, p.slots, h4, [&](int r, int k4, r4u v) {
                     if (v.x == kStop) seen = 1;
                     x_put<BF>(xr + r * XROW, k4, v);
                 });
                 if (__syncthreads_or(seen) || !rc.ok) { go = false; break; }
-                lstm_stage<BF, CLS, RG>(layer == 0 ? w0 : w1, xr + lane_x, step_x, sums, x.wave, x.lane);
+                lstm_stage<BF, CLS>(layer == 0 ? w0 : w1, xr, h4, sums, x.wave, x.lane);
                 __syncthreads();
-#pragma unroll
-                for (int i = 0; i < NB; ++i) {
-                    const int blk = x.wave + i * kResWaves;
-                    if (blk >= 5 * RG) break;
-                    const unsigned o = prelane + (unsigned)blk * 256u;
-                    put_far(x, o, bo.pre + ((unsigned)layer * kResSlots + RES_SLOT(n)) * PSLOT, word_of(stage_sum(sums, blk, x.lane)));
-                    put_far(x, o, bo.pre + ((unsigned)layer * kResSlots + RES_SLOT(n + 2)) * PSLOT, kMark);
+                if (has_cells) {
+                    put_far(x, prelane, bo.pre + ((unsigned)layer * kResSlots + RES_SLOT(n)) * PSLOT, word_of(stage_sum(sums, x.wave, x.lane)));
+                    put_far(x, prelane, bo.pre + ((unsigned)layer * kResSlots + RES_SLOT(n + 2)) * PSLOT, kMark);
                 }
             }
         }
@@ -563,6 +569,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     const int g0 = x.rank * p.pl.jgroups, njg = max(0, min(p.pl.jgroups, (p.J >> 2) - g0));
     const bool has_tail = x.rank < p.pl.n_tail;      // a column of the tail, with column tile 0
     const int tcol = p.pl.nout_m + x.rank;
+    const int n_tok = min(p.VT, p.pl.nout_m) - x.rank * 32;      // token columns of this work-group's tiles
+    const bool dur_cols = p.tdt && p.VT < p.pl.nout_m && x.rank * 32 + 32 > p.VT;      // they hold duration columns
     if (x.tid < kResUnits * 4) rc.b1[x.tid] = (NL > 1 && x.tid < nu * 4) ? p.bias_l[((long long)p.H + u0) * 4 + x.tid] : 0.f;
     if (x.tid < 20) rc.bp[x.tid] = x.tid < njg * 4 ? p.b_pred[g0 * 4 + x.tid] : 0.f;
     if (x.tid < 32) rc.bo[x.tid] = x.rank * 32 + x.tid < p.pl.nout_m ? p.b_out[x.rank * 32 + x.tid] : 0.f;
@@ -578,16 +586,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // out where it is used: kept for the whole loop, values like these take the registers that the
     // weights need.
     struct Place { int row, j, lu, gu; bool ok; };
-    auto place_of = [&](int blk, int lane) {
+    auto place_of = [&](int lane) {
         Place l;
-        const int rg = blk >= 5 ? 1 : 0;
-        l.row = rg * 4 + ((lane >> 2) & 3); l.j = lane & 3;
-        l.lu = (blk - 5 * rg) * 4 + (lane >> 4);
+        l.row = (lane >> 2) & 3; l.j = lane & 3;
+        l.lu = x.wave * 4 + (lane >> 4);
         l.ok = l.lu < nu && l.j == 0 && l.row < p.slots;      // the lanes that publish it
         l.gu = min(u0 + l.lu, p.H - 1);
         return l;
     };
-    const int n_blk = x.wave < 5 * RG ? (x.wave + kResWaves < 5 * RG ? 2 : 1) : 0;    // blocks this wave finishes
     // (joint output: a wave takes every eighth step of K for both column tiles)
     const int la = p.la, ns = p.slots * la;
     const unsigned inv_la = (1024u + (unsigned)la - 1u) / (unsigned)la;             // s / la for s < 32, la <= 16
@@ -595,42 +601,59 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     constexpr int QS = ROW + 16;                     // floats per q row
     float *lq = reinterpret_cast<float *>(lds + lo.q);
     const unsigned lds_p = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)(lds + lo.p);
-    float *part = reinterpret_cast<float *>(lds + lo.p);             // joint sums, see there
+    float *part = reinterpret_cast<float *>(lds + lo.part);          // joint sums, see there
     float *tpart = reinterpret_cast<float *>(lds + lo.tpart);        // [wave][tile][16]
-    float *g4 = reinterpret_cast<float *>(lds + lo.g4);              // [own, fifth group][wave][row group][16]
+    float *g4 = reinterpret_cast<float *>(lds + lo.g4);              // [row group][wave][lane][row]
 
     meet();
     bool ok = rc.ok != 0;
 
-    // state of the lane's cells, [layer][block]: committed and candidate cell value, recurrent
-    // pre-activation W_hh h of the committed and of the candidate vector
-    float cs[NL][NB], cc[NL][NB], ps[NL][NB], pc[NL][NB];
+    // state of the lane's cell, [layer]: committed and candidate cell value, recurrent pre-activation
+    // W_hh h of the committed vector (that of the candidate is in the stage's sums, or comes from the helpers)
+    float cs[NL], cc[NL], ps[NL];
 #pragma unroll
-    for (int l = 0; l < NL; ++l)
-#pragma unroll
-        for (int i = 0; i < NB; ++i) { cs[l][i] = cc[l][i] = ps[l][i] = pc[l][i] = 0.f; }
-    float *sums_ih = lq, *sums_rec = reinterpret_cast<float *>(lds + lo.rec);
+    for (int l = 0; l < NL; ++l) cs[l] = cc[l] = ps[l] = 0.f;
+    float *sums_ih = reinterpret_cast<float *>(lds + lo.ih), *sums_rec = reinterpret_cast<float *>(lds + lo.rec), *sums_rec2 = sums_rec + (NREC - 1) * kResWaves * 256;     // (the top layer's)
     unsigned n_pred = 0, n_joint = 0;
 
     RRows &rows = rc.rows[x.wave];
     int next = 0;                     // first utterance of the list that no row has had
     int n_samples = 0, row_steps = 0;
-    // What the loop control leaves for the steps, lane = row: last label, and what the prediction step
-    // does with the row's candidate state (0 nothing, 1 take it, 2 start afresh); lane = sample:
-    // the sample's row of the projected frames, -1 for none.
+    // What the loop control leaves for the steps: of the row that the lane finishes cells of, the last label
+    // and what the prediction step does with the candidate state (0 nothing, 1 take it, 2 start
+    // afresh); of sample `lane`, its row of the projected frames, -1 for none.
     int last = p.blank, action = 2, pidx = -1;
-    // samples of the next joint step: `la` frames of every row in work
-    auto set_up_samples = [&](int lane, int t, int b, int len, bool active) {
-        const int r = min(row_of(lane & (kResSamples - 1)), kResRows - 1);
-        const int fr = from_lane(t, r) + (lane - r * la), br = from_lane(b, r), lr = from_lane(active ? len : 0, r);
-        pidx = (lane < ns && fr < lr) ? br * p.T + fr : -1;
+    // What a lane needs of the loop control's tables, packed (a register each would be one too many): the
+    // sample's row (2 bits) and place (4), its own row's first sample (5), the word of a row of T0 that
+    // its cell takes (12).
+    int lane_const;
+    {
+        const int srow = min(row_of(x.lane & (kResSamples - 1)), kResRows - 1), si = (x.lane - srow * la) & 15;
+        const Place l = place_of(x.lane);
+        lane_const = srow | si << 2 | (l.row * la) << 6 | (l.gu * 4 + l.j) << 11;
+    }
+    // Samples of the next joint step: `la` frames of every row in work, frame f in the row's place f % la,
+    // so that a frame stays where it is until the row has passed it.  fresh: the samples to load.
+    unsigned long long fresh = 0;
+    const unsigned inv_t = 0xffffffffu / (unsigned)la + 1u;                         // t % la for t < 2^24
+    auto mod_la = [&](int t) { return t - (int)__umulhi((unsigned)t, inv_t) * la; };
+    auto set_up_samples = [&](int lane, int t, int m, int b, int len) {
+        const int from = (lane_const & 3) << 4;                                     // (bytes: four lanes per row)
+        const int base = __builtin_amdgcn_ds_bpermute(from, b * p.T + t);
+        const int info = __builtin_amdgcn_ds_bpermute(from, max(0, min(len - t, la)) | m << 8);
+        int off = ((lane_const >> 2) & 15) - (info >> 8);
+        if (off < 0) off += la;
+        const int was = pidx;
+        pidx = (lane < ns && off < (info & 255)) ? base + off : -1;
+        fresh = __ballot(pidx >= 0 && pidx != was);
         n_samples += __popcll(__ballot(pidx >= 0));
     };
-    // rows that want one get the next utterances of the list
+    // Rows that want one get the next utterances of the list.  (Control state is by row: every lane works on
+    // row lane / 4 % 4, and lanes 0, 4, 8, 12 stand for the rows in ballots.)
     auto refill = [&](int lane, bool want, int &b, int &len) {
-        const unsigned long long m = __ballot(want);
+        const unsigned long long m = __ballot(want) & 0x1111ull;
         if (m == 0ull) return false;
-        const int at = next + __popcll(m & ((1ull << lane) - 1ull));
+        const int at = next + __popcll(m & ((1ull << (lane & 12)) - 1ull));
         const bool got = want && at < rc.n_list;
         if (got) { b = rc.list_b[at]; len = rc.list_len[at]; }
         next += __popcll(m);
@@ -640,177 +663,136 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     bool any_active, need_pred;
     {
         int b = 0, len = 0;
-        const bool got = refill(x.lane, x.lane < p.slots, b, len);
-        if (got) { rows.b[x.lane] = b; rows.len[x.lane] = len; rows.active[x.lane] = 1; }
-        any_active = need_pred = __ballot(got) != 0ull;
-        row_steps = __popcll(__ballot(got));
-        set_up_samples(x.lane, 0, b, len, got);
+        const int r = (x.lane >> 2) & 3;
+        const bool got = refill(x.lane, r < p.slots, b, len);
+        if (got) { rows.b[r] = b; rows.s[r].len = len; }
+        const unsigned long long m = __ballot(got) & 0x1111ull;
+        any_active = need_pred = m != 0ull;
+        row_steps = __popcll(m);
+        set_up_samples(x.lane, 0, 0, b, len);
     }
-    // the rows of the embedding table (folded into the first layer) that the next prediction step adds
-    float t0[NB];
-    auto load_t0 = [&](int lane, int label) {
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-            if (i < n_blk) {
-                const Place l = place_of(x.wave + i * kResWaves, lane);
-                t0[i] = p.T0[((unsigned)from_lane(label, l.row) * (unsigned)p.H + (unsigned)l.gu) * 4u + (unsigned)l.j];
-            }
+    // the row of the embedding table (folded into the first layer) that the next prediction step adds
+    float t0 = 0.f;
+    const unsigned t0_row = (unsigned)p.H * 16u;
+    auto load_t0 = [&]() {
+        t0 = 0.f;
+        if (has_cells) t0 = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(p.T0) + (__umul24((unsigned)last, t0_row) + ((unsigned)lane_const >> 11) * 4u));
     };
+    // kResident2Pair: W_hh h of the last step's candidates as far as it is there, kMark where not
+    unsigned pre[2] = {0u, 0u};
+    auto load_pre = [&](unsigned n) {
+        const unsigned slot = bo.pre + RES_SLOT(n) * PSLOT;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) t0[i] = 0.f;
-    if (need_pred) load_t0(x.lane, last);
+        for (int l = 0; l < 2; ++l) pre[l] = !has_cells ? 0u : get1(x, prelane, slot + (unsigned)l * kResSlots * PSLOT);
+    };
+    if (need_pred) load_t0();
 #ifdef RNNT_PROFILE
     if (x.tid == 0) { for (int i = 0; i < 24; ++i) res_prof[i] = 0; res_prof_last = wall_clock64(); }
 #endif
 
     while (ok && any_active) {
-        if (!need_pred) prefetch_frames<ROW, NMT>(p, x, lds_p, pidx);
+        if (!need_pred)
+            for (int s = x.wave; s < ns; s += kResWaves)
+                if (fresh >> s & 1) load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
         if (need_pred) {
             // ---- prediction step -----------------------------------------------------------------
             ++n_pred;
             const unsigned n = n_pred;
             if (PAIR && n > 1) {
-                // W_hh h of the last step's candidates
-                unsigned v[2][NB], spins = 0;
-                const unsigned s1 = bo.pre + RES_SLOT(n - 1) * PSLOT;
-                for (;;) {
-                    bool missing = false;
-#pragma unroll
-                    for (int l = 0; l < 2; ++l)
-#pragma unroll
-                        for (int i = 0; i < NB; ++i) {
-                            v[l][i] = 0u;
-                            if (i < n_blk) v[l][i] = get1(x, prelane + (unsigned)(x.wave + i * kResWaves) * 256u, s1 + (unsigned)l * kResSlots * PSLOT);
-                        }
-#pragma unroll
-                    for (int l = 0; l < 2; ++l)
-#pragma unroll
-                        for (int i = 0; i < NB; ++i) missing = missing || v[l][i] == kMark;
-                    if (__ballot(missing) == 0ull) break;
+                unsigned spins = 0;
+                while (__ballot(pre[0] == kMark || pre[1] == kMark) != 0ull) {
                     if (wait_expired(p, spins)) { rc.ok = 0; break; }
+                    load_pre(n - 1);
                 }
                 x.polls += spins;
-#pragma unroll
-                for (int l = 0; l < 2; ++l)
-#pragma unroll
-                    for (int i = 0; i < NB; ++i) pc[l][i] = __uint_as_float(v[l][i]);
             }
             RES_MARK(0);
             // rows that emitted take their candidate state, fresh rows start from zero
 #pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                if (i >= n_blk) break;
-                const int act = from_lane(action, place_of(x.wave + i * kResWaves, again(x.lane)).row);
-#pragma unroll
-                for (int l = 0; l < NL; ++l) {
-                    cs[l][i] = act == 1 ? cc[l][i] : (act == 2 ? 0.f : cs[l][i]);
-                    ps[l][i] = act == 1 ? pc[l][i] : (act == 2 ? 0.f : ps[l][i]);
-                }
+            for (int l = 0; l < NL; ++l) {
+                float pc = 0.f;
+                if (PAIR) pc = __uint_as_float(pre[l]);
+                else if (has_cells) pc = stage_sum(l == NL - 1 ? sums_rec2 : sums_rec, x.wave, again(x.lane));
+                cs[l] = action == 1 ? cc[l] : (action == 2 ? 0.f : cs[l]);
+                ps[l] = action == 1 ? pc : (action == 2 ? 0.f : ps[l]);
             }
             // publishes the lane's hidden value of a layer and clears the slot of two steps ago
             auto publish_h = [&](int layer, const Place &l, float h) {
                 if (l.ok) {
                     const unsigned o = (unsigned)l.row * VROW + (unsigned)l.gu * 4u;
                     const unsigned s1 = RES_SLOT(n) * VSLOT, s2 = RES_SLOT(n + 2) * VSLOT;
-                    put(x, o, bo.h[layer] + s1, word_of(h));
+                    put(x, o, bo.h[layer] + s1, bo.h[layer] + s2, word_of(h));
                     if (PAIR) { put_far(x, o, bo.hr[layer] + s1, word_of(h)); put_far(x, o, bo.hr[layer] + s2, kMark); }
-                    put(x, o, bo.h[layer] + s2, kMark);
                 }
             };
-#pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                if (i >= n_blk) break;
-                const Place l = place_of(x.wave + i * kResWaves, again(x.lane));
+            if (has_cells) {
+                const Place l = place_of(again(x.lane));
                 float h;
-                cell(ps[0][i] + t0[i], l.j, cs[0][i], cc[0][i], h);
+                cell(ps[0] + t0, l.j, cs[0], cc[0], h);
                 publish_h(0, l, h);
             }
+            // The frames of the joint step, by the waves that have the least to do here.  A wave's loads return in
+            // order, so these waves see the hidden vector when their frames are there: at about the time it comes.
+            if (x.wave >= 5)
+                for (int s = x.wave - 5; s < ns; s += kResWaves - 5)
+                    if (fresh >> s & 1) load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
             RES_MARK(1);
-            unsigned char *x0 = lds + lo.xh, *x1 = lds + lo.xh + (NL - 1) * 4 * RG * XROW;
-            receive_rows<RG, W>(p, x, bo.h[0] + RES_SLOT(n) * VSLOT, p.slots, h4, [&](int r, int k4, r4u v) { x_put<BF>(x0 + r * XROW, k4, v); });
+            unsigned char *x0 = lds + lo.xh, *x1 = lds + lo.xh + (NL - 1) * kResRows * XROW;
+            receive_rows<W>(p, x, bo.h[0] + RES_SLOT(n) * VSLOT, p.slots, h4, [&](int r, int k4, r4u v) { x_put<BF>(x0 + r * XROW, k4, v); });
             __syncthreads();
-            // (here, and not earlier: a wave's loads return in order, and nothing waits for one of its
-            // loads before the next vector arrives)
-            prefetch_frames<ROW, NMT>(p, x, lds_p, pidx);
             RES_MARK(2);
             if constexpr (NL > 1) {
-                lstm_stage<BF, CLS, RG>(w_ih, x0 + lane_x, step_x, sums_ih, x.wave, x.lane);
+                lstm_stage<BF, CLS>(w_ih, x0, h4, sums_ih, x.wave, again(x.lane));
                 __syncthreads();
                 RES_MARK(3);
-#pragma unroll
-                for (int i = 0; i < NB; ++i) {
-                    if (i >= n_blk) break;
+                if (has_cells) {
                     const int lane = again(x.lane);
-                    const Place l = place_of(x.wave + i * kResWaves, lane);
+                    const Place l = place_of(lane);
                     float h;
-                    cell(stage_sum(sums_ih, x.wave + i * kResWaves, lane) + (ps[1][i] + rc.b1[l.lu * 4 + l.j]), l.j, cs[1][i], cc[1][i], h);
+                    cell(stage_sum(sums_ih, x.wave, lane) + (ps[1] + rc.b1[l.lu * 4 + l.j]), l.j, cs[1], cc[1], h);
                     publish_h(1, l, h);
                 }
                 RES_MARK(4);
                 // (while the hand-over is on its way) the recurrent part of the next step's first layer
-                if constexpr (NREC > 1) lstm_stage<BF, CLS, RG>(w_hh[0], x0 + lane_x, step_x, sums_rec, x.wave, x.lane);
+                if constexpr (NREC > 1) lstm_stage<BF, CLS>(w_hh[0], x0, h4, sums_rec, x.wave, again(x.lane));
                 RES_MARK(5);
-                receive_rows<RG, W>(p, x, bo.h[1] + RES_SLOT(n) * VSLOT, p.slots, h4, [&](int r, int k4, r4u v) { x_put<BF>(x1 + r * XROW, k4, v); });
+                receive_rows<W>(p, x, bo.h[1] + RES_SLOT(n) * VSLOT, p.slots, h4, [&](int r, int k4, r4u v) { x_put<BF>(x1 + r * XROW, k4, v); });
                 __syncthreads();
-                if constexpr (NREC > 1) {
-#pragma unroll
-                    for (int i = 0; i < NB; ++i)
-                        if (i < n_blk) pc[0][i] = stage_sum(sums_rec, x.wave + i * kResWaves, again(x.lane));
-                }
             }
             RES_MARK(6);
-            // prediction-side joint projection: a group per pair of waves, and a fifth one in eighths of K
+            // prediction-side joint projection: a wave's blocks are five groups of four columns times three slices of K;
+            // partial sums through LDS
             {
-                constexpr int NO = res_pred_own(CLS), NF = res_pred_fifth(CLS);
-                const int lane = again(x.lane), q16 = lane >> 4, cb = (lane >> 2) & 3, j = lane & 3;
-                const unsigned char *xl = x1 + j * XROW + (lane >> 2) * Pc::B;
+                constexpr int NP = res_pred_pieces(CLS);
+                {
+                    const int lane = again(x.lane), sl = ((lane >> 2) * 13) >> 6;        // block / 5
+                    const unsigned char *xl = x1 + (lane & 3) * XROW;
+                    Pc v[NP];
 #pragma unroll
-                for (int rg = 0; rg < RG; ++rg) {
-                    const unsigned char *xr = xl + rg * 4 * XROW;
-                    Pc v[NO], v5[NF];
+                    for (int i = 0; i < NP; ++i) v[i].load(xl + min(i * 24 + x.wave * 3 + sl, h4 - 1) * Pc::B);
+                    r4f a[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-                    for (int i = 0; i < NO; ++i) v[i].load(xr + (2 * i + (x.wave >> 2)) * 16 * Pc::B);
-                    // (pieces beyond the last one have zero weights: any piece will do)
+                    for (int i = 0; i < NP; ++i)
 #pragma unroll
-                    for (int i = 0; i < NF; ++i) v5[i].load(x1 + j * XROW + rg * 4 * XROW + min(i * 128 + x.wave * 16 + (lane >> 2), W / 4 - 1) * Pc::B);
-                    r4f a[2], a5 = (r4f){0.f, 0.f, 0.f, 0.f};
-                    a[0] = a[1] = a5;
-#pragma unroll
-                    for (int i = 0; i < NO; ++i)
-#pragma unroll
-                        for (int e = 0; e < Pc::N; ++e) {
-                            v[i].mfma(e, &w_pr.w[i * PR], a[(i * Pc::N + e) & 1]);
-                            if (i < NF) v5[i < NF ? i : 0].mfma(e, &w_pr.w[(NO + (i < NF ? i : 0)) * PR], a5);
-                        }
-                    const float s = sum_blocks(a[0] + a[1]), s5 = sum_blocks(a5);
-                    if (cb == 0) {
-                        g4[(x.wave * RG + rg) * 16 + q16 * 4 + j] = s;
-                        g4[((kResWaves + x.wave) * RG + rg) * 16 + q16 * 4 + j] = s5;
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
+                        for (int e = 0; e < Pc::N; ++e) v[i].mfma(e, &w_pr.w[i * PR], a[(i * Pc::N + e) & 1]);
+                    if (lane < 60) *reinterpret_cast<r4f *>(g4 + (x.wave * 60 + lane) * 4) = a[0] + a[1];
                 }
                 __syncthreads();
-                // one value per thread: column j of group g, row 4 rg + q
-                const int tid = again(x.tid), o = tid & 15, gr = tid >> 4, rg = RG == 1 ? 0 : gr / 5, g = gr - rg * 5, r = rg * 4 + (o >> 2);
-                if (gr < 5 * RG && g < njg && r < p.slots) {
-                    float s;
-                    if (g < 4) {
-                        s = g4[(g * RG + rg) * 16 + o] + g4[((g + 4) * RG + rg) * 16 + o];
-                    } else {
-                        const float *f = g4 + (kResWaves * RG + rg) * 16 + o;
-                        constexpr int st = RG * 16;
-                        s = ((f[0] + f[st]) + (f[2 * st] + f[3 * st])) + ((f[4 * st] + f[5 * st]) + (f[6 * st] + f[7 * st]));
-                    }
-                    const unsigned at = (unsigned)r * VROW + (unsigned)((g0 + g) * 4 + (o & 3)) * 4u;
-                    put(x, at, bo.q + RES_SLOT(n) * VSLOT, word_of(s + rc.bp[g * 4 + (o & 3)]));
-                    put(x, at, bo.q + RES_SLOT(n + 2) * VSLOT, kMark);
+                // four adjacent threads per value (group, column, row), two waves' sums each
+                const int tid = again(x.tid), g = tid >> 6, j = (tid >> 4) & 3, r = (tid >> 2) & 3;
+                if (g < njg) {
+                    const float *f = g4 + ((tid & 3) * 120 + g * 4 + j) * 4 + r;
+                    const float bias = rc.bp[g * 4 + j];
+                    const float s = lane_sum<4>(((f[0] + f[80]) + f[160]) + ((f[240] + f[320]) + f[400]));
+                    if ((tid & 3) == 0 && r < p.slots)
+                        put(x, (unsigned)r * VROW + (unsigned)((g0 + g) * 4 + j) * 4u, bo.q + RES_SLOT(n) * VSLOT, bo.q + RES_SLOT(n + 2) * VSLOT, word_of(s + bias));
                 }
             }
             RES_MARK(7);
             // (while q is on its way) the recurrent part of the top layer's next step
-            if constexpr (NREC > 0) lstm_stage<BF, CLS, RG>(w_hh[NREC - 1], x1 + lane_x, step_x, sums_rec, x.wave, x.lane);
+            if constexpr (NREC > 0) lstm_stage<BF, CLS>(w_hh[NREC - 1], x1, h4, sums_rec2, x.wave, again(x.lane));
             RES_MARK(8);
-            receive_rows<RG, W>(p, x, bo.q + RES_SLOT(n) * VSLOT, p.slots, p.J >> 2, [&](int r, int k4, r4u v) {
+            receive_rows<W>(p, x, bo.q + RES_SLOT(n) * VSLOT, p.slots, p.J >> 2, [&](int r, int k4, r4u v) {
                 *reinterpret_cast<r4u *>(lq + r * QS + k4 * 4) = v;
             });
             RES_MARK(9);
@@ -820,121 +802,82 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         const unsigned jn = n_joint;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the frames of this wave's samples are in LDS
         __syncthreads();
-        if constexpr (NREC > 0) {
-            if (need_pred) {
-#pragma unroll
-                for (int i = 0; i < NB; ++i)
-                    if (i < n_blk) pc[NL - 1][i] = stage_sum(sums_rec, x.wave + i * kResWaves, again(x.lane));
-            }
-        }
         RES_MARK(10);
         {
             r4f acc[NMT][2];                 // [tile of samples][column tile]
             const int lane = again(x.lane), m16 = lane & 15, kq = lane >> 4;
-            if constexpr (BF) {
-                // relu(P + q) as bf16 in place: a 16-byte fp32 piece becomes an 8-byte one, in the first or the
-                // second half of its place by the sample's parity (banks)
-                const int tid = again(x.tid), sr = tid >> 5, pr = tid & 31;
-#pragma unroll
-                for (int mt = 0; mt < NMT; ++mt) {
-                    const int s = mt * 16 + sr;
-                    unsigned char *prow = lds + lo.p + s * ROW * 4 + (((pr & ~15) | ((pr ^ s) & 15)) * 16);
-                    const float *q = lq + min(row_of(s), 4 * RG - 1) * QS + pr * 4;
-#pragma unroll
-                    for (int i = 0; i < ROW / 128; ++i) {
-                        const float4 pa = *reinterpret_cast<const float4 *>(prow + i * 512), qa = *reinterpret_cast<const float4 *>(q + i * 128);
-                        uint2 z;
-                        z.x = bf16_pair(fmaxf(pa.x + qa.x, 0.f), fmaxf(pa.y + qa.y, 0.f));
-                        z.y = bf16_pair(fmaxf(pa.z + qa.z, 0.f), fmaxf(pa.w + qa.w, 0.f));
-                        *reinterpret_cast<uint2 *>(prow + i * 512 + (s & 1) * 8) = z;
-                    }
-                }
-                __syncthreads();
-            }
-            // Piece k4 = 32 ii + 4 wave + kq of sample m16: its low bits are the same for all steps.  fp32: the
-            // operand is formed on the way.
+            // Piece k4 = 32 ii + 4 wave + kq of sample m16: its low bits are the same for all steps.  The operand
+            // relu(P + q) is formed on the way: K is split over the waves, so nobody else needs it.  The
+            // vector instructions of a step come in one run before its matrix instructions: the fp32 ones share
+            // the vector pipe with them, and every change between the two costs some ten cycles.
             const int k40 = x.wave * 4 + kq;
             const unsigned char *pr = lds + lo.p + m16 * ROW * 4 + ((k40 & 16) | ((k40 ^ m16) & 15)) * 16;
+            const float *q[NMT];
+            float4 pv, qv;
 #pragma unroll
-            for (int mt = 0; mt < NMT; ++mt) acc[mt][0] = acc[mt][1] = (r4f){0.f, 0.f, 0.f, 0.f};
+            for (int mt = 0; mt < NMT; ++mt) {
+                acc[mt][0] = acc[mt][1] = (r4f){0.f, 0.f, 0.f, 0.f};
+                q[mt] = lq + min(row_of(mt * 16 + m16), kResRows - 1) * QS + k40 * 4;
+            }
+            auto fetch = [&](int i) {              // operands of tile i % NMT, step i / NMT
+                const int ii = i / NMT, mt = i % NMT;
+                pv = *reinterpret_cast<const float4 *>(pr + mt * 16 * ROW * 4 + ii * 512);
+                qv = *reinterpret_cast<const float4 *>(q[mt] + ii * 128);
+            };
+            fetch(0);
             if constexpr (BF) {
                 struct Q { float a, b; };
+                struct U { unsigned a, b; };
+                // the tail column as an operand of its own: its row 0 is the weights, the others are zeros
+                const unsigned char *wt = lds + lo.tail + (m16 == 0 ? 0 : ROW * 2) + k40 * 8;
                 r4f tacc[NMT];
-                r4s z[NMT][NI];
 #pragma unroll
-                for (int mt = 0; mt < NMT; ++mt) {
-                    tacc[mt] = (r4f){0.f, 0.f, 0.f, 0.f};
+                for (int mt = 0; mt < NMT; ++mt) tacc[mt] = (r4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int ii = 0; ii < NI; ++ii) z[mt][ii] = *reinterpret_cast<const r4s *>(pr + mt * 16 * ROW * 4 + ii * 512 + (m16 & 1) * 8);
-                }
+                for (int i = 0; i < NI * NMT; ++i) {
+                    const int ii = i / NMT, mt = i % NMT;
+                    const r4s z = __builtin_bit_cast(r4s, U{bf16_pair(fmaxf(pv.x + qv.x, 0.f), fmaxf(pv.y + qv.y, 0.f)),
+                                                            bf16_pair(fmaxf(pv.z + qv.z, 0.f), fmaxf(pv.w + qv.w, 0.f))});
+                    if (i + 1 < NI * NMT) fetch(i + 1);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int ii = 0; ii < NI; ++ii)
-#pragma unroll
-                    for (int mt = 0; mt < NMT; ++mt)
-#pragma unroll
-                        for (int c = 0; c < 2; ++c) {
-                            const float *w = &w_ou.w[(ii * 2 + c) * PR];
-                            acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(z[mt][ii], __builtin_bit_cast(r4s, Q{w[0], w[1]}), acc[mt][c], 0, 0, 0);
-                        }
-                if (has_tail) {
-                    // the tail column as an operand of its own: lane column 0 reads the weights, the others zeros
-                    const unsigned char *wt = lds + lo.tail + (m16 == 0 ? 0 : ROW * 2) + k40 * 8;
-#pragma unroll
-                    for (int ii = 0; ii < NI; ++ii) {
-                        const r4s w = *reinterpret_cast<const r4s *>(wt + ii * 256);
-#pragma unroll
-                        for (int mt = 0; mt < NMT; ++mt) tacc[mt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(z[mt][ii], w, tacc[mt], 0, 0, 0);
+                    for (int c = 0; c < 2; ++c) {
+                        const float *w = &w_ou.w[(ii * 2 + c) * PR];
+                        acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(r4s, Q{w[0], w[1]}), z, acc[mt][c], 0, 0, 0);
                     }
-                    // lane 16 q holds column 0 of samples 4 q ..
+                    if (has_tail) tacc[mt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const r4s *>(wt + ii * 256), z, tacc[mt], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (has_tail) {
 #pragma unroll
                     for (int mt = 0; mt < NMT; ++mt)
-                        if (m16 == 0) *reinterpret_cast<r4f *>(tpart + (x.wave * 2 + mt) * 16 + kq * 4) = tacc[mt];
+                        if (kq == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = tacc[mt][0];
                 }
             } else {
                 const float *wt = reinterpret_cast<const float *>(lds + lo.tail) + k40 * 4;
-                const float *q[NMT];
                 float tl[NMT];
 #pragma unroll
-                for (int mt = 0; mt < NMT; ++mt) {
-                    q[mt] = lq + min(row_of(mt * 16 + m16), 4 * RG - 1) * QS + k40 * 4;
-                    tl[mt] = 0.f;
-                }
-                // one step ahead of the matrix instructions, no further (registers)
-                float4 pv[NMT], qv[NMT], wv;
-                wv = *reinterpret_cast<const float4 *>(wt);
+                for (int mt = 0; mt < NMT; ++mt) tl[mt] = 0.f;
+                float4 wv = *reinterpret_cast<const float4 *>(wt);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int mt = 0; mt < NMT; ++mt) {
-                    pv[mt] = *reinterpret_cast<const float4 *>(pr + mt * 16 * ROW * 4);
-                    qv[mt] = *reinterpret_cast<const float4 *>(q[mt]);
-                }
-#pragma unroll
-                for (int ii = 0; ii < NI; ++ii) {
-                    float z[NMT][4];
-                    float4 wn = wv;
-#pragma unroll
-                    for (int mt = 0; mt < NMT; ++mt) {
-                        z[mt][0] = fmaxf(pv[mt].x + qv[mt].x, 0.f); z[mt][1] = fmaxf(pv[mt].y + qv[mt].y, 0.f);
-                        z[mt][2] = fmaxf(pv[mt].z + qv[mt].z, 0.f); z[mt][3] = fmaxf(pv[mt].w + qv[mt].w, 0.f);
-                        if (ii + 1 < NI) {
-                            pv[mt] = *reinterpret_cast<const float4 *>(pr + mt * 16 * ROW * 4 + (ii + 1) * 512);
-                            qv[mt] = *reinterpret_cast<const float4 *>(q[mt] + (ii + 1) * 128);
-                        }
-                    }
-                    if (ii + 1 < NI) wn = *reinterpret_cast<const float4 *>(wt + (ii + 1) * 128);
+                for (int i = 0; i < NI * NMT; ++i) {
+                    const int ii = i / NMT, mt = i % NMT;
+                    float z[4];
+                    z[0] = fmaxf(pv.x + qv.x, 0.f); z[1] = fmaxf(pv.y + qv.y, 0.f);
+                    z[2] = fmaxf(pv.z + qv.z, 0.f); z[3] = fmaxf(pv.w + qv.w, 0.f);
+                    tl[mt] = fmaf(z[3], wv.w, fmaf(z[2], wv.z, fmaf(z[1], wv.y, fmaf(z[0], wv.x, tl[mt]))));
+                    // (the sums are opaque here: otherwise they move behind the loop, under the condition they are used
+                    // under, with every z kept in a register till then)
+                    asm volatile("" : "+v"(tl[mt]));
+                    if (i + 1 < NI * NMT) fetch(i + 1);
+                    if (mt == NMT - 1 && ii + 1 < NI) wv = *reinterpret_cast<const float4 *>(wt + (ii + 1) * 128);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
 #pragma unroll
-                        for (int mt = 0; mt < NMT; ++mt) {
-#pragma unroll
-                            for (int c = 0; c < 2; ++c)
-                                acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(z[mt][e], w_ou.w[(ii * 2 + c) * 4 + e], acc[mt][c], 0, 0, 0);
-                            tl[mt] = fmaf(z[mt][e], e == 0 ? wv.x : (e == 1 ? wv.y : (e == 2 ? wv.z : wv.w)), tl[mt]);
-                        }
-                    wv = wn;
-                    // (the sums are opaque here: otherwise they move behind the loop, under the
-                    // condition they are used under, with every z kept in a register till then)
-#pragma unroll
-                    for (int mt = 0; mt < NMT; ++mt) asm volatile("" : "+v"(tl[mt]));
+                        for (int c = 0; c < 2; ++c)
+                            acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w_ou.w[(ii * 2 + c) * 4 + e], z[e], acc[mt][c], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (has_tail) {
@@ -947,16 +890,13 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     }
                 }
             }
-            __syncthreads();                  // the frames' place is free for the sums
             RES_MARK(11);
             // every wave's sums to LDS, [wave][sample][column]; then sixteen lanes per sample, two columns each
 #pragma unroll
             for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
                 for (int c = 0; c < 2; ++c)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        part[((x.wave * NMT + mt) * 16 + kq * 4 + v) * kResSumRow + c * 16 + m16] = acc[mt][c][v];
+                    *reinterpret_cast<r4f *>(part + ((x.wave * NMT + mt) * 16 + m16) * kResSumRow + c * 16 + kq * 4) = acc[mt][c];
             __syncthreads();
             const int tid = again(x.tid);
             if (tid < 16 * NMT * 16) {
@@ -966,57 +906,51 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 for (int w = 0; w < kResWaves; ++w)
                     o[w] = *reinterpret_cast<const float2 *>(part + (w * NMT * 16 + s) * kResSumRow + col);
                 const float2 bias = *reinterpret_cast<const float2 *>(&rc.bo[col]);
+                float tw[kResWaves];
+                if (has_tail) {
+#pragma unroll
+                    for (int w = 0; w < kResWaves; ++w) tw[w] = tpart[(w * 2 + (s >> 4)) * 16 + (s & 15)];
+                }
                 const float l0 = (((o[0].x + o[1].x) + (o[2].x + o[3].x)) + ((o[4].x + o[5].x) + (o[6].x + o[7].x))) + bias.x;
                 const float l1 = (((o[0].y + o[1].y) + (o[2].y + o[3].y)) + ((o[4].y + o[5].y) + (o[6].y + o[7].y))) + bias.y;
-                const int n_tok = min(p.VT, p.pl.nout_m);
-                const float m0 = gcol < n_tok ? l0 : -INFINITY, m1 = gcol + 1 < n_tok ? l1 : -INFINITY;
+                const float m0 = col < n_tok ? l0 : -INFINITY, m1 = col + 1 < n_tok ? l1 : -INFINITY;
                 const float mine = fmaxf(m0, m1);
-                float m = fmaxf(mine, dppf<0xB1>(mine));
-                m = fmaxf(m, dppf<0x4E>(m)); m = fmaxf(m, dppf<0x141>(m)); m = fmaxf(m, dppf<0x140>(m));
+                float m = lane_max<16>(mine);
                 // the first lane of the sixteen that holds the maximum publishes (without a token column: lane 0)
-                const unsigned hit = (unsigned)(__ballot(mine == m && gcol < n_tok) >> (tid & 48)) & 0xffffu;
-                const int first = hit ? __ffs((int)hit) - 1 : 0;
+                const unsigned hit = (unsigned)(__ballot(mine == m && col < n_tok) >> (tid & 48)) & 0xffffu;
+                const int first = hit ? __builtin_ctz(hit) : 0;
                 int ix = hit ? (m0 == m ? gcol : gcol + 1) : 0x7fffffff;
                 float tail = -INFINITY;
                 if (has_tail) {
-                    float t[kResWaves];
-#pragma unroll
-                    for (int w = 0; w < kResWaves; ++w) t[w] = tpart[(w * 2 + (s >> 4)) * 16 + (s & 15)];
-                    tail = (((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]))) + rc.bt;
+                    tail = (((tw[0] + tw[1]) + (tw[2] + tw[3])) + ((tw[4] + tw[5]) + (tw[6] + tw[7]))) + rc.bt;
                     if (tcol >= p.VT) {
                         if ((tid & 15) == 0 && s < ns) {
                             const unsigned d = ((unsigned)s * kMaxDur + (unsigned)(tcol - p.VT)) * 4u;
-                            put(x, d, bo.dur + RES_SLOT(jn) * DSLOT, word_of(tail));
-                            put(x, d, bo.dur + RES_SLOT(jn + 2) * DSLOT, kMark);
+                            put(x, d, bo.dur + RES_SLOT(jn) * DSLOT, bo.dur + RES_SLOT(jn + 2) * DSLOT, word_of(tail));
                         }
                         tail = -INFINITY;
                     } else if (tail > m) {
                         m = tail; ix = tcol;
                     }
                 }
-                if (p.tdt && gcol + 1 >= p.VT && gcol < p.pl.nout_m && s < ns) {
+                if (dur_cols && s < ns) {
                     // duration columns inside the column tiles
 #pragma unroll
                     for (int c = 0; c < 2; ++c)
                         if (gcol + c >= p.VT && gcol + c < p.pl.nout_m) {
                             const unsigned d = ((unsigned)s * kMaxDur + (unsigned)(gcol + c - p.VT)) * 4u;
-                            put(x, d, bo.dur + RES_SLOT(jn) * DSLOT, word_of(c ? l1 : l0));
-                            put(x, d, bo.dur + RES_SLOT(jn + 2) * DSLOT, kMark);
+                            put(x, d, bo.dur + RES_SLOT(jn) * DSLOT, bo.dur + RES_SLOT(jn + 2) * DSLOT, word_of(c ? l1 : l0));
                         }
                 }
                 const unsigned ko = ((unsigned)s * TS + (unsigned)x.rank) * 8u;
-                if ((tid & 15) == first && s < ns) {
-                    put2(x, ko, bo.key + RES_SLOT(jn) * KSLOT, (r2u){word_of(m), (unsigned)ix});
-                    put2(x, ko, bo.key + RES_SLOT(jn + 2) * KSLOT, (r2u){kMark, kMark});
-                }
+                if ((tid & 15) == first && s < ns)
+                    put2(x, ko, bo.key + RES_SLOT(jn) * KSLOT, bo.key + RES_SLOT(jn + 2) * KSLOT, (r2u){word_of(m), (unsigned)ix});
                 if (p.logps) {
                     float e = (m0 > -INFINITY ? expf(m0 - m) : 0.f) + (m1 > -INFINITY ? expf(m1 - m) : 0.f);
-                    e += dppf<0xB1>(e); e += dppf<0x4E>(e); e += dppf<0x141>(e); e += dppf<0x140>(e);
+                    e = lane_sum<16>(e);
                     if (tail > -INFINITY) e += expf(tail - m);
-                    if ((tid & 15) == 0 && s < ns) {
-                        put(x, ko / 2, bo.lse + RES_SLOT(jn) * (KSLOT / 2), word_of(e));
-                        put(x, ko / 2, bo.lse + RES_SLOT(jn + 2) * (KSLOT / 2), kMark);
-                    }
+                    if ((tid & 15) == 0 && s < ns)
+                        put(x, ko / 2, bo.lse + RES_SLOT(jn) * (KSLOT / 2), bo.lse + RES_SLOT(jn + 2) * (KSLOT / 2), word_of(e));
                 }
             }
         }
@@ -1036,10 +970,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 const bool second = vb > va || (vb == va && ib < ia);
                 const float bv = second ? vb : va;
                 const int bi = second ? ib : ia;
-                float m = fmaxf(bv, dppf<0xB1>(bv));
-                m = fmaxf(m, dppf<0x4E>(m));
-                if (L > 4) m = fmaxf(m, dppf<0x141>(m));
-                if (L > 8) m = fmaxf(m, dppf<0x140>(m));
+                const float m = lane_max<L>(bv);
                 // ranks hold ascending columns; tail columns come after all others
                 const bool top = bv == m;
                 const unsigned h1 = (unsigned)(__ballot(top && bi < p.pl.nout_m) >> (lane & ~(L - 1))) & ((1u << L) - 1u);
@@ -1058,9 +989,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     float t = 0.f;
                     if (va > -INFINITY) t += __uint_as_float(e0) * expf(va - m);
                     if (vb > -INFINITY) t += __uint_as_float(e1) * expf(vb - m);
-                    t += dppf<0xB1>(t); t += dppf<0x4E>(t);
-                    if (L > 4) t += dppf<0x141>(t);
-                    if (L > 8) t += dppf<0x140>(t);
+                    t = lane_sum<L>(t);
                     lp2 = -logf(t);
                 }
                 if (win && s < ns) {
@@ -1098,87 +1027,99 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 }
             }
         }
-        __syncthreads();
-        RES_MARK(14);
-        // ---- loop control: every wave for itself, lane = row -----------------------------------------
+        // ---- loop control: every wave for itself, lane = row (outputs: the last wave, which has the least to do next) ------
         {
-            const int lane = again(x.lane), r = lane & (kResRows - 1);
-            const int mine = rc.s_k[lane & (kResSamples - 1)];
-            int b = rows.b[r], len = rows.len[r], t = rows.t[r], nn = rows.n[r], cnt = rows.cnt[r];
-            bool active = lane < p.slots && rows.active[r];
-            int pos, found = 0, dval = 0;
-            if (!p.tdt && p.VT == p.V1) {
+            const int lane = again(x.lane), r = (lane >> 2) & 3;
+            RRow w = rows.s[r];
+            int b = rows.b[r], m = rows.m[r];
+            __syncthreads();
+            RES_MARK(14);
+            if (PAIR) load_pre(n_pred);       // (on its way during the rest)
+            const int mine = rc.s_k[lane & (kResSamples - 1)], row0 = (lane_const >> 6) & 31, left = w.len - w.t;
+            const bool lead = lane < 16 && (lane & 3) == 0;     // stands for its row
+            const bool writer = x.rank == 0 && x.wave == kResWaves - 1 && lead;
+            const bool walk = p.tdt || p.VT != p.V1;
+            int pos, dval = 0;
+            bool found;
+            if (!walk) {
                 // a blank moves on by one frame: the first label among the frames the row still has
-                const unsigned long long labels = __ballot(lane < ns && mine != p.blank);
-                const int avail = min(la, len - t);
-                const unsigned seg = (unsigned)(labels >> (r * la)) & ((1u << avail) - 1u);
-                pos = seg ? __ffs((int)seg) - 1 : avail;
-                found = seg != 0u;
+                const unsigned labels = (unsigned)__ballot(mine != p.blank);
+                const unsigned at = (labels >> row0) & ((1u << la) - 1u), avail = (unsigned)max(0, min(la, left));     // by place
+                pos = __builtin_ctz(((at >> m) | (at << (la - m))) | (1u << avail));                                  // by frame
+                found = pos < (int)avail;
             } else {
                 // lane = sample: where the walk goes from it (nowhere from a label or beyond the row's
                 // frames); then the steps are doubled until every one reaches its end
-                const int sr = min(row_of(lane & (kResSamples - 1)), kResRows - 1), si = lane - sr * la;
+                const int sr = lane_const & 3, ms = from_lane(m, sr * 4);
+                int si = ((lane_const >> 2) & 15) - ms;
+                if (si < 0) si += la;
                 int to = si;
                 const int d = p.tdt ? rc.s_d[lane & (kResSamples - 1)] & (kMaxDur - 1) : 0;
-                if (mine >= p.V1) to += max(p.durations[mine - p.V1], 1);            // big blank: its span of frames
-                else if (mine == p.blank) to += p.tdt ? max(p.durations[d], 1) : 1;
+                if (mine >= p.V1) to += max(rc.dur[(mine - p.V1) & (kMaxDur - 1)], 1);            // big blank: its span of frames
+                else if (mine == p.blank) to += p.tdt ? max(rc.dur[d], 1) : 1;
                 if (pidx < 0) to = si;
 #pragma unroll
                 for (int i = 1; i < 16; i *= 2) {
-                    const int on = from_lane(to, (sr * la + min(to, la - 1)) & 63);
+                    int at = ms + min(to, la - 1);
+                    if (at >= la) at -= la;
+                    const int on = from_lane(to, (sr * la + at) & 63);
                     if (to < la) to = on;
                 }
-                pos = from_lane(to, (r * la) & 63);
-                found = pos < la && t + pos < len;
+                pos = from_lane(to, (row0 + m) & 63);
+                found = pos < la && pos < left;
             }
-            found = found && active;
-            const int s = max(0, min(r * la + pos, kResSamples - 1));
+            int at = m + pos;
+            if (at >= la) at -= la;
+            const int s = max(0, min(row0 + at, kResSamples - 1));
             const int k = rc.s_k[s];
-            if (p.tdt) dval = p.durations[rc.s_d[s] & (kMaxDur - 1)];
+            if (p.tdt) dval = rc.dur[rc.s_d[s] & (kMaxDur - 1)];
             // the label's row of the embedding table is what the next prediction step waits for
             if (found) last = k;
-            load_t0(lane, last);
-            const int t_emit = t + pos;
-            bool ended = false;
-            action = 0;
-            if (active) {
-                t += pos;
-                if (pos > 0) nn = 0;
-                if (found) {
-                    if (x.rank == 0 && x.wave == 0) {
-                        if (cnt < p.cap) {
-                            const long long o = (long long)b * p.cap + cnt;
-                            p.tokens[o] = k;
-                            if (p.frames) p.frames[o] = t_emit;
-                            if (p.logits) p.logits[o] = rc.s_v[s];
-                            if (p.logps) p.logps[o] = rc.s_lp[s];
-                            if (p.durs) p.durs[o] = dval;
-                        } else {
-                            rc.st_overflow = 1;
-                        }
+            load_t0();
+
+            int adv = left > 0 ? pos : 0;
+            if (adv > 0) w.n = 0;
+            if (found) {
+                if (writer) {
+                    if (w.cnt < p.cap) {
+                        const long long o = (long long)b * p.cap + w.cnt;
+                        p.tokens[o] = k;
+                        if (p.frames) p.frames[o] = w.t + pos;
+                        if (p.logits) p.logits[o] = rc.s_v[s];
+                        if (p.logps) p.logps[o] = rc.s_lp[s];
+                        if (p.durs) p.durs[o] = dval;
+                    } else {
+                        rc.st_overflow = 1;
                     }
-                    ++cnt;
-                    action = 1;
-                    if (p.tdt && dval > 0) { t += dval; nn = 0; }
-                    else { ++nn; if (nn == p.S) { ++t; nn = 0; } }
                 }
-                if (t >= len) {
-                    ended = true; active = false; action = 0;
-                    if (x.rank == 0 && x.wave == 0) res_finish_row(p, b, cnt);
-                }
+                ++w.cnt;
+                if (p.tdt && dval > 0) { adv += dval; w.n = 0; }
+                else if (++w.n == p.S) { ++adv; w.n = 0; }
+            }
+            w.t += adv;
+            const bool ended = left > 0 && adv >= left;
+            action = found && !ended ? 1 : 0;
+            if (walk) {
+                m = mod_la(w.t);
+            } else {
+                m += adv;                               // (at most la + 1)
+                if (m >= la) m -= la;
+                if (m >= la) m -= la;
             }
             if (__ballot(ended) != 0ull) {
-                const bool got = refill(lane, ended, b, len);
-                if (got) { t = 0; nn = 0; cnt = 0; active = true; action = 2; last = p.blank; rows.b[r] = b; rows.len[r] = len; }
-                if (__ballot(got) != 0ull) load_t0(lane, last);
-                if (lane < kResRows) rows.active[r] = active;
+                if (writer && ended) res_finish_row(p, b, w.cnt);
+                const bool got = refill(lane, ended, b, w.len);
+                if (got) { w.t = w.n = w.cnt = m = 0; action = 2; last = p.blank; }
+                if (lead) rows.b[r] = b;
+                load_t0();
             }
-            if (lane < kResRows) { rows.t[r] = t; rows.n[r] = nn; rows.cnt[r] = cnt; }
-            const unsigned long long moved = __ballot(action != 0);      // rows whose next step has new inputs
-            any_active = __ballot(active) != 0ull;
+            if (lead) { rows.s[r] = w; rows.m[r] = m; }
+
+            const unsigned long long moved = __ballot(action != 0) & 0x1111ull;      // rows whose next step has new inputs
+            any_active = __ballot(w.t < w.len) != 0ull;
             need_pred = moved != 0ull;
             row_steps += __popcll(moved);
-            set_up_samples(lane, t, b, len, active);
+            set_up_samples(lane, w.t, m, b, w.len);
         }
         ok = rc.ok != 0;
         RES_MARK(15);
@@ -1201,7 +1142,6 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             long long *sp = p.stats + (long long)team * kStatStride;
             if (p.zero_stats) { sp[kStatPred] = 0; sp[kStatJoint] = 0; sp[kStatSamples] = 0; sp[kStatPolls] = 0; }
             sp[kStatPred] += p.count_rows ? row_steps : (int)n_pred; sp[kStatJoint] += n_joint; sp[kStatSamples] += n_samples; sp[kStatPolls] += x.polls;
-sp[kStatPolls] += x.polls;
 #ifdef RNNT_PROFILE
             for (int i = 0; i < 24; ++i) sp[kStatCount + i] = res_prof[i];
 #endif
@@ -1209,11 +1149,11 @@ sp[kStatPolls] += x.polls;
     }
 }
 
-template <int KIND, bool BF, int CLS, int RG, int NMT>
+template <int KIND, bool BF, int CLS, int NMT>
 hipError_t launch_resident_one(const ResidentParams &p, bool plain, hipStream_t stream)
 {
-    const void *fn = reinterpret_cast<const void *>(&resident_kernel<KIND, BF, CLS, RG, NMT>);
-    constexpr unsigned lds = (unsigned)resident_lds(KIND, BF, CLS, RG, NMT).bytes;
+    const void *fn = reinterpret_cast<const void *>(&resident_kernel<KIND, BF, CLS, NMT>);
+    constexpr unsigned lds = (unsigned)resident_lds(KIND, BF, CLS, NMT).bytes;
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     ResidentParams pc = p;

@@ -2,18 +2,17 @@
 //   -DRNNT_RES_KIND=1|2|3   ResidentKind
 //   -DRNNT_RES_BF=0|1       bfloat16 mode
 //   -DRNNT_RES_CLS=0|1|2    size class
-// with its row-group and sample-tile variants.
+// with its sample-tile variants.
 #include "resident_impl.h"
 
 #define RNNT_CAT_(a, b, c, d, e, f) a##b##c##d##e##f
 #define RNNT_CAT(a, b, c, d, e, f) RNNT_CAT_(a, b, c, d, e, f)
 
 namespace rnnt {
-hipError_t RNNT_CAT(launch_resident_, RNNT_RES_KIND, _, RNNT_RES_BF, _, RNNT_RES_CLS)(const ResidentParams &p, int rg, int nmt,
-                                                                                      bool plain, hipStream_t stream)
+hipError_t RNNT_CAT(launch_resident_, RNNT_RES_KIND, _, RNNT_RES_BF, _, RNNT_RES_CLS)(const ResidentParams &p, int nmt, bool plain,
+                                                                                      hipStream_t stream)
 {
-    if (rg == 2) return launch_resident_one<RNNT_RES_KIND, RNNT_RES_BF != 0, RNNT_RES_CLS, 2, 2>(p, plain, stream);
-    if (nmt == 2) return launch_resident_one<RNNT_RES_KIND, RNNT_RES_BF != 0, RNNT_RES_CLS, 1, 2>(p, plain, stream);
-    return launch_resident_one<RNNT_RES_KIND, RNNT_RES_BF != 0, RNNT_RES_CLS, 1, 1>(p, plain, stream);
+    if (nmt == 2) return launch_resident_one<RNNT_RES_KIND, RNNT_RES_BF != 0, RNNT_RES_CLS, 2>(p, plain, stream);
+    return launch_resident_one<RNNT_RES_KIND, RNNT_RES_BF != 0, RNNT_RES_CLS, 1>(p, plain, stream);
 }
 }  // namespace rnnt

@@ -86,22 +86,19 @@ inline std::vector<uint32_t> pack_resident_main(const ResidentPlan &pl, const Re
             if (pl.kind != kResident2Pair)
                 for (int l = 0; l < rw.L; ++l) put_lstm(next(res_lstm_regs(bf, pl.cls)), pl, (*rw.w_hh)[l], rw.H, rank, wave);
             if (rw.L > 1) put_lstm(next(res_lstm_regs(bf, pl.cls)), pl, (*rw.w_ih)[1], rw.H, rank, wave);
-            // prediction-side projection, lane 4 b + column: the pair's group, pieces 16 (2 i + half) + b, then the
-            // fifth group, pieces 128 i + 16 wave + b
+            // prediction-side projection, lane 4 b + column: block b is group b % 5 and slice 3 wave + b / 5, every 24th
+            // piece of K (block 15: nothing)
             {
                 uint32_t *d = next(res_pred_regs(bf, pl.cls));
-                const int own = res_pred_own(pl.cls), g0 = rank * pl.jgroups, njg = std::max(0, std::min(pl.jgroups, rw.J / 4 - g0));
-                for (int i = 0; i < own + res_pred_fifth(pl.cls); ++i) {
-                    const int g = i < own ? (wave & 3) : 4;
-                    if (g >= njg) continue;
-                    for (int lane = 0; lane < 64; ++lane) {
-                        const int b = lane >> 2, k4 = i < own ? (2 * i + (wave >> 2)) * 16 + b : (i - own) * 128 + wave * 16 + b;
-                        if (k4 * 4 >= rw.H) continue;
+                const int g0 = rank * pl.jgroups, njg = std::max(0, std::min(pl.jgroups, rw.J / 4 - g0));
+                for (int i = 0; i < res_pred_pieces(pl.cls); ++i)
+                    for (int lane = 0; lane < 60; ++lane) {
+                        const int g = (lane >> 2) % 5, k4 = i * 24 + wave * 3 + (lane >> 2) / 5;
+                        if (g >= njg || k4 * 4 >= rw.H) continue;
                         for (int e = 0; e < pr; ++e)
                             d[(i * pr + e) * 64 + lane] =
                                 piece_word(rw.w_pred->data() + (size_t)((g0 + g) * 4 + (lane & 3)) * rw.H, rw.H, k4, e, bf);
                     }
-                }
             }
             // joint output: steps wave, wave + 8, ... of K for both column tiles
             {
