@@ -27,6 +27,7 @@ __device__ __forceinline__ void init_call(const CallInit &ci, int b)
     if (b == 0 && id == 0) {
         for (int i = threadIdx.x; i < ci.n_form; i += blockDim.x) ci.form[i] = 0u;
         if (threadIdx.x == 0 && ci.abort_flag) { *ci.abort_flag = 0u; *ci.status = 0; }
+        if (threadIdx.x == 0 && ci.stats) { ci.stats[kStatCallStart] = wall_clock64(); ci.stats[kStatDecodeEnd] = 0; }
     }
     if (!ci.tokens) return;
     const long long o = (long long)b * ci.cap;

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
+
 #include "plan.h"
 
 namespace rnnt {
@@ -19,8 +21,10 @@ struct StageDev {
     long long rank_stride; // float4 elements per rank
 };
 
-// Slots of the per-team statistics record.
-enum { kStatPred = 0, kStatJoint = 1, kStatSamples = 2, kStatPolls = 3, kStatCount = 8,
+// Slots of the per-team statistics record.  The first team's also keeps the times of a call in the
+// resident kernel (100 MHz clock), written by the kernels: three events on the stream cost 9 us a call.
+enum { kStatPred = 0, kStatJoint = 1, kStatSamples = 2, kStatPolls = 3, kStatCounters = 4,
+       kStatCallStart = 4, kStatDecodeStart = 5, kStatDecodeEnd = 6, kStatCount = 8,
        kStatProf = 24, kStatStride = kStatCount + kStatProf };
 
 struct DecodeParams {
@@ -104,10 +108,45 @@ struct CallInit {
     int *tokens = nullptr, *frames = nullptr, *durs = nullptr;   // output rows [B, cap]
     float *logits = nullptr, *logps = nullptr;
     int cap = 0;
+    long long *stats = nullptr;     // where the call's times go (kStatCallStart ...)
 };
 
 // Keeps the text of a failed HIP call for rnnt_status_string; returns RNNT_ERR_HIP.
 int hip_fail(hipError_t e, const char *what);
+
+// Decode kernels of one device run one after another, whatever their streams: the work-groups of a
+// decode wait for each other, so two of them that each had a part of the compute units would wait
+// forever.  A cooperative launch orders itself behind the other cooperative ones, at 18 us a call
+// (one short utterance: 174 against 156 us); here every decode records an event after itself and waits for
+// that of the one before, which costs nothing on the same stream.  `enqueue` launches the kernels
+// (plain: it may launch them ordinarily).  In a stream capture, where an event from outside cannot be
+// waited for, the launches stay cooperative.
+constexpr int kDevices = 64;
+struct LaunchOrder { std::mutex m; hipEvent_t last = nullptr; bool used = false; };
+inline LaunchOrder &launch_order(int dev)
+{
+    static LaunchOrder devices[kDevices];
+    return devices[dev];
+}
+template <class F>
+inline int in_launch_order(hipStream_t stream, F enqueue)
+{
+    int dev = 0, rc = 0;
+    auto ok = [&](hipError_t e, const char *what) { if (e != hipSuccess) rc = hip_fail(e, what); return e == hipSuccess; };
+    if (!ok(hipGetDevice(&dev), "hipGetDevice")) return rc;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (!ok(hipStreamIsCapturing(stream, &capture), "hipStreamIsCapturing")) return rc;
+    if (dev >= kDevices || capture != hipStreamCaptureStatusNone) return enqueue(false);
+    LaunchOrder &d = launch_order(dev);
+    std::lock_guard<std::mutex> lock(d.m);
+    if (!d.last && !ok(hipEventCreateWithFlags(&d.last, hipEventDisableTiming), "hipEventCreate")) return rc;
+    if (d.used && !ok(hipStreamWaitEvent(stream, d.last, 0), "hipStreamWaitEvent")) return rc;
+    const int done = enqueue(true);
+    // (also after a failed launch: kernels of the call may be under way)
+    if (!ok(hipEventRecord(d.last, stream), "hipEventRecord")) return rc;
+    d.used = true;
+    return done;
+}
 
 hipError_t launch_encoder_projection(const float *enc_out, const int *enc_len, const float *w_enc,
                                      const float *b_enc, float *proj, int B, int T, int F, int J,

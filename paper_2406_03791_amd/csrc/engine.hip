@@ -601,43 +601,44 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
     CallInit ci;
     ci.form = ws.form; ci.n_form = pl.n_xcd * 32; ci.abort_flag = ws.abort_flag; ci.status = ws.status;
     ci.tokens = tokens_out; ci.frames = frames_out; ci.durs = durs_out; ci.logits = logit_out; ci.logps = e->logp_out;
-    ci.cap = cap;
-    HIP_TRY(hipEventRecord(e->ev[0], stream));
+    ci.cap = cap; ci.stats = ws.stats;
     HIP_TRY(launch_encoder_projection(enc_out, enc_len, e->w_enc.as<float>(), e->b_enc.as<float>(), ws.P, B, T, d.F, d.J,
                                       is_bf16_arith(e->wt), ci, stream));
-    HIP_TRY(hipEventRecord(e->ev[1], stream));
     e->last_B = B; e->last_used.clear(); e->last_ws = ws; e->last_resident = true;
     const int launch_rows = kResList * pl.n_teams;
-    for (int off = 0; off < B; off += launch_rows) {
-        const int nb = std::min(launch_rows, B - off);
-        if (off > 0) HIP_TRY(launch_reset_resident(ws.form, pl.n_xcd * 32, ws.abort_flag, stream));
-        ResidentParams p{};
-        p.H = d.H; p.J = d.J; p.V1 = d.V1; p.NOUT = e->NOUT; p.blank = d.blank;
-        p.tdt = variant == kTdtLabelLooping;
-        p.D = p.tdt ? d.D : 0;
-        p.VT = e->multi_blank ? e->NOUT : d.V1;
-        for (int i = 0; i < kMaxDur; ++i) p.durations[i] = e->durations[i];
-        p.B = nb; p.T = T; p.S = S; p.cap = cap;
-        resident_rows(pl, nb, &p.slots, &p.la);
-        p.spin_limit = e->spin_limit;
-        p.pl = pl;
-        const long long oc = (long long)off * cap;
-        p.enc_len = enc_len + off; p.P = ws.P + (long long)off * T * d.J;
-        p.tokens = tokens_out + oc; p.tok_len = tok_len_out + off;
-        p.frames = frames_out ? frames_out + oc : nullptr;
-        p.logits = logit_out ? logit_out + oc : nullptr;
-        p.durs = durs_out ? durs_out + oc : nullptr;
-        p.logps = e->logp_out ? e->logp_out + oc : nullptr;
-        p.done = e->done ? e->done + off : nullptr;
-        p.w = e->res_w.as<float>(); p.w_help = e->res_help.as<float>(); p.w_tail = e->res_tail.as<float>();
-        p.T0 = e->T0.as<float>(); p.bias_l = e->bias_l.as<float>(); p.b_pred = e->b_pred.as<float>(); p.b_out = e->b_out.as<float>();
-        p.xbuf = ws.xbuf;
-        p.form = ws.form; p.abort_flag = ws.abort_flag; p.status = ws.status; p.stats = ws.stats;
-        p.zero_stats = off == 0;
-        p.count_rows = variant == kFrameLooping;
-        HIP_TRY(launch_resident(p, p.slots * p.la <= 16 ? 1 : 2, e->plain_launch, stream));
-    }
-    HIP_TRY(hipEventRecord(e->ev[2], stream));
+    const int rc = in_launch_order(stream, [&](bool plain) -> int {
+        for (int off = 0; off < B; off += launch_rows) {
+            const int nb = std::min(launch_rows, B - off);
+            if (off > 0) HIP_TRY(launch_reset_resident(ws.form, pl.n_xcd * 32, ws.abort_flag, stream));
+            ResidentParams p{};
+            p.H = d.H; p.J = d.J; p.V1 = d.V1; p.NOUT = e->NOUT; p.blank = d.blank;
+            p.tdt = variant == kTdtLabelLooping;
+            p.D = p.tdt ? d.D : 0;
+            p.VT = e->multi_blank ? e->NOUT : d.V1;
+            for (int i = 0; i < kMaxDur; ++i) p.durations[i] = e->durations[i];
+            p.B = nb; p.T = T; p.S = S; p.cap = cap;
+            resident_rows(pl, nb, &p.slots, &p.la);
+            p.spin_limit = e->spin_limit;
+            p.pl = pl;
+            const long long oc = (long long)off * cap;
+            p.enc_len = enc_len + off; p.P = ws.P + (long long)off * T * d.J;
+            p.tokens = tokens_out + oc; p.tok_len = tok_len_out + off;
+            p.frames = frames_out ? frames_out + oc : nullptr;
+            p.logits = logit_out ? logit_out + oc : nullptr;
+            p.durs = durs_out ? durs_out + oc : nullptr;
+            p.logps = e->logp_out ? e->logp_out + oc : nullptr;
+            p.done = e->done ? e->done + off : nullptr;
+            p.w = e->res_w.as<float>(); p.w_help = e->res_help.as<float>(); p.w_tail = e->res_tail.as<float>();
+            p.T0 = e->T0.as<float>(); p.bias_l = e->bias_l.as<float>(); p.b_pred = e->b_pred.as<float>(); p.b_out = e->b_out.as<float>();
+            p.xbuf = ws.xbuf;
+            p.form = ws.form; p.abort_flag = ws.abort_flag; p.status = ws.status; p.stats = ws.stats;
+            p.zero_stats = off == 0;
+            p.count_rows = variant == kFrameLooping;
+            HIP_TRY(launch_resident(p, p.slots * p.la <= 16 ? 1 : 2, plain || e->plain_launch, stream));
+        }
+        return RNNT_OK;
+    });
+    if (rc) return rc;
     e->timed = true;
     return RNNT_OK;
 }
@@ -723,7 +724,11 @@ int run_decode(rnnt_engine *e, int variant, const float *enc_out, const int32_t 
         p.done = e->done ? e->done + off : nullptr;
         // the status word is the engine's (or the static workspace's) for all layouts; the
         // step counts are kept per layout and start at zero in a layout's first launch
-        HIP_TRY(launch_decode(p, off == 0, first_in_layout, stream));
+        const int rc = in_launch_order(stream, [&](bool) -> int {
+            HIP_TRY(launch_decode(p, off == 0, first_in_layout, stream));
+            return RNNT_OK;
+        });
+        if (rc) return rc;
     }
     HIP_TRY(hipEventRecord(e->ev[2], stream));
     e->timed = true;
@@ -1227,8 +1232,8 @@ int rnnt_engine_stats(rnnt_engine *eng, rnnt_stats *out)
         out->lookahead = la;
         out->search_steps = 1;
         if (eng->timed) {
-            HIP_TRY(hipEventElapsedTime(&out->projection_ms, eng->ev[0], eng->ev[1]));
-            HIP_TRY(hipEventElapsedTime(&out->decode_ms, eng->ev[1], eng->ev[2]));
+            out->projection_ms = (st[kStatDecodeStart] - st[kStatCallStart]) * 1e-5f;      // 100 MHz clock
+            out->decode_ms = (st[kStatDecodeEnd] - st[kStatDecodeStart]) * 1e-5f;
         }
         return RNNT_OK;
     }

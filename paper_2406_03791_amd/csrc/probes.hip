@@ -263,10 +263,14 @@ int rnnt_probe_exchange(int32_t team_size, int32_t len, int32_t tagged, double *
         PROBE_TRY(hipMemset(a.ctr, 0, (size_t)a.n_teams * 32 * sizeof(unsigned)));
         PROBE_TRY(hipMemset(a.abort_flag, 0, sizeof(unsigned)));
         void *args[] = {&a};
-        PROBE_TRY(hipEventRecord(t.a, nullptr));
-        PROBE_TRY(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(exchange_kernel), dim3(n_wg), dim3(kT),
-                                             args, 0, nullptr));
-        PROBE_TRY(hipEventRecord(t.b, nullptr));
+        const int rc = rnnt::in_launch_order(nullptr, [&](bool) -> int {
+            PROBE_TRY(hipEventRecord(t.a, nullptr));
+            PROBE_TRY(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(exchange_kernel), dim3(n_wg), dim3(kT),
+                                                 args, 0, nullptr));
+            PROBE_TRY(hipEventRecord(t.b, nullptr));
+            return RNNT_OK;
+        });
+        if (rc) return rc;
         PROBE_TRY(hipEventSynchronize(t.b));
         float ms = 0.f;
         PROBE_TRY(hipEventElapsedTime(&ms, t.a, t.b));

@@ -447,10 +447,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     const int team = (xcd % chain_xcds) + chain_xcds * (place / TS);
     x.rank = place % TS;
     const int n_teams = p.pl.n_teams;
+    if (p.zero_stats && blockIdx.x == 0 && x.tid == 0) p.stats[kStatDecodeStart] = wall_clock64();
     int n_list = 0;
     for (int q = 0; q * n_teams < p.B; ++q) n_list += q * n_teams + ((q & 1) ? n_teams - 1 - team : team) < p.B;
     if (n_list == 0) {
-        if (p.zero_stats && !helper && x.rank == 0 && x.tid < kStatCount) p.stats[(long long)team * kStatStride + x.tid] = 0;
+        if (p.zero_stats && !helper && x.rank == 0 && x.tid < kStatCounters) p.stats[(long long)team * kStatStride + x.tid] = 0;
         return;
     }
     x.buf = __builtin_amdgcn_make_buffer_rsrc(p.xbuf + (size_t)team * bo.bytes, 0, (int)bo.bytes, 0x00020000);
@@ -1142,6 +1143,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             long long *sp = p.stats + (long long)team * kStatStride;
             if (p.zero_stats) { sp[kStatPred] = 0; sp[kStatJoint] = 0; sp[kStatSamples] = 0; sp[kStatPolls] = 0; }
             sp[kStatPred] += p.count_rows ? row_steps : (int)n_pred; sp[kStatJoint] += n_joint; sp[kStatSamples] += n_samples; sp[kStatPolls] += x.polls;
+            atomicMax(reinterpret_cast<unsigned long long *>(p.stats + kStatDecodeEnd), (unsigned long long)wall_clock64());
 #ifdef RNNT_PROFILE
             for (int i = 0; i < 24; ++i) sp[kStatCount + i] = res_prof[i];
 #endif

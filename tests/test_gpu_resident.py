@@ -49,3 +49,35 @@ def test_lists_longer_than_the_rows_in_work(pkg, B, extra):  # noqa: F811
     eng = pkg.Engine(w.model, w.B, w.T)
     check(pkg, w, w.variant, f"list {B} {extra}", engine=eng, logp=True)
     eng.close()
+
+
+def test_two_threads_on_streams_of_their_own(pkg):  # noqa: F811
+    """Decodes of two engines from two threads at once: their work-groups may not share the device."""
+    import threading
+
+    import torch
+    jobs = []
+    for seed, B in ((3, 1), (4, 40)):
+        w = model_inputs(324, 332, 530, 2, B=B, T=40, seed=seed)
+        eng = pkg.Engine(w.model, w.B, w.T)
+        enc, ln = torch.from_numpy(w.enc_out).cuda(), torch.from_numpy(w.enc_len.astype(np.int32)).cuda()
+        want = eng.decode("label", enc, ln, w.max_symbols)["tokens"].clone()
+        jobs.append((eng, enc, ln, w.max_symbols, want, []))
+    torch.cuda.synchronize()
+
+    def work(eng, enc, ln, S, want, same):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            for _ in range(20):
+                out = eng.decode("label", enc, ln, S)
+                stream.synchronize()
+                same.append(bool(torch.equal(out["tokens"], want)))
+
+    threads = [threading.Thread(target=work, args=j) for j in jobs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for eng, _, _, _, _, same in jobs:
+        assert eng.status() == 0 and same == [True] * 20
+        eng.close()
