@@ -413,7 +413,7 @@ __device__ __forceinline__ void load_frame(const ResidentParams &p, const RCtx &
         const unsigned to = m, off = (unsigned)k4 * 16u;
         if (((u + 1) * 64 <= ROW / 4 || lane < ROW / 4 - u * 64) && (j4 == ROW / 4 || u * 64 + k4 < j4))
             asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 offset:%3"
-                         :: "v"(off), "s"(to), "s"(from), "n"(u * 1024) : "memory", "m0");
+                         :: "v"(off), "s"(to), "s"(from), "n"(u * 1024) : "memory");
     });
 }
 
