@@ -73,7 +73,7 @@ static_assert(sizeof(RCtl) <= kResCtl, "the control block has its place");
 #ifdef RNNT_PROFILE
 __shared__ long long res_prof[24];
 __shared__ long long res_prof_last;
-#define RES_MARK(slot) do { __builtin_amdgcn_sched_barrier(0); if (x.tid == 0) { long long t_ = wall_clock64(); res_prof[slot] += t_ - res_prof_last; res_prof_last = t_; } __builtin_amdgcn_sched_barrier(0); } while (0)
+#define RES_MARK(slot) do { __builtin_amdgcn_sched_barrier(0); if (threadIdx.x == 0) { long long t_ = wall_clock64(); res_prof[slot] += t_ - res_prof_last; res_prof_last = t_; } __builtin_amdgcn_sched_barrier(0); } while (0)
 #else
 #define RES_MARK(slot) do { } while (0)
 #endif
@@ -94,8 +94,17 @@ __device__ __forceinline__ void load_regs(RegW<N> &r, const float *src, int firs
     }
 }
 
+// The lane's number, worked out anew wherever it is used: a register that holds it, or anything that
+// the compiler could work out ahead from it, is one that the weights do not get.
+__device__ __forceinline__ int lane_id()
+{
+    unsigned zero = 0;
+    asm volatile("" : "+s"(zero));
+    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
+
 struct RCtx {
-    int tid, lane, wave, rank;
+    int wave, rank;
     bool local;                       // every work-group of the team sits on the same XCD
     __amdgpu_buffer_rsrc_t buf;       // the team's exchange buffers
     int polls;
@@ -157,8 +166,6 @@ __device__ __forceinline__ bool wait_expired(const ResidentParams &p, unsigned &
     return false;
 }
 
-__device__ __forceinline__ int again(int v) { asm volatile("" : "+v"(v)); return v; }
-
 __device__ __forceinline__ bool has_mark(r4u v) { return max(max(v.x, v.y), max(v.z, v.w)) == kMark; }
 
 // N 16-byte pieces per thread: all loads in flight together, all of them again while a lane of the
@@ -176,7 +183,7 @@ __device__ __forceinline__ void receive(const ResidentParams &p, RCtx &x, const 
         if (__ballot(missing) == 0ull) break;
         if (wait_expired(p, spins)) { rc.ok = 0; break; }
     }
-    x.polls += spins;
+    x.polls += __builtin_amdgcn_readfirstlane((int)spins);
 }
 
 // two fp32 values as bf16 (ties to even), first in the low half
@@ -374,7 +381,7 @@ __device__ __forceinline__ void receive_rows(const ResidentParams &p, RCtx &x, u
     constexpr int N = (kResRows * (WIDTH / 4) + kResThreads - 1) / kResThreads;
     unsigned off[N];
     r4u v[N];
-    const unsigned tid = (unsigned)again(x.tid), last = (unsigned)(rows * n4 - 1);
+    const unsigned tid = (unsigned)(x.wave * 64 + lane_id()), last = (unsigned)(rows * n4 - 1);
     const unsigned inv = ((1u << 20) + (unsigned)n4 - 1u) / (unsigned)n4;   // idx / n4 for idx * n4 < 2^20, idx < 2^11
     auto row_of = [&](unsigned idx) { return __umul24(idx, inv) >> 20; };
 #pragma unroll
@@ -391,11 +398,22 @@ __device__ __forceinline__ void receive_rows(const ResidentParams &p, RCtx &x, u
     }
 }
 
-// End of a row: outputs are written by one work-group of the team.
-__device__ __forceinline__ void res_finish_row(const ResidentParams &p, int b, int cnt)
+// The kernel's arguments read again from memory: for what few waves and few steps need, and which would
+// take scalar registers (and vector registers that they are spilled to) for the whole loop.
+typedef const ResidentParams __attribute__((address_space(4))) *Args;
+__device__ __forceinline__ Args args_again()
 {
-    p.tok_len[b] = cnt;
-    if (p.done) __hip_atomic_store(p.done + b, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    Args a = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    return a;
+}
+
+// End of a row: outputs are written by one work-group of the team.
+__device__ __forceinline__ void res_finish_row(int b, int cnt)
+{
+    const Args a = args_again();
+    a->tok_len[b] = cnt;
+    if (a->done) __hip_atomic_store(a->done + b, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Loads row `row` of the projected frames into sample s's place in LDS, straight from memory.  The
@@ -404,7 +422,7 @@ __device__ __forceinline__ void res_finish_row(const ResidentParams &p, int b, i
 template <int ROW>
 __device__ __forceinline__ void load_frame(const ResidentParams &p, const RCtx &x, unsigned lds_p, int row, int s)
 {
-    const int lane = again(x.lane), j4 = p.J >> 2, k4 = lane ^ (s & 15);
+    const int lane = lane_id(), j4 = p.J >> 2, k4 = lane ^ (s & 15);
     const char *src = reinterpret_cast<const char *>(p.P + (long long)row * p.J);
     const unsigned m = (unsigned)__builtin_amdgcn_readfirstlane((int)(lds_p + (unsigned)(s * ROW * 4)));
     static_for<0, (ROW / 4 + 63) / 64>([&](auto u_) {
@@ -437,8 +455,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     constexpr unsigned PSLOT = TS * 5u * 64u * 4u;
 
     RCtx x;
-    x.tid = threadIdx.x; x.lane = x.tid & 63;
-    x.wave = __builtin_amdgcn_readfirstlane(x.tid >> 6);
+    const int tid0 = threadIdx.x, lane0 = tid0 & 63;         // (for the work before and after the loop)
+    x.wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
     x.polls = 0;
     // Work-groups go to the XCDs round-robin: index % n_xcd is the XCD, index / n_xcd the place on it.
     const int n_xcd = p.pl.n_xcd, xcd = blockIdx.x % n_xcd, place = blockIdx.x / n_xcd;
@@ -447,11 +465,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     const int team = (xcd % chain_xcds) + chain_xcds * (place / TS);
     x.rank = place % TS;
     const int n_teams = p.pl.n_teams;
-    if (p.zero_stats && blockIdx.x == 0 && x.tid == 0) p.stats[kStatDecodeStart] = wall_clock64();
+    if (p.zero_stats && blockIdx.x == 0 && tid0 == 0) p.stats[kStatDecodeStart] = wall_clock64();
     int n_list = 0;
     for (int q = 0; q * n_teams < p.B; ++q) n_list += q * n_teams + ((q & 1) ? n_teams - 1 - team : team) < p.B;
     if (n_list == 0) {
-        if (p.zero_stats && !helper && x.rank == 0 && x.tid < kStatCounters) p.stats[(long long)team * kStatStride + x.tid] = 0;
+        if (p.zero_stats && !helper && x.rank == 0 && tid0 < kStatCounters) p.stats[(long long)team * kStatStride + tid0] = 0;
         return;
     }
     x.buf = __builtin_amdgcn_make_buffer_rsrc(p.xbuf + (size_t)team * bo.bytes, 0, (int)bo.bytes, 0x00020000);
@@ -461,29 +479,29 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         // (through to the memory side: whether the team may keep its words in the L2 is known below)
         const unsigned lo_b = helper ? bo.pre : 0u, hi_b = helper ? bo.bytes : (PAIR ? bo.pre : bo.hr[0]);
         const r4u mark = {kMark, kMark, kMark, kMark};
-        for (unsigned o = lo_b + ((unsigned)x.rank * kResThreads + (unsigned)x.tid) * 16u; o < hi_b; o += TS * kResThreads * 16u)
+        for (unsigned o = lo_b + ((unsigned)x.rank * kResThreads + (unsigned)tid0) * 16u; o < hi_b; o += TS * kResThreads * 16u)
             __builtin_amdgcn_raw_buffer_store_b128(mark, x.buf, (int)o, 0, 16);
     }
-    if (x.tid == 0) { rc.ok = 1; rc.n_list = 0; rc.st_clamped = 0; rc.st_overflow = 0; }
-    if (x.tid < kResSamples) { rc.s_k[x.tid] = p.blank; rc.s_d[x.tid] = 0; }
-    if (x.tid < kMaxDur) rc.dur[x.tid] = p.durations[x.tid];
-    if (x.lane < kResRows) {
+    if (tid0 == 0) { rc.ok = 1; rc.n_list = 0; rc.st_clamped = 0; rc.st_overflow = 0; }
+    if (tid0 < kResSamples) { rc.s_k[tid0] = p.blank; rc.s_d[tid0] = 0; }
+    if (tid0 < kMaxDur) rc.dur[tid0] = p.durations[tid0];
+    if (lane0 < kResRows) {
         RRows &w = rc.rows[x.wave];
-        w.s[x.lane] = RRow{0, 0, 0, 0}; w.b[x.lane] = w.m[x.lane] = 0;
+        w.s[lane0] = RRow{0, 0, 0, 0}; w.b[lane0] = w.m[lane0] = 0;
     }
-    for (int i = x.tid * 16; i < lo.bytes; i += kResThreads * 16) *reinterpret_cast<r4u *>(lds + i) = (r4u){0, 0, 0, 0};
+    for (int i = tid0 * 16; i < lo.bytes; i += kResThreads * 16) *reinterpret_cast<r4u *>(lds + i) = (r4u){0, 0, 0, 0};
     // the marks have to be in memory before this work-group says that it is there
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
     // ---- the team meets: everyone announces the XCD it runs on --------------------------------
     auto meet = [&]() {
-        if (x.tid == 0) {
+        if (tid0 == 0) {
             const unsigned id = (__builtin_amdgcn_s_getreg((3 << 11) | 20) & 0xfu) + 1u;
             __hip_atomic_store(p.form + blockIdx.x, id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         // lanes 0 .. TS-1 of the first wave: the chain's work-groups, lanes 32 ..: the helpers
-        const int side = x.lane >> 5, r = x.lane & 31;
+        const int side = lane0 >> 5, r = lane0 & 31;
         const bool mine = x.wave == 0 && r < TS && (side == 0 || PAIR);
         unsigned v = 1;
         if (mine) {
@@ -494,22 +512,22 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 if (wait_expired(p, spins)) { rc.ok = 0; break; }
                 v = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            x.polls += spins;
+            x.polls += __builtin_amdgcn_readfirstlane((int)spins);
         }
         const unsigned first = (unsigned)__builtin_amdgcn_readlane((int)v, helper ? 32 : 0);
         const int same = !(mine && (side == 1) == helper && v != first);
         x.local = __syncthreads_and(same) != 0;
     };
     const bool has_cells = x.wave < 5;          // finishes 16 (unit, row) pairs of the LSTM stages, see stage_sum
-    const unsigned prelane = (((unsigned)x.rank * 5u + (unsigned)x.wave) * 64u + (unsigned)x.lane) * 4u;
+    auto prelane = [&]() { return (((unsigned)x.rank * 5u + (unsigned)x.wave) * 64u + (unsigned)lane_id()) * 4u; };
     const int h4 = p.H >> 2;
 
     if (PAIR && helper) {
         // ---- helpers: W_hh of both layers times the candidate vectors ------------------------
         RegW<LREGS> w0, w1;
         const float *src = p.w_help + (long long)(x.rank * kResWaves + x.wave) * (2 * LREGS) * 64;
-        load_regs(w0, src, 0, x.lane);
-        load_regs(w1, src, LREGS, x.lane);
+        load_regs(w0, src, 0, lane0);
+        load_regs(w1, src, LREGS, lane0);
         meet();
         bool go = rc.ok != 0;
         for (unsigned n = 1; go; ++n) {
@@ -523,15 +541,15 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     x_put<BF>(xr + r * XROW, k4, v);
                 });
                 if (__syncthreads_or(seen) || !rc.ok) { go = false; break; }
-                lstm_stage<BF, CLS>(layer == 0 ? w0 : w1, xr, h4, sums, x.wave, x.lane);
+                lstm_stage<BF, CLS>(layer == 0 ? w0 : w1, xr, h4, sums, x.wave, lane_id());
                 __syncthreads();
                 if (has_cells) {
-                    put_far(x, prelane, bo.pre + ((unsigned)layer * kResSlots + RES_SLOT(n)) * PSLOT, word_of(stage_sum(sums, x.wave, x.lane)));
-                    put_far(x, prelane, bo.pre + ((unsigned)layer * kResSlots + RES_SLOT(n + 2)) * PSLOT, kMark);
+                    put_far(x, prelane(), bo.pre + ((unsigned)layer * kResSlots + RES_SLOT(n)) * PSLOT, word_of(stage_sum(sums, x.wave, lane_id())));
+                    put_far(x, prelane(), bo.pre + ((unsigned)layer * kResSlots + RES_SLOT(n + 2)) * PSLOT, kMark);
                 }
             }
         }
-        if (!rc.ok && x.tid == 0) __hip_atomic_fetch_or(p.status, 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!rc.ok && threadIdx.x == 0) __hip_atomic_fetch_or(p.status, 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
 
@@ -543,14 +561,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         const float *src = p.w + (long long)(x.rank * kResWaves + x.wave) * res_main_regs(KIND, BF, CLS) * 64;
         int first = 0;
 #pragma unroll
-        for (int l = 0; l < NREC; ++l) { load_regs(w_hh[l], src, first, x.lane); first += LREGS; }
-        if (NL > 1) { load_regs(w_ih, src, first, x.lane); first += LREGS; }
-        load_regs(w_pr, src, first, x.lane); first += res_pred_regs(BF, CLS);
-        load_regs(w_ou, src, first, x.lane);
+        for (int l = 0; l < NREC; ++l) { load_regs(w_hh[l], src, first, lane0); first += LREGS; }
+        if (NL > 1) { load_regs(w_ih, src, first, lane0); first += LREGS; }
+        load_regs(w_pr, src, first, lane0); first += res_pred_regs(BF, CLS);
+        load_regs(w_ou, src, first, lane0);
     }
     // utterances of the team: ranked by length (longest first, ties by index), dealt in serpentine
     // order; empty ones are complete from the start
-    for (int b = x.tid; b < p.B; b += kResThreads) {
+    for (int b = tid0; b < p.B; b += kResThreads) {
         const int raw = p.enc_len[b];
         if (raw < 0 || raw > p.T) rc.st_clamped = 1;
         const int len = min(max(raw, 0), p.T);
@@ -563,7 +581,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         if (((q & 1) ? n_teams - 1 - m : m) == team) {
             rc.list_b[q] = b; rc.list_len[q] = len;
             if (len > 0) atomicAdd(&rc.n_list, 1);       // the empty ones are the last of the list
-            else if (x.rank == 0) res_finish_row(p, b, 0);
+            else if (x.rank == 0) res_finish_row(b, 0);
         }
     }
     const int u0 = x.rank * p.pl.units, nu = max(0, min(p.pl.units, p.H - u0));
@@ -572,12 +590,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     const int tcol = p.pl.nout_m + x.rank;
     const int n_tok = min(p.VT, p.pl.nout_m) - x.rank * 32;      // token columns of this work-group's tiles
     const bool dur_cols = p.tdt && p.VT < p.pl.nout_m && x.rank * 32 + 32 > p.VT;      // they hold duration columns
-    if (x.tid < kResUnits * 4) rc.b1[x.tid] = (NL > 1 && x.tid < nu * 4) ? p.bias_l[((long long)p.H + u0) * 4 + x.tid] : 0.f;
-    if (x.tid < 20) rc.bp[x.tid] = x.tid < njg * 4 ? p.b_pred[g0 * 4 + x.tid] : 0.f;
-    if (x.tid < 32) rc.bo[x.tid] = x.rank * 32 + x.tid < p.pl.nout_m ? p.b_out[x.rank * 32 + x.tid] : 0.f;
-    if (x.tid == 0) rc.bt = has_tail ? p.b_out[tcol] : 0.f;
+    if (tid0 < kResUnits * 4) rc.b1[tid0] = (NL > 1 && tid0 < nu * 4) ? p.bias_l[((long long)p.H + u0) * 4 + tid0] : 0.f;
+    if (tid0 < 20) rc.bp[tid0] = tid0 < njg * 4 ? p.b_pred[g0 * 4 + tid0] : 0.f;
+    if (tid0 < 32) rc.bo[tid0] = x.rank * 32 + tid0 < p.pl.nout_m ? p.b_out[x.rank * 32 + tid0] : 0.f;
+    if (tid0 == 0) rc.bt = has_tail ? p.b_out[tcol] : 0.f;
     if (has_tail)
-        for (int i = x.tid; i < ROW; i += kResThreads) {
+        for (int i = tid0; i < ROW; i += kResThreads) {
             const float w = p.w_tail[(long long)x.rank * ROW + i];
             // (bfloat16 mode: bf16 values, followed by as many zeros)
             if (BF) reinterpret_cast<unsigned short *>(lds + lo.tail)[i] = (unsigned short)(__float_as_uint(w) >> 16);
@@ -629,8 +647,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // its cell takes (12).
     int lane_const;
     {
-        const int srow = min(row_of(x.lane & (kResSamples - 1)), kResRows - 1), si = (x.lane - srow * la) & 15;
-        const Place l = place_of(x.lane);
+        const int srow = min(row_of(lane0 & (kResSamples - 1)), kResRows - 1), si = (lane0 - srow * la) & 15;
+        const Place l = place_of(lane0);
         lane_const = srow | si << 2 | (l.row * la) << 6 | (l.gu * 4 + l.j) << 11;
     }
     // Samples of the next joint step: `la` frames of every row in work, frame f in the row's place f % la,
@@ -664,13 +682,13 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     bool any_active, need_pred;
     {
         int b = 0, len = 0;
-        const int r = (x.lane >> 2) & 3;
-        const bool got = refill(x.lane, r < p.slots, b, len);
+        const int r = (lane0 >> 2) & 3;
+        const bool got = refill(lane0, r < p.slots, b, len);
         if (got) { rows.b[r] = b; rows.s[r].len = len; }
         const unsigned long long m = __ballot(got) & 0x1111ull;
         any_active = need_pred = m != 0ull;
         row_steps = __popcll(m);
-        set_up_samples(x.lane, 0, 0, b, len);
+        set_up_samples(lane0, 0, 0, b, len);
     }
     // the row of the embedding table (folded into the first layer) that the next prediction step adds
     float t0 = 0.f;
@@ -684,11 +702,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     auto load_pre = [&](unsigned n) {
         const unsigned slot = bo.pre + RES_SLOT(n) * PSLOT;
 #pragma unroll
-        for (int l = 0; l < 2; ++l) pre[l] = !has_cells ? 0u : get1(x, prelane, slot + (unsigned)l * kResSlots * PSLOT);
+        for (int l = 0; l < 2; ++l) pre[l] = !has_cells ? 0u : get1(x, prelane(), slot + (unsigned)l * kResSlots * PSLOT);
     };
     if (need_pred) load_t0();
 #ifdef RNNT_PROFILE
-    if (x.tid == 0) { for (int i = 0; i < 24; ++i) res_prof[i] = 0; res_prof_last = wall_clock64(); }
+    if (tid0 == 0) { for (int i = 0; i < 24; ++i) res_prof[i] = 0; res_prof_last = wall_clock64(); }
 #endif
 
     while (ok && any_active) {
@@ -705,18 +723,21 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     if (wait_expired(p, spins)) { rc.ok = 0; break; }
                     load_pre(n - 1);
                 }
-                x.polls += spins;
+                x.polls += __builtin_amdgcn_readfirstlane((int)spins);
             }
             RES_MARK(0);
-            // rows that emitted take their candidate state, fresh rows start from zero
-#pragma unroll
-            for (int l = 0; l < NL; ++l) {
+            // rows that emitted take their candidate state, fresh rows start from zero (kResident2: the second
+            // layer's while the first one's vector is on its way)
+            auto commit = [&](int l) {
                 float pc = 0.f;
                 if (PAIR) pc = __uint_as_float(pre[l]);
-                else if (has_cells) pc = stage_sum(l == NL - 1 ? sums_rec2 : sums_rec, x.wave, again(x.lane));
-                cs[l] = action == 1 ? cc[l] : (action == 2 ? 0.f : cs[l]);
-                ps[l] = action == 1 ? pc : (action == 2 ? 0.f : ps[l]);
-            }
+                else if (has_cells) pc = stage_sum(l == NL - 1 ? sums_rec2 : sums_rec, x.wave, lane_id());
+                const bool take = action & 1, fresh_row = action & 2;       // (bits: as a chain of comparisons it became branches)
+                cs[l] = take ? cc[l] : cs[l]; cs[l] = fresh_row ? 0.f : cs[l];
+                ps[l] = take ? pc : ps[l]; ps[l] = fresh_row ? 0.f : ps[l];
+            };
+            commit(0);
+            if constexpr (PAIR) commit(1);       // (here: its load came before the stores below, and waits end in order)
             // publishes the lane's hidden value of a layer and clears the slot of two steps ago
             auto publish_h = [&](int layer, const Place &l, float h) {
                 if (l.ok) {
@@ -727,11 +748,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 }
             };
             if (has_cells) {
-                const Place l = place_of(again(x.lane));
+                const Place l = place_of(lane_id());
                 float h;
                 cell(ps[0] + t0, l.j, cs[0], cc[0], h);
                 publish_h(0, l, h);
             }
+            if constexpr (NREC > 1) commit(1);
             // The frames of the joint step, by the waves that have the least to do here.  A wave's loads return in
             // order, so these waves see the hidden vector when their frames are there: at about the time it comes.
             if (x.wave >= 5)
@@ -743,11 +765,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             __syncthreads();
             RES_MARK(2);
             if constexpr (NL > 1) {
-                lstm_stage<BF, CLS>(w_ih, x0, h4, sums_ih, x.wave, again(x.lane));
+                lstm_stage<BF, CLS>(w_ih, x0, h4, sums_ih, x.wave, lane_id());
                 __syncthreads();
                 RES_MARK(3);
                 if (has_cells) {
-                    const int lane = again(x.lane);
+                    const int lane = lane_id();
                     const Place l = place_of(lane);
                     float h;
                     cell(stage_sum(sums_ih, x.wave, lane) + (ps[1] + rc.b1[l.lu * 4 + l.j]), l.j, cs[1], cc[1], h);
@@ -755,7 +777,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 }
                 RES_MARK(4);
                 // (while the hand-over is on its way) the recurrent part of the next step's first layer
-                if constexpr (NREC > 1) lstm_stage<BF, CLS>(w_hh[0], x0, h4, sums_rec, x.wave, again(x.lane));
+                if constexpr (NREC > 1) lstm_stage<BF, CLS>(w_hh[0], x0, h4, sums_rec, x.wave, lane_id());
                 RES_MARK(5);
                 receive_rows<W>(p, x, bo.h[1] + RES_SLOT(n) * VSLOT, p.slots, h4, [&](int r, int k4, r4u v) { x_put<BF>(x1 + r * XROW, k4, v); });
                 __syncthreads();
@@ -766,7 +788,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             {
                 constexpr int NP = res_pred_pieces(CLS);
                 {
-                    const int lane = again(x.lane), sl = ((lane >> 2) * 13) >> 6;        // block / 5
+                    const int lane = lane_id(), sl = ((lane >> 2) * 13) >> 6;        // block / 5
                     const unsigned char *xl = x1 + (lane & 3) * XROW;
                     Pc v[NP];
 #pragma unroll
@@ -780,7 +802,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 }
                 __syncthreads();
                 // four adjacent threads per value (group, column, row), two waves' sums each
-                const int tid = again(x.tid), g = tid >> 6, j = (tid >> 4) & 3, r = (tid >> 2) & 3;
+                const int tid = (x.wave * 64 + lane_id()), g = tid >> 6, j = (tid >> 4) & 3, r = (tid >> 2) & 3;
                 if (g < njg) {
                     const float *f = g4 + ((tid & 3) * 120 + g * 4 + j) * 4 + r;
                     const float bias = rc.bp[g * 4 + j];
@@ -791,7 +813,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             }
             RES_MARK(7);
             // (while q is on its way) the recurrent part of the top layer's next step
-            if constexpr (NREC > 0) lstm_stage<BF, CLS>(w_hh[NREC - 1], x1, h4, sums_rec2, x.wave, again(x.lane));
+            if constexpr (NREC > 0) lstm_stage<BF, CLS>(w_hh[NREC - 1], x1, h4, sums_rec2, x.wave, lane_id());
             RES_MARK(8);
             receive_rows<W>(p, x, bo.q + RES_SLOT(n) * VSLOT, p.slots, p.J >> 2, [&](int r, int k4, r4u v) {
                 *reinterpret_cast<r4u *>(lq + r * QS + k4 * 4) = v;
@@ -806,7 +828,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         RES_MARK(10);
         {
             r4f acc[NMT][2];                 // [tile of samples][column tile]
-            const int lane = again(x.lane), m16 = lane & 15, kq = lane >> 4;
+            const int lane = lane_id(), m16 = lane & 15, kq = lane >> 4;
             // Piece k4 = 32 ii + 4 wave + kq of sample m16: its low bits are the same for all steps.  The operand
             // relu(P + q) is formed on the way: K is split over the waves, so nobody else needs it.  The
             // vector instructions of a step come in one run before its matrix instructions: the fp32 ones share
@@ -814,71 +836,77 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             const int k40 = x.wave * 4 + kq;
             const unsigned char *pr = lds + lo.p + m16 * ROW * 4 + ((k40 & 16) | ((k40 ^ m16) & 15)) * 16;
             const float *q[NMT];
-            float4 pv, qv;
 #pragma unroll
             for (int mt = 0; mt < NMT; ++mt) {
                 acc[mt][0] = acc[mt][1] = (r4f){0.f, 0.f, 0.f, 0.f};
                 q[mt] = lq + min(row_of(mt * 16 + m16), kResRows - 1) * QS + k40 * 4;
             }
-            auto fetch = [&](int i) {              // operands of tile i % NMT, step i / NMT
-                const int ii = i / NMT, mt = i % NMT;
+            auto fetch = [&](int ii, int mt, float4 &pv, float4 &qv) {
                 pv = *reinterpret_cast<const float4 *>(pr + mt * 16 * ROW * 4 + ii * 512);
                 qv = *reinterpret_cast<const float4 *>(q[mt] + ii * 128);
             };
-            fetch(0);
             if constexpr (BF) {
+                float4 pv, qv;
+                fetch(0, 0, pv, qv);
                 struct Q { float a, b; };
                 struct U { unsigned a, b; };
-                // the tail column as an operand of its own: its row 0 is the weights, the others are zeros
-                const unsigned char *wt = lds + lo.tail + (m16 == 0 ? 0 : ROW * 2) + k40 * 8;
-                r4f tacc[NMT];
-#pragma unroll
-                for (int mt = 0; mt < NMT; ++mt) tacc[mt] = (r4f){0.f, 0.f, 0.f, 0.f};
+                // the tail column as an operand of its own: its row mt is the weights for tile mt, the others are zeros
+                const unsigned char *wt = lds + lo.tail + k40 * 8;
+                r4f tacc = (r4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int i = 0; i < NI * NMT; ++i) {
                     const int ii = i / NMT, mt = i % NMT;
                     const r4s z = __builtin_bit_cast(r4s, U{bf16_pair(fmaxf(pv.x + qv.x, 0.f), fmaxf(pv.y + qv.y, 0.f)),
                                                             bf16_pair(fmaxf(pv.z + qv.z, 0.f), fmaxf(pv.w + qv.w, 0.f))});
-                    if (i + 1 < NI * NMT) fetch(i + 1);
+                    if (i + 1 < NI * NMT) fetch((i + 1) / NMT, (i + 1) % NMT, pv, qv);
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int c = 0; c < 2; ++c) {
                         const float *w = &w_ou.w[(ii * 2 + c) * PR];
                         acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(r4s, Q{w[0], w[1]}), z, acc[mt][c], 0, 0, 0);
                     }
-                    if (has_tail) tacc[mt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const r4s *>(wt + ii * 256), z, tacc[mt], 0, 0, 0);
+                    if (has_tail) tacc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const r4s *>(wt + (m16 == mt ? 0 : ROW * 2) + ii * 256), z, tacc, 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (has_tail) {
 #pragma unroll
                     for (int mt = 0; mt < NMT; ++mt)
-                        if (kq == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = tacc[mt][0];
+                        if (kq == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = tacc[mt];
                 }
             } else {
                 const float *wt = reinterpret_cast<const float *>(lds + lo.tail) + k40 * 4;
                 float tl[NMT];
 #pragma unroll
                 for (int mt = 0; mt < NMT; ++mt) tl[mt] = 0.f;
-                float4 wv = *reinterpret_cast<const float4 *>(wt);
+                float4 wv = *reinterpret_cast<const float4 *>(wt), pv[NMT], qv[NMT];
+#pragma unroll
+                for (int mt = 0; mt < NMT; ++mt) fetch(0, mt, pv[mt], qv[mt]);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = 0; i < NI * NMT; ++i) {
-                    const int ii = i / NMT, mt = i % NMT;
-                    float z[4];
-                    z[0] = fmaxf(pv.x + qv.x, 0.f); z[1] = fmaxf(pv.y + qv.y, 0.f);
-                    z[2] = fmaxf(pv.z + qv.z, 0.f); z[3] = fmaxf(pv.w + qv.w, 0.f);
-                    tl[mt] = fmaf(z[3], wv.w, fmaf(z[2], wv.z, fmaf(z[1], wv.y, fmaf(z[0], wv.x, tl[mt]))));
-                    // (the sums are opaque here: otherwise they move behind the loop, under the condition they are used
-                    // under, with every z kept in a register till then)
-                    asm volatile("" : "+v"(tl[mt]));
-                    if (i + 1 < NI * NMT) fetch(i + 1);
-                    if (mt == NMT - 1 && ii + 1 < NI) wv = *reinterpret_cast<const float4 *>(wt + (ii + 1) * 128);
+                for (int ii = 0; ii < NI; ++ii) {
+                    float z[NMT][4];
+#pragma unroll
+                    for (int mt = 0; mt < NMT; ++mt) {
+                        z[mt][0] = fmaxf(pv[mt].x + qv[mt].x, 0.f); z[mt][1] = fmaxf(pv[mt].y + qv[mt].y, 0.f);
+                        z[mt][2] = fmaxf(pv[mt].z + qv[mt].z, 0.f); z[mt][3] = fmaxf(pv[mt].w + qv[mt].w, 0.f);
+                        tl[mt] = fmaf(z[mt][3], wv.w, fmaf(z[mt][2], wv.z, fmaf(z[mt][1], wv.y, fmaf(z[mt][0], wv.x, tl[mt]))));
+                        // (the sums are opaque here: otherwise they move behind the loop, under the condition they are used
+                        // under, with every z kept in a register till then)
+                        asm volatile("" : "+v"(tl[mt]));
+                    }
+                    if (ii + 1 < NI) {
+#pragma unroll
+                        for (int mt = 0; mt < NMT; ++mt) fetch(ii + 1, mt, pv[mt], qv[mt]);
+                        wv = *reinterpret_cast<const float4 *>(wt + (ii + 1) * 128);
+                    }
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
 #pragma unroll
-                        for (int c = 0; c < 2; ++c)
-                            acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w_ou.w[(ii * 2 + c) * 4 + e], z[e], acc[mt][c], 0, 0, 0);
+                        for (int mt = 0; mt < NMT; ++mt)
+#pragma unroll
+                            for (int c = 0; c < 2; ++c)
+                                acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w_ou.w[(ii * 2 + c) * 4 + e], z[mt][e], acc[mt][c], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (has_tail) {
@@ -899,7 +927,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 for (int c = 0; c < 2; ++c)
                     *reinterpret_cast<r4f *>(part + ((x.wave * NMT + mt) * 16 + m16) * kResSumRow + c * 16 + kq * 4) = acc[mt][c];
             __syncthreads();
-            const int tid = again(x.tid);
+            const int tid = (x.wave * 64 + lane_id());
             if (tid < 16 * NMT * 16) {
                 const int s = tid >> 4, col = (tid & 15) * 2, gcol = x.rank * 32 + col;
                 float2 o[kResWaves];
@@ -907,11 +935,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 for (int w = 0; w < kResWaves; ++w)
                     o[w] = *reinterpret_cast<const float2 *>(part + (w * NMT * 16 + s) * kResSumRow + col);
                 const float2 bias = *reinterpret_cast<const float2 *>(&rc.bo[col]);
-                float tw[kResWaves];
-                if (has_tail) {
-#pragma unroll
-                    for (int w = 0; w < kResWaves; ++w) tw[w] = tpart[(w * 2 + (s >> 4)) * 16 + (s & 15)];
-                }
+                static_assert(kResWaves == 8, "eight lanes add the waves' sums of the tail column");
+                float tw = 0.f;
+                if (has_tail) tw = tpart[((tid & 7) * 2 + (s >> 4)) * 16 + (s & 15)];
                 const float l0 = (((o[0].x + o[1].x) + (o[2].x + o[3].x)) + ((o[4].x + o[5].x) + (o[6].x + o[7].x))) + bias.x;
                 const float l1 = (((o[0].y + o[1].y) + (o[2].y + o[3].y)) + ((o[4].y + o[5].y) + (o[6].y + o[7].y))) + bias.y;
                 const float m0 = col < n_tok ? l0 : -INFINITY, m1 = col + 1 < n_tok ? l1 : -INFINITY;
@@ -923,7 +949,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 int ix = hit ? (m0 == m ? gcol : gcol + 1) : 0x7fffffff;
                 float tail = -INFINITY;
                 if (has_tail) {
-                    tail = (((tw[0] + tw[1]) + (tw[2] + tw[3])) + ((tw[4] + tw[5]) + (tw[6] + tw[7]))) + rc.bt;
+                    tail = lane_sum<8>(tw) + rc.bt;
                     if (tcol >= p.VT) {
                         if ((tid & 15) == 0 && s < ns) {
                             const unsigned d = ((unsigned)s * kMaxDur + (unsigned)(tcol - p.VT)) * 4u;
@@ -958,14 +984,40 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         RES_MARK(12);
         // ---- argmax over the team: TS / 2 adjacent lanes per sample, two candidates per lane --------
         {
-            const int tid = again(x.tid), lane = tid & 63;
+            const int tid = (x.wave * 64 + lane_id()), lane = tid & 63;
             constexpr int L = TS / 2;
             static_assert(16 * NMT * L <= kResThreads, "one piece per thread");
             const int s = tid / L;
             if ((x.wave * 64) / L < ns) {
                 const unsigned off[1] = {(unsigned)min(tid, ns * L - 1) * 16u};
                 r4u v[1];
-                receive<1>(p, x, off, bo.key + RES_SLOT(jn) * KSLOT, v);
+                // TDT: the sample's durations, one or two for each of the first lanes, come along
+                constexpr int ND = L >= kMaxDur ? 1 : kMaxDur / L;
+                const int li = lane & (L - 1), di = (li * ND) & (kMaxDur - 1);
+                unsigned dv[ND];
+                if (p.tdt) {
+                    const int v0 = rc.dur[di], v1 = rc.dur[di + ND - 1];
+                    unsigned spins = 0;
+                    const unsigned o = ((off[0] / (L * 16u)) * kMaxDur + (unsigned)di) * 4u;
+                    for (;;) {
+                        v[0] = get4(x, off[0], bo.key + RES_SLOT(jn) * KSLOT);
+                        bool missing = false;
+#pragma unroll
+                        for (int i = 0; i < ND; ++i) dv[i] = get1(x, o + i * 4u, bo.dur + RES_SLOT(jn) * DSLOT);
+#pragma unroll
+                        for (int i = 0; i < ND; ++i) missing = missing || (di + i < p.D && dv[i] == kMark);
+                        if (__ballot(missing || has_mark(v[0])) == 0ull) break;
+                        if (wait_expired(p, spins)) { rc.ok = 0; break; }
+                    }
+                    x.polls += __builtin_amdgcn_readfirstlane((int)spins);
+                    // best duration, the lowest index on ties
+                    const float d0 = di < p.D ? __uint_as_float(dv[0]) : -INFINITY, d1 = ND > 1 && di + 1 < p.D ? __uint_as_float(dv[ND - 1]) : -INFINITY;
+                    const float dl = fmaxf(d0, d1), dm = lane_max<L>(dl);
+                    const unsigned hit = (unsigned)(__ballot(dl == dm && di < p.D) >> (lane & ~(L - 1))) & ((1u << L) - 1u);
+                    if (li == (hit ? __builtin_ctz(hit) : 0) && s < ns) rc.s_d[s] = d0 == dm || ND == 1 ? v0 : v1;
+                } else {
+                    receive<1>(p, x, off, bo.key + RES_SLOT(jn) * KSLOT, v);
+                }
                 const float va = __uint_as_float(v[0].x), vb = __uint_as_float(v[0].z);
                 const int ia = (int)v[0].y, ib = (int)v[0].w;
                 const bool second = vb > va || (vb == va && ib < ia);
@@ -1000,37 +1052,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 }
             }
             RES_MARK(13);
-            if (p.tdt) {
-                // one lane per sample (last wave): best duration, lowest index on ties
-                const int s = tid - (kResThreads - 64);
-                if (s >= 0 && s < ns) {
-                    r4u d0, d1;
-                    unsigned spins = 0;
-                    const unsigned sl = bo.dur + RES_SLOT(jn) * DSLOT, o = (unsigned)s * kMaxDur * 4u;
-                    for (;;) {
-                        d0 = get4(x, o, sl); d1 = get4(x, o + 16u, sl);
-                        bool all = true;
-#pragma unroll
-                        for (int i = 0; i < kMaxDur; ++i)
-                            if (i < p.D) all = all && (i < 4 ? d0[i & 3] : d1[i & 3]) != kMark;
-                        if (all) break;
-                        if (wait_expired(p, spins)) { rc.ok = 0; break; }
-                    }
-                    x.polls += spins;
-                    float best = -INFINITY; int bd = 0;
-#pragma unroll
-                    for (int i = 0; i < kMaxDur; ++i)
-                        if (i < p.D) {
-                            const float dv = __uint_as_float(i < 4 ? d0[i & 3] : d1[i & 3]);
-                            if (i == 0 || dv > best) { best = dv; bd = i; }
-                        }
-                    rc.s_d[s] = bd;
-                }
-            }
         }
         // ---- loop control: every wave for itself, lane = row (outputs: the last wave, which has the least to do next) ------
         {
-            const int lane = again(x.lane), r = (lane >> 2) & 3;
+            const int lane = lane_id(), r = (lane >> 2) & 3;
             RRow w = rows.s[r];
             int b = rows.b[r], m = rows.m[r];
             __syncthreads();
@@ -1049,46 +1074,45 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 pos = __builtin_ctz(((at >> m) | (at << (la - m))) | (1u << avail));                                  // by frame
                 found = pos < (int)avail;
             } else {
-                // lane = sample: where the walk goes from it (nowhere from a label or beyond the row's
-                // frames); then the steps are doubled until every one reaches its end
+                // lane = sample: the offset (from the row's frame) that the walk goes to from it, its own for a label
+                // or beyond the row's frames, and the lane of that offset, its own where the walk leaves the step;
+                // then the hops are doubled until every one reaches its end
                 const int sr = lane_const & 3, ms = from_lane(m, sr * 4);
-                int si = ((lane_const >> 2) & 15) - ms;
-                if (si < 0) si += la;
-                int to = si;
-                const int d = p.tdt ? rc.s_d[lane & (kResSamples - 1)] & (kMaxDur - 1) : 0;
-                if (mine >= p.V1) to += max(rc.dur[(mine - p.V1) & (kMaxDur - 1)], 1);            // big blank: its span of frames
-                else if (mine == p.blank) to += p.tdt ? max(rc.dur[d], 1) : 1;
-                if (pidx < 0) to = si;
-#pragma unroll
-                for (int i = 1; i < 16; i *= 2) {
-                    int at = ms + min(to, la - 1);
-                    if (at >= la) at -= la;
-                    const int on = from_lane(to, (sr * la + at) & 63);
-                    if (to < la) to = on;
-                }
-                pos = from_lane(to, (row0 + m) & 63);
+                int to = ((lane_const >> 2) & 15) - ms;
+                if (to < 0) to += la;
+                int d = 0;
+                if (mine >= p.V1) d = max(rc.dur[(mine - p.V1) & (kMaxDur - 1)], 1);            // big blank: its span of frames
+                else if (mine == p.blank) d = p.tdt ? max(rc.s_d[lane & (kResSamples - 1)], 1) : 1;
+                if (pidx < 0) d = 0;
+                to += d;
+                int at = ms + to;
+                if (at >= la) at -= la;
+                int hop = (d > 0 && to < la ? (int)__umul24((unsigned)sr, (unsigned)la) + at : lane) << 2;
+                for (int i = 1; i < la; i *= 2) hop = __builtin_amdgcn_ds_bpermute(hop, hop);
+                hop = __builtin_amdgcn_ds_bpermute((row0 + m) << 2, hop);
+                pos = __builtin_amdgcn_ds_bpermute(hop, to);
                 found = pos < la && pos < left;
             }
             int at = m + pos;
             if (at >= la) at -= la;
             const int s = max(0, min(row0 + at, kResSamples - 1));
             const int k = rc.s_k[s];
-            if (p.tdt) dval = rc.dur[rc.s_d[s] & (kMaxDur - 1)];
+            if (p.tdt) dval = rc.s_d[s];
             // the label's row of the embedding table is what the next prediction step waits for
             if (found) last = k;
             load_t0();
-
             int adv = left > 0 ? pos : 0;
             if (adv > 0) w.n = 0;
             if (found) {
                 if (writer) {
-                    if (w.cnt < p.cap) {
-                        const long long o = (long long)b * p.cap + w.cnt;
-                        p.tokens[o] = k;
-                        if (p.frames) p.frames[o] = w.t + pos;
-                        if (p.logits) p.logits[o] = rc.s_v[s];
-                        if (p.logps) p.logps[o] = rc.s_lp[s];
-                        if (p.durs) p.durs[o] = dval;
+                    const Args a = args_again();
+                    if (w.cnt < a->cap) {
+                        const long long o = (long long)b * a->cap + w.cnt;
+                        a->tokens[o] = k;
+                        if (a->frames) a->frames[o] = w.t + pos;
+                        if (a->logits) a->logits[o] = rc.s_v[s];
+                        if (a->logps) a->logps[o] = rc.s_lp[s];
+                        if (a->durs) a->durs[o] = dval;
                     } else {
                         rc.st_overflow = 1;
                     }
@@ -1108,7 +1132,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 if (m >= la) m -= la;
             }
             if (__ballot(ended) != 0ull) {
-                if (writer && ended) res_finish_row(p, b, w.cnt);
+                if (writer && ended) res_finish_row(b, w.cnt);
                 const bool got = refill(lane, ended, b, w.len);
                 if (got) { w.t = w.n = w.cnt = m = 0; action = 2; last = p.blank; }
                 if (lead) rows.b[r] = b;
@@ -1129,12 +1153,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     if (PAIR && rc.ok) {
         // the helpers wait for the next candidate vector: tell them that there is none
         const unsigned o = bo.hr[0] + RES_SLOT(n_pred + 1) * VSLOT;
-        for (int i = x.tid; i < p.slots * nu; i += kResThreads) {
+        for (int i = threadIdx.x; i < p.slots * nu; i += kResThreads) {
             const int r = i / nu, u = i - r * nu;
             put_far(x, (unsigned)r * VROW + (unsigned)(u0 + u) * 4u, o, kStop);
         }
     }
-    if (x.tid == 0) {
+    if (threadIdx.x == 0) {
         int st = 0;
         if (x.rank == 0) st = (rc.st_clamped ? 1 : 0) | (rc.st_overflow ? 2 : 0);
         if (!rc.ok) st |= 4;
