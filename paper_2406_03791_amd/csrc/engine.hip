@@ -1227,7 +1227,7 @@ int rnnt_engine_stats(rnnt_engine *eng, rnnt_stats *out)
         int slots, la;
         resident_rows(pl, std::min(eng->last_B, kResList * pl.n_teams), &slots, &la);
         out->n_teams = pl.n_teams;
-        out->team_size = res_team(pl.cls) * (pl.kind == kResident2Pair ? 2 : 1);
+        out->team_size = res_team(pl.cls);
         out->joint_groups = 1;
         out->lookahead = la;
         out->search_steps = 1;

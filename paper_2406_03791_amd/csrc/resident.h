@@ -44,6 +44,9 @@ enum ResidentKind {
     kResident2 = 2,       // two layers in the bfloat16 mode: the same
     kResident2Pair = 3,   // two layers in fp32: a team on one XCD, the recurrent matrices on a second one
 };
+// kResident2Pair: most XCDs have teams, and each of the others works for up to kResServed of them
+constexpr int kResServed = 2;
+RNNT_HD constexpr int res_chain_xcds(int n_xcd) { return n_xcd * kResServed / (kResServed + 1); }
 
 struct ResidentPlan {
     int kind;             // ResidentKind
@@ -126,7 +129,6 @@ RNNT_HD constexpr ResidentLds resident_lds(int kind, bool bf, int cls, int nmt)
     const int stage = kResWaves * 1024, q = kResRows * (res_row(cls) + 16) * 4;
     l.p = 0;
     l.part = l.xh = frames;
-    if (kind == kResident2Pair && l.xh < stage) l.part = l.xh = stage;         // (the helpers' partial sums)
     // (kResident2Pair: where the first layer's rows are large enough, the projection's sums take their place)
     const int x_row = kResRows * res_xrow(bf, cls), proj = kResWaves * 60 * 16;
     const bool over = kind == kResident2Pair && x_row >= proj;

@@ -62,6 +62,7 @@ struct RCtl {
     float s_v[kResSamples], s_lp[kResSamples];
     int n_list, ok, st_clamped, st_overflow;
     int dur[kMaxDur];
+    unsigned seen[2][kResWaves];      // helpers: what a wave has seen of the teams' vectors
     int list_b[kResList], list_len[kResList];
     // this work-group's slices of the biases: second layer [unit][gate], projection, output and tail column
     float b1[kResUnits * 4], bp[20], bo[32], bt;
@@ -375,25 +376,29 @@ __device__ __forceinline__ void cell(float pre, int j, float c_old, float &c_new
 
 // Receives a vector of `rows` rows of n4 16-byte pieces each (rows row_bytes apart from byte `base`
 // of the exchange buffers on) and hands every piece to f(row, k4, words).
+// (piece i of a thread: number piece_index, of row piece_row; threads beyond the vector read its last
+// piece along)
+__device__ __forceinline__ unsigned piece_index(unsigned tid, int i, int n) { return min(tid + (unsigned)(i * kResThreads), (unsigned)(n - 1)); }
+__device__ __forceinline__ unsigned piece_inverse(int n4) { return ((1u << 20) + (unsigned)n4 - 1u) / (unsigned)n4; }     // idx / n4 for idx * n4 < 2^20, idx < 2^11
+__device__ __forceinline__ unsigned piece_row(unsigned idx, unsigned inv) { return __umul24(idx, inv) >> 20; }
+template <int WIDTH>
+__device__ __forceinline__ unsigned piece_offset(unsigned idx, unsigned inv, int n4)
+{
+    return __umul24(piece_row(idx, inv), WIDTH * 4u - (unsigned)n4 * 16u) + idx * 16u;
+}
 template <int WIDTH, class F>
 __device__ __forceinline__ void receive_rows(const ResidentParams &p, RCtx &x, unsigned base, int rows, int n4, F f)
 {
     constexpr int N = (kResRows * (WIDTH / 4) + kResThreads - 1) / kResThreads;
     unsigned off[N];
     r4u v[N];
-    const unsigned tid = (unsigned)(x.wave * 64 + lane_id()), last = (unsigned)(rows * n4 - 1);
-    const unsigned inv = ((1u << 20) + (unsigned)n4 - 1u) / (unsigned)n4;   // idx / n4 for idx * n4 < 2^20, idx < 2^11
-    auto row_of = [&](unsigned idx) { return __umul24(idx, inv) >> 20; };
+    const unsigned tid = (unsigned)(x.wave * 64 + lane_id()), inv = piece_inverse(n4);
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        // (threads beyond the vector read its last piece along)
-        const unsigned idx = min(tid + (unsigned)(i * kResThreads), last);
-        off[i] = __umul24(row_of(idx), WIDTH * 4u - (unsigned)n4 * 16u) + idx * 16u;
-    }
+    for (int i = 0; i < N; ++i) off[i] = piece_offset<WIDTH>(piece_index(tid, i, rows * n4), inv, n4);
     receive<N>(p, x, off, base, v);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        const unsigned idx = min(tid + (unsigned)(i * kResThreads), last), r = row_of(idx);
+        const unsigned idx = piece_index(tid, i, rows * n4), r = piece_row(idx, inv);
         f((int)r, (int)(idx - __umul24(r, (unsigned)n4)), v[i]);
     }
 }
@@ -460,27 +465,41 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     x.polls = 0;
     // Work-groups go to the XCDs round-robin: index % n_xcd is the XCD, index / n_xcd the place on it.
     const int n_xcd = p.pl.n_xcd, xcd = blockIdx.x % n_xcd, place = blockIdx.x / n_xcd;
-    const int chain_xcds = PAIR ? n_xcd / 2 : n_xcd;
+    const int chain_xcds = PAIR ? res_chain_xcds(n_xcd) : n_xcd, helper_xcds = n_xcd - chain_xcds;
     const bool helper = PAIR && xcd >= chain_xcds;
-    const int team = (xcd % chain_xcds) + chain_xcds * (place / TS);
-    x.rank = place % TS;
     const int n_teams = p.pl.n_teams;
+    x.rank = place % TS;
     if (p.zero_stats && blockIdx.x == 0 && tid0 == 0) p.stats[kStatDecodeStart] = wall_clock64();
-    int n_list = 0;
-    for (int q = 0; q * n_teams < p.B; ++q) n_list += q * n_teams + ((q & 1) ? n_teams - 1 - team : team) < p.B;
-    if (n_list == 0) {
-        if (p.zero_stats && !helper && x.rank == 0 && tid0 < kStatCounters) p.stats[(long long)team * kStatStride + tid0] = 0;
+    // utterances of a team: rank q * n_teams + m of the sorted lengths, m serpentine
+    auto list_of = [&](int team) {
+        int n = 0;
+        for (int q = 0; q * n_teams < p.B; ++q) n += q * n_teams + ((q & 1) ? n_teams - 1 - team : team) < p.B;
+        return n;
+    };
+    auto buffers_of = [&](int team) { return __builtin_amdgcn_make_buffer_rsrc(p.xbuf + (size_t)team * bo.bytes, 0, (int)bo.bytes, 0x00020000); };
+    // this work-group's team; a helper's first, and every helper_xcds-th one of the same place after it
+    const int team = (helper ? xcd - chain_xcds : xcd) + chain_xcds * (place / TS);
+    auto serves = [&](int i) { return team % chain_xcds + i * helper_xcds < chain_xcds && list_of(team + i * helper_xcds) > 0; };
+    if (!helper && list_of(team) == 0) {
+        if (p.zero_stats && x.rank == 0 && tid0 < kStatCounters) p.stats[(long long)team * kStatStride + tid0] = 0;
         return;
     }
-    x.buf = __builtin_amdgcn_make_buffer_rsrc(p.xbuf + (size_t)team * bo.bytes, 0, (int)bo.bytes, 0x00020000);
+    x.buf = buffers_of(team);
 
     // ---- put the mark into this work-group's share of every buffer -----------------------------
-    {
-        // (through to the memory side: whether the team may keep its words in the L2 is known below)
-        const unsigned lo_b = helper ? bo.pre : 0u, hi_b = helper ? bo.bytes : (PAIR ? bo.pre : bo.hr[0]);
+    // (through to the memory side: whether the team may keep its words in the L2 is known below)
+    auto put_marks = [&](unsigned from, unsigned to) {
         const r4u mark = {kMark, kMark, kMark, kMark};
-        for (unsigned o = lo_b + ((unsigned)x.rank * kResThreads + (unsigned)tid0) * 16u; o < hi_b; o += TS * kResThreads * 16u)
+        for (unsigned o = from + ((unsigned)x.rank * kResThreads + (unsigned)tid0) * 16u; o < to; o += TS * kResThreads * 16u)
             __builtin_amdgcn_raw_buffer_store_b128(mark, x.buf, (int)o, 0, 16);
+    };
+    if (!helper) {
+        put_marks(0u, PAIR ? bo.pre : bo.hr[0]);
+    } else {
+        bool any = false;
+        for (int i = 0; i < kResServed; ++i)
+            if (serves(i)) { x.buf = buffers_of(team + i * helper_xcds); put_marks(bo.pre, bo.bytes); any = true; }
+        if (!any) return;
     }
     if (tid0 == 0) { rc.ok = 1; rc.n_list = 0; rc.st_clamped = 0; rc.st_overflow = 0; }
     if (tid0 < kResSamples) { rc.s_k[tid0] = p.blank; rc.s_d[tid0] = 0; }
@@ -495,17 +514,21 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     __syncthreads();
 
     // ---- the team meets: everyone announces the XCD it runs on --------------------------------
-    auto meet = [&]() {
+    auto announce = [&]() {
         if (tid0 == 0) {
             const unsigned id = (__builtin_amdgcn_s_getreg((3 << 11) | 20) & 0xfu) + 1u;
             __hip_atomic_store(p.form + blockIdx.x, id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        // lanes 0 .. TS-1 of the first wave: the chain's work-groups, lanes 32 ..: the helpers
+    };
+    // Waits for team t in the first wave, lanes 0 .. TS-1 for the chain's work-groups and (both) lanes 32 .. for
+    // its helpers; true when the chain's all sit on one XCD.
+    auto meet = [&](int t, bool both) {
         const int side = lane0 >> 5, r = lane0 & 31;
-        const bool mine = x.wave == 0 && r < TS && (side == 0 || PAIR);
+        const bool mine = x.wave == 0 && r < TS && (side == 0 || both);
         unsigned v = 1;
         if (mine) {
-            const unsigned *slot = p.form + (((team / chain_xcds) * TS + r) * n_xcd + team % chain_xcds + side * chain_xcds);
+            const int on = t % chain_xcds, at = side ? chain_xcds + on % helper_xcds : on;
+            const unsigned *slot = p.form + ((t / chain_xcds) * TS + r) * n_xcd + at;
             unsigned spins = 0;
             v = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             while (v == 0u) {
@@ -514,9 +537,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             }
             x.polls += __builtin_amdgcn_readfirstlane((int)spins);
         }
-        const unsigned first = (unsigned)__builtin_amdgcn_readlane((int)v, helper ? 32 : 0);
-        const int same = !(mine && (side == 1) == helper && v != first);
-        x.local = __syncthreads_and(same) != 0;
+        const unsigned first = (unsigned)__builtin_amdgcn_readfirstlane((int)v);
+        return __syncthreads_and(!(mine && side == 0 && v != first)) != 0;
     };
     const bool has_cells = x.wave < 5;          // finishes 16 (unit, row) pairs of the LSTM stages, see stage_sum
     auto prelane = [&]() { return (((unsigned)x.rank * 5u + (unsigned)x.wave) * 64u + (unsigned)lane_id()) * 4u; };
@@ -528,24 +550,88 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         const float *src = p.w_help + (long long)(x.rank * kResWaves + x.wave) * (2 * LREGS) * 64;
         load_regs(w0, src, 0, lane0);
         load_regs(w1, src, LREGS, lane0);
-        meet();
-        bool go = rc.ok != 0;
-        for (unsigned n = 1; go; ++n) {
+        announce();
+        // A helper XCD works for kResServed teams, in the order in which their vectors come: it needs 3 us for
+        // both layers of a step that takes the chain 7 to 10.
+        __amdgpu_buffer_rsrc_t bufs[kResServed];
+        unsigned step[2 * kResServed];             // of team i: step number, and the layer that comes next
+        unsigned live = 0;
 #pragma unroll
-            for (int layer = 0; layer < 2; ++layer) {
-                unsigned char *xr = lds + lo.xh + layer * kResRows * XROW;
-                float *sums = reinterpret_cast<float *>(lds + lo.p);
-                int seen = 0;
-                receive_rows<W>(p, x, bo.hr[layer] + RES_SLOT(n) * VSLOT, p.slots, h4, [&](int r, int k4, r4u v) {
-                    if (v.x == kStop) seen = 1;
-                    x_put<BF>(xr + r * XROW, k4, v);
-                });
-                if (__syncthreads_or(seen) || !rc.ok) { go = false; break; }
-                lstm_stage<BF, CLS>(layer == 0 ? w0 : w1, xr, h4, sums, x.wave, lane_id());
+        for (int i = 0; i < kResServed; ++i) {
+            step[2 * i] = 1; step[2 * i + 1] = 0;
+            bufs[i] = buffers_of(serves(i) ? team + i * helper_xcds : team);
+            if (serves(i)) { (void)meet(team + i * helper_xcds, false); live |= 1u << i; }
+        }
+        __syncthreads();
+        constexpr int N = (kResRows * (W / 4) + kResThreads - 1) / kResThreads;
+        const unsigned inv = piece_inverse(h4);
+        // LDS: partial sums of the teams' stages, then the rows of their vectors
+        constexpr int XR = kResServed * kResWaves * 1024;
+        static_assert(XR + kResServed * kResRows * XROW <= lo.bytes, "the helpers' layout fits");
+        unsigned spins = 0, par = 0;
+        while (live != 0u && rc.ok) {
+            r4u v[kResServed][N];
+            const unsigned tid = (unsigned)(x.wave * 64 + lane_id());
+            unsigned f = 0;                        // bits 0 ..: team i's vector is complete; bits 8 ..: it says stop
+#pragma unroll
+            for (int i = 0; i < kResServed; ++i)
+                if (live >> i & 1u) {
+                    x.buf = bufs[i];
+                    const unsigned at = bo.hr[0] + step[2 * i + 1] * (bo.hr[1] - bo.hr[0]) + RES_SLOT(step[2 * i]) * VSLOT;
+                    bool missing = false;
+#pragma unroll
+                    for (int k = 0; k < N; ++k) v[i][k] = get4(x, piece_offset<W>(piece_index(tid, k, p.slots * h4), inv, h4), at);
+#pragma unroll
+                    for (int k = 0; k < N; ++k) missing = missing || has_mark(v[i][k]);
+                    if (__ballot(missing) == 0ull) f |= 1u << i | (__ballot(v[i][0].x == kStop) != 0ull ? 256u << i : 0u);
+                }
+            if (lane_id() == 0) rc.seen[par][x.wave] = f;
+            __syncthreads();
+            unsigned all = ~0u, any = 0;
+#pragma unroll
+            for (int w = 0; w < kResWaves; ++w) { all &= rc.seen[par][w]; any |= rc.seen[par][w]; }
+            all = (unsigned)__builtin_amdgcn_readfirstlane((int)all) & live;
+            any = (unsigned)__builtin_amdgcn_readfirstlane((int)any);
+            par ^= 1u;
+            if (all == 0u) {
+                if (wait_expired(p, spins)) rc.ok = 0;
+                continue;
+            }
+            spins = 0;
+            unsigned todo = all & ~(any >> 8);
+            live &= ~(all & (any >> 8));
+            // the vectors that are here go to LDS; the second layers' first, which are needed sooner
+            unsigned second = 0;
+#pragma unroll
+            for (int i = 0; i < kResServed; ++i)
+                if (todo >> i & 1u) {
+                    second |= step[2 * i + 1] << i;
+#pragma unroll
+                    for (int k = 0; k < N; ++k) {
+                        const unsigned idx = piece_index(tid, k, p.slots * h4), r = piece_row(idx, inv);
+                        x_put<BF>(lds + XR + (i * kResRows + r) * XROW, (int)(idx - __umul24(r, (unsigned)h4)), v[i][k]);
+                    }
+                }
+            __syncthreads();
+            while (todo != 0u) {
+                const unsigned t = (unsigned)__builtin_ctz(second & todo ? second & todo : todo);
+                todo &= ~(1u << t);
+                unsigned n = 0, layer = 0;
+#pragma unroll
+                for (unsigned i = 0; i < kResServed; ++i)
+                    if (t == i) {
+                        x.buf = bufs[i];
+                        n = step[2 * i]; layer = step[2 * i + 1];
+                        step[2 * i] += layer; step[2 * i + 1] = layer ^ 1u;
+                    }
+                const unsigned char *xr = lds + XR + t * kResRows * XROW;
+                float *sums = reinterpret_cast<float *>(lds) + t * kResWaves * 256;
+                if (layer == 0) lstm_stage<BF, CLS>(w0, xr, h4, sums, x.wave, lane_id());
+                else lstm_stage<BF, CLS>(w1, xr, h4, sums, x.wave, lane_id());
                 __syncthreads();
                 if (has_cells) {
-                    put_far(x, prelane(), bo.pre + ((unsigned)layer * kResSlots + RES_SLOT(n)) * PSLOT, word_of(stage_sum(sums, x.wave, lane_id())));
-                    put_far(x, prelane(), bo.pre + ((unsigned)layer * kResSlots + RES_SLOT(n + 2)) * PSLOT, kMark);
+                    put_far(x, prelane(), bo.pre + (layer * kResSlots + RES_SLOT(n)) * PSLOT, word_of(stage_sum(sums, x.wave, lane_id())));
+                    put_far(x, prelane(), bo.pre + (layer * kResSlots + RES_SLOT(n + 2)) * PSLOT, kMark);
                 }
             }
         }
@@ -624,7 +710,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     float *tpart = reinterpret_cast<float *>(lds + lo.tpart);        // [wave][tile][16]
     float *g4 = reinterpret_cast<float *>(lds + lo.g4);              // [row group][wave][lane][row]
 
-    meet();
+    announce();
+    x.local = meet(team, PAIR);
     bool ok = rc.ok != 0;
 
     // state of the lane's cell, [layer]: committed and candidate cell value, recurrent pre-activation

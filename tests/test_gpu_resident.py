@@ -40,11 +40,11 @@ def test_edges_of_the_size_classes(pkg, H, J, V1, L, bf16):  # noqa: F811
     eng.close()
 
 
-@pytest.mark.parametrize("B", [2, 33, 70, 515])
+@pytest.mark.parametrize("B", [2, 33, 70, 645])
 @pytest.mark.parametrize("extra", [{}, dict(durations=(0, 1, 3, 7)), dict(big_blanks=(2, 5))])
 def test_lists_longer_than_the_rows_in_work(pkg, B, extra):  # noqa: F811
     """Every decoder with one row per team, a partly filled last row, rows that take over the next
-    utterance of the team's list, and (515 utterances on 4 teams) a second launch."""
+    utterance of the team's list, and (645 utterances on 5 teams) a second launch."""
     w = model_inputs(324, 332, 530 if not extra else 520, 2, B=B, T=9, seed=B, **extra)
     eng = pkg.Engine(w.model, w.B, w.T)
     check(pkg, w, w.variant, f"list {B} {extra}", engine=eng, logp=True)
