@@ -24,19 +24,13 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 
-# Phase timers of a profile build (rnnt_engine_phase_timers), in the order of their slots.
-# "general" = prediction step of teams with more than four utterances (barriers, inputs filled
-# from the exchange buffers); the fast step of smaller teams leaves those slots at zero.
-PHASES = ["pred: stage-0 input filled (general)", "pred: recurrent stage of all layers",
-          "pred: layer-0 cell and store", "pred: barrier (general)",
-          "pred: hidden vectors of the layer below received", "pred: input stage of a layer",
-          "pred: cell of a layer and store", "pred: barrier (general)",
-          "pred: top hidden vectors received", "pred: prediction-side projection stage",
-          "pred: q stored", "pred: barrier (general)", "pred: q received",
-          "joint: z rows complete (work-group barrier)", "joint: output stage", "joint: candidates scanned, partial published",
-          "control: results walked, labels emitted", "joint: argmax exchange", "control: before a step",
-          "control: row states exchanged between joint groups", "joint: candidates from partial sums",
-          "unused", "joint: frame loads and first weight loads issued", "joint: z formed"]
+# Phase timers of a profile build (rnnt_engine_phase_timers), in the order of their slots, of the kernel
+# with register-resident weights, which runs the models measured here.
+PHASES = ["pred: helpers' results", "pred: layer-0 cell, published", "pred: layer-0 vector received", "pred: input stage of layer 1",
+          "pred: layer-1 cell, published", "pred: recurrent stage of layer 0", "pred: layer-1 vector received",
+          "pred: projection stage, q published", "pred: recurrent stage of the top layer", "pred: q received",
+          "joint: frames there (work-group barrier)", "joint: output stage", "joint: sums, argmax published", "joint: keys received",
+          "joint: result shared (work-group barrier)", "control: hops, labels emitted, next samples"]
 
 
 def algorithmic_bytes(dims, B, variant, enc_len, tok_frames, S, wbytes=4):
@@ -73,12 +67,9 @@ def algorithmic_bytes(dims, B, variant, enc_len, tok_frames, S, wbytes=4):
 
 
 def issued_weight_bytes(dims, stats, bytes_per_weight=4):
-    """Bytes of the steps the device ran, from its own step counters: every prediction
-    step of a team streams the recurrent and upper-layer LSTM weights and W_pred (layer 0's
-    input weights are folded into a table and never stream), every joint step of a joint
-    group streams W_out.  The joint counter covers the first group of each team; the other
-    groups are taken to be alike.  Part of it is served by the L2 of an XCD that several
-    teams share, so the profiled HBM traffic is lower."""
+    """Bytes of the weights applied by the steps the device ran, from its own step counters: every
+    prediction step of a team the recurrent and upper-layer LSTM weights and W_pred (layer 0's
+    input weights are folded into a table), every joint step W_out."""
     H, L, J = dims.H, dims.L, dims.J
     pred = bytes_per_weight * (sum(4 * H * (H + (H if l else 0)) for l in range(L)) + J * H)
     joint = bytes_per_weight * dims.n_out * J
@@ -341,8 +332,7 @@ def main() -> int:
         w.model.dims, w.B, args.variant, w.enc_len, r["frames"], w.max_symbols, wb)
     min_bytes, min_pred, min_joint, _ = minimum_schedule_bytes(
         w.model.dims, w.B, args.variant, w.enc_len, r["frames"], w.max_symbols, wb)
-    # bytes of the steps the device counted (every team step reads its streamed weights once,
-    # out of the L2 of its XCD)
+    # bytes of the weights that the steps the device counted apply
     step_bytes = issued_weight_bytes(w.model.dims, r["stats"], wb)
     t_dec = r["dec_ms"] * 1e-3
     achieved = min_bytes / t_dec / 1e9
@@ -358,7 +348,7 @@ def main() -> int:
         "data": "synthetic",
         "timing_note": "value and ms_per_step are host wall time over the timed calls, each followed "
                        "by rnnt_engine_stats (a device synchronisation and a small copy), so they "
-                       "are conservative; kernel_ms are HIP-event times around each launch, median "
+                       "are conservative; kernel_ms are times on the device's clock, median "
                        "and minimum over the timed calls",
         "config": {"workload": f"config {dict(frame=2, label=3, tdt=4)[args.variant]}: "
                                f"{w.name}, B={w.B}, T<={w.T}, frames={n_frames}, "
@@ -376,7 +366,7 @@ def main() -> int:
                    "engine": r["stats"]},
         # The numerator is the method's minimum: the bytes of the fewest batched steps an exact
         # schedule needs on this batch, every weight once per step.  The kernel is not bound by
-        # HBM: its weight streams are served by the XCD L2s and its time is the latency of the
+        # HBM: its weights stay in registers for the launch and its time is the latency of the
         # longest utterance's chain of dependent steps; the fraction says how far that leaves it
         # from streaming the minimum schedule at HBM speed.
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -386,16 +376,16 @@ def main() -> int:
                                    "utterance + 1, joint steps = most (frames + labels) of an "
                                    "utterance, each step touching every weight once",
                      "limited_by": "latency of the dependent step chain of the longest utterance "
-                                   "(weight streams come out of the XCD L2s, not HBM)",
+                                   "(the weights stay in registers; nothing of a step comes from HBM)",
                      "minimum_schedule": {"prediction_steps": min_pred, "joint_steps": min_joint},
                      "hbm_measured": None if traffic is None else {
                          "bytes": traffic, "GBs": traffic / t_dec / 1e9,
                          "frac": traffic / t_dec / 1e9 / HBM_PEAK_GBS},
-                     "l2_stream": {"served_bytes": step_bytes, "achieved": step_bytes / t_dec / 1e9,
-                                   "peak_measured": l2_peak, "unit": "GB/s",
-                                   "frac": None if not l2_peak else step_bytes / t_dec / 1e9 / l2_peak,
-                                   "note": "bytes of the team steps the device counted x weights "
-                                           "streamed per step; peak from bench.py --probes"},
+                     "weights_applied": {"bytes": step_bytes, "GBs": step_bytes / t_dec / 1e9,
+                                         "l2_stream_peak_measured": l2_peak,
+                                         "note": "bytes of the team steps the device counted x weights "
+                                                 "of a step; they stay in registers, so this may pass "
+                                                 "what the L2s could stream (bench.py --probes)"},
                      "literal_schedule": {"prediction_steps": lit_pred, "joint_steps": lit_joint,
                                           "bytes": lit_bytes, "achieved": lit_bytes / t_dec / 1e9,
                                           "note": "the timed decoder's own schedule run on the whole "

@@ -95,6 +95,8 @@ typedef struct rnnt_model_desc {
 /* Work counters of the last decode call (rnnt_engine_stats). */
 typedef struct rnnt_stats {
     int64_t pred_steps;   /* batched prediction-network steps, summed over teams */
+                          /* (by utterance for rnnt_greedy_decode, in the kernel */
+                          /* with register-resident weights)                     */
     int64_t joint_steps;  /* batched joint steps (chunks), summed over the first */
                           /* joint group of every team                           */
     int64_t max_pred_steps;   /* the same, for the team that did the most        */
@@ -111,8 +113,8 @@ typedef struct rnnt_stats {
                               /* next prediction step (0 = no limit)             */
     float projection_ms;      /* device time of the encoder-projection kernel    */
     float decode_ms;          /* device time of the persistent decode kernel,    */
-                              /* both from HIP events recorded on the call's     */
-                              /* stream around each launch                       */
+                              /* from the device's clock (streaming kernel: from */
+                              /* HIP events recorded around each launch)         */
 } rnnt_stats;
 
 /*
@@ -211,11 +213,14 @@ int rnnt_quantize_blocks_e2m1(const float *w, int64_t rows, int64_t cols, float 
 /*
  * rnnt_engine_create flag: launch the decode kernel with an ordinary launch
  * instead of a cooperative one.  The kernel's teams synchronise among
- * themselves, which needs all work-groups resident at once; the cooperative
- * launch guarantees that, an ordinary launch of one work-group per compute
- * unit has it on a device that runs nothing else (every wait in the kernel is
- * bounded, so a call that does not get it ends with RNNT_DEV_ABORTED instead
- * of hanging).  For profiling runs: a process that has run a cooperative
+ * themselves, which needs all work-groups resident at once.  The library orders
+ * the decodes of a device one after another, whatever their streams and
+ * threads, so an ordinary launch of one work-group per compute unit gets there
+ * as other kernels end (every wait in the kernel is bounded, so a call that
+ * does not ends with RNNT_DEV_ABORTED instead of hanging).  The kernel with
+ * register-resident weights is always launched that way (except into a stream
+ * capture); the flag is for the other one, in
+ * profiling runs: a process that has run a cooperative
  * launch under rocprofv3's kernel trace has been seen to crash in its exit
  * handlers.  May be combined with a storage flag.
  */
@@ -258,7 +263,14 @@ int rnnt_quantize_blocks_e2m1(const float *w, int64_t rows, int64_t cols, float 
  * The two bias vectors of an LSTM layer are added once on the host while the
  * weights are repacked (b_ih + b_hh in fp32).
  * max_B itself has no limit but memory (the projected frames take
- * max_B * max_T * J floats): a call with more than 128 utterances is decoded
+ * max_B * max_T * J floats).
+ * Models of one or two LSTM layers of at most 640 units, a joint width of at
+ * most 640 and at most 1056 output columns are decoded by a kernel that keeps
+ * the weights in registers; one launch of it takes up to 128 utterances per
+ * team (rnnt_stats.n_teams).  The rest of this paragraph is about the other
+ * kernel, which streams them, and which those models use too once
+ * rnnt_engine_configure has asked for something.
+ * A call with more than 128 utterances is decoded
  * by consecutive launches of up to 128 utterances each, in the caller's order,
  * after one projection of the whole batch (on MI355X that is faster than
  * larger launches); status word and statistics cover the whole call, and
@@ -274,9 +286,9 @@ int rnnt_quantize_blocks_e2m1(const float *w, int64_t rows, int64_t cols, float 
  * the device (fewer joint groups, then more teams, then fewer) before it
  * refuses.
  * Device memory of an engine: the projected frames (max_B * max_T * J floats)
- * and, per team layout (up to eleven, see rnnt_engine_configure), a packed
- * copy of the streamed weights and a few megabytes of workspace: about
- * 0.4 GB besides the projected frames for the Parakeet shape in fp32.
+ * and a packed copy of the weights and a few megabytes of workspace, 40 MB
+ * for the Parakeet shape in fp32; of the streaming kernel one copy per team
+ * layout (up to eleven, see rnnt_engine_configure), about 0.4 GB.
  * Synchronous.  *out is set only on success.
  */
 int rnnt_engine_create(const rnnt_model_desc *desc, int32_t max_B, int32_t max_T,
@@ -379,7 +391,11 @@ int rnnt_engine_status(rnnt_engine *eng, int32_t *status_out);
 int rnnt_engine_stats(rnnt_engine *eng, rnnt_stats *out);
 
 /*
- * Tuning knobs, for measurement.  By default an engine holds one team layout
+ * Tuning knobs, for measurement, of the streaming kernel: a call that gives one
+ * moves the engine to it (its layouts are made then), and one that gives none
+ * (0, 0, 0, 0), on an engine whose n_teams was never given, moves it back to
+ * the kernel with register-resident weights where the model fits that.
+ * Without knobs the streaming kernel has one team layout
  * per range of launch sizes (1-2, 3-8, 9-16, ... utterances, up to
  * min(max_B, 128)), each with its own packed copy of the weights, and a
  * launch runs in the one for its size: a small batch is decoded the way an
@@ -442,13 +458,13 @@ int rnnt_engine_set_done_flags(rnnt_engine *eng, int32_t *done);
 /*
  * How long the device-side waits of the decode calls that follow may last.  The
  * work-groups of a team wait for each other's results by polling; every such
- * wait gives up after `polls` repeated polls (one takes about a microsecond),
+ * wait gives up after `polls` repeated polls (one takes 0.1 to 1 microsecond),
  * raises a flag that makes every other wait of the launch give up too, and the
  * call ends in the ordinary way with RNNT_DEV_ABORTED in the status word and
  * outputs that must not be used (Algorithm 1's loops have no such exit: this
  * is the bound that keeps a launch that did not get all its work-groups
  * resident, or a failing device, from hanging the stream).  polls = -1
- * restores the default, 2^22 (a few seconds); 0 lets a wait poll once, which
+ * restores the default, 2^22 to 2^24 by kernel (a few seconds); 0 lets a wait poll once, which
  * makes the first wait of a launch fail -- the way the tests reach the failure
  * path.  A later call on the engine starts clean.  RNNT_ERR_SHAPE for values
  * below -1 or above 2^32 - 1.

@@ -618,7 +618,7 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
             for (int i = 0; i < kMaxDur; ++i) p.durations[i] = e->durations[i];
             p.B = nb; p.T = T; p.S = S; p.cap = cap;
             resident_rows(pl, nb, &p.slots, &p.la);
-            p.spin_limit = e->spin_limit;
+            p.spin_limit = e->spin_limit == kDefaultSpinLimit ? kDefaultSpinLimit * 4u : e->spin_limit;      // (its polls are shorter)
             p.pl = pl;
             const long long oc = (long long)off * cap;
             p.enc_len = enc_len + off; p.P = ws.P + (long long)off * T * d.J;

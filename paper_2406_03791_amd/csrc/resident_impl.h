@@ -3,36 +3,42 @@
 // The step chain of a decode (a prediction step, a joint step, and again) is bound by latency:
 // three dense stages and four hand-overs between work-groups per label.  Two things make it
 // short here.  (1) Every weight of the step is held in the registers of one compute unit for the
-// whole launch: four waves of 512 registers keep up to 368 weight registers per lane, 92 K fp32
-// values per compute unit, so a stage reads nothing but its input vector.  (2) A team of
-// work-groups sits inside one XCD, so its hand-overs go through that XCD's L2: a store that stays
-// in the L2 and a load that passes by the L1 hand 640 floats to 32 work-groups in 0.97 us, where
-// stores and loads through the memory side take 1.76 us (4 x 640 floats: 1.2 against 1.95 us).
+// whole launch: eight waves of 256 registers, of which up to 196 hold weights, so a stage reads
+// nothing but its input vector (streamed out of L2, the weights took 5 to 27 us of a step).  (2) A team
+// of work-groups sits inside one XCD, so its hand-overs go through that XCD's L2: a store that stays
+// in the L2 and a load that passes by the L1 hand 640 floats to 32 work-groups in 0.70 us, where
+// stores and loads through the memory side take 1.3 us (4 x 640 floats: 0.88 against 1.4 us).
+// 32 utterances of a two-layer model of 640 units: 4.35 to 1.9 ms, one of 500 frames 1.63 to 0.5 ms.
 //
 // Work split inside a team of `ts` work-groups: LSTM units, projection columns and output columns
-// in contiguous ranges.  LSTM stages run on v_mfma 4x4 (16 blocks): a wave owns five units (the
-// four gates of a unit are a block's four columns) and its 16 blocks are 16 slices of K, so the
-// sums of a unit meet inside one wave (permlane swaps and DPP adds) and the pointwise part follows
-// without a barrier.  The joint output runs on v_mfma 16x16 (16 samples x 16 columns, two column
-// tiles x two halves of K over the four waves); its operand relu(P + q) is formed on the way from
+// in contiguous ranges.  LSTM stages and the projection run on v_mfma 4x4 (16 blocks): the rows of a
+// block are four utterances, its columns the gates of a unit or four columns, K is split over the waves
+// and the partial sums meet in LDS.  The joint output runs on v_mfma 16x16 (16 columns x 16 samples,
+// two column tiles, K in eighths over the waves); its operand relu(P + q) is formed on the way from
 // LDS to the matrix instruction.
 //
 // Two-layer fp32 models have more weights than one XCD's registers hold (24 MB against 12 + 4):
-// there a team owns two XCDs.  The work-groups of the first run the whole step chain and keep the
-// input, projection and output matrices; those of the second keep the recurrent matrices and
-// compute W_hh h of the candidate state, which the chain needs only at the next label: their
-// hand-overs across the XCDs (1.8 us each way) run beside the rest of the step.
+// there the teams' XCDs keep the input, projection and output matrices and run the whole step chain;
+// the helpers' XCDs keep the recurrent matrices and compute W_hh h of the candidate states, which the
+// chain needs only at the next label: their hand-overs across the XCDs run beside the rest of the
+// step.  A helper is busy 3 us of a team's step and serves two teams: 128 utterances 7.7 ms with one team
+// per helper, 6.5 with five teams on three XCDs of helpers, 7.1 with six on two.
 //
 // Utterances are decoded label-looping fashion: every utterance has its own frame index, a joint
 // step examines `la` frames of every utterance, and the next prediction step runs as soon as one
 // of them has a label.  A team takes a list of utterances and decodes up to kResRows at a time;
-// when one ends the next of the list takes its place.
+// when one ends the next of the list takes its place.  (Eight rows of four frames took 15 us a step
+// where four rows of eight take 10.)
 //
 // Exchange: a vector's buffer has four slots used in turn; words are 32-bit floats, all ones
 // meaning "not there yet" (readers poll the data itself).  A work-group puts that mark back into
 // slot n - 2 when it publishes step n: by then it has received something of step n - 1 from
 // everyone, which everyone sent after reading step n - 2; and it waits for that store before it
 // publishes step n + 1, so nobody can look for step n + 2's data in a slot that still holds old data.
+//
+// Registers decide what the code looks like: values that could be kept for the whole loop are worked out
+// where they are used (lane_id), state that few waves need lies in LDS, arguments that few steps need are
+// read again (args_again).  A spilled weight is a load from memory in the middle of a stage.
 #pragma once
 #include <type_traits>
 
