@@ -129,6 +129,8 @@ struct TeamConfig {
     unsigned lds_bytes = 0;
 };
 
+typedef std::vector<std::unique_ptr<TeamConfig>> TeamConfigs;
+
 struct rnnt_engine {
     rnnt_model_desc d{};
     int durations[kMaxDur] = {0};
@@ -161,8 +163,8 @@ struct rnnt_engine {
     // the rows per team, hence the prediction path) changes, in ascending order of for_B: a
     // launch of nb utterances runs in the first layout planned for at least nb.  An engine for
     // many utterances so decodes a small batch the way an engine made for that batch would.
-    std::vector<std::unique_ptr<TeamConfig>> frame_cfgs;   // Algorithm 1
-    std::vector<std::unique_ptr<TeamConfig>> label_cfgs;   // label looping, RNN-T and TDT
+    TeamConfigs frame_cfgs;         // Algorithm 1
+    TeamConfigs label_cfgs;         // label looping, RNN-T and TDT
     // layouts (and workspaces) the launches of the last call ran in: where its statistics are
     struct Used { const TeamConfig *t; Workspace ws; int nb; };   // nb: utterances of its latest launch
     std::vector<Used> last_used;
@@ -406,7 +408,7 @@ int plan_and_pack(rnnt_engine *e, TeamConfig &t, int n_teams, int groups, int fo
 //   per team from 9 utterances on, four for an RNN-T with five to eight utterances per team.
 //   Engines for one or two utterances: 4 teams of 64 for either decoder (2-5 % faster than 8
 //   teams of 32 there, equal from four utterances on; teams of 128 and 256 are slower).
-int default_layouts(rnnt_engine *e)
+int default_layouts(rnnt_engine *e, TeamConfigs &frame_cfgs, TeamConfigs &label_cfgs)
 {
     // A layout whose state does not fit the compute units' local memory (wide layers, many
     // layers, many rows per team) is followed by the others that divide the device, teams
@@ -430,21 +432,20 @@ int default_layouts(rnnt_engine *e)
         v.push_back(e->plan_B);
         return v;
     };
-    e->frame_cfgs.clear();
-    e->label_cfgs.clear();
-    e->last_used.clear();
+    frame_cfgs.clear();
+    label_cfgs.clear();
     // (32 and 64: one and two rows per team of the 32-team arrangement, whose LDS plan keeps the
     // finer K slicing that the plan for four rows has no room for)
     for (int B : sizes({2, 8, 16, 32, 64})) {
         int nf = B <= 2 ? 4 : (B <= 8 ? 8 : (B <= 16 ? 16 : 32));
         while (nf > 1 && e->n_wg % nf != 0) nf /= 2;
         while ((B + nf - 1) / nf > kMaxRows) nf *= 2;
-        e->frame_cfgs.emplace_back(new TeamConfig());
-        e->frame_cfgs.back()->is_frame = true;
-        const int rc = with_fallbacks(*e->frame_cfgs.back(), nf, 1, B);
+        frame_cfgs.emplace_back(new TeamConfig());
+        frame_cfgs.back()->is_frame = true;
+        const int rc = with_fallbacks(*frame_cfgs.back(), nf, 1, B);
         // a launch size whose state fits in no layout ends the list: larger calls are then
         // decoded in launches of the largest size that does fit
-        if (rc == RNNT_ERR_UNSUPPORTED && e->frame_cfgs.size() > 1) { e->frame_cfgs.pop_back(); break; }
+        if (rc == RNNT_ERR_UNSUPPORTED && frame_cfgs.size() > 1) { frame_cfgs.pop_back(); break; }
         if (rc) return rc;
     }
     // label looping: up to 64 utterances a team has at most four rows (the prediction step
@@ -459,16 +460,16 @@ int default_layouts(rnnt_engine *e)
         // five to eight rows per team: four groups of two rows keep a joint step at 16 samples
         // (2-3 % faster than two groups for an RNN-T at 72-128 utterances; slower for TDT)
         if (groups == 2 && rows >= 5 && rows <= 8 && ts % 4 == 0 && e->d.D == 0) groups = 4;
-        e->label_cfgs.emplace_back(new TeamConfig());
-        const int rc = with_fallbacks(*e->label_cfgs.back(), nl, groups, B);
-        if (rc == RNNT_ERR_UNSUPPORTED && e->label_cfgs.size() > 1) { e->label_cfgs.pop_back(); break; }
+        label_cfgs.emplace_back(new TeamConfig());
+        const int rc = with_fallbacks(*label_cfgs.back(), nl, groups, B);
+        if (rc == RNNT_ERR_UNSUPPORTED && label_cfgs.size() > 1) { label_cfgs.pop_back(); break; }
         if (rc) return rc;
     }
     return RNNT_OK;
 }
 
 // The layout a launch of nb utterances runs in: the first one planned for at least nb.
-const TeamConfig &pick_layout(const std::vector<std::unique_ptr<TeamConfig>> &cfgs, int nb)
+const TeamConfig &pick_layout(const TeamConfigs &cfgs, int nb)
 {
     for (const auto &t : cfgs)
         if (t->for_B >= nb) return *t;
@@ -935,7 +936,7 @@ int rnnt_engine_create(const rnnt_model_desc *desc, int32_t max_B, int32_t max_T
     if (e->res.kind != kResidentNone) {
         if ((rc = make_resident(e))) return rc;
         e->use_streaming = false;
-    } else if ((rc = default_layouts(e))) {
+    } else if ((rc = default_layouts(e, e->frame_cfgs, e->label_cfgs))) {
         return rc;
     }
     for (auto &x : e->ev) HIP_TRY(hipEventCreate(&x));
@@ -1007,54 +1008,67 @@ int rnnt_engine_configure(rnnt_engine *eng, int32_t n_teams, int32_t joint_group
         return RNNT_ERR_SHAPE;
     if (n_teams == 0 && joint_groups != 0) return RNNT_ERR_SHAPE;
     if (search_steps < -1) return RNNT_ERR_SHAPE;
+    if (n_teams > 0 && eng->n_wg % n_teams != 0) return RNNT_ERR_SHAPE;
     HIP_TRY(hipDeviceSynchronize());
-    if (eng->res.kind != kResidentNone) {
-        eng->own_layout = eng->own_layout || n_teams > 0;
-        const bool streaming = eng->own_layout || lookahead != 0 || search_steps != 0;
-        if (streaming && eng->label_cfgs.empty() && n_teams == 0) {
-            const int rc = default_layouts(eng);
+    const bool own_layout = eng->own_layout || n_teams > 0;
+    const bool streaming = eng->res.kind == kResidentNone || own_layout || lookahead != 0 || search_steps != 0;
+    // Layouts are made beside those in force and take their place once all of them exist, and the
+    // knobs with them: a call that is refused leaves the engine as it was.
+    TeamConfigs frame, label;
+    auto make = [&]() -> int {
+        if (n_teams > 0) {
+            // one layout for launches of every size: plain teams for Algorithm 1; the label-looping
+            // decoders split each team further
+            eng->lookahead = lookahead;   // the layouts are sized for it
+            frame.emplace_back(new TeamConfig());
+            label.emplace_back(new TeamConfig());
+            frame.back()->is_frame = true;
+            const int rc = plan_and_pack(eng, *frame.back(), n_teams, 1, eng->plan_B);
+            return rc ? rc : plan_and_pack(eng, *label.back(), n_teams, joint_groups ? joint_groups : 1, eng->plan_B);
+        }
+        if (!streaming) return RNNT_OK;
+        if (eng->label_cfgs.empty()) {
+            eng->lookahead = 0;
+            const int rc = default_layouts(eng, frame, label);
             if (rc) return rc;
         }
+        if (lookahead == eng->lookahead) return RNNT_OK;
+        // the LDS layouts are sized for the samples of a joint step, which depend on the lookahead
+        eng->lookahead = lookahead;
+        auto replan = [&](const TeamConfigs &from, TeamConfigs &to) -> int {
+            TeamConfigs made;
+            for (const auto &t : from) {
+                made.emplace_back(new TeamConfig());
+                made.back()->is_frame = t->is_frame;
+                const int rc = plan_and_pack(eng, *made.back(), t->n_teams, t->groups, t->for_B);
+                if (rc) return rc;
+            }
+            to = std::move(made);
+            return RNNT_OK;
+        };
+        const int rc = replan(frame.empty() ? eng->frame_cfgs : frame, frame);
+        return rc ? rc : replan(label.empty() ? eng->label_cfgs : label, label);
+    };
+    const int lookahead_before = eng->lookahead;
+    const int rc = make();
+    if (rc) {
+        eng->lookahead = lookahead_before;
+        return rc;
+    }
+    if (!label.empty() || eng->res.kind != kResidentNone) {
+        // the workspaces the last call's statistics live in may go away
         eng->last_used.clear();
         eng->last_ws = Workspace();
         eng->last_resident = false;
-        eng->use_streaming = streaming;
-        if (!streaming) { eng->lookahead = 0; eng->search_steps = 0; return RNNT_OK; }
     }
-    if (n_teams > 0) {
-        eng->last_used.clear();       // the workspaces the last call's statistics live in go away
-        eng->last_ws = Workspace();
-        eng->lookahead = lookahead;   // the layouts are sized for it
-        // one layout for launches of every size: plain teams for Algorithm 1; the label-looping
-        // decoders split each team further
-        if (eng->n_wg % n_teams != 0) return RNNT_ERR_SHAPE;
-        std::unique_ptr<TeamConfig> f(new TeamConfig()), l(new TeamConfig());
-        f->is_frame = true;
-        int rc = plan_and_pack(eng, *f, n_teams, 1, eng->plan_B);
-        if (!rc) rc = plan_and_pack(eng, *l, n_teams, joint_groups ? joint_groups : 1, eng->plan_B);
-        if (rc) return rc;            // the layouts in use stay as they were
-        eng->frame_cfgs.clear(); eng->label_cfgs.clear();
-        eng->frame_cfgs.push_back(std::move(f));
-        eng->label_cfgs.push_back(std::move(l));
+    if (!label.empty()) {
+        eng->frame_cfgs = std::move(frame);
+        eng->label_cfgs = std::move(label);
     }
-    const bool replan = n_teams == 0 && lookahead != eng->lookahead;
+    eng->own_layout = own_layout;
+    eng->use_streaming = streaming;
     eng->lookahead = lookahead;
     eng->search_steps = search_steps;
-    if (replan) {
-        // the LDS layouts are sized for the samples of a joint step, which depend on the lookahead
-        eng->last_used.clear();
-        eng->last_ws = Workspace();
-        int rc = RNNT_OK;
-        for (auto &t : eng->frame_cfgs)
-            if (!rc) rc = plan_and_pack(eng, *t, t->n_teams, 1, t->for_B);
-        for (auto &t : eng->label_cfgs)
-            if (!rc) rc = plan_and_pack(eng, *t, t->n_teams, t->groups, t->for_B);
-        if (rc) {
-            eng->lookahead = 0;
-            (void)default_layouts(eng);
-            return rc;
-        }
-    }
     return RNNT_OK;
 }
 

@@ -81,3 +81,26 @@ def test_two_threads_on_streams_of_their_own(pkg):  # noqa: F811
     for eng, _, _, _, _, same in jobs:
         assert eng.status() == 0 and same == [True] * 20
         eng.close()
+
+
+@pytest.mark.parametrize("L", [2, 3])
+def test_a_refused_configuration_changes_nothing(pkg, L):  # noqa: F811
+    """A fresh engine, and one with a layout and a lookahead of its own, decode after a refused
+    rnnt_engine_configure (teams that do not divide the device, joint groups that do not divide a
+    team, more than 16 utterances per team) with what was in force before it."""
+    w = model_inputs(324, 332, 530, L, B=40, T=12, seed=40 + L)
+    refused = [dict(n_teams=3), dict(n_teams=8, joint_groups=3), dict(n_teams=2), dict(joint_groups=2), dict(lookahead=33),
+               dict(n_teams=7, lookahead=4), dict(n_teams=3, search_steps=2), dict(search_steps=-2)]
+    eng = pkg.Engine(w.model, w.B, w.T)
+    for knobs in ({}, dict(n_teams=8, joint_groups=2, lookahead=3, search_steps=2), dict(lookahead=5)):
+        eng.configure(**knobs)
+        in_force = ("n_teams", "team_size", "joint_groups", "lookahead", "search_steps")
+        before = {v: check(pkg, w, v, f"in force {knobs}", engine=eng)[2] for v in ("label", "frame", "label_noalloc")}
+        for bad in refused:
+            with pytest.raises(pkg.RnntError) as err:
+                eng.configure(**bad)
+            assert err.value.code == -2, bad
+            for v in ("label", "frame", "label_noalloc"):
+                after = check(pkg, w, v, f"refused {bad}", engine=eng)[2]
+                assert [after[k] for k in in_force] == [before[v][k] for k in in_force], (knobs, bad, v)
+    eng.close()
