@@ -137,7 +137,7 @@ struct rnnt_engine {
     int NOUT = 0, max_B = 0, max_T = 0;
     int plan_B = 0;        // utterances the team layouts are planned for: min(max_B, kLaunchRows)
     int n_wg = 0;          // work-groups the device can keep resident (one per CU)
-    int lookahead = 0;
+    int lookahead = 0;     // of the streaming kernel, and what its layouts are sized for
     int search_steps = 0;  // 0: chosen per call, -1: no limit, > 0: as given
     int wt = kWeightF32;   // storage of the packed (streamed) weights
     bool plain_launch = false;   // RNNT_FLAG_PLAIN_LAUNCH
@@ -1067,7 +1067,7 @@ int rnnt_engine_configure(rnnt_engine *eng, int32_t n_teams, int32_t joint_group
     }
     eng->own_layout = own_layout;
     eng->use_streaming = streaming;
-    eng->lookahead = lookahead;
+    if (streaming) eng->lookahead = lookahead;      // (else: still the one the streaming kernel's layouts are sized for)
     eng->search_steps = search_steps;
     return RNNT_OK;
 }

@@ -104,3 +104,17 @@ def test_a_refused_configuration_changes_nothing(pkg, L):  # noqa: F811
                 after = check(pkg, w, v, f"refused {bad}", engine=eng)[2]
                 assert [after[k] for k in in_force] == [before[v][k] for k in in_force], (knobs, bad, v)
     eng.close()
+
+
+def test_the_default_lookahead_after_a_return_to_the_resident_kernel(pkg):  # noqa: F811
+    """Layouts sized for another lookahead are replanned when the streaming kernel is asked for again:
+    96 utterances of a TDT model in three rows per joint group, 8 frames each, not the 5 that fit
+    layouts made for one."""
+    w = model_inputs(324, 332, 520, 2, B=96, T=12, seed=96, durations=(0, 1, 3))
+    eng = pkg.Engine(w.model, w.B, w.T)
+    for knobs, lookahead in ((dict(lookahead=1), 1), (dict(), None), (dict(search_steps=1), 8)):
+        eng.configure(**knobs)
+        stats = check(pkg, w, "tdt", f"lookahead after {knobs}", engine=eng)[2]
+        if lookahead is not None:
+            assert stats["lookahead"] == lookahead and stats["n_teams"] == 16
+    eng.close()
