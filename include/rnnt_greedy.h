@@ -463,7 +463,8 @@ int rnnt_engine_set_done_flags(rnnt_engine *eng, int32_t *done);
  * outputs that must not be used (Algorithm 1's loops have no such exit: this
  * is the bound that keeps a launch that did not get all its work-groups
  * resident, or a failing device, from hanging the stream).  polls = -1
- * restores the default, 2^22 to 2^24 by kernel (a few seconds); 0 lets a wait poll once, which
+ * restores the default (a few seconds: 2^22 polls of the streaming kernel, 2^24
+ * of the one with register-resident weights); 0 lets a wait poll once, which
  * makes the first wait of a launch fail -- the way the tests reach the failure
  * path.  A later call on the engine starts clean.  RNNT_ERR_SHAPE for values
  * below -1 or above 2^32 - 1.

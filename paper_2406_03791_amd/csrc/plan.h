@@ -82,6 +82,12 @@ RNNT_HD inline int joint_row_groups(int samples)
     return samples <= 4 ? 1 : (samples <= 8 ? 2 : (samples <= 16 ? 4 : 8));
 }
 
+// Polls that a wait on another work-group may repeat: a few seconds by default.  The streaming
+// kernel polls about once a microsecond, the resident one four times as often.
+constexpr unsigned kStreamingWait = 1u << 22, kResidentWait = 1u << 24;
+// `limit` as rnnt_engine_set_wait_limit took it: -1 for the kernel's default, any other value as it is
+inline unsigned wait_polls(int64_t limit, unsigned by_default) { return limit < 0 ? by_default : (unsigned)limit; }
+
 // Contiguous share of n items owned by `rank` out of `ts`.
 RNNT_HD inline int range_lo(int rank, int ts, int n) { return (int)(((int64_t)rank * n) / ts); }
 RNNT_HD inline int range_hi(int rank, int ts, int n) { return (int)(((int64_t)(rank + 1) * n) / ts); }

@@ -213,6 +213,10 @@ int main()
                             }
                         }
     }
+    // a wait limit counts as given, the defaults' own values included
+    for (unsigned polls : {0u, 1u, kStreamingWait, kResidentWait, 0xffffffffu})
+        for (unsigned by_default : {kStreamingWait, kResidentWait})
+            if (wait_polls(polls, by_default) != polls || wait_polls(-1, by_default) != by_default) { std::printf("wait limit\n"); return 1; }
     std::printf("ok %ld\n", checked);
     return 0;
 }
