@@ -508,8 +508,12 @@ int rnnt_engine_phase_timers(rnnt_engine *eng, int32_t team, double *us_out, int
  *   rnnt_probe_e2m1_widening  the same for the 4-bit form: bf16_out is a HOST
  *                        array of 4 * 256 * 2 entries, [byte position][byte
  *                        value][code in the low, then the high nibble].
+ *   rnnt_probe_gate      sigmoid (is_tanh = 0) or tanh of n floats as the decode
+ *                        kernel with register-resident weights computes them;
+ *                        x and out are HOST arrays, n at most 2^28.
  * Return RNNT_OK or an RNNT_ERR_* code.
  */
+int rnnt_probe_gate(int32_t is_tanh, const float *x, int64_t n, float *out);
 int rnnt_probe_e4m3_widening(float scale, uint16_t *bf16_out);
 int rnnt_probe_e2m1_widening(float scale, uint16_t *bf16_out);
 int rnnt_probe_stream(int32_t from_l2, double *gbytes_per_s_out, double *per_cu_out);

@@ -32,6 +32,7 @@ from .binding import (  # noqa: F401
     rnnt_quantize_rows_e4m3,
     rnnt_quantize_blocks_e2m1,
     rnnt_probe_e2m1_widening,
+    rnnt_probe_gate,
     RNNT_FLAG_FP4_WEIGHTS,
     RNNT_FP4_BLOCK,
     rnnt_probe_exchange,

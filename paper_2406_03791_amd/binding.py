@@ -24,6 +24,7 @@ EXPORTS = (
     "rnnt_engine_phase_timers",
     "rnnt_probe_stream", "rnnt_probe_exchange", "rnnt_probe_mfma", "rnnt_probe_e4m3_widening",
     "rnnt_quantize_rows_e4m3", "rnnt_quantize_blocks_e2m1", "rnnt_probe_e2m1_widening",
+    "rnnt_probe_gate",
 )
 
 
@@ -121,6 +122,7 @@ def load_library():
             getattr(lib, name).argtypes = [C.POINTER(C.c_float), C.c_int64, C.c_int64,
                                            C.POINTER(C.c_float), C.POINTER(C.c_float)]
         lib.rnnt_probe_e2m1_widening.argtypes = [C.c_float, C.POINTER(C.c_uint16)]
+        lib.rnnt_probe_gate.argtypes = [C.c_int32, C.POINTER(C.c_float), C.c_int64, C.POINTER(C.c_float)]
         lib.rnnt_status_string.argtypes = [C.c_int]
         lib.rnnt_status_string.restype = C.c_char_p
         for name in EXPORTS:
@@ -304,6 +306,16 @@ def rnnt_probe_e2m1_widening(scale: float = 1.0):
     import numpy as np
     out = np.zeros((4, 256, 2), dtype=np.uint16)
     _check(load_library().rnnt_probe_e2m1_widening(C.c_float(scale), out.ctypes.data_as(C.POINTER(C.c_uint16))))
+    return out
+
+
+def rnnt_probe_gate(is_tanh: bool, x):
+    """sigmoid or tanh of a float32 numpy array as the resident decode kernel computes them."""
+    import numpy as np
+    x = np.ascontiguousarray(x, dtype=np.float32)
+    out = np.empty_like(x)
+    fp = C.POINTER(C.c_float)
+    _check(load_library().rnnt_probe_gate(int(bool(is_tanh)), x.ctypes.data_as(fp), x.size, out.ctypes.data_as(fp)))
     return out
 
 

@@ -5,12 +5,14 @@
 //   * exchange: what one all-to-all hand-over of a vector costs inside a team of work-groups,
 //               with a counter barrier and with tagged words;
 //   * mfma:     the fp32 matrix rate of the two MFMA shapes the library uses.
+// and so that the tests can check the widening instructions and the gate functions on their own.
 // None of this is on the decode path.
 #include "../../include/rnnt_greedy.h"
 
 #include <hip/hip_runtime.h>
 
 #include "engine.h"
+#include "gate.h"
 
 #include <algorithm>
 #include <cstdint>
@@ -161,6 +163,13 @@ struct Timer {
     ~Timer() { if (a) (void)hipEventDestroy(a); if (b) (void)hipEventDestroy(b); }
 };
 
+// ---- gate functions ------------------------------------------------------------------------
+__global__ void gate_kernel(float *v, long long n, bool is_tanh)
+{
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) v[i] = rnnt::gate_act(v[i], is_tanh);
+}
+
 }  // namespace
 
 // Every e4m3 code through the conversion the bfloat16 mode with e4m3-stored weights uses, in
@@ -305,6 +314,20 @@ int rnnt_probe_e2m1_widening(float scale, uint16_t *bf16_out)
     PROBE_TRY(hipGetLastError());
     PROBE_TRY(hipMemcpy(bf16_out, dev, 4 * 256 * 2 * sizeof(uint16_t), hipMemcpyDeviceToHost));
     (void)hipFree(dev);
+    return RNNT_OK;
+}
+
+int rnnt_probe_gate(int32_t is_tanh, const float *x, int64_t n, float *out)
+{
+    if (!x || !out) return RNNT_ERR_NULL;
+    if (n < 1 || n > (int64_t)1 << 28) return RNNT_ERR_SHAPE;
+    float *dev = nullptr;
+    PROBE_TRY(hipMalloc(&dev, (size_t)n * sizeof(float)));
+    struct Free { float *p; ~Free() { (void)hipFree(p); } } guard{dev};
+    PROBE_TRY(hipMemcpy(dev, x, (size_t)n * sizeof(float), hipMemcpyHostToDevice));
+    hipLaunchKernelGGL(gate_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, nullptr, dev, (long long)n, is_tanh != 0);
+    PROBE_TRY(hipGetLastError());
+    PROBE_TRY(hipMemcpy(out, dev, (size_t)n * sizeof(float), hipMemcpyDeviceToHost));
     return RNNT_OK;
 }
 

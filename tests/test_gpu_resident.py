@@ -118,3 +118,15 @@ def test_the_default_lookahead_after_a_return_to_the_resident_kernel(pkg):  # no
         if lookahead is not None:
             assert stats["lookahead"] == lookahead and stats["n_teams"] == 16
     eng.close()
+
+
+@pytest.mark.parametrize("is_tanh", [False, True])
+def test_gates_pass_on_nan_and_saturate_at_infinity(pkg, is_tanh):  # noqa: F811
+    x = np.array([np.nan, -np.nan, np.inf, -np.inf, 1e30, -1e30, 0.0, -0.0], dtype=np.float32)
+    got = pkg.rnnt_probe_gate(is_tanh, x)
+    assert np.isnan(got[:2]).all()
+    if is_tanh:
+        assert got[2:].tolist() == [1.0, -1.0, 1.0, -1.0, 0.0, 0.0]
+    else:
+        assert got[2] == got[4] == 1.0 and got[6] == got[7] == 0.5
+        assert 0.0 <= got[3] <= 2e-35 and 0.0 <= got[5] <= 2e-35          # exp(-80), where the argument is limited
