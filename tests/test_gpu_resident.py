@@ -129,4 +129,24 @@ def test_gates_pass_on_nan_and_saturate_at_infinity(pkg, is_tanh):  # noqa: F811
         assert got[2:].tolist() == [1.0, -1.0, 1.0, -1.0, 0.0, 0.0]
     else:
         assert got[2] == got[4] == 1.0 and got[6] == got[7] == 0.5
-        assert 0.0 <= got[3] <= 2e-35 and 0.0 <= got[5] <= 2e-35          # exp(-80), where the argument is limited
+        assert 0.0 <= got[3] <= 2e-38 and 0.0 <= got[5] <= 2e-38          # exp(-87), where the argument is limited
+
+
+@pytest.mark.parametrize("is_tanh,ulps", [(False, 2.2), (True, 1.3)])
+def test_gates_against_64_bits(pkg, is_tanh, ulps):  # noqa: F811
+    """Every 31st float of magnitude 2^-33 to 87, both signs, and zero: within the bound that holds for all of them
+    (2.10 and 1.22 units in the last place, measured once over every float), and the sigmoid within 2e-38
+    below -87, where its argument is limited."""
+    top = int(np.float32(87.0).view(np.uint32))
+    bits = np.concatenate([np.arange(0x2F000000, top, 31, dtype=np.uint32), np.array([0, top], dtype=np.uint32)])
+    worst = 0.0
+    for part in np.array_split(np.concatenate([bits, bits | np.uint32(1 << 31)]), 8):
+        x = part.view(np.float32)
+        got, xd = pkg.rnnt_probe_gate(is_tanh, x).astype(np.float64), x.astype(np.float64)
+        want = np.tanh(xd) if is_tanh else 1.0 / (1.0 + np.exp(-xd))
+        ulp = np.ldexp(1.0, np.maximum(np.frexp(want)[1], -125) - 24)
+        worst = max(worst, float((np.abs(got - want) / ulp).max()))
+    assert worst <= ulps, worst
+    if not is_tanh:
+        low = np.linspace(-200.0, -87.0, 4096, dtype=np.float32)
+        assert np.abs(pkg.rnnt_probe_gate(False, low).astype(np.float64) - 1.0 / (1.0 + np.exp(-low.astype(np.float64)))).max() <= 2e-38
