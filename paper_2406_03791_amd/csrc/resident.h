@@ -14,6 +14,7 @@ constexpr int kResUnits = 20;             // LSTM units per work-group at most
 constexpr int kResSlots = 4;              // exchange slots per vector, used in turn
 constexpr int kResRows = 4;               // utterances a team decodes at the same time at most
 constexpr int kResSamples = 32;           // (utterance, frame) pairs per joint step at most
+constexpr int kResCalm = 16;              // joint steps after which a row's frames are halved, see the loop control
 constexpr int kResList = 128;             // utterances a team takes per launch at most
 
 // Size classes: the register arrays, LDS rows and exchange buffers have compile-time sizes, so the

@@ -61,7 +61,11 @@ constexpr unsigned kStop = 0xfffffffeu;    // to the helpers: the team is done
 // Rows in work: every wave keeps a copy of its own and takes the same decisions from the same
 // results, so loop control needs no work-group barrier.
 struct __align__(16) RRow { int t, len, n, cnt; };       // frame, frames, labels of this frame, labels; t >= len: idle
-struct RRows { RRow s[kResRows]; int b[kResRows], m[kResRows]; };   // utterance; t modulo the frames of a joint step
+struct RRows {
+    RRow s[kResRows];
+    int b[kResRows], m[kResRows];     // utterance; t modulo the frames of a joint step
+    int since[kResRows], next;        // t some steps ago; first utterance of the list that no row has had
+};
 
 struct RCtl {
     RRows rows[kResWaves];
@@ -140,6 +144,17 @@ __device__ __forceinline__ void put2(const RCtx &x, unsigned off, unsigned now, 
         __builtin_amdgcn_raw_buffer_store_b64(v, x.buf, (int)off, (int)now, 16);
         __builtin_amdgcn_raw_buffer_store_b64(mark, x.buf, (int)off, (int)old, 16);
     }
+}
+__device__ __forceinline__ void put_mark(const RCtx &x, unsigned off, unsigned old)
+{
+    if (x.local) __builtin_amdgcn_raw_buffer_store_b32(kMark, x.buf, (int)off, (int)old, 0);
+    else __builtin_amdgcn_raw_buffer_store_b32(kMark, x.buf, (int)off, (int)old, 16);
+}
+__device__ __forceinline__ void put_mark2(const RCtx &x, unsigned off, unsigned old)
+{
+    const r2u mark = {kMark, kMark};
+    if (x.local) __builtin_amdgcn_raw_buffer_store_b64(mark, x.buf, (int)off, (int)old, 0);
+    else __builtin_amdgcn_raw_buffer_store_b64(mark, x.buf, (int)off, (int)old, 16);
 }
 __device__ __forceinline__ void put_far(const RCtx &x, unsigned off, unsigned imm, unsigned v)
 {
@@ -356,6 +371,9 @@ __device__ __forceinline__ void cell(float pre, int j, float c_old, float &c_new
     h = o_ * gate_act(c_new, true);
 }
 
+// What the prediction step does with a row's candidate state: take it, or start afresh (else nothing).
+constexpr int kTake = 1 << 30, kFresh = (int)(1u << 31);
+
 #define RES_SLOT(n) ((unsigned)(n) & (kResSlots - 1))
 
 // Receives a vector of `rows` rows of n4 16-byte pieces each (rows row_bytes apart from byte `base`
@@ -436,6 +454,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     constexpr int W = res_width(CLS), ROW = res_row(CLS), TS = res_team(CLS), XROW = res_xrow(BF, CLS);
     constexpr int NI = res_joint_steps(CLS), PR = res_piece_regs(BF), LREGS = res_lstm_regs(BF, CLS);
     typedef Piece<BF> Pc;
+    constexpr bool HALVES = PAIR && NMT == 2;     // steps with one tile of samples as well, see after the loop
     constexpr int NREC = PAIR ? 0 : NL;          // recurrent matrices the chain's work-groups hold
     constexpr ResidentBuf bo = resident_buf(CLS);
     constexpr ResidentLds lo = resident_lds(KIND, BF, CLS, NMT);
@@ -490,7 +509,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     if (tid0 < kMaxDur) rc.dur[tid0] = p.durations[tid0];
     if (lane0 < kResRows) {
         RRows &w = rc.rows[x.wave];
-        w.s[lane0] = RRow{0, 0, 0, 0}; w.b[lane0] = w.m[lane0] = 0;
+        w.s[lane0] = RRow{0, 0, 0, 0}; w.b[lane0] = w.m[lane0] = w.since[lane0] = w.next = 0;
     }
     for (int i = tid0 * 16; i < lo.bytes; i += kResThreads * 16) *reinterpret_cast<r4u *>(lds + i) = (r4u){0, 0, 0, 0};
     // the marks have to be in memory before this work-group says that it is there
@@ -684,9 +703,29 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         return l;
     };
     // (joint output: a wave takes every eighth step of K for both column tiles)
-    const int la = p.la, ns = p.slots * la;
-    const unsigned inv_la = (1024u + (unsigned)la - 1u) / (unsigned)la;             // s / la for s < 32, la <= 16
-    auto row_of = [&](int s) { return (int)(((unsigned)s * inv_la) >> 10); };
+    // Frames per row and samples of a joint step with NT tiles of samples: p.la, or half of it with one tile instead
+    // of two.  (That is read and worked out anew, or it and all that follows from it takes scalar registers in the
+    // steps with two.)
+    struct Frames {
+        int la, ns;
+        unsigned inv_la, inv_t;
+        __device__ __forceinline__ int row_of(int s) const { return (int)(((unsigned)s * inv_la) >> 10); }      // s / la for s < 32, la <= 16
+        __device__ __forceinline__ int mod_la(int t) const { return t - (int)__umulhi((unsigned)t, inv_t) * la; }      // t % la for t < 2^24
+    };
+    auto frames_of = [&](auto nt_) {
+        Frames f;
+        if constexpr (HALVES) {
+            const Args a = args_again();
+            f.la = decltype(nt_)::value < NMT ? a->la >> 1 : a->la;
+            f.ns = a->slots * f.la;
+        } else {
+            f.la = p.la;
+            f.ns = p.slots * f.la;
+        }
+        f.inv_la = (1024u + (unsigned)f.la - 1u) / (unsigned)f.la;
+        f.inv_t = 0xffffffffu / (unsigned)f.la + 1u;
+        return f;
+    };
     constexpr int QS = ROW + 16;                     // floats per q row
     float *lq = reinterpret_cast<float *>(lds + lo.q);
     const unsigned lds_p = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)(lds + lo.p);
@@ -707,27 +746,28 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     unsigned n_pred = 0, n_joint = 0;
 
     RRows &rows = rc.rows[x.wave];
-    int next = 0;                     // first utterance of the list that no row has had
     int n_samples = 0, row_steps = 0;
     // What the loop control leaves for the steps: of the row that the lane finishes cells of, the last label
-    // and what the prediction step does with the candidate state (0 nothing, 1 take it, 2 start
-    // afresh); of sample `lane`, its row of the projected frames, -1 for none.
-    int last = p.blank, action = 2, pidx = -1;
+    // (and, in lane_const, what the prediction step does with the candidate state); of sample `lane`, its row
+    // of the projected frames, -1 for none.
+    int last = p.blank, pidx = -1;
     // What a lane needs of the loop control's tables, packed (a register each would be one too many): the
     // sample's row (2 bits) and place (4), its own row's first sample (5), the word of a row of T0 that
-    // its cell takes (12).
-    int lane_const;
-    {
-        const int srow = min(row_of(lane0 & (kResSamples - 1)), kResRows - 1), si = (lane0 - srow * la) & 15;
-        const Place l = place_of(lane0);
-        lane_const = srow | si << 2 | (l.row * la) << 6 | (l.gu * 4 + l.j) << 11;
-    }
+    // its cell takes (12); kTake and kFresh.
+    int lane_const = kFresh;
+    auto pack_lane = [&](const Frames &f, int lane) {
+        const int srow = min(f.row_of(lane & (kResSamples - 1)), kResRows - 1), si = (lane - srow * f.la) & 15;
+        const Place l = place_of(lane);
+        lane_const = srow | si << 2 | (l.row * f.la) << 6 | (l.gu * 4 + l.j) << 11 | (lane_const & (kTake | kFresh));
+    };
+    std::integral_constant<int, NMT> all_tiles;
+    const Frames f_all = frames_of(all_tiles);
+    pack_lane(f_all, lane0);
     // Samples of the next joint step: `la` frames of every row in work, frame f in the row's place f % la,
     // so that a frame stays where it is until the row has passed it.  fresh: the samples to load.
     unsigned long long fresh = 0;
-    const unsigned inv_t = 0xffffffffu / (unsigned)la + 1u;                         // t % la for t < 2^24
-    auto mod_la = [&](int t) { return t - (int)__umulhi((unsigned)t, inv_t) * la; };
-    auto set_up_samples = [&](int lane, int t, int m, int b, int len) {
+    auto set_up_samples = [&](const Frames &f, int lane, int t, int m, int b, int len) {
+        const int la = f.la, ns = f.ns;
         const int from = (lane_const & 3) << 4;                                     // (bytes: four lanes per row)
         const int base = __builtin_amdgcn_ds_bpermute(from, b * p.T + t);
         const int info = __builtin_amdgcn_ds_bpermute(from, max(0, min(len - t, la)) | m << 8);
@@ -743,10 +783,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     auto refill = [&](int lane, bool want, int &b, int &len) {
         const unsigned long long m = __ballot(want) & 0x1111ull;
         if (m == 0ull) return false;
-        const int at = next + __popcll(m & ((1ull << (lane & 12)) - 1ull));
+        const int next = rows.next, at = next + __popcll(m & ((1ull << (lane & 12)) - 1ull));
         const bool got = want && at < rc.n_list;
         if (got) { b = rc.list_b[at]; len = rc.list_len[at]; }
-        next += __popcll(m);
+        rows.next = next + __popcll(m);
         return got;
     };
     __syncthreads();                  // the list is complete
@@ -759,28 +799,37 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         const unsigned long long m = __ballot(got) & 0x1111ull;
         any_active = need_pred = m != 0ull;
         row_steps = __popcll(m);
-        set_up_samples(lane0, 0, 0, b, len);
+        set_up_samples(f_all, lane0, 0, 0, b, len);
     }
     // the row of the embedding table (folded into the first layer) that the next prediction step adds
     float t0 = 0.f;
     const unsigned t0_row = (unsigned)p.H * 16u;
     auto load_t0 = [&]() {
         t0 = 0.f;
-        if (has_cells) t0 = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(p.T0) + (__umul24((unsigned)last, t0_row) + ((unsigned)lane_const >> 11) * 4u));
+        if (has_cells) t0 = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(p.T0) + (__umul24((unsigned)last, t0_row) + ((unsigned)lane_const >> 9 & 0x3ffcu)));
     };
     // kResident2Pair: W_hh h of the last step's candidates as far as it is there, kMark where not
     unsigned pre[2] = {0u, 0u};
-    auto load_pre = [&](unsigned n) {
+    auto load_pre = [&](unsigned n, unsigned (&to)[2]) {
         const unsigned slot = bo.pre + RES_SLOT(n) * PSLOT;
 #pragma unroll
-        for (int l = 0; l < 2; ++l) pre[l] = !has_cells ? 0u : get1(x, prelane(), slot + (unsigned)l * kResSlots * PSLOT);
+        for (int l = 0; l < 2; ++l) to[l] = !has_cells ? 0u : get1(x, prelane(), slot + (unsigned)l * kResSlots * PSLOT);
     };
     if (need_pred) load_t0();
 #ifdef RNNT_PROFILE
     if (tid0 == 0) { for (int i = 0; i < 24; ++i) res_prof[i] = 0; res_prof_last = wall_clock64(); }
 #endif
 
-    while (ok && any_active) {
+    // Steps with NT tiles of samples: until the team is done, or the other number of tiles suits its rows better.
+    auto steps = [&](auto nt_) {
+    constexpr int NT = decltype(nt_)::value;
+    const Frames f = HALVES ? frames_of(nt_) : f_all;
+    const int la = f.la, ns = f.ns;
+    bool change = false;
+    // (Two teams of short steps keep their helpers busy: half the results come after the control's start has
+    // asked for them, and one more round trip costs 1.3 us; asked for again at its end, 0.16 us a step less.)
+    unsigned later[2] = {kMark, kMark};
+    while (ok && any_active && !change) {
         if (!need_pred)
             for (int s = x.wave; s < ns; s += kResWaves)
                 if (fresh >> s & 1) load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
@@ -790,9 +839,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             const unsigned n = n_pred;
             if (PAIR && n > 1) {
                 unsigned spins = 0;
+                if (NT < NMT && __ballot(pre[0] == kMark || pre[1] == kMark) != 0ull) { pre[0] = later[0]; pre[1] = later[1]; }
                 while (__ballot(pre[0] == kMark || pre[1] == kMark) != 0ull) {
                     if (wait_expired(p, spins)) { rc.ok = 0; break; }
-                    load_pre(n - 1);
+                    load_pre(n - 1, pre);
                 }
                 x.polls += __builtin_amdgcn_readfirstlane((int)spins);
             }
@@ -803,7 +853,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 float pc = 0.f;
                 if (PAIR) pc = __uint_as_float(pre[l]);
                 else if (has_cells) pc = stage_sum(l == NL - 1 ? sums_rec2 : sums_rec, x.wave, lane_id());
-                const bool take = action & 1, fresh_row = action & 2;       // (bits: as a chain of comparisons it became branches)
+                const bool take = lane_const & kTake, fresh_row = lane_const & kFresh;       // (bits: as a chain of comparisons it became branches)
                 cs[l] = take ? cc[l] : cs[l]; cs[l] = fresh_row ? 0.f : cs[l];
                 ps[l] = take ? pc : ps[l]; ps[l] = fresh_row ? 0.f : ps[l];
             };
@@ -875,9 +925,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 // four adjacent threads per value (group, column, row), two waves' sums each
                 const int tid = (x.wave * 64 + lane_id()), g = tid >> 6, j = (tid >> 4) & 3, r = (tid >> 2) & 3;
                 if (g < njg) {
-                    const float *f = g4 + ((tid & 3) * 120 + g * 4 + j) * 4 + r;
+                    const float *v = g4 + ((tid & 3) * 120 + g * 4 + j) * 4 + r;
                     const float bias = rc.bp[g * 4 + j];
-                    const float s = lane_sum<4>(((f[0] + f[80]) + f[160]) + ((f[240] + f[320]) + f[400]));
+                    const float s = lane_sum<4>(((v[0] + v[80]) + v[160]) + ((v[240] + v[320]) + v[400]));
                     if ((tid & 3) == 0 && r < p.slots)
                         put(x, (unsigned)r * VROW + (unsigned)((g0 + g) * 4 + j) * 4u, bo.q + RES_SLOT(n) * VSLOT, bo.q + RES_SLOT(n + 2) * VSLOT, word_of(s + bias));
                 }
@@ -898,7 +948,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         __syncthreads();
         RES_MARK(10);
         {
-            r4f acc[NMT][2];                 // [tile of samples][column tile]
+            r4f acc[NT][2];                 // [tile of samples][column tile]
             const int lane = lane_id(), m16 = lane & 15, kq = lane >> 4;
             // Piece k4 = 32 ii + 4 wave + kq of sample m16: its low bits are the same for all steps.  The operand
             // relu(P + q) is formed on the way: K is split over the waves, so nobody else needs it.  The
@@ -906,11 +956,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             // the vector pipe with them, and every change between the two costs some ten cycles.
             const int k40 = x.wave * 4 + kq;
             const unsigned char *pr = lds + lo.p + m16 * ROW * 4 + ((k40 & 16) | ((k40 ^ m16) & 15)) * 16;
-            const float *q[NMT];
+            const float *q[NT];
 #pragma unroll
-            for (int mt = 0; mt < NMT; ++mt) {
+            for (int mt = 0; mt < NT; ++mt) {
                 acc[mt][0] = acc[mt][1] = (r4f){0.f, 0.f, 0.f, 0.f};
-                q[mt] = lq + min(row_of(mt * 16 + m16), kResRows - 1) * QS + k40 * 4;
+                q[mt] = lq + min(f.row_of(mt * 16 + m16), kResRows - 1) * QS + k40 * 4;
             }
             auto fetch = [&](int ii, int mt, float4 &pv, float4 &qv) {
                 pv = *reinterpret_cast<const float4 *>(pr + mt * 16 * ROW * 4 + ii * 512);
@@ -925,11 +975,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 const unsigned char *wt = lds + lo.tail + k40 * 8;
                 r4f tacc = (r4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i = 0; i < NI * NMT; ++i) {
-                    const int ii = i / NMT, mt = i % NMT;
+                for (int i = 0; i < NI * NT; ++i) {
+                    const int ii = i / NT, mt = i % NT;
                     const r4s z = __builtin_bit_cast(r4s, U{bf16_pair(fmaxf(pv.x + qv.x, 0.f), fmaxf(pv.y + qv.y, 0.f)),
                                                             bf16_pair(fmaxf(pv.z + qv.z, 0.f), fmaxf(pv.w + qv.w, 0.f))});
-                    if (i + 1 < NI * NMT) fetch((i + 1) / NMT, (i + 1) % NMT, pv, qv);
+                    if (i + 1 < NI * NT) fetch((i + 1) / NT, (i + 1) % NT, pv, qv);
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int c = 0; c < 2; ++c) {
@@ -941,23 +991,23 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 }
                 if (has_tail) {
 #pragma unroll
-                    for (int mt = 0; mt < NMT; ++mt)
+                    for (int mt = 0; mt < NT; ++mt)
                         if (kq == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = tacc[mt];
                 }
             } else {
                 const float *wt = reinterpret_cast<const float *>(lds + lo.tail) + k40 * 4;
-                float tl[NMT];
+                float tl[NT];
 #pragma unroll
-                for (int mt = 0; mt < NMT; ++mt) tl[mt] = 0.f;
-                float4 wv = *reinterpret_cast<const float4 *>(wt), pv[NMT], qv[NMT];
+                for (int mt = 0; mt < NT; ++mt) tl[mt] = 0.f;
+                float4 wv = *reinterpret_cast<const float4 *>(wt), pv[NT], qv[NT];
 #pragma unroll
-                for (int mt = 0; mt < NMT; ++mt) fetch(0, mt, pv[mt], qv[mt]);
+                for (int mt = 0; mt < NT; ++mt) fetch(0, mt, pv[mt], qv[mt]);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int ii = 0; ii < NI; ++ii) {
-                    float z[NMT][4];
+                    float z[NT][4];
 #pragma unroll
-                    for (int mt = 0; mt < NMT; ++mt) {
+                    for (int mt = 0; mt < NT; ++mt) {
                         z[mt][0] = fmaxf(pv[mt].x + qv[mt].x, 0.f); z[mt][1] = fmaxf(pv[mt].y + qv[mt].y, 0.f);
                         z[mt][2] = fmaxf(pv[mt].z + qv[mt].z, 0.f); z[mt][3] = fmaxf(pv[mt].w + qv[mt].w, 0.f);
                         tl[mt] = fmaf(z[mt][3], wv.w, fmaf(z[mt][2], wv.z, fmaf(z[mt][1], wv.y, fmaf(z[mt][0], wv.x, tl[mt]))));
@@ -967,14 +1017,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     }
                     if (ii + 1 < NI) {
 #pragma unroll
-                        for (int mt = 0; mt < NMT; ++mt) fetch(ii + 1, mt, pv[mt], qv[mt]);
+                        for (int mt = 0; mt < NT; ++mt) fetch(ii + 1, mt, pv[mt], qv[mt]);
                         wv = *reinterpret_cast<const float4 *>(wt + (ii + 1) * 128);
                     }
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
 #pragma unroll
-                        for (int mt = 0; mt < NMT; ++mt)
+                        for (int mt = 0; mt < NT; ++mt)
 #pragma unroll
                             for (int c = 0; c < 2; ++c)
                                 acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w_ou.w[(ii * 2 + c) * 4 + e], z[mt][e], acc[mt][c], 0, 0, 0);
@@ -982,7 +1032,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 }
                 if (has_tail) {
 #pragma unroll
-                    for (int mt = 0; mt < NMT; ++mt) {
+                    for (int mt = 0; mt < NT; ++mt) {
                         float a = tl[mt], b = tl[mt];
                         swap32(a, b); a += b; b = a;
                         swap16(a, b); a += b;
@@ -993,18 +1043,18 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             RES_MARK(11);
             // every wave's sums to LDS, [wave][sample][column]; then sixteen lanes per sample, two columns each
 #pragma unroll
-            for (int mt = 0; mt < NMT; ++mt)
+            for (int mt = 0; mt < NT; ++mt)
 #pragma unroll
                 for (int c = 0; c < 2; ++c)
-                    *reinterpret_cast<r4f *>(part + ((x.wave * NMT + mt) * 16 + m16) * kResSumRow + c * 16 + kq * 4) = acc[mt][c];
+                    *reinterpret_cast<r4f *>(part + ((x.wave * NT + mt) * 16 + m16) * kResSumRow + c * 16 + kq * 4) = acc[mt][c];
             __syncthreads();
             const int tid = (x.wave * 64 + lane_id());
-            if (tid < 16 * NMT * 16) {
+            if (tid < 16 * NT * 16) {
                 const int s = tid >> 4, col = (tid & 15) * 2, gcol = x.rank * 32 + col;
                 float2 o[kResWaves];
 #pragma unroll
                 for (int w = 0; w < kResWaves; ++w)
-                    o[w] = *reinterpret_cast<const float2 *>(part + (w * NMT * 16 + s) * kResSumRow + col);
+                    o[w] = *reinterpret_cast<const float2 *>(part + (w * NT * 16 + s) * kResSumRow + col);
                 const float2 bias = *reinterpret_cast<const float2 *>(&rc.bo[col]);
                 static_assert(kResWaves == 8, "eight lanes add the waves' sums of the tail column");
                 float tw = 0.f;
@@ -1052,12 +1102,30 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 }
             }
         }
+        if constexpr (NT < NMT) {
+            // the samples that this step does not have: the marks that their words of step jn + 2 need
+            const int tid = x.wave * 64 + lane_id(), s = tid >> 4;
+            if (s >= ns && s < ns * 2) {
+                const int gcol = x.rank * 32 + (tid & 15) * 2;
+                const unsigned ko = ((unsigned)s * TS + (unsigned)x.rank) * 8u, ds = (unsigned)s * kMaxDur * 4u;
+                const bool lead = (tid & 15) == 0;
+                if (lead) put_mark2(x, ko, bo.key + RES_SLOT(jn + 2) * KSLOT);
+                if (lead && p.logps) put_mark(x, ko / 2, bo.lse + RES_SLOT(jn + 2) * (KSLOT / 2));
+                if (lead && has_tail && tcol >= p.VT) put_mark(x, ds + (unsigned)(tcol - p.VT) * 4u, bo.dur + RES_SLOT(jn + 2) * DSLOT);
+                if (dur_cols) {
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+                        if (gcol + c >= p.VT && gcol + c < p.pl.nout_m)
+                            put_mark(x, ds + (unsigned)(gcol + c - p.VT) * 4u, bo.dur + RES_SLOT(jn + 2) * DSLOT);
+                }
+            }
+        }
         RES_MARK(12);
         // ---- argmax over the team: TS / 2 adjacent lanes per sample, two candidates per lane --------
         {
             const int tid = (x.wave * 64 + lane_id()), lane = tid & 63;
             constexpr int L = TS / 2;
-            static_assert(16 * NMT * L <= kResThreads, "one piece per thread");
+            static_assert(16 * NT * L <= kResThreads, "one piece per thread");
             const int s = tid / L;
             if ((x.wave * 64) / L < ns) {
                 const unsigned off[1] = {(unsigned)min(tid, ns * L - 1) * 16u};
@@ -1131,7 +1199,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             int b = rows.b[r], m = rows.m[r];
             __syncthreads();
             RES_MARK(14);
-            if (PAIR) load_pre(n_pred);       // (on its way during the rest)
+            if (PAIR) load_pre(n_pred, pre);       // (on its way during the rest)
             const int mine = rc.s_k[lane & (kResSamples - 1)], row0 = (lane_const >> 6) & 31, left = w.len - w.t;
             const bool lead = lane < 16 && (lane & 3) == 0;     // stands for its row
             const bool writer = x.rank == 0 && x.wave == kResWaves - 1 && lead;
@@ -1194,9 +1262,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             }
             w.t += adv;
             const bool ended = left > 0 && adv >= left;
-            action = found && !ended ? 1 : 0;
+            int action = found && !ended ? kTake : 0;
             if (walk) {
-                m = mod_la(w.t);
+                m = f.mod_la(w.t);
             } else {
                 m += adv;                               // (at most la + 1)
                 if (m >= la) m -= la;
@@ -1205,20 +1273,67 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             if (__ballot(ended) != 0ull) {
                 if (writer && ended) res_finish_row(b, w.cnt);
                 const bool got = refill(lane, ended, b, w.len);
-                if (got) { w.t = w.n = w.cnt = m = 0; action = 2; last = p.blank; }
+                if (got) { w.t = w.n = w.cnt = m = 0; action = kFresh; last = p.blank; }
                 if (lead) rows.b[r] = b;
                 load_t0();
             }
+            lane_const = (lane_const & ~(kTake | kFresh)) | action;
             if (lead) { rows.s[r] = w; rows.m[r] = m; }
 
             const unsigned long long moved = __ballot(action != 0) & 0x1111ull;      // rows whose next step has new inputs
             any_active = __ballot(w.t < w.len) != 0ull;
             need_pred = moved != 0ull;
             row_steps += __popcll(moved);
-            set_up_samples(lane, w.t, m, b, w.len);
+            if constexpr (HALVES && NT == NMT) {
+                // every so many steps: have all rows in work gone on by less than one and a half frames a step?
+                // (No lane condition around the store: `change` would count as different from lane to lane.)
+                if ((jn & (kResCalm - 1)) == 0) {
+                    const int from = rows.since[r], on = w.t < from ? w.t : w.t - from;
+                    change = __ballot(w.t < w.len && on > kResCalm * 3 / 2) == 0ull;
+                    rows.since[r] = w.t;
+                }
+            }
+            if constexpr (NT < NMT) change = __ballot(left > 0 && !found && !ended) != 0ull;      // a row's next label is further away
+            if (!change) set_up_samples(f, lane, w.t, m, b, w.len);
+            if (PAIR && NT < NMT) load_pre(n_pred, later);
         }
         ok = rc.ok != 0;
         RES_MARK(15);
+    }
+    };
+    if constexpr (!HALVES) {
+        steps(all_tiles);
+    } else {
+        // Where the rows go on by less than one and a half frames a step (ten labels on every frame, say), the second
+        // tile of samples is computed for nothing: then the team goes on with half the frames per row, until
+        // a row's next label is not among them.  128 utterances of ten labels on every frame: 9.7 us a step with two
+        // tiles, 8.8 with one (136.4 and 123.6 ms a call; the streaming kernel: 125.8), and with ten labels on every
+        // other frame 68.5 and 61.7 ms (62.7).  At 0.7 labels a frame the two are even; below, a team hardly ever
+        // gets here, and what looking out for it costs is within 0.6 % of a call.
+        // Two-layer fp32 models only: the others were faster than the streaming kernel on such input as well, and
+        // their second loop costs more registers than there are (bfloat16 mode: twelve spilled, 4 to 6 % of a call).
+        std::integral_constant<int, 1> one_tile;
+        auto changed_to = [&](auto nt_) {
+            const int lane = lane_id(), r = (lane >> 2) & 3;
+            const RRow w = rows.s[r];
+            const Frames f = frames_of(nt_);
+            const int m = f.mod_la(w.t);
+            pack_lane(f, lane);
+            if (lane < 16 && (lane & 3) == 0) {
+                rows.m[r] = m;
+                rows.since[r] = -0x10000000;      // (not after less than kResCalm steps)
+            }
+            pidx = -1;                // every frame has another place
+            set_up_samples(f, lane, w.t, m, rows.b[r], w.len);
+        };
+        for (;;) {
+            steps(all_tiles);
+            if (!ok || !any_active) break;
+            changed_to(one_tile);
+            steps(one_tile);
+            if (!ok || !any_active) break;
+            changed_to(all_tiles);
+        }
     }
     __syncthreads();
     if (PAIR && rc.ok) {

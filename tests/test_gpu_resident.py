@@ -150,3 +150,39 @@ def test_gates_against_64_bits(pkg, is_tanh, ulps):  # noqa: F811
     if not is_tanh:
         low = np.linspace(-200.0, -87.0, 4096, dtype=np.float32)
         assert np.abs(pkg.rnnt_probe_gate(False, low).astype(np.float64) - 1.0 / (1.0 + np.exp(-low.astype(np.float64)))).max() <= 2e-38
+
+
+@pytest.mark.parametrize("B", [15, 20])
+@pytest.mark.parametrize("extra", [{}, dict(durations=(0, 1)), dict(big_blanks=(2, 5))])
+def test_label_dense_and_sparse_stretches(pkg, B, extra):  # noqa: F811
+    """Rows of 25 frames with up to four labels each, then 25 blank ones, at different times: teams of three and
+    four rows change to half the frames per row and back."""
+    dims = synth.ModelDims(F=336, E=24, H=324, L=2, J=332, V1=530, durations=extra.get("durations", ()),
+                           big_blanks=extra.get("big_blanks", ()))
+    model = synth.make_model(dims, B, weight_range=0.15, emb_gain=4.0, pred_gain=3.0, blank_bias=-1.0)
+    # a frame that drives the blank's logit up, whatever the prediction side adds
+    want = 60.0 * np.maximum(model.w_out[dims.blank].astype(np.float64), 0.0) - model.b_enc
+    blank = np.linalg.lstsq(model.w_enc.astype(np.float64), want, rcond=None)[0].astype(np.float32)
+    x, ln = synth.make_inputs(B, B, 100, dims.F, 50, 100)
+    t, b = np.arange(100)[None, :], np.arange(B)[:, None]
+    x = np.where(((t + 5 * b) // 25 % 2 == 0)[:, :, None], x, blank[None, None]).astype(np.float32)
+    w = synth.Workload("dense and sparse", "tdt" if dims.D else "label", model, x, ln, 4)
+    eng = pkg.Engine(w.model, w.B, w.T)
+    ref, _, stats = check(pkg, w, w.variant, f"dense and sparse {B} {extra}", engine=eng, logp=True)
+    eng.close()
+    # what a team that never changes examines: `la` frames of every row at every step, as far as it has them
+    la, full = stats["lookahead"], 0
+    for i in range(B):
+        at, n, k, frames, length = 0, 0, 0, ref.frames[i], int(ln[i])
+        while at < length:
+            full += min(la, length - at)
+            if k == len(frames) or frames[k] >= at + la:
+                at, n = at + la, 0
+                continue
+            n = n if frames[k] == at else 0
+            at, n, move = int(frames[k]), n + 1, int(ref.durs[i][k])
+            if move > 0 or n == w.max_symbols:
+                at, n = at + max(move, 1), 0
+            k += 1
+    print(f"samples {stats['joint_samples']}, without changes {full}", flush=True)
+    assert stats["joint_samples"] < 0.95 * full
