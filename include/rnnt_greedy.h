@@ -23,6 +23,18 @@
  *     same engine must be ordered by the caller (same stream or events).  A
  *     decode launch occupies every compute unit, so calls of different engines
  *     gain nothing from running on different streams; order them too.
+ *   - The work-groups of a decode wait for each other, so all of them have to be
+ *     on the device at once: two decodes that each got a part of it would wait
+ *     until their limit (rnnt_engine_set_wait_limit) and end with
+ *     RNNT_DEV_ABORTED.  The library orders the decodes that it enqueues on a
+ *     device, whatever their engines, streams and threads.  It cannot order
+ *     what it does not enqueue: decodes of another process on the same device
+ *     (several workers per GPU), of a second copy of the library, or of a
+ *     replayed HIP graph.  A caller who may have those beside decodes of this
+ *     library creates all engines with RNNT_FLAG_COOPERATIVE_LAUNCH: the runtime
+ *     then runs such launches of one process one after another, and refuses
+ *     those of a second process (RNNT_ERR_HIP from the decode call) while the
+ *     first one lives.  Decodes of two processes never run side by side.
  *   - Return value: RNNT_OK (0) or a negative RNNT_ERR_* code, detected on the
  *     host before anything is queued.  Conditions only the device can see are
  *     reported through rnnt_engine_status().
@@ -214,17 +226,29 @@ int rnnt_quantize_blocks_e2m1(const float *w, int64_t rows, int64_t cols, float 
  * rnnt_engine_create flag: launch the decode kernel with an ordinary launch
  * instead of a cooperative one.  The kernel's teams synchronise among
  * themselves, which needs all work-groups resident at once.  The library orders
- * the decodes of a device one after another, whatever their streams and
- * threads, so an ordinary launch of one work-group per compute unit gets there
- * as other kernels end (every wait in the kernel is bounded, so a call that
- * does not ends with RNNT_DEV_ABORTED instead of hanging).  The kernel with
- * register-resident weights is always launched that way (except into a stream
- * capture); the flag is for the other one, in
- * profiling runs: a process that has run a cooperative
- * launch under rocprofv3's kernel trace has been seen to crash in its exit
- * handlers.  May be combined with a storage flag.
+ * its decodes of a device one after another, whatever their streams and threads
+ * (see the conventions above for what it cannot order), so an ordinary launch
+ * of one work-group per compute unit gets there as other kernels end (every
+ * wait in the kernel is bounded, so a call that does not ends with
+ * RNNT_DEV_ABORTED instead of hanging).  The kernel with register-resident
+ * weights is always launched that way (except into a stream capture, or with
+ * RNNT_FLAG_COOPERATIVE_LAUNCH); the flag is for the other one, in profiling
+ * runs: a process that has run a cooperative launch under rocprofv3's kernel
+ * trace has been seen to crash in its exit handlers.  May be combined with a
+ * storage flag.
  */
 #define RNNT_FLAG_PLAIN_LAUNCH 4
+
+/*
+ * rnnt_engine_create flag: every decode kernel of the engine is launched
+ * cooperatively, so that the runtime, which admits such a launch only as a
+ * whole, keeps it apart from cooperative launches that this library does not
+ * enqueue, or refuses it (see the conventions above).  Costs 17 to 55 microseconds a call
+ * of a model with register-resident weights; the streaming kernel is launched
+ * that way in any case.  Excludes RNNT_FLAG_PLAIN_LAUNCH (RNNT_ERR_SHAPE); may
+ * be combined with the other flags.
+ */
+#define RNNT_FLAG_COOPERATIVE_LAUNCH 128
 
 /*
  * RNNT_FLAG_MULTI_BLANK: the model is a multi-blank transducer (the paper's
@@ -251,8 +275,8 @@ int rnnt_quantize_blocks_e2m1(const float *w, int64_t rows, int64_t cols, float 
  * flags: 0 or one of RNNT_FLAG_BF16_WEIGHTS / RNNT_FLAG_FP8_WEIGHTS /
  * RNNT_FLAG_BF16_ARITHMETIC (or the last with RNNT_FLAG_FP8_WEIGHTS or
  * RNNT_FLAG_FP4_WEIGHTS), optionally with
- * RNNT_FLAG_PLAIN_LAUNCH and RNNT_FLAG_MULTI_BLANK; other bits are
- * RNNT_ERR_SHAPE.
+ * RNNT_FLAG_PLAIN_LAUNCH or RNNT_FLAG_COOPERATIVE_LAUNCH and
+ * RNNT_FLAG_MULTI_BLANK; other bits are RNNT_ERR_SHAPE.
  * Limits of this implementation, checked here before anything is allocated
  * (RNNT_ERR_UNSUPPORTED): F must be a multiple of 16 (K tile of the projection
  * GEMM); H and J multiples of 4 (rows are read 16 bytes at a time); V1 + D at

@@ -34,6 +34,7 @@ RNNT_FLAG_PLAIN_LAUNCH = 4
 RNNT_FLAG_BF16_ARITHMETIC = 8
 RNNT_FLAG_MULTI_BLANK = 16
 RNNT_FLAG_FP4_WEIGHTS = 32
+RNNT_FLAG_COOPERATIVE_LAUNCH = 128
 RNNT_FP4_BLOCK = 128
 
 

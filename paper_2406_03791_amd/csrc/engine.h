@@ -116,10 +116,12 @@ int hip_fail(hipError_t e, const char *what);
 
 // Decode kernels of one device run one after another, whatever their streams: the work-groups of a
 // decode wait for each other, so two of them that each had a part of the compute units would wait
-// forever.  A cooperative launch orders itself behind the other cooperative ones, at 18 us a call
-// (one short utterance: 174 against 156 us); here every decode records an event after itself and waits for
-// that of the one before, which costs nothing on the same stream.  `enqueue` launches the kernels
-// (plain: it may launch them ordinarily).  In a stream capture, where an event from outside cannot be
+// forever.  A cooperative launch orders itself behind the other cooperative ones of the process, at 17 to
+// 55 us a call (one short utterance of a tiny model: 170 against 117 us); here every decode records an event
+// after itself and waits for that of the one before, which costs nothing on the same stream, and holds for the
+// decodes that one copy of this library enqueues.  (RNNT_FLAG_COOPERATIVE_LAUNCH: for callers who have others; of
+// two processes with cooperative launches the runtime refused the second one's, "operation cannot be performed in the
+// present state".)  `enqueue` launches the kernels (plain: it may launch them ordinarily).  In a stream capture, where an event from outside cannot be
 // waited for, the launches stay cooperative.
 constexpr int kDevices = 64;
 struct LaunchOrder { std::mutex m; hipEvent_t last = nullptr; bool used = false; };

@@ -139,6 +139,7 @@ struct rnnt_engine {
     int search_steps = 0;  // 0: chosen per call, -1: no limit, > 0: as given
     int wt = kWeightF32;   // storage of the packed (streamed) weights
     bool plain_launch = false;   // RNNT_FLAG_PLAIN_LAUNCH
+    bool coop_launch = false;    // RNNT_FLAG_COOPERATIVE_LAUNCH
     bool multi_blank = false;    // RNNT_FLAG_MULTI_BLANK: the D extra output columns are big blanks
     float *logp_out = nullptr;   // caller's [B, cap] buffer for log-probabilities, or none
     int32_t *done = nullptr;     // caller's [B] completion flags, or none
@@ -633,7 +634,7 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
             p.form = ws.form; p.abort_flag = ws.abort_flag; p.status = ws.status; p.stats = ws.stats;
             p.zero_stats = off == 0;
             p.count_rows = variant == kFrameLooping;
-            HIP_TRY(launch_resident(p, p.slots * p.la <= 16 ? 1 : 2, plain || e->plain_launch, stream));
+            HIP_TRY(launch_resident(p, p.slots * p.la <= 16 ? 1 : 2, (plain && !e->coop_launch) || e->plain_launch, stream));
         }
         return RNNT_OK;
     });
@@ -743,8 +744,9 @@ int rnnt_engine_create(const rnnt_model_desc *desc, int32_t max_B, int32_t max_T
 {
     if (!desc || !out) return RNNT_ERR_NULL;
     if (flags & ~(RNNT_FLAG_BF16_WEIGHTS | RNNT_FLAG_FP8_WEIGHTS | RNNT_FLAG_PLAIN_LAUNCH | RNNT_FLAG_BF16_ARITHMETIC |
-                  RNNT_FLAG_MULTI_BLANK | RNNT_FLAG_FP4_WEIGHTS))
+                  RNNT_FLAG_MULTI_BLANK | RNNT_FLAG_FP4_WEIGHTS | RNNT_FLAG_COOPERATIVE_LAUNCH))
         return RNNT_ERR_SHAPE;
+    if ((flags & RNNT_FLAG_PLAIN_LAUNCH) && (flags & RNNT_FLAG_COOPERATIVE_LAUNCH)) return RNNT_ERR_SHAPE;
     {   // at most one of the three formats, or the bfloat16 mode with e4m3- or e2m1-stored weights
         const int fmt = flags & (RNNT_FLAG_BF16_WEIGHTS | RNNT_FLAG_FP8_WEIGHTS | RNNT_FLAG_BF16_ARITHMETIC |
                                  RNNT_FLAG_FP4_WEIGHTS);
@@ -794,6 +796,7 @@ int rnnt_engine_create(const rnnt_model_desc *desc, int32_t max_B, int32_t max_T
         e->wt = (flags & RNNT_FLAG_FP8_WEIGHTS) ? kWeightFp8Bf16Arith
                                                 : ((flags & RNNT_FLAG_FP4_WEIGHTS) ? kWeightFp4Bf16Arith : kWeightBf16Arith);
     e->plain_launch = (flags & RNNT_FLAG_PLAIN_LAUNCH) != 0;
+    e->coop_launch = (flags & RNNT_FLAG_COOPERATIVE_LAUNCH) != 0;
     e->multi_blank = multi_blank;
     e->n_wg = (prop.multiProcessorCount / 32) * 32;   // every layout divides it
     if (e->n_wg < 32) return RNNT_ERR_UNSUPPORTED;

@@ -85,6 +85,7 @@ def test_create_refuses_unsupported_shapes_before_touching_the_device():
     assert create(flags=32) == -2                                    # 4-bit weights without the bfloat16 mode
     assert create(flags=pkg.RNNT_FLAG_BF16_ARITHMETIC | pkg.RNNT_FLAG_BF16_WEIGHTS) == -2
     assert create(flags=pkg.RNNT_FLAG_BF16_WEIGHTS | pkg.RNNT_FLAG_FP8_WEIGHTS) == -2
+    assert create(flags=pkg.RNNT_FLAG_PLAIN_LAUNCH | pkg.RNNT_FLAG_COOPERATIVE_LAUNCH) == -2
     # multi-blank: needs big blanks, each spanning at least one frame
     assert create(flags=pkg.RNNT_FLAG_MULTI_BLANK) == -2
     assert create(flags=pkg.RNNT_FLAG_MULTI_BLANK, D=2) == -2         # the test's spans start at 0

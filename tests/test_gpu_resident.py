@@ -83,6 +83,19 @@ def test_two_threads_on_streams_of_their_own(pkg):  # noqa: F811
         eng.close()
 
 
+def test_cooperative_launches_on_request(pkg):  # noqa: F811
+    """Engines of either kernel that launch cooperatively, beside one that does not."""
+    for L in (1, 2, 3):
+        w = model_inputs(324, 332, 530, L, B=33, T=12, seed=50 + L)
+        coop = pkg.Engine(w.model, w.B, w.T, flags=pkg.RNNT_FLAG_COOPERATIVE_LAUNCH)
+        plain = pkg.Engine(w.model, w.B, w.T)
+        for v in ("label", "frame", "label_noalloc"):
+            check(pkg, w, v, f"cooperative {L}", engine=coop)
+            check(pkg, w, v, f"ordinary {L}", engine=plain)
+        coop.close()
+        plain.close()
+
+
 @pytest.mark.parametrize("L", [2, 3])
 def test_a_refused_configuration_changes_nothing(pkg, L):  # noqa: F811
     """A fresh engine, and one with a layout and a lookahead of its own, decode after a refused
