@@ -35,10 +35,23 @@ def pkg():
 _ENGINES = {}
 
 
-def engine_for(pkg, key, model, max_B, max_T):
-    k = (key, max_B, max_T)
+# Models of one or two layers have two decode kernels: the one with register-resident weights, which
+# runs them unless rnnt_engine_configure asked for something, and the streaming one.
+both_kernels = pytest.mark.parametrize("kernel", ["streaming", "resident"])
+
+
+def moved_to(kernel, eng):
+    """The engine, moved to the streaming kernel in its default layouts and lookaheads by a search limit
+    that no default layout has by itself (2) and that changes no token."""
+    if kernel == "streaming":
+        eng.configure(search_steps=2)
+    return eng
+
+
+def engine_for(pkg, key, model, max_B, max_T, kernel="default"):
+    k = (key, max_B, max_T, kernel)
     if k not in _ENGINES:
-        _ENGINES[k] = pkg.Engine(model, max_B, max_T)
+        _ENGINES[k] = moved_to(kernel, pkg.Engine(model, max_B, max_T))
     return _ENGINES[k]
 
 
@@ -57,9 +70,9 @@ def run_gpu(eng, w, variant, S, cap=None, pad_nan=True, logp=False):
 
 
 def check(pkg, w, variant, key, S=None, max_B=None, engine=None, expect_status=0, logp=False,
-          bf16=False):
+          bf16=False, kernel="default"):
     S = w.max_symbols if S is None else S
-    eng = engine or engine_for(pkg, key, w.model, max_B or w.B, w.T)
+    eng = engine or engine_for(pkg, key, w.model, max_B or w.B, w.T, kernel)
     net = oracle.LstmNet(w.model, bf16=bf16)
     ref = oracle.decode(net, w.enc_out, w.enc_len, S, "seq", n_threads=N_THREADS)
     got, status, stats = run_gpu(eng, w, variant, S, logp=logp)
@@ -67,6 +80,9 @@ def check(pkg, w, variant, key, S=None, max_B=None, engine=None, expect_status=0
         f"status={status} stats={stats}")
     assert status == expect_status
     assert stats["xcd_mismatch"] == 0
+    # (Algorithm 1 has no label search; the resident kernel always goes on after one joint step)
+    if kernel != "default":
+        assert stats["search_steps"] == {"resident": 1, "streaming": 0 if variant == "frame" else 2}[kernel]
     if bf16:
         ties = compare(w, net, ref, got, S, margin=BF16_MARGIN, logit_rtol=BF16_LOGIT_RTOL)
     else:
@@ -426,14 +442,15 @@ def test_adversarial_batches(pkg):
             assert [len(t) for t in got["tokens"]] == want.tolist()
 
 
-def test_finished_utterances_are_flagged_while_the_call_runs(pkg):
+@both_kernels
+def test_finished_utterances_are_flagged_while_the_call_runs(pkg, kernel):
     # Row 0 emits max_symbols labels on every frame, the other rows only blanks: their
     # results must be readable from pinned host memory, and right, long before row 0 is done.
     import time
     w = synth.make_adversarial("one_slow_row", cfg=2, B=8, T=60)
     net = oracle.LstmNet(w.model)
     ref = oracle.decode(net, w.enc_out, w.enc_len, w.max_symbols, "seq", n_threads=N_THREADS)
-    eng = engine_for(pkg, "parakeet_slow_row", w.model, w.B, w.T)
+    eng = engine_for(pkg, "parakeet_slow_row", w.model, w.B, w.T, kernel)
     enc = torch.from_numpy(w.enc_out).cuda()
     ln = torch.from_numpy(w.enc_len).cuda()
     cap = w.T * w.max_symbols
@@ -463,14 +480,16 @@ def test_finished_utterances_are_flagged_while_the_call_runs(pkg):
         for b in range(w.B):
             assert np.array_equal(seen[b][1], ref.tokens[b]), (variant, b)
         assert any(b != 0 for b in early)
+        assert (eng.stats()["search_steps"] == 1) == (kernel == "resident")
         assert len(ref.tokens[0]) == w.T * w.max_symbols
 
 
-def test_compact_weight_storage(pkg):
+@both_kernels
+def test_compact_weight_storage(pkg, kernel):
     """Engines with the streamed weights kept as bf16 or as 8-bit e4m3 (lossless storage of a
-    model whose streamed matrices hold such values) against the oracle on that same model; a
-    model with other values is refused.  Also logs how many rows differ from the decode of the
-    unrounded model."""
+    model whose streamed matrices hold such values; the resident kernel holds them widened) against the
+    oracle on that same model; a model with other values is refused.  Also logs how many rows differ
+    from the decode of the unrounded model."""
     import dataclasses
     kinds = [("bf16w", pkg.RNNT_FLAG_BF16_WEIGHTS, synth.with_bf16_streamed_weights),
              ("fp8w", pkg.RNNT_FLAG_FP8_WEIGHTS, synth.with_fp8_streamed_weights)]
@@ -485,9 +504,9 @@ def test_compact_weight_storage(pkg):
                 pkg.Engine(w32.model, w32.B, w32.T, flags=flag)
             assert err.value.code == -2
             w = dataclasses.replace(w32, model=transform(w32.model))
-            eng = pkg.Engine(w.model, w.B, w.T, flags=flag)
+            eng = moved_to(kernel, pkg.Engine(w.model, w.B, w.T, flags=flag))
             for variant in variants:
-                ref, got, _ = check(pkg, w, variant, f"cfg{cfg}/{name}", engine=eng)
+                ref, got, _ = check(pkg, w, variant, f"cfg{cfg}/{name}", engine=eng, kernel=kernel)
                 moved = sum(int(not np.array_equal(ref.tokens[b], ref32.tokens[b])) for b in range(w.B))
                 log(f"  rows whose tokens differ from the fp32 model's: {moved}/{w.B}")
             eng.close()
@@ -519,22 +538,23 @@ def test_log_probabilities(pkg):
         eng.close()
 
 
-def test_full_size_label_looping_with_scores_and_compact_storage(pkg):
+@both_kernels
+def test_full_size_label_looping_with_scores_and_compact_storage(pkg, kernel):
     """Config 3 at its full size, in the launch configuration bench.py times: label looping with
     the log-probability output, and the same on the bf16-valued model stored as bf16 and the
     e4m3-valued model stored as e4m3."""
     import dataclasses
     w = synth.make_workload(3, pad="nan")
-    check(pkg, w, "label", "cfg3/full/logp", logp=True)
+    check(pkg, w, "label", "cfg3/full/logp", logp=True, kernel=kernel)
     wb = dataclasses.replace(w, model=synth.with_bf16_streamed_weights(w.model))
-    eng = pkg.Engine(wb.model, wb.B, wb.T, flags=pkg.RNNT_FLAG_BF16_WEIGHTS)
-    check(pkg, wb, "label", "cfg3/full/bf16w", engine=eng, logp=True)
-    check(pkg, wb, "frame", "cfg2/full/bf16w", engine=eng)
+    eng = moved_to(kernel, pkg.Engine(wb.model, wb.B, wb.T, flags=pkg.RNNT_FLAG_BF16_WEIGHTS))
+    check(pkg, wb, "label", "cfg3/full/bf16w", engine=eng, logp=True, kernel=kernel)
+    check(pkg, wb, "frame", "cfg2/full/bf16w", engine=eng, kernel=kernel)
     eng.close()
     w8 = dataclasses.replace(w, model=synth.with_fp8_streamed_weights(w.model))
-    eng = pkg.Engine(w8.model, w8.B, w8.T, flags=pkg.RNNT_FLAG_FP8_WEIGHTS)
-    check(pkg, w8, "label", "cfg3/full/fp8w", engine=eng, logp=True)
-    check(pkg, w8, "frame", "cfg2/full/fp8w", engine=eng)
+    eng = moved_to(kernel, pkg.Engine(w8.model, w8.B, w8.T, flags=pkg.RNNT_FLAG_FP8_WEIGHTS))
+    check(pkg, w8, "label", "cfg3/full/fp8w", engine=eng, logp=True, kernel=kernel)
+    check(pkg, w8, "frame", "cfg2/full/fp8w", engine=eng, kernel=kernel)
     eng.close()
 
 
@@ -544,8 +564,9 @@ def test_row_group_counts_between_the_kernel_instances(pkg):
     team), 4 teams with 40 utterances (10 rows), and 160 utterances in the default layouts (two
     launches)."""
     w = synth.make_workload(3, pad="nan", B=160, T=40, len_lo=10, len_hi=40)
-    check(pkg, w, "label", "parakeet160")
-    check(pkg, w, "frame", "parakeet160")
+    for kernel in ("streaming", "resident"):
+        check(pkg, w, "label", "parakeet160", kernel=kernel)
+        check(pkg, w, "frame", "parakeet160", kernel=kernel)
     w96 = synth.make_workload(3, pad="nan", B=96, T=40, len_lo=10, len_hi=40)
     eng = pkg.Engine(w96.model, w96.B, w96.T)
     eng.configure(n_teams=8, joint_groups=2)
@@ -573,15 +594,17 @@ def test_joint_steps_between_the_kernel_instances(pkg):
     label-looping layout (3 rows per joint group x 8 frames = 24 samples), TDT at 72, and
     lookaheads that give 18, 20, 25 and 28 samples."""
     w = synth.make_workload(3, pad="nan", B=96, T=48, len_lo=10, len_hi=48)
-    check(pkg, w, "label", "parakeet96")
-    check(pkg, w, "frame", "parakeet96")
+    for kernel in ("streaming", "resident"):
+        check(pkg, w, "label", "parakeet96", kernel=kernel)
+        check(pkg, w, "frame", "parakeet96", kernel=kernel)
     eng = pkg.Engine(w.model, w.B, w.T)
     eng.configure(lookahead=6)                      # 3 rows x 6 frames
     check(pkg, w, "frame", "parakeet96/lookahead 6", engine=eng)
     check(pkg, w, "label", "parakeet96/lookahead 6", engine=eng)
     eng.close()
     w80 = synth.make_workload(3, pad="nan", B=80, T=48, len_lo=10, len_hi=48)
-    check(pkg, w80, "label", "parakeet80")
+    for kernel in ("streaming", "resident"):
+        check(pkg, w80, "label", "parakeet80", kernel=kernel)
     w40 = synth.make_workload(3, pad="nan", B=40, T=40, len_lo=10, len_hi=40)
     eng = pkg.Engine(w40.model, w40.B, w40.T)
     for la in (4, 5):                               # 5 rows per joint group x 4 or 5 frames
@@ -594,29 +617,33 @@ def test_joint_steps_between_the_kernel_instances(pkg):
     check(pkg, w56, "label", "parakeet56/8 teams/lookahead 4", engine=eng)
     eng.close()
     w4 = synth.make_workload(4, pad="nan", B=72, T=48, len_lo=10, len_hi=48)
-    check(pkg, w4, "tdt", "tdt72")
+    for kernel in ("streaming", "resident"):
+        check(pkg, w4, "tdt", "tdt72", kernel=kernel)
 
 
-def test_every_default_layout_class_of_the_parakeet_shape(pkg):
+@both_kernels
+def test_every_default_layout_class_of_the_parakeet_shape(pkg, kernel):
     """Engines of many sizes, each decoding a full batch of short utterances in its default
-    layout: every combination of rows per team, joint groups and lookahead the defaults
-    produce between 1 and 256 utterances is run once against the oracle."""
+    layout: every combination of rows per team, joint groups and lookahead the defaults of the streaming
+    kernel produce between 1 and 256 utterances, and the rows and frames of the resident one, are run
+    once against the oracle."""
     sizes = [1, 2, 3, 4, 5, 7, 8, 9, 12, 16, 17, 24, 31, 33, 40, 48, 56, 63, 65, 72, 88, 104, 112,
              120, 129, 144, 176, 192, 208, 224, 240, 255, 256]
     for B in sizes:
         w = synth.make_workload(3, pad="nan", B=B, T=16, len_lo=5, len_hi=16)
-        eng = pkg.Engine(w.model, w.B, w.T)
-        check(pkg, w, "label", f"parakeet{B}", engine=eng)
-        check(pkg, w, "frame", f"parakeet{B}", engine=eng)
+        eng = moved_to(kernel, pkg.Engine(w.model, w.B, w.T))
+        check(pkg, w, "label", f"parakeet{B}", engine=eng, kernel=kernel)
+        check(pkg, w, "frame", f"parakeet{B}", engine=eng, kernel=kernel)
         eng.close()
     for B in [3, 9, 20, 36, 66, 90, 100, 136, 200, 250]:
         w = synth.make_workload(4, pad="nan", B=B, T=16, len_lo=5, len_hi=16)
-        eng = pkg.Engine(w.model, w.B, w.T)
-        check(pkg, w, "tdt", f"tdt{B}", engine=eng)
+        eng = moved_to(kernel, pkg.Engine(w.model, w.B, w.T))
+        check(pkg, w, "tdt", f"tdt{B}", engine=eng, kernel=kernel)
         eng.close()
 
 
-def test_default_layout_classes_of_the_other_weight_forms(pkg):
+@both_kernels
+def test_default_layout_classes_of_the_other_weight_forms(pkg, kernel):
     """The LDS layout depends on the K values a load carries: the same sweep, coarser, for bf16
     and e4m3 storage and for the bfloat16 arithmetic with bf16, e4m3 or e2m1 storage."""
     import dataclasses
@@ -632,9 +659,9 @@ def test_default_layout_classes_of_the_other_weight_forms(pkg):
             w0 = synth.make_workload(cfg, pad="nan", B=B, T=16, len_lo=5, len_hi=16)
             for name, flag, transform, bf16 in forms:
                 w = dataclasses.replace(w0, model=transform(w0.model)) if transform else w0
-                eng = pkg.Engine(w.model, w.B, w.T, flags=flag)
+                eng = moved_to(kernel, pkg.Engine(w.model, w.B, w.T, flags=flag))
                 for variant in variants:
-                    check(pkg, w, variant, f"cfg{cfg}/{name}/{B}", engine=eng, bf16=bf16)
+                    check(pkg, w, variant, f"cfg{cfg}/{name}/{B}", engine=eng, bf16=bf16, kernel=kernel)
                 eng.close()
 
 
@@ -665,17 +692,18 @@ def test_optional_outputs_may_be_null(pkg):
             log(f"[null outputs cfg{cfg}/{variant}] {int(full['tok_len'].sum())} tokens equal")
 
 
-def test_soak_repeated_calls_give_the_same_tokens(pkg):
-    """The team barriers and tagged exchanges are built on relaxed device-scope atomics: a race
-    would show as a run that differs.  200 calls per decoder on one engine at the full size of
+@both_kernels
+def test_soak_repeated_calls_give_the_same_tokens(pkg, kernel):
+    """The team barriers and tagged exchanges are built on relaxed device-scope atomics, the resident
+    kernel's hand-overs on plain stores and polled loads: a race would show as a run that differs.  200 calls per decoder on one engine at the full size of
     configurations 2 and 3 (B = 32), every output compared with the first call's, which is
     compared with the oracle; stops at the first difference or status bit."""
     w = synth.make_workload(3, pad="nan")
-    eng = engine_for(pkg, "parakeet", w.model, w.B, w.T)
+    eng = engine_for(pkg, "parakeet", w.model, w.B, w.T, kernel)
     enc = torch.from_numpy(w.enc_out).cuda().contiguous()
     ln = torch.from_numpy(w.enc_len).cuda()
     for variant in ("label", "frame"):
-        _, first, _ = check(pkg, w, variant, "soak/first", engine=eng)
+        _, first, _ = check(pkg, w, variant, "soak/first", engine=eng, kernel=kernel)
         ref_tok = torch.from_numpy(first["raw_tokens"]).cuda()
         ref_len = torch.from_numpy(first["tok_len"]).cuda()
         out = eng.alloc_outputs(w.B, w.T * w.max_symbols)
@@ -688,16 +716,18 @@ def test_soak_repeated_calls_give_the_same_tokens(pkg):
         log(f"[soak/{variant}] 200 calls identical to the first")
 
 
-def test_more_joint_steps_than_the_exchange_tag_counts(pkg):
-    """The argmax partials carry a 16-bit step tag.  A never-blank decode of the tiny model over
+@both_kernels
+def test_more_joint_steps_than_the_exchange_tag_counts(pkg, kernel):
+    """The argmax partials of the streaming kernel carry a 16-bit step tag (the resident kernel's four slots
+    are used in turn).  A never-blank decode of the tiny model over
     6 600 frames takes more than 65 536 joint steps in one call; the tokens must still be the
     oracle's (max_symbols labels on every frame)."""
     w = synth.make_workload(0, T=6600, len_lo=6600, len_hi=6600,
                             model_overrides=dict(blank_bias=-1e4))
     w.max_symbols = 10
-    eng = pkg.Engine(w.model, w.B, w.T)
+    eng = moved_to(kernel, pkg.Engine(w.model, w.B, w.T))
     for variant in ("frame", "label"):
-        ref, got, stats = check(pkg, w, variant, "tag wrap", engine=eng)
+        ref, got, stats = check(pkg, w, variant, "tag wrap", engine=eng, kernel=kernel)
         assert stats["joint_steps"] > 65536
         assert got["tok_len"].tolist() == [66000]
     eng.close()
@@ -899,13 +929,14 @@ def test_weight_only_4_bit_quantised_models(pkg):
         assert err.value.code == -2
 
 
-def test_a_wait_that_expires_ends_the_call_with_the_aborted_bit(pkg):
+@both_kernels
+def test_a_wait_that_expires_ends_the_call_with_the_aborted_bit(pkg, kernel):
     """The failure path, forced from the host: with a wait limit of 0 polls the first wait on
     another work-group gives up, every other wait follows, and each launch ends in the ordinary
     way with RNNT_DEV_ABORTED.  The next call on the engine, with the default limit back,
     decodes as if nothing had happened."""
     w = synth.make_workload(1)
-    eng = pkg.Engine(w.model, w.B, w.T)
+    eng = moved_to(kernel, pkg.Engine(w.model, w.B, w.T))
     for bad in (-2, 1 << 32):
         with pytest.raises(pkg.RnntError) as ei:
             eng.set_wait_limit(bad)
@@ -913,7 +944,7 @@ def test_a_wait_that_expires_ends_the_call_with_the_aborted_bit(pkg):
     enc = torch.from_numpy(w.enc_out).cuda().contiguous()
     ln = torch.from_numpy(w.enc_len).cuda()
     for variant in ("frame", "label"):
-        check(pkg, w, variant, "abort/before", engine=eng)
+        check(pkg, w, variant, "abort/before", engine=eng, kernel=kernel)
         eng.set_wait_limit(0)
         eng.decode(variant, enc, ln, w.max_symbols)
         torch.cuda.synchronize()
@@ -921,7 +952,7 @@ def test_a_wait_that_expires_ends_the_call_with_the_aborted_bit(pkg):
         log(f"[abort/{variant}] status with a wait limit of 0 polls: {status}")
         assert status & pkg.RNNT_DEV_ABORTED
         eng.set_wait_limit(-1)
-        check(pkg, w, variant, "abort/after", engine=eng)
+        check(pkg, w, variant, "abort/after", engine=eng, kernel=kernel)
     eng.close()
 
 

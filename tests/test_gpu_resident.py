@@ -181,7 +181,13 @@ def test_label_dense_and_sparse_stretches(pkg, B, extra):  # noqa: F811
     x = np.where(((t + 5 * b) // 25 % 2 == 0)[:, :, None], x, blank[None, None]).astype(np.float32)
     w = synth.Workload("dense and sparse", "tdt" if dims.D else "label", model, x, ln, 4)
     eng = pkg.Engine(w.model, w.B, w.T)
-    ref, _, stats = check(pkg, w, w.variant, f"dense and sparse {B} {extra}", engine=eng, logp=True)
+    ref, got, stats = check(pkg, w, w.variant, f"dense and sparse {B} {extra}", engine=eng, logp=True)
+    import torch
+    enc, lens = torch.from_numpy(w.enc_out).cuda(), torch.from_numpy(w.enc_len.astype(np.int32)).cuda()
+    for i in range(50):        # the same hand-overs in whatever order they come
+        again = eng.decode(w.variant, enc, lens, w.max_symbols, logp=i % 2 == 0)["tokens"].cpu().numpy()
+        assert np.array_equal(again, got["raw_tokens"]), i
+    assert eng.status() == 0
     eng.close()
     # what a team that never changes examines: `la` frames of every row at every step, as far as it has them
     la, full = stats["lookahead"], 0
