@@ -145,10 +145,10 @@ def test_gates_pass_on_nan_and_saturate_at_infinity(pkg, is_tanh):  # noqa: F811
         assert 0.0 <= got[3] <= 2e-38 and 0.0 <= got[5] <= 2e-38          # exp(-87), where the argument is limited
 
 
-@pytest.mark.parametrize("is_tanh,ulps", [(False, 2.2), (True, 1.3)])
+@pytest.mark.parametrize("is_tanh,ulps", [(False, 2.6), (True, 1.3)])
 def test_gates_against_64_bits(pkg, is_tanh, ulps):  # noqa: F811
     """Every 31st float of magnitude 2^-33 to 87, both signs, and zero: within the bound that holds for all of them
-    (2.10 and 1.22 units in the last place, measured once over every float), and the sigmoid within 2e-38
+    (2.58 and 1.21 units in the last place, measured once over every float), and the sigmoid within 2e-38
     below -87, where its argument is limited."""
     top = int(np.float32(87.0).view(np.uint32))
     bits = np.concatenate([np.arange(0x2F000000, top, 31, dtype=np.uint32), np.array([0, top], dtype=np.uint32)])
