@@ -123,7 +123,11 @@ typedef struct rnnt_stats {
                               /* own (1 = the whole team together)               */
     int32_t search_steps;     /* joint steps a label search may take before the  */
                               /* next prediction step (0 = no limit)             */
-    float projection_ms;      /* device time of the encoder-projection kernel    */
+    float projection_ms;      /* device time from the start of the projection    */
+                              /* kernel to that of the decode kernel: a wait for */
+                              /* another decode, and in a first call the loading */
+                              /* of the kernel, included                         */
+                              /* (streaming kernel: of the projection alone)     */
     float decode_ms;          /* device time of the persistent decode kernel,    */
                               /* from the device's clock (streaming kernel: from */
                               /* HIP events recorded around each launch)         */
@@ -132,7 +136,9 @@ typedef struct rnnt_stats {
 /*
  * Engine flags.  RNNT_FLAG_BF16_WEIGHTS: keep the weights that are streamed at
  * every step (W_hh of every layer, W_ih of the layers above the first, W_pred,
- * W_out) as bf16 in the engine's packed copy, half the bytes per step.  The
+ * W_out) as bf16 in the packed copy of the streaming kernel, half the bytes per
+ * step; the kernel with register-resident weights, which reads them once per
+ * launch, keeps them widened to fp32.  The
  * storage is lossless or refused: every one of those weights must already be
  * a bf16 value (low 16 bits of the float zero), otherwise create returns
  * RNNT_ERR_SHAPE; the arithmetic stays fp32 (a stored weight is widened before
@@ -146,7 +152,8 @@ typedef struct rnnt_stats {
 /*
  * rnnt_engine_create flag: the same matrices are kept as 8-bit floats in the
  * OCP e4m3 format (1 sign, 4 exponent, 3 mantissa bits; largest value 448, no
- * scale factors), a quarter of the fp32 bytes per step.  Lossless or refused
+ * scale factors), a quarter of the fp32 bytes per step of the streaming kernel
+ * (widened to fp32 in the resident one, as above).  Lossless or refused
  * like the bf16 flag: every streamed weight must be an e4m3 value or create
  * returns RNNT_ERR_SHAPE; the arithmetic stays fp32.  Weight-only 8-bit storage
  * is the direction the paper's conclusion names for the next speed-up (there
@@ -169,7 +176,8 @@ typedef struct rnnt_stats {
  * reference that rounds at the same places (up to summation order).  Excludes
  * RNNT_FLAG_BF16_WEIGHTS (RNNT_ERR_SHAPE).  Together with RNNT_FLAG_FP8_WEIGHTS
  * it is the weight-only 8-bit form of the mode (the quantised products of the
- * paper's conclusion): the streamed weights are kept as e4m3 codes with one
+ * paper's conclusion): the streamed weights are kept as e4m3 codes (by the
+ * kernel with register-resident weights: as the bf16 values of the codes) with one
  * power-of-two scale per weight row (per output of the product).  The engine
  * finds the scale itself -- 2^k with the smallest k for which the row's largest
  * magnitude times 2^-k is at most 448 -- and every weight of the row times 2^-k
@@ -198,7 +206,7 @@ int rnnt_quantize_rows_e4m3(const float *w, int64_t rows, int64_t cols, float *o
 /*
  * rnnt_engine_create flag, only together with RNNT_FLAG_BF16_ARITHMETIC (alone,
  * or with another format flag, RNNT_ERR_SHAPE): the weight-only 4-bit form of
- * the bfloat16 mode.  The streamed weights are kept as codes of the OCP e2m1
+ * the bfloat16 mode.  The streamed weights are kept (as above) as codes of the OCP e2m1
  * format (1 sign, 2 exponent, 1 mantissa bit: magnitudes 0, 0.5, 1, 1.5, 2, 3,
  * 4, 6) with one power-of-two scale per block of RNNT_FP4_BLOCK consecutive
  * weights of a row (the last block of a row may be shorter).  The engine finds
@@ -499,8 +507,8 @@ int rnnt_engine_set_wait_limit(rnnt_engine *eng, int64_t polls);
  * Phase timers of the last decode call, for libraries built with
  * -DRNNT_PROFILE (RNNT_PROFILE=1 in the environment of build.py): microseconds
  * rank 0 of `team` spent in each phase of the prediction and joint steps, as
- * many as n (at most 24) into the HOST array us_out.  The phases are listed in
- * bench.py (--phases).  An ordinary build returns RNNT_ERR_UNSUPPORTED.  Waits
+ * many as n (at most 24) into the HOST array us_out.  The phases of either
+ * kernel are listed in bench.py (--phases).  An ordinary build returns RNNT_ERR_UNSUPPORTED.  Waits
  * for the device.
  */
 int rnnt_engine_phase_timers(rnnt_engine *eng, int32_t team, double *us_out, int32_t n);
