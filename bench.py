@@ -24,13 +24,23 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 
-# Phase timers of a profile build (rnnt_engine_phase_timers), in the order of their slots, of the kernel
-# with register-resident weights, which runs the models measured here.
+# Phase timers of a profile build (rnnt_engine_phase_timers), in the order of their slots: of the kernel
+# with register-resident weights, which runs the models measured here, and of the streaming one (--streaming).
 PHASES = ["pred: helpers' results", "pred: layer-0 cell, published", "pred: layer-0 vector received", "pred: input stage of layer 1",
           "pred: layer-1 cell, published", "pred: recurrent stage of layer 0", "pred: layer-1 vector received",
           "pred: projection stage, q published", "pred: recurrent stage of the top layer", "pred: q received",
           "joint: frames there (work-group barrier)", "joint: output stage", "joint: sums, argmax published", "joint: keys received",
           "joint: result shared (work-group barrier)", "control: hops, labels emitted, next samples"]
+STREAMING_PHASES = ["pred: stage-0 input filled (general)", "pred: recurrent stage of all layers",
+                    "pred: layer-0 cell and store", "pred: barrier (general)",
+                    "pred: hidden vectors of the layer below received", "pred: input stage of a layer",
+                    "pred: cell of a layer and store", "pred: barrier (general)",
+                    "pred: top hidden vectors received", "pred: prediction-side projection stage",
+                    "pred: q stored", "pred: barrier (general)", "pred: q received",
+                    "joint: z rows complete (work-group barrier)", "joint: output stage", "joint: candidates scanned, partial published",
+                    "control: results walked, labels emitted", "joint: argmax exchange", "control: before a step",
+                    "control: row states exchanged between joint groups", "joint: candidates from partial sums",
+                    "unused", "joint: frame loads and first weight loads issued", "joint: z formed"]
 
 
 def algorithmic_bytes(dims, B, variant, enc_len, tok_frames, S, wbytes=4):
@@ -160,6 +170,9 @@ def main() -> int:
                     help="instead of the benchmark line: time the decoders under other team layouts "
                          "(rnnt_engine_configure) than the default ones, one utterance and B = 32, and "
                          "print them as JSON (the figures behind the default layouts)")
+    ap.add_argument("--streaming", action="store_true",
+                    help="run the streaming decode kernel (rnnt_engine_configure) instead of the one with "
+                         "register-resident weights")
     ap.add_argument("--all-variants", action="store_true",
                     help="also time label looping with log-probabilities, the single-layer second "
                          "workload and the three decoders with bf16-stored and 8-bit (e4m3) stored "
@@ -194,7 +207,46 @@ def main() -> int:
             for tagged in (False, True):
                 exch.append({"team_size": ts, "floats": 640 * rows, "tagged_words": tagged,
                              "us_per_exchange": pkg.rnnt_probe_exchange(ts, 640 * rows, tagged)})
+
+        def best_ms(fn, calls):
+            """Milliseconds a call, the best of five runs of `calls` calls."""
+            fn()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            best = float("inf")
+            for _ in range(5):
+                a.record()
+                for _ in range(calls):
+                    fn()
+                b.record()
+                b.synchronize()
+                best = min(best, a.elapsed_time(b) / calls)
+            return best
+
+        def product(m, k, n, dtype):
+            x, y = torch.randn(m, k, device="cuda", dtype=dtype), torch.randn(k, n, device="cuda", dtype=dtype)
+            z = torch.empty(m, n, device="cuda", dtype=dtype)
+            return 2e-9 * m * k * n / best_ms(lambda: torch.mm(x, y, out=z), 20)
+
+        src = torch.randn(1 << 30, device="cuda")
+        dst = torch.empty_like(src)
+        card = {"copy_4GiB_GBs_read_and_written": 8e-6 * src.numel() / best_ms(lambda: dst.copy_(src), 5)}
+        del src, dst
+        for name, dtype in (("fp32", torch.float32), ("bf16", torch.bfloat16)):
+            card[f"library_product_8192_{name}_tflops"] = product(8192, 8192, 8192, dtype)
+        # the projection kernel on a dense batch of the same shape, in turn with the library's product
+        for B in (22, 90):
+            dims = synth.ModelDims(F=1024, E=8, H=8, L=1, J=640, V1=5)
+            eng = pkg.Engine(synth.make_model(dims, 1), B, 500)
+            enc = torch.randn(B, 500, 1024, device="cuda")
+            ln = torch.full((B,), 500, dtype=torch.int32, device="cuda")
+            proj = torch.zeros(B, 500, 640, device="cuda")
+            stream = torch.cuda.current_stream().cuda_stream
+            ms = best_ms(lambda: pkg.rnnt_encoder_projection(eng.handle, enc, ln, B, 500, proj, stream), 20)
+            card[f"product_{B * 500}x1024x640_fp32_tflops"] = {"projection_kernel": 2e-9 * B * 500 * 1024 * 640 / ms,
+                                                               "library": product(B * 500, 1024, 640, torch.float32)}
+            eng.close()
         print(json.dumps({"probes": {
+            "card": card,
             "stream_from_l2": {"GBs": l2, "GBs_per_cu": l2_cu,
                                "pattern": "16 slices of 1.5 MiB, slice i%16 for work-group i, 64 passes"},
             "stream_from_hbm": {"GBs": hbm, "GBs_per_cu": hbm_cu, "pattern": "8 MiB per work-group, one pass"},
@@ -281,6 +333,8 @@ def main() -> int:
         if args.plain_launch:
             flags |= pkg.RNNT_FLAG_PLAIN_LAUNCH
         eng = pkg.Engine(w.model, w.B, w.T, flags=flags)
+        if args.streaming:
+            eng.configure(search_steps=1)      # its default where a joint group has two rows or more
         enc = torch.from_numpy(w.enc_out).cuda().contiguous()
         ln = torch.from_numpy(w.enc_len).cuda()
         out = eng.alloc_outputs(w.B, w.T * w.max_symbols)
@@ -305,7 +359,7 @@ def main() -> int:
         if args.phases:
             per_team = [eng.phase_timers(t) for t in range(st["n_teams"])]
             slow = max(range(len(per_team)), key=lambda t: sum(per_team[t]))
-            phases = {"team": slow, "us": dict(zip(PHASES, per_team[slow]))}
+            phases = {"team": slow, "us": dict(zip(STREAMING_PHASES if args.streaming else PHASES, per_team[slow]))}
         res = dict(w=w, w_orig=w_orig, wall=wall, steps=steps, phases=phases, dec_ms=float(np.median(dec_ms)),
                    proj_ms=float(np.median(proj_ms)), dec_ms_min=float(np.min(dec_ms)), stats=st,
                    status=status, frames=frames, tokens=tokens, tok_len=tok_len)
@@ -348,7 +402,8 @@ def main() -> int:
         "data": "synthetic",
         "timing_note": "value and ms_per_step are host wall time over the timed calls, each followed "
                        "by rnnt_engine_stats (a device synchronisation and a small copy), so they "
-                       "are conservative; kernel_ms are times on the device's clock, median "
+                       "are conservative; kernel_ms are times on the device's clock (the projection's up to the "
+                       "start of the decode kernel), median "
                        "and minimum over the timed calls",
         "config": {"workload": f"config {dict(frame=2, label=3, tdt=4)[args.variant]}: "
                                f"{w.name}, B={w.B}, T<={w.T}, frames={n_frames}, "
@@ -500,12 +555,14 @@ def main() -> int:
         # alternating batch and an input that emits max_symbols labels on every frame
         line["sweep"] = []
         for kind in ("typical",) + tuple(synth.PATTERNS[1:]):
-            for B in (1, 8, 32, 128) + ((256,) if kind == "typical" else ()):   # 256: two launches of 128
+            for B in (1, 8, 32, 128, 256):
                 if kind == "typical":
                     ws = synth.make_workload(2, B=B)
                 else:
                     ws = synth.make_adversarial(kind, cfg=2, B=B, T=200)
                 eng = pkg.Engine(ws.model, ws.B, ws.T)
+                if args.streaming:
+                    eng.configure(search_steps=1)
                 enc = torch.from_numpy(ws.enc_out).cuda().contiguous()
                 ln = torch.from_numpy(ws.enc_len).cuda()
                 out = eng.alloc_outputs(ws.B, ws.T * ws.max_symbols)
