@@ -58,11 +58,12 @@ __device__ __forceinline__ const char *uniform(const char *p)
 // that reads of 16 bytes by 8 rows meet different banks.  A lane reads four k's at once (K is the same
 // permutation of itself in both operands), and the loop has next to no vector instructions, which
 // the fp32 matrix instructions would share their pipe with.
-// fp32, 1024 x 640, valid rows only: 11200 rows 155 us (195 before), 44700 rows 540 us (711), 500 rows
-// 15 us (50); a dense batch of that shape runs at 114 TFLOP/s, the rate of the library's product.
+// fp32, 1024 x 640, valid rows of ragged batches: 11300 rows 145 us (a grid over utterances and padded tiles
+// took 195), 43100 rows 494 us (711), 500 rows 15 us (50); a dense batch of 45000 rows runs at 122 TFLOP/s,
+// the library's product of that shape at 123.
 // bfloat16 mode (BF): the frames are rounded to bfloat16 (ties to even) between LDS and the matrix
 // instruction, W_enc holds bfloat16 values already (its low halves are zero), products are
-// exact in fp32 and the sums are fp32: 11200 rows 57 us (64).
+// exact in fp32 and the sums are fp32: 11300 rows 55 us (64).
 template <int BM, int BN, int WM, int WN, int WK, bool BF>
 __global__ void __launch_bounds__(256)
 enc_proj_kernel(const float *__restrict__ x, const int *__restrict__ enc_len, const float *__restrict__ w_enc,
@@ -230,14 +231,14 @@ hipError_t launch_encoder_projection(const float *enc_out, const int *enc_len, c
                            proj, B, T, F, J, ci);
     };
     // Few rows: small tiles with K split over the waves, so that there are blocks for all compute units and the
-    // chain of each is short (500 rows: 15 against 28 us; even at 3700 rows in fp32, 2.4 blocks of 32 x 128
+    // chain of each is short (fp32, 500 rows: 15 against 28 us; even at 3700 rows in fp32, 2.4 blocks of 32 x 128
     // per unit; in the bfloat16 mode 10 against 17 and, at 3700 rows, 38 against 26).
     const long long blocks = (long long)B * ((T + 31) / 32) * ((J + 127) / 128);
     if (round_x) {
         if (blocks <= 512) run(enc_proj_kernel<32, 32, 1, 1, 4, true>, 32, 32);
         else run(enc_proj_kernel<64, 128, 2, 2, 1, true>, 64, 128);
     } else {
-        // (32-row tiles waste the least on an utterance's last one: 44700 rows 540 us, with 64 rows 565)
+        // (32-row tiles waste the least on an utterance's last one: with 64 rows 5 % slower at 44700 rows)
         if (blocks <= 1024) run(enc_proj_kernel<32, 32, 1, 1, 4, false>, 32, 32);
         else run(enc_proj_kernel<32, 128, 1, 4, 1, false>, 32, 128);
     }

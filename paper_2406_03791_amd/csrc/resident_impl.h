@@ -8,7 +8,7 @@
 // of work-groups sits inside one XCD, so its hand-overs go through that XCD's L2: a store that stays
 // in the L2 and a load that passes by the L1 hand 640 floats to 32 work-groups in 0.70 us, where
 // stores and loads through the memory side take 1.3 us (4 x 640 floats: 0.88 against 1.4 us).
-// 32 utterances of a two-layer model of 640 units: 4.35 to 1.9 ms, one of 500 frames 1.63 to 0.5 ms.
+// 32 utterances of a two-layer model of 640 units: 4.35 to 2.06 ms, one of 500 frames 1.63 to 0.53 ms.
 //
 // Work split inside a team of `ts` work-groups: LSTM units, projection columns and output columns
 // in contiguous ranges.  LSTM stages and the projection run on v_mfma 4x4 (16 blocks): the rows of a
@@ -25,7 +25,8 @@
 // per helper, 6.5 with five teams on three XCDs of helpers, 7.1 with six on two.
 //
 // Utterances are decoded label-looping fashion: every utterance has its own frame index, a joint
-// step examines `la` frames of every utterance, and the next prediction step runs as soon as one
+// step examines `la` frames of every utterance (half as many in label-dense stretches of two-layer fp32
+// models, see the end of the loop), and the next prediction step runs as soon as one
 // of them has a label.  A team takes a list of utterances and decodes up to kResRows at a time;
 // when one ends the next of the list takes its place.  (Eight rows of four frames took 15 us a step
 // where four rows of eight take 10.)
