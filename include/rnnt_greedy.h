@@ -446,7 +446,8 @@ int rnnt_engine_stats(rnnt_engine *eng, rnnt_stats *out);
  * RNNT_ERR_SHAPE for values the engine cannot run (the work-groups do not
  * divide into the teams or groups, more than 16 utterances per team) and
  * RNNT_ERR_UNSUPPORTED when the layout does not fit the LDS; a refused call
- * leaves the engine as it was, its layouts, knobs and kernel included.
+ * leaves the engine as it was, its layouts, knobs and kernel included.  (New
+ * layouts are made beside the old ones, in memory of their own.)
  */
 int rnnt_engine_configure(rnnt_engine *eng, int32_t n_teams, int32_t joint_groups,
                           int32_t lookahead, int32_t search_steps);

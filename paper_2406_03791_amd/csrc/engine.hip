@@ -30,10 +30,13 @@ thread_local std::string g_hip_error;
 
 }  // namespace
 
-// Records the text rnnt_status_string(RNNT_ERR_HIP) returns; shared with the probes.
+// Records the text rnnt_status_string(RNNT_ERR_HIP) returns; shared with the probes.  The runtime keeps a
+// failed call's error for whoever asks next (the launch of the next decode, or other code of the thread): it is
+// reported here, so it is taken back.
 int rnnt::hip_fail(hipError_t e, const char *what)
 {
     g_hip_error = std::string("HIP error in ") + what + ": " + hipGetErrorString(e);
+    (void)hipGetLastError();
     return RNNT_ERR_HIP;
 }
 

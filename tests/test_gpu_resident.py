@@ -1,8 +1,9 @@
 """The decode kernel with register-resident weights at the edges of what it holds: the widest and
 narrowest layers of every size class and one unit beyond, output layers that just fill the column
 tiles, the tail columns and no longer, one and two layers, one utterance, teams whose list is longer
-than the rows they decode at a time, and more utterances than one launch takes.  Against the
-oracle, through the C ABI."""
+than the rows they decode at a time, more utterances than one launch takes, and label-dense stretches.
+Against the oracle, through the C ABI.  Also its gates alone, and what engines do between the two
+kernels: refused configurations and allocations, launches on request, threads."""
 import dataclasses
 
 import numpy as np
@@ -205,3 +206,16 @@ def test_label_dense_and_sparse_stretches(pkg, B, extra):  # noqa: F811
             k += 1
     print(f"samples {stats['joint_samples']}, without changes {full}", flush=True)
     assert stats["joint_samples"] < 0.95 * full
+
+
+def test_an_engine_that_does_not_fit_the_memory_leaves_the_others_alone(pkg):  # noqa: F811
+    """The projected frames of 2^27 padded frames take 320 GiB: refused by the allocator, and the next call of an
+    engine that exists does not report that error."""
+    w = model_inputs(324, 640, 530, 2, B=9, T=12, seed=9)
+    eng = pkg.Engine(w.model, w.B, w.T)
+    for v in ("label", "frame"):
+        with pytest.raises(pkg.RnntError) as err:
+            pkg.Engine(w.model, 1 << 14, 1 << 13)
+        assert err.value.code == -4
+        check(pkg, w, v, "after a refused allocation", engine=eng)
+    eng.close()
