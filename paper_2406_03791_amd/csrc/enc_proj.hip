@@ -75,6 +75,7 @@ enc_proj_kernel(const float *__restrict__ x, const int *__restrict__ enc_len, co
     constexpr int CNT = (BM + BN) / 8 * WK / 4;                      // loads (of 8 rows) of a wave per stage
     __shared__ __align__(16) unsigned char lds[2 * STAGE];
     init_call(ci, B);
+    const TopWord call = !BF && ci.p_top ? ci.p_top[kTopWords * kTopStride] : 0;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ny = (J + BN - 1) / BN, slot = blockIdx.x >> 3, tile = (slot / ny) * 8 + (blockIdx.x & 7), n0 = slot % ny * BN;
     // the utterance and row that valid row tile number `tile` is of
@@ -189,8 +190,13 @@ enc_proj_kernel(const float *__restrict__ x, const int *__restrict__ enc_len, co
         if (s + 1 < ns) step(s + 1, ns, 1);
     }
     // accumulator register v of lane l holds row 8*(v/4) + 4*(l/32) + v%4, column l%32
+    float top = 0.f;                 // the largest finite value
+    bool infinite = false;
     auto store = [&](int row, int col, float v) {
-        if (row < len) proj[((long long)b * T + row) * J + col] = v;
+        if (row < len) {
+            proj[((long long)b * T + row) * J + col] = v;
+            if (!BF) { infinite = infinite || v == INFINITY; top = fmaxf(top, v == INFINITY ? 0.f : v); }
+        }
     };
     if constexpr (WK == 1) {
 #pragma unroll
@@ -217,6 +223,16 @@ enc_proj_kernel(const float *__restrict__ x, const int *__restrict__ enc_len, co
             for (int v = wk * 4; v < wk * 4 + 4; ++v)
                 store(m0 + 8 * (v >> 2) + 4 * kh + (v & 3), col,
                       ((red[v * 64 + lane] + red[(16 + v) * 64 + lane]) + (red[(32 + v) * 64 + lane] + red[(48 + v) * 64 + lane])) + bias);
+        }
+    }
+    if (!BF && ci.p_top) {
+#pragma unroll
+        for (int i = 32; i; i >>= 1) top = fmaxf(top, __shfl_xor(top, i));
+        TopWord *word = ci.p_top + (blockIdx.x % kTopWords) * kTopStride;
+        const bool any = __ballot(infinite) != 0ull;
+        if (lane == 0) {
+            atomicMax(word, call << 16 | (__float_as_uint(top) + 0xffffu) >> 16);
+            if (any) atomicMax(word + 1, call << 16 | 1u);
         }
     }
 }

@@ -61,7 +61,9 @@ constexpr int kStaticLds = 3072;        // kept free for the kernel's static LDS
 // projected frames and the team workspace of one call.  One copy per device, held until the
 // process ends.  In host code this name is only a handle for hipGetSymbolAddress: the address
 // kernels and copies use is the one that call returns (rnnt_engine::scratch).
-static __device__ __align__(256) unsigned char scratch[RNNT_NOALLOC_SCRATCH_BYTES];
+// kScratchTop: where the words on a call's P have their place, which every call finds as the last one left them.
+constexpr size_t kScratchTop = RNNT_NOALLOC_SCRATCH_BYTES;
+static __device__ __align__(256) unsigned char scratch[kScratchTop + kTopTotal * sizeof(TopWord)];
 
 struct DevBuf {
     void *p = nullptr;
@@ -100,6 +102,7 @@ struct Workspace {
     // resident kernel: exchange buffers of all teams, meeting words
     unsigned char *xbuf = nullptr;
     unsigned *form = nullptr;
+    TopWord *top = nullptr;             // on what P is like
 };
 
 // Bytes of each part of the team workspace for a layout (everything but P).
@@ -158,7 +161,8 @@ struct rnnt_engine {
     // (res.kind), unless rnnt_engine_configure asks for a team layout, lookahead or search limit:
     // those are the streaming kernel's, whose layouts are made then (or at once for other models).
     ResidentPlan res{};
-    DevBuf res_w, res_help, res_tail, res_xbuf, res_form, res_stats;
+    float res_q_bound = 0.f;
+    DevBuf res_w, res_help, res_tail, res_scales, res_top, res_xbuf, res_form, res_stats;
     bool use_streaming = true;
     bool own_layout = false;        // n_teams was configured
     // Team layouts, one per range of launch sizes in which the measured best arrangement (or
@@ -550,35 +554,37 @@ Workspace resident_workspace(const rnnt_engine *e)
     Workspace w;
     w.P = e->P.as<float>(); w.abort_flag = e->abort_flag.as<unsigned>(); w.status = e->status.as<int>();
     w.stats = e->res_stats.as<long long>(); w.xbuf = e->res_xbuf.as<unsigned char>(); w.form = e->res_form.as<unsigned>();
+    w.top = e->res_top.as<TopWord>();
     return w;
 }
 
-// Packs the weights for the resident kernel.  Synchronous.
-int make_resident(rnnt_engine *e)
+// Packs the weights for the resident kernel, from the model's own matrices.  Synchronous.
+int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
 {
     const ResidentPlan &pl = e->res;
-    auto put = [](DevBuf &dst, const void *src, size_t bytes) -> int {
-        HIP_TRY(dst.alloc(bytes));
-        HIP_TRY(hipMemcpy(dst.p, src, bytes, hipMemcpyHostToDevice));
-        return RNNT_OK;
-    };
-    const ResidentWeights rw{e->d.H, e->d.J, e->d.L, &e->w_hh, &e->w_ih, &e->w_pred, &e->w_out};
-    int rc;
-    {
-        const std::vector<uint32_t> w = pack_resident_main(pl, rw);
-        if ((rc = put(e->res_w, w.data(), w.size() * 4))) return rc;
-    }
-    if (pl.kind == kResident2Pair) {
-        const std::vector<uint32_t> w = pack_resident_helper(pl, rw);
-        if ((rc = put(e->res_help, w.data(), w.size() * 4))) return rc;
-    }
-    if (pl.n_tail) {
-        std::vector<float> t((size_t)pl.n_tail * res_row(pl.cls), 0.f);
-        for (int i = 0; i < pl.n_tail; ++i)
-            std::copy_n(e->w_out.data() + (size_t)(pl.nout_m + i) * e->d.J, e->d.J, t.data() + (size_t)i * res_row(pl.cls));
-        if ((rc = put(e->res_tail, t.data(), t.size() * 4))) return rc;
-    }
-    HIP_TRY(e->res_xbuf.alloc((size_t)resident_buf(pl.cls).bytes * pl.n_teams));
+    const bool bf = pl.bf != 0;
+    const size_t images = (size_t)res_team(pl.cls) * kResWaves * 64 * sizeof(float), scales = (size_t)e->NOUT + d.J + (d.L > 1 ? 4 * (d.L + 1) : 4) * (size_t)d.H;
+    HIP_TRY(e->res_w.alloc(images * res_main_regs(pl.kind, bf, pl.cls)));
+    if (pl.kind == kResident2Pair) HIP_TRY(e->res_help.alloc(images * 2 * res_lstm_regs(bf, pl.cls)));
+    if (pl.n_tail) HIP_TRY(e->res_tail.alloc((size_t)pl.n_tail * res_row(pl.cls) * sizeof(float)));
+    HIP_TRY(e->res_top.alloc(kTopTotal * sizeof(TopWord)));
+    HIP_TRY(hipMemset(e->res_top.p, 0, kTopTotal * sizeof(TopWord)));
+    HIP_TRY(e->res_scales.alloc((2 * scales + 2) * sizeof(float)));        // (the second half is for the packing)
+    float *rows = e->res_scales.as<float>() + scales;
+    unsigned *check = reinterpret_cast<unsigned *>(rows + scales);
+    HIP_TRY(hipMemset(check, 0, 2 * sizeof(unsigned)));
+    ResidentWeights rw{d.H, d.J, d.L, {d.w_hh[0], d.L > 1 ? d.w_hh[1] : nullptr}, d.L > 1 ? d.w_ih[1] : nullptr, d.w_pred, d.b_pred, d.w_out};
+    ResidentImages im{e->res_w.as<float>(), e->res_help.as<float>(), e->res_tail.as<float>(), e->res_scales.as<float>(), nullptr, nullptr, {nullptr, nullptr},
+                      rows, check};
+    im.s_pred = im.s_out + e->NOUT; im.s_ih = im.s_pred + d.J;
+    im.s_hh[0] = im.s_ih + (d.L > 1 ? 4 * d.H : 0); im.s_hh[1] = im.s_hh[0] + 4 * d.H;
+    HIP_TRY(pack_resident(pl, rw, im, nullptr));
+    unsigned found[2] = {0, 0};
+    HIP_TRY(hipMemcpy(found, check, sizeof found, hipMemcpyDeviceToHost));
+    // (infinite or undefined weights have no fp16 parts: such a model is left to the other kernel)
+    if (found[0]) { e->res.kind = kResidentNone; return RNNT_OK; }
+    std::memcpy(&e->res_q_bound, &found[1], sizeof(float));
+    HIP_TRY(e->res_xbuf.alloc((size_t)resident_buf(pl.cls, 4).bytes * pl.n_teams));
     HIP_TRY(e->res_form.alloc((size_t)pl.n_xcd * 32 * sizeof(unsigned)));
     HIP_TRY(e->res_stats.alloc((size_t)pl.n_teams * kStatStride * sizeof(long long)));
     HIP_TRY(hipMemset(e->res_form.p, 0, (size_t)pl.n_xcd * 32 * sizeof(unsigned)));
@@ -589,7 +595,7 @@ int make_resident(rnnt_engine *e)
 // Utterances a team decodes at a time and frames per utterance and joint step for a launch of nb.
 void resident_rows(const ResidentPlan &pl, int nb, int *slots, int *la)
 {
-    *slots = std::min(kResRows, (nb + pl.n_teams - 1) / pl.n_teams);
+    *slots = std::min(4, (nb + pl.n_teams - 1) / pl.n_teams);
     *la = *slots <= 2 ? 16 / *slots : kResSamples / *slots;
     *la = std::min(*la, 16);
 }
@@ -605,6 +611,7 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
     ci.form = ws.form; ci.n_form = pl.n_xcd * 32; ci.abort_flag = ws.abort_flag; ci.status = ws.status;
     ci.tokens = tokens_out; ci.frames = frames_out; ci.durs = durs_out; ci.logits = logit_out; ci.logps = e->logp_out;
     ci.cap = cap; ci.stats = ws.stats;
+    ci.p_top = res_whole(pl.bf != 0, pl.cls) ? nullptr : ws.top;
     HIP_TRY(launch_encoder_projection(enc_out, enc_len, e->w_enc.as<float>(), e->b_enc.as<float>(), ws.P, B, T, d.F, d.J,
                                       is_bf16_arith(e->wt), ci, stream));
     e->last_B = B; e->last_used.clear(); e->last_ws = ws; e->last_resident = true;
@@ -632,6 +639,10 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
             p.logps = e->logp_out ? e->logp_out + oc : nullptr;
             p.done = e->done ? e->done + off : nullptr;
             p.w = e->res_w.as<float>(); p.w_help = e->res_help.as<float>(); p.w_tail = e->res_tail.as<float>();
+            p.q_bound = e->res_q_bound;
+            p.p_top = ws.top;
+            p.s_out = e->res_scales.as<float>(); p.s_pred = p.s_out + e->NOUT; p.s_ih = p.s_pred + d.J;
+            p.s_hh[0] = p.s_ih + (d.L > 1 ? 4 * d.H : 0); p.s_hh[1] = p.s_hh[0] + 4 * d.H;
             p.T0 = e->T0.as<float>(); p.bias_l = e->bias_l.as<float>(); p.b_pred = e->b_pred.as<float>(); p.b_out = e->b_out.as<float>();
             p.xbuf = ws.xbuf;
             p.form = ws.form; p.abort_flag = ws.abort_flag; p.status = ws.status; p.stats = ws.stats;
@@ -938,11 +949,10 @@ int rnnt_engine_create(const rnnt_model_desc *desc, int32_t max_B, int32_t max_T
     HIP_TRY(hipMemset(e->status.p, 0, sizeof(int)));
     e->res = plan_resident(d.H, d.J, d.L, e->NOUT, is_bf16_arith(e->wt), prop.multiProcessorCount);
     if (e->res.kind != kResidentNone) {
-        if ((rc = make_resident(e))) return rc;
-        e->use_streaming = false;
-    } else if ((rc = default_layouts(e, e->frame_cfgs, e->label_cfgs))) {
-        return rc;
+        if ((rc = make_resident(e, d))) return rc;
+        e->use_streaming = e->res.kind == kResidentNone;
     }
+    if (e->res.kind == kResidentNone && (rc = default_layouts(e, e->frame_cfgs, e->label_cfgs))) return rc;
     for (auto &x : e->ev) HIP_TRY(hipEventCreate(&x));
     HIP_TRY(hipDeviceSynchronize());
     guard.e = nullptr;
@@ -1138,11 +1148,11 @@ int rnnt_label_looping_decode_noalloc(rnnt_engine *eng, const float *enc_out, co
         size_t off = 0;
         auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
         const size_t o_P = take((size_t)B * T * eng->d.J * sizeof(float));
-        const size_t o_x = take((size_t)resident_buf(pl.cls).bytes * pl.n_teams);
+        const size_t o_x = take((size_t)resident_buf(pl.cls, 4).bytes * pl.n_teams);
         const size_t o_f = take((size_t)pl.n_xcd * 32 * sizeof(unsigned));
         const size_t o_s = take((size_t)pl.n_teams * kStatStride * sizeof(long long));
         const size_t o_a = take(sizeof(unsigned)), o_st = take(sizeof(int));
-        if (off > (size_t)RNNT_NOALLOC_SCRATCH_BYTES) return RNNT_ERR_SCRATCH;
+        if (off > RNNT_NOALLOC_SCRATCH_BYTES) return RNNT_ERR_SCRATCH;
         unsigned char *base = static_cast<unsigned char *>(eng->scratch);
         Workspace ws;
         ws.P = reinterpret_cast<float *>(base + o_P);
@@ -1151,6 +1161,7 @@ int rnnt_label_looping_decode_noalloc(rnnt_engine *eng, const float *enc_out, co
         ws.stats = reinterpret_cast<long long *>(base + o_s);
         ws.abort_flag = reinterpret_cast<unsigned *>(base + o_a);
         ws.status = reinterpret_cast<int *>(base + o_st);
+        ws.top = reinterpret_cast<TopWord *>(base + kScratchTop);
         return run_decode(eng, kLabelLooping, enc_out, enc_len, B, T, max_symbols, tokens_out, tok_len_out, cap, frames_out,
                           logit_out, nullptr, static_cast<hipStream_t>(stream), &ws);
     }

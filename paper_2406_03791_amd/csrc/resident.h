@@ -12,7 +12,7 @@ constexpr int kResThreads = 512;          // eight waves, two per SIMD: 256 regi
 constexpr int kResWaves = 8;
 constexpr int kResUnits = 20;             // LSTM units per work-group at most
 constexpr int kResSlots = 4;              // exchange slots per vector, used in turn
-constexpr int kResRows = 4;               // utterances a team decodes at the same time at most
+constexpr int kResRows = 8;               // utterances a team decodes at the same time at most: instances for 4 and 8
 constexpr int kResSamples = 32;           // (utterance, frame) pairs per joint step at most
 constexpr int kResCalm = 16;              // joint steps after which a row's frames are halved, see the loop control
 constexpr int kResList = 128;             // utterances a team takes per launch at most
@@ -24,19 +24,25 @@ RNNT_HD constexpr int res_width(int cls) { return cls == 0 ? 640 : (cls == 1 ? 3
 RNNT_HD constexpr int res_team(int cls) { return cls == 0 ? 32 : (cls == 1 ? 16 : 8); }         // work-groups per team
 RNNT_HD constexpr int res_row(int cls) { return cls == 0 ? 640 : (cls == 1 ? 384 : 128); }      // floats per frame row in LDS
 
-// K comes in pieces of four values: four registers and four 4x4x1 instructions in fp32, two registers
-// and one 4x4x4 instruction in the bfloat16 mode.
-RNNT_HD constexpr int res_piece_regs(bool bf) { return bf ? 2 : 4; }
-RNNT_HD constexpr int res_pieces(int cls) { return res_width(cls) / 4; }
-// LSTM stages: waves 0 .. 5 hold a sixth of K for units 0 .. 15, waves 6 and 7 an eighth per block for units 16 .. 19
-RNNT_HD constexpr int res_lstm_pieces(int cls) { return (res_pieces(cls) + 5) / 6; }
-// prediction-side projection: fifteen of a wave's blocks are five groups of columns times three slices of K, so
-// 24 slices in all
-RNNT_HD constexpr int res_pred_pieces(int cls) { return (res_pieces(cls) + 23) / 24; }
-// joint steps per wave: 16 K values each, every eighth one of the joint width
-RNNT_HD constexpr int res_joint_steps(int cls) { return res_row(cls) / 128; }
-// bytes of an activation row in LDS; the rows start 64 bytes apart modulo the banks
-RNNT_HD constexpr int res_xrow(bool bf, int cls) { return res_width(cls) * (bf ? 2 : 4) + 64; }
+// Every dense stage: a wave takes an eighth of K (80, 48 or 16 values, one after the other) in blocks of 32, one
+// 16x16x32 matrix instruction each, and where it is odd a last half block of 16.  res_halves: half blocks.
+RNNT_HD constexpr int res_halves(int cls) { return res_row(cls) / 128; }
+// Parts of an fp32 value on the 16-bit matrix instructions: value = high + low, two fp16 numbers of 11 bits
+// (the low one's sign makes 23), after a power of two that takes the largest of a row to 2^14 .. 2^15.
+// Kept in as many registers as the value itself.  Against 64 bits the logits of layers of 320 and 640 are 0 to 6 % closer
+// than with fp32 products in a chain.  In the narrowest class, whose chains are short, they were 7 % further
+// off: its joint output has whole fp32 values (res_whole, four 16x16x4 for a half block).
+constexpr int kResHiddenExp = 15;         // hidden values travel as fp16 parts of 2^15 times themselves (fp32)
+RNNT_HD constexpr bool res_whole(bool bf, int cls) { return !bf && res_halves(cls) == 1; }
+RNNT_HD constexpr int res_parts(bool bf) { return bf ? 1 : 2; }
+// registers of a wave's share of T tiles of 16 outputs, and the place of block kb (kb == halves / 2: the half
+// block), tile t, part (0 high, 1 low) among them
+RNNT_HD constexpr int res_tile_regs(bool bf, int cls, int T) { return T * res_halves(cls) * 2 * res_parts(bf); }
+RNNT_HD constexpr int res_tile_at(bool bf, int cls, int T, int kb, int t, int part)
+{
+    return kb < res_halves(cls) / 2 ? ((kb * T + t) * res_parts(bf) + part) * 4
+                                    : res_halves(cls) / 2 * T * res_parts(bf) * 4 + (t * res_parts(bf) + part) * 2;
+}
 
 // Kinds of resident decoders (which weights sit where).
 enum ResidentKind {
@@ -75,7 +81,11 @@ struct ResidentParams {
     int *done;
     const float *w;       // packed registers of the (main) work-groups: [rank][wave][register][lane]
     const float *w_help;  // the same of the helpers (kResident2Pair)
-    const float *w_tail;  // [n_tail][res_row(cls)]
+    const float *w_tail;  // [n_tail][res_row(cls)], scaled as the packed output columns
+    // fp32: what sums of the scaled weights of an output are multiplied by; LSTM matrices [H][gate]
+    const float *s_out, *s_pred, *s_ih, *s_hh[2];
+    float q_bound;        // no |q| is larger: hidden values are within +-1
+    unsigned long long *p_top;            // fp32: what the call's P is like (TopWord)
     const float *T0, *bias_l, *b_pred, *b_out;
     unsigned char *xbuf;  // exchange buffers, resident_buf(cls).bytes per team
     unsigned *form;       // one word per work-group, zero at launch: the XCD it runs on
@@ -86,66 +96,77 @@ struct ResidentParams {
     int count_rows;       // prediction steps are counted per utterance (Algorithm 1) instead of per team
 };
 
-// Byte offsets of a team's exchange buffers; every vector has kResSlots slots.
-struct ResidentBuf {
-    unsigned h[2], q, key, dur, lse, hr[2], pre, bytes;
-};
-RNNT_HD constexpr ResidentBuf resident_buf(int cls)
+// Byte offsets of a team's exchange buffers, every vector in kResSlots slots; R: rows of the instance, 4 or 8.
+struct ResidentBuf { unsigned h[2], q, key, dur, lse, hr[2], pre, bytes; };
+RNNT_HD constexpr ResidentBuf resident_buf(int cls, int R)
 {
-    const unsigned vec = kResSlots * kResRows * (unsigned)res_width(cls) * 4u;
+    const unsigned vec = kResSlots * (unsigned)(R * res_width(cls)) * 4u;
     const unsigned recs = kResSlots * kResSamples * (unsigned)res_team(cls);
     ResidentBuf b{};
     b.h[0] = 0; b.h[1] = vec; b.q = 2 * vec; b.key = 3 * vec;
     b.dur = b.key + recs * 8u;
     b.lse = b.dur + kResSlots * kResSamples * kMaxDur * 4u;
     b.hr[0] = b.lse + recs * 4u; b.hr[1] = b.hr[0] + vec; b.pre = b.hr[1] + vec;
-    // [layer][slot][rank][wave of the cells][lane]
-    b.bytes = b.pre + 2u * kResSlots * (unsigned)res_team(cls) * 5u * 64u * 4u;
+    // [layer][slot][rank][wave of the cells][lane][gate]
+    b.bytes = b.pre + 2u * kResSlots * (unsigned)res_team(cls) * 5u * 64u * (unsigned)(R / 4) * 4u;
     return b;
 }
 
 // Registers per lane of a work-group, in packing order: recurrent matrices (kResident1: layer 0;
 // kResident2: both layers), input matrix of the second layer, prediction-side projection, joint
 // output.  The helpers of kResident2Pair hold the two recurrent matrices.
-RNNT_HD constexpr int res_lstm_regs(bool bf, int cls) { return res_lstm_pieces(cls) * res_piece_regs(bf); }
-RNNT_HD constexpr int res_pred_regs(bool bf, int cls) { return res_pred_pieces(cls) * res_piece_regs(bf); }
-RNNT_HD constexpr int res_joint_regs(bool bf, int cls) { return res_joint_steps(cls) * 2 * res_piece_regs(bf); }
+RNNT_HD constexpr int res_lstm_regs(bool bf, int cls) { return res_tile_regs(bf, cls, 5); }
+RNNT_HD constexpr int res_pred_regs(bool bf, int cls) { return res_tile_regs(bf, cls, 2); }
+RNNT_HD constexpr int res_joint_regs(bool bf, int cls) { return res_tile_regs(bf, cls, 2); }
 RNNT_HD constexpr int res_main_regs(int kind, bool bf, int cls)
 {
     return (kind == kResident2 ? 3 : 1) * res_lstm_regs(bf, cls) + res_pred_regs(bf, cls) + res_joint_regs(bf, cls);
 }
 
-// LDS layout in bytes (dynamic part): frames of the joint step's samples, activation rows of the LSTM
-// stages and partial sums of the projection (both done with when the joint step's partial sums take
-// their place; so rows that no utterance is in hold anything), q rows (zeros beyond the joint width: what
-// stands there is multiplied by zero weights), tail column, partial sums of the input stage and of the
-// recurrent stages.
-// nmt: tiles of 16 samples.
-struct ResidentLds { int p, part, xh, g4, q, tail, ih, rec, tpart, bytes; };
-constexpr int kResSumRow = 36;            // floats per sample row of the joint step's partial sums
-RNNT_HD constexpr ResidentLds resident_lds(int kind, bool bf, int cls, int nmt)
+// LDS layout in bytes (dynamic part).  p: frames of the joint step's samples.  part: the joint step's partial sums;
+// before it, in their place, those of the input stage (ih).  proj: partial sums of the projection (read after
+// the work-group's last barrier before the joint step).  rec0, rec: those of the first and of the top layer's
+// recurrent stage, kept till the next prediction step (eight rows: till they are read, rec0 then beside ih).
+// q: every wave's eighth of q, rows of res_q_row floats (zeros beyond the joint width).  tail: the tail column (see output()),
+// tpart: its partial sums.  state: cell state and recurrent pre-activations [layer][field][wave][lane] where they are
+// not in registers.
+// nmt: tiles of 16 samples.  Helpers: their own, from 0 on.
+struct ResidentLds { int p, part, ih, rec0, proj, rec, q, tail, tpart, state, bytes; };
+constexpr int kResSumRow = 36;            // floats per row of partial sums: of the joint step, of the projection
+constexpr int kResStageRow = 80;          // and of the LSTM stages
+RNNT_HD constexpr int res_q_row(int cls) { return res_row(cls) / 8 + 4; }
+RNNT_HD constexpr ResidentLds resident_lds(int kind, int cls, int nmt, int R)
 {
     ResidentLds l{};
-    const int frames = 16 * nmt * res_row(cls) * 4, sums = kResWaves * 16 * nmt * kResSumRow * 4;
-    const int stage = kResWaves * 1024, q = kResRows * (res_row(cls) + 16) * 4;
+    const int stage = kResWaves * R * kResStageRow * 4, sums = kResWaves * 16 * nmt * kResSumRow * 4;
     l.p = 0;
-    l.part = l.xh = frames;
-    // (kResident2Pair: where the first layer's rows are large enough, the projection's sums take their place)
-    const int x_row = kResRows * res_xrow(bf, cls), proj = kResWaves * 60 * 16;
-    const bool over = kind == kResident2Pair && x_row >= proj;
-    l.g4 = over ? l.xh : l.xh + (kind == kResident1 ? 1 : 2) * x_row;
-    l.q = over ? l.xh + 2 * x_row : l.g4 + proj;
-    if (l.q < l.part + sums) l.q = l.part + sums;
-    l.tail = l.q + q;
-    l.ih = l.tail + res_row(cls) * 4;
-    l.rec = l.ih + (kind == kResident1 ? 0 : stage);
-    l.tpart = l.rec + (kind == kResident2Pair ? 0 : (kind == kResident2 ? 2 : 1) * stage);
-    l.bytes = l.tpart + kResWaves * 2 * 16 * 4;
+    l.part = l.ih = 16 * nmt * res_row(cls) * 4;
+    int at = l.ih + (kind == kResident1 ? 0 : stage);
+    if (kind == kResident2 && R == 8) { l.rec0 = at; at += stage; }
+    if (at < l.part + sums) at = l.part + sums;
+    l.proj = at; at += kResWaves * R * kResSumRow * 4;
+    if (kind == kResident2 && R != 8) { l.rec0 = at; at += stage; }
+    l.rec = at; at += kind == kResident2Pair ? 0 : stage;
+    l.q = at; at += kResWaves * R * res_q_row(cls) * 4;
+    l.tail = at; at += (kind == kResident2 ? 2 : res_halves(cls) == 1 ? 4 : 3) * res_row(cls) * 2;
+    l.tpart = at; at += kResWaves * 2 * 16 * 4;
+    l.state = at; at += kind == kResident2Pair && R == 4 ? 6 * 5 * 64 * 4 : 0;
+    const int help = 2 * stage + kResWaves * kResServed * ((res_halves(cls) + 1) / 2) * 1024;
+    if (kind == kResident2Pair && at < help) at = help;
+    l.bytes = (at + 15) & ~15;
     return l;
 }
-constexpr int kResCtl = 3840;             // bytes kept for the control block
-static_assert(resident_lds(kResident1, false, 0, 2).bytes + kResCtl <= 160 * 1024 && resident_lds(kResident2, true, 0, 2).bytes + kResCtl <= 160 * 1024 &&
-              resident_lds(kResident2Pair, false, 0, 2).bytes + kResCtl <= 160 * 1024, "the largest layouts and the control block fit the LDS");
+constexpr int kResCtl = 5376;             // bytes kept for the control block
+static_assert(resident_lds(kResident1, 0, 2, 4).bytes + kResCtl <= 160 * 1024 && resident_lds(kResident2, 0, 2, 4).bytes + kResCtl <= 160 * 1024 &&
+              resident_lds(kResident2Pair, 0, 2, 4).bytes + kResCtl <= 160 * 1024, "the largest layouts and the control block fit the LDS");
+
+// The model's matrices on the device (rows as in the model), and where their packed forms go: register images of the
+// teams' and the helpers' work-groups, [rank][wave][register][lane]; tail columns; what sums are multiplied by; the
+// scales of the rows, in the order of these, and two words, zero before: not every value is finite, and the largest
+// sum of the magnitudes of a row of w_pred and its bias (a float's bits; both fp32 only).
+struct ResidentWeights { int H, J, L; const float *w_hh[2], *w_ih1, *w_pred, *b_pred, *w_out; };
+struct ResidentImages { float *w, *w_help, *w_tail, *s_out, *s_pred, *s_ih, *s_hh[2], *row_scales; unsigned *check; };
+hipError_t pack_resident(const ResidentPlan &pl, const ResidentWeights &rw, const ResidentImages &im, hipStream_t stream);
 
 // nmt: tiles of 16 samples a joint step has, 1 or 2
 hipError_t launch_resident(const ResidentParams &p, int nmt, bool plain, hipStream_t stream);

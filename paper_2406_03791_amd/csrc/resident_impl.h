@@ -11,25 +11,29 @@
 // 32 utterances of a two-layer model of 640 units: 4.35 to 2.06 ms, one of 500 frames 1.63 to 0.53 ms.
 //
 // Work split inside a team of `ts` work-groups: LSTM units, projection columns and output columns
-// in contiguous ranges.  LSTM stages and the projection run on v_mfma 4x4 (16 blocks): the rows of a
-// block are four utterances, its columns the gates of a unit or four columns, K is split over the waves
-// and the partial sums meet in LDS.  The joint output runs on v_mfma 16x16 (16 columns x 16 samples,
-// two column tiles, K in eighths over the waves); its operand relu(P + q) is formed on the way from
-// LDS to the matrix instruction.
+// in contiguous ranges.  Every dense stage is the same: K in eighths over the waves, tiles of 16 outputs
+// (the gates of four units, or columns) by 16 columns of the operand on v_mfma 16x16x32, and the waves' partial sums
+// meet in LDS.  Columns of the LSTM stages and the projection are the team's utterances, which a wave receives
+// straight into the operand's registers (Operand); those of the joint output are samples, whose operand relu(P + q)
+// is formed on the way from LDS to the matrix instruction.
+//
+// fp32 values run on the 16-bit matrix instructions as two fp16 parts each, weights and vectors alike: 23 bits,
+// all four products (the joint of the widest class: three, see there), fp32 sums.  On the fp32 instructions a step's stages were
+// bound by the matrix pipe, which they share with everything else: a 4x4 one per row group and 32 k's, 16x16x4 in
+// the joint step.  A joint step of 32 utterances 9.7 to 8.8 us, of one utterance 7.8 to 6.6, of a model of the
+// narrowest class 4.2 to 4.0 (with phase timers).
 //
 // Two-layer fp32 models have more weights than one XCD's registers hold (24 MB against 12 + 4):
 // there the teams' XCDs keep the input, projection and output matrices and run the whole step chain;
 // the helpers' XCDs keep the recurrent matrices and compute W_hh h of the candidate states, which the
 // chain needs only at the next label: their hand-overs across the XCDs run beside the rest of the
-// step.  A helper is busy 3 us of a team's step and serves two teams: 128 utterances 7.7 ms with one team
-// per helper, 6.5 with five teams on three XCDs of helpers, 7.1 with six on two.
+// step.  A helper is busy 1.6 us of a team's step and serves two.
 //
 // Utterances are decoded label-looping fashion: every utterance has its own frame index, a joint
 // step examines `la` frames of every utterance (half as many in label-dense stretches of two-layer fp32
 // models, see the end of the loop), and the next prediction step runs as soon as one
-// of them has a label.  A team takes a list of utterances and decodes up to kResRows at a time;
-// when one ends the next of the list takes its place.  (Eight rows of four frames took 15 us a step
-// where four rows of eight take 10.)
+// of them has a label.  A team takes a list of utterances and decodes up to R at a time;
+// when one ends the next of the list takes its place.
 //
 // Exchange: a vector's buffer has four slots used in turn; words are 32-bit floats, all ones
 // meaning "not there yet" (readers poll the data itself).  A work-group puts that mark back into
@@ -55,6 +59,8 @@ typedef unsigned r4u __attribute__((ext_vector_type(4)));
 typedef unsigned r2u __attribute__((ext_vector_type(2)));
 typedef short r4s __attribute__((ext_vector_type(4)));
 typedef __bf16 r8b __attribute__((ext_vector_type(8)));
+typedef _Float16 r8h __attribute__((ext_vector_type(8)));
+typedef _Float16 r4h __attribute__((ext_vector_type(4)));
 
 constexpr unsigned kMark = 0xffffffffu;    // no data yet
 constexpr unsigned kStop = 0xfffffffeu;    // to the helpers: the team is done
@@ -75,9 +81,14 @@ struct RCtl {
     int n_list, ok, st_clamped, st_overflow;
     int dur[kMaxDur];
     unsigned seen[2][kResWaves];      // helpers: what a wave has seen of the teams' vectors
-    int list_b[kResList], list_len[kResList];
-    // this work-group's slices of the biases: second layer [unit][gate], projection, output and tail column
-    float b1[kResUnits * 4], bp[20], bo[32], bt;
+    unsigned short list_b[kResList];
+    int list_len[kResList];
+    // this work-group's slices of the biases: second layer [unit][gate], projection, output and tail column; and of
+    // what sums are multiplied by (fp32): the same and [layer][unit][gate] of the recurrent matrices
+    float b1[kResUnits * 4], bp[20];
+    float s1[kResUnits * 4], sp[20], sh[2][kResUnits * 4];
+    float2 bo[16], so[16];
+    float bt, st;
 };
 __shared__ RCtl rc;
 static_assert(sizeof(RCtl) <= kResCtl, "the control block has its place");
@@ -91,19 +102,29 @@ __shared__ long long res_prof_last;
 #define RES_MARK(slot) do { } while (0)
 #endif
 
-template <int N> struct RegW { float w[N]; };
-
+// Weights: in groups of four registers, as the matrix instructions take them (half blocks: two groups of two).
+typedef float r2f __attribute__((ext_vector_type(2)));
+template <int N> struct RegW {
+    r4f q[N / 4];
+    r2f rest;                         // N % 4 == 2
+};
 // Loads registers [first, first + N) of the wave's packed run.  The empty asm makes each value
-// opaque, so that it stays in its register and is never read from memory again.
+// opaque, so that it stays in its registers and is never read from memory again.
 template <int N>
 __device__ __forceinline__ void load_regs(RegW<N> &r, const float *src, int first, int lane)
 {
+    static_assert(N % 2 == 0, "pairs");
+    src += first * 64 + lane;
 #pragma unroll
-    for (int i0 = 0; i0 < N; i0 += 32) {          // 32 loads in flight
+    for (int i0 = 0; i0 < N / 4; i0 += 8) {       // 32 loads in flight
 #pragma unroll
-        for (int i = i0; i < N && i < i0 + 32; ++i) r.w[i] = src[(first + i) * 64 + lane];
+        for (int i = i0; i < N / 4 && i < i0 + 8; ++i) r.q[i] = (r4f){src[i * 256], src[i * 256 + 64], src[i * 256 + 128], src[i * 256 + 192]};
 #pragma unroll
-        for (int i = i0; i < N && i < i0 + 32; ++i) asm volatile("" : "+v"(r.w[i]));
+        for (int i = i0; i < N / 4 && i < i0 + 8; ++i) asm volatile("" : "+v"(r.q[i]));
+    }
+    if (N % 4) {
+        r.rest = (r2f){src[N / 4 * 256], src[N / 4 * 256 + 64]};
+        asm volatile("" : "+v"(r.rest));
     }
 }
 
@@ -195,15 +216,19 @@ __device__ __forceinline__ bool has_mark(r4u v) { return max(max(v.x, v.y), max(
 // N 16-byte pieces per thread: all loads in flight together, all of them again while a lane of the
 // wave misses a word.
 template <int N>
-__device__ __forceinline__ void receive(const ResidentParams &p, RCtx &x, const unsigned (&off)[N], unsigned imm, r4u (&v)[N])
+__device__ __forceinline__ void receive(const ResidentParams &p, RCtx &x, const unsigned (&off)[N], unsigned imm, r4u (&v)[N], bool takes = true)
 {
     unsigned spins = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = (r4u){0u, 0u, 0u, 0u};
     for (;;) {
         bool missing = false;
+        if (takes) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = get4(x, off[i], imm);
+            for (int i = 0; i < N; ++i) v[i] = get4(x, off[i], imm);
 #pragma unroll
-        for (int i = 0; i < N; ++i) missing = missing || has_mark(v[i]);
+            for (int i = 0; i < N; ++i) missing = missing || has_mark(v[i]);
+        }
         if (__ballot(missing) == 0ull) break;
         if (wait_expired(p, spins)) { rc.ok = 0; break; }
     }
@@ -218,46 +243,6 @@ __device__ __forceinline__ unsigned bf16_pair(float a, float b)
     const f2 v = {a, b};
     return __builtin_bit_cast(unsigned, __builtin_convertvector(v, b2));
 }
-
-// Stores piece k4 (four values) of an activation row in LDS.
-template <bool BF>
-__device__ __forceinline__ void x_put(unsigned char *row, int k4, r4u v)
-{
-    if (BF) {
-        uint2 o;
-        o.x = bf16_pair(__uint_as_float(v.x), __uint_as_float(v.y));
-        o.y = bf16_pair(__uint_as_float(v.z), __uint_as_float(v.w));
-        *reinterpret_cast<uint2 *>(row + k4 * 8) = o;
-    } else {
-        *reinterpret_cast<r4u *>(row + k4 * 16) = v;
-    }
-}
-
-// A piece of K of an activation row, and the matrix instructions that take it: four fp32 (e = 0 .. 3)
-// or one bf16.
-template <bool BF> struct Piece;
-template <> struct Piece<false> {
-    static constexpr int N = 4, B = 16;
-    float4 v;
-    __device__ __forceinline__ void load(const unsigned char *p) { v = *reinterpret_cast<const float4 *>(p); }
-    // S, ID: the blocks form groups of 2^S that all take the operand of block ID of their group
-    template <int S = 0, int ID = 0>
-    __device__ __forceinline__ void mfma(int e, const float *w, r4f &acc) const
-    {
-        acc = __builtin_amdgcn_mfma_f32_4x4x1f32(e == 0 ? v.x : (e == 1 ? v.y : (e == 2 ? v.z : v.w)), w[e], acc, S, ID, 0);
-    }
-};
-template <> struct Piece<true> {
-    static constexpr int N = 1, B = 8;
-    r4s v;
-    __device__ __forceinline__ void load(const unsigned char *p) { v = *reinterpret_cast<const r4s *>(p); }
-    template <int S = 0, int ID = 0>
-    __device__ __forceinline__ void mfma(int, const float *w, r4f &acc) const
-    {
-        struct P { float a, b; };
-        acc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(v, __builtin_bit_cast(r4s, P{w[0], w[1]}), acc, S, ID, 0);
-    }
-};
 
 template <int CTRL>
 __device__ __forceinline__ float dppf(float v)
@@ -296,6 +281,63 @@ __device__ __forceinline__ void swap16(float &a, float &b)
     a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
 }
 
+// Two fp32 values as fp16 parts (ties to even), the first in the low half: the nearest fp16 numbers, and those nearest
+// to what is left.  (v_fma_mixlo_f16 and v_fma_mixhi_f16 would do each of the four in one instruction, but they write
+// half a register and take twice the time of others: 8.7 cycles against 4.3 to 4.9.)
+__device__ __forceinline__ unsigned f16_pair(float a, float b)
+{
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const f2 v = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, h2));
+}
+__device__ __forceinline__ void f16_parts(float a, float b, unsigned &high, unsigned &low)
+{
+    high = f16_pair(a, b);
+    // (in instructions that take the fp16 number as it is: from C++ a conversion and a subtraction come)
+    float ra, rb;
+    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[0,0,1]" : "=v"(ra) : "v"(a), "v"(high));
+    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(rb) : "v"(b), "v"(high));
+    low = f16_pair(ra, rb);
+}
+
+// Matrix instruction on a block of a wave's share of K: `w` and `z` from the registers of that block on, four
+// of either (32 k's), two for a half block.  A matrix instruction that adds to what one of the other kind right
+// before it leaves gives wrong sums (the compiler places no wait between them): where a sum takes both kinds, the
+// half block comes first and 32 cycles or more of something else after it (ordered: nothing moves across), or it
+// is two sums.
+template <bool BF>
+__device__ __forceinline__ r4f tile_mfma(r4f w, const unsigned *z, r4f acc)
+{
+    const r4u zv = {z[0], z[1], z[2], z[3]};
+    if constexpr (BF) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(r8b, w), __builtin_bit_cast(r8b, zv), acc, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(r8h, w), __builtin_bit_cast(r8h, zv), acc, 0, 0, 0);
+}
+// fp32 values, of a half block
+__device__ __forceinline__ r4f whole_mfma(r4f w, const unsigned *z, r4f acc)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[e], __uint_as_float(z[e]), acc, 0, 0, 0);
+    return acc;
+}
+template <bool BF>
+__device__ __forceinline__ r4f tile_mfma(r2f w, const unsigned *z, r4f acc)
+{
+    const r2u zv = {z[0], z[1]};
+    if constexpr (BF) return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(r4s, w), __builtin_bit_cast(r4s, zv), acc, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(r4h, w), __builtin_bit_cast(r4h, zv), acc, 0, 0, 0);
+}
+// the weights of block kb of tile t
+template <bool BF, int CLS, int T, int KB, int PART, int N>
+__device__ __forceinline__ auto weights_of(const RegW<N> &w, int t)
+{
+    const int at = res_tile_at(BF, CLS, T, KB, t, PART);
+    if constexpr (KB < res_halves(CLS) / 2) return w.q[at / 4];
+    else return at / 4 == N / 4 ? w.rest : (at % 4 ? w.q[at / 4].zw : w.q[at / 4].xy);
+}
+
+__device__ __forceinline__ void ordered() { __builtin_amdgcn_sched_barrier(0); }
+
 // compile-time loop: f(std::integral_constant<int, I>) for I = LO .. HI - 1
 template <int LO, int HI, class F>
 __device__ __forceinline__ void static_for(F f)
@@ -306,104 +348,163 @@ __device__ __forceinline__ void static_for(F f)
     }
 }
 
-// One LSTM stage over the wave's part of K: partial sums of the work-group's units for all rows go to
-// LDS, [row group][wave][lane] with a lane's four rows; the readers add six or eight of them
-// (stage_sum), so there are no sums across lanes.  The activation rows x are read once: lane 4 b + r
-// fetches another piece of row r for every block b, and the matrix instruction's broadcast hands each of
-// them to all blocks in turn (waves 6 and 7: to the four blocks of a slice of K).  Reading a piece
-// once per block instead kept the LDS as busy as the matrix cores: 2.8 against 1.9 us for eight rows.
-template <bool BF, int CLS>
-__device__ __forceinline__ void lstm_stage(const RegW<res_lstm_regs(BF, CLS)> &w, const unsigned char *x, int h4, float *sums, int wave, int lane)
+// Hidden values as they travel, one word each: fp16 parts of 2^15 times the value (high in the low half), or bf16.
+template <bool BF>
+__device__ __forceinline__ unsigned hidden_word(float h)
 {
-    constexpr int N = res_lstm_pieces(CLS), N8 = res_pieces(CLS) / 8, PR = res_piece_regs(BF), XROW = res_xrow(BF, CLS);
-    typedef Piece<BF> Pc;
-    r4f acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-    const int b = lane >> 2;
-    const unsigned char *xr = x + (lane & 3) * XROW;       // (pieces beyond the last have zero weights: the last will do)
-    if (wave < 6) {
-        constexpr int Q = (N + 15) / 16;
-        Pc q[Q];
+    if (BF) return bf16_pair(h, 0.f);
+    unsigned high, low;
+    h *= (float)(1 << kResHiddenExp);
+    f16_parts(h, h, high, low);
+    const unsigned u = __builtin_amdgcn_perm(low, high, 0x05040100u);
+    return u >= kStop ? 0x7e007e00u : u;
+}
+
+// The operand of a dense stage: the wave's eighth of K of the rows' hidden values, columns 0 .. 15 of the matrix
+// instructions.  R rows take R columns; fp32: R with the high parts are followed by R with the low ones (R == 4:
+// and the same again), so a product with the weights' high and one with their low parts give
+// all four.  A lane loads four words of a block, exchanges halves with the lane R columns on (whose words are the
+// block's other four of the same row and group), and has what the instruction takes: nothing of it
+// goes through LDS, and a wave goes on as soon as its own eighth is there.
+template <bool BF, int CLS, int R>
+struct Operand {
+    static constexpr int NH = res_halves(CLS), NF = NH / 2, NB = NF + (NH & 1);
+    unsigned z[NH * 2];
+    // words of block i for the lane: byte offset in a vector of rows of `W` words; n4 pieces of four words a row, the
+    // last one stands for those beyond (their weights are zeros)
+    static __device__ __forceinline__ unsigned offset(int i, int wave, int lane, int n4)
+    {
+        const int n = lane & 15, g = lane >> 4, other = (n / R) & 1, row = n & (R - 1);
+        const int k4 = wave * (NH * 4) + i * 8 + (i < NF ? 2 * g + other : g);
+        return (unsigned)(row * (res_width(CLS) * 4)) + (unsigned)min(k4, n4 - 1) * 16u;
+    }
+    // the lanes that load: a copy of somebody else's words would travel for nothing
+    static __device__ __forceinline__ bool takes(int lane, int slots) { return (lane & 15) < 2 * R && (lane & (R - 1)) < slots; }
+    __device__ __forceinline__ void set(const r4u (&v)[NB], int lane)
+    {
+        const bool other = ((lane & 15) / R) & 1;
+        const unsigned keep = !BF && other ? 0x07060302u : 0x05040100u, send = !BF && !other ? 0x07060302u : 0x05040100u;
 #pragma unroll
-        for (int h = 0; h < Q; ++h) q[h].load(xr + min(wave * N + h * 16 + b, h4 - 1) * Pc::B);
-        static_for<0, N>([&](auto i_) {
-            constexpr int i = decltype(i_)::value;
+        for (int i = 0; i < NB; ++i) {
+            const unsigned k0 = __builtin_amdgcn_perm(v[i].y, v[i].x, keep), k1 = __builtin_amdgcn_perm(v[i].w, v[i].z, keep);
+            if (i < NF) {
+                const unsigned s0 = __builtin_amdgcn_perm(v[i].y, v[i].x, send), s1 = __builtin_amdgcn_perm(v[i].w, v[i].z, send);
+                constexpr int UP = 0x110 + R, DOWN = 0x100 + R, FIRST = R == 8 ? 0x3 : 0x1, SECOND = R == 8 ? 0xc : 0x2;       // banks of four lanes
+                z[i * 4] = (unsigned)__builtin_amdgcn_update_dpp((int)k0, (int)s0, UP, 0xf, SECOND, false);
+                z[i * 4 + 1] = (unsigned)__builtin_amdgcn_update_dpp((int)k1, (int)s1, UP, 0xf, SECOND, false);
+                z[i * 4 + 2] = (unsigned)__builtin_amdgcn_update_dpp((int)k0, (int)s0, DOWN, 0xf, FIRST, false);
+                z[i * 4 + 3] = (unsigned)__builtin_amdgcn_update_dpp((int)k1, (int)s1, DOWN, 0xf, FIRST, false);
+            } else {
+                z[i * 4] = k0; z[i * 4 + 1] = k1;
+            }
+        }
+    }
+    __device__ __forceinline__ void receive_from(const ResidentParams &p, RCtx &x, unsigned base, int n4)
+    {
+        unsigned off[NB];
+        r4u v[NB];
+        const int lane = lane_id();
 #pragma unroll
-            for (int e = 0; e < Pc::N; ++e) q[i / 16].template mfma<4, i % 16>(e, &w.w[i * PR], acc[(i * Pc::N + e) & 1]);
-        });
+        for (int i = 0; i < NB; ++i) off[i] = offset(i, x.wave, lane, n4);
+        receive<NB>(p, x, off, base, v, takes(lane, p.slots));
+        set(v, lane);
+    }
+};
+
+// A dense stage with T tiles of 16 outputs: the sums over the wave's eighth of K go to LDS, [wave][row][ROW floats].
+// fp32: the products with the weights' low parts come before the others, to be added at their own size.
+template <bool BF, int CLS, int R, int T, int ROW>
+__device__ __forceinline__ void stage(const RegW<res_tile_regs(BF, CLS, T)> &w, const Operand<BF, CLS, R> &x, float *sums, int wave)
+{
+    constexpr int NH = res_halves(CLS), NF = NH / 2;
+    constexpr bool MIXED = NF > 0 && NH % 2 != 0, APART = MIXED && T < 4;
+    r4f sum[T], half[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) sum[t] = half[t] = (r4f){0.f, 0.f, 0.f, 0.f};
+    auto block = [&](auto kb_, auto part_) {
+        constexpr int kb = decltype(kb_)::value, part = decltype(part_)::value;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            r4f &to = APART && kb == NF ? half[t] : sum[t];
+            to = tile_mfma<BF>(weights_of<BF, CLS, T, kb, part>(w, t), x.z + kb * 4, to);
+        }
+    };
+    std::integral_constant<int, NF> last;
+    std::integral_constant<int, 0> high;
+    std::integral_constant<int, 1> low;
+    if constexpr (NH % 2 != 0) {
+        if constexpr (!BF) block(last, low);
+        block(last, high);
+        if constexpr (MIXED && !APART) {
+            ordered();
+#pragma unroll
+            for (int t = 0; t < T; ++t) asm volatile("" : "+v"(sum[t]));
+            asm volatile("s_nop 15\n\ts_nop 15");
+            ordered();
+        }
+    }
+    if constexpr (!BF) static_for<0, NF>([&](auto kb_) { block(kb_, low); });
+    static_for<0, NF>([&](auto kb_) { block(kb_, high); });
+    const int lane = lane_id(), n = lane & 15;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        r4f v = sum[t];
+        if constexpr (APART) v += half[t];
+        if (!BF) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] += dppf<0x100 + R>(v[i]);
+        }
+        if (n < R) *reinterpret_cast<r4f *>(sums + (wave * R + n) * ROW + t * 16 + (lane >> 4) * 4) = v;
+    }
+}
+
+// What a lane finishes in the LSTM stages, waves 0 .. 4: G = R / 4 gates from G j on of unit 4 wave + lane / 16 for
+// row lane / (4 / G) % R.  Its sums over the waves:
+template <int R>
+__device__ __forceinline__ void stage_sum(const float *sums, int blk, int lane, float (&v)[R / 4])
+{
+    constexpr int G = R / 4, L = 4 / G;
+    const float *s = sums + ((lane / L) & (R - 1)) * kResStageRow + (blk * 4 + (lane >> 4)) * 4 + (lane & (L - 1)) * G;
+    if constexpr (G == 1) {
+        float o[kResWaves];
+#pragma unroll
+        for (int w = 0; w < kResWaves; ++w) o[w] = s[w * R * kResStageRow];
+        v[0] = ((o[0] + o[1]) + (o[2] + o[3])) + ((o[4] + o[5]) + (o[6] + o[7]));
     } else {
-        constexpr int Q = (N8 + 3) / 4;
-        Pc q[2];
-        auto fetch = [&](int h) { q[h & 1].load(xr + min((h * 4 + (b & 3)) * 8 + (wave - 6) * 4 + (b >> 2), h4 - 1) * Pc::B); };
-        fetch(0);
-        static_for<0, Q>([&](auto h_) {
-            constexpr int h = decltype(h_)::value;
-            if constexpr (h + 1 < Q) fetch(h + 1);
-            __builtin_amdgcn_sched_barrier(0);
-            static_for<h * 4, (h * 4 + 4 < N8 ? h * 4 + 4 : N8)>([&](auto i_) {
-                constexpr int i = decltype(i_)::value;
+        float2 o[kResWaves];
 #pragma unroll
-                for (int e = 0; e < Pc::N; ++e) q[h & 1].template mfma<2, i % 4>(e, &w.w[i * PR], acc[(i * Pc::N + e) & 1]);
-            });
-        });
+        for (int w = 0; w < kResWaves; ++w) o[w] = *reinterpret_cast<const float2 *>(s + w * R * kResStageRow);
+        v[0] = ((o[0].x + o[1].x) + (o[2].x + o[3].x)) + ((o[4].x + o[5].x) + (o[6].x + o[7].x));
+        v[G - 1] = ((o[0].y + o[1].y) + (o[2].y + o[3].y)) + ((o[4].y + o[5].y) + (o[6].y + o[7].y));
     }
-    *reinterpret_cast<r4f *>(sums + (wave * 64 + lane) * 4) = acc[0] + acc[1];
 }
 
-// The stage's sum for lane `lane` of wave `blk` < 5: unit 4 blk + lane / 16, row lane / 4 % 4, gate lane % 4.
-__device__ __forceinline__ float stage_sum(const float *sums, int blk, int lane)
+// LSTM cell on the four (G == 2: two) adjacent lanes of a unit and row: lane j holds the pre-activations of gate j
+// (gates 2 j and 2 j + 1) of i, f, g, o.  Every lane gets the results.
+template <int G>
+__device__ __forceinline__ void cell(const float (&pre)[G], int j, float c_old, float &c_new, float &h)
 {
-    const int uu = lane >> 4, row = (lane >> 2) & 3, j = lane & 3;
-    const float *s = sums + row;
-    if (blk < 4) {
-        s += (4 * (blk * 4 + uu) + j) * 4;
-        return (s[0] + (s[256] + s[512])) + (s[768] + (s[1024] + s[1280]));
+    if constexpr (G == 1) {
+        const float act = gate_act(pre[0], j == 2);
+        const float i_ = dppf<0x00>(act), f_ = dppf<0x55>(act), g_ = dppf<0xAA>(act), o_ = dppf<0xFF>(act);
+        c_new = fmaf(f_, c_old, i_ * g_);
+        h = o_ * gate_act(c_new, true);
+    } else {
+        const float a0 = gate_act(pre[0], j == 1), a1 = gate_act(pre[1], false);
+        const float b0 = dppf<0xB1>(a0), b1 = dppf<0xB1>(a1);
+        c_new = fmaf(j ? b1 : a1, c_old, a0 * b0);
+        h = (j ? a1 : b1) * gate_act(c_new, true);
     }
-    s += 6 * 256 + (4 * uu + j) * 4;         // slices 64 floats apart
-    return ((s[0] + s[64]) + (s[128] + s[192])) + ((s[256] + s[320]) + (s[384] + s[448]));
-}
-
-// LSTM cell on the four lanes of a block: lane j holds the pre-activation of gate j (i, f, g, o).
-// Every lane of the block gets the results.
-__device__ __forceinline__ void cell(float pre, int j, float c_old, float &c_new, float &h)
-{
-    const float act = gate_act(pre, j == 2);
-    const float i_ = dppf<0x00>(act), f_ = dppf<0x55>(act), g_ = dppf<0xAA>(act), o_ = dppf<0xFF>(act);
-    c_new = fmaf(f_, c_old, i_ * g_);
-    h = o_ * gate_act(c_new, true);
 }
 
 // What the prediction step does with a row's candidate state: take it, or start afresh (else nothing).
 constexpr int kTake = 1 << 30, kFresh = (int)(1u << 31);
 
-#define RES_SLOT(n) ((unsigned)(n) & (kResSlots - 1))
-
-// Receives a vector of `rows` rows of n4 16-byte pieces each (rows row_bytes apart from byte `base`
-// of the exchange buffers on) and hands every piece to f(row, k4, words).
-// (piece i of a thread: number piece_index, of row piece_row; threads beyond the vector read its last
-// piece along)
-__device__ __forceinline__ unsigned piece_index(unsigned tid, int i, int n) { return min(tid + (unsigned)(i * kResThreads), (unsigned)(n - 1)); }
-__device__ __forceinline__ unsigned piece_inverse(int n4) { return ((1u << 20) + (unsigned)n4 - 1u) / (unsigned)n4; }     // idx / n4 for idx * n4 < 2^20, idx < 2^11
-__device__ __forceinline__ unsigned piece_row(unsigned idx, unsigned inv) { return __umul24(idx, inv) >> 20; }
-template <int WIDTH>
-__device__ __forceinline__ unsigned piece_offset(unsigned idx, unsigned inv, int n4)
+// Byte offset of step n's slot among slots of `bytes`.  (In a scalar register by force: the compiler multiplies in a
+// vector instruction and puts a loop over its lanes' values around every load and store that takes the offset.)
+__device__ __forceinline__ unsigned slot_at(unsigned n, unsigned bytes)
 {
-    return __umul24(piece_row(idx, inv), WIDTH * 4u - (unsigned)n4 * 16u) + idx * 16u;
-}
-template <int WIDTH, class F>
-__device__ __forceinline__ void receive_rows(const ResidentParams &p, RCtx &x, unsigned base, int rows, int n4, F f)
-{
-    constexpr int N = (kResRows * (WIDTH / 4) + kResThreads - 1) / kResThreads;
-    unsigned off[N];
-    r4u v[N];
-    const unsigned tid = (unsigned)(x.wave * 64 + lane_id()), inv = piece_inverse(n4);
-#pragma unroll
-    for (int i = 0; i < N; ++i) off[i] = piece_offset<WIDTH>(piece_index(tid, i, rows * n4), inv, n4);
-    receive<N>(p, x, off, base, v);
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const unsigned idx = piece_index(tid, i, rows * n4), r = piece_row(idx, inv);
-        f((int)r, (int)(idx - __umul24(r, (unsigned)n4)), v[i]);
-    }
+    return (unsigned)__builtin_amdgcn_readfirstlane((int)((n & (kResSlots - 1)) * bytes));
 }
 
 // The kernel's arguments read again from memory: for what few waves and few steps need, and which would
@@ -445,23 +546,28 @@ __device__ __forceinline__ void load_frame(const ResidentParams &p, const RCtx &
 
 __device__ __forceinline__ int from_lane(int v, int lane) { return __builtin_amdgcn_ds_bpermute(lane << 2, v); }
 
-// KIND: ResidentKind; BF: bfloat16 mode; CLS: size class; NMT: tiles of 16 samples of a joint step
-template <int KIND, bool BF, int CLS, int NMT>
+// KIND: ResidentKind; BF: bfloat16 mode; CLS: size class; NMT: tiles of 16 samples of a joint step; R: rows
+template <int KIND, bool BF, int CLS, int NMT, int R>
 __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const ResidentParams p)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     constexpr int NL = KIND == kResident1 ? 1 : 2;
     constexpr bool PAIR = KIND == kResident2Pair;
-    constexpr int W = res_width(CLS), ROW = res_row(CLS), TS = res_team(CLS), XROW = res_xrow(BF, CLS);
-    constexpr int NI = res_joint_steps(CLS), PR = res_piece_regs(BF), LREGS = res_lstm_regs(BF, CLS);
-    typedef Piece<BF> Pc;
+    constexpr int W = res_width(CLS), ROW = res_row(CLS), TS = res_team(CLS);
+    constexpr int NH = res_halves(CLS), NF = NH / 2, NB = NF + (NH & 1), LREGS = res_lstm_regs(BF, CLS);
+    constexpr bool WHOLE = res_whole(BF, CLS);
+    // What is left of the recurrent stages till the next prediction step: their sums in LDS, or (eight rows: there is
+    // no room for them) the pre-activations in registers, at the price of a barrier while q travels.
+    constexpr bool HOLD = R == 8 || PAIR;
+    constexpr int G = R / 4, LR = 16 / R;        // gates a lane finishes in the LSTM stages, lanes per row in the loop control
+    typedef Operand<BF, CLS, R> Op;
     constexpr bool HALVES = PAIR && NMT == 2;     // steps with one tile of samples as well, see after the loop
     constexpr int NREC = PAIR ? 0 : NL;          // recurrent matrices the chain's work-groups hold
-    constexpr ResidentBuf bo = resident_buf(CLS);
-    constexpr ResidentLds lo = resident_lds(KIND, BF, CLS, NMT);
-    constexpr unsigned VROW = W * 4u, VSLOT = kResRows * VROW;                      // h and q rows
+    constexpr ResidentBuf bo = resident_buf(CLS, R);
+    constexpr ResidentLds lo = resident_lds(KIND, CLS, NMT, R);
+    constexpr unsigned VROW = W * 4u, VSLOT = R * VROW;                      // h and q rows
     constexpr unsigned KSLOT = kResSamples * TS * 8u, DSLOT = kResSamples * kMaxDur * 4u;
-    constexpr unsigned PSLOT = TS * 5u * 64u * 4u;
+    constexpr unsigned PSLOT = TS * 5u * 64u * G * 4u;
 
     RCtx x;
     const int tid0 = threadIdx.x, lane0 = tid0 & 63;         // (for the work before and after the loop)
@@ -545,49 +651,71 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         return __syncthreads_and(!(mine && side == 0 && v != first)) != 0;
     };
     const bool has_cells = x.wave < 5;          // finishes 16 (unit, row) pairs of the LSTM stages, see stage_sum
-    auto prelane = [&]() { return (((unsigned)x.rank * 5u + (unsigned)x.wave) * 64u + (unsigned)lane_id()) * 4u; };
+    auto prelane = [&]() { return (((unsigned)x.rank * 5u + (unsigned)x.wave) * 64u + (unsigned)lane_id()) * (G * 4u); };
     const int h4 = p.H >> 2;
 
-    if (PAIR && helper) {
+    if constexpr (PAIR) if (helper) {
         // ---- helpers: W_hh of both layers times the candidate vectors ------------------------
         RegW<LREGS> w0, w1;
         const float *src = p.w_help + (long long)(x.rank * kResWaves + x.wave) * (2 * LREGS) * 64;
         load_regs(w0, src, 0, lane0);
         load_regs(w1, src, LREGS, lane0);
         announce();
-        // A helper XCD works for kResServed teams, in the order in which their vectors come: it needs 3 us for
-        // both layers of a step that takes the chain 7 to 10.
-        __amdgpu_buffer_rsrc_t bufs[kResServed];
-        unsigned step[2 * kResServed];             // of team i: step number, and the layer that comes next
+        // A helper XCD works for kResServed teams, in the order in which their vectors come (the second layer's first, which
+        // are needed sooner).  Every wave asks for its eighth of each team's next vector straight into LDS, and while
+        // these loads are on their way from the memory side (1.2 us) the work-group computes what came before:
+        // 1.6 us a team's step, 3.8 when a wave waited for its loads before it asked again.
+        if (tid0 < kResUnits * 4)
+            for (int l = 0; l < 2; ++l) rc.sh[l][tid0] = x.rank * p.pl.units * 4 + tid0 < p.H * 4 ? p.s_hh[l][x.rank * p.pl.units * 4 + tid0] : 0.f;
+        unsigned step[kResServed], layer[kResServed];            // of team i: step number and layer of the next vector
         unsigned live = 0;
 #pragma unroll
         for (int i = 0; i < kResServed; ++i) {
-            step[2 * i] = 1; step[2 * i + 1] = 0;
-            bufs[i] = buffers_of(serves(i) ? team + i * helper_xcds : team);
+            step[i] = 1; layer[i] = 0;
             if (serves(i)) { (void)meet(team + i * helper_xcds, false); live |= 1u << i; }
         }
         __syncthreads();
-        constexpr int N = (kResRows * (W / 4) + kResThreads - 1) / kResThreads;
-        const unsigned inv = piece_inverse(h4);
-        // LDS: partial sums of the teams' stages, then the rows of their vectors
-        constexpr int XR = kResServed * kResWaves * 1024;
-        static_assert(XR + kResServed * kResRows * XROW <= lo.bytes, "the helpers' layout fits");
-        unsigned spins = 0, par = 0;
+        // LDS: partial sums of a stage (two, in turn), then what a wave has asked for, [wave][team][block][lane]
+        constexpr int SUMS = kResWaves * R * kResStageRow * 4, AREA = kResServed * NB * 1024;
+        static_assert(2 * SUMS + kResWaves * AREA <= lo.bytes, "the helpers' layout fits");
+        const unsigned area = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds + 2 * SUMS + x.wave * AREA;
+        auto ask = [&](int i) {
+            const unsigned at = (layer[i] ? bo.hr[1] : bo.hr[0]) + slot_at(step[i], VSLOT);
+            const unsigned char *base = p.xbuf + (size_t)(team + i * helper_xcds) * bo.bytes + at;
+            const int lane = lane_id();
+            if (Op::takes(lane, p.slots)) {
+#pragma unroll
+                for (int k = 0; k < NB; ++k) {
+                    const unsigned to = (unsigned)__builtin_amdgcn_readfirstlane((int)(area + (unsigned)((i * NB + k) * 1024)));
+                    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 sc1"
+                                 :: "v"(Op::offset(k, x.wave, lane, h4)), "s"(to), "s"(base) : "memory");
+                }
+            }
+        };
+        auto answer = [&](int i, r4u (&v)[NB]) {
+#pragma unroll
+            for (int k = 0; k < NB; ++k) v[k] = *reinterpret_cast<const r4u *>(lds + 2 * SUMS + x.wave * AREA + (i * NB + k) * 1024 + lane_id() * 16);
+        };
+        unsigned spins = 0, par = 0, buffer = 0;
+        bool stored = false;                       // results were stored after the last loads were asked for
+#pragma unroll
+        for (int i = 0; i < kResServed; ++i)
+            if (live >> i & 1u) ask(i);
         while (live != 0u && rc.ok) {
-            r4u v[kResServed][N];
-            const unsigned tid = (unsigned)(x.wave * 64 + lane_id());
+            // the loads, without the stores behind them (which take their time to the memory side as well)
+            if (stored) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(G * 2) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            stored = false;
             unsigned f = 0;                        // bits 0 ..: team i's vector is complete; bits 8 ..: it says stop
 #pragma unroll
             for (int i = 0; i < kResServed; ++i)
                 if (live >> i & 1u) {
-                    x.buf = bufs[i];
-                    const unsigned at = bo.hr[0] + step[2 * i + 1] * (bo.hr[1] - bo.hr[0]) + RES_SLOT(step[2 * i]) * VSLOT;
+                    r4u v[NB];
+                    answer(i, v);
                     bool missing = false;
 #pragma unroll
-                    for (int k = 0; k < N; ++k) v[i][k] = get4(x, piece_offset<W>(piece_index(tid, k, p.slots * h4), inv, h4), at);
-#pragma unroll
-                    for (int k = 0; k < N; ++k) missing = missing || has_mark(v[i][k]);
-                    if (__ballot(missing) == 0ull) f |= 1u << i | (__ballot(v[i][0].x == kStop) != 0ull ? 256u << i : 0u);
+                    for (int k = 0; k < NB; ++k) missing = missing || has_mark(v[k]);
+                    if (__ballot(missing) == 0ull) f |= 1u << i | (__ballot(v[0].x == kStop) != 0ull ? 256u << i : 0u);
                 }
             if (lane_id() == 0) rc.seen[par][x.wave] = f;
             __syncthreads();
@@ -597,48 +725,54 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             all = (unsigned)__builtin_amdgcn_readfirstlane((int)all) & live;
             any = (unsigned)__builtin_amdgcn_readfirstlane((int)any);
             par ^= 1u;
+            live &= ~(all & (any >> 8));
+            const unsigned todo = all & live;
+#pragma unroll
+            for (int i = 0; i < kResServed; ++i)
+                if ((live & ~todo) >> i & 1u) ask(i);
             if (all == 0u) {
                 if (wait_expired(p, spins)) rc.ok = 0;
                 continue;
             }
             spins = 0;
-            unsigned todo = all & ~(any >> 8);
-            live &= ~(all & (any >> 8));
-            // the vectors that are here go to LDS; the second layers' first, which are needed sooner
             unsigned second = 0;
 #pragma unroll
-            for (int i = 0; i < kResServed; ++i)
-                if (todo >> i & 1u) {
-                    second |= step[2 * i + 1] << i;
+            for (int i = 0; i < kResServed; ++i) second |= layer[i] << i;
+            static_for<0, 2 * kResServed>([&](auto n_) {
+                constexpr int i = decltype(n_)::value % kResServed, l = decltype(n_)::value < kResServed ? 1 : 0;
+                if ((todo >> i & 1u) != 0u && (second >> i & 1u) == (unsigned)l) {
+                    Op op;
+                    {
+                        r4u v[NB];
+                        answer(i, v);
+                        op.set(v, lane_id());
+                    }
+                    const unsigned n = step[i];
+                    step[i] += l; layer[i] = l ^ 1;
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (read before it is written again)
+                    ask(i);
+                    float *sums = reinterpret_cast<float *>(lds + buffer * SUMS);
+                    buffer ^= 1u;
+                    stage<BF, CLS, R, 5, kResStageRow>(l ? w1 : w0, op, sums, x.wave);
+                    __syncthreads();
+                    if (has_cells) {
+                        const int lane = lane_id();
+                        float o[G];
+                        stage_sum<R>(sums, x.wave, lane, o);
+                        const float *sc = &rc.sh[l][(x.wave * 4 + (lane >> 4)) * 4 + (lane & (LR - 1)) * G];
+                        x.buf = buffers_of(team + i * helper_xcds);
 #pragma unroll
-                    for (int k = 0; k < N; ++k) {
-                        const unsigned idx = piece_index(tid, k, p.slots * h4), r = piece_row(idx, inv);
-                        x_put<BF>(lds + XR + (i * kResRows + r) * XROW, (int)(idx - __umul24(r, (unsigned)h4)), v[i][k]);
+                        for (int e = 0; e < G; ++e) {
+                            if (!BF) o[e] *= sc[e];
+                            put_far(x, prelane() + e * 4u, bo.pre + l * kResSlots * PSLOT + slot_at(n, PSLOT), word_of(o[e]));
+                            put_far(x, prelane() + e * 4u, bo.pre + l * kResSlots * PSLOT + slot_at(n + 2, PSLOT), kMark);
+                        }
+                        stored = true;
                     }
                 }
-            __syncthreads();
-            while (todo != 0u) {
-                const unsigned t = (unsigned)__builtin_ctz(second & todo ? second & todo : todo);
-                todo &= ~(1u << t);
-                unsigned n = 0, layer = 0;
-#pragma unroll
-                for (unsigned i = 0; i < kResServed; ++i)
-                    if (t == i) {
-                        x.buf = bufs[i];
-                        n = step[2 * i]; layer = step[2 * i + 1];
-                        step[2 * i] += layer; step[2 * i + 1] = layer ^ 1u;
-                    }
-                const unsigned char *xr = lds + XR + t * kResRows * XROW;
-                float *sums = reinterpret_cast<float *>(lds) + t * kResWaves * 256;
-                if (layer == 0) lstm_stage<BF, CLS>(w0, xr, h4, sums, x.wave, lane_id());
-                else lstm_stage<BF, CLS>(w1, xr, h4, sums, x.wave, lane_id());
-                __syncthreads();
-                if (has_cells) {
-                    put_far(x, prelane(), bo.pre + (layer * kResSlots + RES_SLOT(n)) * PSLOT, word_of(stage_sum(sums, x.wave, lane_id())));
-                    put_far(x, prelane(), bo.pre + (layer * kResSlots + RES_SLOT(n + 2)) * PSLOT, kMark);
-                }
-            }
+            });
         }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (nothing is on its way into LDS when the work-group ends)
         if (!rc.ok && threadIdx.x == 0) __hip_atomic_fetch_or(p.status, 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
@@ -669,7 +803,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         }
         const int q = pos / n_teams, m = pos - q * n_teams;
         if (((q & 1) ? n_teams - 1 - m : m) == team) {
-            rc.list_b[q] = b; rc.list_len[q] = len;
+            rc.list_b[q] = (unsigned short)b; rc.list_len[q] = len;
             if (len > 0) atomicAdd(&rc.n_list, 1);       // the empty ones are the last of the list
             else if (x.rank == 0) res_finish_row(b, 0);
         }
@@ -682,14 +816,23 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     const bool dur_cols = p.tdt && p.VT < p.pl.nout_m && x.rank * 32 + 32 > p.VT;      // they hold duration columns
     if (tid0 < kResUnits * 4) rc.b1[tid0] = (NL > 1 && tid0 < nu * 4) ? p.bias_l[((long long)p.H + u0) * 4 + tid0] : 0.f;
     if (tid0 < 20) rc.bp[tid0] = tid0 < njg * 4 ? p.b_pred[g0 * 4 + tid0] : 0.f;
-    if (tid0 < 32) rc.bo[tid0] = x.rank * 32 + tid0 < p.pl.nout_m ? p.b_out[x.rank * 32 + tid0] : 0.f;
+    if (tid0 < 32) reinterpret_cast<float *>(rc.bo)[tid0] = x.rank * 32 + tid0 < p.pl.nout_m ? p.b_out[x.rank * 32 + tid0] : 0.f;
     if (tid0 == 0) rc.bt = has_tail ? p.b_out[tcol] : 0.f;
+    if (tid0 < kResUnits * 4) {
+        const bool mine = tid0 < nu * 4;
+        rc.s1[tid0] = NL > 1 && mine ? p.s_ih[u0 * 4 + tid0] : 0.f;
+        for (int l = 0; l < NREC; ++l) rc.sh[l][tid0] = mine ? p.s_hh[l][u0 * 4 + tid0] : 0.f;
+    }
+    if (tid0 < 20) rc.sp[tid0] = tid0 < njg * 4 ? p.s_pred[g0 * 4 + tid0] : 0.f;
     if (has_tail)
         for (int i = tid0; i < ROW; i += kResThreads) {
             const float w = p.w_tail[(long long)x.rank * ROW + i];
-            // (bfloat16 mode: bf16 values, followed by as many zeros)
-            if (BF) reinterpret_cast<unsigned short *>(lds + lo.tail)[i] = (unsigned short)(__float_as_uint(w) >> 16);
-            else reinterpret_cast<float *>(lds + lo.tail)[i] = w;
+            // (rows of 16-bit values: high parts, low parts, zeros; or bf16 values, zeros; or rows of fp32 values, zeros)
+            unsigned short *row = reinterpret_cast<unsigned short *>(lds + lo.tail);
+            unsigned high = __float_as_uint(w) >> 16, low = 0;
+            if (!BF) f16_parts(w, 0.f, high, low);
+            if (WHOLE) reinterpret_cast<float *>(row)[i] = w;
+            else { row[i] = (unsigned short)high; row[ROW + i] = (unsigned short)low; }
         }
     // What a lane finishes in the LSTM stages, see stage_sum: a row of the team, a unit and a gate.  Worked
     // out where it is used: kept for the whole loop, values like these take the registers that the
@@ -697,7 +840,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     struct Place { int row, j, lu, gu; bool ok; };
     auto place_of = [&](int lane) {
         Place l;
-        l.row = (lane >> 2) & 3; l.j = lane & 3;
+        l.row = (lane / LR) & (R - 1); l.j = lane & (LR - 1);
         l.lu = x.wave * 4 + (lane >> 4);
         l.ok = l.lu < nu && l.j == 0 && l.row < p.slots;      // the lanes that publish it
         l.gu = min(u0 + l.lu, p.H - 1);
@@ -727,23 +870,52 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         f.inv_t = 0xffffffffu / (unsigned)f.la + 1u;
         return f;
     };
-    constexpr int QS = ROW + 16;                     // floats per q row
-    float *lq = reinterpret_cast<float *>(lds + lo.q);
+    constexpr int QS = res_q_row(CLS);               // floats per row of a wave's eighth of q
+    float *lq = reinterpret_cast<float *>(lds + lo.q) + x.wave * (R * QS);
     const unsigned lds_p = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)(lds + lo.p);
     float *part = reinterpret_cast<float *>(lds + lo.part);          // joint sums, see there
     float *tpart = reinterpret_cast<float *>(lds + lo.tpart);        // [wave][tile][16]
-    float *g4 = reinterpret_cast<float *>(lds + lo.g4);              // [row group][wave][lane][row]
+    float *sums_pr = reinterpret_cast<float *>(lds + lo.proj), *sums_ih = reinterpret_cast<float *>(lds + lo.ih);
+    float *sums_rec0 = reinterpret_cast<float *>(lds + lo.rec0), *sums_top = reinterpret_cast<float *>(lds + lo.rec);
+
+    // fp32: the power of two that takes the bound max P + max |q| of the launch to 2^14 .. 2^15, which the joint step's
+    // operand, and q in LDS, is multiplied by.  (Of a call with an infinite P the finite ones count, see the joint step.)
+    float z_scale = 1.f;
+    bool huge = false;
+    if constexpr (!BF && !WHOLE) {
+        static_assert(kTopWords == 64, "one for every lane");
+        TopWord top = p.p_top[lane0 * kTopStride];
+        const TopWord inf = p.p_top[lane0 * kTopStride + 1];
+#pragma unroll
+        for (int i = 32; i; i >>= 1) top = max(top, (TopWord)__shfl_xor(top, i));
+        huge = __ballot(inf >> 16 == top >> 16 && (inf & 1u) != 0u) != 0ull;
+        const float bound = fminf(__uint_as_float((unsigned)top << 16) + p.q_bound, 1e38f);
+        z_scale = __uint_as_float((unsigned)__builtin_amdgcn_readfirstlane((int)((268u << 23) - max(__float_as_uint(bound) & 0x7f800000u, 27u << 23))));
+        if (x.rank == 0 && team == 0 && tid0 == 0) ++p.p_top[kTopWords * kTopStride];        // (of those here nobody reads it)
+    }
+    const float back = __uint_as_float(0x7f000000u - __float_as_uint(z_scale));       // 1 / z_scale
+    if (tid0 < 32) reinterpret_cast<float *>(rc.so)[tid0] = x.rank * 32 + tid0 < p.pl.nout_m ? p.s_out[x.rank * 32 + tid0] * back : 0.f;
+    if (tid0 == 0) rc.st = has_tail ? p.s_out[tcol] * back : 0.f;
 
     announce();
     x.local = meet(team, PAIR);
     bool ok = rc.ok != 0;
 
-    // state of the lane's cell, [layer]: committed and candidate cell value, recurrent pre-activation
-    // W_hh h of the committed vector (that of the candidate is in the stage's sums, or comes from the helpers)
-    float cs[NL], cc[NL], ps[NL];
+    // state of the lane's cell, [layer]: committed and candidate cell value; recurrent pre-activations W_hh h of the
+    // committed vector and (pre, see HOLD; kResident2Pair: as far as they are there, kMark where not) of the last
+    // step's candidate
+    // (kResident2Pair, four rows: in LDS, where the others have their recurrent sums; the weights need the registers)
+    constexpr bool STORED = PAIR && R == 4;
+    float *state = reinterpret_cast<float *>(lds + lo.state);
+    auto stored = [&](int field) { return state + (field * 5 + x.wave) * 64 + lane_id(); };
+    float cs[NL], cc[NL], ps[NL][G];
+    unsigned pre[NL][G];
 #pragma unroll
-    for (int l = 0; l < NL; ++l) cs[l] = cc[l] = ps[l] = 0.f;
-    float *sums_ih = reinterpret_cast<float *>(lds + lo.ih), *sums_rec = reinterpret_cast<float *>(lds + lo.rec), *sums_rec2 = sums_rec + (NREC - 1) * kResWaves * 256;     // (the top layer's)
+    for (int l = 0; l < NL; ++l) {
+        cs[l] = cc[l] = 0.f;
+#pragma unroll
+        for (int i = 0; i < G; ++i) { ps[l][i] = 0.f; pre[l][i] = 0u; }
+    }
     unsigned n_pred = 0, n_joint = 0;
 
     RRows &rows = rc.rows[x.wave];
@@ -753,13 +925,13 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // of the projected frames, -1 for none.
     int last = p.blank, pidx = -1;
     // What a lane needs of the loop control's tables, packed (a register each would be one too many): the
-    // sample's row (2 bits) and place (4), its own row's first sample (5), the word of a row of T0 that
+    // sample's row (3 bits) and place (4), its own row's first sample (5), the word of a row of T0 that
     // its cell takes (12); kTake and kFresh.
     int lane_const = kFresh;
     auto pack_lane = [&](const Frames &f, int lane) {
-        const int srow = min(f.row_of(lane & (kResSamples - 1)), kResRows - 1), si = (lane - srow * f.la) & 15;
+        const int srow = min(f.row_of(lane & (kResSamples - 1)), R - 1), si = (lane - srow * f.la) & 15;
         const Place l = place_of(lane);
-        lane_const = srow | si << 2 | (l.row * f.la) << 6 | (l.gu * 4 + l.j) << 11 | (lane_const & (kTake | kFresh));
+        lane_const = srow | si << 3 | (min(l.row, p.slots - 1) * f.la) << 7 | (l.gu * 4 + l.j * G) << 12 | (lane_const & (kTake | kFresh));
     };
     std::integral_constant<int, NMT> all_tiles;
     const Frames f_all = frames_of(all_tiles);
@@ -769,10 +941,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     unsigned long long fresh = 0;
     auto set_up_samples = [&](const Frames &f, int lane, int t, int m, int b, int len) {
         const int la = f.la, ns = f.ns;
-        const int from = (lane_const & 3) << 4;                                     // (bytes: four lanes per row)
+        const int from = (lane_const & 7) * (LR * 4);                               // (bytes: LR lanes per row)
         const int base = __builtin_amdgcn_ds_bpermute(from, b * p.T + t);
         const int info = __builtin_amdgcn_ds_bpermute(from, max(0, min(len - t, la)) | m << 8);
-        int off = ((lane_const >> 2) & 15) - (info >> 8);
+        int off = ((lane_const >> 3) & 15) - (info >> 8);
         if (off < 0) off += la;
         const int was = pidx;
         pidx = (lane < ns && off < (info & 255)) ? base + off : -1;
@@ -780,11 +952,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         n_samples += __popcll(__ballot(pidx >= 0));
     };
     // Rows that want one get the next utterances of the list.  (Control state is by row: every lane works on
-    // row lane / 4 % 4, and lanes 0, 4, 8, 12 stand for the rows in ballots.)
+    // row lane / LR % R, and the first of LR lanes below 16 stands for its row in ballots.)
+    constexpr unsigned long long LEADS = R == 4 ? 0x1111ull : 0x5555ull;
     auto refill = [&](int lane, bool want, int &b, int &len) {
-        const unsigned long long m = __ballot(want) & 0x1111ull;
+        const unsigned long long m = __ballot(want) & LEADS;
         if (m == 0ull) return false;
-        const int next = rows.next, at = next + __popcll(m & ((1ull << (lane & 12)) - 1ull));
+        const int next = rows.next, at = next + __popcll(m & ((1ull << (lane & (16 - LR))) - 1ull));
         const bool got = want && at < rc.n_list;
         if (got) { b = rc.list_b[at]; len = rc.list_len[at]; }
         rows.next = next + __popcll(m);
@@ -794,28 +967,47 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     bool any_active, need_pred;
     {
         int b = 0, len = 0;
-        const int r = (lane0 >> 2) & 3;
+        const int r = (lane0 / LR) & (R - 1);
         const bool got = refill(lane0, r < p.slots, b, len);
         if (got) { rows.b[r] = b; rows.s[r].len = len; }
-        const unsigned long long m = __ballot(got) & 0x1111ull;
+        const unsigned long long m = __ballot(got) & LEADS;
         any_active = need_pred = m != 0ull;
         row_steps = __popcll(m);
         set_up_samples(f_all, lane0, 0, 0, b, len);
     }
     // the row of the embedding table (folded into the first layer) that the next prediction step adds
-    float t0 = 0.f;
+    float t0[G];
     const unsigned t0_row = (unsigned)p.H * 16u;
     auto load_t0 = [&]() {
-        t0 = 0.f;
-        if (has_cells) t0 = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(p.T0) + (__umul24((unsigned)last, t0_row) + ((unsigned)lane_const >> 9 & 0x3ffcu)));
-    };
-    // kResident2Pair: W_hh h of the last step's candidates as far as it is there, kMark where not
-    unsigned pre[2] = {0u, 0u};
-    auto load_pre = [&](unsigned n, unsigned (&to)[2]) {
-        const unsigned slot = bo.pre + RES_SLOT(n) * PSLOT;
 #pragma unroll
-        for (int l = 0; l < 2; ++l) to[l] = !has_cells ? 0u : get1(x, prelane(), slot + (unsigned)l * kResSlots * PSLOT);
+        for (int i = 0; i < G; ++i) t0[i] = 0.f;
+        if (has_cells) {
+            const char *from = reinterpret_cast<const char *>(p.T0) + (__umul24((unsigned)last, t0_row) + ((unsigned)lane_const >> 10 & 0x3ffcu));
+            if constexpr (G == 1) t0[0] = *reinterpret_cast<const float *>(from);
+            else { const float2 v = *reinterpret_cast<const float2 *>(from); t0[0] = v.x; t0[G - 1] = v.y; }
+        }
     };
+    // kResident2Pair: W_hh h of the last step's candidates of a layer as far as it is there
+    auto load_pre = [&](unsigned n, int l, unsigned (&to)[NL][G]) {
+        const unsigned slot = bo.pre + slot_at(n, PSLOT);
+#pragma unroll
+        for (int i = 0; i < G; ++i) to[l][i] = !has_cells ? 0u : get1(x, prelane() + i * 4u, slot + (unsigned)l * kResSlots * PSLOT);
+    };
+    auto no_pre = [&](int l) {
+        bool none = false;
+#pragma unroll
+        for (int i = 0; i < G; ++i) none = none || pre[l][i] == kMark;
+        return __ballot(none) != 0ull;
+    };
+    auto wait_pre = [&](unsigned n, int l) {
+        unsigned spins = 0;
+        while (no_pre(l)) {
+            if (wait_expired(p, spins)) { rc.ok = 0; break; }
+            load_pre(n, l, pre);
+        }
+        x.polls += __builtin_amdgcn_readfirstlane((int)spins);
+    };
+    for (int i = 0; i < G; ++i) t0[i] = 0.f;
     if (need_pred) load_t0();
 #ifdef RNNT_PROFILE
     if (tid0 == 0) { for (int i = 0; i < 24; ++i) res_prof[i] = 0; res_prof_last = wall_clock64(); }
@@ -829,51 +1021,76 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     bool change = false;
     // (Two teams of short steps keep their helpers busy: half the results come after the control's start has
     // asked for them, and one more round trip costs 1.3 us; asked for again at its end, 0.16 us a step less.)
-    unsigned later[2] = {kMark, kMark};
+    unsigned later[NL][G];
+#pragma unroll
+    for (int l = 0; l < NL; ++l)
+#pragma unroll
+        for (int i = 0; i < G; ++i) later[l][i] = kMark;
     while (ok && any_active && !change) {
-        if (!need_pred)
-            for (int s = x.wave; s < ns; s += kResWaves)
-                if (fresh >> s & 1) load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
         if (need_pred) {
             // ---- prediction step -----------------------------------------------------------------
             ++n_pred;
             const unsigned n = n_pred;
             if (PAIR && n > 1) {
-                unsigned spins = 0;
-                if (NT < NMT && __ballot(pre[0] == kMark || pre[1] == kMark) != 0ull) { pre[0] = later[0]; pre[1] = later[1]; }
-                while (__ballot(pre[0] == kMark || pre[1] == kMark) != 0ull) {
-                    if (wait_expired(p, spins)) { rc.ok = 0; break; }
-                    load_pre(n - 1, pre);
+                if (NT < NMT && no_pre(0)) {
+#pragma unroll
+                    for (int l = 0; l < NL; ++l)
+#pragma unroll
+                        for (int i = 0; i < G; ++i) pre[l][i] = later[l][i];
                 }
-                x.polls += __builtin_amdgcn_readfirstlane((int)spins);
+                wait_pre(n - 1, 0);
             }
             RES_MARK(0);
+            if constexpr (STORED) {
+#pragma unroll
+                for (int l = 0; l < NL; ++l) {
+                    cs[l] = cc[l] = ps[l][0] = 0.f;
+                    if (has_cells) { cs[l] = *stored(l * 3); cc[l] = *stored(l * 3 + 1); ps[l][0] = *stored(l * 3 + 2); }
+                }
+            }
             // rows that emitted take their candidate state, fresh rows start from zero (kResident2: the second
-            // layer's while the first one's vector is on its way)
+            // layer's while the first one's vector is on its way; kResident2Pair: not before its own cell, the helpers
+            // have till then)
+            // a stage's sums for the lane, as they are to be used
+            auto sums_of = [&](const float *sums, const float *scales, float (&v)[G]) {
+                const int lane = lane_id();
+                stage_sum<R>(sums, x.wave, lane, v);
+#pragma unroll
+                for (int i = 0; i < G; ++i)
+                    if (!BF) v[i] *= scales[(x.wave * 4 + (lane >> 4)) * 4 + (lane & (LR - 1)) * G + i];
+            };
             auto commit = [&](int l) {
-                float pc = 0.f;
-                if (PAIR) pc = __uint_as_float(pre[l]);
-                else if (has_cells) pc = stage_sum(l == NL - 1 ? sums_rec2 : sums_rec, x.wave, lane_id());
+                float pc[G];
+#pragma unroll
+                for (int i = 0; i < G; ++i) pc[i] = __uint_as_float(pre[l][i]);
+                if constexpr (!HOLD) {
+                    if (has_cells) sums_of(l == NL - 1 ? sums_top : sums_rec0, rc.sh[l], pc);
+                }
                 const bool take = lane_const & kTake, fresh_row = lane_const & kFresh;       // (bits: as a chain of comparisons it became branches)
                 cs[l] = take ? cc[l] : cs[l]; cs[l] = fresh_row ? 0.f : cs[l];
-                ps[l] = take ? pc : ps[l]; ps[l] = fresh_row ? 0.f : ps[l];
+#pragma unroll
+                for (int i = 0; i < G; ++i) {
+                    ps[l][i] = take ? pc[i] : ps[l][i]; ps[l][i] = fresh_row ? 0.f : ps[l][i];
+                }
             };
             commit(0);
-            if constexpr (PAIR) commit(1);       // (here: its load came before the stores below, and waits end in order)
             // publishes the lane's hidden value of a layer and clears the slot of two steps ago
             auto publish_h = [&](int layer, const Place &l, float h) {
                 if (l.ok) {
-                    const unsigned o = (unsigned)l.row * VROW + (unsigned)l.gu * 4u;
-                    const unsigned s1 = RES_SLOT(n) * VSLOT, s2 = RES_SLOT(n + 2) * VSLOT;
-                    put(x, o, bo.h[layer] + s1, bo.h[layer] + s2, word_of(h));
-                    if (PAIR) { put_far(x, o, bo.hr[layer] + s1, word_of(h)); put_far(x, o, bo.hr[layer] + s2, kMark); }
+                    const unsigned o = (unsigned)l.row * VROW + (unsigned)l.gu * 4u, v = hidden_word<BF>(h);
+                    const unsigned s1 = slot_at(n, VSLOT), s2 = slot_at(n + 2, VSLOT);
+                    put(x, o, bo.h[layer] + s1, bo.h[layer] + s2, v);
+                    if (PAIR) { put_far(x, o, bo.hr[layer] + s1, v); put_far(x, o, bo.hr[layer] + s2, kMark); }
                 }
             };
             if (has_cells) {
                 const Place l = place_of(lane_id());
-                float h;
-                cell(ps[0] + t0, l.j, cs[0], cc[0], h);
+                float h, v[G];
+#pragma unroll
+                for (int i = 0; i < G; ++i) v[i] = ps[0][i] + t0[i];
+                cell<G>(v, l.j, cs[0], cc[0], h);
                 publish_h(0, l, h);
+                if constexpr (STORED) { *stored(0) = cs[0]; *stored(1) = cc[0]; *stored(2) = ps[0][0]; }
             }
             if constexpr (NREC > 1) commit(1);
             // The frames of the joint step, by the waves that have the least to do here.  A wave's loads return in
@@ -882,172 +1099,253 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 for (int s = x.wave - 5; s < ns; s += kResWaves - 5)
                     if (fresh >> s & 1) load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
             RES_MARK(1);
-            unsigned char *x0 = lds + lo.xh, *x1 = lds + lo.xh + (NL - 1) * kResRows * XROW;
-            receive_rows<W>(p, x, bo.h[0] + RES_SLOT(n) * VSLOT, p.slots, h4, [&](int r, int k4, r4u v) { x_put<BF>(x0 + r * XROW, k4, v); });
-            __syncthreads();
+            Op x1;
+            x1.receive_from(p, x, bo.h[0] + slot_at(n, VSLOT), h4);
             RES_MARK(2);
             if constexpr (NL > 1) {
-                lstm_stage<BF, CLS>(w_ih, x0, h4, sums_ih, x.wave, lane_id());
+                const Op x0 = x1;
+                // The second layer's results, if they were not there, are asked for again, to come during the stage; to
+                // registers of their own, for what waits for them waits for the stores before them as well.
+                const bool again = PAIR && n > 1 && no_pre(NL - 1);
+                unsigned second[NL][G];
+                if (again) load_pre(n - 1, NL - 1, second);
+                stage<BF, CLS, R, 5, kResStageRow>(w_ih, x0, sums_ih, x.wave);
                 __syncthreads();
                 RES_MARK(3);
+                if constexpr (PAIR) {
+                    if (again) {
+#pragma unroll
+                        for (int i = 0; i < G; ++i) pre[NL - 1][i] = second[NL - 1][i];
+                        wait_pre(n - 1, NL - 1);
+                    }
+                    commit(NL - 1);
+                }
                 if (has_cells) {
-                    const int lane = lane_id();
-                    const Place l = place_of(lane);
-                    float h;
-                    cell(stage_sum(sums_ih, x.wave, lane) + (ps[1] + rc.b1[l.lu * 4 + l.j]), l.j, cs[1], cc[1], h);
+                    const Place l = place_of(lane_id());
+                    float h, v[G];
+                    sums_of(sums_ih, rc.s1, v);
+#pragma unroll
+                    for (int i = 0; i < G; ++i) v[i] += ps[1][i] + rc.b1[l.lu * 4 + l.j * G + i];
+                    cell<G>(v, l.j, cs[1], cc[1], h);
                     publish_h(1, l, h);
+                    if constexpr (STORED) { *stored(3) = cs[1]; *stored(4) = cc[1]; *stored(5) = ps[1][0]; }
                 }
                 RES_MARK(4);
                 // (while the hand-over is on its way) the recurrent part of the next step's first layer
-                if constexpr (NREC > 1) lstm_stage<BF, CLS>(w_hh[0], x0, h4, sums_rec, x.wave, lane_id());
+                if constexpr (NREC > 1) stage<BF, CLS, R, 5, kResStageRow>(w_hh[0], x0, sums_rec0, x.wave);
                 RES_MARK(5);
-                receive_rows<W>(p, x, bo.h[1] + RES_SLOT(n) * VSLOT, p.slots, h4, [&](int r, int k4, r4u v) { x_put<BF>(x1 + r * XROW, k4, v); });
-                __syncthreads();
+                x1.receive_from(p, x, bo.h[1] + slot_at(n, VSLOT), h4);
             }
             RES_MARK(6);
-            // prediction-side joint projection: a wave's blocks are five groups of four columns times three slices of K;
-            // partial sums through LDS
+            // prediction-side joint projection
+            stage<BF, CLS, R, 2, kResSumRow>(w_pr, x1, sums_pr, x.wave);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's frames are in LDS
+            __syncthreads();
             {
-                constexpr int NP = res_pred_pieces(CLS);
-                {
-                    const int lane = lane_id(), sl = ((lane >> 2) * 13) >> 6;        // block / 5
-                    const unsigned char *xl = x1 + (lane & 3) * XROW;
-                    Pc v[NP];
+                // LR adjacent threads per value (group of four columns, column, row), R / 2 waves' sums each
+                const int tid = (x.wave * 64 + lane_id()), col = tid >> 4, r = (tid / LR) & (R - 1);
+                if (col < njg * 4) {
+                    const float *v = sums_pr + ((tid & (LR - 1)) * (R / 2) * R + r) * kResSumRow + col;
+                    float o = v[0];
 #pragma unroll
-                    for (int i = 0; i < NP; ++i) v[i].load(xl + min(i * 24 + x.wave * 3 + sl, h4 - 1) * Pc::B);
-                    r4f a[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-                    for (int i = 0; i < NP; ++i)
-#pragma unroll
-                        for (int e = 0; e < Pc::N; ++e) v[i].mfma(e, &w_pr.w[i * PR], a[(i * Pc::N + e) & 1]);
-                    if (lane < 60) *reinterpret_cast<r4f *>(g4 + (x.wave * 60 + lane) * 4) = a[0] + a[1];
-                }
-                __syncthreads();
-                // four adjacent threads per value (group, column, row), two waves' sums each
-                const int tid = (x.wave * 64 + lane_id()), g = tid >> 6, j = (tid >> 4) & 3, r = (tid >> 2) & 3;
-                if (g < njg) {
-                    const float *v = g4 + ((tid & 3) * 120 + g * 4 + j) * 4 + r;
-                    const float bias = rc.bp[g * 4 + j];
-                    const float s = lane_sum<4>(((v[0] + v[80]) + v[160]) + ((v[240] + v[320]) + v[400]));
-                    if ((tid & 3) == 0 && r < p.slots)
-                        put(x, (unsigned)r * VROW + (unsigned)((g0 + g) * 4 + j) * 4u, bo.q + RES_SLOT(n) * VSLOT, bo.q + RES_SLOT(n + 2) * VSLOT, word_of(s + bias));
+                    for (int i = 1; i < R / 2; ++i) o += v[i * R * kResSumRow];
+                    o = lane_sum<LR>(o);
+                    o = BF ? o + rc.bp[col] : fmaf(o, rc.sp[col], rc.bp[col]);
+                    if ((tid & (LR - 1)) == 0 && r < p.slots)
+                        put(x, (unsigned)r * VROW + (unsigned)(g0 * 4 + col) * 4u, bo.q + slot_at(n, VSLOT), bo.q + slot_at(n + 2, VSLOT), word_of(o));
                 }
             }
             RES_MARK(7);
             // (while q is on its way) the recurrent part of the top layer's next step
-            if constexpr (NREC > 0) lstm_stage<BF, CLS>(w_hh[NREC - 1], x1, h4, sums_rec2, x.wave, lane_id());
+            auto keep_sums = [&](int l, const float *sums) {
+                if (has_cells) {
+                    float v[G];
+                    sums_of(sums, rc.sh[l], v);
+#pragma unroll
+                    for (int i = 0; i < G; ++i) pre[l][i] = __float_as_uint(v[i]);
+                }
+            };
+            if constexpr (NREC > 1 && HOLD) keep_sums(0, sums_rec0);
+            if constexpr (NREC > 0) {
+                stage<BF, CLS, R, 5, kResStageRow>(w_hh[NREC - 1], x1, sums_top, x.wave);
+                if constexpr (HOLD) {
+                    __syncthreads();
+                    keep_sums(NL - 1, sums_top);
+                }
+            }
             RES_MARK(8);
-            receive_rows<W>(p, x, bo.q + RES_SLOT(n) * VSLOT, p.slots, p.J >> 2, [&](int r, int k4, r4u v) {
-                *reinterpret_cast<r4u *>(lq + r * QS + k4 * 4) = v;
-            });
+            {
+                // the wave's eighth of q, NH * 4 pieces a row
+                constexpr int PW = NH * 4, N = (R * PW + 63) / 64;
+                constexpr unsigned INV = (65536u + PW - 1u) / PW;         // i / PW for i < 256
+                unsigned off[N];
+                r4u v[N];
+                const int lane = lane_id(), j4 = p.J >> 2;
+                auto index = [&](int i) { return (unsigned)min(lane + i * 64, p.slots * PW - 1); };
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    const unsigned at = index(i), r = __umul24(at, INV) >> 16;
+                    off[i] = r * VROW + (unsigned)min(x.wave * PW + (int)(at - r * PW), j4 - 1) * 16u;
+                }
+                receive<N>(p, x, off, bo.q + slot_at(n, VSLOT), v);
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    const unsigned at = index(i), r = __umul24(at, INV) >> 16;
+                    float4 o = __builtin_bit_cast(float4, v[i]);
+                    if (!BF && !WHOLE) o = make_float4(o.x * z_scale, o.y * z_scale, o.z * z_scale, o.w * z_scale);
+                    if (x.wave * PW + (int)(at - r * PW) < j4) *reinterpret_cast<float4 *>(lq + r * QS + (at - r * PW) * 4) = o;
+                }
+            }
             RES_MARK(9);
+        } else {
+            for (int s = x.wave; s < ns; s += kResWaves)
+                if (fresh >> s & 1) load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            RES_MARK(10);
         }
         // ---- joint step ----------------------------------------------------------------------------
         ++n_joint;
         const unsigned jn = n_joint;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the frames of this wave's samples are in LDS
-        __syncthreads();
-        RES_MARK(10);
         {
-            r4f acc[NT][2];                 // [tile of samples][column tile]
-            const int lane = lane_id(), m16 = lane & 15, kq = lane >> 4;
-            // Piece k4 = 32 ii + 4 wave + kq of sample m16: its low bits are the same for all steps.  The operand
-            // relu(P + q) is formed on the way: K is split over the waves, so nobody else needs it.  The
-            // vector instructions of a step come in one run before its matrix instructions: the fp32 ones share
-            // the vector pipe with them, and every change between the two costs some ten cycles.
-            const int k40 = x.wave * 4 + kq;
-            const unsigned char *pr = lds + lo.p + m16 * ROW * 4 + ((k40 & 16) | ((k40 ^ m16) & 15)) * 16;
-            const float *q[NT];
-#pragma unroll
-            for (int mt = 0; mt < NT; ++mt) {
-                acc[mt][0] = acc[mt][1] = (r4f){0.f, 0.f, 0.f, 0.f};
-                q[mt] = lq + min(f.row_of(mt * 16 + m16), kResRows - 1) * QS + k40 * 4;
-            }
-            auto fetch = [&](int ii, int mt, float4 &pv, float4 &qv) {
-                pv = *reinterpret_cast<const float4 *>(pr + mt * 16 * ROW * 4 + ii * 512);
-                qv = *reinterpret_cast<const float4 *>(q[mt] + ii * 128);
+            // A wave has an eighth of K for both column tiles, so the operand z = relu(P + q) of a lane's sample is
+            // formed on the way: nobody else needs it.  fp32: every product is that of two fp16 parts of
+            // either side (see z_scale; layers of 640: without low times low, which made the joint step 0.1 us longer and
+            // the logits' error 2 % smaller); products with a low part are summed apart from the others.
+            // (a half block comes first)
+            auto block_of = [](int b) { return NH % 2 != 0 ? (b + NB - 1) % NB : b % NB; };
+            auto form = [&](float p_, float q_) { return fmaxf(BF || WHOLE ? p_ + q_ : fmaf(p_, z_scale, q_), 0.f); };
+            auto relu = [&](float4 p_, float4 q_) { return make_float4(form(p_.x, q_.x), form(p_.y, q_.y), form(p_.z, q_.z), form(p_.w, q_.w)); };
+            // Where the lane's part of sample 16 mt + lane % 16 lies in the wave's eighth: of its frame and of its row's q,
+            // the first four words of block i (the second four: 16 in the address inverted, or added).
+            // Worked out anew for every tile: kept across all of them it takes registers that the weights need.
+            int m16, g, k40, frame0;
+            auto place_lane = [&]() {
+                const int lane = lane_id();
+                m16 = lane & 15; g = lane >> 4;
+                k40 = x.wave * (NH * 4) + 2 * g; frame0 = lo.p + (int)__umul24((unsigned)m16, ROW * 4u);
             };
-            if constexpr (BF) {
-                float4 pv, qv;
-                fetch(0, 0, pv, qv);
-                struct Q { float a, b; };
-                struct U { unsigned a, b; };
-                // the tail column as an operand of its own: its row mt is the weights for tile mt, the others are zeros
-                const unsigned char *wt = lds + lo.tail + k40 * 8;
-                r4f tacc = (r4f){0.f, 0.f, 0.f, 0.f};
+            auto frame_at = [&](int mt, int i) { return frame0 + ((k40 + i * 8 - (i < NF ? 0 : g)) ^ m16) * 16 + mt * 16 * ROW * 4; };
+            auto q_of = [&](int mt) {
+                const unsigned row = min(__umul24((unsigned)(mt * 16 + m16), f.inv_la) >> 10, (unsigned)(R - 1));
+                return lo.q + (int)__umul24(row, QS * 4u) + x.wave * (R * QS * 4) + g * 32;
+            };
+            auto q_at = [&](int of, int i) { return of + i * 128 - (i < NF ? 0 : g * 16); };
+            auto at = [&](int a) { return *reinterpret_cast<const float4 *>(lds + a); };
+            auto output = [&](auto tail_) {
+                constexpr bool TAIL = decltype(tail_)::value;
+                const r4f zero = {0.f, 0.f, 0.f, 0.f};
+                r4f big[2], small[2], tb, ts;                // (bfloat16 mode: big alone)
+                float4 pv[2], qv[2];
+                int qo = 0;
+                auto fetch = [&](int b) {
+                    const int mt = b / NB, i = block_of(b % NB);
+                    if (b % NB == 0) { place_lane(); qo = q_of(mt); }
+                    const int pa = frame_at(mt, i), qa = q_at(qo, i);
+                    pv[0] = at(pa); qv[0] = at(qa);
+                    if (i < NF && !TAIL) { pv[1] = at(pa ^ 16); qv[1] = at(qa + 16); }
+                };
+                fetch(0);
+                static_for<0, NB * NT>([&](auto b_) {
+                    constexpr int b = decltype(b_)::value, mt = b / NB, i = block_of(b % NB);
+                    constexpr bool FULL = i < NF;
+                    if constexpr (b % NB == 0) { big[0] = big[1] = small[0] = small[1] = tb = ts = zero; }
+                    unsigned zh[4], zl[4];
+                    if constexpr (FULL && TAIL) { pv[1] = at(frame_at(mt, i) ^ 16); qv[1] = at(q_at(qo, i) + 16); }      // (registers)
 #pragma unroll
-                for (int i = 0; i < NI * NT; ++i) {
-                    const int ii = i / NT, mt = i % NT;
-                    const r4s z = __builtin_bit_cast(r4s, U{bf16_pair(fmaxf(pv.x + qv.x, 0.f), fmaxf(pv.y + qv.y, 0.f)),
-                                                            bf16_pair(fmaxf(pv.z + qv.z, 0.f), fmaxf(pv.w + qv.w, 0.f))});
-                    if (i + 1 < NI * NT) fetch((i + 1) / NT, (i + 1) % NT, pv, qv);
-                    __builtin_amdgcn_sched_barrier(0);
+                    for (int j = 0; j < (FULL ? 2 : 1); ++j) {
+                        const float4 z = relu(pv[j], qv[j]);
+                        if constexpr (WHOLE) {
+                            zh[0] = __float_as_uint(z.x); zh[1] = __float_as_uint(z.y); zh[2] = __float_as_uint(z.z); zh[3] = __float_as_uint(z.w);
+                        } else if constexpr (BF) {
+                            zh[j * 2] = bf16_pair(z.x, z.y); zh[j * 2 + 1] = bf16_pair(z.z, z.w);
+                        } else {
+                            f16_parts(z.x, z.y, zh[j * 2], zl[j * 2]);
+                            f16_parts(z.z, z.w, zh[j * 2 + 1], zl[j * 2 + 1]);
+                        }
+                    }
+                    if constexpr (b + 1 < NB * NT) fetch(b + 1);
+                    ordered();
+                    if constexpr (BF) {
+                        // (the sums of the half block have to be there, see tile_mfma)
+                        if constexpr (NH % 2 != 0 && NF > 0 && b % NB == 1) {
+                            asm volatile("s_nop 15" : "+v"(big[0]), "+v"(big[1]));
+                            if (TAIL) asm volatile("" : "+v"(tb));
+                            ordered();
+                        }
+                    } else if constexpr (!WHOLE) {
+                        if constexpr (NF < 2) {
+#pragma unroll
+                            for (int c = 0; c < 2; ++c) small[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 1>(w_ou, c), zl, small[c]);
+                        }
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) small[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 0>(w_ou, c), zl, small[c]);
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) small[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 1>(w_ou, c), zh, small[c]);
+                    }
 #pragma unroll
                     for (int c = 0; c < 2; ++c) {
-                        const float *w = &w_ou.w[(ii * 2 + c) * PR];
-                        acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(r4s, Q{w[0], w[1]}), z, acc[mt][c], 0, 0, 0);
+                        if constexpr (WHOLE) big[c] = whole_mfma(w_ou.q[c], zh, big[c]);
+                        else big[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 0>(w_ou, c), zh, big[c]);
                     }
-                    if (has_tail) tacc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*reinterpret_cast<const r4s *>(wt + (m16 == mt ? 0 : ROW * 2) + ii * 256), z, tacc, 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                if (has_tail) {
+                    // the tail column: its high and low parts (bfloat16 mode: its values) are rows of their own of the
+                    // operand, the others zeros
+                    if constexpr (TAIL && WHOLE) {
+                        tb = whole_mfma(*reinterpret_cast<const r4f *>(lds + lo.tail + (min(m16, 1) * ROW + x.wave * 16 + g * 4) * 4), zh, tb);
+                    } else if constexpr (TAIL) {
+                        const auto w = *reinterpret_cast<const std::conditional_t<FULL, r4f, r2f> *>(lds + lo.tail + (min(m16, BF ? 1 : 2) * ROW + x.wave * (NH * 16) + i * 32 + g * (FULL ? 8 : 4)) * 2);
+                        if constexpr (!BF) ts = tile_mfma<BF>(w, zl, ts);
+                        tb = tile_mfma<BF>(w, zh, tb);
+                    }
+                    ordered();
+                    if constexpr (b % NB == NB - 1) {
+                        if constexpr (!BF && !WHOLE) {
+                            big[0] += small[0]; big[1] += small[1];
+                            if (TAIL) tb += ts;
+                        }
+                        if (TAIL && g == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = BF || WHOLE ? tb[0] : tb[0] + tb[1];
+                        // every wave's sums to LDS, [wave][sample][column]
+#pragma unroll
+                        for (int c = 0; c < 2; ++c)
+                            *reinterpret_cast<r4f *>(part + ((x.wave * NT + mt) * 16 + m16) * kResSumRow + c * 16 + g * 4) = big[c];
+                    }
+                });
+            };
+            if (has_tail) output(std::true_type());
+            else output(std::false_type());
+            if constexpr (!BF && !WHOLE) {
+                // An infinite z has no low part: there the high ones decide.
+                if (huge) {
 #pragma unroll
                     for (int mt = 0; mt < NT; ++mt)
-                        if (kq == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = tacc[mt];
-                }
-            } else {
-                const float *wt = reinterpret_cast<const float *>(lds + lo.tail) + k40 * 4;
-                float tl[NT];
 #pragma unroll
-                for (int mt = 0; mt < NT; ++mt) tl[mt] = 0.f;
-                float4 wv = *reinterpret_cast<const float4 *>(wt), pv[NT], qv[NT];
+                        for (int c = 0; c < 2; ++c) {
+                            place_lane();
+                            const int qo = q_of(mt);
+                            r4f high = {0.f, 0.f, 0.f, 0.f};
+                            float m = 0.f;
+                            static_for<0, NB>([&](auto k_) {
+                                constexpr int k = block_of(decltype(k_)::value);
+                                unsigned z[4];
 #pragma unroll
-                for (int mt = 0; mt < NT; ++mt) fetch(0, mt, pv[mt], qv[mt]);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int ii = 0; ii < NI; ++ii) {
-                    float z[NT][4];
-#pragma unroll
-                    for (int mt = 0; mt < NT; ++mt) {
-                        z[mt][0] = fmaxf(pv[mt].x + qv[mt].x, 0.f); z[mt][1] = fmaxf(pv[mt].y + qv[mt].y, 0.f);
-                        z[mt][2] = fmaxf(pv[mt].z + qv[mt].z, 0.f); z[mt][3] = fmaxf(pv[mt].w + qv[mt].w, 0.f);
-                        tl[mt] = fmaf(z[mt][3], wv.w, fmaf(z[mt][2], wv.z, fmaf(z[mt][1], wv.y, fmaf(z[mt][0], wv.x, tl[mt]))));
-                        // (the sums are opaque here: otherwise they move behind the loop, under the condition they are used
-                        // under, with every z kept in a register till then)
-                        asm volatile("" : "+v"(tl[mt]));
-                    }
-                    if (ii + 1 < NI) {
-#pragma unroll
-                        for (int mt = 0; mt < NT; ++mt) fetch(ii + 1, mt, pv[mt], qv[mt]);
-                        wv = *reinterpret_cast<const float4 *>(wt + (ii + 1) * 128);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-#pragma unroll
-                        for (int mt = 0; mt < NT; ++mt)
-#pragma unroll
-                            for (int c = 0; c < 2; ++c)
-                                acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w_ou.w[(ii * 2 + c) * 4 + e], z[mt][e], acc[mt][c], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                if (has_tail) {
-#pragma unroll
-                    for (int mt = 0; mt < NT; ++mt) {
-                        float a = tl[mt], b = tl[mt];
-                        swap32(a, b); a += b; b = a;
-                        swap16(a, b); a += b;
-                        if (lane < 16) tpart[(x.wave * 2 + mt) * 16 + lane] = a;
-                    }
+                                for (int j = 0; j < (k < NF ? 2 : 1); ++j) {
+                                    const float4 v = relu(at(frame_at(mt, k) ^ (j * 16)), at(q_at(qo, k) + j * 16));
+                                    z[j * 2] = f16_pair(v.x, v.y); z[j * 2 + 1] = f16_pair(v.z, v.w);
+                                    m = fmaxf(fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)), m);
+                                }
+                                asm volatile("s_nop 15" : "+v"(high));
+                                high = tile_mfma<BF>(weights_of<BF, CLS, 2, k, 0>(w_ou, c), z, high);
+                                ordered();
+                            });
+                            float o = m;
+                            swap32(m, o); m = fmaxf(m, o); o = m;
+                            swap16(m, o); m = fmaxf(m, o);
+                            if (m == INFINITY) *reinterpret_cast<r4f *>(part + ((x.wave * NT + mt) * 16 + m16) * kResSumRow + c * 16 + g * 4) = high;
+                        }
                 }
             }
             RES_MARK(11);
-            // every wave's sums to LDS, [wave][sample][column]; then sixteen lanes per sample, two columns each
-#pragma unroll
-            for (int mt = 0; mt < NT; ++mt)
-#pragma unroll
-                for (int c = 0; c < 2; ++c)
-                    *reinterpret_cast<r4f *>(part + ((x.wave * NT + mt) * 16 + m16) * kResSumRow + c * 16 + kq * 4) = acc[mt][c];
+            // sixteen lanes per sample, two columns each
             __syncthreads();
             const int tid = (x.wave * 64 + lane_id());
             if (tid < 16 * NT * 16) {
@@ -1056,12 +1354,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
 #pragma unroll
                 for (int w = 0; w < kResWaves; ++w)
                     o[w] = *reinterpret_cast<const float2 *>(part + (w * NT * 16 + s) * kResSumRow + col);
-                const float2 bias = *reinterpret_cast<const float2 *>(&rc.bo[col]);
+                const float2 bias = rc.bo[tid & 15], scale = rc.so[tid & 15];
                 static_assert(kResWaves == 8, "eight lanes add the waves' sums of the tail column");
                 float tw = 0.f;
                 if (has_tail) tw = tpart[((tid & 7) * 2 + (s >> 4)) * 16 + (s & 15)];
-                const float l0 = (((o[0].x + o[1].x) + (o[2].x + o[3].x)) + ((o[4].x + o[5].x) + (o[6].x + o[7].x))) + bias.x;
-                const float l1 = (((o[0].y + o[1].y) + (o[2].y + o[3].y)) + ((o[4].y + o[5].y) + (o[6].y + o[7].y))) + bias.y;
+                const float l0 = (((o[0].x + o[1].x) + (o[2].x + o[3].x)) + ((o[4].x + o[5].x) + (o[6].x + o[7].x))) * scale.x + bias.x;
+                const float l1 = (((o[0].y + o[1].y) + (o[2].y + o[3].y)) + ((o[4].y + o[5].y) + (o[6].y + o[7].y))) * scale.y + bias.y;
                 const float m0 = col < n_tok ? l0 : -INFINITY, m1 = col + 1 < n_tok ? l1 : -INFINITY;
                 const float mine = fmaxf(m0, m1);
                 float m = lane_max<16>(mine);
@@ -1071,11 +1369,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 int ix = hit ? (m0 == m ? gcol : gcol + 1) : 0x7fffffff;
                 float tail = -INFINITY;
                 if (has_tail) {
-                    tail = lane_sum<8>(tw) + rc.bt;
+                    tail = lane_sum<8>(tw) * rc.st + rc.bt;
                     if (tcol >= p.VT) {
                         if ((tid & 15) == 0 && s < ns) {
                             const unsigned d = ((unsigned)s * kMaxDur + (unsigned)(tcol - p.VT)) * 4u;
-                            put(x, d, bo.dur + RES_SLOT(jn) * DSLOT, bo.dur + RES_SLOT(jn + 2) * DSLOT, word_of(tail));
+                            put(x, d, bo.dur + slot_at(jn, DSLOT), bo.dur + slot_at(jn + 2, DSLOT), word_of(tail));
                         }
                         tail = -INFINITY;
                     } else if (tail > m) {
@@ -1088,18 +1386,18 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     for (int c = 0; c < 2; ++c)
                         if (gcol + c >= p.VT && gcol + c < p.pl.nout_m) {
                             const unsigned d = ((unsigned)s * kMaxDur + (unsigned)(gcol + c - p.VT)) * 4u;
-                            put(x, d, bo.dur + RES_SLOT(jn) * DSLOT, bo.dur + RES_SLOT(jn + 2) * DSLOT, word_of(c ? l1 : l0));
+                            put(x, d, bo.dur + slot_at(jn, DSLOT), bo.dur + slot_at(jn + 2, DSLOT), word_of(c ? l1 : l0));
                         }
                 }
                 const unsigned ko = ((unsigned)s * TS + (unsigned)x.rank) * 8u;
                 if ((tid & 15) == first && s < ns)
-                    put2(x, ko, bo.key + RES_SLOT(jn) * KSLOT, bo.key + RES_SLOT(jn + 2) * KSLOT, (r2u){word_of(m), (unsigned)ix});
+                    put2(x, ko, bo.key + slot_at(jn, KSLOT), bo.key + slot_at(jn + 2, KSLOT), (r2u){word_of(m), (unsigned)ix});
                 if (p.logps) {
                     float e = (m0 > -INFINITY ? expf(m0 - m) : 0.f) + (m1 > -INFINITY ? expf(m1 - m) : 0.f);
                     e = lane_sum<16>(e);
                     if (tail > -INFINITY) e += expf(tail - m);
                     if ((tid & 15) == 0 && s < ns)
-                        put(x, ko / 2, bo.lse + RES_SLOT(jn) * (KSLOT / 2), bo.lse + RES_SLOT(jn + 2) * (KSLOT / 2), word_of(e));
+                        put(x, ko / 2, bo.lse + slot_at(jn, KSLOT / 2), bo.lse + slot_at(jn + 2, KSLOT / 2), word_of(e));
                 }
             }
         }
@@ -1110,14 +1408,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 const int gcol = x.rank * 32 + (tid & 15) * 2;
                 const unsigned ko = ((unsigned)s * TS + (unsigned)x.rank) * 8u, ds = (unsigned)s * kMaxDur * 4u;
                 const bool lead = (tid & 15) == 0;
-                if (lead) put_mark2(x, ko, bo.key + RES_SLOT(jn + 2) * KSLOT);
-                if (lead && p.logps) put_mark(x, ko / 2, bo.lse + RES_SLOT(jn + 2) * (KSLOT / 2));
-                if (lead && has_tail && tcol >= p.VT) put_mark(x, ds + (unsigned)(tcol - p.VT) * 4u, bo.dur + RES_SLOT(jn + 2) * DSLOT);
+                if (lead) put_mark2(x, ko, bo.key + slot_at(jn + 2, KSLOT));
+                if (lead && p.logps) put_mark(x, ko / 2, bo.lse + slot_at(jn + 2, KSLOT / 2));
+                if (lead && has_tail && tcol >= p.VT) put_mark(x, ds + (unsigned)(tcol - p.VT) * 4u, bo.dur + slot_at(jn + 2, DSLOT));
                 if (dur_cols) {
 #pragma unroll
                     for (int c = 0; c < 2; ++c)
                         if (gcol + c >= p.VT && gcol + c < p.pl.nout_m)
-                            put_mark(x, ds + (unsigned)(gcol + c - p.VT) * 4u, bo.dur + RES_SLOT(jn + 2) * DSLOT);
+                            put_mark(x, ds + (unsigned)(gcol + c - p.VT) * 4u, bo.dur + slot_at(jn + 2, DSLOT));
                 }
             }
         }
@@ -1140,10 +1438,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     unsigned spins = 0;
                     const unsigned o = ((off[0] / (L * 16u)) * kMaxDur + (unsigned)di) * 4u;
                     for (;;) {
-                        v[0] = get4(x, off[0], bo.key + RES_SLOT(jn) * KSLOT);
+                        v[0] = get4(x, off[0], bo.key + slot_at(jn, KSLOT));
                         bool missing = false;
 #pragma unroll
-                        for (int i = 0; i < ND; ++i) dv[i] = get1(x, o + i * 4u, bo.dur + RES_SLOT(jn) * DSLOT);
+                        for (int i = 0; i < ND; ++i) dv[i] = get1(x, o + i * 4u, bo.dur + slot_at(jn, DSLOT));
 #pragma unroll
                         for (int i = 0; i < ND; ++i) missing = missing || (di + i < p.D && dv[i] == kMark);
                         if (__ballot(missing || has_mark(v[0])) == 0ull) break;
@@ -1156,7 +1454,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     const unsigned hit = (unsigned)(__ballot(dl == dm && di < p.D) >> (lane & ~(L - 1))) & ((1u << L) - 1u);
                     if (li == (hit ? __builtin_ctz(hit) : 0) && s < ns) rc.s_d[s] = d0 == dm || ND == 1 ? v0 : v1;
                 } else {
-                    receive<1>(p, x, off, bo.key + RES_SLOT(jn) * KSLOT, v);
+                    receive<1>(p, x, off, bo.key + slot_at(jn, KSLOT), v);
                 }
                 const float va = __uint_as_float(v[0].x), vb = __uint_as_float(v[0].z);
                 const int ia = (int)v[0].y, ib = (int)v[0].w;
@@ -1173,8 +1471,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 if (p.logps) {
                     unsigned e0, e1, spins = 0;
                     for (;;) {
-                        e0 = get1(x, off[0] >> 1, bo.lse + RES_SLOT(jn) * (KSLOT / 2));
-                        e1 = get1(x, (off[0] >> 1) + 4u, bo.lse + RES_SLOT(jn) * (KSLOT / 2));
+                        e0 = get1(x, off[0] >> 1, bo.lse + slot_at(jn, KSLOT / 2));
+                        e1 = get1(x, (off[0] >> 1) + 4u, bo.lse + slot_at(jn, KSLOT / 2));
                         if (__ballot(e0 == kMark || e1 == kMark) == 0ull) break;
                         if (wait_expired(p, spins)) { rc.ok = 0; break; }
                     }
@@ -1195,14 +1493,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         }
         // ---- loop control: every wave for itself, lane = row (outputs: the last wave, which has the least to do next) ------
         {
-            const int lane = lane_id(), r = (lane >> 2) & 3;
+            const int lane = lane_id(), r = (lane / LR) & (R - 1);
             RRow w = rows.s[r];
             int b = rows.b[r], m = rows.m[r];
             __syncthreads();
             RES_MARK(14);
-            if (PAIR) load_pre(n_pred, pre);       // (on its way during the rest)
-            const int mine = rc.s_k[lane & (kResSamples - 1)], row0 = (lane_const >> 6) & 31, left = w.len - w.t;
-            const bool lead = lane < 16 && (lane & 3) == 0;     // stands for its row
+            if (PAIR) { load_pre(n_pred, 0, pre); load_pre(n_pred, 1, pre); }       // (on their way during the rest)
+            const int mine = rc.s_k[lane & (kResSamples - 1)], row0 = (lane_const >> 7) & 31, left = w.len - w.t;
+            const bool lead = lane < 16 && (lane & (LR - 1)) == 0;     // stands for its row
             const bool writer = x.rank == 0 && x.wave == kResWaves - 1 && lead;
             const bool walk = p.tdt || p.VT != p.V1;
             int pos, dval = 0;
@@ -1217,8 +1515,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 // lane = sample: the offset (from the row's frame) that the walk goes to from it, its own for a label
                 // or beyond the row's frames, and the lane of that offset, its own where the walk leaves the step;
                 // then the hops are doubled until every one reaches its end
-                const int sr = lane_const & 3, ms = from_lane(m, sr * 4);
-                int to = ((lane_const >> 2) & 15) - ms;
+                const int sr = lane_const & 7, ms = from_lane(m, sr * LR);
+                int to = ((lane_const >> 3) & 15) - ms;
                 if (to < 0) to += la;
                 int d = 0;
                 if (mine >= p.V1) d = max(rc.dur[(mine - p.V1) & (kMaxDur - 1)], 1);            // big blank: its span of frames
@@ -1281,7 +1579,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             lane_const = (lane_const & ~(kTake | kFresh)) | action;
             if (lead) { rows.s[r] = w; rows.m[r] = m; }
 
-            const unsigned long long moved = __ballot(action != 0) & 0x1111ull;      // rows whose next step has new inputs
+            const unsigned long long moved = __ballot(action != 0) & LEADS;      // rows whose next step has new inputs
             any_active = __ballot(w.t < w.len) != 0ull;
             need_pred = moved != 0ull;
             row_steps += __popcll(moved);
@@ -1296,7 +1594,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             }
             if constexpr (NT < NMT) change = __ballot(left > 0 && !found && !ended) != 0ull;      // a row's next label is further away
             if (!change) set_up_samples(f, lane, w.t, m, b, w.len);
-            if (PAIR && NT < NMT) load_pre(n_pred, later);
+            if (PAIR && NT < NMT) { load_pre(n_pred, 0, later); load_pre(n_pred, 1, later); }
         }
         ok = rc.ok != 0;
         RES_MARK(15);
@@ -1315,12 +1613,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         // their second loop costs more registers than there are (bfloat16 mode: twelve spilled, 4 to 6 % of a call).
         std::integral_constant<int, 1> one_tile;
         auto changed_to = [&](auto nt_) {
-            const int lane = lane_id(), r = (lane >> 2) & 3;
+            const int lane = lane_id(), r = (lane / LR) & (R - 1);
             const RRow w = rows.s[r];
             const Frames f = frames_of(nt_);
             const int m = f.mod_la(w.t);
             pack_lane(f, lane);
-            if (lane < 16 && (lane & 3) == 0) {
+            if (lane < 16 && (lane & (LR - 1)) == 0) {
                 rows.m[r] = m;
                 rows.since[r] = -0x10000000;      // (not after less than kResCalm steps)
             }
@@ -1339,7 +1637,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     __syncthreads();
     if (PAIR && rc.ok) {
         // the helpers wait for the next candidate vector: tell them that there is none
-        const unsigned o = bo.hr[0] + RES_SLOT(n_pred + 1) * VSLOT;
+        const unsigned o = bo.hr[0] + slot_at(n_pred + 1, VSLOT);
         for (int i = threadIdx.x; i < p.slots * nu; i += kResThreads) {
             const int r = i / nu, u = i - r * nu;
             put_far(x, (unsigned)r * VROW + (unsigned)(u0 + u) * 4u, o, kStop);
@@ -1362,11 +1660,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     }
 }
 
-template <int KIND, bool BF, int CLS, int NMT>
+template <int KIND, bool BF, int CLS, int NMT, int R>
 hipError_t launch_resident_one(const ResidentParams &p, bool plain, hipStream_t stream)
 {
-    const void *fn = reinterpret_cast<const void *>(&resident_kernel<KIND, BF, CLS, NMT>);
-    constexpr unsigned lds = (unsigned)resident_lds(KIND, BF, CLS, NMT).bytes;
+    const void *fn = reinterpret_cast<const void *>(&resident_kernel<KIND, BF, CLS, NMT, R>);
+    constexpr unsigned lds = (unsigned)resident_lds(KIND, CLS, NMT, R).bytes;
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     ResidentParams pc = p;

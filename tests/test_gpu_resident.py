@@ -219,3 +219,65 @@ def test_an_engine_that_does_not_fit_the_memory_leaves_the_others_alone(pkg):  #
         assert err.value.code == -4
         check(pkg, w, v, "after a refused allocation", engine=eng)
     eng.close()
+
+
+def test_more_utterances_than_one_launch_takes(pkg):  # noqa: F811
+    """A team takes 128 utterances a launch; two-layer fp32 models have up to 24 teams of the narrowest class."""
+    w = model_inputs(324, 332, 530, 2, B=12 * 128 + 7, T=5, seed=11)
+    eng = pkg.Engine(w.model, w.B, w.T)
+    check(pkg, w, "label", "two launches", engine=eng)
+    eng.close()
+
+
+@pytest.mark.parametrize("H,J,V1,L", [(128, 128, 255, 1), (316, 320, 529, 1), (324, 640, 530, 2), (640, 636, 1025, 2)])
+def test_rows_of_very_different_magnitude(pkg, H, J, V1, L):  # noqa: F811
+    """fp32 weights are held as fp16 parts after a power of two for each row: matrices whose rows span 2^-40 to 2^12,
+    projected frames of up to 2^12, and a row of zeros.  To the usual bar: a power of two changes no rounding."""
+    w = model_inputs(H, J, V1, L, B=5, T=12, seed=H + V1)
+    m, rng = w.model, np.random.default_rng(7)
+
+    def scale(n, lo, hi):
+        return np.exp2(rng.integers(lo, hi + 1, n)).astype(np.float32)[:, None]
+
+    for a in (m.w_hh[0], m.w_hh[-1], m.w_ih[-1]):
+        a *= scale(a.shape[0], -40, 1)
+    m.w_pred *= scale(J, -40, 6)
+    m.w_enc *= scale(J, -20, 12)
+    m.w_out *= scale(m.w_out.shape[0], -40, -10)
+    m.w_hh[0][3], m.w_pred[1], m.w_out[2] = 0.0, 0.0, 0.0
+    eng = pkg.Engine(m, w.B, w.T)
+    check(pkg, w, "label", f"magnitudes {H}/{J}/{V1}/{L}", engine=eng, logp=True)
+    eng.close()
+
+
+@pytest.mark.parametrize("value", [np.inf, 3e38])
+@pytest.mark.parametrize("H,J,V1,L", [(100, 128, 255, 1), (324, 332, 529, 1), (324, 640, 530, 2)])
+def test_projected_frames_without_a_bound(pkg, H, J, V1, L, value):  # noqa: F811
+    """One column of the projected frames is infinite, or as large as fp32 holds: the label is the first with an
+    infinite logit, or the one with the largest weight, as for the oracle."""
+    w = model_inputs(H, J, V1, L, B=20, T=4, seed=H + V1, max_symbols=2)
+    m = w.model
+    m.b_enc[7] = value
+    m.w_out[:9, 7] = -np.abs(m.w_out[:9, 7])         # (not the first label)
+    eng = pkg.Engine(m, w.B, w.T)
+    import torch
+    out = eng.decode("label", torch.from_numpy(w.enc_out).cuda(), torch.from_numpy(w.enc_len.astype(np.int32)).cuda(), w.max_symbols)
+    got = out["tokens"].cpu().numpy().reshape(w.B, -1)
+    assert eng.status() == 0
+    eng.close()
+    import oracle
+    ref = oracle.decode(oracle.LstmNet(m), w.enc_out, w.enc_len, w.max_symbols, "label")
+    for b in range(w.B):
+        assert got[b, :len(ref.tokens[b])].tolist() == ref.tokens[b].tolist(), b
+
+
+def test_weights_that_are_not_finite_run_in_the_streaming_kernel(pkg):  # noqa: F811
+    """fp16 parts of an infinite weight do not exist; the bfloat16 mode has none to form."""
+    w = model_inputs(324, 332, 530, 2, B=9, T=8, seed=13)
+    w.model.w_pred[5, 7] = np.inf
+    for flags, streaming in ((0, True), (pkg.RNNT_FLAG_BF16_ARITHMETIC, False)):
+        eng = pkg.Engine(w.model, w.B, w.T, flags=flags)
+        import torch
+        eng.decode("label", torch.from_numpy(w.enc_out).cuda(), torch.from_numpy(w.enc_len.astype(np.int32)).cuda(), w.max_symbols)
+        assert eng.status() == 0 and (eng.stats()["search_steps"] != 1) == streaming
+        eng.close()
