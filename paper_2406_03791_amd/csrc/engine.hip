@@ -61,8 +61,10 @@ constexpr int kStaticLds = 3072;        // kept free for the kernel's static LDS
 // projected frames and the team workspace of one call.  One copy per device, held until the
 // process ends.  In host code this name is only a handle for hipGetSymbolAddress: the address
 // kernels and copies use is the one that call returns (rnnt_engine::scratch).
+// (Calls are measured against RNNT_NOALLOC_SCRATCH_BYTES with five teams of the resident kernel for every six that
+// two-layer fp32 models have: the sixth ones' workspace lies in the room behind.)
 // kScratchTop: where the words on a call's P have their place, which every call finds as the last one left them.
-constexpr size_t kScratchTop = RNNT_NOALLOC_SCRATCH_BYTES;
+constexpr size_t kScratchTop = RNNT_NOALLOC_SCRATCH_BYTES + (1u << 20);
 static __device__ __align__(256) unsigned char scratch[kScratchTop + kTopTotal * sizeof(TopWord)];
 
 struct DevBuf {
@@ -1152,7 +1154,10 @@ int rnnt_label_looping_decode_noalloc(rnnt_engine *eng, const float *enc_out, co
         const size_t o_f = take((size_t)pl.n_xcd * 32 * sizeof(unsigned));
         const size_t o_s = take((size_t)pl.n_teams * kStatStride * sizeof(long long));
         const size_t o_a = take(sizeof(unsigned)), o_st = take(sizeof(int));
-        if (off > RNNT_NOALLOC_SCRATCH_BYTES) return RNNT_ERR_SCRATCH;
+        auto sized = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
+        auto of_teams = [&](int n) { return sized((size_t)resident_buf(pl.cls, 4).bytes * n) + sized((size_t)n * kStatStride * sizeof(long long)); };
+        const size_t extra = pl.kind == kResident2Pair ? of_teams(pl.n_teams) - of_teams(pl.n_teams - pl.n_teams / 6) : 0;
+        if (off > RNNT_NOALLOC_SCRATCH_BYTES + extra || off > kScratchTop) return RNNT_ERR_SCRATCH;
         unsigned char *base = static_cast<unsigned char *>(eng->scratch);
         Workspace ws;
         ws.P = reinterpret_cast<float *>(base + o_P);

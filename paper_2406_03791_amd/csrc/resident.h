@@ -51,8 +51,10 @@ enum ResidentKind {
     kResident2 = 2,       // two layers in the bfloat16 mode: the same
     kResident2Pair = 3,   // two layers in fp32: a team on one XCD, the recurrent matrices on a second one
 };
-// kResident2Pair: most XCDs have teams, and each of the others works for up to kResServed of them
-constexpr int kResServed = 2;
+// kResident2Pair: most XCDs have teams, and each of the others works for up to kResServed of them.  (Three: a helper needs
+// 1.6 us of each team's step, half of the 8 to 9 us that it has, so its results are late for some steps and a step
+// takes 0.7 us more than with two, but the sixth team saves a seventh of the steps.)
+constexpr int kResServed = 3;
 RNNT_HD constexpr int res_chain_xcds(int n_xcd) { return n_xcd * kResServed / (kResServed + 1); }
 
 struct ResidentPlan {
