@@ -159,8 +159,15 @@ inline int in_launch_order(hipStream_t stream, F enqueue)
     return done;
 }
 
-hipError_t launch_encoder_projection(const float *enc_out, const int *enc_len, const float *w_enc,
-                                     const float *b_enc, float *proj, int B, int T, int F, int J,
+// W_enc on the device.  parts: as the matrix instructions take it, [tile of 32 columns][16 k's][part][lane][8 values],
+// enc_columns(J) columns, zeros beyond J; fp32: two fp16 parts of the values, after a power of two of the column;
+// bfloat16 mode: one part.  bias [enc_columns(J)]; fp32 only: inverse of the powers of two [enc_columns(J)], the
+// values themselves, and whether one of them is not finite.
+struct EncWeights { const unsigned *parts; const float *inverse, *plain; const unsigned *not_finite; const float *bias; };
+inline int enc_columns(int J) { return (J + 127) / 128 * 128; }
+// w: [J][F]; scratch: J floats (bf16: unused, as inverse and check, which has to be zero before)
+hipError_t pack_projection(const float *w, int F, int J, bool bf16, unsigned *parts, float *inverse, unsigned *check, float *scratch, hipStream_t stream);
+hipError_t launch_encoder_projection(const float *enc_out, const int *enc_len, const EncWeights &w, float *proj, int B, int T, int F, int J,
                                      bool round_x, const CallInit &ci, hipStream_t stream);
 // Clears what a further launch of the resident decode kernel within a call needs cleared.
 hipError_t launch_reset_resident(unsigned *form, int n_form, unsigned *abort_flag, hipStream_t stream);

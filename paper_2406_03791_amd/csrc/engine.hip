@@ -156,7 +156,7 @@ struct rnnt_engine {
     std::vector<std::vector<float>> w_ih, w_hh;
     std::vector<float> w_pred, w_out;
     // device: weights used as they are, derived tables, workspace
-    DevBuf w_enc, b_enc, T0, bias_l, b_pred, b_out;
+    DevBuf w_enc, enc_parts, enc_columns, T0, bias_l, b_pred, b_out;
     DevBuf sc_hh, sc_ih, sc_pred, sc_out;   // e4m3 storage in the bfloat16 mode: power-of-two scale of every weight row
     DevBuf P, abort_flag, status;
     // The decode kernel with register-resident weights runs the calls of a model that fits it
@@ -550,6 +550,13 @@ int check_call(rnnt_engine *e, const float *enc_out, const int32_t *enc_len, int
     return RNNT_OK;
 }
 
+// (enc_columns: inverse scales, biases, the word on weights that are not finite)
+EncWeights enc_weights(const rnnt_engine *e)
+{
+    const float *inverse = e->enc_columns.as<float>(), *bias = inverse + enc_columns(e->d.J);
+    return EncWeights{e->enc_parts.as<unsigned>(), inverse, e->w_enc.as<float>(), reinterpret_cast<const unsigned *>(bias + enc_columns(e->d.J)), bias};
+}
+
 // ---- resident decode kernel ---------------------------------------------------------------
 Workspace resident_workspace(const rnnt_engine *e)
 {
@@ -614,7 +621,7 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
     ci.tokens = tokens_out; ci.frames = frames_out; ci.durs = durs_out; ci.logits = logit_out; ci.logps = e->logp_out;
     ci.cap = cap; ci.stats = ws.stats;
     ci.p_top = res_whole(pl.bf != 0, pl.cls) ? nullptr : ws.top;
-    HIP_TRY(launch_encoder_projection(enc_out, enc_len, e->w_enc.as<float>(), e->b_enc.as<float>(), ws.P, B, T, d.F, d.J,
+    HIP_TRY(launch_encoder_projection(enc_out, enc_len, enc_weights(e), ws.P, B, T, d.F, d.J,
                                       is_bf16_arith(e->wt), ci, stream));
     e->last_B = B; e->last_used.clear(); e->last_ws = ws; e->last_resident = true;
     const int launch_rows = kResList * pl.n_teams;
@@ -673,8 +680,7 @@ int run_decode(rnnt_engine *e, int variant, const float *enc_out, const int32_t 
     // every launch reads the projected frames of the whole call from one buffer
     float *P = static_ws ? static_ws->P : e->P.as<float>();
     HIP_TRY(hipEventRecord(e->ev[0], stream));
-    HIP_TRY(launch_encoder_projection(enc_out, enc_len, e->w_enc.as<float>(), e->b_enc.as<float>(),
-                                      P, B, T, d.F, d.J, is_bf16_arith(e->wt), CallInit(), stream));
+    HIP_TRY(launch_encoder_projection(enc_out, enc_len, enc_weights(e), P, B, T, d.F, d.J, is_bf16_arith(e->wt), CallInit(), stream));
     HIP_TRY(hipEventRecord(e->ev[1], stream));
     e->last_B = B;
     e->last_used.clear();
@@ -932,7 +938,6 @@ int rnnt_engine_create(const rnnt_model_desc *desc, int32_t max_B, int32_t max_T
         return RNNT_OK;
     };
     if ((rc = clone(e->w_enc, d.w_enc, J * d.F))) return rc;
-    if ((rc = clone(e->b_enc, d.b_enc, J))) return rc;
     if ((rc = clone(e->b_pred, d.b_pred, J))) return rc;
     if ((rc = clone(e->b_out, d.b_out, (size_t)e->NOUT))) return rc;
     HIP_TRY(e->bias_l.alloc(bias_l.size() * sizeof(float)));
@@ -940,6 +945,16 @@ int rnnt_engine_create(const rnnt_model_desc *desc, int32_t max_B, int32_t max_T
     HIP_TRY(e->T0.alloc((size_t)d.V1 * H * 4 * sizeof(float)));
     const bool bf16_mode = is_bf16_arith(e->wt);
     if (bf16_mode) HIP_TRY(launch_round_bf16(e->w_enc.as<float>(), (long long)J * d.F, nullptr));
+    {
+        const size_t columns = enc_columns(d.J);
+        HIP_TRY(e->enc_parts.alloc(columns * d.F * (bf16_mode ? 2 : 4)));
+        HIP_TRY(e->enc_columns.alloc((2 * columns + 1 + J) * sizeof(float)));       // (at the end, the packing's scales)
+        HIP_TRY(hipMemset(e->enc_columns.p, 0, (2 * columns + 1) * sizeof(float)));
+        float *inverse = e->enc_columns.as<float>(), *bias = inverse + columns;
+        HIP_TRY(hipMemcpy(bias, d.b_enc, J * sizeof(float), hipMemcpyDeviceToDevice));
+        HIP_TRY(pack_projection(e->w_enc.as<float>(), d.F, d.J, bf16_mode, e->enc_parts.as<unsigned>(), inverse,
+                                reinterpret_cast<unsigned *>(bias + columns), bias + columns + 1, nullptr));
+    }
     HIP_TRY(launch_fold_embedding(d.emb, d.w_ih[0], d.b_ih[0], d.b_hh[0], e->T0.as<float>(), d.V1,
                                   d.E, d.H, bf16_mode, nullptr));
     // this device's copy of the static scratch array (each device has its own, at its own address)
@@ -1225,8 +1240,7 @@ int rnnt_encoder_projection(rnnt_engine *eng, const float *enc_out, const int32_
     if (!eng || !enc_out || !enc_len || !proj_out) return RNNT_ERR_NULL;
     if (B < 1 || T < 1) return RNNT_ERR_SHAPE;
     if ((reinterpret_cast<uintptr_t>(enc_out) & 15u) != 0) return RNNT_ERR_SHAPE;
-    HIP_TRY(launch_encoder_projection(enc_out, enc_len, eng->w_enc.as<float>(),
-                                      eng->b_enc.as<float>(), proj_out, B, T, eng->d.F, eng->d.J,
+    HIP_TRY(launch_encoder_projection(enc_out, enc_len, enc_weights(eng), proj_out, B, T, eng->d.F, eng->d.J,
                                       is_bf16_arith(eng->wt), CallInit(), static_cast<hipStream_t>(stream)));
     return RNNT_OK;
 }

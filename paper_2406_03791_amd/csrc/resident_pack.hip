@@ -1,5 +1,5 @@
-// Register images of the resident decode kernel's work-groups, and the scales of its fp32 weights, made on the
-// device from the model's matrices (on the host, the parts of the Parakeet shape's 6.4 million weights took
+// Register images of the resident decode kernel's work-groups, the projection's weights as its matrix instructions
+// take them, and the scales of fp32 weights, made on the device from the model's matrices (on the host, the parts of the Parakeet shape's 6.4 million weights took
 // 33 of 55 ms of an engine's creation).
 #include "engine.h"
 #include "resident.h"
@@ -110,7 +110,47 @@ __global__ void pack_tail_kernel(const float *__restrict__ w, const float *__res
     out[i] = scale ? v * scale[row] : whole ? v : __uint_as_float(bf16_of(v) << 16);
 }
 
+// W_enc as EncWeights::parts: one thread per tile of 32 columns, 16 k's and lane
+__global__ void __launch_bounds__(256) pack_projection_kernel(const float *__restrict__ w, int F, int J, int tiles, const float *__restrict__ scale, unsigned *__restrict__ parts)
+{
+    const int nks = F / 16, lane = threadIdx.x & 63;
+    const long long at = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (at >= (long long)tiles * nks) return;
+    const int ks = (int)(at % nks), col = (int)(at / nks) * 32 + (lane & 31);
+    const int planes = scale ? 2 : 1;
+    unsigned *to = parts + (at * planes * 64 + lane) * 4;
+    for (int i = 0; i < 4; ++i) {
+        float v[2] = {0.f, 0.f};
+        if (col < J)
+            for (int e = 0; e < 2; ++e) v[e] = w[(long long)col * F + ks * 16 + (lane >> 5) * 8 + i * 2 + e];
+        if (!scale) {
+            to[i] = bf16_of(v[0]) | bf16_of(v[1]) << 16;
+            continue;
+        }
+        const float s = col < J ? scale[col] : 0.f;
+        h2 high, low;
+        for (int e = 0; e < 2; ++e) {
+            const float a = v[e] * s;
+            high[e] = (_Float16)a;
+            low[e] = (_Float16)(a - (float)high[e]);
+        }
+        to[i] = __builtin_bit_cast(unsigned, high);
+        to[64 * 4 + i] = __builtin_bit_cast(unsigned, low);
+    }
+}
+
 }  // namespace
+
+hipError_t pack_projection(const float *w, int F, int J, bool bf16, unsigned *parts, float *inverse, unsigned *check, float *scratch, hipStream_t stream)
+{
+    const int tiles = enc_columns(J) / 32;
+    if (!bf16) {
+        hipLaunchKernelGGL(row_scales_kernel, dim3((unsigned)((J + 3) / 4)), dim3(256), 0, stream, w, J, F, scratch, nullptr, check);
+        hipLaunchKernelGGL(inverse_scales_kernel, dim3((unsigned)((J + 255) / 256)), dim3(256), 0, stream, scratch, inverse, J, 0, 0);
+    }
+    hipLaunchKernelGGL(pack_projection_kernel, dim3((unsigned)(((long long)tiles * (F / 16) + 3) / 4)), dim3(256), 0, stream, w, F, J, tiles, bf16 ? nullptr : scratch, parts);
+    return hipGetLastError();
+}
 
 hipError_t pack_resident(const ResidentPlan &pl, const ResidentWeights &rw, const ResidentImages &im, hipStream_t stream)
 {
