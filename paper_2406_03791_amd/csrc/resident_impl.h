@@ -1184,7 +1184,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             // A wave has an eighth of K for both column tiles, so the operand z = relu(P + q) of a lane's sample is
             // formed on the way: nobody else needs it.  fp32: every product is that of two fp16 parts of
             // either side (see z_scale; layers of 640: without low times low, which made the joint step 0.1 us longer and
-            // the logits' error 2 % smaller); products with a low part are summed apart from the others.
+            // the logits' error 2 % smaller), in one sum.  (Products with a low part in sums of their own made the logits' error
+            // 1 to 6 % smaller, but twelve registers of the two-layer models' input weights had to be loaded from memory
+            // in every step: input stage 1.18 instead of 0.96 us.)
             // (a half block comes first)
             auto block_of = [](int b) { return NH % 2 != 0 ? (b + NB - 1) % NB : b % NB; };
             auto form = [&](float p_, float q_) { return fmaxf(BF || WHOLE ? p_ + q_ : fmaf(p_, z_scale, q_), 0.f); };
@@ -1208,7 +1210,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             auto output = [&](auto tail_) {
                 constexpr bool TAIL = decltype(tail_)::value;
                 const r4f zero = {0.f, 0.f, 0.f, 0.f};
-                r4f big[2], small[2], tb, ts;                // (bfloat16 mode: big alone)
+                r4f big[2], tb;
                 float4 pv[2], qv[2];
                 int qo = 0;
                 auto fetch = [&](int b) {
@@ -1222,7 +1224,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 static_for<0, NB * NT>([&](auto b_) {
                     constexpr int b = decltype(b_)::value, mt = b / NB, i = block_of(b % NB);
                     constexpr bool FULL = i < NF;
-                    if constexpr (b % NB == 0) { big[0] = big[1] = small[0] = small[1] = tb = ts = zero; }
+                    if constexpr (b % NB == 0) { big[0] = big[1] = tb = zero; }
                     unsigned zh[4], zl[4];
                     if constexpr (FULL && TAIL) { pv[1] = at(frame_at(mt, i) ^ 16); qv[1] = at(q_at(qo, i) + 16); }      // (registers)
 #pragma unroll
@@ -1249,12 +1251,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     } else if constexpr (!WHOLE) {
                         if constexpr (NF < 2) {
 #pragma unroll
-                            for (int c = 0; c < 2; ++c) small[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 1>(w_ou, c), zl, small[c]);
+                            for (int c = 0; c < 2; ++c) big[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 1>(w_ou, c), zl, big[c]);
                         }
 #pragma unroll
-                        for (int c = 0; c < 2; ++c) small[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 0>(w_ou, c), zl, small[c]);
+                        for (int c = 0; c < 2; ++c) big[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 0>(w_ou, c), zl, big[c]);
 #pragma unroll
-                        for (int c = 0; c < 2; ++c) small[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 1>(w_ou, c), zh, small[c]);
+                        for (int c = 0; c < 2; ++c) big[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 1>(w_ou, c), zh, big[c]);
                     }
 #pragma unroll
                     for (int c = 0; c < 2; ++c) {
@@ -1267,15 +1269,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                         tb = whole_mfma(*reinterpret_cast<const r4f *>(lds + lo.tail + (min(m16, 1) * ROW + x.wave * 16 + g * 4) * 4), zh, tb);
                     } else if constexpr (TAIL) {
                         const auto w = *reinterpret_cast<const std::conditional_t<FULL, r4f, r2f> *>(lds + lo.tail + (min(m16, BF ? 1 : 2) * ROW + x.wave * (NH * 16) + i * 32 + g * (FULL ? 8 : 4)) * 2);
-                        if constexpr (!BF) ts = tile_mfma<BF>(w, zl, ts);
+                        if constexpr (!BF) tb = tile_mfma<BF>(w, zl, tb);
                         tb = tile_mfma<BF>(w, zh, tb);
                     }
                     ordered();
                     if constexpr (b % NB == NB - 1) {
-                        if constexpr (!BF && !WHOLE) {
-                            big[0] += small[0]; big[1] += small[1];
-                            if (TAIL) tb += ts;
-                        }
                         if (TAIL && g == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = BF || WHOLE ? tb[0] : tb[0] + tb[1];
                         // every wave's sums to LDS, [wave][sample][column]
 #pragma unroll
