@@ -61,10 +61,10 @@ constexpr int kStaticLds = 3072;        // kept free for the kernel's static LDS
 // projected frames and the team workspace of one call.  One copy per device, held until the
 // process ends.  In host code this name is only a handle for hipGetSymbolAddress: the address
 // kernels and copies use is the one that call returns (rnnt_engine::scratch).
-// (Calls are measured against RNNT_NOALLOC_SCRATCH_BYTES with five teams of the resident kernel for every six that
-// two-layer fp32 models have: the sixth ones' workspace lies in the room behind.)
+// (Calls are measured against RNNT_NOALLOC_SCRATCH_BYTES with a quarter of the room for the helpers' results, and with five teams
+// for every six that two-layer fp32 models have: the rest lies in the room behind, 7.9 MB at most.)
 // kScratchTop: where the words on a call's P have their place, which every call finds as the last one left them.
-constexpr size_t kScratchTop = RNNT_NOALLOC_SCRATCH_BYTES + (1u << 20);
+constexpr size_t kScratchTop = RNNT_NOALLOC_SCRATCH_BYTES + (8u << 20);
 static __device__ __align__(256) unsigned char scratch[kScratchTop + kTopTotal * sizeof(TopWord)];
 
 struct DevBuf {
@@ -574,7 +574,7 @@ int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
     const bool bf = pl.bf != 0;
     const size_t images = (size_t)res_team(pl.cls) * kResWaves * 64 * sizeof(float), scales = (size_t)e->NOUT + d.J + (d.L > 1 ? 4 * (d.L + 1) : 4) * (size_t)d.H;
     HIP_TRY(e->res_w.alloc(images * res_main_regs(pl.kind, bf, pl.cls)));
-    if (pl.kind == kResident2Pair) HIP_TRY(e->res_help.alloc(images * 2 * res_lstm_regs(bf, pl.cls)));
+    if (pl.kind == kResident2Pair) HIP_TRY(e->res_help.alloc(images * 2 * res_help_regs(pl.cls)));
     if (pl.n_tail) HIP_TRY(e->res_tail.alloc((size_t)pl.n_tail * res_row(pl.cls) * sizeof(float)));
     HIP_TRY(e->res_top.alloc(kTopTotal * sizeof(TopWord)));
     HIP_TRY(hipMemset(e->res_top.p, 0, kTopTotal * sizeof(TopWord)));
@@ -1170,8 +1170,10 @@ int rnnt_label_looping_decode_noalloc(rnnt_engine *eng, const float *enc_out, co
         const size_t o_s = take((size_t)pl.n_teams * kStatStride * sizeof(long long));
         const size_t o_a = take(sizeof(unsigned)), o_st = take(sizeof(int));
         auto sized = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
-        auto of_teams = [&](int n) { return sized((size_t)resident_buf(pl.cls, 4).bytes * n) + sized((size_t)n * kStatStride * sizeof(long long)); };
-        const size_t extra = pl.kind == kResident2Pair ? of_teams(pl.n_teams) - of_teams(pl.n_teams - pl.n_teams / 6) : 0;
+        auto of_teams = [&](int n, size_t buf) { return sized(buf * n) + sized((size_t)n * kStatStride * sizeof(long long)); };
+        const ResidentBuf buf = resident_buf(pl.cls, 4);
+        const int teams = pl.kind == kResident2Pair ? pl.n_teams - pl.n_teams / 6 : pl.n_teams;
+        const size_t extra = of_teams(pl.n_teams, buf.bytes) - of_teams(teams, buf.pre + (buf.bytes - buf.pre) / kResQuarters);
         if (off > RNNT_NOALLOC_SCRATCH_BYTES + extra || off > kScratchTop) return RNNT_ERR_SCRATCH;
         unsigned char *base = static_cast<unsigned char *>(eng->scratch);
         Workspace ws;

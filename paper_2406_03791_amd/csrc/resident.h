@@ -44,6 +44,11 @@ RNNT_HD constexpr int res_tile_at(bool bf, int cls, int T, int kb, int t, int pa
                                     : res_halves(cls) / 2 * T * res_parts(bf) * 4 + (t * res_parts(bf) + part) * 2;
 }
 
+// Helpers of kResident2Pair: a work-group's quarter of K in whole blocks, and the registers of a wave's three tiles of 16 outputs.
+constexpr int kResQuarters = 4;
+RNNT_HD constexpr int res_help_blocks(int cls) { return res_row(cls) / (32 * kResQuarters); }
+RNNT_HD constexpr int res_help_regs(int cls) { return res_help_blocks(cls) * 3 * 2 * 4; }
+
 // Kinds of resident decoders (which weights sit where).
 enum ResidentKind {
     kResidentNone = 0,
@@ -51,11 +56,10 @@ enum ResidentKind {
     kResident2 = 2,       // two layers in the bfloat16 mode: the same
     kResident2Pair = 3,   // two layers in fp32: a team on one XCD, the recurrent matrices on a second one
 };
-// kResident2Pair: most XCDs have teams, and each of the others works for up to kResServed of them.  (Three: a helper needs
-// 1.6 us of each team's step, half of the 8 to 9 us that it has, so its results are late for some steps and a step
-// takes 0.7 us more than with two, but the sixth team saves a seventh of the steps.)
-constexpr int kResServed = 3;
-RNNT_HD constexpr int res_chain_xcds(int n_xcd) { return n_xcd * kResServed / (kResServed + 1); }
+// kResident2Pair: most XCDs have teams, and each pair of the others, one for either layer, works for up to kResServed of them.
+// (Six and two of eight: with five and three, helpers had more time, and 128 utterances took 5.65 instead of 5.29 ms.)
+constexpr int kResServed = 6;
+RNNT_HD constexpr int res_chain_xcds(int n_xcd) { return n_xcd - (n_xcd + kResServed + 1) / (kResServed + 2) * 2; }
 
 struct ResidentPlan {
     int kind;             // ResidentKind
@@ -82,7 +86,7 @@ struct ResidentParams {
     float *logits, *logps;
     int *done;
     const float *w;       // packed registers of the (main) work-groups: [rank][wave][register][lane]
-    const float *w_help;  // the same of the helpers (kResident2Pair)
+    const float *w_help;  // the same of the helpers (kResident2Pair), layer by layer
     const float *w_tail;  // [n_tail][res_row(cls)], scaled as the packed output columns
     // fp32: what sums of the scaled weights of an output are multiplied by; LSTM matrices [H][gate]
     const float *s_out, *s_pred, *s_ih, *s_hh[2];
@@ -99,6 +103,7 @@ struct ResidentParams {
 };
 
 // Byte offsets of a team's exchange buffers, every vector in kResSlots slots; R: rows of the instance, 4 or 8.
+// pre: [layer][slot][quarter of K][rank][wave of the cells][lane]
 struct ResidentBuf { unsigned h[2], q, key, dur, lse, hr[2], pre, bytes; };
 RNNT_HD constexpr ResidentBuf resident_buf(int cls, int R)
 {
@@ -109,14 +114,13 @@ RNNT_HD constexpr ResidentBuf resident_buf(int cls, int R)
     b.dur = b.key + recs * 8u;
     b.lse = b.dur + kResSlots * kResSamples * kMaxDur * 4u;
     b.hr[0] = b.lse + recs * 4u; b.hr[1] = b.hr[0] + vec; b.pre = b.hr[1] + vec;
-    // [layer][slot][rank][wave of the cells][lane][gate]
-    b.bytes = b.pre + 2u * kResSlots * (unsigned)res_team(cls) * 5u * 64u * (unsigned)(R / 4) * 4u;
+    b.bytes = b.pre + 2u * kResSlots * kResQuarters * (unsigned)res_team(cls) * 5u * 64u * 4u;
     return b;
 }
 
 // Registers per lane of a work-group, in packing order: recurrent matrices (kResident1: layer 0;
 // kResident2: both layers), input matrix of the second layer, prediction-side projection, joint
-// output.  The helpers of kResident2Pair hold the two recurrent matrices.
+// output.  The helpers of kResident2Pair hold the recurrent matrices, see res_help_regs.
 RNNT_HD constexpr int res_lstm_regs(bool bf, int cls) { return res_tile_regs(bf, cls, 5); }
 RNNT_HD constexpr int res_pred_regs(bool bf, int cls) { return res_tile_regs(bf, cls, 2); }
 RNNT_HD constexpr int res_joint_regs(bool bf, int cls) { return res_tile_regs(bf, cls, 2); }
@@ -153,7 +157,7 @@ RNNT_HD constexpr ResidentLds resident_lds(int kind, int cls, int nmt, int R)
     l.tail = at; at += (kind == kResident2 ? 2 : res_halves(cls) == 1 ? 4 : 3) * res_row(cls) * 2;
     l.tpart = at; at += kResWaves * 2 * 16 * 4;
     l.state = at; at += kind == kResident2Pair && R == 4 ? 6 * 5 * 64 * 4 : 0;
-    const int help = 2 * stage + kResWaves * kResServed * ((res_halves(cls) + 1) / 2) * 1024;
+    const int help = 2048 + 2 * (kResServed / 2) * res_help_blocks(cls) * 1024;
     if (kind == kResident2Pair && at < help) at = help;
     l.bytes = (at + 15) & ~15;
     return l;

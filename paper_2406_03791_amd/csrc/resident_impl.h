@@ -24,11 +24,10 @@
 // narrowest class 4.2 to 4.0 (with phase timers).
 //
 // Two-layer fp32 models have more weights than one XCD's registers hold (24 MB against 12 + 4):
-// there the teams' XCDs keep the input, projection and output matrices and run the whole step chain;
-// the helpers' XCDs keep the recurrent matrices and compute W_hh h of the candidate states, which the
-// chain needs only at the next label: their hand-overs across the XCDs run beside the rest of the
-// step.  A helper is busy 1.6 us of a team's step and serves three: with six teams on six XCDs and two
-// XCDs of helpers 128 utterances take 5.29 ms of decode, 32 take 1.72 ms; with five and three 5.65 and 1.79.
+// there six XCDs with a team each keep the input, projection and output matrices and run the whole step chain;
+// two XCDs of helpers, one for either layer, keep the recurrent matrices and compute W_hh h of the candidate states,
+// which the chain needs only at the next label: their hand-overs across the XCDs, 1.2 us each way, run beside the rest
+// of the step.
 //
 // Utterances are decoded label-looping fashion: every utterance has its own frame index, a joint
 // step examines `la` frames of every utterance (half as many in label-dense stretches of two-layer fp32
@@ -540,7 +539,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     constexpr ResidentLds lo = resident_lds(KIND, CLS, NMT, R);
     constexpr unsigned VROW = W * 4u, VSLOT = R * VROW;                      // h and q rows
     constexpr unsigned KSLOT = kResSamples * TS * 8u, DSLOT = kResSamples * kMaxDur * 4u;
-    constexpr unsigned PSLOT = TS * 5u * 64u * G * 4u;
+    constexpr unsigned QSLOT = TS * 5u * 64u * 4u, PSLOT = kResQuarters * QSLOT;         // pre-activations: a quarter of K, all
 
     RCtx x;
     const int tid0 = threadIdx.x, lane0 = tid0 & 63;         // (for the work before and after the loop)
@@ -560,9 +559,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         return n;
     };
     auto buffers_of = [&](int team) { return __builtin_amdgcn_make_buffer_rsrc(p.xbuf + (size_t)team * bo.bytes, 0, (int)bo.bytes, 0x00020000); };
-    // this work-group's team; a helper's first, and every helper_xcds-th one of the same place after it
-    const int team = (helper ? xcd - chain_xcds : xcd) + chain_xcds * (place / TS);
-    auto serves = [&](int i) { return team % chain_xcds + i * helper_xcds < chain_xcds && list_of(team + i * helper_xcds) > 0; };
+    // This work-group's team; a helper's first.  Helpers' XCDs go in pairs, an XCD for either layer, and the teams' go
+    // round the pairs.
+    const int team = (helper ? (xcd - chain_xcds) / 2 : xcd) + chain_xcds * (place / TS), pairs = helper_xcds / 2;
+    const int my_layer = (xcd - chain_xcds) & 1;
+    auto serves = [&](int i) { return (xcd - chain_xcds) / 2 + i * pairs < chain_xcds && list_of(team + i * pairs) > 0; };
     if (!helper && list_of(team) == 0) {
         if (p.zero_stats && x.rank == 0 && tid0 < kStatCounters) p.stats[(long long)team * kStatStride + tid0] = 0;
         return;
@@ -581,7 +582,15 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     } else {
         bool any = false;
         for (int i = 0; i < kResServed; ++i)
-            if (serves(i)) { x.buf = buffers_of(team + i * helper_xcds); put_marks(bo.pre, bo.bytes); any = true; }
+            if (serves(i)) {
+                x.buf = buffers_of(team + i * pairs); any = true;
+                // (zeros where no unit is: nobody sends these words)
+                for (unsigned o = ((unsigned)x.rank * kResThreads + (unsigned)tid0) * 16u; o < kResSlots * PSLOT; o += TS * kResThreads * 16u) {
+                    const int word = (int)(o / 4u) % (TS * 320), r = word / 320, lu = word % 320 >> 4;
+                    const unsigned v = lu < p.pl.units && r * p.pl.units + lu < p.H ? kMark : 0u;
+                    __builtin_amdgcn_raw_buffer_store_b128((r4u){v, v, v, v}, x.buf, (int)(bo.pre + my_layer * kResSlots * PSLOT + o), 0, 16);
+                }
+            }
         if (!any) return;
     }
     if (tid0 == 0) { rc.ok = 1; rc.n_list = 0; rc.st_clamped = 0; rc.st_overflow = 0; }
@@ -603,14 +612,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             __hip_atomic_store(p.form + blockIdx.x, id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     };
-    // Waits for team t in the first wave, lanes 0 .. TS-1 for the chain's work-groups and (both) lanes 32 .. for
-    // its helpers; true when the chain's all sit on one XCD.
+    // Waits for team t in the first waves: lanes 0 .. TS-1 of the first for the chain's work-groups and (both) of the
+    // next two for the helpers of either layer; true when the chain's all sit on one XCD.
     auto meet = [&](int t, bool both) {
-        const int side = lane0 >> 5, r = lane0 & 31;
-        const bool mine = x.wave == 0 && r < TS && (side == 0 || both);
+        const int side = x.wave, r = lane0;
+        const bool mine = r < TS && (side == 0 || (both && side < 3));
         unsigned v = 1;
         if (mine) {
-            const int on = t % chain_xcds, at = side ? chain_xcds + on % helper_xcds : on;
+            const int on = t % chain_xcds, at = side ? chain_xcds + on % pairs * 2 + side - 1 : on;
             const unsigned *slot = p.form + ((t / chain_xcds) * TS + r) * n_xcd + at;
             unsigned spins = 0;
             v = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -624,126 +633,165 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         return __syncthreads_and(!(mine && side == 0 && v != first)) != 0;
     };
     const bool has_cells = x.wave < 5;          // finishes 16 (unit, row) pairs of the LSTM stages, see stage_sum
-    auto prelane = [&]() { return (((unsigned)x.rank * 5u + (unsigned)x.wave) * 64u + (unsigned)lane_id()) * (G * 4u); };
+    // (beyond the buffer for waves without cells, whose loads give zeros: a branch around the loads would make the
+    // compiler wait for them where it waits for an older one)
+    unsigned pre_wave = has_cells ? ((unsigned)x.rank * 5u + (unsigned)x.wave) * 256u : 0x80000000u;
+    asm volatile("" : "+s"(pre_wave));
     const int h4 = p.H >> 2;
 
     if constexpr (PAIR) if (helper) {
-        // ---- helpers: W_hh of both layers times the candidate vectors ------------------------
-        RegW<LREGS> w0, w1;
-        const float *src = p.w_help + (long long)(x.rank * kResWaves + x.wave) * (2 * LREGS) * 64;
-        load_regs(w0, src, 0, lane0);
-        load_regs(w1, src, LREGS, lane0);
+        // ---- helpers: W_hh of a layer times the candidate vectors -----------------------------
+        // A work-group has a quarter of K and eighty units: with all of K and twenty units, the work-groups fetched four times
+        // as much from the memory side (72 KB each in 3 us, most of it not there yet), and results came too late for
+        // the next step: 8.5 us a step of 32 utterances now, 9.4 then, of 128 utterances 9.0 and 9.8.  The chain adds the quarters.
+        // Twenty tiles of four units, three for the first four waves and two for the others (waves w and w + 4
+        // share a SIMD), which need no sums from each other.  The columns of the matrix instructions are the rows of two
+        // teams, in two parts.
+        static_assert(R == 4 && !BF, "two teams' rows in two parts are the sixteen columns");
+        constexpr int HB = res_help_blocks(CLS), HREGS = res_help_regs(CLS);
+        const int quarter = x.rank & 3, first_unit = (x.rank >> 2) * 80, tile0 = x.wave < 4 ? x.wave * 3 : x.wave * 2 + 4;
+        const bool third = x.wave < 4;
+        RegW<HREGS> w;
+        load_regs(w, p.w_help + ((long long)(my_layer * TS + x.rank) * kResWaves + x.wave) * HREGS * 64, 0, lane0);
         announce();
-        // A helper XCD works for kResServed teams, in the order in which their vectors come (the second layer's first, which
-        // are needed sooner).  Every wave asks for its eighth of each team's next vector straight into LDS, and while
-        // these loads are on their way from the memory side (1.2 us) the work-group computes what came before:
-        // 1.6 us a team's step, 3.8 when a wave waited for its loads before it asked again.
-        if (tid0 < kResUnits * 4)
-            for (int l = 0; l < 2; ++l) rc.sh[l][tid0] = x.rank * p.pl.units * 4 + tid0 < p.H * 4 ? p.s_hh[l][x.rank * p.pl.units * 4 + tid0] : 0.f;
-        unsigned step[kResServed], layer[kResServed];            // of team i: step number and layer of the next vector
         unsigned live = 0;
 #pragma unroll
-        for (int i = 0; i < kResServed; ++i) {
-            step[i] = 1; layer[i] = 0;
-            if (serves(i)) { (void)meet(team + i * helper_xcds, false); live |= 1u << i; }
-        }
+        for (int i = 0; i < kResServed; ++i)
+            if (serves(i)) { (void)meet(team + i * pairs, false); live |= 1u << i; }
+        // LDS: the scales of the work-group's outputs; twice, for vectors that come and those in work, [two teams][block][lane]
+        constexpr int TWOS = kResServed / 2, AREA = TWOS * HB * 1024, AT = 2048;
+        static_assert(AT + 2 * AREA <= lo.bytes, "the helpers' layout fits");
+        for (int i = tid0; i < 320; i += kResThreads)
+            reinterpret_cast<float *>(lds)[i] = first_unit * 4 + i < p.H * 4 ? p.s_hh[my_layer][first_unit * 4 + i] : 0.f;
         __syncthreads();
-        // LDS: partial sums of a stage (two, in turn), then what a wave has asked for, [wave][team][block][lane]
-        constexpr int SUMS = kResWaves * R * kResStageRow * 4, AREA = kResServed * NB * 1024;
-        static_assert(2 * SUMS + kResWaves * AREA <= lo.bytes, "the helpers' layout fits");
-        const unsigned area = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds + 2 * SUMS + x.wave * AREA;
-        auto ask = [&](int i) {
-            const unsigned at = (layer[i] ? bo.hr[1] : bo.hr[0]) + slot_at(step[i], VSLOT);
-            const unsigned char *base = p.xbuf + (size_t)(team + i * helper_xcds) * bo.bytes + at;
-            const int lane = lane_id();
-            if (Op::takes(lane, p.slots)) {
+        const unsigned area_m0 = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds + AT));
+        const unsigned pre_at = bo.pre + my_layer * kResSlots * PSLOT + quarter * QSLOT;
+        const unsigned apart = (unsigned)pairs * bo.bytes;       // from one team to the next
+        const unsigned char *base = p.xbuf + (size_t)team * bo.bytes;
+        x.buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(base), 0, (int)((kResServed - 1) * apart + bo.bytes), 0x00020000);
+        // Where the lane's words of block 0 are in a vector, columns 8 .. 15 being the second team, see Operand::offset; and where its
+        // results go (beyond the buffer: nowhere)
+        const int col = lane0 & 15, g = lane0 >> 4;
+        const unsigned row_at = (my_layer ? bo.hr[1] : bo.hr[0]) + (unsigned)(lane0 & 3) * VROW + (lane0 & 8 ? apart : 0u);
+        const int piece = quarter * (HB * 8) + 2 * g + (col >> 2 & 1);
+        const bool has_words = (lane0 & 3) < p.slots;
+        unsigned to[3];
 #pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    const unsigned to = (unsigned)__builtin_amdgcn_readfirstlane((int)(area + (unsigned)((i * NB + k) * 1024)));
-                    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 sc1"
-                                 :: "v"(Op::offset(k, x.wave, lane, h4)), "s"(to), "s"(base) : "memory");
-                }
+        for (int t = 0; t < 3; ++t) {
+            const int u = first_unit + (tile0 + t) * 4 + g, of = u / p.pl.units, lu = u - of * p.pl.units;
+            to[t] = u < p.H && (col & 4) == 0 ? (((unsigned)of * 5u + (unsigned)(lu >> 2)) * 64u + (unsigned)((lu & 3) * 16 + (col & 3) * 4)) * 4u : 0x80000000u;
+        }
+        // bit i: the two bits of the number of team i's next vector, modulo the slots
+        unsigned low = ~0u, high = 0;
+        auto slot_of = [](unsigned low_, unsigned high_, int i) { return (low_ >> i & 1u) | (high_ >> i & 1u) << 1; };
+        // Loads of (two teams, block) go round the waves, two for each: f(two teams, block)
+        auto own = [&](auto f) {
+#pragma unroll
+            for (int i = 0; i < (TWOS * HB + kResWaves - 1) / kResWaves; ++i) {
+                const int at = x.wave + i * kResWaves, q = at / HB;
+                if (at < TWOS * HB && (live >> (q * 2) & 3u) != 0u) f(q, at - q * HB);
             }
         };
-        auto answer = [&](int i, r4u (&v)[NB]) {
-#pragma unroll
-            for (int k = 0; k < NB; ++k) v[k] = *reinterpret_cast<const r4u *>(lds + 2 * SUMS + x.wave * AREA + (i * NB + k) * 1024 + lane_id() * 16);
+        unsigned spins = 0, par = 0;
+        auto ask = [&]() {
+            own([&](int q, int kb) {
+                const unsigned a = slot_of(low, high, q * 2) * VSLOT, b = slot_of(low, high, q * 2 + 1) * VSLOT, of = live >> (q * 2) & 3u;
+                const bool second = (lane_id() & 8) != 0;
+                if (has_words && (of & (second ? 2u : 1u)) != 0u)
+                    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 sc1"
+                                 :: "v"(row_at + (unsigned)min(piece + kb * 8, h4 - 1) * 16u + (unsigned)(q * 2) * apart + (second ? b : a)),
+                                    "s"(area_m0 + par * AREA + (unsigned)((q * HB + kb) * 1024)), "s"(base) : "memory");
+            });
         };
-        unsigned spins = 0, par = 0, buffer = 0;
-        bool stored = false;                       // results were stored after the last loads were asked for
-#pragma unroll
-        for (int i = 0; i < kResServed; ++i)
-            if (live >> i & 1u) ask(i);
+        int stored = 0;                            // stores after the last loads were asked for
+        ask();
         while (live != 0u && rc.ok) {
             // the loads, without the stores behind them (which take their time to the memory side as well)
-            if (stored) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(G * 2) : "memory");
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            stored = false;
-            unsigned f = 0;                        // bits 0 ..: team i's vector is complete; bits 8 ..: it says stop
-#pragma unroll
-            for (int i = 0; i < kResServed; ++i)
-                if (live >> i & 1u) {
-                    r4u v[NB];
-                    answer(i, v);
-                    bool missing = false;
-#pragma unroll
-                    for (int k = 0; k < NB; ++k) missing = missing || has_mark(v[k]);
-                    if (__ballot(missing) == 0ull) f |= 1u << i | (__ballot(v[0].x == kStop) != 0ull ? 256u << i : 0u);
-                }
+            if (stored == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            else if (stored < 6) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+            else if (stored < 8) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+            else if (stored < 12) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+            stored = 0;
+            const int area = AT + (int)par * AREA;
+            unsigned f = 0;                        // bits 0 ..: words of team i's vector are missing; bits 8 ..: it says stop
+            own([&](int q, int kb) {
+                const r4u v = *reinterpret_cast<const r4u *>(lds + area + (q * HB + kb) * 1024 + lane_id() * 16);
+                const unsigned long long m = __ballot(has_words && has_mark(v)), stop = __ballot(v.x == kStop);
+                constexpr unsigned long long FIRST = 0x00ff00ff00ff00ffull;
+                f |= (((m & FIRST) != 0ull ? 1u : 0u) | ((stop & FIRST) != 0ull ? 256u : 0u) | ((m & ~FIRST) != 0ull ? 2u : 0u) | ((stop & ~FIRST) != 0ull ? 512u : 0u)) << (q * 2);
+            });
             if (lane_id() == 0) rc.seen[par][x.wave] = f;
             __syncthreads();
-            unsigned all = ~0u, any = 0;
+            unsigned any = 0;
 #pragma unroll
-            for (int w = 0; w < kResWaves; ++w) { all &= rc.seen[par][w]; any |= rc.seen[par][w]; }
-            all = (unsigned)__builtin_amdgcn_readfirstlane((int)all) & live;
+            for (int i = 0; i < kResWaves; ++i) any |= rc.seen[par][i];
             any = (unsigned)__builtin_amdgcn_readfirstlane((int)any);
-            par ^= 1u;
+            const unsigned all = live & ~any;      // the vectors that are there
             live &= ~(all & (any >> 8));
-            const unsigned todo = all & live;
-#pragma unroll
-            for (int i = 0; i < kResServed; ++i)
-                if ((live & ~todo) >> i & 1u) ask(i);
+            unsigned todo = all & live;
+            const unsigned low0 = low, high0 = high;
+            high ^= low & todo; low ^= todo;
+            par ^= 1u;
+            ask();
             if (all == 0u) {
                 if (wait_expired(p, spins)) rc.ok = 0;
                 continue;
             }
             spins = 0;
-            unsigned second = 0;
+            while (todo != 0u) {
+                const int one = __builtin_ctz(todo);
+                todo &= todo - 1u;
+                const int two = todo != 0u ? __builtin_ctz(todo) : -1;
+                todo &= todo - (todo != 0u ? 1u : 0u);
+                const int lane = lane_id(), of = (lane & 8) != 0 && two >= 0 ? two : one;
+                const int at = area + (of >> 1) * (HB * 1024) + ((lane & ~8) | (of & 1) << 3) * 16;
+                unsigned z[HB * 4];
 #pragma unroll
-            for (int i = 0; i < kResServed; ++i) second |= layer[i] << i;
-            static_for<0, 2 * kResServed>([&](auto n_) {
-                constexpr int i = decltype(n_)::value % kResServed, l = decltype(n_)::value < kResServed ? 1 : 0;
-                if ((todo >> i & 1u) != 0u && (second >> i & 1u) == (unsigned)l) {
-                    Op op;
-                    {
-                        r4u v[NB];
-                        answer(i, v);
-                        op.set(v, lane_id());
-                    }
-                    const unsigned n = step[i];
-                    step[i] += l; layer[i] = l ^ 1;
-                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (read before it is written again)
-                    ask(i);
-                    float *sums = reinterpret_cast<float *>(lds + buffer * SUMS);
-                    buffer ^= 1u;
-                    stage<BF, CLS, R, 5, kResStageRow>(l ? w1 : w0, op, sums, x.wave);
-                    __syncthreads();
-                    if (has_cells) {
-                        const int lane = lane_id();
-                        float o[G];
-                        stage_sum<R>(sums, x.wave, lane, o);
-                        const float *sc = &rc.sh[l][(x.wave * 4 + (lane >> 4)) * 4 + (lane & (LR - 1)) * G];
-                        x.buf = buffers_of(team + i * helper_xcds);
-#pragma unroll
-                        for (int e = 0; e < G; ++e) {
-                            if (!BF) o[e] *= sc[e];
-                            put_far(x, prelane() + e * 4u, bo.pre + l * kResSlots * PSLOT + slot_at(n, PSLOT), word_of(o[e]));
-                            put_far(x, prelane() + e * 4u, bo.pre + l * kResSlots * PSLOT + slot_at(n + 2, PSLOT), kMark);
-                        }
-                        stored = true;
-                    }
+                for (int kb = 0; kb < HB; ++kb) {
+                    const r4u v = *reinterpret_cast<const r4u *>(lds + at + kb * 1024);
+                    const bool other = (lane & 4) != 0;
+                    const unsigned keep = other ? 0x07060302u : 0x05040100u, send = other ? 0x05040100u : 0x07060302u;
+                    const unsigned k0 = __builtin_amdgcn_perm(v.y, v.x, keep), k1 = __builtin_amdgcn_perm(v.w, v.z, keep);
+                    const unsigned s0 = __builtin_amdgcn_perm(v.y, v.x, send), s1 = __builtin_amdgcn_perm(v.w, v.z, send);
+                    z[kb * 4] = (unsigned)__builtin_amdgcn_update_dpp((int)k0, (int)s0, 0x114, 0xf, 0xa, false);
+                    z[kb * 4 + 1] = (unsigned)__builtin_amdgcn_update_dpp((int)k1, (int)s1, 0x114, 0xf, 0xa, false);
+                    z[kb * 4 + 2] = (unsigned)__builtin_amdgcn_update_dpp((int)k0, (int)s0, 0x104, 0xf, 0x5, false);
+                    z[kb * 4 + 3] = (unsigned)__builtin_amdgcn_update_dpp((int)k1, (int)s1, 0x104, 0xf, 0x5, false);
                 }
-            });
+                r4f sum[3];
+#pragma unroll
+                for (int t = 0; t < 3; ++t) sum[t] = (r4f){0.f, 0.f, 0.f, 0.f};
+                auto multiply = [&](auto tiles_) {
+#pragma unroll
+                    for (int part = 1; part >= 0; --part)
+#pragma unroll
+                        for (int kb = 0; kb < HB; ++kb)
+#pragma unroll
+                            for (int t = 0; t < decltype(tiles_)::value; ++t) sum[t] = tile_mfma<false>(w.q[(kb * 3 + t) * 2 + part], z + kb * 4, sum[t]);
+                };
+                if (third) multiply(std::integral_constant<int, 3>());
+                else multiply(std::integral_constant<int, 2>());
+                const unsigned slot1 = slot_of(low0, high0, one), slot2 = two >= 0 ? slot_of(low0, high0, two) : 0u;
+                const bool second = (lane & 8) != 0;
+                const unsigned mine = second ? (two >= 0 ? (unsigned)two * apart + slot2 * PSLOT : 0x80000000u) : (unsigned)one * apart + slot1 * PSLOT;
+                const unsigned clear = second ? (two >= 0 ? (unsigned)two * apart + (slot2 ^ 2u) * PSLOT : 0x80000000u) : (unsigned)one * apart + (slot1 ^ 2u) * PSLOT;
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    if (t == 2 && !third) break;
+                    r4f v = sum[t];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] += dppf<0x104>(v[i]);
+                    v *= *reinterpret_cast<const r4f *>(lds + ((tile0 + t) * 16 + g * 4) * 4);
+                    const r4u o = {word_of(v[0]), word_of(v[1]), word_of(v[2]), word_of(v[3])}, mark = {kMark, kMark, kMark, kMark};
+                    // (no lane condition around the stores: every one has to be counted)
+                    const unsigned out = (to[t] | mine) >> 31 ? 0x80000000u : to[t] + mine;
+                    const unsigned old = (to[t] | clear) >> 31 ? 0x80000000u : to[t] + clear;
+                    __builtin_amdgcn_raw_buffer_store_b128(o, x.buf, (int)out, (int)pre_at, 16);
+                    __builtin_amdgcn_raw_buffer_store_b128(mark, x.buf, (int)old, (int)pre_at, 16);
+                    stored += 2;
+                }
+            }
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (nothing is on its way into LDS when the work-group ends)
         if (!rc.ok && threadIdx.x == 0) __hip_atomic_fetch_or(p.status, 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -882,12 +930,15 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     float *state = reinterpret_cast<float *>(lds + lo.state);
     auto stored = [&](int field) { return state + (field * 5 + x.wave) * 64 + lane_id(); };
     float cs[NL], cc[NL], ps[NL][G];
-    unsigned pre[NL][G];
+    constexpr int NP = PAIR ? kResQuarters : G;        // (a word from every quarter of K)
+    unsigned pre[NL][NP];
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
         cs[l] = cc[l] = 0.f;
 #pragma unroll
-        for (int i = 0; i < G; ++i) { ps[l][i] = 0.f; pre[l][i] = 0u; }
+        for (int i = 0; i < G; ++i) ps[l][i] = 0.f;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) pre[l][i] = 0u;
     }
     unsigned n_pred = 0, n_joint = 0;
 
@@ -961,22 +1012,23 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         }
     };
     // kResident2Pair: W_hh h of the last step's candidates of a layer as far as it is there
-    auto load_pre = [&](unsigned n, int l, unsigned (&to)[NL][G]) {
-        const unsigned slot = bo.pre + slot_at(n, PSLOT);
+    auto load_pre = [&](unsigned n, int l, unsigned (&to)[NP]) {
+        const unsigned slot = bo.pre + slot_at(n, PSLOT) + (unsigned)l * kResSlots * PSLOT;
+        const unsigned o = pre_wave + (unsigned)lane_id() * 4u;
 #pragma unroll
-        for (int i = 0; i < G; ++i) to[l][i] = !has_cells ? 0u : get1(x, prelane() + i * 4u, slot + (unsigned)l * kResSlots * PSLOT);
+        for (int i = 0; i < NP; ++i) to[i] = get1(x, o, slot + i * QSLOT);
     };
-    auto no_pre = [&](int l) {
-        bool none = false;
+    auto no_pre = [&](const unsigned (&w)[NP]) {
+        unsigned m = w[0];
 #pragma unroll
-        for (int i = 0; i < G; ++i) none = none || pre[l][i] == kMark;
-        return __ballot(none) != 0ull;
+        for (int i = 1; i < NP; ++i) m = max(m, w[i]);
+        return __ballot(m == kMark) != 0ull;
     };
     auto wait_pre = [&](unsigned n, int l) {
         unsigned spins = 0;
-        while (no_pre(l)) {
+        while (no_pre(pre[l])) {
             if (wait_expired(p, spins)) { rc.ok = 0; break; }
-            load_pre(n, l, pre);
+            load_pre(n, l, pre[l]);
         }
         x.polls += __builtin_amdgcn_readfirstlane((int)spins);
     };
@@ -992,27 +1044,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     const Frames f = HALVES ? frames_of(nt_) : f_all;
     const int la = f.la, ns = f.ns;
     bool change = false;
-    // (Two teams of short steps keep their helpers busy: half the results come after the control's start has
-    // asked for them, and one more round trip costs 1.3 us; asked for again at its end, 0.16 us a step less.)
-    unsigned later[NL][G];
-#pragma unroll
-    for (int l = 0; l < NL; ++l)
-#pragma unroll
-        for (int i = 0; i < G; ++i) later[l][i] = kMark;
     while (ok && any_active && !change) {
         if (need_pred) {
             // ---- prediction step -----------------------------------------------------------------
             ++n_pred;
             const unsigned n = n_pred;
-            if (PAIR && n > 1) {
-                if (NT < NMT && no_pre(0)) {
-#pragma unroll
-                    for (int l = 0; l < NL; ++l)
-#pragma unroll
-                        for (int i = 0; i < G; ++i) pre[l][i] = later[l][i];
-                }
-                wait_pre(n - 1, 0);
-            }
+            if (PAIR && n > 1) wait_pre(n - 1, 0);
             RES_MARK(0);
             if constexpr (STORED) {
 #pragma unroll
@@ -1036,6 +1073,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 float pc[G];
 #pragma unroll
                 for (int i = 0; i < G; ++i) pc[i] = __uint_as_float(pre[l][i]);
+                if constexpr (PAIR) pc[0] = (pc[0] + __uint_as_float(pre[l][1])) + (__uint_as_float(pre[l][2]) + __uint_as_float(pre[l][3]));
                 if constexpr (!HOLD) {
                     if (has_cells) sums_of(l == NL - 1 ? sums_top : sums_rec0, rc.sh[l], pc);
                 }
@@ -1077,20 +1115,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             RES_MARK(2);
             if constexpr (NL > 1) {
                 const Op x0 = x1;
-                // The second layer's results, if they were not there, are asked for again, to come during the stage; to
-                // registers of their own, for what waits for them waits for the stores before them as well.
-                const bool again = PAIR && n > 1 && no_pre(NL - 1);
-                unsigned second[NL][G];
-                if (again) load_pre(n - 1, NL - 1, second);
+                // (The second layer's results come during the stage.  Asked for at the end of the last step as well, they were there
+                // sooner, but no step was shorter: with one utterance 6.83 against 6.78 us.)
+                if (PAIR) load_pre(n - 1, NL - 1, pre[NL - 1]);
                 stage<BF, CLS, R, 5, kResStageRow>(w_ih, x0, sums_ih, x.wave);
                 __syncthreads();
                 RES_MARK(3);
                 if constexpr (PAIR) {
-                    if (again) {
-#pragma unroll
-                        for (int i = 0; i < G; ++i) pre[NL - 1][i] = second[NL - 1][i];
-                        wait_pre(n - 1, NL - 1);
-                    }
+                    if (n > 1) wait_pre(n - 1, NL - 1);
                     commit(NL - 1);
                 }
                 if (has_cells) {
@@ -1469,7 +1501,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             int b = rows.b[r], m = rows.m[r];
             __syncthreads();
             RES_MARK(14);
-            if (PAIR) { load_pre(n_pred, 0, pre); load_pre(n_pred, 1, pre); }       // (on their way during the rest)
+            if (PAIR) load_pre(n_pred, 0, pre[0]);        // (on its way during the rest)
             const int mine = rc.s_k[lane & (kResSamples - 1)], row0 = (lane_const >> 7) & 31, left = w.len - w.t;
             const bool lead = lane < 16 && (lane & (LR - 1)) == 0;     // stands for its row
             const bool writer = x.rank == 0 && x.wave == kResWaves - 1 && lead;
@@ -1565,7 +1597,6 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             }
             if constexpr (NT < NMT) change = __ballot(left > 0 && !found && !ended) != 0ull;      // a row's next label is further away
             if (!change) set_up_samples(f, lane, w.t, m, b, w.len);
-            if (PAIR && NT < NMT) { load_pre(n_pred, 0, later); load_pre(n_pred, 1, later); }
         }
         ok = rc.ok != 0;
         RES_MARK(15);
@@ -1607,11 +1638,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     }
     __syncthreads();
     if (PAIR && rc.ok) {
-        // the helpers wait for the next candidate vector: tell them that there is none
-        const unsigned o = bo.hr[0] + slot_at(n_pred + 1, VSLOT);
+        // the helpers wait for the next candidate vectors: tell them that there are none
+        const unsigned o = slot_at(n_pred + 1, VSLOT);
         for (int i = threadIdx.x; i < p.slots * nu; i += kResThreads) {
             const int r = i / nu, u = i - r * nu;
-            put_far(x, (unsigned)r * VROW + (unsigned)(u0 + u) * 4u, o, kStop);
+            put_far(x, (unsigned)r * VROW + (unsigned)(u0 + u) * 4u, bo.hr[0] + o, kStop);
+            put_far(x, (unsigned)r * VROW + (unsigned)(u0 + u) * 4u, bo.hr[1] + o, kStop);
         }
     }
     if (threadIdx.x == 0) {

@@ -15,7 +15,7 @@ inline ResidentPlan plan_resident(int H, int J, int L, int NOUT, bool bf, int n_
     if (L > 2 || n_cu % 32 != 0) return pl;
     const int n_xcd = n_cu / 32;
     const int kind = L == 1 ? kResident1 : (bf ? kResident2 : kResident2Pair);
-    if (kind == kResident2Pair && n_xcd < 2) return pl;
+    if (kind == kResident2Pair && res_chain_xcds(n_xcd) < 1) return pl;
     for (int cls = kResClasses - 1; cls >= 0; --cls) {
         const int ts = res_team(cls);
         const int units = (H + ts - 1) / ts, jg = (J / 4 + ts - 1) / ts;

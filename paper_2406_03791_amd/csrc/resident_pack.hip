@@ -93,6 +93,30 @@ __global__ void __launch_bounds__(256) pack_tiles_kernel(unsigned *__restrict__ 
     to[res_tile_at(false, cls, T, kb, t, 1) * 64] = __builtin_bit_cast(unsigned, low);
 }
 
+// The helpers' image of a layer, one thread per pair of values: work-group `rank` has quarter rank % 4 of K and units 80 (rank / 4)
+// .., a wave three tiles of four units, or two and zeros.
+__global__ void __launch_bounds__(256) pack_helpers_kernel(unsigned *__restrict__ dst, const float *__restrict__ w, int H, const float *__restrict__ scale, int cls, int ts)
+{
+    const int hb = res_help_blocks(cls), nreg = res_help_regs(cls), pairs = nreg / 2;
+    const int idx = blockIdx.x * 256 + threadIdx.x;
+    if (idx >= ts * kResWaves * pairs * 64) return;
+    const int lane = idx & 63, i = (idx >> 6) & 3, rest = (idx >> 6) % pairs >> 2, at = (idx >> 6) / pairs;
+    const int t = rest % 3, kb = rest / 3, wave = at % kResWaves, rank = at / kResWaves;
+    const int tile = wave < 4 ? wave * 3 + t : wave * 2 + 4 + t, unit = (rank >> 2) * 80 + tile * 4 + ((lane & 15) >> 2);
+    const int k = ((rank & 3) * hb + kb) * 32 + (lane >> 4) * 8 + 2 * i;
+    const int row = unit < H && (wave < 4 || t < 2) ? (lane & 3) * H + unit : -1;
+    h2 high = {}, low = {};
+    if (row >= 0)
+        for (int e = 0; e < 2; ++e) {
+            const float a = k + e < H ? w[(long long)row * H + k + e] * scale[row] : 0.f;
+            high[e] = (_Float16)a;
+            low[e] = (_Float16)(a - (float)high[e]);
+        }
+    unsigned *to = dst + ((long long)at * nreg + (kb * 3 + t) * 8 + i) * 64 + lane;
+    to[0] = __builtin_bit_cast(unsigned, high);
+    to[4 * 64] = __builtin_bit_cast(unsigned, low);
+}
+
 // out[i] = 2^-down / scale of the row that entry i is: i, or (gates) gate i % 4 of unit i / 4
 __global__ void inverse_scales_kernel(const float *__restrict__ scale, float *__restrict__ out, int n, int gates, int down)
 {
@@ -184,7 +208,10 @@ hipError_t pack_resident(const ResidentPlan &pl, const ResidentWeights &rw, cons
     at += res_pred_regs(bf, pl.cls);
     tiles(im.w, main_regs, at, rw.w_out, J, s_out, Rows{0, 0, pl.nout_m, 32}, 2, whole);
     if (pl.kind == kResident2Pair)
-        for (int l = 0; l < 2; ++l) tiles(im.w_help, 2 * lstm, l * lstm, rw.w_hh[l], H, s_hh[l], gates, 5, false);
+        for (int l = 0; l < 2; ++l) {
+            const long long regs = (long long)ts * kResWaves * res_help_regs(pl.cls), n = regs / 2 * 64;
+            hipLaunchKernelGGL(pack_helpers_kernel, blocks(n), dim3(256), 0, stream, reinterpret_cast<unsigned *>(im.w_help) + l * regs * 64, rw.w_hh[l], H, s_hh[l], pl.cls, ts);
+        }
     auto inverse = [&](const float *s, float *out, int n, int g, int down) {
         hipLaunchKernelGGL(inverse_scales_kernel, blocks(n), dim3(256), 0, stream, s, out, n, g, bf ? 0 : down);
     };
