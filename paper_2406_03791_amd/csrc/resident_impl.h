@@ -235,6 +235,27 @@ __device__ __forceinline__ void receive(const ResidentParams &p, RCtx &x, const 
     }
     x.polls += __builtin_amdgcn_readfirstlane((int)spins);
 }
+// The same with the first loads ahead of what is done meanwhile.
+template <int N>
+__device__ __forceinline__ void request(const RCtx &x, const unsigned (&off)[N], unsigned imm, r4u (&v)[N], bool takes = true)
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = (r4u){0u, 0u, 0u, 0u};
+    if (takes) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = get4(x, off[i], imm);
+    }
+}
+template <int N>
+__device__ __forceinline__ void receive_rest(const ResidentParams &p, RCtx &x, const unsigned (&off)[N], unsigned imm, r4u (&v)[N], bool takes = true)
+{
+    bool missing = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) missing = missing || has_mark(v[i]);
+    if (__ballot(missing) == 0ull) return;
+    ++x.polls;
+    receive<N>(p, x, off, imm, v, takes);
+}
 
 template <int CTRL>
 __device__ __forceinline__ float dppf(float v)
@@ -385,8 +406,10 @@ struct Operand {
 
 // A dense stage with T tiles of 16 outputs: the sums over the wave's eighth of K go to LDS, [wave][row][ROW floats].
 // fp32: the products with the weights' low parts come before the others, to be added at their own size.
-template <bool BF, int CLS, int R, int T, int ROW>
-__device__ __forceinline__ void stage(const RegW<res_tile_regs(BF, CLS, T)> &w, const Operand<BF, CLS, R> &x, float *sums, int wave)
+// behind(): done while the matrix instructions end.
+struct Nothing { __device__ __forceinline__ void operator()() const {} };
+template <bool BF, int CLS, int R, int T, int ROW, class F = Nothing>
+__device__ __forceinline__ void stage(const RegW<res_tile_regs(BF, CLS, T)> &w, const Operand<BF, CLS, R> &x, float *sums, int wave, F behind = F())
 {
     constexpr int NH = res_halves(CLS), NF = NH / 2;
     constexpr bool MIXED = NF > 0 && NH % 2 != 0, APART = MIXED && T < 4;
@@ -417,6 +440,7 @@ __device__ __forceinline__ void stage(const RegW<res_tile_regs(BF, CLS, T)> &w, 
     }
     if constexpr (!BF) static_for<0, NF>([&](auto kb_) { block(kb_, low); });
     static_for<0, NF>([&](auto kb_) { block(kb_, high); });
+    behind();
     const int lane = lane_id(), n = lane & 15;
 #pragma unroll
     for (int t = 0; t < T; ++t) {
@@ -1137,9 +1161,29 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 }
                 RES_MARK(4);
                 // (while the hand-over is on its way) the recurrent part of the next step's first layer
-                if constexpr (NREC > 1) stage<BF, CLS, R, 5, kResStageRow>(w_hh[0], x0, sums_rec0, x.wave);
-                RES_MARK(5);
-                x1.receive_from(p, x, bo.h[1] + slot_at(n, VSLOT), h4);
+                if constexpr (NREC > 1) {
+                    r4u v[NB];
+                    auto places = [&](unsigned (&off)[NB], int lane) {
+#pragma unroll
+                        for (int i = 0; i < NB; ++i) off[i] = Op::offset(i, x.wave, lane, h4);
+                    };
+                    stage<BF, CLS, R, 5, kResStageRow>(w_hh[0], x0, sums_rec0, x.wave, [&]() {
+                        unsigned off[NB];
+                        const int lane = lane_id();
+                        places(off, lane);
+                        request<NB>(x, off, bo.h[1] + slot_at(n, VSLOT), v, Op::takes(lane, p.slots));
+                        ordered();
+                    });
+                    RES_MARK(5);
+                    unsigned off[NB];
+                    const int lane = lane_id();
+                    places(off, lane);
+                    receive_rest<NB>(p, x, off, bo.h[1] + slot_at(n, VSLOT), v, Op::takes(lane, p.slots));
+                    x1.set(v, lane);
+                } else {
+                    RES_MARK(5);
+                    x1.receive_from(p, x, bo.h[1] + slot_at(n, VSLOT), h4);
+                }
             }
             RES_MARK(6);
             // prediction-side joint projection
@@ -1171,31 +1215,46 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 }
             };
             if constexpr (NREC > 1 && HOLD) keep_sums(0, sums_rec0);
-            if constexpr (NREC > 0) {
-                stage<BF, CLS, R, 5, kResStageRow>(w_hh[NREC - 1], x1, sums_top, x.wave);
-                if constexpr (HOLD) {
-                    __syncthreads();
-                    keep_sums(NL - 1, sums_top);
-                }
-            }
-            RES_MARK(8);
             {
                 // the wave's eighth of q, NH * 4 pieces a row
                 constexpr int PW = NH * 4, N = (R * PW + 63) / 64;
+                constexpr bool EARLY = NREC > 0 && NF > 0;
                 constexpr unsigned INV = (65536u + PW - 1u) / PW;         // i / PW for i < 256
-                unsigned off[N];
                 r4u v[N];
-                const int lane = lane_id(), j4 = p.J >> 2;
-                auto index = [&](int i) { return (unsigned)min(lane + i * 64, p.slots * PW - 1); };
+                const int j4 = p.J >> 2;
+                auto index = [&](int lane, int i) { return (unsigned)min(lane + i * 64, p.slots * PW - 1); };
+                auto places = [&](unsigned (&off)[N], int lane) {
 #pragma unroll
-                for (int i = 0; i < N; ++i) {
-                    const unsigned at = index(i), r = __umul24(at, INV) >> 16;
-                    off[i] = r * VROW + (unsigned)min(x.wave * PW + (int)(at - r * PW), j4 - 1) * 16u;
+                    for (int i = 0; i < N; ++i) {
+                        const unsigned at = index(lane, i), r = __umul24(at, INV) >> 16;
+                        off[i] = r * VROW + (unsigned)min(x.wave * PW + (int)(at - r * PW), j4 - 1) * 16u;
+                    }
+                };
+                unsigned off[N];
+                if constexpr (NREC > 0) {
+                    // (Asked for when the work that fills the time is all but done: with the same for the second layer's vector
+                    // above, 32 utterances in the bfloat16 mode take 962 instead of 980 us.  In the narrowest class there is
+                    // less to do and it comes too early: 126.7 instead of 125.8 us for one utterance of 20 frames.)
+                    stage<BF, CLS, R, 5, kResStageRow>(w_hh[NREC - 1], x1, sums_top, x.wave, [&]() {
+                        if (!EARLY) return;
+                        unsigned o[N];
+                        places(o, lane_id());
+                        request<N>(x, o, bo.q + slot_at(n, VSLOT), v);
+                        ordered();
+                    });
+                    if constexpr (HOLD) {
+                        __syncthreads();
+                        keep_sums(NL - 1, sums_top);
+                    }
                 }
-                receive<N>(p, x, off, bo.q + slot_at(n, VSLOT), v);
+                RES_MARK(8);
+                const int lane = lane_id();
+                places(off, lane);
+                if constexpr (EARLY) receive_rest<N>(p, x, off, bo.q + slot_at(n, VSLOT), v);
+                else receive<N>(p, x, off, bo.q + slot_at(n, VSLOT), v);
 #pragma unroll
                 for (int i = 0; i < N; ++i) {
-                    const unsigned at = index(i), r = __umul24(at, INV) >> 16;
+                    const unsigned at = index(lane, i), r = __umul24(at, INV) >> 16;
                     float4 o = __builtin_bit_cast(float4, v[i]);
                     if (!BF && !WHOLE) o = make_float4(o.x * z_scale, o.y * z_scale, o.z * z_scale, o.w * z_scale);
                     if (x.wave * PW + (int)(at - r * PW) < j4) *reinterpret_cast<float4 *>(lq + r * QS + (at - r * PW) * 4) = o;
