@@ -593,7 +593,7 @@ int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
     // (infinite or undefined weights have no fp16 parts: such a model is left to the other kernel)
     if (found[0]) { e->res.kind = kResidentNone; return RNNT_OK; }
     std::memcpy(&e->res_q_bound, &found[1], sizeof(float));
-    HIP_TRY(e->res_xbuf.alloc((size_t)resident_buf(pl.cls, 4).bytes * pl.n_teams));
+    HIP_TRY(e->res_xbuf.alloc((size_t)resident_buf(pl.cls).bytes * pl.n_teams));
     HIP_TRY(e->res_form.alloc((size_t)pl.n_xcd * 32 * sizeof(unsigned)));
     HIP_TRY(e->res_stats.alloc((size_t)pl.n_teams * kStatStride * sizeof(long long)));
     HIP_TRY(hipMemset(e->res_form.p, 0, (size_t)pl.n_xcd * 32 * sizeof(unsigned)));
@@ -604,7 +604,7 @@ int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
 // Utterances a team decodes at a time and frames per utterance and joint step for a launch of nb.
 void resident_rows(const ResidentPlan &pl, int nb, int *slots, int *la)
 {
-    *slots = std::min(4, (nb + pl.n_teams - 1) / pl.n_teams);
+    *slots = std::min(kResRows, (nb + pl.n_teams - 1) / pl.n_teams);
     *la = *slots <= 2 ? 16 / *slots : kResSamples / *slots;
     *la = std::min(*la, 16);
 }
@@ -1165,13 +1165,13 @@ int rnnt_label_looping_decode_noalloc(rnnt_engine *eng, const float *enc_out, co
         size_t off = 0;
         auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
         const size_t o_P = take((size_t)B * T * eng->d.J * sizeof(float));
-        const size_t o_x = take((size_t)resident_buf(pl.cls, 4).bytes * pl.n_teams);
+        const size_t o_x = take((size_t)resident_buf(pl.cls).bytes * pl.n_teams);
         const size_t o_f = take((size_t)pl.n_xcd * 32 * sizeof(unsigned));
         const size_t o_s = take((size_t)pl.n_teams * kStatStride * sizeof(long long));
         const size_t o_a = take(sizeof(unsigned)), o_st = take(sizeof(int));
         auto sized = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
         auto of_teams = [&](int n, size_t buf) { return sized(buf * n) + sized((size_t)n * kStatStride * sizeof(long long)); };
-        const ResidentBuf buf = resident_buf(pl.cls, 4);
+        const ResidentBuf buf = resident_buf(pl.cls);
         const int teams = pl.kind == kResident2Pair ? pl.n_teams - pl.n_teams / 6 : pl.n_teams;
         const size_t extra = of_teams(pl.n_teams, buf.bytes) - of_teams(teams, buf.pre + (buf.bytes - buf.pre) / kResQuarters);
         if (off > RNNT_NOALLOC_SCRATCH_BYTES + extra || off > kScratchTop) return RNNT_ERR_SCRATCH;

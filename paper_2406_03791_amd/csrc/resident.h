@@ -12,7 +12,7 @@ constexpr int kResThreads = 512;          // eight waves, two per SIMD: 256 regi
 constexpr int kResWaves = 8;
 constexpr int kResUnits = 20;             // LSTM units per work-group at most
 constexpr int kResSlots = 4;              // exchange slots per vector, used in turn
-constexpr int kResRows = 8;               // utterances a team decodes at the same time at most: instances for 4 and 8
+constexpr int kResRows = 4;               // utterances a team decodes at the same time at most
 constexpr int kResSamples = 32;           // (utterance, frame) pairs per joint step at most
 constexpr int kResCalm = 16;              // joint steps after which a row's frames are halved, see the loop control
 constexpr int kResList = 128;             // utterances a team takes per launch at most
@@ -57,7 +57,7 @@ enum ResidentKind {
     kResident2Pair = 3,   // two layers in fp32: a team on one XCD, the recurrent matrices on a second one
 };
 // kResident2Pair: most XCDs have teams, and each pair of the others, one for either layer, works for up to kResServed of them.
-// (Six and two of eight: with five and three, helpers had more time, and 128 utterances took 5.65 instead of 5.29 ms.)
+// (Six and two of eight: with five and three, and helpers that had both matrices, 128 utterances took 5.65 instead of 5.29 ms.)
 constexpr int kResServed = 6;
 RNNT_HD constexpr int res_chain_xcds(int n_xcd) { return n_xcd - (n_xcd + kResServed + 1) / (kResServed + 2) * 2; }
 
@@ -102,12 +102,12 @@ struct ResidentParams {
     int count_rows;       // prediction steps are counted per utterance (Algorithm 1) instead of per team
 };
 
-// Byte offsets of a team's exchange buffers, every vector in kResSlots slots; R: rows of the instance, 4 or 8.
+// Byte offsets of a team's exchange buffers, every vector in kResSlots slots.
 // pre: [layer][slot][quarter of K][rank][wave of the cells][lane]
 struct ResidentBuf { unsigned h[2], q, key, dur, lse, hr[2], pre, bytes; };
-RNNT_HD constexpr ResidentBuf resident_buf(int cls, int R)
+RNNT_HD constexpr ResidentBuf resident_buf(int cls)
 {
-    const unsigned vec = kResSlots * (unsigned)(R * res_width(cls)) * 4u;
+    const unsigned vec = kResSlots * (unsigned)(kResRows * res_width(cls)) * 4u;
     const unsigned recs = kResSlots * kResSamples * (unsigned)res_team(cls);
     ResidentBuf b{};
     b.h[0] = 0; b.h[1] = vec; b.q = 2 * vec; b.key = 3 * vec;
@@ -132,7 +132,7 @@ RNNT_HD constexpr int res_main_regs(int kind, bool bf, int cls)
 // LDS layout in bytes (dynamic part).  p: frames of the joint step's samples.  part: the joint step's partial sums;
 // before it, in their place, those of the input stage (ih).  proj: partial sums of the projection (read after
 // the work-group's last barrier before the joint step).  rec0, rec: those of the first and of the top layer's
-// recurrent stage, kept till the next prediction step (eight rows: till they are read, rec0 then beside ih).
+// recurrent stage, kept till the next prediction step.
 // q: every wave's eighth of q, rows of res_q_row floats (zeros beyond the joint width).  tail: the tail column (see output()),
 // tpart: its partial sums.  state: cell state and recurrent pre-activations [layer][field][wave][lane] where they are
 // not in registers.
@@ -141,30 +141,29 @@ struct ResidentLds { int p, part, ih, rec0, proj, rec, q, tail, tpart, state, by
 constexpr int kResSumRow = 36;            // floats per row of partial sums: of the joint step, of the projection
 constexpr int kResStageRow = 80;          // and of the LSTM stages
 RNNT_HD constexpr int res_q_row(int cls) { return res_row(cls) / 8 + 4; }
-RNNT_HD constexpr ResidentLds resident_lds(int kind, int cls, int nmt, int R)
+RNNT_HD constexpr ResidentLds resident_lds(int kind, int cls, int nmt)
 {
     ResidentLds l{};
-    const int stage = kResWaves * R * kResStageRow * 4, sums = kResWaves * 16 * nmt * kResSumRow * 4;
+    const int stage = kResWaves * kResRows * kResStageRow * 4, sums = kResWaves * 16 * nmt * kResSumRow * 4;
     l.p = 0;
     l.part = l.ih = 16 * nmt * res_row(cls) * 4;
     int at = l.ih + (kind == kResident1 ? 0 : stage);
-    if (kind == kResident2 && R == 8) { l.rec0 = at; at += stage; }
     if (at < l.part + sums) at = l.part + sums;
-    l.proj = at; at += kResWaves * R * kResSumRow * 4;
-    if (kind == kResident2 && R != 8) { l.rec0 = at; at += stage; }
+    l.proj = at; at += kResWaves * kResRows * kResSumRow * 4;
+    if (kind == kResident2) { l.rec0 = at; at += stage; }
     l.rec = at; at += kind == kResident2Pair ? 0 : stage;
-    l.q = at; at += kResWaves * R * res_q_row(cls) * 4;
+    l.q = at; at += kResWaves * kResRows * res_q_row(cls) * 4;
     l.tail = at; at += (kind == kResident2 ? 2 : res_halves(cls) == 1 ? 4 : 3) * res_row(cls) * 2;
     l.tpart = at; at += kResWaves * 2 * 16 * 4;
-    l.state = at; at += kind == kResident2Pair && R == 4 ? 6 * 5 * 64 * 4 : 0;
+    l.state = at; at += kind == kResident2Pair ? 6 * 5 * 64 * 4 : 0;
     const int help = 2048 + 2 * (kResServed / 2) * res_help_blocks(cls) * 1024;
     if (kind == kResident2Pair && at < help) at = help;
     l.bytes = (at + 15) & ~15;
     return l;
 }
 constexpr int kResCtl = 5376;             // bytes kept for the control block
-static_assert(resident_lds(kResident1, 0, 2, 4).bytes + kResCtl <= 160 * 1024 && resident_lds(kResident2, 0, 2, 4).bytes + kResCtl <= 160 * 1024 &&
-              resident_lds(kResident2Pair, 0, 2, 4).bytes + kResCtl <= 160 * 1024, "the largest layouts and the control block fit the LDS");
+static_assert(resident_lds(kResident1, 0, 2).bytes + kResCtl <= 160 * 1024 && resident_lds(kResident2, 0, 2).bytes + kResCtl <= 160 * 1024 &&
+              resident_lds(kResident2Pair, 0, 2).bytes + kResCtl <= 160 * 1024, "the largest layouts and the control block fit the LDS");
 
 // The model's matrices on the device (rows as in the model), and where their packed forms go: register images of the
 // teams' and the helpers' work-groups, [rank][wave][register][lane]; tail columns; what sums are multiplied by; the
