@@ -1615,9 +1615,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     } else {
         // Where the rows go on by less than one and a half frames a step (ten labels on every frame, say), the second
         // tile of samples is computed for nothing: then the team goes on with half the frames per row, until
-        // a row's next label is not among them.  128 utterances of ten labels on every frame: 9.7 us a step with two
-        // tiles, 8.8 with one (136.4 and 123.6 ms a call; the streaming kernel: 125.8), and with ten labels on every
-        // other frame 68.5 and 61.7 ms (62.7).  At 0.7 labels a frame the two are even; below, a team hardly ever
+        // a row's next label is not among them.  128 utterances of ten labels on every frame: 8.4 us a step with two
+        // tiles, 7.7 with one (100.7 and 92.1 ms a call), and with ten labels on every other frame 50.5 and 46.2 ms a
+        // call.  At 0.7 labels a frame the two are even; below, a team hardly ever
         // gets here, and what looking out for it costs is within 0.6 % of a call.
         // Two-layer fp32 models only: the others were faster than the streaming kernel on such input as well, and
         // their second loop costs more registers than there are (bfloat16 mode: twelve spilled, 4 to 6 % of a call).
