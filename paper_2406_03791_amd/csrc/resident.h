@@ -90,7 +90,7 @@ struct ResidentParams {
     const float *w_tail;  // [n_tail][res_row(cls)], scaled as the packed output columns
     // fp32: what sums of the scaled weights of an output are multiplied by; LSTM matrices [H][gate]
     const float *s_out, *s_pred, *s_ih, *s_hh[2];
-    float q_bound;        // no |q| is larger: hidden values are within +-1
+    float q_bound;        // no q is larger: hidden values are within +-1
     unsigned long long *p_top;            // fp32: what the call's P is like (TopWord)
     const float *T0, *bias_l, *b_pred, *b_out;
     unsigned char *xbuf;  // exchange buffers, resident_buf(cls).bytes per team
@@ -168,7 +168,7 @@ static_assert(resident_lds(kResident1, 0, 2).bytes + kResCtl <= 160 * 1024 && re
 // The model's matrices on the device (rows as in the model), and where their packed forms go: register images of the
 // teams' and the helpers' work-groups, [rank][wave][register][lane]; tail columns; what sums are multiplied by; the
 // scales of the rows, in the order of these, and two words, zero before: not every value is finite, and the largest
-// sum of the magnitudes of a row of w_pred and its bias (a float's bits; both fp32 only).
+// value of q, from above (a float's bits; both fp32 only).
 struct ResidentWeights { int H, J, L; const float *w_hh[2], *w_ih1, *w_pred, *b_pred, *w_out; };
 struct ResidentImages { float *w, *w_help, *w_tail, *s_out, *s_pred, *s_ih, *s_hh[2], *row_scales; unsigned *check; };
 hipError_t pack_resident(const ResidentPlan &pl, const ResidentWeights &rw, const ResidentImages &im, hipStream_t stream);

@@ -906,7 +906,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     float *sums_pr = reinterpret_cast<float *>(lds + lo.proj), *sums_ih = reinterpret_cast<float *>(lds + lo.ih);
     float *sums_rec0 = reinterpret_cast<float *>(lds + lo.rec0), *sums_top = reinterpret_cast<float *>(lds + lo.rec);
 
-    // fp32: the power of two that takes the bound max P + max |q| of the launch to 2^14 .. 2^15, which the joint step's
+    // fp32: the power of two that takes the bound max P + max q of the launch to 2^14 .. 2^15, which the joint step's
     // operand, and q in LDS, is multiplied by.  (Of a call with an infinite P the finite ones count, see the joint step.)
     float z_scale = 1.f;
     bool huge = false;

@@ -19,7 +19,8 @@ __device__ __forceinline__ unsigned bf16_of(float v)
 
 // One wave per row of a matrix: 2^k with 2^14 <= 2^k max|row| < 2^15, as far as it and its inverse (times the scale of
 // hidden values) are ordinary floats; check[0] is raised by a value that is not finite, check[1] is the largest row
-// sum of magnitudes, plus that of `extra`, as a float's bits.
+// sum of magnitudes and `extra`, or zero, as a float's bits: what comes before the joint's relu is bounded from above, and
+// a unit that its bias switches off, with -inf or -1e30, says nothing of the others.
 __global__ void __launch_bounds__(256) row_scales_kernel(const float *__restrict__ w, int rows, int K, float *__restrict__ scale, const float *__restrict__ extra, unsigned *check)
 {
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -35,7 +36,7 @@ __global__ void __launch_bounds__(256) row_scales_kernel(const float *__restrict
     for (int i = 32; i; i >>= 1) { top = max(top, (unsigned)__shfl_xor((int)top, i)); sum += __shfl_xor(sum, i); }
     if (lane) return;
     if (top >= 0x7f800000u) atomicOr(check, 1u);
-    if (extra) atomicMax(check + 1, __float_as_uint(fminf((sum + fabsf(extra[row])) * 1.001f, 1e38f)));
+    if (extra) atomicMax(check + 1, __float_as_uint(fminf(fmaxf((sum + extra[row]) * 1.001f, 0.f), 1e38f)));
     const float m = __uint_as_float(top);
     const int e = top >= 0x7f800000u ? 0 : (m > 0.f ? min(14 - ilogbf(m), 126 - kResHiddenExp) : 0);
     scale[row] = ldexpf(1.f, e);

@@ -281,3 +281,17 @@ def test_weights_that_are_not_finite_run_in_the_streaming_kernel(pkg):  # noqa: 
         eng.decode("label", torch.from_numpy(w.enc_out).cuda(), torch.from_numpy(w.enc_len.astype(np.int32)).cuda(), w.max_symbols)
         assert eng.status() == 0 and (eng.stats()["search_steps"] != 1) == streaming
         eng.close()
+
+
+# one layer in the two wider size classes, the widest with a tail column, and two layers
+WIDE = [(316, 320, 520, 1), (640, 640, 1025, 1), (324, 640, 530, 2)]
+
+
+@pytest.mark.parametrize("H,J,V1,L", WIDE)
+def test_prediction_biases_that_switch_joint_units_off(pkg, H, J, V1, L):  # noqa: F811
+    """-inf and -1e30 of b_pred are zeros behind the relu, and nothing to the other units."""
+    w = model_inputs(H, J, V1, L, B=9, T=12, seed=H + 1)
+    w.model.b_pred[7], w.model.b_pred[11], w.model.b_pred[J - 1] = -np.inf, -1e30, -3e38
+    eng = pkg.Engine(w.model, w.B, w.T)
+    check(pkg, w, "label", f"units off {H}/{J}/{V1}/{L}", engine=eng, logp=True)
+    eng.close()
