@@ -112,7 +112,7 @@ enc_proj_kernel(const float *__restrict__ x, const int *__restrict__ enc_len, co
     static_assert(WK == 1 || WAVES * NI * 4096 <= XBYTES, "the sums of the waves fit");
     __shared__ __align__(16) unsigned char lds[LDS];
     init_call(ci, B);
-    const TopWord call = !BF && ci.p_top ? ci.p_top[kTopWords * kTopStride] : 0;
+    const TopWord call = !BF && ci.p_top ? *ci.p_top : 0;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ny = (J + NI * 32 - 1) / (NI * 32), slot = blockIdx.x >> 3, group = (slot / ny) * 8 + (blockIdx.x & 7), n0 = slot % ny * (NI * 32);
     RowTile r = row_tile(enc_len, B, T, WK == 1 ? group * 4 + wave : group, lane);
@@ -362,7 +362,7 @@ enc_proj_kernel(const float *__restrict__ x, const int *__restrict__ enc_len, co
     if (!BF && ci.p_top) {
 #pragma unroll
         for (int i = 32; i; i >>= 1) top = fmaxf(top, __shfl_xor(top, i));
-        TopWord *word = ci.p_top + (blockIdx.x % kTopWords) * kTopStride;
+        TopWord *word = ci.p_top + top_words(r.b) + blockIdx.x % kTopParts * kTopStride;
         const bool any = __ballot(infinite) != 0ull;
         if (lane == 0) {
             atomicMax(word, call << 16 | (__float_as_uint(top) + 0xffffu) >> 16);

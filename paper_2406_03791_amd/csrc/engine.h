@@ -99,13 +99,15 @@ struct DecodeParams {
 // (zero_stats); later launches add to them.
 hipError_t launch_decode(const DecodeParams &p, bool zero_status, bool zero_stats, hipStream_t stream);
 
-// What a call's P is like, for the resident decode kernel: kTopWords pairs of words, a line of memory each (one pair
-// for all blocks took 24 us of a projection of 150), the first of the largest finite value and the second of infinite
-// ones; behind them the number of the call, which the decode kernel counts up (so a captured call does it too).  Words
-// are number << 16 | upper half of the value, rounded up, and only ever grow: nothing needs to be cleared between
-// calls, the words with the largest number are the call's.
-constexpr int kTopWords = 64, kTopStride = 8, kTopTotal = kTopWords * kTopStride + 1;
+// What a call's P is like, for the resident decode kernel: the number of the call, which the decode kernel counts up (so
+// a captured call does it too), and kTopParts pairs of words for every utterance, a line of memory each (one pair for all blocks
+// that have an utterance took 5.5 us of a projection of 17), the first of its largest finite value and the second of infinite
+// ones.  Words are number << 16 | upper half of the value, rounded up, and only
+// ever grow: nothing needs to be cleared between calls, an utterance's words with the largest number are the call's.
+// (Of the utterance, not of the call: what scales an utterance's values may not depend on the others'.)
 typedef unsigned long long TopWord;
+constexpr int kTopParts = 16, kTopStride = 8;
+constexpr size_t top_words(size_t utterances) { return (utterances * kTopParts + 1) * kTopStride; }
 
 // What the projection kernel clears for the decode kernel behind it; nothing where NULL.
 struct CallInit {
@@ -117,7 +119,7 @@ struct CallInit {
     float *logits = nullptr, *logps = nullptr;
     int cap = 0;
     long long *stats = nullptr;     // where the call's times go (kStatCallStart ...)
-    TopWord *p_top = nullptr;       // kTopTotal words on what the call's P is like
+    TopWord *p_top = nullptr;       // top_words(B) words on what the call's P is like
 };
 
 // Keeps the text of a failed HIP call for rnnt_status_string; returns RNNT_ERR_HIP.

@@ -65,7 +65,7 @@ constexpr int kStaticLds = 3072;        // kept free for the kernel's static LDS
 // for every six that two-layer fp32 models have: the rest lies in the room behind, 7.9 MB at most.)
 // kScratchTop: where the words on a call's P have their place, which every call finds as the last one left them.
 constexpr size_t kScratchTop = RNNT_NOALLOC_SCRATCH_BYTES + (8u << 20);
-static __device__ __align__(256) unsigned char scratch[kScratchTop + kTopTotal * sizeof(TopWord)];
+static __device__ __align__(256) unsigned char scratch[kScratchTop + top_words(kLaunchRows) * sizeof(TopWord)];
 
 struct DevBuf {
     void *p = nullptr;
@@ -576,8 +576,8 @@ int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
     HIP_TRY(e->res_w.alloc(images * res_main_regs(pl.kind, bf, pl.cls)));
     if (pl.kind == kResident2Pair) HIP_TRY(e->res_help.alloc(images * 2 * res_help_regs(pl.cls)));
     if (pl.n_tail) HIP_TRY(e->res_tail.alloc((size_t)pl.n_tail * res_row(pl.cls) * sizeof(float)));
-    HIP_TRY(e->res_top.alloc(kTopTotal * sizeof(TopWord)));
-    HIP_TRY(hipMemset(e->res_top.p, 0, kTopTotal * sizeof(TopWord)));
+    HIP_TRY(e->res_top.alloc(top_words(e->max_B) * sizeof(TopWord)));
+    HIP_TRY(hipMemset(e->res_top.p, 0, top_words(e->max_B) * sizeof(TopWord)));
     HIP_TRY(e->res_scales.alloc((2 * scales + 2) * sizeof(float)));        // (the second half is for the packing)
     float *rows = e->res_scales.as<float>() + scales;
     unsigned *check = reinterpret_cast<unsigned *>(rows + scales);
@@ -649,7 +649,8 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
             p.done = e->done ? e->done + off : nullptr;
             p.w = e->res_w.as<float>(); p.w_help = e->res_help.as<float>(); p.w_tail = e->res_tail.as<float>();
             p.q_bound = e->res_q_bound;
-            p.p_top = ws.top;
+            p.p_top = ws.top + top_words(off);
+            p.p_call = off == 0 ? ws.top : nullptr;
             p.s_out = e->res_scales.as<float>(); p.s_pred = p.s_out + e->NOUT; p.s_ih = p.s_pred + d.J;
             p.s_hh[0] = p.s_ih + (d.L > 1 ? 4 * d.H : 0); p.s_hh[1] = p.s_hh[0] + 4 * d.H;
             p.T0 = e->T0.as<float>(); p.bias_l = e->bias_l.as<float>(); p.b_pred = e->b_pred.as<float>(); p.b_out = e->b_out.as<float>();

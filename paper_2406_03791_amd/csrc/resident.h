@@ -91,7 +91,9 @@ struct ResidentParams {
     // fp32: what sums of the scaled weights of an output are multiplied by; LSTM matrices [H][gate]
     const float *s_out, *s_pred, *s_ih, *s_hh[2];
     float q_bound;        // no q is larger: hidden values are within +-1
-    unsigned long long *p_top;            // fp32: what the call's P is like (TopWord)
+    // fp32: what P is like (TopWord), from the first utterance's words on; the number of the call, for its first launch
+    const unsigned long long *p_top;
+    unsigned long long *p_call;
     const float *T0, *bias_l, *b_pred, *b_out;
     unsigned char *xbuf;  // exchange buffers, resident_buf(cls).bytes per team
     unsigned *form;       // one word per work-group, zero at launch: the XCD it runs on
@@ -161,7 +163,7 @@ RNNT_HD constexpr ResidentLds resident_lds(int kind, int cls, int nmt)
     l.bytes = (at + 15) & ~15;
     return l;
 }
-constexpr int kResCtl = 5376;             // bytes kept for the control block
+constexpr int kResCtl = 5568;             // bytes kept for the control block
 static_assert(resident_lds(kResident1, 0, 2).bytes + kResCtl <= 160 * 1024 && resident_lds(kResident2, 0, 2).bytes + kResCtl <= 160 * 1024 &&
               resident_lds(kResident2Pair, 0, 2).bytes + kResCtl <= 160 * 1024, "the largest layouts and the control block fit the LDS");
 

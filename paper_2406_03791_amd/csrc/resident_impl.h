@@ -93,6 +93,9 @@ struct RCtl {
     float s1[kResUnits * 4], sp[20], sh[2][kResUnits * 4];
     float2 bo[16], so[16];
     float bt, st;
+    float list_scale[kResList];       // fp32: what the joint's operand of an utterance is multiplied by, see joint_scale
+    float scale[kResRows];            // of the utterances in work
+    int huge;                         // one of the team's has an infinite P
 };
 __shared__ RCtl rc;
 static_assert(sizeof(RCtl) <= kResCtl, "the control block has its place");
@@ -482,6 +485,14 @@ __device__ __forceinline__ void cell(float pre, int j, float c_old, float &c_new
 // What the prediction step does with a row's candidate state: take it, or start afresh (else nothing).
 constexpr int kTake = 1 << 30, kFresh = (int)(1u << 31);
 
+// fp32: the power of two that takes the bound max P + max q of an utterance to 2^14 .. 2^15, which its operands of the
+// joint step, and its q in LDS, are multiplied by.  (Of infinite values of P the finite ones count, see the joint step.)
+__device__ __forceinline__ float joint_scale(TopWord top, float q_bound)
+{
+    const float bound = fminf(__uint_as_float((unsigned)top << 16) + q_bound, 1e38f);
+    return __uint_as_float((268u << 23) - max(__float_as_uint(bound) & 0x7f800000u, 27u << 23));
+}
+
 // Byte offset of step n's slot among slots of `bytes`.  (In a scalar register by force: the compiler multiplies in a
 // vector instruction and puts a loop over its lanes' values around every load and store that takes the offset.)
 __device__ __forceinline__ unsigned slot_at(unsigned n, unsigned bytes)
@@ -600,9 +611,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             }
         if (!any) return;
     }
-    if (tid0 == 0) { rc.ok = 1; rc.n_list = 0; rc.st_clamped = 0; rc.st_overflow = 0; }
+    if (tid0 == 0) { rc.ok = 1; rc.n_list = rc.huge = 0; rc.st_clamped = 0; rc.st_overflow = 0; }
     if (tid0 < kResSamples) { rc.s_k[tid0] = p.blank; rc.s_d[tid0] = 0; }
     if (tid0 < kMaxDur) rc.dur[tid0] = p.durations[tid0];
+    if (tid0 < kResRows) rc.scale[tid0] = 1.f;
     if (lane0 < kResRows) {
         RRows &w = rc.rows[x.wave];
         w.s[lane0] = RRow{0, 0, 0, 0}; w.b[lane0] = w.m[lane0] = w.since[lane0] = w.next = 0;
@@ -832,6 +844,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         const int q = pos / n_teams, m = pos - q * n_teams;
         if (((q & 1) ? n_teams - 1 - m : m) == team) {
             rc.list_b[q] = (unsigned short)b; rc.list_len[q] = len;
+            if constexpr (!BF && !WHOLE) {
+                const TopWord *words = p.p_top + (long long)b * (kTopParts * kTopStride);
+                TopWord top = 0, inf = 0;
+#pragma unroll 4                 // (the weights have the registers)
+                for (int i = 0; i < kTopParts; ++i) { top = max(top, words[i * kTopStride]); inf = max(inf, words[i * kTopStride + 1]); }
+                rc.list_scale[q] = joint_scale(top, p.q_bound);
+                if (inf >> 16 == top >> 16 && (inf & 1u) != 0u && len > 0) rc.huge = 1;
+            }
             if (len > 0) atomicAdd(&rc.n_list, 1);       // the empty ones are the last of the list
             else if (x.rank == 0) res_finish_row(b, 0);
         }
@@ -906,24 +926,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     float *sums_pr = reinterpret_cast<float *>(lds + lo.proj), *sums_ih = reinterpret_cast<float *>(lds + lo.ih);
     float *sums_rec0 = reinterpret_cast<float *>(lds + lo.rec0), *sums_top = reinterpret_cast<float *>(lds + lo.rec);
 
-    // fp32: the power of two that takes the bound max P + max q of the launch to 2^14 .. 2^15, which the joint step's
-    // operand, and q in LDS, is multiplied by.  (Of a call with an infinite P the finite ones count, see the joint step.)
-    float z_scale = 1.f;
-    bool huge = false;
-    if constexpr (!BF && !WHOLE) {
-        static_assert(kTopWords == 64, "one for every lane");
-        TopWord top = p.p_top[lane0 * kTopStride];
-        const TopWord inf = p.p_top[lane0 * kTopStride + 1];
-#pragma unroll
-        for (int i = 32; i; i >>= 1) top = max(top, (TopWord)__shfl_xor(top, i));
-        huge = __ballot(inf >> 16 == top >> 16 && (inf & 1u) != 0u) != 0ull;
-        const float bound = fminf(__uint_as_float((unsigned)top << 16) + p.q_bound, 1e38f);
-        z_scale = __uint_as_float((unsigned)__builtin_amdgcn_readfirstlane((int)((268u << 23) - max(__float_as_uint(bound) & 0x7f800000u, 27u << 23))));
-        if (x.rank == 0 && team == 0 && tid0 == 0) ++p.p_top[kTopWords * kTopStride];        // (of those here nobody reads it)
-    }
-    const float back = __uint_as_float(0x7f000000u - __float_as_uint(z_scale));       // 1 / z_scale
-    if (tid0 < 32) reinterpret_cast<float *>(rc.so)[tid0] = x.rank * 32 + tid0 < p.pl.nout_m ? p.s_out[x.rank * 32 + tid0] * back : 0.f;
-    if (tid0 == 0) rc.st = has_tail ? p.s_out[tcol] * back : 0.f;
+    if (!BF && !WHOLE && p.p_call && x.rank == 0 && team == 0 && tid0 == 0) ++*p.p_call;        // (of those here nobody reads it)
+    if (tid0 < 32) reinterpret_cast<float *>(rc.so)[tid0] = x.rank * 32 + tid0 < p.pl.nout_m ? p.s_out[x.rank * 32 + tid0] : 0.f;
+    if (tid0 == 0) rc.st = has_tail ? p.s_out[tcol] : 0.f;
 
     announce();
     x.local = meet(team, PAIR);
@@ -986,6 +991,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         const int next = rows.next, at = next + __popcll(m & ((1ull << (lane & (16 - LR))) - 1ull));
         const bool got = want && at < rc.n_list;
         if (got) { b = rc.list_b[at]; len = rc.list_len[at]; }
+        // (one place for all waves: they write the same, between the same barriers)
+        if constexpr (!BF && !WHOLE)
+            if (got) rc.scale[(lane / LR) & (R - 1)] = rc.list_scale[at];
         rows.next = next + __popcll(m);
         return got;
     };
@@ -1198,13 +1206,19 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 RES_MARK(8);
                 const int lane = lane_id();
                 places(off, lane);
+                float by[N];
+                if constexpr (!BF && !WHOLE) {
+#pragma unroll
+                    for (int i = 0; i < N; ++i) by[i] = rc.scale[__umul24(index(lane, i), INV) >> 16];
+                    ordered();                   // (read while q is on its way)
+                }
                 if constexpr (EARLY) receive_rest<N>(p, x, off, bo.q + slot_at(n, VSLOT), v);
                 else receive<N>(p, x, off, bo.q + slot_at(n, VSLOT), v);
 #pragma unroll
                 for (int i = 0; i < N; ++i) {
                     const unsigned at = index(lane, i), r = __umul24(at, INV) >> 16;
                     float4 o = __builtin_bit_cast(float4, v[i]);
-                    if (!BF && !WHOLE) o = make_float4(o.x * z_scale, o.y * z_scale, o.z * z_scale, o.w * z_scale);
+                    if constexpr (!BF && !WHOLE) o = make_float4(o.x * by[i], o.y * by[i], o.z * by[i], o.w * by[i]);
                     if (x.wave * PW + (int)(at - r * PW) < j4) *reinterpret_cast<float4 *>(lq + r * QS + (at - r * PW) * 4) = o;
                 }
             }
@@ -1222,13 +1236,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         {
             // A wave has an eighth of K for both column tiles, so the operand z = relu(P + q) of a lane's sample is
             // formed on the way: nobody else needs it.  fp32: every product is that of two fp16 parts of
-            // either side (see z_scale; layers of 640: without low times low, which made the joint step 0.1 us longer and
+            // either side (after a power of two of the utterance, see joint_scale; layers of 640: without low times low, which made the joint step 0.1 us longer and
             // the logits' error 2 % smaller), in one sum.  (Products with a low part in sums of their own made the logits' error
             // 1 to 6 % smaller, but twelve registers of the two-layer models' input weights had to be loaded from memory
             // in every step: input stage 1.18 instead of 0.96 us.)
             // (a half block comes first)
+            float scale = 1.f;               // of the lane's sample
             auto block_of = [](int b) { return NH % 2 != 0 ? (b + NB - 1) % NB : b % NB; };
-            auto form = [&](float p_, float q_) { return fmaxf(BF || WHOLE ? p_ + q_ : fmaf(p_, z_scale, q_), 0.f); };
+            auto form = [&](float p_, float q_) { return fmaxf(BF || WHOLE ? p_ + q_ : fmaf(p_, scale, q_), 0.f); };
             auto relu = [&](float4 p_, float4 q_) { return make_float4(form(p_.x, q_.x), form(p_.y, q_.y), form(p_.z, q_.z), form(p_.w, q_.w)); };
             // Where the lane's part of sample 16 mt + lane % 16 lies in the wave's eighth: of its frame and of its row's q,
             // the first four words of block i (the second four: 16 in the address inverted, or added).
@@ -1242,6 +1257,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             auto frame_at = [&](int mt, int i) { return frame0 + ((k40 + i * 8 - (i < NF ? 0 : g)) ^ m16) * 16 + mt * 16 * ROW * 4; };
             auto q_of = [&](int mt) {
                 const unsigned row = min(__umul24((unsigned)(mt * 16 + m16), f.inv_la) >> 10, (unsigned)(R - 1));
+                if constexpr (!BF && !WHOLE) scale = rc.scale[row];
                 return lo.q + (int)__umul24(row, QS * 4u) + x.wave * (R * QS * 4) + g * 32;
             };
             auto q_at = [&](int of, int i) { return of + i * 128 - (i < NF ? 0 : g * 16); };
@@ -1325,7 +1341,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             else output(std::false_type());
             if constexpr (!BF && !WHOLE) {
                 // An infinite z has no low part: there the high ones decide.
-                if (huge) {
+                if (rc.huge) {
 #pragma unroll
                     for (int mt = 0; mt < NT; ++mt)
 #pragma unroll
@@ -1366,10 +1382,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     o[w] = *reinterpret_cast<const float2 *>(part + (w * NT * 16 + s) * kResSumRow + col);
                 const float2 bias = rc.bo[tid & 15], scale = rc.so[tid & 15];
                 static_assert(kResWaves == 8, "eight lanes add the waves' sums of the tail column");
-                float tw = 0.f;
+                float tw = 0.f, back = 1.f;
+                if constexpr (!BF && !WHOLE) back = __uint_as_float(0x7f000000u - __float_as_uint(rc.scale[min(f.row_of(s), R - 1)]));
                 if (has_tail) tw = tpart[((tid & 7) * 2 + (s >> 4)) * 16 + (s & 15)];
-                const float l0 = (((o[0].x + o[1].x) + (o[2].x + o[3].x)) + ((o[4].x + o[5].x) + (o[6].x + o[7].x))) * scale.x + bias.x;
-                const float l1 = (((o[0].y + o[1].y) + (o[2].y + o[3].y)) + ((o[4].y + o[5].y) + (o[6].y + o[7].y))) * scale.y + bias.y;
+                const float l0 = (((o[0].x + o[1].x) + (o[2].x + o[3].x)) + ((o[4].x + o[5].x) + (o[6].x + o[7].x))) * scale.x * back + bias.x;
+                const float l1 = (((o[0].y + o[1].y) + (o[2].y + o[3].y)) + ((o[4].y + o[5].y) + (o[6].y + o[7].y))) * scale.y * back + bias.y;
                 const float m0 = col < n_tok ? l0 : -INFINITY, m1 = col + 1 < n_tok ? l1 : -INFINITY;
                 const float mine = fmaxf(m0, m1);
                 float m = lane_max<16>(mine);
@@ -1379,7 +1396,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 int ix = hit ? (m0 == m ? gcol : gcol + 1) : 0x7fffffff;
                 float tail = -INFINITY;
                 if (has_tail) {
-                    tail = lane_sum<8>(tw) * rc.st + rc.bt;
+                    tail = lane_sum<8>(tw) * rc.st * back + rc.bt;
                     if (tcol >= p.VT) {
                         if ((tid & 15) == 0 && s < ns) {
                             const unsigned d = ((unsigned)s * kMaxDur + (unsigned)(tcol - p.VT)) * 4u;

@@ -295,3 +295,19 @@ def test_prediction_biases_that_switch_joint_units_off(pkg, H, J, V1, L):  # noq
     eng = pkg.Engine(w.model, w.B, w.T)
     check(pkg, w, "label", f"units off {H}/{J}/{V1}/{L}", engine=eng, logp=True)
     eng.close()
+
+
+@pytest.mark.parametrize("H,J,V1,L", WIDE)
+@pytest.mark.parametrize("B", [6, 40])
+def test_a_large_utterance_leaves_the_others_alone(pkg, H, J, V1, L, B):  # noqa: F811
+    """Utterances of 1e12 and of 3e38 among ordinary ones, and one of 1e-12: every one as the oracle has it."""
+    w = model_inputs(H, J, V1, L, B=B, T=10, seed=H + B)
+    x = w.enc_out.copy()
+    x[1] *= np.float32(1e12)
+    x[4] = 0.0
+    x[4, :, 0] = 3e38                     # (its projected frames: up to 4.5e37)
+    x[5] *= np.float32(1e-12)
+    w = dataclasses.replace(w, enc_out=x, enc_len=np.maximum(w.enc_len, 3))
+    eng = pkg.Engine(w.model, w.B, w.T)
+    check(pkg, w, "label", f"large utterance {H}/{J}/{V1}/{L} {B}", engine=eng, logp=B <= 6)
+    eng.close()
