@@ -289,17 +289,6 @@ __device__ __forceinline__ float lane_sum(float v)
     return v;
 }
 
-__device__ __forceinline__ void swap32(float &a, float &b)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
-}
-__device__ __forceinline__ void swap16(float &a, float &b)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
-}
-
 // Matrix instruction on a block of a wave's share of K: `w` and `z` from the registers of that block on, four
 // of either (32 k's), two for a half block.  A matrix instruction that adds to what one of the other kind right
 // before it leaves gives wrong sums (the compiler places no wait between them): where a sum takes both kinds, the
@@ -492,6 +481,8 @@ __device__ __forceinline__ float joint_scale(TopWord top, float q_bound)
     const float bound = fminf(__uint_as_float((unsigned)top << 16) + q_bound, 1e38f);
     return __uint_as_float((268u << 23) - max(__float_as_uint(bound) & 0x7f800000u, 27u << 23));
 }
+
+__device__ __forceinline__ float inverse_power(float two_to_n) { return __uint_as_float(0x7f000000u - __float_as_uint(two_to_n)); }
 
 // Byte offset of step n's slot among slots of `bytes`.  (In a scalar register by force: the compiler multiplies in a
 // vector instruction and puts a loop over its lanes' values around every load and store that takes the offset.)
@@ -1340,34 +1331,46 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             if (has_tail) output(std::true_type());
             else output(std::false_type());
             if constexpr (!BF && !WHOLE) {
-                // An infinite z has no low part: there the high ones decide.
+                // An infinite z has no low part: then the step is computed once more, as fp32 products (the weights' parts
+                // added up again).  The lane's e-th value of a block times its e-th weight is one 16x16x4 instruction.
                 if (rc.huge) {
+#pragma unroll 1
+                    for (int mt = 0; mt < NT; ++mt) {
+                        place_lane();
+                        const int qo = q_of(mt);
+                        const float back = inverse_power(scale);
+                        r4f sum[2], tail = {0.f, 0.f, 0.f, 0.f};
+                        sum[0] = sum[1] = tail;
+                        static_for<0, NB>([&](auto k_) {
+                            constexpr int k = decltype(k_)::value, N = k < NF ? 8 : 4;
+                            typedef _Float16 Halves __attribute__((ext_vector_type(N)));
+                            float z[N];
 #pragma unroll
-                    for (int mt = 0; mt < NT; ++mt)
+                            for (int j = 0; j < N / 4; ++j) {
+                                const float4 p_ = at(frame_at(mt, k) ^ (j * 16)), q_ = at(q_at(qo, k) + j * 16);
+                                z[j * 4] = fmaxf(fmaf(q_.x, back, p_.x), 0.f); z[j * 4 + 1] = fmaxf(fmaf(q_.y, back, p_.y), 0.f);
+                                z[j * 4 + 2] = fmaxf(fmaf(q_.z, back, p_.z), 0.f); z[j * 4 + 3] = fmaxf(fmaf(q_.w, back, p_.w), 0.f);
+                            }
 #pragma unroll
-                        for (int c = 0; c < 2; ++c) {
-                            place_lane();
-                            const int qo = q_of(mt);
-                            r4f high = {0.f, 0.f, 0.f, 0.f};
-                            float m = 0.f;
-                            static_for<0, NB>([&](auto k_) {
-                                constexpr int k = block_of(decltype(k_)::value);
-                                unsigned z[4];
+                            for (int c = 0; c < 2; ++c) {
+                                auto wh = weights_of<BF, CLS, 2, k, 0>(w_ou, c), wl = weights_of<BF, CLS, 2, k, 1>(w_ou, c);
+                                asm volatile("" : "+v"(wh), "+v"(wl));           // (not added up ahead: that takes registers for the whole loop)
+                                const Halves high = __builtin_bit_cast(Halves, wh), low = __builtin_bit_cast(Halves, wl);
 #pragma unroll
-                                for (int j = 0; j < (k < NF ? 2 : 1); ++j) {
-                                    const float4 v = relu(at(frame_at(mt, k) ^ (j * 16)), at(q_at(qo, k) + j * 16));
-                                    z[j * 2] = f16_pair(v.x, v.y); z[j * 2 + 1] = f16_pair(v.z, v.w);
-                                    m = fmaxf(fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)), m);
-                                }
-                                asm volatile("s_nop 15" : "+v"(high));
-                                high = tile_mfma<BF>(weights_of<BF, CLS, 2, k, 0>(w_ou, c), z, high);
+                                for (int e = 0; e < N; ++e) sum[c] = __builtin_amdgcn_mfma_f32_16x16x4f32((float)high[e] + (float)low[e], z[e], sum[c], 0, 0, 0);
                                 ordered();
-                            });
-                            float o = m;
-                            swap32(m, o); m = fmaxf(m, o); o = m;
-                            swap16(m, o); m = fmaxf(m, o);
-                            if (m == INFINITY) *reinterpret_cast<r4f *>(part + ((x.wave * NT + mt) * 16 + m16) * kResSumRow + c * 16 + g * 4) = high;
-                        }
+                            }
+                            if (has_tail) {
+                                const _Float16 *w = reinterpret_cast<const _Float16 *>(lds + lo.tail) + x.wave * (NH * 16) + k * 32 + g * N;
+#pragma unroll
+                                for (int e = 0; e < N; ++e) tail = __builtin_amdgcn_mfma_f32_16x16x4f32(m16 == 0 ? (float)w[e] + (float)w[ROW + e] : 0.f, z[e], tail, 0, 0, 0);
+                            }
+                        });
+                        if (has_tail && g == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = tail[0] * scale;
+#pragma unroll
+                        for (int c = 0; c < 2; ++c)
+                            *reinterpret_cast<r4f *>(part + ((x.wave * NT + mt) * 16 + m16) * kResSumRow + c * 16 + g * 4) = sum[c] * scale;
+                    }
                 }
             }
             RES_MARK(11);
@@ -1383,7 +1386,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 const float2 bias = rc.bo[tid & 15], scale = rc.so[tid & 15];
                 static_assert(kResWaves == 8, "eight lanes add the waves' sums of the tail column");
                 float tw = 0.f, back = 1.f;
-                if constexpr (!BF && !WHOLE) back = __uint_as_float(0x7f000000u - __float_as_uint(rc.scale[min(f.row_of(s), R - 1)]));
+                if constexpr (!BF && !WHOLE) back = inverse_power(rc.scale[min(f.row_of(s), R - 1)]);
                 if (has_tail) tw = tpart[((tid & 7) * 2 + (s >> 4)) * 16 + (s & 15)];
                 const float l0 = (((o[0].x + o[1].x) + (o[2].x + o[3].x)) + ((o[4].x + o[5].x) + (o[6].x + o[7].x))) * scale.x * back + bias.x;
                 const float l1 = (((o[0].y + o[1].y) + (o[2].y + o[3].y)) + ((o[4].y + o[5].y) + (o[6].y + o[7].y))) * scale.y * back + bias.y;

@@ -250,6 +250,22 @@ def test_rows_of_very_different_magnitude(pkg, H, J, V1, L):  # noqa: F811
     eng.close()
 
 
+def tokens_as_the_oracle_has_them(pkg, w):  # noqa: F811
+    """Labels alone, where logits are infinite."""
+    import torch
+
+    import oracle
+    eng = pkg.Engine(w.model, w.B, w.T)
+    out = eng.decode(w.variant, torch.from_numpy(w.enc_out).cuda(), torch.from_numpy(w.enc_len.astype(np.int32)).cuda(), w.max_symbols)
+    got, n = out["tokens"].cpu().numpy().reshape(w.B, -1), out["tok_len"].cpu().numpy()
+    assert eng.status() == 0
+    eng.close()
+    ref = oracle.decode(oracle.LstmNet(w.model), w.enc_out, w.enc_len, w.max_symbols, "seq")
+    assert n.tolist() == ref.tok_len.tolist()
+    for b in range(w.B):
+        assert got[b, :n[b]].tolist() == ref.tokens[b].tolist(), b
+
+
 @pytest.mark.parametrize("value", [np.inf, 3e38])
 @pytest.mark.parametrize("H,J,V1,L", [(100, 128, 255, 1), (324, 332, 529, 1), (324, 640, 530, 2)])
 def test_projected_frames_without_a_bound(pkg, H, J, V1, L, value):  # noqa: F811
@@ -259,16 +275,7 @@ def test_projected_frames_without_a_bound(pkg, H, J, V1, L, value):  # noqa: F81
     m = w.model
     m.b_enc[7] = value
     m.w_out[:9, 7] = -np.abs(m.w_out[:9, 7])         # (not the first label)
-    eng = pkg.Engine(m, w.B, w.T)
-    import torch
-    out = eng.decode("label", torch.from_numpy(w.enc_out).cuda(), torch.from_numpy(w.enc_len.astype(np.int32)).cuda(), w.max_symbols)
-    got = out["tokens"].cpu().numpy().reshape(w.B, -1)
-    assert eng.status() == 0
-    eng.close()
-    import oracle
-    ref = oracle.decode(oracle.LstmNet(m), w.enc_out, w.enc_len, w.max_symbols, "label")
-    for b in range(w.B):
-        assert got[b, :len(ref.tokens[b])].tolist() == ref.tokens[b].tolist(), b
+    tokens_as_the_oracle_has_them(pkg, w)
 
 
 def test_weights_that_are_not_finite_run_in_the_streaming_kernel(pkg):  # noqa: F811
@@ -311,3 +318,18 @@ def test_a_large_utterance_leaves_the_others_alone(pkg, H, J, V1, L, B):  # noqa
     eng = pkg.Engine(w.model, w.B, w.T)
     check(pkg, w, "label", f"large utterance {H}/{J}/{V1}/{L} {B}", engine=eng, logp=B <= 6)
     eng.close()
+
+
+@pytest.mark.parametrize("value", [np.inf, 3e38])
+@pytest.mark.parametrize("L,durations", [(1, ()), (2, ()), (1, (0, 1, 2, 3, 4)), (2, (0, 1, 2, 3, 4))])
+def test_projected_frames_without_a_bound_reach_the_tail_column(pkg, L, durations, value):  # noqa: F811
+    """640/640/1025: blank is a tail column, and so are all five durations.  An infinite column of the projected frames
+    makes the blank (TDT: label 9 and duration 3) the only infinite output that is positive."""
+    V1 = 1025
+    w = model_inputs(640, 640, V1, L, B=20, T=6, seed=L, durations=durations, max_symbols=2)
+    m = w.model
+    m.b_enc[7] = value
+    m.w_out[:, 7] = -np.abs(m.w_out[:, 7]) - np.float32(1e-3)
+    for row in (9, V1 + 3) if durations else (V1 - 1,):
+        m.w_out[row, 7] = 0.125
+    tokens_as_the_oracle_has_them(pkg, w)
