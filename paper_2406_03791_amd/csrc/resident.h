@@ -32,6 +32,7 @@ RNNT_HD constexpr int res_halves(int cls) { return res_row(cls) / 128; }
 // Kept in as many registers as the value itself.  Against 64 bits the logits of layers of 320 and 640 are 0 to 6 % closer
 // than with fp32 products in a chain.  In the narrowest class, whose chains are short, they were 7 % further
 // off: its joint output has whole fp32 values (res_whole, four 16x16x4 for a half block).
+constexpr float kResHuge = 1e38f;         // operands of the joint step from here on may have no parts
 constexpr int kResHiddenExp = 15;         // hidden values travel as fp16 parts of 2^15 times themselves (fp32)
 RNNT_HD constexpr bool res_whole(bool bf, int cls) { return !bf && res_halves(cls) == 1; }
 RNNT_HD constexpr int res_parts(bool bf) { return bf ? 1 : 2; }
@@ -90,7 +91,7 @@ struct ResidentParams {
     const float *w_tail;  // [n_tail][res_row(cls)], scaled as the packed output columns
     // fp32: what sums of the scaled weights of an output are multiplied by; LSTM matrices [H][gate]
     const float *s_out, *s_pred, *s_ih, *s_hh[2];
-    float q_bound;        // no q is larger: hidden values are within +-1
+    float q_bound;        // no q is larger, or from kResHuge on there is no bound: hidden values are within +-1
     // fp32: what P is like (TopWord), from the first utterance's words on; the number of the call, for its first launch
     const unsigned long long *p_top;
     unsigned long long *p_call;

@@ -95,7 +95,7 @@ struct RCtl {
     float bt, st;
     float list_scale[kResList];       // fp32: what the joint's operand of an utterance is multiplied by, see joint_scale
     float scale[kResRows];            // of the utterances in work
-    int huge;                         // one of the team's has an infinite P
+    int huge;                         // one of the team's may have infinite operands
 };
 __shared__ RCtl rc;
 static_assert(sizeof(RCtl) <= kResCtl, "the control block has its place");
@@ -475,10 +475,12 @@ __device__ __forceinline__ void cell(float pre, int j, float c_old, float &c_new
 constexpr int kTake = 1 << 30, kFresh = (int)(1u << 31);
 
 // fp32: the power of two that takes the bound max P + max q of an utterance to 2^14 .. 2^15, which its operands of the
-// joint step, and its q in LDS, are multiplied by.  (Of infinite values of P the finite ones count, see the joint step.)
-__device__ __forceinline__ float joint_scale(TopWord top, float q_bound)
+// joint step, and its q in LDS, are multiplied by.  (Of infinite values of P the finite ones count, and huge is for
+// what has no parts: see the joint step.)
+__device__ __forceinline__ float joint_scale(TopWord top, float q_bound, bool &huge)
 {
-    const float bound = fminf(__uint_as_float((unsigned)top << 16) + q_bound, 1e38f);
+    const float sum = __uint_as_float((unsigned)top << 16) + q_bound, bound = fminf(sum, kResHuge);
+    huge = !(sum < kResHuge);
     return __uint_as_float((268u << 23) - max(__float_as_uint(bound) & 0x7f800000u, 27u << 23));
 }
 
@@ -840,8 +842,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 TopWord top = 0, inf = 0;
 #pragma unroll 4                 // (the weights have the registers)
                 for (int i = 0; i < kTopParts; ++i) { top = max(top, words[i * kTopStride]); inf = max(inf, words[i * kTopStride + 1]); }
-                rc.list_scale[q] = joint_scale(top, p.q_bound);
-                if (inf >> 16 == top >> 16 && (inf & 1u) != 0u && len > 0) rc.huge = 1;
+                bool huge;
+                rc.list_scale[q] = joint_scale(top, p.q_bound, huge);
+                if ((huge || (inf >> 16 == top >> 16 && (inf & 1u) != 0u)) && len > 0) rc.huge = 1;
             }
             if (len > 0) atomicAdd(&rc.n_list, 1);       // the empty ones are the last of the list
             else if (x.rank == 0) res_finish_row(b, 0);
@@ -1331,8 +1334,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             if (has_tail) output(std::true_type());
             else output(std::false_type());
             if constexpr (!BF && !WHOLE) {
-                // An infinite z has no low part: then the step is computed once more, as fp32 products (the weights' parts
-                // added up again).  The lane's e-th value of a block times its e-th weight is one 16x16x4 instruction.
+                // An infinite z, of P or of q, has no low part: then the step is computed once more, as fp32 products (the
+                // weights' parts added up again).  The lane's e-th value of a block times its e-th weight is one 16x16x4 instruction.
                 if (rc.huge) {
 #pragma unroll 1
                     for (int mt = 0; mt < NT; ++mt) {
@@ -1347,9 +1350,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                             float z[N];
 #pragma unroll
                             for (int j = 0; j < N / 4; ++j) {
-                                const float4 p_ = at(frame_at(mt, k) ^ (j * 16)), q_ = at(q_at(qo, k) + j * 16);
-                                z[j * 4] = fmaxf(fmaf(q_.x, back, p_.x), 0.f); z[j * 4 + 1] = fmaxf(fmaf(q_.y, back, p_.y), 0.f);
-                                z[j * 4 + 2] = fmaxf(fmaf(q_.z, back, p_.z), 0.f); z[j * 4 + 3] = fmaxf(fmaf(q_.w, back, p_.w), 0.f);
+                                const float4 v = relu(at(frame_at(mt, k) ^ (j * 16)), at(q_at(qo, k) + j * 16));
+                                z[j * 4] = v.x * back * scale; z[j * 4 + 1] = v.y * back * scale;        // (infinite where the sum is)
+                                z[j * 4 + 2] = v.z * back * scale; z[j * 4 + 3] = v.w * back * scale;
                             }
 #pragma unroll
                             for (int c = 0; c < 2; ++c) {
@@ -1366,10 +1369,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                                 for (int e = 0; e < N; ++e) tail = __builtin_amdgcn_mfma_f32_16x16x4f32(m16 == 0 ? (float)w[e] + (float)w[ROW + e] : 0.f, z[e], tail, 0, 0, 0);
                             }
                         });
-                        if (has_tail && g == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = tail[0] * scale;
+                        if (has_tail && g == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = tail[0];
 #pragma unroll
                         for (int c = 0; c < 2; ++c)
-                            *reinterpret_cast<r4f *>(part + ((x.wave * NT + mt) * 16 + m16) * kResSumRow + c * 16 + g * 4) = sum[c] * scale;
+                            *reinterpret_cast<r4f *>(part + ((x.wave * NT + mt) * 16 + m16) * kResSumRow + c * 16 + g * 4) = sum[c];
                     }
                 }
             }

@@ -36,7 +36,7 @@ __global__ void __launch_bounds__(256) row_scales_kernel(const float *__restrict
     for (int i = 32; i; i >>= 1) { top = max(top, (unsigned)__shfl_xor((int)top, i)); sum += __shfl_xor(sum, i); }
     if (lane) return;
     if (top >= 0x7f800000u) atomicOr(check, 1u);
-    if (extra) atomicMax(check + 1, __float_as_uint(fminf(fmaxf((sum + extra[row]) * 1.001f, 0.f), 1e38f)));
+    if (extra) atomicMax(check + 1, __float_as_uint(fminf(fmaxf((sum + extra[row]) * 1.001f, 0.f), kResHuge)));
     const float m = __uint_as_float(top);
     const int e = top >= 0x7f800000u ? 0 : (m > 0.f ? min(14 - ilogbf(m), 126 - kResHiddenExp) : 0);
     scale[row] = ldexpf(1.f, e);

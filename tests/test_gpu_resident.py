@@ -333,3 +333,13 @@ def test_projected_frames_without_a_bound_reach_the_tail_column(pkg, L, duration
     for row in (9, V1 + 3) if durations else (V1 - 1,):
         m.w_out[row, 7] = 0.125
     tokens_as_the_oracle_has_them(pkg, w)
+
+
+@pytest.mark.parametrize("value", [np.inf, 3.4e38, 1e30])
+@pytest.mark.parametrize("H,J,V1,L", [(100, 128, 255, 1), (324, 332, 529, 1), (324, 640, 530, 2), (640, 640, 1025, 1)])
+def test_prediction_biases_without_a_bound(pkg, H, J, V1, L, value):  # noqa: F811
+    """A joint unit that its bias makes infinite, or as large as fp32 holds: as for infinite projected frames."""
+    w = model_inputs(H, J, V1, L, B=20, T=4, seed=H + V1, max_symbols=2)
+    w.model.b_pred[7] = value
+    w.model.w_out[:9, 7] = -np.abs(w.model.w_out[:9, 7])         # (not the first label)
+    tokens_as_the_oracle_has_them(pkg, w)
