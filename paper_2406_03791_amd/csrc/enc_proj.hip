@@ -315,7 +315,6 @@ enc_proj_kernel(const float *__restrict__ x, const int *__restrict__ enc_len, co
         return o;
     };
     float top = 0.f;                 // the largest finite value
-    bool infinite = false;
     const bool wide = J % 4 == 0 && (reinterpret_cast<uintptr_t>(proj) & 15u) == 0;
     auto store = [&](int ni, int j, v4f v) {
         const int col = n0 + ni * 32 + j * 8 + kh * 4;
@@ -330,7 +329,7 @@ enc_proj_kernel(const float *__restrict__ x, const int *__restrict__ enc_len, co
         }
         if (!BF) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) { infinite = infinite || v[e] == INFINITY; top = fmaxf(top, v[e] == INFINITY ? 0.f : v[e]); }
+            for (int e = 0; e < 4; ++e) top = fmaxf(top, v[e] == INFINITY ? 0.f : v[e]);
         }
     };
     if constexpr (WK == 1) {
@@ -362,12 +361,7 @@ enc_proj_kernel(const float *__restrict__ x, const int *__restrict__ enc_len, co
     if (!BF && ci.p_top) {
 #pragma unroll
         for (int i = 32; i; i >>= 1) top = fmaxf(top, __shfl_xor(top, i));
-        TopWord *word = ci.p_top + top_words(r.b) + blockIdx.x % kTopParts * kTopStride;
-        const bool any = __ballot(infinite) != 0ull;
-        if (lane == 0) {
-            atomicMax(word, call << 16 | (__float_as_uint(top) + 0xffffu) >> 16);
-            if (any) atomicMax(word + 1, call << 16 | 1u);
-        }
+        if (lane == 0) atomicMax(ci.p_top + top_words(r.b) + blockIdx.x % kTopParts * kTopStride, call << 16 | (__float_as_uint(top) + 0xffffu) >> 16);
     }
 }
 

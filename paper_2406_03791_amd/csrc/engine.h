@@ -100,11 +100,10 @@ struct DecodeParams {
 hipError_t launch_decode(const DecodeParams &p, bool zero_status, bool zero_stats, hipStream_t stream);
 
 // What a call's P is like, for the resident decode kernel: the number of the call, which the decode kernel counts up (so
-// a captured call does it too), and kTopParts pairs of words for every utterance, a line of memory each (one pair for all blocks
-// that have an utterance took 5.5 us of a projection of 17), the first of its largest finite value and the second of infinite
-// ones.  Words are number << 16 | upper half of the value, rounded up, and only
-// ever grow: nothing needs to be cleared between calls, an utterance's words with the largest number are the call's.
-// (Of the utterance, not of the call: what scales an utterance's values may not depend on the others'.)
+// a captured call does it too), and kTopParts words for every utterance, a line of memory each (one word for all blocks
+// that have an utterance took 5.5 us of a projection of 17): its largest finite value, as number << 16 | upper half of the
+// value, rounded up.  They only ever grow: nothing needs to be cleared between calls, an utterance's words with the
+// largest number are the call's.  (Of the utterance, not of the call: one with large values costs the others no time.)
 typedef unsigned long long TopWord;
 constexpr int kTopParts = 16, kTopStride = 8;
 constexpr size_t top_words(size_t utterances) { return (utterances * kTopParts + 1) * kTopStride; }

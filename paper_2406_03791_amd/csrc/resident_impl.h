@@ -95,7 +95,6 @@ struct RCtl {
     float bt, st;
     float list_scale[kResList];       // fp32: what the joint's operand of an utterance is multiplied by, see joint_scale
     float scale[kResRows];            // of the utterances in work
-    int huge;                         // one of the team's may have infinite operands
 };
 __shared__ RCtl rc;
 static_assert(sizeof(RCtl) <= kResCtl, "the control block has its place");
@@ -475,13 +474,21 @@ __device__ __forceinline__ void cell(float pre, int j, float c_old, float &c_new
 constexpr int kTake = 1 << 30, kFresh = (int)(1u << 31);
 
 // fp32: the power of two that takes the bound max P + max q of an utterance to 2^14 .. 2^15, which its operands of the
-// joint step, and its q in LDS, are multiplied by.  (Of infinite values of P the finite ones count, and huge is for
-// what has no parts: see the joint step.)
-__device__ __forceinline__ float joint_scale(TopWord top, float q_bound, bool &huge)
+// joint step, and its q in LDS, are multiplied by.  (Of infinite values of P the finite ones count.)
+__device__ __forceinline__ float joint_scale(TopWord top, float q_bound)
 {
-    const float sum = __uint_as_float((unsigned)top << 16) + q_bound, bound = fminf(sum, kResHuge);
-    huge = !(sum < kResHuge);
+    const float bound = fminf(__uint_as_float((unsigned)top << 16) + q_bound, kResHuge);
     return __uint_as_float((268u << 23) - max(__float_as_uint(bound) & 0x7f800000u, 27u << 23));
+}
+
+// Where the largest operand of a sample in a wave's eighth of K has to lie for two fp16 parts to hold the eighth as well
+// as fp32 does: parts are off by 2^-25 at most, which is 2^-23 of the least one; beyond the most there are none.
+constexpr float kResLeast = 0.25f, kResMost = 65504.f;
+// of a ballot: samples (lane % 16) that one of their four lanes speaks for
+__device__ __forceinline__ unsigned samples_of(unsigned long long m)
+{
+    const unsigned both = (unsigned)m | (unsigned)(m >> 32);
+    return (both | both >> 16) & 0xffffu;
 }
 
 __device__ __forceinline__ float inverse_power(float two_to_n) { return __uint_as_float(0x7f000000u - __float_as_uint(two_to_n)); }
@@ -604,7 +611,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             }
         if (!any) return;
     }
-    if (tid0 == 0) { rc.ok = 1; rc.n_list = rc.huge = 0; rc.st_clamped = 0; rc.st_overflow = 0; }
+    if (tid0 == 0) { rc.ok = 1; rc.n_list = 0; rc.st_clamped = 0; rc.st_overflow = 0; }
     if (tid0 < kResSamples) { rc.s_k[tid0] = p.blank; rc.s_d[tid0] = 0; }
     if (tid0 < kMaxDur) rc.dur[tid0] = p.durations[tid0];
     if (tid0 < kResRows) rc.scale[tid0] = 1.f;
@@ -839,12 +846,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             rc.list_b[q] = (unsigned short)b; rc.list_len[q] = len;
             if constexpr (!BF && !WHOLE) {
                 const TopWord *words = p.p_top + (long long)b * (kTopParts * kTopStride);
-                TopWord top = 0, inf = 0;
+                TopWord top = 0;
 #pragma unroll 4                 // (the weights have the registers)
-                for (int i = 0; i < kTopParts; ++i) { top = max(top, words[i * kTopStride]); inf = max(inf, words[i * kTopStride + 1]); }
-                bool huge;
-                rc.list_scale[q] = joint_scale(top, p.q_bound, huge);
-                if ((huge || (inf >> 16 == top >> 16 && (inf & 1u) != 0u)) && len > 0) rc.huge = 1;
+                for (int i = 0; i < kTopParts; ++i) top = max(top, words[i * kTopStride]);
+                rc.list_scale[q] = joint_scale(top, p.q_bound);
             }
             if (len > 0) atomicAdd(&rc.n_list, 1);       // the empty ones are the last of the list
             else if (x.rank == 0) res_finish_row(b, 0);
@@ -1256,10 +1261,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             };
             auto q_at = [&](int of, int i) { return of + i * 128 - (i < NF ? 0 : g * 16); };
             auto at = [&](int a) { return *reinterpret_cast<const float4 *>(lds + a); };
+            unsigned again = 0;              // samples whose operand has too few bits in parts, or none
             auto output = [&](auto tail_) {
                 constexpr bool TAIL = decltype(tail_)::value;
                 const r4f zero = {0.f, 0.f, 0.f, 0.f};
                 r4f big[2], tb;
+                float top = 0.f;
                 float4 pv[2], qv[2];
                 int qo = 0;
                 auto fetch = [&](int b) {
@@ -1273,7 +1280,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 static_for<0, NB * NT>([&](auto b_) {
                     constexpr int b = decltype(b_)::value, mt = b / NB, i = block_of(b % NB);
                     constexpr bool FULL = i < NF;
-                    if constexpr (b % NB == 0) { big[0] = big[1] = tb = zero; }
+                    if constexpr (b % NB == 0) { big[0] = big[1] = tb = zero; top = 0.f; }
                     unsigned zh[4], zl[4];
                     if constexpr (FULL && TAIL) { pv[1] = at(frame_at(mt, i) ^ 16); qv[1] = at(q_at(qo, i) + 16); }      // (registers)
 #pragma unroll
@@ -1286,6 +1293,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                         } else {
                             f16_parts(z.x, z.y, zh[j * 2], zl[j * 2]);
                             f16_parts(z.z, z.w, zh[j * 2 + 1], zl[j * 2 + 1]);
+                            top = fmaxf(fmaxf(z.z, z.w), fmaxf(fmaxf(z.x, z.y), top));
                         }
                     }
                     if constexpr (b + 1 < NB * NT) fetch(b + 1);
@@ -1323,6 +1331,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     }
                     ordered();
                     if constexpr (b % NB == NB - 1) {
+                        if constexpr (!BF && !WHOLE)
+                            again |= ((samples_of(__ballot(top > 0.f)) & ~samples_of(__ballot(top >= kResLeast))) | samples_of(__ballot(top > kResMost))) << (mt * 16);
                         if (TAIL && g == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = BF || WHOLE ? tb[0] : tb[0] + tb[1];
                         // every wave's sums to LDS, [wave][sample][column]
 #pragma unroll
@@ -1334,9 +1344,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             if (has_tail) output(std::true_type());
             else output(std::false_type());
             if constexpr (!BF && !WHOLE) {
-                // An infinite z, of P or of q, has no low part: then the step is computed once more, as fp32 products (the
-                // weights' parts added up again).  The lane's e-th value of a block times its e-th weight is one 16x16x4 instruction.
-                if (rc.huge) {
+                // Samples whose operand does not lie between kResLeast and kResMost in the wave's eighth, far below the bound or
+                // infinite, are computed once more as fp32 products (the weights' parts added up again).  The lane's e-th value of
+                // a block times its e-th weight is one 16x16x4 instruction.
+                if (again != 0u) {
 #pragma unroll 1
                     for (int mt = 0; mt < NT; ++mt) {
                         place_lane();
@@ -1369,10 +1380,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                                 for (int e = 0; e < N; ++e) tail = __builtin_amdgcn_mfma_f32_16x16x4f32(m16 == 0 ? (float)w[e] + (float)w[ROW + e] : 0.f, z[e], tail, 0, 0, 0);
                             }
                         });
-                        if (has_tail && g == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = tail[0];
+                        if ((again >> (mt * 16 + m16) & 1u) != 0u) {
+                            if (has_tail && g == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = tail[0];
 #pragma unroll
-                        for (int c = 0; c < 2; ++c)
-                            *reinterpret_cast<r4f *>(part + ((x.wave * NT + mt) * 16 + m16) * kResSumRow + c * 16 + g * 4) = sum[c];
+                            for (int c = 0; c < 2; ++c)
+                                *reinterpret_cast<r4f *>(part + ((x.wave * NT + mt) * 16 + m16) * kResSumRow + c * 16 + g * 4) = sum[c];
+                        }
                     }
                 }
             }

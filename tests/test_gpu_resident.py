@@ -343,3 +343,33 @@ def test_prediction_biases_without_a_bound(pkg, H, J, V1, L, value):  # noqa: F8
     w.model.b_pred[7] = value
     w.model.w_out[:9, 7] = -np.abs(w.model.w_out[:9, 7])         # (not the first label)
     tokens_as_the_oracle_has_them(pkg, w)
+
+
+# ... and TDT with every duration in the tail
+WIDE_TDT = [(*s, ()) for s in WIDE] + [(640, 640, 1025, 1, (0, 1, 2, 3, 4)), (640, 640, 1024, 2, (0, 1, 2, 3, 4))]
+
+
+@pytest.mark.parametrize("H,J,V1,L,durations", WIDE_TDT)
+@pytest.mark.parametrize("B,size", [(3, 1e12), (40, 1e12), (9, 1e30), (9, 1e7)])
+def test_a_large_frame_leaves_its_neighbours_alone(pkg, H, J, V1, L, durations, B, size):  # noqa: F811
+    """One or two frames of every other utterance are far larger than the rest: every frame as the oracle has it."""
+    w = model_inputs(H, J, V1, L, B=B, T=12, seed=H + B, durations=durations)
+    x = w.enc_out.copy()
+    x[::2, 2] *= np.float32(size)
+    x[::4, 7] *= np.float32(size)
+    w = dataclasses.replace(w, enc_out=x, enc_len=np.maximum(w.enc_len, 5))
+    eng = pkg.Engine(w.model, w.B, w.T)
+    check(pkg, w, w.variant, f"large frame {H}/{J}/{V1}/{L} {durations} {B} {size}", engine=eng, logp=B <= 9)
+    eng.close()
+
+
+@pytest.mark.parametrize("H,J,V1,L,durations", WIDE_TDT)
+def test_a_joint_unit_with_large_weights_that_is_off(pkg, H, J, V1, L, durations):  # noqa: F811
+    """A row of w_pred of 1e9 whose bias of -1e11 its hidden values hardly ever make good: what the unit could be
+    says nothing of the others' size."""
+    w = model_inputs(H, J, V1, L, B=9, T=12, seed=H + 2, durations=durations)
+    w.model.w_pred[5] *= np.float32(1e10 / 0.45)
+    w.model.b_pred[5] = -5e11
+    eng = pkg.Engine(w.model, w.B, w.T)
+    check(pkg, w, w.variant, f"unit off {H}/{J}/{V1}/{L} {durations}", engine=eng, logp=True)
+    eng.close()
