@@ -138,9 +138,9 @@ RNNT_HD constexpr int res_main_regs(int kind, bool bf, int cls)
 // recurrent stage, kept till the next prediction step.
 // q: every wave's eighth of q, rows of res_q_row floats (zeros beyond the joint width).  tail: the tail column (see output()),
 // tpart: its partial sums.  state: cell state and recurrent pre-activations [layer][field][wave][lane] where they are
-// not in registers.
+// not in registers.  scale: powers of two of the team's list (fp32).
 // nmt: tiles of 16 samples.  Helpers: their own, from 0 on.
-struct ResidentLds { int p, part, ih, rec0, proj, rec, q, tail, tpart, state, bytes; };
+struct ResidentLds { int p, part, ih, rec0, proj, rec, q, tail, tpart, state, scale, bytes; };
 constexpr int kResSumRow = 36;            // floats per row of partial sums: of the joint step, of the projection
 constexpr int kResStageRow = 80;          // and of the LSTM stages
 RNNT_HD constexpr int res_q_row(int cls) { return res_row(cls) / 8 + 4; }
@@ -159,12 +159,13 @@ RNNT_HD constexpr ResidentLds resident_lds(int kind, int cls, int nmt)
     l.tail = at; at += (kind == kResident2 ? 2 : res_halves(cls) == 1 ? 4 : 3) * res_row(cls) * 2;
     l.tpart = at; at += kResWaves * 2 * 16 * 4;
     l.state = at; at += kind == kResident2Pair ? 6 * 5 * 64 * 4 : 0;
+    l.scale = at; at += kind == kResident2 ? 0 : kResList * 4;
     const int help = 2048 + 2 * (kResServed / 2) * res_help_blocks(cls) * 1024;
     if (kind == kResident2Pair && at < help) at = help;
     l.bytes = (at + 15) & ~15;
     return l;
 }
-constexpr int kResCtl = 5568;             // bytes kept for the control block
+constexpr int kResCtl = 5376;             // bytes kept for the control block and votes
 static_assert(resident_lds(kResident1, 0, 2).bytes + kResCtl <= 160 * 1024 && resident_lds(kResident2, 0, 2).bytes + kResCtl <= 160 * 1024 &&
               resident_lds(kResident2Pair, 0, 2).bytes + kResCtl <= 160 * 1024, "the largest layouts and the control block fit the LDS");
 

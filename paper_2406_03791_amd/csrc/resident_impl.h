@@ -93,11 +93,10 @@ struct RCtl {
     float s1[kResUnits * 4], sp[20], sh[2][kResUnits * 4];
     float2 bo[16], so[16];
     float bt, st;
-    float list_scale[kResList];       // fp32: what the joint's operand of an utterance is multiplied by, see joint_scale
-    float scale[kResRows];            // of the utterances in work
+    float scale[kResRows];            // fp32: of the utterances in work, see joint_scale
 };
 __shared__ RCtl rc;
-static_assert(sizeof(RCtl) <= kResCtl, "the control block has its place");
+static_assert(sizeof(RCtl) + 256 <= kResCtl, "the control block has its place, and what the compiler keeps for votes of a work-group");
 
 // Phase timers (100 MHz wall clock), compiled in only for profiling builds.
 #ifdef RNNT_PROFILE
@@ -830,6 +829,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         load_regs(w_pr, src, first, lane0); first += res_pred_regs(BF, CLS);
         load_regs(w_ou, src, first, lane0);
     }
+    // fp32: what the joint's operands of an utterance are multiplied by, see joint_scale
+    float *list_scale = reinterpret_cast<float *>(lds + lo.scale);
     // utterances of the team: ranked by length (longest first, ties by index), dealt in serpentine
     // order; empty ones are complete from the start
     for (int b = tid0; b < p.B; b += kResThreads) {
@@ -849,7 +850,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 TopWord top = 0;
 #pragma unroll 4                 // (the weights have the registers)
                 for (int i = 0; i < kTopParts; ++i) top = max(top, words[i * kTopStride]);
-                rc.list_scale[q] = joint_scale(top, p.q_bound);
+                list_scale[q] = joint_scale(top, p.q_bound);
             }
             if (len > 0) atomicAdd(&rc.n_list, 1);       // the empty ones are the last of the list
             else if (x.rank == 0) res_finish_row(b, 0);
@@ -992,7 +993,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         if (got) { b = rc.list_b[at]; len = rc.list_len[at]; }
         // (one place for all waves: they write the same, between the same barriers)
         if constexpr (!BF && !WHOLE)
-            if (got) rc.scale[(lane / LR) & (R - 1)] = rc.list_scale[at];
+            if (got) rc.scale[(lane / LR) & (R - 1)] = list_scale[at];
         rows.next = next + __popcll(m);
         return got;
     };

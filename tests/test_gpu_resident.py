@@ -373,3 +373,13 @@ def test_a_joint_unit_with_large_weights_that_is_off(pkg, H, J, V1, L, durations
     eng = pkg.Engine(w.model, w.B, w.T)
     check(pkg, w, w.variant, f"unit off {H}/{J}/{V1}/{L} {durations}", engine=eng, logp=True)
     eng.close()
+
+
+@pytest.mark.parametrize("L", [1, 2])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_the_largest_instances(pkg, L, bf16):  # noqa: F811
+    """The widest layers with a tail column and two tiles of samples: what takes the most of the LDS."""
+    w = model_inputs(640, 640, 1025, L, B=24, T=9, seed=L)
+    eng = pkg.Engine(w.model, w.B, w.T, flags=pkg.RNNT_FLAG_BF16_ARITHMETIC if bf16 else 0)
+    check(pkg, w, "label", f"largest {L} bf16={bf16}", engine=eng, bf16=bf16, logp=True)
+    eng.close()
