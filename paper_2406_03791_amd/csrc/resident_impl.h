@@ -290,8 +290,8 @@ __device__ __forceinline__ float lane_sum(float v)
 // Matrix instruction on a block of a wave's share of K: `w` and `z` from the registers of that block on, four
 // of either (32 k's), two for a half block.  A matrix instruction that adds to what one of the other kind right
 // before it leaves gives wrong sums (the compiler places no wait between them): where a sum takes both kinds, the
-// half block comes first and 32 cycles or more of something else after it (ordered: nothing moves across), or it
-// is two sums.
+// half block comes first and a wait after it, of 32 cycles or for a read of the sum (there; ordered: nothing moves
+// across), or it is two sums.
 template <bool BF>
 __device__ __forceinline__ r4f tile_mfma(r4f w, const unsigned *z, r4f acc)
 {
@@ -323,6 +323,13 @@ __device__ __forceinline__ auto weights_of(const RegW<N> &w, int t)
 }
 
 __device__ __forceinline__ void ordered() { __builtin_amdgcn_sched_barrier(0); }
+
+// Reads a matrix instruction's result: the compiler places what wait that needs after the instruction, if any.
+__device__ __forceinline__ void there(r4f sum)
+{
+    const int v = __builtin_amdgcn_readfirstlane((int)__float_as_uint(sum.x));
+    asm volatile("" :: "s"(v));
+}
 
 // compile-time loop: f(std::integral_constant<int, I>) for I = LO .. HI - 1
 template <int LO, int HI, class F>
@@ -1298,15 +1305,13 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                         }
                     }
                     if constexpr (b + 1 < NB * NT) fetch(b + 1);
+                    if constexpr (NH % 2 != 0 && NF > 0 && b % NB == 1) {
+                        // the sums of the half block have to be there
+                        there(big[0]); there(big[1]);
+                        if (TAIL) there(tb);
+                    }
                     ordered();
-                    if constexpr (BF) {
-                        // (the sums of the half block have to be there, see tile_mfma)
-                        if constexpr (NH % 2 != 0 && NF > 0 && b % NB == 1) {
-                            asm volatile("s_nop 15" : "+v"(big[0]), "+v"(big[1]));
-                            if (TAIL) asm volatile("" : "+v"(tb));
-                            ordered();
-                        }
-                    } else if constexpr (!WHOLE) {
+                    if constexpr (!BF && !WHOLE) {
                         if constexpr (NF < 2) {
 #pragma unroll
                             for (int c = 0; c < 2; ++c) big[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 1>(w_ou, c), zl, big[c]);
