@@ -480,7 +480,7 @@ __device__ __forceinline__ void cell(float pre, int j, float c_old, float &c_new
 constexpr int kTake = 1 << 30, kFresh = (int)(1u << 31);
 
 // fp32: the power of two that takes the bound max P + max q of an utterance to 2^14 .. 2^15, which its operands of the
-// joint step, and its q in LDS, are multiplied by.  (Of infinite values of P the finite ones count.)
+// joint step, and its q as it travels, are multiplied by.  (Of infinite values of P the finite ones count.)
 __device__ __forceinline__ float joint_scale(TopWord top, float q_bound)
 {
     const float bound = fminf(__uint_as_float((unsigned)top << 16) + q_bound, kResHuge);
@@ -1176,6 +1176,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     for (int i = 1; i < R / 2; ++i) o += v[i * R * kResSumRow];
                     o = lane_sum<LR>(o);
                     o = BF ? o + rc.bp[col] : fmaf(o, rc.sp[col], rc.bp[col]);
+                    if constexpr (!BF && !WHOLE) o *= rc.scale[r];
                     if ((tid & (LR - 1)) == 0 && r < p.slots)
                         put(x, (unsigned)r * VROW + (unsigned)(g0 * 4 + col) * 4u, bo.q + slot_at(n, VSLOT), bo.q + slot_at(n + 2, VSLOT), word_of(o));
                 }
@@ -1213,19 +1214,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 RES_MARK(8);
                 const int lane = lane_id();
                 places(off, lane);
-                float by[N];
-                if constexpr (!BF && !WHOLE) {
-#pragma unroll
-                    for (int i = 0; i < N; ++i) by[i] = rc.scale[__umul24(index(lane, i), INV) >> 16];
-                    ordered();                   // (read while q is on its way)
-                }
                 if constexpr (EARLY) receive_rest<N>(p, x, off, bo.q + slot_at(n, VSLOT), v);
                 else receive<N>(p, x, off, bo.q + slot_at(n, VSLOT), v);
 #pragma unroll
                 for (int i = 0; i < N; ++i) {
                     const unsigned at = index(lane, i), r = __umul24(at, INV) >> 16;
-                    float4 o = __builtin_bit_cast(float4, v[i]);
-                    if constexpr (!BF && !WHOLE) o = make_float4(o.x * by[i], o.y * by[i], o.z * by[i], o.w * by[i]);
+                    const float4 o = __builtin_bit_cast(float4, v[i]);
                     if (x.wave * PW + (int)(at - r * PW) < j4) *reinterpret_cast<float4 *>(lq + r * QS + (at - r * PW) * 4) = o;
                 }
             }
