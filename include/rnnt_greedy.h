@@ -372,13 +372,15 @@ int rnnt_label_looping_decode(rnnt_engine *eng, const float *enc_out, const int3
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, same
  * outputs, same errors.  The call's scratch -- the projected frames
  * [B, T, J] and what the teams exchange -- does not come from the engine's
- * workspace but from one array of RNNT_NOALLOC_SCRATCH_BYTES bytes that the
- * library holds as a static device object on every device it runs on, until
- * the process ends.  The entry point calls no hipMalloc, hipFree or other
- * allocating routine; the engine (its packed weights) is created beforehand.
- * A call that needs more (roughly B * T * J * 4 bytes plus 9 MiB at the
- * Parakeet shape), or one of more than 128 utterances (it would take more than
- * one launch), returns RNNT_ERR_SCRATCH and queues nothing.
+ * workspace but from one array that the library holds as a static device
+ * object on every device it runs on, until the process ends:
+ * RNNT_NOALLOC_SCRATCH_BYTES bytes that calls are measured against, and some
+ * 8 MiB more that the library keeps for itself.  The entry point calls no
+ * hipMalloc, hipFree or other allocating routine; the engine (its packed
+ * weights) is created beforehand.  A call that is charged more (roughly
+ * B * T * J * 4 bytes plus 9 MiB at the Parakeet shape), or one of more than
+ * 128 utterances (it would take more than one launch), returns
+ * RNNT_ERR_SCRATCH and queues nothing.
  * All calls on one device share the array, which keeps the last call's
  * contents (the call clears what must start at zero): calls through this entry
  * point that overlap on one device race, whatever engines and streams they use;

@@ -61,9 +61,8 @@ constexpr int kStaticLds = 3072;        // kept free for the kernel's static LDS
 // projected frames and the team workspace of one call.  One copy per device, held until the
 // process ends.  In host code this name is only a handle for hipGetSymbolAddress: the address
 // kernels and copies use is the one that call returns (rnnt_engine::scratch).
-// (Calls are measured against RNNT_NOALLOC_SCRATCH_BYTES with a quarter of the room for the helpers' results, and with five teams
-// for every six that two-layer fp32 models have: the rest lies in the room behind, 7.9 MB at most.)
-// kScratchTop: where the words on a call's P have their place, which every call finds as the last one left them.
+// Behind RNNT_NOALLOC_SCRATCH_BYTES there is room for what calls take beyond what they are charged (charged_bytes), 7.9 MB at most;
+// kScratchTop: and for the words on a call's P, which every call finds as the last one left them.
 constexpr size_t kScratchTop = RNNT_NOALLOC_SCRATCH_BYTES + (8u << 20);
 static __device__ __align__(256) unsigned char scratch[kScratchTop + top_words(kLaunchRows) * sizeof(TopWord)];
 
@@ -558,6 +557,18 @@ EncWeights enc_weights(const rnnt_engine *e)
 }
 
 // ---- resident decode kernel ---------------------------------------------------------------
+// What a call of the entry point that allocates nothing is charged of RNNT_NOALLOC_SCRATCH_BYTES, for P and its workspace.  Which
+// calls are refused is part of the interface, so this stays as it was when every kind had buffers of two recurrent
+// vectors and one sum a unit, and two-layer fp32 models five teams where they have six.
+size_t charged_bytes(const ResidentPlan &pl, size_t p_bytes)
+{
+    auto sized = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
+    const ResidentBuf buf = resident_buf(kResident2Pair, pl.cls);
+    const size_t teams = pl.kind == kResident2Pair ? pl.n_teams - pl.n_teams / 6 : pl.n_teams;
+    return sized(p_bytes) + sized((buf.pre + (buf.bytes - buf.pre) / kResQuarters) * teams) + sized((size_t)pl.n_xcd * 32 * sizeof(unsigned)) +
+           sized(teams * kStatStride * sizeof(long long)) + sized(sizeof(unsigned)) + sized(sizeof(int));
+}
+
 Workspace resident_workspace(const rnnt_engine *e)
 {
     Workspace w;
@@ -593,7 +604,7 @@ int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
     // (infinite or undefined weights have no fp16 parts: such a model is left to the other kernel)
     if (found[0]) { e->res.kind = kResidentNone; return RNNT_OK; }
     std::memcpy(&e->res_q_bound, &found[1], sizeof(float));
-    HIP_TRY(e->res_xbuf.alloc((size_t)resident_buf(pl.cls).bytes * pl.n_teams));
+    HIP_TRY(e->res_xbuf.alloc((size_t)resident_buf(pl.kind, pl.cls).bytes * pl.n_teams));
     HIP_TRY(e->res_form.alloc((size_t)pl.n_xcd * 32 * sizeof(unsigned)));
     HIP_TRY(e->res_stats.alloc((size_t)pl.n_teams * kStatStride * sizeof(long long)));
     HIP_TRY(hipMemset(e->res_form.p, 0, (size_t)pl.n_xcd * 32 * sizeof(unsigned)));
@@ -1166,16 +1177,11 @@ int rnnt_label_looping_decode_noalloc(rnnt_engine *eng, const float *enc_out, co
         size_t off = 0;
         auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
         const size_t o_P = take((size_t)B * T * eng->d.J * sizeof(float));
-        const size_t o_x = take((size_t)resident_buf(pl.cls).bytes * pl.n_teams);
+        const size_t o_x = take((size_t)resident_buf(pl.kind, pl.cls).bytes * pl.n_teams);
         const size_t o_f = take((size_t)pl.n_xcd * 32 * sizeof(unsigned));
         const size_t o_s = take((size_t)pl.n_teams * kStatStride * sizeof(long long));
         const size_t o_a = take(sizeof(unsigned)), o_st = take(sizeof(int));
-        auto sized = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
-        auto of_teams = [&](int n, size_t buf) { return sized(buf * n) + sized((size_t)n * kStatStride * sizeof(long long)); };
-        const ResidentBuf buf = resident_buf(pl.cls);
-        const int teams = pl.kind == kResident2Pair ? pl.n_teams - pl.n_teams / 6 : pl.n_teams;
-        const size_t extra = of_teams(pl.n_teams, buf.bytes) - of_teams(teams, buf.pre + (buf.bytes - buf.pre) / kResQuarters);
-        if (off > RNNT_NOALLOC_SCRATCH_BYTES + extra || off > kScratchTop) return RNNT_ERR_SCRATCH;
+        if (charged_bytes(pl, (size_t)B * T * eng->d.J * sizeof(float)) > RNNT_NOALLOC_SCRATCH_BYTES || off > kScratchTop) return RNNT_ERR_SCRATCH;
         unsigned char *base = static_cast<unsigned char *>(eng->scratch);
         Workspace ws;
         ws.P = reinterpret_cast<float *>(base + o_P);

@@ -96,7 +96,7 @@ struct ResidentParams {
     const unsigned long long *p_top;
     unsigned long long *p_call;
     const float *T0, *bias_l, *b_pred, *b_out;
-    unsigned char *xbuf;  // exchange buffers, resident_buf(cls).bytes per team
+    unsigned char *xbuf;  // exchange buffers, resident_buf(kind, cls).bytes per team
     unsigned *form;       // one word per work-group, zero at launch: the XCD it runs on
     unsigned *abort_flag;
     int *status;
@@ -106,9 +106,9 @@ struct ResidentParams {
 };
 
 // Byte offsets of a team's exchange buffers, every vector in kResSlots slots.
-// pre: [layer][slot][quarter of K][rank][wave of the cells][lane]
+// hr, pre: kResident2Pair; pre: [layer][slot][quarter of K][rank][wave of the cells][lane]
 struct ResidentBuf { unsigned h[2], q, key, dur, lse, hr[2], pre, bytes; };
-RNNT_HD constexpr ResidentBuf resident_buf(int cls)
+RNNT_HD constexpr ResidentBuf resident_buf(int kind, int cls)
 {
     const unsigned vec = kResSlots * (unsigned)(kResRows * res_width(cls)) * 4u;
     const unsigned recs = kResSlots * kResSamples * (unsigned)res_team(cls);
@@ -116,7 +116,9 @@ RNNT_HD constexpr ResidentBuf resident_buf(int cls)
     b.h[0] = 0; b.h[1] = vec; b.q = 2 * vec; b.key = 3 * vec;
     b.dur = b.key + recs * 8u;
     b.lse = b.dur + kResSlots * kResSamples * kMaxDur * 4u;
-    b.hr[0] = b.lse + recs * 4u; b.hr[1] = b.hr[0] + vec; b.pre = b.hr[1] + vec;
+    b.hr[0] = b.hr[1] = b.pre = b.bytes = b.lse + recs * 4u;
+    if (kind != kResident2Pair) return b;
+    b.hr[1] = b.hr[0] + vec; b.pre = b.hr[1] + vec;
     b.bytes = b.pre + 2u * kResSlots * kResQuarters * (unsigned)res_team(cls) * 5u * 64u * 4u;
     return b;
 }

@@ -559,7 +559,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     typedef Operand<BF, CLS, R> Op;
     constexpr bool HALVES = PAIR && NMT == 2;     // steps with one tile of samples as well, see after the loop
     constexpr int NREC = PAIR ? 0 : NL;          // recurrent matrices the chain's work-groups hold
-    constexpr ResidentBuf bo = resident_buf(CLS);
+    constexpr ResidentBuf bo = resident_buf(KIND, CLS);
     constexpr ResidentLds lo = resident_lds(KIND, CLS, NMT);
     constexpr unsigned VROW = W * 4u, VSLOT = R * VROW;                      // h and q rows
     constexpr unsigned KSLOT = kResSamples * TS * 8u, DSLOT = kResSamples * kMaxDur * 4u;
@@ -602,7 +602,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             __builtin_amdgcn_raw_buffer_store_b128(mark, x.buf, (int)o, 0, 16);
     };
     if (!helper) {
-        put_marks(0u, PAIR ? bo.pre : bo.hr[0]);
+        put_marks(0u, bo.pre);
     } else {
         bool any = false;
         for (int i = 0; i < kResServed; ++i)
