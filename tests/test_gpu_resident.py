@@ -41,11 +41,11 @@ def test_edges_of_the_size_classes(pkg, H, J, V1, L, bf16):  # noqa: F811
     eng.close()
 
 
-@pytest.mark.parametrize("B", [2, 33, 70, 645])
+@pytest.mark.parametrize("B", [2, 33, 70, 773])
 @pytest.mark.parametrize("extra", [{}, dict(durations=(0, 1, 3, 7)), dict(big_blanks=(2, 5))])
 def test_lists_longer_than_the_rows_in_work(pkg, B, extra):  # noqa: F811
     """Every decoder with one row per team, a partly filled last row, rows that take over the next
-    utterance of the team's list, and (645 utterances on 5 teams) a second launch."""
+    utterance of the team's list, and (773 utterances on 6 teams that take 128 each) a second launch."""
     w = model_inputs(324, 332, 530 if not extra else 520, 2, B=B, T=9, seed=B, **extra)
     eng = pkg.Engine(w.model, w.B, w.T)
     check(pkg, w, w.variant, f"list {B} {extra}", engine=eng, logp=True)
@@ -221,11 +221,18 @@ def test_an_engine_that_does_not_fit_the_memory_leaves_the_others_alone(pkg):  #
     eng.close()
 
 
-def test_more_utterances_than_one_launch_takes(pkg):  # noqa: F811
-    """A team takes 128 utterances a launch; two-layer fp32 models have up to 24 teams of the narrowest class."""
-    w = model_inputs(324, 332, 530, 2, B=12 * 128 + 7, T=5, seed=11)
+@pytest.mark.parametrize("extra", [{}, dict(durations=(0, 1, 3, 7)), dict(big_blanks=(2, 5))])
+@pytest.mark.parametrize("L,teams", [(1, 8), (2, 6)])
+def test_more_utterances_than_one_launch_takes(pkg, L, teams, extra):  # noqa: F811
+    """A team takes 128 utterances a launch: three launches, the last of seven utterances, with every output of a
+    decoder, and an utterance of large values in the second and third."""
+    w = model_inputs(324, 332, 530 if not extra else 520, L, B=2 * teams * 128 + 7, T=5, seed=11, **extra)
+    x = w.enc_out.copy()
+    x[teams * 128 + 3] *= np.float32(1e6)
+    x[2 * teams * 128 + 2] *= np.float32(1e6)
+    w = dataclasses.replace(w, enc_out=x)
     eng = pkg.Engine(w.model, w.B, w.T)
-    check(pkg, w, "label", "two launches", engine=eng)
+    check(pkg, w, w.variant, f"three launches {L} {extra}", engine=eng, logp=True)
     eng.close()
 
 
