@@ -86,17 +86,19 @@ def issued_weight_bytes(dims, stats, bytes_per_weight=4):
     return stats["pred_steps"] * pred + stats["joint_steps"] * stats["joint_groups"] * joint
 
 
-def mfma_fraction(dims, stats, B, dec_ms):
+def mfma_fraction(dims, stats, B, dec_ms, fp32_instructions):
     """Multiply-adds of the counted steps (rows a team really has, samples the joint really
-    evaluated; the folded layer-0 input product is a gather and not counted)."""
+    evaluated; the folded layer-0 input product is a gather and not counted), once each, whatever
+    number of fp16 products an fp32 one is made of, against the dense rate of the instructions
+    that the kernel runs them on: 16-bit ones, or fp32 ones in the streaming kernel."""
     H, L, J = dims.H, dims.L, dims.J
     w_pred_step = sum(4 * H * (H + (H if l else 0)) for l in range(L)) + J * H
     rows_per_team = B / min(B, stats["n_teams"])
     flops = 2.0 * (stats["pred_steps"] * rows_per_team * w_pred_step +
                    stats["joint_samples"] * stats["joint_groups"] * dims.n_out * J)
     ach = flops / (dec_ms * 1e-3) / 1e12
-    return {"useful_flops": flops, "peak": 157.3, "unit": "TFLOP/s", "achieved": ach,
-            "frac": ach / 157.3}
+    peak = 157.3 if fp32_instructions else 2500.0
+    return {"useful_flops": flops, "peak": peak, "unit": "TFLOP/s", "achieved": ach, "frac": ach / peak}
 
 
 def profiled(variant, key):
@@ -447,10 +449,11 @@ def main() -> int:
                                                   "batch in lock-step; above the peak means the "
                                                   "kernel does less than that schedule (unchanged "
                                                   "prediction steps skipped, utterances independent)"},
-                     # useful flops of the counted steps against the fp32 matrix peak: small, the
+                     # useful flops of the counted steps against the matrix peak: small, the
                      # path is not a dense contraction at these batch sizes (the counter-based
                      # figure of the MFMA work executed, row padding included, is in profiles/)
-                     "mfma": mfma_fraction(w.model.dims, r["stats"], w.B, r["dec_ms"]),
+                     "mfma": mfma_fraction(w.model.dims, r["stats"], w.B, r["dec_ms"],
+                                           args.streaming and args.arithmetic == "f32"),
                      "gpu_busy_frac": (r["dec_ms"] + r["proj_ms"]) / ms_per_step,
                      "us_per_lockstep_frame": 1e3 * ms_per_step / int(w.enc_len.max())},
     }

@@ -532,8 +532,9 @@ int rnnt_engine_phase_timers(rnnt_engine *eng, int32_t team, double *us_out, int
  *                        behind a counter barrier (tagged = 0) or as tagged
  *                        64-bit words that the readers poll (tagged = 1).
  *   rnnt_probe_mfma      fp32 matrix rate in TFLOP/s of the MFMA shape 4x4x1
- *                        in 16 blocks (shape 0, the decode kernel's) or
- *                        32x32x2 (shape 1, the projection kernel's).
+ *                        in 16 blocks (shape 0: the decode kernel that
+ *                        streams its weights) or 32x32x2 (shape 1: the
+ *                        projection of values without fp16 parts).
  *   rnnt_probe_e4m3_widening  the bf16 (as 16-bit codes) that the conversion
  *                        used by the bfloat16 mode with e4m3-stored weights
  *                        makes of every e4m3 code under the scale operand

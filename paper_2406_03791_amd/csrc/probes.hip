@@ -4,7 +4,8 @@
 //               (the decode kernel's situation), and how fast they stream from HBM;
 //   * exchange: what one all-to-all hand-over of a vector costs inside a team of work-groups,
 //               with a counter barrier and with tagged words;
-//   * mfma:     the fp32 matrix rate of the two MFMA shapes the library uses.
+//   * mfma:     the fp32 matrix rate of two MFMA shapes (4x4x1: the decode kernel that streams its
+//               weights; 32x32x2: the projection's for values that have no fp16 parts).
 // and so that the tests can check the widening instructions and the gate functions on their own.
 // None of this is on the decode path.
 #include "../../include/rnnt_greedy.h"

@@ -32,8 +32,8 @@ RNNT_HD constexpr int res_halves(int cls) { return res_row(cls) / 128; }
 // Kept in as many registers as the value itself.  Against 64 bits the logits of layers of 320 and 640 are 0 to 6 % closer
 // than with fp32 products in a chain.  In the narrowest class, whose chains are short, they were 7 % further
 // off: its joint output has whole fp32 values (res_whole, four 16x16x4 for a half block).
-constexpr float kResHuge = 1e38f;         // operands of the joint step from here on may have no parts
 constexpr int kResHiddenExp = 15;         // hidden values travel as fp16 parts of 2^15 times themselves (fp32)
+constexpr float kResHuge = 1e38f;         // no bound of the joint step's operands is taken to be larger than this
 RNNT_HD constexpr bool res_whole(bool bf, int cls) { return !bf && res_halves(cls) == 1; }
 RNNT_HD constexpr int res_parts(bool bf) { return bf ? 1 : 2; }
 // registers of a wave's share of T tiles of 16 outputs, and the place of block kb (kb == halves / 2: the half
@@ -55,7 +55,7 @@ enum ResidentKind {
     kResidentNone = 0,
     kResident1 = 1,       // one LSTM layer: a team inside one XCD holds everything
     kResident2 = 2,       // two layers in the bfloat16 mode: the same
-    kResident2Pair = 3,   // two layers in fp32: a team on one XCD, the recurrent matrices on a second one
+    kResident2Pair = 3,   // two layers in fp32: a team on one XCD, the recurrent matrices on two others
 };
 // kResident2Pair: most XCDs have teams, and each pair of the others, one for either layer, works for up to kResServed of them.
 // (Six and two of eight: with five and three, and helpers that had both matrices, 128 utterances took 5.65 instead of 5.29 ms.)
@@ -91,7 +91,7 @@ struct ResidentParams {
     const float *w_tail;  // [n_tail][res_row(cls)], scaled as the packed output columns
     // fp32: what sums of the scaled weights of an output are multiplied by; LSTM matrices [H][gate]
     const float *s_out, *s_pred, *s_ih, *s_hh[2];
-    float q_bound;        // no q is larger, or from kResHuge on there is no bound: hidden values are within +-1
+    float q_bound;        // no q is larger (hidden values are within +-1), unless this is kResHuge
     // fp32: what P is like (TopWord), from the first utterance's words on; the number of the call, for its first launch
     const unsigned long long *p_top;
     unsigned long long *p_call;

@@ -3,7 +3,7 @@
 // The step chain of a decode (a prediction step, a joint step, and again) is bound by latency:
 // three dense stages and four hand-overs between work-groups per label.  Two things make it
 // short here.  (1) Every weight of the step is held in the registers of one compute unit for the
-// whole launch: eight waves of 256 registers, of which up to 196 hold weights, so a stage reads
+// whole launch: eight waves of 256 registers, of which up to 190 hold weights, so a stage reads
 // nothing but its input vector (streamed out of L2, the weights took 5 to 27 us of a step).  (2) A team
 // of work-groups sits inside one XCD, so its hand-overs go through that XCD's L2: a store that stays
 // in the L2 and a load that passes by the L1 hand 640 floats to 32 work-groups in 0.70 us, where
@@ -354,9 +354,8 @@ __device__ __forceinline__ unsigned hidden_word(float h)
 }
 
 // The operand of a dense stage: the wave's eighth of K of the rows' hidden values, columns 0 .. 15 of the matrix
-// instructions.  R rows take R columns; fp32: R with the high parts are followed by R with the low ones (four rows:
-// and the same again), so a product with the weights' high and one with their low parts give
-// all four.  A lane loads four words of a block, exchanges halves with the lane R columns on (whose words are the
+// instructions.  R rows take R columns; fp32: R with the high parts are followed by R with the low ones, so a product
+// with the weights' high and one with their low parts give all four (the columns beyond are nobody's).  A lane loads four words of a block, exchanges halves with the lane R columns on (whose words are the
 // block's other four of the same row and group), and has what the instruction takes: nothing of it
 // goes through LDS, and a wave goes on as soon as its own eighth is there.
 template <bool BF, int CLS, int R>
