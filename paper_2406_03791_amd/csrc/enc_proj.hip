@@ -87,7 +87,8 @@ __device__ __forceinline__ RowTile row_tile(const int *__restrict__ enc_len, int
 // fp32: frames and weights are two fp16 parts each (22 bits and a sign), weights with a power of two for each column,
 // frames with one for each row; three products (low times low is beyond what fp32 sums keep), those with a low part
 // summed apart.  The row's power of two is that of its first slice, to 2^12 .. 2^13 with room for values eight times
-// as large; a larger one later on lowers it, and the sums with it.  Infinite frames have no parts: their tile is computed
+// as large; a larger one later on lowers it, and the sums with it.  Infinite frames have no parts, and where sixteen values of a
+// frame are all far below its largest (2^-14 to 2^-18 of it) theirs have too few bits: such a tile is computed
 // once more from the fp32 values (as is everything for weights that are not finite).
 // On the fp32 matrix instructions the product was bound by their rate, 154 TFLOP/s; these would do 59 us of it in 33.
 // Against 64 bits, rms, frames of 1024 values: 4.1e-7 (WK > 1: 2.3e-7), on the fp32 instructions 1.06e-6 (5.4e-7).
@@ -193,11 +194,15 @@ enc_proj_kernel(const float *__restrict__ x, const int *__restrict__ enc_len, co
         for (int i = 0; i < 4; ++i) m = fmaxf(fmaxf(fmaxf(fabsf(v.a[i].x), fabsf(v.a[i].y)), m), fmaxf(fabsf(v.a[i].z), fabsf(v.a[i].w)));
         return m;
     };
+    // Far below the row's largest value, parts have fewer bits than fp32: a lane's 16 values of a slice are off by 2^-25 of
+    // the scaled range, more than 2^-23 of the largest of them from here on.
+    auto lost = [&](float m) { return m > 0.f && m * scale < 0.25f; };
     // the parts of a slice, if need be with another scale
     auto parts_of = [&](const Slice &v) {
         if constexpr (!BF) {
             const float m = largest(v);
             if (__ballot(m > limit) != 0ull) rescale(m);
+            bad = bad || lost(m);
         }
         return split(v);
     };
@@ -246,6 +251,7 @@ enc_proj_kernel(const float *__restrict__ x, const int *__restrict__ enc_len, co
                 if constexpr (!BF) {
                     const float m = largest(v);
                     if (__ballot(m > limit) != 0ull) { rescale(m); next = split(v); }
+                    bad = bad || lost(m);
                 }
             } else multiply(p, s * 2 + 1 < nks, weight);
         };
@@ -296,17 +302,25 @@ enc_proj_kernel(const float *__restrict__ x, const int *__restrict__ enc_len, co
         for (int ni = 0; ni < NI; ++ni) big[ni] += small[ni];
         if ((__ballot(bad) != 0ull && r.len > 0) || *w.not_finite != 0u) {
             plain = true;
-            const float *row = x + ((long long)r.b * T + max(min(r.m0 + c, r.len - 1), 0)) * F + kh;
+            const float *row = x + ((long long)r.b * T + max(min(r.m0 + c, r.len - 1), 0)) * F + kh * 4;
+            const float *col[NI];
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
-                const float *col = w.plain + (long long)min(n0 + ni * 32 + c, J - 1) * F + kh;
-                v16f sum;
+                col[ni] = w.plain + (long long)min(n0 + ni * 32 + c, J - 1) * F + kh * 4;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) sum[v] = 0.f;
-                for (int s = WK == 1 ? 0 : wave; s < n_slices; s += WK)
-                    for (int k = s * 32; k < min(s * 32 + 32, F); k += 2) sum = __builtin_amdgcn_mfma_f32_32x32x2f32(col[k], row[k], sum, 0, 0, 0);
-                big[ni] = sum;
+                for (int v = 0; v < 16; ++v) big[ni][v] = 0.f;
             }
+            // (eight k's, four of either half of the lanes: which k an instruction takes does not matter, both operands take the same)
+            for (int s = WK == 1 ? 0 : wave; s < n_slices; s += WK)
+                for (int k = s * 32; k < min(s * 32 + 32, F); k += 8) {
+                    const v4f xv = *reinterpret_cast<const v4f *>(row + k);
+#pragma unroll
+                    for (int ni = 0; ni < NI; ++ni) {
+                        const v4f wv = *reinterpret_cast<const v4f *>(col[ni] + k);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) big[ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[e], xv[e], big[ni], 0, 0, 0);
+                    }
+                }
         }
     }
     auto value = [&](int ni, int j) {

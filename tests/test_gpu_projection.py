@@ -65,6 +65,28 @@ def test_projection_of_frames_and_weights_of_very_different_magnitude(pkg, B, T,
 
 
 @pytest.mark.parametrize("B,T,F,J", [(2, 40, 1040, 68), (2, 40, 272, 68), (40, 70, 112, 1028)])
+@pytest.mark.parametrize("size", [1e5, 1e7, 1e12])
+@pytest.mark.parametrize("at", [5, -1])
+def test_projection_of_frames_with_one_large_feature(pkg, B, T, F, J, at, size):  # noqa: F811
+    """A feature far larger than the others, whose weights are that much smaller, or zero: sums as accurate as fp32
+    products are, K 2^-24 of their magnitudes."""
+    import torch
+    model = synth.make_model(synth.ModelDims(F=F, E=8, H=8, L=1, J=J, V1=5), 3)
+    rng = np.random.default_rng(B + F)
+    x = rng.standard_normal((B, T, F)).astype(np.float32)
+    x[:, ::3, at] *= np.float32(size)
+    model.w_enc[:, at] /= np.float32(size)
+    model.w_enc[::2, at] = 0.0
+    ln = np.full(B, T, np.int32)
+    eng = pkg.Engine(model, B, T)
+    got = eng.encoder_projection(torch.from_numpy(x).cuda(), torch.from_numpy(ln).cuda()).cpu().numpy()
+    eng.close()
+    x, w = x.astype(np.float64), model.w_enc.astype(np.float64)
+    bound = (F + 4) * 2.0 ** -24 * (np.abs(x) @ np.abs(w).T + np.abs(model.b_enc))
+    assert (np.abs(got - (x @ w.T + model.b_enc)) <= bound).all()
+
+
+@pytest.mark.parametrize("B,T,F,J", [(2, 40, 1040, 68), (2, 40, 272, 68), (40, 70, 112, 1028)])
 @pytest.mark.parametrize("where", ["frames", "weights"])
 def test_projection_of_values_that_are_not_finite(pkg, B, T, F, J, where):  # noqa: F811
     """Infinities and NaN come out where the fp32 product has them, and the rest as ever."""
