@@ -487,14 +487,20 @@ __device__ __forceinline__ float joint_scale(TopWord top, float q_bound)
     return __uint_as_float((268u << 23) - max(__float_as_uint(bound) & 0x7f800000u, 27u << 23));
 }
 
-// Where the largest operand of a sample in a wave's eighth of K has to lie for two fp16 parts to hold the eighth as well
-// as fp32 does: parts are off by 2^-25 at most, which is 2^-23 of the least one; beyond the most there are none.
+// Where the largest operand of a sample in a lane's quarter of the wave's eighth of K has to lie for two fp16 parts to hold them
+// as well as fp32 does: parts are off by 2^-25 at most, which is 2^-23 of the least one; beyond the most there are none.
 constexpr float kResLeast = 0.25f, kResMost = 65504.f;
-// of a ballot: samples (lane % 16) that one of their four lanes speaks for
-__device__ __forceinline__ unsigned samples_of(unsigned long long m)
+// Samples (lane % 16) that parts do not hold, of ballots of the lanes whose largest operand is below the least one (and not
+// zero), not below it, and beyond the most.  One quarter in which all that is not zero is small is nothing unusual behind a
+// relu; it matters where hardly anything else is there: two such, or one, and not two quarters with ordinary values.
+__device__ __forceinline__ unsigned unheld(unsigned long long small, unsigned long long fine, unsigned long long beyond)
 {
-    const unsigned both = (unsigned)m | (unsigned)(m >> 32);
-    return (both | both >> 16) & 0xffffu;
+    auto any = [](unsigned long long m) { const unsigned b = (unsigned)m | (unsigned)(m >> 32); return b | b >> 16; };
+    auto two = [](unsigned long long m) {
+        const unsigned a = (unsigned)m, b = (unsigned)(m >> 32), both = a & b, one = a | b;
+        return both | both >> 16 | (one & one >> 16);
+    };
+    return ((two(small) & ~two(fine)) | (any(small) & ~any(fine)) | any(beyond)) & 0xffffu;
 }
 
 __device__ __forceinline__ float inverse_power(float two_to_n) { return __uint_as_float(0x7f000000u - __float_as_uint(two_to_n)); }
@@ -1331,8 +1337,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     }
                     ordered();
                     if constexpr (b % NB == NB - 1) {
-                        if constexpr (!BF && !WHOLE)
-                            again |= ((samples_of(__ballot(top > 0.f)) & ~samples_of(__ballot(top >= kResLeast))) | samples_of(__ballot(top > kResMost))) << (mt * 16);
+                        if constexpr (!BF && !WHOLE) {
+                            const unsigned long long fine = __ballot(top >= kResLeast), small = __ballot(top > 0.f) & ~fine, beyond = __ballot(top > kResMost);
+                            if ((small | beyond) != 0ull) again |= unheld(small, fine, beyond) << (mt * 16);
+                        }
                         if (TAIL && g == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = BF || WHOLE ? tb[0] : tb[0] + tb[1];
                         // every wave's sums to LDS, [wave][sample][column]
 #pragma unroll
@@ -1344,8 +1352,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             if (has_tail) output(std::true_type());
             else output(std::false_type());
             if constexpr (!BF && !WHOLE) {
-                // Samples whose operand does not lie between kResLeast and kResMost in the wave's eighth, far below the bound or
-                // infinite, are computed once more as fp32 products (the weights' parts added up again).  The lane's e-th value of
+                // Samples whose operand parts do not hold in the wave's eighth, far below the bound or infinite, are computed once more
+                // as fp32 products (the weights' parts added up again; two tiles of samples 6.5 us).  The lane's e-th value of
                 // a block times its e-th weight is one 16x16x4 instruction.
                 if (again != 0u) {
 #pragma unroll 1

@@ -390,3 +390,15 @@ def test_the_largest_instances(pkg, L, bf16):  # noqa: F811
     eng = pkg.Engine(w.model, w.B, w.T, flags=pkg.RNNT_FLAG_BF16_ARITHMETIC if bf16 else 0)
     check(pkg, w, "label", f"largest {L} bf16={bf16}", engine=eng, bf16=bf16, logp=True)
     eng.close()
+
+
+@pytest.mark.parametrize("H,J,V1,L,durations", WIDE_TDT)
+@pytest.mark.parametrize("size", [1e7, 1e12])
+def test_a_large_joint_unit_that_nobody_reads(pkg, H, J, V1, L, durations, size):  # noqa: F811
+    """One unit of every frame is far larger than the others and has no weights in the output layer."""
+    w = model_inputs(H, J, V1, L, B=9, T=12, seed=H + 3, durations=durations)
+    w.model.b_enc[7] = size
+    w.model.w_out[:, 7] = 0.0
+    eng = pkg.Engine(w.model, w.B, w.T)
+    check(pkg, w, w.variant, f"large unit {H}/{J}/{V1}/{L} {durations} {size}", engine=eng, logp=True)
+    eng.close()
