@@ -1355,6 +1355,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 // Samples whose operand parts do not hold in the wave's eighth, far below the bound or infinite, are computed once more
                 // as fp32 products (the weights' parts added up again; two tiles of samples 6.5 us).  The lane's e-th value of
                 // a block times its e-th weight is one 16x16x4 instruction.
+                // (Of the step's own samples: what rows without an utterance, and places without a frame, hold may be of any size.)
+                if (again != 0u) again &= (unsigned)__ballot(pidx >= 0);
                 if (again != 0u) {
 #pragma unroll 1
                     for (int mt = 0; mt < NT; ++mt) {
