@@ -612,7 +612,7 @@ int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
     return RNNT_OK;
 }
 
-// Utterances a team decodes at a time and frames per utterance and joint step for a launch of nb.
+// Utterances a team decodes at a time for a launch of nb, and frames of each and joint step while there are as many.
 void resident_rows(const ResidentPlan &pl, int nb, int *slots, int *la)
 {
     *slots = std::min(kResRows, (nb + pl.n_teams - 1) / pl.n_teams);
@@ -647,7 +647,8 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
             p.VT = e->multi_blank ? e->NOUT : d.V1;
             for (int i = 0; i < kMaxDur; ++i) p.durations[i] = e->durations[i];
             p.B = nb; p.T = T; p.S = S; p.cap = cap;
-            resident_rows(pl, nb, &p.slots, &p.la);
+            int la;
+            resident_rows(pl, nb, &p.slots, &la);
             p.spin_limit = wait_polls(e->wait_limit, kResidentWait);
             p.pl = pl;
             const long long oc = (long long)off * cap;
@@ -669,7 +670,7 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
             p.form = ws.form; p.abort_flag = ws.abort_flag; p.status = ws.status; p.stats = ws.stats;
             p.zero_stats = off == 0;
             p.count_rows = variant == kFrameLooping;
-            HIP_TRY(launch_resident(p, p.slots * p.la <= 16 ? 1 : 2, (plain && !e->coop_launch) || e->plain_launch, stream));
+            HIP_TRY(launch_resident(p, p.slots <= 2 ? 1 : 2, (plain && !e->coop_launch) || e->plain_launch, stream));
         }
         return RNNT_OK;
     });

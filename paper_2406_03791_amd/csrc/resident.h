@@ -14,7 +14,7 @@ constexpr int kResUnits = 20;             // LSTM units per work-group at most
 constexpr int kResSlots = 4;              // exchange slots per vector, used in turn
 constexpr int kResRows = 4;               // utterances a team decodes at the same time at most
 constexpr int kResSamples = 32;           // (utterance, frame) pairs per joint step at most
-constexpr int kResCalm = 16;              // joint steps after which a row's frames are halved, see the loop control
+constexpr int kResCalm = 8;               // joint steps after which a row's frames may be halved, see the loop control
 constexpr int kResList = 128;             // utterances a team takes per launch at most
 
 // Size classes: the register arrays, LDS rows and exchange buffers have compile-time sizes, so the
@@ -78,7 +78,7 @@ struct ResidentParams {
     int tdt;
     int durations[kMaxDur];
     int B, T, S, cap;
-    int slots, la;        // utterances decoded at a time per team, frames per utterance and joint step
+    int slots;            // utterances decoded at a time per team
     unsigned spin_limit;
     ResidentPlan pl;
     const int *enc_len;
@@ -179,7 +179,7 @@ struct ResidentWeights { int H, J, L; const float *w_hh[2], *w_ih1, *w_pred, *b_
 struct ResidentImages { float *w, *w_help, *w_tail, *s_out, *s_pred, *s_ih, *s_hh[2], *row_scales; unsigned *check; };
 hipError_t pack_resident(const ResidentPlan &pl, const ResidentWeights &rw, const ResidentImages &im, hipStream_t stream);
 
-// nmt: tiles of 16 samples a joint step has, 1 or 2
+// nmt: tiles of 16 samples a joint step has, 1 (up to two utterances at a time per team) or 2
 hipError_t launch_resident(const ResidentParams &p, int nmt, bool plain, hipStream_t stream);
 
 }  // namespace rnnt

@@ -20,7 +20,7 @@ RNNT_DECLARE(3, 0)
 hipError_t launch_resident(const ResidentParams &p, int nmt, bool plain, hipStream_t stream)
 {
     // what the kernel's buffers are laid out for
-    if (nmt < 1 || nmt > 2 || p.slots < 1 || p.slots > kResRows || p.la < 1 || p.slots * p.la > 16 * nmt ||
+    if (nmt < 1 || nmt > 2 || p.slots < 1 || p.slots > (nmt == 1 ? 2 : kResRows) ||
         p.pl.cls < 0 || p.pl.cls >= kResClasses || (p.B + p.pl.n_teams - 1) / p.pl.n_teams > kResList)
         return hipErrorInvalidValue;
     switch (p.pl.kind) {

@@ -31,10 +31,10 @@
 // of the step.
 //
 // Utterances are decoded label-looping fashion: every utterance has its own frame index, a joint
-// step examines `la` frames of every utterance (half as many in label-dense stretches of two-layer fp32
-// models, see the end of the loop), and the next prediction step runs as soon as one
+// step examines `la` frames of every utterance in work (16 or 32 in all; half as many in label-dense stretches of two-layer
+// fp32 models, see the end of the loop), and the next prediction step runs as soon as one
 // of them has a label.  A team takes a list of utterances and decodes up to R at a time;
-// when one ends the next of the list takes its place.
+// when one ends the next of the list takes its place, or, if there is none, the others get its frames.
 //
 // Exchange: a vector's buffer has four slots used in turn; words are 32-bit floats, all ones
 // meaning "not there yet" (readers poll the data itself).  A work-group puts that mark back into
@@ -908,29 +908,6 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         return l;
     };
     // (joint output: a wave takes every eighth step of K for both column tiles)
-    // Frames per row and samples of a joint step with NT tiles of samples: p.la, or half of it with one tile instead
-    // of two.  (That is read and worked out anew, or it and all that follows from it takes scalar registers in the
-    // steps with two.)
-    struct Frames {
-        int la, ns;
-        unsigned inv_la, inv_t;
-        __device__ __forceinline__ int row_of(int s) const { return (int)(((unsigned)s * inv_la) >> 10); }      // s / la for s < 32, la <= 16
-        __device__ __forceinline__ int mod_la(int t) const { return t - (int)__umulhi((unsigned)t, inv_t) * la; }      // t % la for t < 2^24
-    };
-    auto frames_of = [&](auto nt_) {
-        Frames f;
-        if constexpr (HALVES) {
-            const Args a = args_again();
-            f.la = decltype(nt_)::value < NMT ? a->la >> 1 : a->la;
-            f.ns = a->slots * f.la;
-        } else {
-            f.la = p.la;
-            f.ns = p.slots * f.la;
-        }
-        f.inv_la = (1024u + (unsigned)f.la - 1u) / (unsigned)f.la;
-        f.inv_t = 0xffffffffu / (unsigned)f.la + 1u;
-        return f;
-    };
     constexpr int QS = res_q_row(CLS);               // floats per row of a wave's eighth of q
     float *lq = reinterpret_cast<float *>(lds + lo.q) + x.wave * (R * QS);
     const unsigned lds_p = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)(lds + lo.p);
@@ -968,30 +945,50 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // (and, in lane_const, what the prediction step does with the candidate state); of sample `lane`, its row
     // of the projected frames, -1 for none.
     int last = p.blank, pidx = -1;
-    // What a lane needs of the loop control's tables, packed (a register each would be one too many): the
-    // sample's row (3 bits) and place (4), its own row's first sample (5), the word of a row of T0 that
-    // its cell takes (12); kTake and kFresh.
+    // What a lane needs of the loop control's tables, packed (a register each would be one too many): rows of the
+    // samples lane % 16, 16 + lane % 16, four times the wave plus lane / 16, and lane % 32 (2 bits each, at 0, 14, 16 and 28);
+    // bytes to the word of a row of T0 that its cell takes (2 .. 13); the place of sample lane % 32 among its row's
+    // (5 bits, at 18); its own row's first sample (5, at 23); kTake and kFresh.
     int lane_const = kFresh;
-    auto pack_lane = [&](const Frames &f, int lane) {
-        const int srow = min(f.row_of(lane & (kResSamples - 1)), R - 1), si = (lane - srow * f.la) & 15;
+    // Rows that take part in the joint step (one bit in four, as in LEADS), and the frames of each: the samples are dealt
+    // evenly to the rows with an utterance, so that the last ones of a team's list go on faster when the others have
+    // ended.  (One row of 32 samples: 31, which shifts of a word by 0 to 31 do for.)  With eight frames a row whatever
+    // its neighbours do, 32 utterances on six teams took 178, 170 and 151 joint steps instead of 161, 160 and 139 (three
+    // draws; 1544, 1450 and 1348 us instead of 1470, 1412 and 1283), 19 of a multi-blank model 105, 89 and 69 instead of
+    // 85, 76 and 54 (846, 760 and 602 us instead of 757, 711 and 520).
+    unsigned part_rows = 0;
+    int la = 0;
+    auto part_samples = [&]() { return __builtin_popcount(part_rows) * la; };
+    auto lay_out = [&](auto nt_, int lane, unsigned of) {
+        part_rows = of;
+        const int n = __builtin_popcount(of);
+        // (a byte for every number of rows; label-dense: no more than a team of all rows has, they are not looked at)
+        la = (int)((decltype(nt_)::value == 2 ? 0x080a101fu : NMT == 1 ? 0x04050810u : 0x04050505u) >> (max(n - 1, 0) * 8) & 0xffu);
+        unsigned rows_of = 0;            // the rows that take part, one after the other, two bits each
+        int at = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (of >> (r * LR) & 1u) { rows_of |= (unsigned)r << at; at += 2; }
+        auto turn_of = [&](int s) { return (s >= la ? 1 : 0) + (s >= 2 * la ? 1 : 0) + (s >= 3 * la ? 1 : 0); };
+        auto row_of = [&](int s) { return (int)(rows_of >> (turn_of(s) * 2) & 3u); };
+        const int s = lane & (kResSamples - 1);
         const Place l = place_of(lane);
-        lane_const = srow | si << 3 | (min(l.row, p.slots - 1) * f.la) << 7 | (l.gu * 4 + l.j) << 12 | (lane_const & (kTake | kFresh));
+        const int first = __builtin_popcount(of & ((1u << (lane & 12)) - 1u)) * la;
+        lane_const = row_of(s & 15) | l.gu * 16 + l.j * 4 | row_of(16 + (s & 15)) << 14 | row_of((x.wave * 4 + (lane >> 4)) & 31) << 16 |
+                     ((s - turn_of(s) * la) & 31) << 18 | (first & 31) << 23 | row_of(s) << 28 | (lane_const & (kTake | kFresh));
     };
     std::integral_constant<int, NMT> all_tiles;
-    const Frames f_all = frames_of(all_tiles);
-    pack_lane(f_all, lane0);
-    // Samples of the next joint step: `la` frames of every row in work, frame f in the row's place f % la,
-    // so that a frame stays where it is until the row has passed it.  fresh: the samples to load.
+    // Samples of the next joint step: `la` frames of every row in work, each in a place of the row's that it keeps
+    // until the row has passed it (m: the place of the row's frame t, the next ones follow in a ring).  fresh: the samples to load.
     unsigned long long fresh = 0;
-    auto set_up_samples = [&](const Frames &f, int lane, int t, int m, int b, int len) {
-        const int la = f.la, ns = f.ns;
-        const int from = (lane_const & 7) * (LR * 4);                               // (bytes: LR lanes per row)
+    auto set_up_samples = [&](int lane, int t, int m, int b, int len) {
+        const int from = (lane_const >> 28 & 3) * (LR * 4);                         // (bytes: LR lanes per row)
         const int base = __builtin_amdgcn_ds_bpermute(from, b * p.T + t);
         const int info = __builtin_amdgcn_ds_bpermute(from, max(0, min(len - t, la)) | m << 8);
-        int off = ((lane_const >> 3) & 15) - (info >> 8);
+        int off = (lane_const >> 18 & 31) - (info >> 8);
         if (off < 0) off += la;
         const int was = pidx;
-        pidx = (lane < ns && off < (info & 255)) ? base + off : -1;
+        pidx = (lane < part_samples() && off < (info & 255)) ? base + off : -1;
         fresh = __ballot(pidx >= 0 && pidx != was);
         n_samples += __popcll(__ballot(pidx >= 0));
     };
@@ -1020,7 +1017,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         const unsigned long long m = __ballot(got) & LEADS;
         any_active = need_pred = m != 0ull;
         row_steps = __popcll(m);
-        set_up_samples(f_all, lane0, 0, 0, b, len);
+        lay_out(all_tiles, lane0, (unsigned)m);
+        set_up_samples(lane0, 0, 0, b, len);
     }
     // the row of the embedding table (folded into the first layer) that the next prediction step adds
     float t0 = 0.f;
@@ -1028,7 +1026,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     auto load_t0 = [&]() {
         t0 = 0.f;
         if (has_cells)
-            t0 = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(p.T0) + (__umul24((unsigned)last, t0_row) + ((unsigned)lane_const >> 10 & 0x3ffcu)));
+            t0 = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(p.T0) + (__umul24((unsigned)last, t0_row) + ((unsigned)lane_const & 0x3ffcu)));
     };
     // kResident2Pair: W_hh h of the last step's candidates of a layer as far as it is there
     auto load_pre = [&](unsigned n, int l, unsigned (&to)[kResQuarters]) {
@@ -1059,8 +1057,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // Steps with NT tiles of samples: until the team is done, or the other number of tiles suits its rows better.
     auto steps = [&](auto nt_) {
     constexpr int NT = decltype(nt_)::value;
-    const Frames f = HALVES ? frames_of(nt_) : f_all;
-    const int la = f.la, ns = f.ns;
+    constexpr int NS = 16 * NT;
     bool change = false;
     while (ok && any_active && !change) {
         if (need_pred) {
@@ -1116,7 +1113,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             // The frames of the joint step, by the waves that have the least to do here.  A wave's loads return in
             // order, so these waves see the hidden vector when their frames are there: at about the time it comes.
             if (x.wave >= 5)
-                for (int s = x.wave - 5; s < ns; s += kResWaves - 5)
+                for (int s = x.wave - 5; s < part_samples(); s += kResWaves - 5)
                     if (fresh >> s & 1) load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
             RES_MARK(1);
             Op x1;
@@ -1231,7 +1228,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             }
             RES_MARK(9);
         } else {
-            for (int s = x.wave; s < ns; s += kResWaves)
+            for (int s = x.wave; s < part_samples(); s += kResWaves)
                 if (fresh >> s & 1) load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
@@ -1263,7 +1260,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             };
             auto frame_at = [&](int mt, int i) { return frame0 + ((k40 + i * 8 - (i < NF ? 0 : g)) ^ m16) * 16 + mt * 16 * ROW * 4; };
             auto q_of = [&](int mt) {
-                const unsigned row = min(__umul24((unsigned)(mt * 16 + m16), f.inv_la) >> 10, (unsigned)(R - 1));
+                const unsigned row = (unsigned)lane_const >> (mt ? 14 : 0) & 3u;
                 if constexpr (!BF && !WHOLE) scale = rc.scale[row];
                 return lo.q + (int)__umul24(row, QS * 4u) + x.wave * (R * QS * 4) + g * 32;
             };
@@ -1412,7 +1409,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 const float2 bias = rc.bo[tid & 15], scale = rc.so[tid & 15];
                 static_assert(kResWaves == 8, "eight lanes add the waves' sums of the tail column");
                 float tw = 0.f, back = 1.f;
-                if constexpr (!BF && !WHOLE) back = inverse_power(rc.scale[min(f.row_of(s), R - 1)]);
+                if constexpr (!BF && !WHOLE) back = inverse_power(rc.scale[lane_const >> 16 & 3]);
                 if (has_tail) tw = tpart[((tid & 7) * 2 + (s >> 4)) * 16 + (s & 15)];
                 const float l0 = (((o[0].x + o[1].x) + (o[2].x + o[3].x)) + ((o[4].x + o[5].x) + (o[6].x + o[7].x))) * scale.x * back + bias.x;
                 const float l1 = (((o[0].y + o[1].y) + (o[2].y + o[3].y)) + ((o[4].y + o[5].y) + (o[6].y + o[7].y))) * scale.y * back + bias.y;
@@ -1427,7 +1424,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 if (has_tail) {
                     tail = lane_sum<8>(tw) * rc.st * back + rc.bt;
                     if (tcol >= p.VT) {
-                        if ((tid & 15) == 0 && s < ns) {
+                        if ((tid & 15) == 0) {
                             const unsigned d = ((unsigned)s * kMaxDur + (unsigned)(tcol - p.VT)) * 4u;
                             put(x, d, bo.dur + slot_at(jn, DSLOT), bo.dur + slot_at(jn + 2, DSLOT), word_of(tail));
                         }
@@ -1436,7 +1433,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                         m = tail; ix = tcol;
                     }
                 }
-                if (dur_cols && s < ns) {
+                if (dur_cols) {
                     // duration columns inside the column tiles
 #pragma unroll
                     for (int c = 0; c < 2; ++c)
@@ -1446,13 +1443,13 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                         }
                 }
                 const unsigned ko = ((unsigned)s * TS + (unsigned)x.rank) * 8u;
-                if ((tid & 15) == first && s < ns)
+                if ((tid & 15) == first)
                     put2(x, ko, bo.key + slot_at(jn, KSLOT), bo.key + slot_at(jn + 2, KSLOT), (r2u){word_of(m), (unsigned)ix});
                 if (p.logps) {
                     float e = (m0 > -INFINITY ? expf(m0 - m) : 0.f) + (m1 > -INFINITY ? expf(m1 - m) : 0.f);
                     e = lane_sum<16>(e);
                     if (tail > -INFINITY) e += expf(tail - m);
-                    if ((tid & 15) == 0 && s < ns)
+                    if ((tid & 15) == 0)
                         put(x, ko / 2, bo.lse + slot_at(jn, KSLOT / 2), bo.lse + slot_at(jn + 2, KSLOT / 2), word_of(e));
                 }
             }
@@ -1460,7 +1457,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         if constexpr (NT < NMT) {
             // the samples that this step does not have: the marks that their words of step jn + 2 need
             const int tid = x.wave * 64 + lane_id(), s = tid >> 4;
-            if (s >= ns && s < ns * 2) {
+            if (s >= NS && s < NS * 2) {
                 const int gcol = x.rank * 32 + (tid & 15) * 2;
                 const unsigned ko = ((unsigned)s * TS + (unsigned)x.rank) * 8u, ds = (unsigned)s * kMaxDur * 4u;
                 const bool lead = (tid & 15) == 0;
@@ -1482,8 +1479,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             constexpr int L = TS / 2;
             static_assert(16 * NT * L <= kResThreads, "one piece per thread");
             const int s = tid / L;
-            if ((x.wave * 64) / L < ns) {
-                const unsigned off[1] = {(unsigned)min(tid, ns * L - 1) * 16u};
+            if ((x.wave * 64) / L < NS) {
+                const unsigned off[1] = {(unsigned)tid * 16u};
                 r4u v[1];
                 // TDT: the sample's durations, one or two for each of the first lanes, come along
                 constexpr int ND = L >= kMaxDur ? 1 : kMaxDur / L;
@@ -1508,7 +1505,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     const float d0 = di < p.D ? __uint_as_float(dv[0]) : -INFINITY, d1 = ND > 1 && di + 1 < p.D ? __uint_as_float(dv[ND - 1]) : -INFINITY;
                     const float dl = fmaxf(d0, d1), dm = lane_max<L>(dl);
                     const unsigned hit = (unsigned)(__ballot(dl == dm && di < p.D) >> (lane & ~(L - 1))) & ((1u << L) - 1u);
-                    if (li == (hit ? __builtin_ctz(hit) : 0) && s < ns) rc.s_d[s] = d0 == dm || ND == 1 ? v0 : v1;
+                    if (li == (hit ? __builtin_ctz(hit) : 0)) rc.s_d[s] = d0 == dm || ND == 1 ? v0 : v1;
                 } else {
                     receive<1>(p, x, off, bo.key + slot_at(jn, KSLOT), v);
                 }
@@ -1539,7 +1536,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     t = lane_sum<L>(t);
                     lp2 = -logf(t);
                 }
-                if (win && s < ns) {
+                if (win) {
                     rc.s_k[s] = (unsigned)bi < (unsigned)p.VT ? bi : p.blank;
                     rc.s_v[s] = m + 0.0f;
                     if (p.logps) rc.s_lp[s] = lp2;
@@ -1556,7 +1553,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             if (PAIR) load_pre(n_pred, 0, pre[0]);
             __syncthreads();
             RES_MARK(14);
-            const int mine = rc.s_k[lane & (kResSamples - 1)], row0 = (lane_const >> 7) & 31, left = w.len - w.t;
+            const int mine = rc.s_k[lane & (kResSamples - 1)], row0 = lane_const >> 23 & 31;
+            // (a row that does not take part has nothing left for now)
+            const bool in = (part_rows >> (lane & 12) & 1u) != 0u;
+            const int left = in ? w.len - w.t : 0;
             const bool lead = lane < 16 && (lane & (LR - 1)) == 0;     // stands for its row
             const bool writer = x.rank == 0 && x.wave == kResWaves - 1 && lead;
             const bool walk = p.tdt || p.VT != p.V1;
@@ -1572,8 +1572,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 // lane = sample: the offset (from the row's frame) that the walk goes to from it, its own for a label
                 // or beyond the row's frames, and the lane of that offset, its own where the walk leaves the step;
                 // then the hops are doubled until every one reaches its end
-                const int sr = lane_const & 7, ms = from_lane(m, sr * LR);
-                int to = ((lane_const >> 3) & 15) - ms;
+                const int ms = from_lane(m, (lane_const >> 28 & 3) * LR), si = lane_const >> 18 & 31;
+                int to = si - ms;
                 if (to < 0) to += la;
                 int d = 0;
                 if (mine >= p.V1) d = max(rc.dur[(mine - p.V1) & (kMaxDur - 1)], 1);            // big blank: its span of frames
@@ -1582,7 +1582,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 to += d;
                 int at = ms + to;
                 if (at >= la) at -= la;
-                int hop = (d > 0 && to < la ? (int)__umul24((unsigned)sr, (unsigned)la) + at : lane) << 2;
+                int hop = (d > 0 && to < la ? lane - si + at : lane) << 2;
                 for (int i = 1; i < la; i *= 2) hop = __builtin_amdgcn_ds_bpermute(hop, hop);
                 hop = __builtin_amdgcn_ds_bpermute((row0 + m) << 2, hop);
                 pos = __builtin_amdgcn_ds_bpermute(hop, to);
@@ -1619,13 +1619,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             w.t += adv;
             const bool ended = left > 0 && adv >= left;
             int action = found && !ended ? kTake : 0;
-            if (walk) {
-                m = f.mod_la(w.t);
-            } else {
-                m += adv;                               // (at most la + 1)
-                if (m >= la) m -= la;
-                if (m >= la) m -= la;
-            }
+            // (where no frame of the step is left, any place will do)
+            m = adv < la ? m + adv : 0;
+            if (m >= la) m -= la;
             if (__ballot(ended) != 0ull) {
                 if (writer && ended) res_finish_row(b, w.cnt);
                 const bool got = refill(lane, ended, b, w.len);
@@ -1633,11 +1629,17 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 if (lead) rows.b[r] = b;
                 load_t0();
             }
-            lane_const = (lane_const & ~(kTake | kFresh)) | action;
-            if (lead) { rows.s[r] = w; rows.m[r] = m; }
-
+            if (in) lane_const = (lane_const & ~(kTake | kFresh)) | action;
             const unsigned long long moved = __ballot(action != 0) & LEADS;      // rows whose next step has new inputs
-            any_active = __ballot(w.t < w.len) != 0ull;
+            const unsigned active = (unsigned)(__ballot(w.t < w.len) & LEADS);
+            any_active = active != 0u;
+            if (active != part_rows && any_active) {
+                // (a row has ended for good: its samples go to the others)
+                lay_out(nt_, lane, active);
+                m = 0;
+                pidx = -1;                // every frame has another place
+            }
+            if (lead) { rows.s[r] = w; rows.m[r] = m; }
             need_pred = moved != 0ull;
             row_steps += __popcll(moved);
             if constexpr (HALVES && NT == NMT) {
@@ -1650,7 +1652,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 }
             }
             if constexpr (NT < NMT) change = __ballot(left > 0 && !found && !ended) != 0ull;      // a row's next label is further away
-            if (!change) set_up_samples(f, lane, w.t, m, b, w.len);
+            if (!change) set_up_samples(lane, w.t, m, b, w.len);
         }
         ok = rc.ok != 0;
         RES_MARK(15);
@@ -1671,15 +1673,13 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         auto changed_to = [&](auto nt_) {
             const int lane = lane_id(), r = (lane / LR) & (R - 1);
             const RRow w = rows.s[r];
-            const Frames f = frames_of(nt_);
-            const int m = f.mod_la(w.t);
-            pack_lane(f, lane);
+            lay_out(nt_, lane, part_rows);
             if (lane < 16 && (lane & (LR - 1)) == 0) {
-                rows.m[r] = m;
+                rows.m[r] = 0;
                 rows.since[r] = -0x10000000;      // (not after less than kResCalm steps)
             }
             pidx = -1;                // every frame has another place
-            set_up_samples(f, lane, w.t, m, rows.b[r], w.len);
+            set_up_samples(lane, w.t, 0, rows.b[r], w.len);
         };
         for (;;) {
             steps(all_tiles);

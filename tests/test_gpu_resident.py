@@ -15,8 +15,8 @@ from test_gpu_parity import check, pkg  # noqa: F401  (pkg: fixture)
 pytestmark = pytest.mark.gpu
 
 
-def model_inputs(H, J, V1, L, B, T, seed, durations=(), big_blanks=(), max_symbols=4):
-    dims = synth.ModelDims(F=32, E=24, H=H, L=L, J=J, V1=V1, durations=tuple(durations), big_blanks=tuple(big_blanks))
+def model_inputs(H, J, V1, L, B, T, seed, durations=(), big_blanks=(), max_symbols=4, F=32):
+    dims = synth.ModelDims(F=F, E=24, H=H, L=L, J=J, V1=V1, durations=tuple(durations), big_blanks=tuple(big_blanks))
     model = synth.make_model(dims, seed, weight_range=0.15, emb_gain=4.0, pred_gain=3.0, blank_bias=1.5)
     x, ln = synth.make_inputs(seed, B, T, dims.F, 0, T)
     variant = "tdt" if durations else "label"
@@ -206,6 +206,32 @@ def test_label_dense_and_sparse_stretches(pkg, B, extra):  # noqa: F811
             k += 1
     print(f"samples {stats['joint_samples']}, without changes {full}", flush=True)
     assert stats["joint_samples"] < 0.95 * full
+
+
+@pytest.mark.parametrize("extra", [{}, dict(durations=(0, 1, 9, 40)), dict(big_blanks=(2, 33))])
+@pytest.mark.parametrize("H,J,V1,L", [(64, 68, 60, 1), (316, 320, 500, 1), (324, 332, 520, 2)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_rows_that_end_one_after_the_other(pkg, H, J, V1, L, extra, bf16):  # noqa: F811
+    """Four rows a team that end at different times, so that the joint step goes from 8 frames a row to 10, 16 and 31, and
+    (two rows a team) from 8 to 16: labels in the first and the last frame that such a step holds, skips beyond it,
+    one frame more than the last rows' steps hold, and utterances that start when others have ended."""
+    n_teams = {60: 32, 500: 16, 520: 6 if not bf16 else 8}[V1]
+    for rows, more in ((4, 2), (2, 0)):
+        B = rows * n_teams + more
+        w = model_inputs(H, J, V1, L, B=B, T=97, seed=H + rows, F=(J + 15) // 16 * 16, **extra)
+        # few labels: a frame without one for most of the frames
+        want = 60.0 * np.maximum(w.model.w_out[w.model.dims.blank].astype(np.float64), 0.0) - w.model.b_enc
+        blank = np.linalg.lstsq(w.model.w_enc.astype(np.float64), want, rcond=None)[0].astype(np.float32)
+        g = np.random.default_rng(B)
+        gap = np.array([1, 8, 10, 11, 16, 17, 31, 32, 63])[g.integers(0, 9, (B, 97))].cumsum(1)
+        label = (gap[:, :, None] == np.arange(97)[None, None, :] + 1).any(1)
+        x = np.where(label[:, :, None], w.enc_out, blank[None, None]).astype(np.float32)
+        length = np.sort(g.integers(1, 98, B))[::-1].astype(np.int32)
+        length[-more or B:] = 5
+        w = dataclasses.replace(w, enc_out=x, enc_len=length)
+        eng = pkg.Engine(w.model, w.B, w.T, flags=pkg.RNNT_FLAG_BF16_ARITHMETIC if bf16 else 0)
+        check(pkg, w, w.variant, f"rows that end {H}/{J}/{V1}/{L} {extra} {rows} bf16={bf16}", engine=eng, bf16=bf16, logp=not bf16)
+        eng.close()
 
 
 def test_an_engine_that_does_not_fit_the_memory_leaves_the_others_alone(pkg):  # noqa: F811
