@@ -1042,11 +1042,13 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         return __ballot(m == kMark) != 0ull;
     };
     auto wait_pre = [&](unsigned n, int l) {
+        // (the first look apart, which does not wait for stores behind the loads)
+        if (!no_pre(pre[l])) return;
         unsigned spins = 0;
-        while (no_pre(pre[l])) {
+        do {
             if (wait_expired(p, spins)) { rc.ok = 0; break; }
             load_pre(n, l, pre[l]);
-        }
+        } while (no_pre(pre[l]));
         x.polls += __builtin_amdgcn_readfirstlane((int)spins);
     };
     if (need_pred) load_t0();
@@ -1092,38 +1094,51 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 cs[l] = take ? cc[l] : cs[l]; cs[l] = fresh_row ? 0.f : cs[l];
                 ps[l] = take ? pc : ps[l]; ps[l] = fresh_row ? 0.f : ps[l];
             };
-            commit(0);
             // publishes the lane's hidden value of a layer and clears the slot of two steps ago
+            unsigned word = 0;
             auto publish_h = [&](int layer, const Place &l, float h) {
-                if (l.ok) {
-                    const unsigned o = (unsigned)l.row * VROW + (unsigned)l.gu * 4u, v = hidden_word<BF>(h);
-                    const unsigned s1 = slot_at(n, VSLOT), s2 = slot_at(n + 2, VSLOT);
-                    put(x, o, bo.h[layer] + s1, bo.h[layer] + s2, v);
-                    if (PAIR) { put_far(x, o, bo.hr[layer] + s1, v); put_far(x, o, bo.hr[layer] + s2, kMark); }
-                }
+                word = hidden_word<BF>(h);
+                if (l.ok) put(x, (unsigned)l.row * VROW + (unsigned)l.gu * 4u, bo.h[layer] + slot_at(n, VSLOT), bo.h[layer] + slot_at(n + 2, VSLOT), word);
             };
+            // The same to the helpers, when the team's own vector is there: loads and stores of a wave are counted in one
+            // order, so polls behind these stores wait for the memory side to take them (label looping of 32 utterances 1470 us with the
+            // stores before the polls, 1374 us now, together with the polls apart, below).
+            // (No condition around the stores, or what was loaded before them would be waited for together with them.)
+            auto forward_h = [&](int layer) {
+                const Place l = place_of(lane_id());
+                const unsigned o = has_cells && l.ok ? (unsigned)l.row * VROW + (unsigned)l.gu * 4u : 0x80000000u;
+                put_far(x, o, bo.hr[layer] + slot_at(n, VSLOT), word);
+                put_far(x, o, bo.hr[layer] + slot_at(n + 2, VSLOT), kMark);
+            };
+            // Polls of its own for either kind of wave.  The compiler knows by register what is on its way from memory, not by
+            // wave: behind a common branch around the cells it waits for T0's row, and so for the stores just made
+            // or the frames, before a register that the row may still come to is used for the polls.  (The two copies: bfloat16
+            // mode 978 us with a common branch, 957 us with two; one utterance 529 and 515 us.)
+            Op x1;
             if (has_cells) {
+                commit(0);
                 const Place l = place_of(lane_id());
                 float h;
                 cell(ps[0] + t0, l.j, cs[0], cc[0], h);
                 publish_h(0, l, h);
                 if constexpr (PAIR) { *stored(0) = cs[0]; *stored(1) = cc[0]; *stored(2) = ps[0]; }
-            }
-            if constexpr (NREC > 1) commit(1);
-            // The frames of the joint step, by the waves that have the least to do here.  A wave's loads return in
-            // order, so these waves see the hidden vector when their frames are there: at about the time it comes.
-            if (x.wave >= 5)
+                if constexpr (NREC > 1) commit(1);
+                RES_MARK(1);
+                x1.receive_from(p, x, bo.h[0] + slot_at(n, VSLOT), h4);
+            } else {
+                // The frames of the joint step, by the waves that have the least to do here.  A wave's loads return in
+                // order, so these waves see the hidden vector when their frames are there: at about the time it comes.
                 for (int s = x.wave - 5; s < part_samples(); s += kResWaves - 5)
                     if (fresh >> s & 1) load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
-            RES_MARK(1);
-            Op x1;
-            x1.receive_from(p, x, bo.h[0] + slot_at(n, VSLOT), h4);
+                x1.receive_from(p, x, bo.h[0] + slot_at(n, VSLOT), h4);
+                asm volatile("" :: "v"(t0), "v"(pre[0][0]), "v"(pre[0][1]), "v"(pre[0][2]), "v"(pre[0][3]));
+            }
             RES_MARK(2);
             if constexpr (NL > 1) {
                 const Op x0 = x1;
                 // (The second layer's results come during the stage.  Asked for at the end of the last step as well, they were there
                 // sooner, but no step was shorter: with one utterance 6.83 against 6.78 us.)
-                if (PAIR) load_pre(n - 1, NL - 1, pre[NL - 1]);
+                if (PAIR) { load_pre(n - 1, NL - 1, pre[NL - 1]); forward_h(0); }
                 stage<BF, CLS, R, 5, kResStageRow>(w_ih, x0, sums_ih, x.wave);
                 __syncthreads();
                 RES_MARK(3);
@@ -1162,12 +1177,13 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 } else {
                     RES_MARK(5);
                     x1.receive_from(p, x, bo.h[1] + slot_at(n, VSLOT), h4);
+                    if (PAIR) forward_h(1);
                 }
             }
             RES_MARK(6);
             // prediction-side joint projection
             stage<BF, CLS, R, 2, kResSumRow>(w_pr, x1, sums_pr, x.wave);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's frames are in LDS
+            if (x.wave >= 5) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's frames are in LDS
             __syncthreads();
             {
                 // LR adjacent threads per value (group of four columns, column, row), R / 2 waves' sums each
