@@ -21,6 +21,7 @@
 #include "pack.h"
 #include "resident.h"
 #include "resident_pack.h"
+#include "solo.h"
 
 using namespace rnnt;
 
@@ -559,12 +560,12 @@ EncWeights enc_weights(const rnnt_engine *e)
 // ---- resident decode kernel ---------------------------------------------------------------
 // What a call of the entry point that allocates nothing is charged of RNNT_NOALLOC_SCRATCH_BYTES, for P and its workspace.  Which
 // calls are refused is part of the interface, so this stays as it was when every kind had buffers of two recurrent
-// vectors and one sum a unit, and two-layer fp32 models five teams where they have six.
+// vectors and one sum a unit, two-layer fp32 models five teams where they have six, and the smallest models teams as well.
 size_t charged_bytes(const ResidentPlan &pl, size_t p_bytes)
 {
     auto sized = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
     const ResidentBuf buf = resident_buf(kResident2Pair, pl.cls);
-    const size_t teams = pl.kind == kResident2Pair ? pl.n_teams - pl.n_teams / 6 : pl.n_teams;
+    const size_t teams = pl.solo ? pl.n_teams / res_team(pl.cls) : pl.kind == kResident2Pair ? pl.n_teams - pl.n_teams / 6 : pl.n_teams;
     return sized(p_bytes) + sized((buf.pre + (buf.bytes - buf.pre) / kResQuarters) * teams) + sized((size_t)pl.n_xcd * 32 * sizeof(unsigned)) +
            sized(teams * kStatStride * sizeof(long long)) + sized(sizeof(unsigned)) + sized(sizeof(int));
 }
@@ -583,6 +584,18 @@ int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
 {
     const ResidentPlan &pl = e->res;
     const bool bf = pl.bf != 0;
+    if (pl.solo) {
+        const size_t groups = (size_t)solo_parts(solo_tiles(e->NOUT)) * 256;
+        HIP_TRY(e->res_w.alloc(groups * sizeof(float4) + sizeof(unsigned)));
+        unsigned *check = reinterpret_cast<unsigned *>(e->res_w.as<float4>() + groups), found = 0;
+        HIP_TRY(hipMemset(check, 0, sizeof found));
+        HIP_TRY(pack_solo(d.w_hh[0], d.w_pred, d.w_out, d.H, d.J, e->NOUT, e->res_w.as<float4>(), check, nullptr));
+        HIP_TRY(hipMemcpy(&found, check, sizeof found, hipMemcpyDeviceToHost));
+        if (found) { e->res.kind = kResidentNone; return RNNT_OK; }       // (as below)
+        HIP_TRY(e->res_stats.alloc((size_t)pl.n_teams * kStatStride * sizeof(long long)));
+        HIP_TRY(hipMemset(e->res_stats.p, 0, (size_t)pl.n_teams * kStatStride * sizeof(long long)));
+        return RNNT_OK;
+    }
     const size_t images = (size_t)res_team(pl.cls) * kResWaves * 64 * sizeof(float), scales = (size_t)e->NOUT + d.J + (d.L > 1 ? 4 * (d.L + 1) : 4) * (size_t)d.H;
     HIP_TRY(e->res_w.alloc(images * res_main_regs(pl.kind, bf, pl.cls)));
     if (pl.kind == kResident2Pair) HIP_TRY(e->res_help.alloc(images * 2 * res_help_regs(pl.cls)));
@@ -615,6 +628,7 @@ int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
 // Utterances a team decodes at a time for a launch of nb, and frames of each and joint step while there are as many.
 void resident_rows(const ResidentPlan &pl, int nb, int *slots, int *la)
 {
+    if (pl.solo) { *slots = 1; *la = kSoloFrames; return; }
     *slots = std::min(kResRows, (nb + pl.n_teams - 1) / pl.n_teams);
     *la = *slots <= 2 ? 16 / *slots : kResSamples / *slots;
     *la = std::min(*la, 16);
@@ -628,13 +642,30 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
     const ResidentPlan &pl = e->res;
     const Workspace ws = static_ws ? *static_ws : resident_workspace(e);
     CallInit ci;
-    ci.form = ws.form; ci.n_form = pl.n_xcd * 32; ci.abort_flag = ws.abort_flag; ci.status = ws.status;
+    ci.form = ws.form; ci.n_form = pl.solo ? 0 : pl.n_xcd * 32; ci.abort_flag = ws.abort_flag; ci.status = ws.status;
     ci.tokens = tokens_out; ci.frames = frames_out; ci.durs = durs_out; ci.logits = logit_out; ci.logps = e->logp_out;
     ci.cap = cap; ci.stats = ws.stats;
     ci.p_top = res_whole(pl.bf != 0, pl.cls) ? nullptr : ws.top;
     HIP_TRY(launch_encoder_projection(enc_out, enc_len, enc_weights(e), ws.P, B, T, d.F, d.J,
                                       is_bf16_arith(e->wt), ci, stream));
     e->last_B = B; e->last_used.clear(); e->last_ws = ws; e->last_resident = true;
+    if (pl.solo) {
+        // (its work-groups wait for nobody: in no order with other decodes)
+        SoloParams p{};
+        p.H = d.H; p.J = d.J; p.V1 = d.V1; p.NOUT = e->NOUT; p.blank = d.blank;
+        p.tdt = variant == kTdtLabelLooping;
+        p.D = p.tdt ? d.D : 0;
+        p.VT = e->multi_blank ? e->NOUT : d.V1;
+        for (int i = 0; i < kMaxDur; ++i) p.durations[i] = e->durations[i];
+        p.B = B; p.T = T; p.S = S; p.cap = cap;
+        p.enc_len = enc_len; p.P = ws.P; p.w = e->res_w.as<float4>();
+        p.T0 = e->T0.as<float>(); p.b_pred = e->b_pred.as<float>(); p.b_out = e->b_out.as<float>();
+        p.tokens = tokens_out; p.tok_len = tok_len_out; p.frames = frames_out; p.durs = durs_out; p.logits = logit_out; p.logps = e->logp_out;
+        p.done = e->done; p.status = ws.status; p.stats = ws.stats; p.n_records = pl.n_teams;
+        HIP_TRY(launch_solo(p, stream));
+        e->timed = true;
+        return RNNT_OK;
+    }
     const int launch_rows = kResList * pl.n_teams;
     const int rc = in_launch_order(stream, [&](bool plain) -> int {
         for (int off = 0; off < B; off += launch_rows) {
@@ -1178,7 +1209,7 @@ int rnnt_label_looping_decode_noalloc(rnnt_engine *eng, const float *enc_out, co
         size_t off = 0;
         auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
         const size_t o_P = take((size_t)B * T * eng->d.J * sizeof(float));
-        const size_t o_x = take((size_t)resident_buf(pl.kind, pl.cls).bytes * pl.n_teams);
+        const size_t o_x = take(pl.solo ? 0 : (size_t)resident_buf(pl.kind, pl.cls).bytes * pl.n_teams);
         const size_t o_f = take((size_t)pl.n_xcd * 32 * sizeof(unsigned));
         const size_t o_s = take((size_t)pl.n_teams * kStatStride * sizeof(long long));
         const size_t o_a = take(sizeof(unsigned)), o_st = take(sizeof(int));
@@ -1285,7 +1316,7 @@ int rnnt_engine_stats(rnnt_engine *eng, rnnt_stats *out)
         int slots, la;
         resident_rows(pl, std::min(eng->last_B, kResList * pl.n_teams), &slots, &la);
         out->n_teams = pl.n_teams;
-        out->team_size = res_team(pl.cls);
+        out->team_size = pl.solo ? 1 : res_team(pl.cls);
         out->joint_groups = 1;
         out->lookahead = la;
         out->search_steps = 1;

@@ -71,6 +71,7 @@ struct ResidentPlan {
     int units;            // LSTM units per work-group
     int jgroups;          // groups of 4 columns of the prediction-side projection per work-group
     int nout_m, n_tail;   // joint output columns on the matrix instruction, and the few after them (one per work-group)
+    int solo;             // a model for the kernel of one work-group per utterance (solo.h): n_teams work-groups, and nothing else of this
 };
 
 struct ResidentParams {

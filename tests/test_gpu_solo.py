@@ -1,0 +1,96 @@
+"""The decode kernel of one work-group per utterance: the narrowest and widest models it takes, one and two pairs of column
+tiles, more utterances than work-groups, frames that go round its ring of 128, skips over whole chunks of them, and every
+output, against the oracle."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import synth
+from test_gpu_parity import check, pkg  # noqa: F401  (pkg: fixture)
+from test_gpu_resident import model_inputs
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+# (H, J, V1): outputs that just fill two and four tiles of 16 and one more or less, with the durations or big blanks
+SHAPES = [(4, 4, 2), (64, 64, 17), (60, 64, 28), (64, 60, 29), (8, 52, 32), (64, 64, 33), (36, 64, 60), (64, 64, 64)]
+
+
+@pytest.mark.parametrize("H,J,V1", SHAPES)
+@pytest.mark.parametrize("extra", [{}, dict(durations=(0, 1, 3, 90)), dict(big_blanks=(2, 70, 300, 5))])
+def test_shapes_and_decoders(pkg, H, J, V1, extra):  # noqa: F811
+    if extra and V1 > 60:
+        V1 = 60
+    for B, T in ((1, 3), (7, 131), (300, 12)):
+        w = model_inputs(H, J, V1, 1, B=B, T=T, seed=H + J + V1 + B, **extra)
+        eng = pkg.Engine(w.model, w.B, w.T)
+        _, _, stats = check(pkg, w, w.variant, f"solo {H}/{J}/{V1} {extra} {B}", engine=eng, logp=True)
+        assert stats["team_size"] == 1
+        if not extra:
+            check(pkg, w, "frame", f"solo {H}/{J}/{V1} {B}", engine=eng)
+        eng.close()
+
+
+@pytest.mark.parametrize("T", [63, 64, 65, 127, 128, 129, 400])
+@pytest.mark.parametrize("extra", [{}, dict(durations=(0, 1, 49, 64, 128)), dict(big_blanks=(15, 16, 17, 65))])
+def test_frames_in_the_ring(pkg, T, extra):  # noqa: F811
+    """Mostly blank frames, so that steps move on by sixteen; every length around a chunk's end."""
+    w = model_inputs(64, 64, 20, 1, B=9, T=T, seed=T, F=64, **extra)
+    want = 60.0 * np.maximum(w.model.w_out[w.model.dims.blank].astype(np.float64), 0.0) - w.model.b_enc
+    blank = np.linalg.lstsq(w.model.w_enc.astype(np.float64), want, rcond=None)[0].astype(np.float32)
+    g = np.random.default_rng(T)
+    x = np.where(g.random((9, T, 1)) < 0.1, w.enc_out, blank[None, None]).astype(np.float32)
+    w = dataclasses.replace(w, enc_out=x, enc_len=np.array([T, T - 1, T - 2, 0, 1, 16, 17, T // 2, min(T, 65)], dtype=np.int32))
+    eng = pkg.Engine(w.model, w.B, w.T)
+    check(pkg, w, w.variant, f"ring {T} {extra}", engine=eng, logp=True)
+    eng.close()
+
+
+def test_what_a_call_leaves(pkg):  # noqa: F811
+    """Rows that are too short for their labels, lengths out of range, flags, the entry point without allocations, a smaller
+    call after a larger one, a replayed graph, and weights that are not finite."""
+    w = model_inputs(64, 64, 17, 1, B=40, T=30, seed=5)
+    eng = pkg.Engine(w.model, w.B, w.T)
+    ref, got, _ = check(pkg, w, "label", "solo", engine=eng)
+    enc, ln = torch.from_numpy(w.enc_out).cuda(), torch.from_numpy(w.enc_len.astype(np.int32)).cuda()
+    want = eng.decode("label", enc, ln, 4)
+    want = {k: v.cpu().numpy() for k, v in want.items()}
+    other = eng.decode("label_noalloc", enc, ln, 4)
+    assert all(np.array_equal(other[k].cpu().numpy(), want[k]) for k in want)
+    small = eng.decode("label", enc[:3].contiguous(), ln[:3].contiguous(), 4)
+    n = small["tokens"].shape[1]
+    assert np.array_equal(small["tokens"].cpu().numpy(), want["tokens"][:3, :n]) and eng.stats()["joint_samples"] > 0
+    # out of range lengths, and room for two labels a row
+    bad = ln.clone()
+    bad[0], bad[1] = -3, 31
+    tokens = torch.full((40, 2), 7, dtype=torch.int32, device="cuda")
+    count = torch.zeros(40, dtype=torch.int32, device="cuda")
+    done = torch.zeros(40, dtype=torch.int32, device="cuda")
+    pkg.rnnt_engine_set_done_flags(eng.handle, done)
+    pkg.rnnt_label_looping_decode(eng.handle, enc, bad, 40, 30, 4, tokens, count, 2,
+                                  stream=torch.cuda.current_stream().cuda_stream)
+    assert eng.status() == 3 and int(done.sum()) == 40
+    full = eng.decode("label", enc, bad.clamp(0, 30), 4)
+    assert torch.equal(count, full["tok_len"]) and torch.equal(tokens, full["tokens"][:, :2])
+    pkg.rnnt_engine_set_done_flags(eng.handle, None)
+    # a captured call
+    out = {k: torch.from_numpy(v).cuda() for k, v in want.items()}
+    stream = torch.cuda.Stream()
+    cap = out["tokens"].shape[1]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        pkg.rnnt_label_looping_decode(eng.handle, enc, ln, 40, 30, 4, out["tokens"], out["tok_len"], cap, out["frames"],
+                                      out["logits"], stream=torch.cuda.current_stream().cuda_stream)
+    for i in range(3):
+        for v in out.values():
+            v.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(np.array_equal(out[k].cpu().numpy(), want[k]) for k in ("tokens", "tok_len", "frames", "logits")), i
+    eng.close()
+    w.model.w_out[3, 5] = np.inf
+    eng = pkg.Engine(w.model, w.B, w.T)
+    eng.decode("label", enc, ln, 4)
+    assert eng.stats()["team_size"] != 1
+    eng.close()
