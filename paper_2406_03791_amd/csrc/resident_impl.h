@@ -872,8 +872,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     }
     const int u0 = x.rank * p.pl.units, nu = max(0, min(p.pl.units, p.H - u0));
     const int g0 = x.rank * p.pl.jgroups, njg = max(0, min(p.pl.jgroups, (p.J >> 2) - g0));
-    const bool has_tail = x.rank < p.pl.n_tail;      // a column of the tail, with column tile 0
-    const int tcol = p.pl.nout_m + x.rank;
+    // A column of the tail: with two tiles of samples for those of one, if there are ranks enough, so that the others wait for half
+    // of what it takes beside the 32 columns of every work-group (0.45 us a step of two tiles; bfloat16 mode 0.39.  32
+    // utterances 1366 us with all samples in one work-group, 1345 with two, bfloat16 mode 867 and 844).
+    const bool share = NMT == 2 && p.pl.n_tail * 2 <= TS;
+    const int tcol = p.pl.nout_m + (share ? x.rank >> 1 : x.rank);
+    const bool has_tail = tcol < p.pl.nout_m + p.pl.n_tail;
+    const unsigned tails = !has_tail ? 0u : share ? 1u << (x.rank & 1) : 3u;      // the tiles, a bit each
+    auto tail_for = [&](int tile) { return NMT == 1 ? has_tail : (tails >> tile & 1u) != 0u; };
     const int n_tok = min(p.VT, p.pl.nout_m) - x.rank * 32;      // token columns of this work-group's tiles
     const bool dur_cols = p.tdt && p.VT < p.pl.nout_m && x.rank * 32 + 32 > p.VT;      // they hold duration columns
     if (tid0 < kResUnits * 4) rc.b1[tid0] = (NL > 1 && tid0 < nu * 4) ? p.bias_l[((long long)p.H + u0) * 4 + tid0] : 0.f;
@@ -888,7 +894,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     if (tid0 < 20) rc.sp[tid0] = tid0 < njg * 4 ? p.s_pred[g0 * 4 + tid0] : 0.f;
     if (has_tail)
         for (int i = tid0; i < ROW; i += kResThreads) {
-            const float w = p.w_tail[(long long)x.rank * ROW + i];
+            const float w = p.w_tail[(long long)(tcol - p.pl.nout_m) * ROW + i];
             // (rows of 16-bit values: high parts, low parts, zeros; or bf16 values, zeros; or rows of fp32 values, zeros)
             unsigned short *row = reinterpret_cast<unsigned short *>(lds + lo.tail);
             unsigned high = __float_as_uint(w) >> 16, low = 0;
@@ -1284,8 +1290,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             auto q_at = [&](int of, int i) { return of + i * 128 - (i < NF ? 0 : g * 16); };
             auto at = [&](int a) { return *reinterpret_cast<const float4 *>(lds + a); };
             unsigned again = 0;              // samples whose operand has too few bits in parts, or none
-            auto output = [&](auto tail_) {
-                constexpr bool TAIL = decltype(tail_)::value;
+            auto output = [&](auto tails_) {
+                constexpr unsigned TAILS = decltype(tails_)::value;
                 const r4f zero = {0.f, 0.f, 0.f, 0.f};
                 r4f big[2], tb;
                 float top = 0.f;
@@ -1296,12 +1302,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     if (b % NB == 0) { place_lane(); qo = q_of(mt); }
                     const int pa = frame_at(mt, i), qa = q_at(qo, i);
                     pv[0] = at(pa); qv[0] = at(qa);
-                    if (i < NF && !TAIL) { pv[1] = at(pa ^ 16); qv[1] = at(qa + 16); }
+                    if (i < NF && !(TAILS >> mt & 1u)) { pv[1] = at(pa ^ 16); qv[1] = at(qa + 16); }
                 };
                 fetch(0);
                 static_for<0, NB * NT>([&](auto b_) {
                     constexpr int b = decltype(b_)::value, mt = b / NB, i = block_of(b % NB);
-                    constexpr bool FULL = i < NF;
+                    constexpr bool FULL = i < NF, TAIL = (TAILS >> mt & 1u) != 0u;
                     if constexpr (b % NB == 0) { big[0] = big[1] = tb = zero; top = 0.f; }
                     unsigned zh[4], zl[4];
                     if constexpr (FULL && TAIL) { pv[1] = at(frame_at(mt, i) ^ 16); qv[1] = at(q_at(qo, i) + 16); }      // (registers)
@@ -1363,8 +1369,15 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     }
                 });
             };
-            if (has_tail) output(std::true_type());
-            else output(std::false_type());
+            if constexpr (NT == 1) {
+                if (tail_for(0)) output(std::integral_constant<unsigned, 1>());
+                else output(std::integral_constant<unsigned, 0>());
+            } else {
+                if (tails == 0u) output(std::integral_constant<unsigned, 0>());
+                else if (tails == 1u) output(std::integral_constant<unsigned, 1>());
+                else if (tails == 2u) output(std::integral_constant<unsigned, 2>());
+                else output(std::integral_constant<unsigned, 3>());
+            }
             if constexpr (!BF && !WHOLE) {
                 // Samples whose operand parts do not hold in the wave's eighth, far below the bound or infinite, are computed once more
                 // as fp32 products (the weights' parts added up again; two tiles of samples 6.5 us).  The lane's e-th value of
@@ -1398,14 +1411,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                                 for (int e = 0; e < N; ++e) sum[c] = __builtin_amdgcn_mfma_f32_16x16x4f32((float)high[e] + (float)low[e], z[e], sum[c], 0, 0, 0);
                                 ordered();
                             }
-                            if (has_tail) {
+                            if (tail_for(mt)) {
                                 const _Float16 *w = reinterpret_cast<const _Float16 *>(lds + lo.tail) + x.wave * (NH * 16) + k * 32 + g * N;
 #pragma unroll
                                 for (int e = 0; e < N; ++e) tail = __builtin_amdgcn_mfma_f32_16x16x4f32(m16 == 0 ? (float)w[e] + (float)w[ROW + e] : 0.f, z[e], tail, 0, 0, 0);
                             }
                         });
                         if ((again >> (mt * 16 + m16) & 1u) != 0u) {
-                            if (has_tail && g == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = tail[0];
+                            if (tail_for(mt) && g == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = tail[0];
 #pragma unroll
                             for (int c = 0; c < 2; ++c)
                                 *reinterpret_cast<r4f *>(part + ((x.wave * NT + mt) * 16 + m16) * kResSumRow + c * 16 + g * 4) = sum[c];
@@ -1427,7 +1440,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 static_assert(kResWaves == 8, "eight lanes add the waves' sums of the tail column");
                 float tw = 0.f, back = 1.f;
                 if constexpr (!BF && !WHOLE) back = inverse_power(rc.scale[lane_const >> 16 & 3]);
-                if (has_tail) tw = tpart[((tid & 7) * 2 + (s >> 4)) * 16 + (s & 15)];
+                const bool tail_here = tail_for(x.wave >> 2);          // (a wave has four samples)
+                if (tail_here) tw = tpart[((tid & 7) * 2 + (s >> 4)) * 16 + (s & 15)];
                 const float l0 = (((o[0].x + o[1].x) + (o[2].x + o[3].x)) + ((o[4].x + o[5].x) + (o[6].x + o[7].x))) * scale.x * back + bias.x;
                 const float l1 = (((o[0].y + o[1].y) + (o[2].y + o[3].y)) + ((o[4].y + o[5].y) + (o[6].y + o[7].y))) * scale.y * back + bias.y;
                 const float m0 = col < n_tok ? l0 : -INFINITY, m1 = col + 1 < n_tok ? l1 : -INFINITY;
@@ -1438,7 +1452,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 const int first = hit ? __builtin_ctz(hit) : 0;
                 int ix = hit ? (m0 == m ? gcol : gcol + 1) : 0x7fffffff;
                 float tail = -INFINITY;
-                if (has_tail) {
+                if (tail_here) {
                     tail = lane_sum<8>(tw) * rc.st * back + rc.bt;
                     if (tcol >= p.VT) {
                         if ((tid & 15) == 0) {
@@ -1480,7 +1494,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 const bool lead = (tid & 15) == 0;
                 if (lead) put_mark2(x, ko, bo.key + slot_at(jn + 2, KSLOT));
                 if (lead && p.logps) put_mark(x, ko / 2, bo.lse + slot_at(jn + 2, KSLOT / 2));
-                if (lead && has_tail && tcol >= p.VT) put_mark(x, ds + (unsigned)(tcol - p.VT) * 4u, bo.dur + slot_at(jn + 2, DSLOT));
+                if (lead && tail_for(1) && tcol >= p.VT) put_mark(x, ds + (unsigned)(tcol - p.VT) * 4u, bo.dur + slot_at(jn + 2, DSLOT));
                 if (dur_cols) {
 #pragma unroll
                     for (int c = 0; c < 2; ++c)
