@@ -540,6 +540,20 @@ __device__ __forceinline__ void load_frame(const ResidentParams &p, const RCtx &
     const int lane = lane_id(), j4 = p.J >> 2, k4 = lane ^ (s & 15);
     const char *src = reinterpret_cast<const char *>(p.P + (long long)row * p.J);
     const unsigned m = (unsigned)__builtin_amdgcn_readfirstlane((int)(lds_p + (unsigned)(s * ROW * 4)));
+    // a row that fills its place: all of it, with no branch around a load
+    if (j4 == ROW / 4) {
+        const unsigned off = (unsigned)k4 * 16u;
+        constexpr int FULL = ROW / 256;
+        if constexpr (FULL == 2)
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\tglobal_load_lds_dwordx4 %0, %2 offset:1024\n\t"
+                         "s_mov_b32 exec_hi, 0\n\tglobal_load_lds_dwordx4 %0, %2 offset:2048\n\ts_mov_b32 exec_hi, -1" :: "v"(off), "s"(m), "s"(src) : "memory");
+        else if constexpr (FULL == 1)
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\t"
+                         "s_mov_b32 exec_hi, 0\n\tglobal_load_lds_dwordx4 %0, %2 offset:1024\n\ts_mov_b32 exec_hi, -1" :: "v"(off), "s"(m), "s"(src) : "memory");
+        else
+            asm volatile("s_mov_b32 m0, %1\n\ts_mov_b32 exec_hi, 0\n\tglobal_load_lds_dwordx4 %0, %2\n\ts_mov_b32 exec_hi, -1" :: "v"(off), "s"(m), "s"(src) : "memory");
+        return;
+    }
     static_for<0, (ROW / 4 + 63) / 64>([&](auto u_) {
         constexpr int u = decltype(u_)::value;
         const char *from = src;
@@ -999,6 +1013,22 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         fresh = __ballot(pidx >= 0 && pidx != was);
         n_samples += __popcll(__ballot(pidx >= 0));
     };
+    // Loads the samples' frames that are new, of samples `from`, `from` + `step` and so on; `of`: the same ones as bits.  The
+    // waves that do it beside the cells are the last to look for the hidden vector, so an instruction here is one of the
+    // step: with a branch around every load and a look at every sample 32 utterances took 1331, 1357 and 1177 us (three
+    // draws), with neither 1309, 1335 and 1155, TDT 988, 968, 987 and 962, 943, 958.  (One tile, where a wave has few to look at:
+    // over the bits 536 us for one utterance, over the samples 527.)
+    auto load_frames = [&](unsigned of, int from, int step) {
+        if constexpr (NMT == 1) {
+            for (int s = from; s < part_samples(); s += step)
+                if (fresh >> s & 1) load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
+        } else {
+            for (unsigned m = (unsigned)fresh & of; m != 0u; m &= m - 1u) {
+                const int s = __builtin_ctz(m);
+                load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
+            }
+        }
+    };
     // Rows that want one get the next utterances of the list.  (Control state is by row: every lane works on
     // row lane / LR % R, and the first of LR lanes below 16 stands for its row in ballots.)
     constexpr unsigned long long LEADS = 0x1111ull;
@@ -1135,8 +1165,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             } else {
                 // The frames of the joint step, by the waves that have the least to do here.  A wave's loads return in
                 // order, so these waves see the hidden vector when their frames are there: at about the time it comes.
-                for (int s = x.wave - 5; s < part_samples(); s += kResWaves - 5)
-                    if (fresh >> s & 1) load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
+                load_frames(0x49249249u << (x.wave - 5), x.wave - 5, kResWaves - 5);
                 x1.receive_from(p, x, bo.h[0] + slot_at(n, VSLOT), h4);
                 asm volatile("" :: "v"(t0), "v"(pre[0][0]), "v"(pre[0][1]), "v"(pre[0][2]), "v"(pre[0][3]));
             }
@@ -1251,8 +1280,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             }
             RES_MARK(9);
         } else {
-            for (int s = x.wave; s < part_samples(); s += kResWaves)
-                if (fresh >> s & 1) load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
+            load_frames(0x01010101u << x.wave, x.wave, kResWaves);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
             RES_MARK(10);
