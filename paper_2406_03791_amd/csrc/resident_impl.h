@@ -460,7 +460,7 @@ __device__ __forceinline__ void stage(const RegW<res_tile_regs(BF, CLS, T)> &w, 
 template <int R>
 __device__ __forceinline__ float stage_sum(const float *sums, int blk, int lane)
 {
-    const float *s = sums + ((lane / 4) & (R - 1)) * kResStageRow + (blk * 4 + (lane >> 4)) * 4 + (lane & 3);
+    const float *s = sums + ((unsigned)lane / 4 & (R - 1)) * kResStageRow + (blk * 4 + ((unsigned)lane >> 4)) * 4 + (lane & 3);
     float o[kResWaves];
 #pragma unroll
     for (int w = 0; w < kResWaves; ++w) o[w] = s[w * R * kResStageRow];
@@ -922,7 +922,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     struct Place { int row, j, lu, gu; bool ok; };
     auto place_of = [&](int lane) {
         Place l;
-        l.row = (lane / LR) & (R - 1); l.j = lane & (LR - 1);
+        l.row = (int)((unsigned)lane / LR) & (R - 1); l.j = lane & (LR - 1);
         l.lu = x.wave * 4 + (lane >> 4);
         l.ok = l.lu < nu && l.j == 0 && l.row < p.slots;      // the lanes that publish it
         l.gu = min(u0 + l.lu, p.H - 1);
@@ -949,7 +949,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // committed vector (kResident2Pair: in LDS, where the others have their recurrent sums; the weights need the registers)
     // and, kResident2Pair, of the last step's candidate, a word from every quarter of K as far as it is there, kMark where not
     float *state = reinterpret_cast<float *>(lds + lo.state);
-    auto stored = [&](int field) { return state + (field * 5 + x.wave) * 64 + lane_id(); };
+    auto stored = [&]() { return state + x.wave * 64 + lane_id(); };               // (fields 5 * 64 floats apart)
+    constexpr int FIELD = 5 * 64;
     float cs[NL], cc[NL], ps[NL];
     unsigned pre[NL][kResQuarters];
 #pragma unroll
@@ -1040,7 +1041,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         if (got) { b = rc.list_b[at]; len = rc.list_len[at]; }
         // (one place for all waves: they write the same, between the same barriers)
         if constexpr (!BF && !WHOLE)
-            if (got) rc.scale[(lane / LR) & (R - 1)] = list_scale[at];
+            if (got) rc.scale[(int)((unsigned)lane / LR) & (R - 1)] = list_scale[at];
         rows.next = next + __popcll(m);
         return got;
     };
@@ -1048,7 +1049,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     bool any_active, need_pred, later = false;
     {
         int b = 0, len = 0;
-        const int r = (lane0 / LR) & (R - 1);
+        const int r = (int)((unsigned)lane0 / LR) & (R - 1);
         const bool got = refill(lane0, r < p.slots, b, len);
         if (got) { rows.b[r] = b; rows.s[r].len = len; }
         const unsigned long long m = __ballot(got) & LEADS;
@@ -1106,10 +1107,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             if (PAIR && n > 1) wait_pre(n - 1, 0);
             RES_MARK(0);
             if constexpr (PAIR) {
+                const float *from = stored();
 #pragma unroll
                 for (int l = 0; l < NL; ++l) {
                     cs[l] = cc[l] = ps[l] = 0.f;
-                    if (has_cells) { cs[l] = *stored(l * 3); cc[l] = *stored(l * 3 + 1); ps[l] = *stored(l * 3 + 2); }
+                    if (has_cells) { cs[l] = from[l * 3 * FIELD]; cc[l] = from[(l * 3 + 1) * FIELD]; ps[l] = from[(l * 3 + 2) * FIELD]; }
                 }
             }
             // rows that emitted take their candidate state, fresh rows start from zero (kResident2: the second
@@ -1135,7 +1137,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             unsigned word = 0;
             auto publish_h = [&](int layer, const Place &l, float h) {
                 word = hidden_word<BF>(h);
-                if (l.ok) put(x, (unsigned)l.row * VROW + (unsigned)l.gu * 4u, bo.h[layer] + slot_at(n, VSLOT), bo.h[layer] + slot_at(n + 2, VSLOT), word);
+                // (l.gu is u0 + l.lu where a lane publishes; of one layer's models the small one was 1.4 % slower without its limit)
+                if (l.ok) put(x, (unsigned)l.row * VROW + (unsigned)(NL > 1 ? u0 + l.lu : l.gu) * 4u, bo.h[layer] + slot_at(n, VSLOT), bo.h[layer] + slot_at(n + 2, VSLOT), word);
             };
             // The same to the helpers, when the team's own vector is there: loads and stores of a wave are counted in one
             // order, so polls behind these stores wait for the memory side to take them (label looping of 32 utterances 1470 us with the
@@ -1143,7 +1146,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             // (No condition around the stores, or what was loaded before them would be waited for together with them.)
             auto forward_h = [&](int layer) {
                 const Place l = place_of(lane_id());
-                const unsigned o = has_cells && l.ok ? (unsigned)l.row * VROW + (unsigned)l.gu * 4u : 0x80000000u;
+                const unsigned o = has_cells && l.ok ? (unsigned)l.row * VROW + (unsigned)(u0 + l.lu) * 4u : 0x80000000u;
                 put_far(x, o, bo.hr[layer] + slot_at(n, VSLOT), word);
                 put_far(x, o, bo.hr[layer] + slot_at(n + 2, VSLOT), kMark);
             };
@@ -1158,10 +1161,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 float h;
                 cell(ps[0] + t0, l.j, cs[0], cc[0], h);
                 publish_h(0, l, h);
-                if constexpr (PAIR) { *stored(0) = cs[0]; *stored(1) = cc[0]; *stored(2) = ps[0]; }
+                if constexpr (PAIR) { float *to = stored(); to[0] = cs[0]; to[FIELD] = cc[0]; to[2 * FIELD] = ps[0]; }
                 if constexpr (NREC > 1) commit(1);
                 if (NMT == 2 && later) {
-                    const int lane = lane_id(), r = (lane / LR) & (R - 1);
+                    const int lane = lane_id(), r = (int)((unsigned)lane / LR) & (R - 1);
                     const RRow o = rows.s[r];
                     set_up_samples(lane, o.t, rows.m[r], rows.b[r], o.len);
                     later = false;
@@ -1193,7 +1196,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     float h;
                     cell(sum_of(sums_ih, rc.s1) + (ps[1] + rc.b1[l.lu * 4 + l.j]), l.j, cs[1], cc[1], h);
                     publish_h(1, l, h);
-                    if constexpr (PAIR) { *stored(3) = cs[1]; *stored(4) = cc[1]; *stored(5) = ps[1]; }
+                    if constexpr (PAIR) { float *to = stored() + 3 * FIELD; to[0] = cs[1]; to[FIELD] = cc[1]; to[2 * FIELD] = ps[1]; }
                 }
                 RES_MARK(4);
                 // (while the hand-over is on its way) the recurrent part of the next step's first layer
@@ -1218,6 +1221,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     x1.set(v, lane);
                 } else {
                     RES_MARK(5);
+                    // A poll that comes too early is repeated after 0.25 us, and slows down what it waits for: the first one
+                    // 320 cycles on.  (32 utterances 1292, 1316 and 1144 us without the pause, three draws, 1266, 1285, 1120 with 128
+                    // cycles, 1263, 1281, 1115 with 192, 1256, 1277, 1108 with 320, 1267, 1285, 1116 with 448; one utterance 525, 522, 521, 522, 522.
+                    // Pauses before the other polls: no gain, there is work in between.)
+                    __builtin_amdgcn_s_sleep(5);
                     x1.receive_from(p, x, bo.h[1] + slot_at(n, VSLOT), h4);
                     if (PAIR) forward_h(1);
                 }
@@ -1229,7 +1237,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             __syncthreads();
             {
                 // LR adjacent threads per value (group of four columns, column, row), R / 2 waves' sums each
-                const int tid = (x.wave * 64 + lane_id()), col = tid >> 4, r = (tid / LR) & (R - 1);
+                const int tid = (x.wave * 64 + lane_id()), col = tid >> 4, r = (int)((unsigned)tid / LR) & (R - 1);
                 if (col < njg * 4) {
                     const float *v = sums_pr + ((tid & (LR - 1)) * (R / 2) * R + r) * kResSumRow + col;
                     float o = v[0];
@@ -1611,7 +1619,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         }
         // ---- loop control: every wave for itself, lane = row (outputs: the last wave, which has the least to do next) ------
         {
-            const int lane = lane_id(), r = (lane / LR) & (R - 1);
+            const int lane = lane_id(), r = (int)((unsigned)lane / LR) & (R - 1);
             RRow w = rows.s[r];
             int b = rows.b[r], m = rows.m[r];
             // (on its way during the rest: the helpers' results take 0.85 us, and what is left of the step 0.75)
@@ -1753,7 +1761,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         // their second loop costs more registers than there are (bfloat16 mode: twelve spilled, 4 to 6 % of a call).
         std::integral_constant<int, 1> one_tile;
         auto changed_to = [&](auto nt_) {
-            const int lane = lane_id(), r = (lane / LR) & (R - 1);
+            const int lane = lane_id(), r = (int)((unsigned)lane / LR) & (R - 1);
             const RRow w = rows.s[r];
             lay_out(nt_, lane, part_rows);
             if (lane < 16 && (lane & (LR - 1)) == 0) {
