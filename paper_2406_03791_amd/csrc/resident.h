@@ -45,6 +45,13 @@ RNNT_HD constexpr int res_tile_at(bool bf, int cls, int T, int kb, int t, int pa
                                     : res_halves(cls) / 2 * T * res_parts(bf) * 4 + (t * res_parts(bf) + part) * 2;
 }
 
+// Place of register `reg` of a run of n in its image of n * 64 words: groups of four, the lanes' one after the other, as they are loaded
+// (n % 4 == 2: two groups of two at the end).
+RNNT_HD constexpr int res_place(int n, int reg, int lane)
+{
+    return reg < n / 4 * 4 ? reg / 4 * 256 + lane * 4 + reg % 4 : n / 4 * 256 + lane * 2 + reg % 4;
+}
+
 // Helpers of kResident2Pair: a work-group's quarter of K in whole blocks, and the registers of a wave's three tiles of 16 outputs.
 constexpr int kResQuarters = 4;
 RNNT_HD constexpr int res_help_blocks(int cls) { return res_row(cls) / (32 * kResQuarters); }
@@ -87,7 +94,7 @@ struct ResidentParams {
     int *tokens, *tok_len, *frames, *durs;
     float *logits, *logps;
     int *done;
-    const float *w;       // packed registers of the (main) work-groups: [rank][wave][register][lane]
+    const float *w;       // packed registers of the (main) work-groups: [rank][wave], runs of registers as in res_place
     const float *w_help;  // the same of the helpers (kResident2Pair), layer by layer
     const float *w_tail;  // [n_tail][res_row(cls)], scaled as the packed output columns
     // fp32: what sums of the scaled weights of an output are multiplied by; LSTM matrices [H][gate]
@@ -173,7 +180,7 @@ static_assert(resident_lds(kResident1, 0, 2).bytes + kResCtl <= 160 * 1024 && re
               resident_lds(kResident2Pair, 0, 2).bytes + kResCtl <= 160 * 1024, "the largest layouts and the control block fit the LDS");
 
 // The model's matrices on the device (rows as in the model), and where their packed forms go: register images of the
-// teams' and the helpers' work-groups, [rank][wave][register][lane]; tail columns; what sums are multiplied by; the
+// teams' and the helpers' work-groups, [rank][wave][runs of registers, see res_place]; tail columns; what sums are multiplied by; the
 // scales of the rows, in the order of these, and two words, zero before: not every value is finite, and the largest
 // value of q, from above (a float's bits; both fp32 only).
 struct ResidentWeights { int H, J, L; const float *w_hh[2], *w_ih1, *w_pred, *b_pred, *w_out; };

@@ -115,24 +115,43 @@ template <int N> struct RegW {
     r4f q[N / 4];
     r2f rest;                         // N % 4 == 2
 };
-// Loads registers [first, first + N) of the wave's packed run.  The empty asm makes each value
-// opaque, so that it stays in its registers and is never read from memory again.
-template <int N>
+// A wave's loads of weights all go out before the first is waited for, sixteen bytes at a time: 8.0 us of a launch of the largest
+// class (12.4 in single words, 32 in flight).
+// PAIRS: eight bytes at a time, as relaxed atomics that are not put together again.  For bf16 with two recurrent layers, whose
+// registers are full: groups of four from one load left it 8 that are written out and read back in every step (one utterance:
+// 2.5 % of a call).
+__device__ __forceinline__ float load_one(const float *at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT); }
+__device__ __forceinline__ r2f load_pair(const float *at)
+{
+    return __builtin_bit_cast(r2f, __hip_atomic_load(reinterpret_cast<const long long *>(at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT));
+}
+// Asks for registers [first, first + N) of the wave's packed run, see res_place.
+template <bool PAIRS, int N>
 __device__ __forceinline__ void load_regs(RegW<N> &r, const float *src, int first, int lane)
 {
     static_assert(N % 2 == 0, "pairs");
-    src += first * 64 + lane;
+    src += first * 64;
 #pragma unroll
-    for (int i0 = 0; i0 < N / 4; i0 += 8) {       // 32 loads in flight
-#pragma unroll
-        for (int i = i0; i < N / 4 && i < i0 + 8; ++i) r.q[i] = (r4f){src[i * 256], src[i * 256 + 64], src[i * 256 + 128], src[i * 256 + 192]};
-#pragma unroll
-        for (int i = i0; i < N / 4 && i < i0 + 8; ++i) asm volatile("" : "+v"(r.q[i]));
+    for (int i = 0; i < N / 4; ++i) {
+        const float *at = src + i * 256 + lane * 4;
+        if constexpr (PAIRS) {
+            const r2f a = load_pair(at), b = load_pair(at + 2);
+            r.q[i] = (r4f){a.x, a.y, b.x, b.y};
+        } else r.q[i] = *reinterpret_cast<const r4f *>(at);
     }
     if (N % 4) {
-        r.rest = (r2f){src[N / 4 * 256], src[N / 4 * 256 + 64]};
-        asm volatile("" : "+v"(r.rest));
+        const float *at = src + N / 4 * 256 + lane * 2;
+        if constexpr (PAIRS) r.rest = (r2f){load_one(at), load_one(at + 1)};
+        else r.rest = *reinterpret_cast<const r2f *>(at);
     }
+}
+// The empty asm makes each value opaque, so that it stays in its registers and is never read from memory again.
+template <int N>
+__device__ __forceinline__ void keep_regs(RegW<N> &r)
+{
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i) asm volatile("" : "+v"(r.q[i]));
+    if (N % 4) asm volatile("" : "+v"(r.rest));
 }
 
 // The lane's number, worked out anew wherever it is used: a register that holds it, or anything that
@@ -698,8 +717,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         const int quarter = x.rank & 3, first_unit = (x.rank >> 2) * 80, tile0 = x.wave < 4 ? x.wave * 3 : x.wave * 2 + 4;
         const bool third = x.wave < 4;
         RegW<HREGS> w;
-        load_regs(w, p.w_help + ((long long)(my_layer * TS + x.rank) * kResWaves + x.wave) * HREGS * 64, 0, lane0);
         announce();
+        load_regs<false>(w, p.w_help + ((long long)(my_layer * TS + x.rank) * kResWaves + x.wave) * HREGS * 64, 0, lane0);
+        keep_regs(w);
         unsigned live = 0;
 #pragma unroll
         for (int i = 0; i < kResServed; ++i)
@@ -845,44 +865,20 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     }
 
     // ---- the chain's work-groups ---------------------------------------------------------------
-    RegW<LREGS> w_hh[NREC > 0 ? NREC : 1], w_ih;
-    RegW<res_pred_regs(BF, CLS)> w_pr;
-    RegW<res_joint_regs(BF, CLS)> w_ou;
-    {
-        const float *src = p.w + (long long)(x.rank * kResWaves + x.wave) * res_main_regs(KIND, BF, CLS) * 64;
-        int first = 0;
-#pragma unroll
-        for (int l = 0; l < NREC; ++l) { load_regs(w_hh[l], src, first, lane0); first += LREGS; }
-        if (NL > 1) { load_regs(w_ih, src, first, lane0); first += LREGS; }
-        load_regs(w_pr, src, first, lane0); first += res_pred_regs(BF, CLS);
-        load_regs(w_ou, src, first, lane0);
-    }
+    announce();
+    // What else is read before the first step comes first, in three trips to memory (lengths and small tables, scales, weights).
+    // The ranks of the utterances are worked out from the LDS: each of 32 lengths read by one lane alone, one after the other,
+    // and tables a piece at a time took 11 us, this 4.6; up to the first step 16 us in place of 27 (32 utterances, fp32,
+    // two layers).  With the weights asked for before all that, the same call took 0.6 % longer.
     // fp32: what the joint's operands of an utterance are multiplied by, see joint_scale
     float *list_scale = reinterpret_cast<float *>(lds + lo.scale);
-    // utterances of the team: ranked by length (longest first, ties by index), dealt in serpentine
-    // order; empty ones are complete from the start
+    // (the lengths, in the frames' place)
+    static_assert(kResList * (CLS == 0 ? 8 : CLS == 1 ? 16 : 32) * 4 <= 32 * ROW * 4, "the lengths of a launch fit the places of 32 frames");
+    int *lengths = reinterpret_cast<int *>(lds + lo.p);
     for (int b = tid0; b < p.B; b += kResThreads) {
         const int raw = p.enc_len[b];
         if (raw < 0 || raw > p.T) rc.st_clamped = 1;
-        const int len = min(max(raw, 0), p.T);
-        int pos = 0;
-        for (int o = 0; o < p.B; ++o) {
-            const int l2 = min(max(p.enc_len[o], 0), p.T);
-            pos += (l2 > len || (l2 == len && o < b)) ? 1 : 0;
-        }
-        const int q = pos / n_teams, m = pos - q * n_teams;
-        if (((q & 1) ? n_teams - 1 - m : m) == team) {
-            rc.list_b[q] = (unsigned short)b; rc.list_len[q] = len;
-            if constexpr (!BF && !WHOLE) {
-                const TopWord *words = p.p_top + (long long)b * (kTopParts * kTopStride);
-                TopWord top = 0;
-#pragma unroll 4                 // (the weights have the registers)
-                for (int i = 0; i < kTopParts; ++i) top = max(top, words[i * kTopStride]);
-                list_scale[q] = joint_scale(top, p.q_bound);
-            }
-            if (len > 0) atomicAdd(&rc.n_list, 1);       // the empty ones are the last of the list
-            else if (x.rank == 0) res_finish_row(b, 0);
-        }
+        lengths[b] = min(max(raw, 0), p.T);
     }
     const int u0 = x.rank * p.pl.units, nu = max(0, min(p.pl.units, p.H - u0));
     const int g0 = x.rank * p.pl.jgroups, njg = max(0, min(p.pl.jgroups, (p.J >> 2) - g0));
@@ -896,16 +892,27 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     auto tail_for = [&](int tile) { return NMT == 1 ? has_tail : (tails >> tile & 1u) != 0u; };
     const int n_tok = min(p.VT, p.pl.nout_m) - x.rank * 32;      // token columns of this work-group's tiles
     const bool dur_cols = p.tdt && p.VT < p.pl.nout_m && x.rank * 32 + 32 > p.VT;      // they hold duration columns
-    if (tid0 < kResUnits * 4) rc.b1[tid0] = (NL > 1 && tid0 < nu * 4) ? p.bias_l[((long long)p.H + u0) * 4 + tid0] : 0.f;
-    if (tid0 < 20) rc.bp[tid0] = tid0 < njg * 4 ? p.b_pred[g0 * 4 + tid0] : 0.f;
-    if (tid0 < 32) reinterpret_cast<float *>(rc.bo)[tid0] = x.rank * 32 + tid0 < p.pl.nout_m ? p.b_out[x.rank * 32 + tid0] : 0.f;
-    if (tid0 == 0) rc.bt = has_tail ? p.b_out[tcol] : 0.f;
-    if (tid0 < kResUnits * 4) {
-        const bool mine = tid0 < nu * 4;
-        rc.s1[tid0] = NL > 1 && mine ? p.s_ih[u0 * 4 + tid0] : 0.f;
-        for (int l = 0; l < NREC; ++l) rc.sh[l][tid0] = mine ? p.s_hh[l][u0 * 4 + tid0] : 0.f;
+    {
+        const int at = tid0;
+        const bool gate = at < nu * 4, col = at < njg * 4, out = at < 32 && x.rank * 32 + at < p.pl.nout_m;
+        float b1 = 0.f, s1 = 0.f, sh[NL] = {}, bp = 0.f, sp = 0.f, bo_ = 0.f, so_ = 0.f, bt = 0.f, st = 0.f;
+        if (gate) {
+            if (NL > 1) { b1 = p.bias_l[((long long)p.H + u0) * 4 + at]; s1 = p.s_ih[u0 * 4 + at]; }
+#pragma unroll
+            for (int l = 0; l < NREC; ++l) sh[l] = p.s_hh[l][u0 * 4 + at];
+        }
+        if (col) { bp = p.b_pred[g0 * 4 + at]; sp = p.s_pred[g0 * 4 + at]; }
+        if (out) { bo_ = p.b_out[x.rank * 32 + at]; so_ = p.s_out[x.rank * 32 + at]; }
+        if (at == 0 && has_tail) { bt = p.b_out[tcol]; st = p.s_out[tcol]; }
+        if (at < kResUnits * 4) {
+            rc.b1[at] = b1; rc.s1[at] = s1;
+#pragma unroll
+            for (int l = 0; l < NREC; ++l) rc.sh[l][at] = sh[l];
+        }
+        if (at < 20) { rc.bp[at] = bp; rc.sp[at] = sp; }
+        if (at < 32) { reinterpret_cast<float *>(rc.bo)[at] = bo_; reinterpret_cast<float *>(rc.so)[at] = so_; }
+        if (at == 0) { rc.bt = bt; rc.st = st; }
     }
-    if (tid0 < 20) rc.sp[tid0] = tid0 < njg * 4 ? p.s_pred[g0 * 4 + tid0] : 0.f;
     if (has_tail)
         for (int i = tid0; i < ROW; i += kResThreads) {
             const float w = p.w_tail[(long long)(tcol - p.pl.nout_m) * ROW + i];
@@ -916,6 +923,50 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             if (WHOLE) reinterpret_cast<float *>(row)[i] = w;
             else { row[i] = (unsigned short)high; row[ROW + i] = (unsigned short)low; }
         }
+    __syncthreads();
+    // utterances of the team: ranked by length (longest first, ties by index), dealt in serpentine
+    // order; empty ones are complete from the start
+    for (int b = tid0; b < p.B; b += kResThreads) {
+        const int len = lengths[b];
+        int pos = 0;
+#pragma unroll 8
+        for (int o = 0; o < p.B; ++o) pos += (lengths[o] > len || (lengths[o] == len && o < b)) ? 1 : 0;
+        const int q = pos / n_teams, m = pos - q * n_teams;
+        if (((q & 1) ? n_teams - 1 - m : m) == team) {
+            rc.list_b[q] = (unsigned short)b; rc.list_len[q] = len;
+            if (len > 0) atomicAdd(&rc.n_list, 1);       // the empty ones are the last of the list
+            else if (x.rank == 0) res_finish_row(b, 0);
+        }
+    }
+    __syncthreads();
+    for (int b = tid0; b < p.B; b += kResThreads) lengths[b] = 0;
+    if constexpr (!BF && !WHOLE) {
+        // sixteen lanes to an utterance of the list
+        static_assert(kTopParts == 16, "a word for each of sixteen lanes");
+        for (int q = tid0 >> 4; q < rc.n_list; q += kResThreads / 16) {
+            TopWord top = p.p_top[((long long)rc.list_b[q] * kTopParts + (lane0 & 15)) * kTopStride];
+#pragma unroll
+            for (int i = 1; i < 16; i *= 2) top = max(top, (TopWord)__shfl_xor((long long)top, i));
+            if ((lane0 & 15) == 0) list_scale[q] = joint_scale(top, p.q_bound);
+        }
+    }
+    RegW<LREGS> w_hh[NREC > 0 ? NREC : 1], w_ih;
+    RegW<res_pred_regs(BF, CLS)> w_pr;
+    RegW<res_joint_regs(BF, CLS)> w_ou;
+    {
+        const float *src = p.w + (long long)(x.rank * kResWaves + x.wave) * res_main_regs(KIND, BF, CLS) * 64;
+        int first = 0;
+#pragma unroll
+        for (int l = 0; l < NREC; ++l) { load_regs<KIND == kResident2>(w_hh[l], src, first, lane0); first += LREGS; }
+        if (NL > 1) { load_regs<KIND == kResident2>(w_ih, src, first, lane0); first += LREGS; }
+        load_regs<KIND == kResident2>(w_pr, src, first, lane0); first += res_pred_regs(BF, CLS);
+        load_regs<KIND == kResident2>(w_ou, src, first, lane0);
+#pragma unroll
+        for (int l = 0; l < NREC; ++l) keep_regs(w_hh[l]);
+        if (NL > 1) keep_regs(w_ih);
+        keep_regs(w_pr);
+        keep_regs(w_ou);
+    }
     // What a lane finishes in the LSTM stages, see stage_sum: a row of the team, a unit and a gate.  Worked
     // out where it is used: kept for the whole loop, values like these take the registers that the
     // weights need.
@@ -938,10 +989,6 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     float *sums_rec0 = reinterpret_cast<float *>(lds + lo.rec0), *sums_top = reinterpret_cast<float *>(lds + lo.rec);
 
     if (!BF && !WHOLE && p.p_call && x.rank == 0 && team == 0 && tid0 == 0) ++*p.p_call;        // (of those here nobody reads it)
-    if (tid0 < 32) reinterpret_cast<float *>(rc.so)[tid0] = x.rank * 32 + tid0 < p.pl.nout_m ? p.s_out[x.rank * 32 + tid0] : 0.f;
-    if (tid0 == 0) rc.st = has_tail ? p.s_out[tcol] : 0.f;
-
-    announce();
     x.local = meet(team, PAIR);
     bool ok = rc.ok != 0;
 

@@ -54,7 +54,7 @@ __device__ __forceinline__ int row_of(const Rows &r, int rank, int o)
 
 // A wave's eighth of K of T tiles of 16 outputs, one thread per pair of values and work-group: lane l holds output
 // l % 16 of a tile, of a block of 32 k's the eight from 8 (l / 16) on, of a half block four.  dst: the images
-// [rank][wave][nreg][lane] from register `first` on.  scale (fp32): a row's, else bf16 values; whole: fp32
+// [rank][wave][nreg][lane], a run of registers from `first` on (res_place).  scale (fp32): a row's, else bf16 values; whole: fp32
 // values, four registers of a half block.
 __global__ void __launch_bounds__(256) pack_tiles_kernel(unsigned *__restrict__ dst, int nreg, int first, const float *__restrict__ w, int K, const float *__restrict__ scale,
                                                          Rows rows, int T, int cls, int ts, bool whole)
@@ -72,15 +72,16 @@ __global__ void __launch_bounds__(256) pack_tiles_kernel(unsigned *__restrict__ 
     if (row >= 0)
         for (int e = 0; e < 2; ++e)
             if (k + e < K) v[e] = w[(long long)row * K + k + e];
-    unsigned *to = dst + ((long long)(rank * kResWaves + wave) * nreg + first + i) * 64 + lane;
+    unsigned *to = dst + ((long long)(rank * kResWaves + wave) * nreg + first) * 64;
+    const int n = res_tile_regs(!scale && !whole, cls, T);
     if (whole) {
-        for (int e = 0; e < 2; ++e) to[(t * 4 + i + e) * 64] = __float_as_uint(v[e]);
+        for (int e = 0; e < 2; ++e) to[res_place(n, t * 4 + 2 * i + e, lane)] = __float_as_uint(v[e]);
         return;
     }
     if (!scale) {
         unsigned u = 0;
         for (int e = 0; e < 2; ++e) u |= bf16_of(v[e]) << (16 * e);
-        to[res_tile_at(true, cls, T, kb, t, 0) * 64] = u;
+        to[res_place(n, res_tile_at(true, cls, T, kb, t, 0) + i, lane)] = u;
         return;
     }
     const float s = row >= 0 ? scale[row] : 0.f;
@@ -90,8 +91,8 @@ __global__ void __launch_bounds__(256) pack_tiles_kernel(unsigned *__restrict__ 
         high[e] = (_Float16)a;
         low[e] = (_Float16)(a - (float)high[e]);
     }
-    to[res_tile_at(false, cls, T, kb, t, 0) * 64] = __builtin_bit_cast(unsigned, high);
-    to[res_tile_at(false, cls, T, kb, t, 1) * 64] = __builtin_bit_cast(unsigned, low);
+    to[res_place(n, res_tile_at(false, cls, T, kb, t, 0) + i, lane)] = __builtin_bit_cast(unsigned, high);
+    to[res_place(n, res_tile_at(false, cls, T, kb, t, 1) + i, lane)] = __builtin_bit_cast(unsigned, low);
 }
 
 // The helpers' image of a layer, one thread per pair of values: work-group `rank` has quarter rank % 4 of K and units 80 (rank / 4)
@@ -113,9 +114,9 @@ __global__ void __launch_bounds__(256) pack_helpers_kernel(unsigned *__restrict_
             high[e] = (_Float16)a;
             low[e] = (_Float16)(a - (float)high[e]);
         }
-    unsigned *to = dst + ((long long)at * nreg + (kb * 3 + t) * 8 + i) * 64 + lane;
-    to[0] = __builtin_bit_cast(unsigned, high);
-    to[4 * 64] = __builtin_bit_cast(unsigned, low);
+    unsigned *to = dst + (long long)at * nreg * 64;
+    to[res_place(nreg, (kb * 3 + t) * 8 + i, lane)] = __builtin_bit_cast(unsigned, high);
+    to[res_place(nreg, (kb * 3 + t) * 8 + 4 + i, lane)] = __builtin_bit_cast(unsigned, low);
 }
 
 // out[i] = 2^-down / scale of the row that entry i is: i, or (gates) gate i % 4 of unit i / 4
