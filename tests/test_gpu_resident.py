@@ -262,6 +262,18 @@ def test_more_utterances_than_one_launch_takes(pkg, L, teams, extra):  # noqa: F
     eng.close()
 
 
+@pytest.mark.parametrize("H,J,V1,L,bf16,teams", [(320, 320, 257, 1, False, 16), (128, 128, 127, 1, False, 32), (128, 128, 127, 2, True, 32)])
+def test_full_lists_of_the_smaller_classes(pkg, H, J, V1, L, bf16, teams):  # noqa: F811
+    """As many utterances as a launch takes, their lengths ranked in the place of the frames, and seven in another; many of
+    the lengths are equal, some are 0."""
+    w = model_inputs(H, J, V1, L, B=teams * 128 + 7, T=4, seed=12)
+    lens = np.random.default_rng(12).integers(0, 5, w.B).astype(np.int32)
+    w = dataclasses.replace(w, enc_len=lens)
+    eng = pkg.Engine(w.model, w.B, w.T, flags=pkg.RNNT_FLAG_BF16_ARITHMETIC if bf16 else 0)
+    check(pkg, w, w.variant, f"full lists {H} {L}", engine=eng, bf16=bf16)
+    eng.close()
+
+
 @pytest.mark.parametrize("H,J,V1,L", [(128, 128, 255, 1), (316, 320, 529, 1), (324, 640, 530, 2), (640, 636, 1025, 2)])
 def test_rows_of_very_different_magnitude(pkg, H, J, V1, L):  # noqa: F811
     """fp32 weights are held as fp16 parts after a power of two for each row: matrices whose rows span 2^-40 to 2^12,
