@@ -15,6 +15,9 @@ constexpr int kResSlots = 4;              // exchange slots per vector, used in 
 constexpr int kResRows = 4;               // utterances a team decodes at the same time at most
 constexpr int kResSamples = 32;           // (utterance, frame) pairs per joint step at most
 constexpr int kResCalm = 8;               // joint steps after which a row's frames may be halved, see the loop control
+// Projected frames from which on they are brought to the L2 ahead of the steps that load them: what all XCDs' L2 hold.  (19 utterances of
+// 333 frames, 16 MB: 618 us without, 621 with it; 32 of 500, 41 MB: 1278 and 1270.)
+constexpr long long kResTouchBytes = 32 << 20;
 constexpr int kResList = 128;             // utterances a team takes per launch at most
 
 // Size classes: the register arrays, LDS rows and exchange buffers have compile-time sizes, so the
@@ -87,6 +90,7 @@ struct ResidentParams {
     int durations[kMaxDur];
     int B, T, S, cap;
     int slots;            // utterances decoded at a time per team
+    int touch_rows;       // rows of P, if frames are to be brought to the L2 ahead (see the joint step), or 0
     unsigned spin_limit;
     ResidentPlan pl;
     const int *enc_len;
@@ -148,9 +152,10 @@ RNNT_HD constexpr int res_main_regs(int kind, bool bf, int cls)
 // recurrent stage, kept till the next prediction step.
 // q: every wave's eighth of q, rows of res_q_row floats (zeros beyond the joint width).  tail: the tail column (see output()),
 // tpart: its partial sums.  state: cell state and recurrent pre-activations [layer][field][wave][lane] where they are
-// not in registers.  scale: powers of two of the team's list (fp32).
+// not in registers.  scale: powers of two of the team's list (fp32).  touch: for words that are loaded for their
+// lines only.
 // nmt: tiles of 16 samples.  Helpers: their own, from 0 on.
-struct ResidentLds { int p, part, ih, rec0, proj, rec, q, tail, tpart, state, scale, bytes; };
+struct ResidentLds { int p, part, ih, rec0, proj, rec, q, tail, tpart, state, scale, touch, bytes; };
 constexpr int kResSumRow = 36;            // floats per row of partial sums: of the joint step, of the projection
 constexpr int kResStageRow = 80;          // and of the LSTM stages
 RNNT_HD constexpr int res_q_row(int cls) { return res_row(cls) / 8 + 4; }
@@ -170,6 +175,7 @@ RNNT_HD constexpr ResidentLds resident_lds(int kind, int cls, int nmt)
     l.tpart = at; at += kResWaves * 2 * 16 * 4;
     l.state = at; at += kind == kResident2Pair ? 6 * 5 * 64 * 4 : 0;
     l.scale = at; at += kind == kResident2 ? 0 : kResList * 4;
+    l.touch = at; at += kind == kResident2Pair && cls == 0 && nmt == 2 ? 256 : 0;
     const int help = 2048 + 2 * (kResServed / 2) * res_help_blocks(cls) * 1024;
     if (kind == kResident2Pair && at < help) at = help;
     l.bytes = (at + 15) & ~15;

@@ -702,6 +702,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // and 880, 128 utterances 4173 and 4150, bfloat16 mode 873 and 866, 57 with e4m3 weights 727 and 716, 14 of a one-layer model 467 and
     // 461 (means of up to eight draws).  The waves with cells first: 0.6 % longer than without.  fp32 models with one tile of samples: no difference.
     constexpr bool FRAMES_FIRST = NMT == 2 || BF;
+    constexpr bool TOUCH = PAIR && CLS == 0 && NMT == 2;          // see the joint step
     const bool has_cells = x.wave < 5;          // finishes 16 (unit, row) pairs of the LSTM stages, see stage_sum
     // (beyond the buffer for waves without cells, whose loads give zeros: a branch around the loads would make the
     // compiler wait for them where it waits for an older one)
@@ -1356,6 +1357,20 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         // ---- joint step ----------------------------------------------------------------------------
         ++n_joint;
         const unsigned jn = n_joint;
+        // The frames that come after those of this step are brought to the XCD's L2 meanwhile, a work-group asking for a word of every
+        // line of one: the frames' loads of the next step are what the waves without cells wait for.  (Into LDS, where nobody reads them: a
+        // register would be waited for.  By the wave that is done first; its next wait, for the keys, is 1.5 us on.)  128 utterances, whose
+        // projected frames are in no L2 any more, 4147 us without and 4075 with it, 80 utterances 2988 and 2965, 32 utterances 1278 and
+        // 1270, TDT 879 and 879.  (One tile of samples: no gain; one-layer and bfloat16 models: weights spilled.  A scalar branch around
+        // it instead of touch_rows: 32 utterances 0.3 % longer than without.)
+        if constexpr (TOUCH) if (x.wave == 0) {
+            static_assert(TS == kResSamples, "a sample for every work-group");
+            const int lane = lane_id(), s = x.rank + (lane >> 5) * TS, k = (lane & 31) * 32;          // (the lower half of the lanes)
+            const int row = from_lane(pidx, s & (kResSamples - 1)) + la;                // (of whose utterance does not matter)
+            const unsigned to = (unsigned)__builtin_amdgcn_readfirstlane((int)(lds_p + (unsigned)(lo.touch - lo.p)));
+            if (s < NS && row >= la && row < p.touch_rows && k < p.J)
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" :: "v"(p.P + (long long)row * p.J + k), "s"(to) : "memory");
+        }
         {
             // A wave has an eighth of K for both column tiles, so the operand z = relu(P + q) of a lane's sample is
             // formed on the way: nobody else needs it.  fp32: every product is that of two fp16 parts of

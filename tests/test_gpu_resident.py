@@ -430,6 +430,19 @@ def test_the_largest_instances(pkg, L, bf16):  # noqa: F811
     eng.close()
 
 
+@pytest.mark.parametrize("J,B,T,durations", [(640, 27, 500, ()), (404, 41, 510, (0, 1, 3, 7))])
+def test_frames_asked_for_ahead_end_with_the_batch(pkg, J, B, T, durations):  # noqa: F811
+    """Projected frames of more than 32 MB, the last utterance up to the last row of them, the others short."""
+    assert B * T * J * 4 > 32 << 20
+    w = model_inputs(324, J, 530, 2, B=B, T=T, seed=J, durations=durations)
+    ln = np.minimum(w.enc_len, 17)
+    ln[-1], ln[0] = T, T - 3
+    w = dataclasses.replace(w, enc_len=ln)
+    eng = pkg.Engine(w.model, w.B, w.T)
+    check(pkg, w, w.variant, f"ahead {J} {B} {T} {durations}", engine=eng)
+    eng.close()
+
+
 @pytest.mark.parametrize("H,J,V1,L,durations", WIDE_TDT)
 @pytest.mark.parametrize("size", [1e7, 1e12])
 def test_a_large_joint_unit_that_nobody_reads(pkg, H, J, V1, L, durations, size):  # noqa: F811
