@@ -244,12 +244,12 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
                     v[i] = ((o[0][i] + o[1][i]) + (o[2][i] + o[3][i])) + b_out[i];
                     mine = fmaxf(mine, first + i < p.VT ? v[i] : -INFINITY);
                 }
-                // the lowest of equal outputs
-                int k = first;
+                // the lowest of equal outputs (none: they are all NaN, and a frame with nothing else is a blank)
+                int k = -1;
 #pragma unroll
                 for (int i = TILES - 1; i >= 0; --i) k = first + i < p.VT && v[i] == mine ? first + i : k;
                 const float m = max16(mine);
-                const unsigned hit = (unsigned)(__ballot(mine == m && first < p.VT) >> (lane & 48)) & 0xffffu;
+                const unsigned hit = (unsigned)(__ballot(mine == m && k >= 0) >> (lane & 48)) & 0xffffu;
                 const int lead = hit ? __builtin_ctz(hit) : 0;
                 if (l == lead) *reinterpret_cast<int2 *>(res + s * 2) = make_int2(hit ? k : p.blank, __float_as_int(m + 0.0f));
                 if (tdt) {
@@ -257,12 +257,13 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
 #pragma unroll
                     for (int i = 0; i < TILES; ++i) dm = fmaxf(dm, first + i >= p.VT && first + i < p.NOUT ? v[i] : -INFINITY);
                     const float top = max16(dm);
-                    const unsigned dhit = (unsigned)(__ballot(dm == top && first + TILES > p.VT && first < p.NOUT) >> (lane & 48)) & 0xffffu;
-                    int d = first;
+                    int d = -1;
 #pragma unroll
                     for (int i = TILES - 1; i >= 0; --i) d = first + i >= p.VT && first + i < p.NOUT && v[i] == top ? first + i : d;
+                    const unsigned dhit = (unsigned)(__ballot(dm == top && d >= 0) >> (lane & 48)) & 0xffffu;
                     const int dlead = dhit ? __builtin_ctz(dhit) : 0;
-                    if (l == dlead) res_d[s] = durations[dhit ? min(max(d - p.VT, 0), kMaxDur - 1) : 0];
+                    // (no duration where all are NaN: what the resident kernel then takes)
+                    if (l == dlead) res_d[s] = durations[dhit ? min(d - p.VT, kMaxDur - 1) : p.D & 1 ? p.D : 1];
                 }
                 if (p.logps) {
                     float e = 0.f;

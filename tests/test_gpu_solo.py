@@ -94,3 +94,28 @@ def test_what_a_call_leaves(pkg):  # noqa: F811
     eng.decode("label", enc, ln, 4)
     assert eng.stats()["team_size"] != 1
     eng.close()
+
+
+@pytest.mark.parametrize("durations,skipped", [((), 1), ((1, 2), 2), ((3, 2, 1), 1)])
+def test_a_frame_whose_outputs_are_no_numbers_is_a_blank(pkg, durations, skipped):  # noqa: F811
+    """An infinite value of a frame makes every output of it NaN: it has no label, and the frames around it are as without it.  (TDT:
+    the second duration for an even number of them, else none.)"""
+    w = model_inputs(64, 64, 17, 1, B=5, T=20, seed=3, durations=durations)
+    w.model.b_out[w.model.dims.blank] -= 1.3          # (labels on a part of the frames)
+    x, ln = w.enc_out.copy(), np.maximum(w.enc_len, 5)
+    x[:, 3, 0] = np.inf
+    at = 0 if durations else 3           # (TDT: the first frame, as no label goes past it)
+    x, ln = np.ascontiguousarray(x[:, 3 - at:]), ln - (3 - at)
+    eng = pkg.Engine(w.model, w.B, w.T)
+
+    def run(a, n):
+        out = eng.decode(w.variant, torch.from_numpy(a).cuda(), torch.from_numpy(n.astype(np.int32)).cuda(), 4)
+        return {k: v.cpu().numpy() for k, v in out.items()}
+
+    got, want = run(x, ln), run(np.ascontiguousarray(np.delete(x, range(at, at + skipped), axis=1)), np.maximum(ln - skipped, 0))
+    assert np.array_equal(got["tok_len"], want["tok_len"]) and got["tok_len"].max() > 0
+    for b, n in enumerate(got["tok_len"]):
+        assert np.array_equal(got["tokens"][b, :n], want["tokens"][b, :n])
+        f = want["frames"][b, :n]
+        assert np.array_equal(got["frames"][b, :n], f + skipped * (f >= at))
+    eng.close()
