@@ -650,7 +650,6 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
                                       is_bf16_arith(e->wt), ci, stream));
     e->last_B = B; e->last_used.clear(); e->last_ws = ws; e->last_resident = true;
     if (pl.solo) {
-        // (its work-groups wait for nobody: in no order with other decodes)
         SoloParams p{};
         p.H = d.H; p.J = d.J; p.V1 = d.V1; p.NOUT = e->NOUT; p.blank = d.blank;
         p.tdt = variant == kTdtLabelLooping;
@@ -662,7 +661,12 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
         p.T0 = e->T0.as<float>(); p.b_pred = e->b_pred.as<float>(); p.b_out = e->b_out.as<float>();
         p.tokens = tokens_out; p.tok_len = tok_len_out; p.frames = frames_out; p.durs = durs_out; p.logits = logit_out; p.logps = e->logp_out;
         p.done = e->done; p.status = ws.status; p.stats = ws.stats; p.n_records = pl.n_teams;
-        HIP_TRY(launch_solo(p, stream));
+        // (Its work-groups wait for nobody, but while they run another decode's would get a part of the device, and wait.)
+        const int rc = in_launch_order(stream, [&](bool plain) -> int {
+            HIP_TRY(launch_solo(p, (plain && !e->coop_launch) || e->plain_launch, stream));
+            return RNNT_OK;
+        });
+        if (rc) return rc;
         e->timed = true;
         return RNNT_OK;
     }

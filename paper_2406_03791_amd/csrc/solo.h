@@ -36,6 +36,6 @@ struct SoloParams {
 
 // w: solo_parts(solo_tiles(NOUT)) * 256 groups of four; *check, zero before: raised if a weight is not finite
 hipError_t pack_solo(const float *w_hh, const float *w_pred, const float *w_out, int H, int J, int NOUT, float4 *w, unsigned *check, hipStream_t stream);
-hipError_t launch_solo(const SoloParams &p, hipStream_t stream);
+hipError_t launch_solo(const SoloParams &p, bool plain, hipStream_t stream);
 
 }  // namespace rnnt

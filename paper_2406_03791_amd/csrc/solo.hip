@@ -334,7 +334,7 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
 }
 
 template <int TILES, bool WALK>
-hipError_t launch_tiles(const SoloParams &p, hipStream_t stream)
+hipError_t launch_tiles(const SoloParams &p, bool plain, hipStream_t stream)
 {
     const void *fn = reinterpret_cast<const void *>(&solo_kernel<TILES, WALK>);
     const unsigned lds = (unsigned)solo_lds(p.V1, TILES).total * 4u;
@@ -342,7 +342,9 @@ hipError_t launch_tiles(const SoloParams &p, hipStream_t stream)
     if (e != hipSuccess) return e;
     SoloParams pc = p;
     void *args[] = {&pc};
-    return hipLaunchKernel(fn, dim3((unsigned)(p.B < p.n_records ? p.B : p.n_records)), dim3(kSoloThreads), args, lds, stream);
+    const dim3 grid((unsigned)(p.B < p.n_records ? p.B : p.n_records)), block(kSoloThreads);
+    if (plain) return hipLaunchKernel(fn, grid, block, args, lds, stream);
+    return hipLaunchCooperativeKernel(fn, grid, block, args, lds, stream);
 }
 
 }  // namespace
@@ -354,14 +356,14 @@ hipError_t pack_solo(const float *w_hh, const float *w_pred, const float *w_out,
     return hipGetLastError();
 }
 
-hipError_t launch_solo(const SoloParams &p, hipStream_t stream)
+hipError_t launch_solo(const SoloParams &p, bool plain, hipStream_t stream)
 {
     // what the kernel is laid out for
     if (p.H < 1 || p.H > kSoloWidth || p.J < 1 || p.J > kSoloWidth || p.J % 4 != 0 || p.NOUT > kSoloOutputs || p.V1 > p.NOUT || p.B < 1 || p.n_records < 1)
         return hipErrorInvalidValue;
     const bool walk = p.tdt || p.VT != p.V1;
-    if (solo_tiles(p.NOUT) == 2) return walk ? launch_tiles<2, true>(p, stream) : launch_tiles<2, false>(p, stream);
-    return walk ? launch_tiles<4, true>(p, stream) : launch_tiles<4, false>(p, stream);
+    if (solo_tiles(p.NOUT) == 2) return walk ? launch_tiles<2, true>(p, plain, stream) : launch_tiles<2, false>(p, plain, stream);
+    return walk ? launch_tiles<4, true>(p, plain, stream) : launch_tiles<4, false>(p, plain, stream);
 }
 
 }  // namespace rnnt

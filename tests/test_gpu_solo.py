@@ -6,8 +6,10 @@ import dataclasses
 import numpy as np
 import pytest
 
+import oracle
 import synth
-from test_gpu_parity import check, pkg  # noqa: F401  (pkg: fixture)
+from parity_util import compare, to_lists
+from test_gpu_parity import N_THREADS, check, pkg  # noqa: F401  (pkg: fixture)
 from test_gpu_resident import model_inputs
 
 pytestmark = pytest.mark.gpu
@@ -119,3 +121,38 @@ def test_a_frame_whose_outputs_are_no_numbers_is_a_blank(pkg, durations, skipped
         f = want["frames"][b, :n]
         assert np.array_equal(got["frames"][b, :n], f + skipped * (f >= at))
     eng.close()
+
+
+@pytest.mark.parametrize("cooperative", [False, True])
+def test_decodes_of_other_engines_come_after(pkg, cooperative):  # noqa: F811
+    """Decodes of a device run one after another, whatever their engines and streams: what is copied behind a short call on one
+    stream is the finished result of a long call on another, where either, or both, are this kernel's."""
+    flags = pkg.RNNT_FLAG_COOPERATIVE_LAUNCH if cooperative else 0
+    small, wide = (64, 64, 17, 1), (324, 332, 520, 2)
+    streams = torch.cuda.Stream(), torch.cuda.Stream()
+    for first, then in ((small, small), (small, wide), (wide, small)):
+        ws = [model_inputs(*first, B=4, T=4000, seed=8), model_inputs(*then, B=2, T=6, seed=9)]
+        ws = [dataclasses.replace(w, enc_len=np.full(w.B, w.T, dtype=np.int32)) for w in ws]
+        for w in ws:
+            w.model.b_out[w.model.dims.blank] -= 4.0          # (labels on most frames: the long call takes milliseconds)
+        engines = [pkg.Engine(w.model, w.B, w.T, flags=flags) for w in ws]
+        calls = []
+        for w, eng in zip(ws, engines):
+            out = eng.alloc_outputs(w.B, w.T * w.max_symbols)
+            out["tok_len"].fill_(-1)
+            calls.append((eng, torch.from_numpy(w.enc_out).cuda(), torch.from_numpy(w.enc_len).cuda(), out))
+        there = torch.full_like(calls[0][3]["tok_len"], -2)
+        torch.cuda.synchronize()
+        for stream, w, (eng, enc, ln, out) in zip(streams, ws, calls):
+            with torch.cuda.stream(stream):
+                eng.decode("label", enc, ln, w.max_symbols, out=out)
+        with torch.cuda.stream(streams[1]):
+            there.copy_(calls[0][3]["tok_len"])
+        torch.cuda.synchronize()
+        for w, (eng, _, _, out) in zip(ws, calls):
+            assert eng.status() == 0
+            net = oracle.LstmNet(w.model)
+            ref = oracle.decode(net, w.enc_out, w.enc_len, w.max_symbols, "seq", n_threads=N_THREADS)
+            compare(w, net, ref, to_lists(out, w.B), w.max_symbols)
+            eng.close()
+        assert torch.equal(there, calls[0][3]["tok_len"]) and int(there.min()) > 1000, (first, then, there)
