@@ -1643,11 +1643,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                         if (wait_expired(p, spins)) { rc.ok = 0; break; }
                     }
                     x.polls += __builtin_amdgcn_readfirstlane((int)spins);
-                    // best duration, the lowest index on ties
+                    // best duration, the lowest index on ties, and the first one where all are NaN
                     const float d0 = di < p.D ? __uint_as_float(dv[0]) : -INFINITY, d1 = ND > 1 && di + 1 < p.D ? __uint_as_float(dv[ND - 1]) : -INFINITY;
-                    const float dl = fmaxf(d0, d1), dm = lane_max<L>(dl);
-                    const unsigned hit = (unsigned)(__ballot(dl == dm && di < p.D) >> (lane & ~(L - 1))) & ((1u << L) - 1u);
-                    if (li == (hit ? __builtin_ctz(hit) : 0)) rc.s_d[s] = d0 == dm || ND == 1 ? v0 : v1;
+                    const float dm = lane_max<L>(fmaxf(d0, d1));
+                    const bool odd = ND > 1 && di + 1 < p.D && d1 == dm && d0 != dm;
+                    const unsigned hit = (unsigned)(__ballot((d0 == dm && di < p.D) || odd) >> (lane & ~(L - 1))) & ((1u << L) - 1u);
+                    if (li == (hit ? __builtin_ctz(hit) : 0)) rc.s_d[s] = odd ? v1 : v0;
                 } else {
                     receive<1>(p, x, off, bo.key + slot_at(jn, KSLOT), v);
                 }

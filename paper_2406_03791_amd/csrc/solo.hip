@@ -262,8 +262,8 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
                     for (int i = TILES - 1; i >= 0; --i) d = first + i >= p.VT && first + i < p.NOUT && v[i] == top ? first + i : d;
                     const unsigned dhit = (unsigned)(__ballot(dm == top && d >= 0) >> (lane & 48)) & 0xffffu;
                     const int dlead = dhit ? __builtin_ctz(dhit) : 0;
-                    // (no duration where all are NaN: what the resident kernel then takes)
-                    if (l == dlead) res_d[s] = durations[dhit ? min(d - p.VT, kMaxDur - 1) : p.D & 1 ? p.D : 1];
+                    // (the first one where all are NaN)
+                    if (l == dlead) res_d[s] = durations[dhit ? min(d - p.VT, kMaxDur - 1) : 0];
                 }
                 if (p.logps) {
                     float e = 0.f;

@@ -234,6 +234,23 @@ def test_rows_that_end_one_after_the_other(pkg, H, J, V1, L, extra, bf16):  # no
         eng.close()
 
 
+@pytest.mark.parametrize("H,J,V1,L,bf16", [(64, 64, 40, 1, False), (128, 124, 100, 1, False), (100, 128, 255, 1, True), (128, 128, 254, 2, False),
+                                           (320, 316, 257, 1, False), (324, 332, 520, 2, False), (324, 332, 520, 2, True)])
+@pytest.mark.parametrize("durations", [(2,), (2, 1), (0, 3, 1), (1, 0, 2, 3, 4, 5, 6, 7)])
+def test_durations_that_are_no_numbers(pkg, H, J, V1, L, bf16, durations):  # noqa: F811
+    """Where every duration's output is NaN the first one is taken, as where all are equal, whatever their number and the model's size."""
+    w = model_inputs(H, J, V1, L, B=19, T=23, seed=len(durations), durations=durations)
+    nan = np.full(len(durations), np.nan, dtype=np.float32)
+    w.model.w_out[V1:], w.model.b_out[V1:] = 0.0, nan
+    w.model.b_out[w.model.dims.blank] -= 1.5          # (labels and blanks)
+    eng = pkg.Engine(w.model, w.B, w.T, flags=pkg.RNNT_FLAG_BF16_ARITHMETIC if bf16 else 0)
+    w.model.b_out[V1:] = 0.0
+    _, got, _ = check(pkg, w, "tdt", f"NaN durations {H}/{L}/{bf16} {durations}", engine=eng, bf16=bf16)
+    durs = np.concatenate(got["durs"])           # (in the bfloat16 mode another one would pass for a tie)
+    assert len(durs) > w.B and (durs == durations[0]).all()
+    eng.close()
+
+
 def test_an_engine_that_does_not_fit_the_memory_leaves_the_others_alone(pkg):  # noqa: F811
     """The projected frames of 2^27 padded frames take 320 GiB: refused by the allocator, and the next call of an
     engine that exists does not report that error."""
