@@ -553,31 +553,33 @@ __device__ __forceinline__ void res_finish_row(int b, int cnt)
 // Loads row `row` of the projected frames into sample s's place in LDS, straight from memory.  The
 // 16-byte piece k4 goes to position (k4 with its low four bits xored with s), so that sixteen samples'
 // pieces of the same k sit in different banks.  (The instruction's offset counts on both sides.)
-template <int ROW>
+template <int CLS>
 __device__ __forceinline__ void load_frame(const ResidentParams &p, const RCtx &x, unsigned lds_p, int row, int s)
 {
+    constexpr int ROW = res_row(CLS);
     const int lane = lane_id(), j4 = p.J >> 2, k4 = lane ^ (s & 15);
     const char *src = reinterpret_cast<const char *>(p.P + (long long)row * p.J);
     const unsigned m = (unsigned)__builtin_amdgcn_readfirstlane((int)(lds_p + (unsigned)(s * ROW * 4)));
-    // a row that fills its place: all of it, with no branch around a load
-    if (j4 == ROW / 4) {
+    // A row that fills its place (no joint layer does in the middle class): all of it, with no branch around a load.  The last load takes half
+    // a wave, with all of its lanes on before and after: which waves load which samples goes by wave, so they are.  (m0 is
+    // reserved: the compiler keeps nothing in it.)
+    if constexpr (ROW == res_width(CLS)) if (j4 == ROW / 4) {
         const unsigned off = (unsigned)k4 * 16u;
-        constexpr int FULL = ROW / 256;
-        if constexpr (FULL == 2)
+        static_assert(ROW % 256 == 128, "whole waves, and a half one");
+        if constexpr (ROW / 256 == 2)
             asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\tglobal_load_lds_dwordx4 %0, %2 offset:1024\n\t"
                          "s_mov_b32 exec_hi, 0\n\tglobal_load_lds_dwordx4 %0, %2 offset:2048\n\ts_mov_b32 exec_hi, -1" :: "v"(off), "s"(m), "s"(src) : "memory");
-        else if constexpr (FULL == 1)
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\t"
-                         "s_mov_b32 exec_hi, 0\n\tglobal_load_lds_dwordx4 %0, %2 offset:1024\n\ts_mov_b32 exec_hi, -1" :: "v"(off), "s"(m), "s"(src) : "memory");
-        else
+        else {
+            static_assert(ROW / 256 == 0 || ROW / 256 == 2, "written out for these");
             asm volatile("s_mov_b32 m0, %1\n\ts_mov_b32 exec_hi, 0\n\tglobal_load_lds_dwordx4 %0, %2\n\ts_mov_b32 exec_hi, -1" :: "v"(off), "s"(m), "s"(src) : "memory");
+        }
         return;
     }
     static_for<0, (ROW / 4 + 63) / 64>([&](auto u_) {
         constexpr int u = decltype(u_)::value;
         const char *from = src;
         const unsigned to = m, off = (unsigned)k4 * 16u;
-        if (((u + 1) * 64 <= ROW / 4 || lane < ROW / 4 - u * 64) && (j4 == ROW / 4 || u * 64 + k4 < j4))
+        if (((u + 1) * 64 <= ROW / 4 || lane < ROW / 4 - u * 64) && u * 64 + k4 < j4)
             asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 offset:%3"
                          :: "v"(off), "s"(to), "s"(from), "n"(u * 1024) : "memory");
     });
@@ -1075,11 +1077,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     auto load_frames = [&](unsigned of, int from, int step) {
         if constexpr (NMT == 1) {
             for (int s = from; s < part_samples(); s += step)
-                if (fresh >> s & 1) load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
+                if (fresh >> s & 1) load_frame<CLS>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
         } else {
             for (unsigned m = (unsigned)fresh & of; m != 0u; m &= m - 1u) {
                 const int s = __builtin_ctz(m);
-                load_frame<ROW>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
+                load_frame<CLS>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
             }
         }
     };
