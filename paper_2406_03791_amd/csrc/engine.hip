@@ -685,7 +685,7 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
             int la;
             resident_rows(pl, nb, &p.slots, &la);
             p.spin_limit = wait_polls(e->wait_limit, kResidentWait);
-            p.touch_rows = (long long)nb * T * d.J * (long long)sizeof(float) > kResTouchBytes ? nb * T : 0;
+            p.touch_rows = touch_rows(nb, T, d.J);
             p.pl = pl;
             const long long oc = (long long)off * cap;
             p.enc_len = enc_len + off; p.P = ws.P + (long long)off * T * d.J;

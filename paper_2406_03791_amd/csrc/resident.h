@@ -18,6 +18,15 @@ constexpr int kResCalm = 8;               // joint steps after which a row's fra
 // Projected frames from which on they are brought to the L2 ahead of the steps that load them: what all XCDs' L2 hold.  (19 utterances of
 // 333 frames, 16 MB: 618 us without, 621 with it; 32 of 500, 41 MB: 1278 and 1270.)
 constexpr long long kResTouchBytes = 32 << 20;
+// Rows of P of a launch of nb utterances that may be asked for, none if it stays below that.
+inline int touch_rows(int nb, int T, int J) { return (long long)nb * T * J * (long long)sizeof(float) > kResTouchBytes ? nb * T : 0; }
+// Where the frames `la` after a sample's are, -1 beyond the last of `rows` or for no sample (row -1).  The frame may be of the next utterance,
+// or padding: it is brought to the L2 and not looked at.
+RNNT_HD constexpr int touch_row(int row, int la, int rows)
+{
+    const int at = (int)((unsigned)row + (unsigned)la);          // (negative beyond 2^31)
+    return at >= la && at < rows ? at : -1;
+}
 constexpr int kResList = 128;             // utterances a team takes per launch at most
 
 // Size classes: the register arrays, LDS rows and exchange buffers have compile-time sizes, so the

@@ -1367,10 +1367,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         // it instead of touch_rows: 32 utterances 0.3 % longer than without.)
         if constexpr (TOUCH) if (x.wave == 0) {
             static_assert(TS == kResSamples, "a sample for every work-group");
-            const int lane = lane_id(), s = x.rank + (lane >> 5) * TS, k = (lane & 31) * 32;          // (the lower half of the lanes)
-            const int row = from_lane(pidx, s & (kResSamples - 1)) + la;                // (of whose utterance does not matter)
+            const int lane = lane_id(), s = x.rank + (lane >> 5) * TS, k = (lane & 31) * 32;          // (upper half of the lanes: beyond NS)
+            const int row = touch_row(from_lane(pidx, s & (kResSamples - 1)), la, p.touch_rows);
             const unsigned to = (unsigned)__builtin_amdgcn_readfirstlane((int)(lds_p + (unsigned)(lo.touch - lo.p)));
-            if (s < NS && row >= la && row < p.touch_rows && k < p.J)
+            if (s < NS && row >= 0 && k < p.J)
                 asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" :: "v"(p.P + (long long)row * p.J + k), "s"(to) : "memory");
         }
         {

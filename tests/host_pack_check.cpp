@@ -1,16 +1,17 @@
-// Host-only check of the stage planner and the weight packer (csrc/plan.h, csrc/pack.h), meant
+// Host-only check of the stage planner and the weight packer (csrc/plan.h, csrc/pack.h) and of rules in csrc/resident.h, meant
 // to be built with AddressSanitizer and UndefinedBehaviorSanitizer and run by the CPU test
 // suite.  For a sweep of shapes and every weight storage it packs a matrix whose entry
 // (col, k) encodes its own position, then walks the packed image the way the kernel's lanes
 // do and checks that every (col, k) of the matrix turns up exactly once, at the place the
 // plan says, and that everything else is zero.  Also checks e4m3_bits on all 256 codes, the
-// row-scaled e4m3 and block-scaled e2m1 forms (exponent rules, rounding, packed codes) and the split of the joint
-// output stage into an MFMA part and tail columns.
+// row-scaled e4m3 and block-scaled e2m1 forms (exponent rules, rounding, packed codes), the split of the joint
+// output stage into an MFMA part and tail columns, and which rows of the projected frames are asked for ahead.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
 
 #include "pack.h"
+#include "resident.h"
 
 using namespace rnnt;
 
@@ -217,6 +218,20 @@ int main()
     for (unsigned polls : {0u, 1u, kStreamingWait, kResidentWait, 0xffffffffu})
         for (unsigned by_default : {kStreamingWait, kResidentWait})
             if (wait_polls(polls, by_default) != polls || wait_polls(-1, by_default) != by_default) { std::printf("wait limit\n"); return 1; }
+    // frames that are asked for ahead: the sample's row and the frames of a step, of the launch's rows only
+    if (touch_rows(64, 256, 512) != 0 || touch_rows(27, 500, 640) != 27 * 500 || touch_rows(1, 2147483647, 4) != 2147483647) {
+        std::printf("touch rows\n");
+        return 1;
+    }
+    for (int rows : {0, 1, 4, 31, 32, 13500, 2147483647})
+        for (int la : {4, 5, 8, 10, 16, 31}) {
+            for (int row : {-1, 0, 1, rows - 2 * la, rows - la - 1, rows - la, rows - 2, rows - 1}) {
+                if (row < -1 || row >= rows) continue;
+                const int64_t at = (int64_t)row + la, got = touch_row(row, la, rows);
+                if (got != (row >= 0 && at < rows ? at : -1)) { std::printf("row %d of %d, %d on\n", row, rows, la); return 1; }
+                ++checked;
+            }
+        }
     std::printf("ok %ld\n", checked);
     return 0;
 }

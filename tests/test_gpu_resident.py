@@ -448,8 +448,9 @@ def test_the_largest_instances(pkg, L, bf16):  # noqa: F811
 
 
 @pytest.mark.parametrize("J,B,T,durations", [(640, 27, 500, ()), (404, 41, 510, (0, 1, 3, 7))])
-def test_frames_asked_for_ahead_end_with_the_batch(pkg, J, B, T, durations):  # noqa: F811
-    """Projected frames of more than 32 MB, the last utterance up to the last row of them, the others short."""
+def test_large_batches_whose_frames_are_asked_for_ahead(pkg, J, B, T, durations):  # noqa: F811
+    """Projected frames of more than 32 MB, the last utterance up to the last row of them, the others short: results with the loads
+    ahead (host_pack_check.cpp has which rows they are of)."""
     assert B * T * J * 4 > 32 << 20
     w = model_inputs(324, J, 530, 2, B=B, T=T, seed=J, durations=durations)
     ln = np.minimum(w.enc_len, 17)
