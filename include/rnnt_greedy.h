@@ -20,10 +20,11 @@
  *   - Decode calls only enqueue work on `stream` and return; they never wait
  *     for the device and never read device memory from the host.
  *   - One engine serves one call at a time (shared workspace): calls on the
- *     same engine must be ordered by the caller (same stream or events).  A
- *     decode launch occupies every compute unit, so calls of different engines
- *     gain nothing from running on different streams; order them too.
- *   - The work-groups of a decode wait for each other, so all of them have to be
+ *     same engine must be ordered by the caller (same stream or events).
+ *     Decodes of a device run one after another (below), so calls of different
+ *     engines gain nothing from running on different streams; order them too.
+ *   - The work-groups of a decode wait for each other (but for the smallest
+ *     models, see rnnt_engine_create), so all of them have to be
  *     on the device at once: two decodes that each got a part of it would wait
  *     until their limit (rnnt_engine_set_wait_limit) and end with
  *     RNNT_DEV_ABORTED.  The library orders the decodes that it enqueues on a
@@ -300,7 +301,10 @@ int rnnt_quantize_blocks_e2m1(const float *w, int64_t rows, int64_t cols, float 
  * Models of one or two LSTM layers of at most 640 units, a joint width of at
  * most 640 and at most 1056 output columns are decoded by a kernel that keeps
  * the weights in registers; one launch of it takes up to 128 utterances per
- * team (rnnt_stats.n_teams).  The rest of this paragraph is about the other
+ * team (rnnt_stats.n_teams).  Of these the fp32 models of one layer whose
+ * widths and outputs are at most 64 have a work-group per utterance, which
+ * waits for no other, and any number of utterances in a launch (n_teams: the
+ * work-groups there may be).  The rest of this paragraph is about the other
  * kernel, which streams them, and which those models use too once
  * rnnt_engine_configure has asked for something.
  * A call with more than 128 utterances is decoded
@@ -512,8 +516,9 @@ int rnnt_engine_set_wait_limit(rnnt_engine *eng, int64_t polls);
  * -DRNNT_PROFILE (RNNT_PROFILE=1 in the environment of build.py): microseconds
  * rank 0 of `team` spent in each phase of the prediction and joint steps, as
  * many as n (at most 24) into the HOST array us_out.  The phases of either
- * kernel are listed in bench.py (--phases).  An ordinary build returns RNNT_ERR_UNSUPPORTED.  Waits
- * for the device.
+ * kernel are listed in bench.py (--phases); models of a work-group per utterance
+ * have none (zeros).  An ordinary build returns RNNT_ERR_UNSUPPORTED.  Waits for
+ * the device.
  */
 int rnnt_engine_phase_timers(rnnt_engine *eng, int32_t team, double *us_out, int32_t n);
 

@@ -661,7 +661,8 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
         p.T0 = e->T0.as<float>(); p.b_pred = e->b_pred.as<float>(); p.b_out = e->b_out.as<float>();
         p.tokens = tokens_out; p.tok_len = tok_len_out; p.frames = frames_out; p.durs = durs_out; p.logits = logit_out; p.logps = e->logp_out;
         p.done = e->done; p.status = ws.status; p.stats = ws.stats; p.n_records = pl.n_teams;
-        // (Its work-groups wait for nobody, but while they run another decode's would get a part of the device, and wait.)
+        // (Its work-groups wait for nobody, but while they run another decode's would get a part of the device, and wait.  One utterance of 20 frames
+        // 53.4 us in no order, 56.6 in this one.)
         const int rc = in_launch_order(stream, [&](bool plain) -> int {
             HIP_TRY(launch_solo(p, (plain && !e->coop_launch) || e->plain_launch, stream));
             return RNNT_OK;

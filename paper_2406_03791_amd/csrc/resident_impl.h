@@ -41,6 +41,9 @@
 // slot n - 2 when it publishes step n: by then it has received something of step n - 1 from
 // everyone, which everyone sent after reading step n - 2; and it waits for that store before it
 // publishes step n + 1, so nobody can look for step n + 2's data in a slot that still holds old data.
+// (No wait for the store as such: a wave's loads and stores are counted in the order they were issued in, and every wave
+// polls for a vector, or waits for its frames, behind its stores of a step and ahead of the barrier that its
+// work-group's next words of that kind come after.  A wave that skips such a poll needs a wait in its place.)
 //
 // Registers decide what the code looks like: values that could be kept for the whole loop are worked out
 // where they are used (lane_id), state that few waves need lies in LDS, arguments that few steps need are
@@ -76,7 +79,7 @@ struct RRows {
     static constexpr int kPlaces = 8;
     static_assert(kResRows <= kPlaces, "a place for every row");
     RRow s[kPlaces];
-    int b[kPlaces], m[kPlaces];       // utterance; t modulo the frames of a joint step
+    int b[kPlaces], m[kPlaces];       // utterance; place of frame t among the row's samples, a ring (0 when they are dealt anew)
     int since[kPlaces], next;         // t some steps ago; first utterance of the list that no row has had
 };
 
@@ -1198,7 +1201,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             // The same to the helpers, when the team's own vector is there: loads and stores of a wave are counted in one
             // order, so polls behind these stores wait for the memory side to take them (label looping of 32 utterances 1470 us with the
             // stores before the polls, 1374 us now, together with the polls apart, below).
-            // (No condition around the stores, or what was loaded before them would be waited for together with them.)
+            // (No condition around the stores, or what was loaded before them would be waited for together with them.  They are done, the
+            // marks among them, when the wave's next polls are: of the second layer's vector, or of q.)
             auto forward_h = [&](int layer) {
                 const Place l = place_of(lane_id());
                 const unsigned o = has_cells && l.ok ? (unsigned)l.row * VROW + (unsigned)(u0 + l.lu) * 4u : 0x80000000u;
@@ -1280,7 +1284,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     // A poll that comes too early is repeated after 0.25 us, and slows down what it waits for: the first one
                     // 320 cycles on.  (32 utterances 1292, 1316 and 1144 us without the pause, three draws, 1266, 1285, 1120 with 128
                     // cycles, 1263, 1281, 1115 with 192, 1256, 1277, 1108 with 320, 1267, 1285, 1116 with 448; one utterance 525, 522, 521, 522, 522.
-                    // Pauses before the other polls: no gain, there is work in between.)
+                    // Narrower classes, calls of 1 to 96 utterances of 320 or 128 units, 65 to 170 us: 48 of 320 units 1.2 % shorter with it, the others
+                    // within 0.4 %.  Pauses before the other polls: no gain, there is work in between.)
                     __builtin_amdgcn_s_sleep(5);
                     x1.receive_from(p, x, bo.h[1] + slot_at(n, VSLOT), h4);
                     if (PAIR) forward_h(1);
@@ -1289,7 +1294,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             RES_MARK(6);
             // prediction-side joint projection
             stage<BF, CLS, R, 2, kResSumRow>(w_pr, x1, sums_pr, x.wave);
-            if (x.wave >= 5) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's frames are in LDS
+            // this wave's frames are in LDS (what the other waves have stored by now, marks too, their polls for q wait for)
+            if (x.wave >= 5) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
             {
                 // LR adjacent threads per value (group of four columns, column, row), R / 2 waves' sums each

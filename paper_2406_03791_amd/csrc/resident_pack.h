@@ -25,7 +25,7 @@ inline ResidentPlan plan_resident(int H, int J, int L, int NOUT, bool bf, int n_
         pl.kind = kind; pl.cls = cls; pl.bf = bf; pl.n_xcd = n_xcd;
         pl.n_teams = (kind == kResident2Pair ? res_chain_xcds(n_xcd) : n_xcd) * (32 / ts);
         pl.units = units; pl.jgroups = jg; pl.nout_m = nout_m; pl.n_tail = n_tail;
-        // Whatever a compute unit holds goes there: hand-overs inside a team are most of such a model's steps (solo.hip).
+        // Models that a work-group decodes alone: hand-overs inside a team are most of their steps (solo.hip).
         pl.solo = solo_holds(H, J, L, NOUT, bf);
         if (pl.solo) pl.n_teams = n_cu;
         return pl;

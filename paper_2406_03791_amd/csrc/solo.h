@@ -1,4 +1,5 @@
-// Decode of models that one compute unit holds: one LSTM layer, no layer wider than 64, at most 64 outputs, fp32.
+// Decode of small models by a work-group per utterance: one LSTM layer, no layer wider than 64, at most 64 outputs, fp32.  (That is what the
+// kernel's threads and tiles are laid out for; a compute unit would hold more.)
 #pragma once
 #include <hip/hip_runtime.h>
 

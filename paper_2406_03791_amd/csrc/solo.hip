@@ -1,4 +1,4 @@
-// Decode kernel for models that one compute unit holds (solo.h).
+// Decode kernel for small models (solo.h).
 //
 // One work-group per utterance, and nothing goes from one work-group to another.  Spread over the eight work-groups of a
 // team of the resident kernel, as every model of one layer was, a model of 64 units and 17 outputs spent its steps on hand-overs:
