@@ -1754,7 +1754,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(const DecodeParams p)
                                 pos += max(c.durations[k - p.V1], 1);
                                 c.n[r] = 0;
                             } else if (k == p.blank) {
-                                pos += tdt ? max(dval, 1) : 1;
+                                pos += tdt ? min(max(dval, 1), kFarthest) : 1;
                                 c.n[r] = 0;
                             } else {
                                 found = 1;
@@ -1784,7 +1784,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(const DecodeParams p)
                     const int r = g + w.lane * G;
                     const int dval = c.hold_d[r];
                     emit_row(p, w, r, c.hold_k[r], c.t[r], c.hold_v[r], c.hold_lp[r], dval);
-                    if (tdt && dval > 0) { c.t[r] += dval; c.n[r] = 0; }
+                    if (tdt && dval > 0) { c.t[r] += min(dval, kFarthest); c.n[r] = 0; }
                     else { c.n[r] += 1; if (c.n[r] == p.S) { c.t[r] += 1; c.n[r] = 0; } }
                     c.active[r] = c.t[r] < c.len[r];
                     c.emitted[r] = 1;

@@ -858,7 +858,8 @@ int rnnt_engine_create(const rnnt_model_desc *desc, int32_t max_B, int32_t max_T
     struct Guard { rnnt_engine *e; ~Guard() { delete e; } } guard{e};
     e->d = d;
     e->d.durations = nullptr;
-    for (int i = 0; i < d.D; ++i) e->durations[i] = d.durations[i];
+    // (a big blank's span is not reported, so it is limited here)
+    for (int i = 0; i < d.D; ++i) e->durations[i] = multi_blank ? std::min(d.durations[i], kFarthest) : d.durations[i];
     e->NOUT = d.V1 + d.D;
     e->max_B = max_B; e->max_T = max_T;
     e->plan_B = std::min((int)max_B, kLaunchRows);

@@ -23,6 +23,7 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kBlocksPerWg = kWaves * 16;   // 4-lane MFMA blocks per work-group
 constexpr int kMaxLayers = 4;
 constexpr int kMaxDur = 8;
+constexpr int kFarthest = 1 << 30;   // frames that a duration moves on by at most: to the end of any utterance, and no frame number overflows
 constexpr int kMaxRows = 16;         // utterances per team
 constexpr int kMaxSamples = 32;      // (utterance, frame) pairs per joint step
 constexpr int kStepUnroll = 4;       // weight loads (16 bytes per lane) per software-pipeline batch

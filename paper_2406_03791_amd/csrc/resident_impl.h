@@ -1729,7 +1729,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 if (to < 0) to += la;
                 int d = 0;
                 if (mine >= p.V1) d = max(rc.dur[(mine - p.V1) & (kMaxDur - 1)], 1);            // big blank: its span of frames
-                else if (mine == p.blank) d = p.tdt ? max(rc.s_d[lane & (kResSamples - 1)], 1) : 1;
+                else if (mine == p.blank) d = p.tdt ? min(max(rc.s_d[lane & (kResSamples - 1)], 1), kFarthest) : 1;
                 if (pidx < 0) d = 0;
                 to += d;
                 int at = ms + to;
@@ -1765,7 +1765,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     }
                 }
                 ++w.cnt;
-                if (p.tdt && dval > 0) { adv += dval; w.n = 0; }
+                if (p.tdt && dval > 0) { adv += min(dval, kFarthest); w.n = 0; }
                 else if (++w.n == p.S) { ++adv; w.n = 0; }
             }
             w.t += adv;

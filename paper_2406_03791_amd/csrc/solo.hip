@@ -288,7 +288,7 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
                 while (pos < NF && pos < left) {
                     const int k = __builtin_amdgcn_readlane(mine, pos);
                     if (k != p.blank && k < p.V1) { found = true; break; }
-                    pos += max(k >= p.V1 ? __builtin_amdgcn_readfirstlane(durations[(k - p.V1) & (kMaxDur - 1)]) : (tdt ? __builtin_amdgcn_readlane(dur, pos) : 1), 1);
+                    pos += max(k >= p.V1 ? __builtin_amdgcn_readfirstlane(durations[(k - p.V1) & (kMaxDur - 1)]) : (tdt ? min(__builtin_amdgcn_readlane(dur, pos), kFarthest) : 1), 1);
                 }
             }
             int adv = pos;
@@ -309,7 +309,7 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
                     }
                 }
                 ++cnt;
-                if (tdt && d > 0) { adv += d; n = 0; }
+                if (tdt && d > 0) { adv += min(d, kFarthest); n = 0; }
                 else if (++n == p.S) { ++adv; n = 0; }
             }
             t = adv >= left ? len : t + adv;

@@ -9,8 +9,10 @@ import dataclasses
 import numpy as np
 import pytest
 
+import oracle
 import synth
-from test_gpu_parity import check, pkg  # noqa: F401  (pkg: fixture)
+from parity_util import compare
+from test_gpu_parity import N_THREADS, check, pkg, run_gpu  # noqa: F401  (pkg: fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -248,6 +250,29 @@ def test_durations_that_are_no_numbers(pkg, H, J, V1, L, bf16, durations):  # no
     _, got, _ = check(pkg, w, "tdt", f"NaN durations {H}/{L}/{bf16} {durations}", engine=eng, bf16=bf16)
     durs = np.concatenate(got["durs"])           # (in the bfloat16 mode another one would pass for a tie)
     assert len(durs) > w.B and (durs == durations[0]).all()
+    eng.close()
+
+
+@pytest.mark.parametrize("H,J,V1,L", [(64, 64, 40, 1), (128, 124, 100, 1), (320, 316, 257, 1), (324, 332, 520, 2)])
+@pytest.mark.parametrize("extra", [dict(durations=(0, 2**31 - 1, 1, 2)), dict(durations=(1, 2, 3, 2**31 - 20)), dict(big_blanks=(2, 2**31 - 1))])
+@pytest.mark.parametrize("streaming", [False, True])
+def test_durations_beyond_any_utterance(pkg, H, J, V1, L, extra, streaming):  # noqa: F811
+    """Durations and spans up to the largest int end an utterance from any frame, as 2^30 does, and are reported as they are."""
+    w = model_inputs(H, J, V1, L, B=21, T=29, seed=H + 1, **extra)
+    w.model.b_out[w.model.dims.blank] -= 0.7
+    eng = pkg.Engine(w.model, w.B, w.T)
+    if streaming:
+        eng.configure(search_steps=2)
+    short = lambda v: tuple(min(d, 2**30) for d in v)  # noqa: E731
+    dims = dataclasses.replace(w.model.dims, durations=short(w.model.dims.durations), big_blanks=short(w.model.dims.big_blanks))
+    near = dataclasses.replace(w, model=dataclasses.replace(w.model, dims=dims, durations=np.minimum(w.model.durations, 2**30)))
+    net = oracle.LstmNet(near.model)
+    ref = oracle.decode(net, w.enc_out, w.enc_len, w.max_symbols, "seq", n_threads=N_THREADS)
+    got, status, _ = run_gpu(eng, w, w.variant, w.max_symbols)
+    assert status == 0 and ref.tok_len.sum() > w.B // 2
+    assert set(np.concatenate(got["durs"])) <= set(w.model.dims.durations or (0,))
+    got["durs"] = [np.minimum(d, 2**30) for d in got["durs"]]
+    assert not compare(near, net, ref, got, w.max_symbols)
     eng.close()
 
 
