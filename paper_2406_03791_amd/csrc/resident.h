@@ -117,7 +117,7 @@ struct ResidentParams {
     const unsigned long long *p_top;
     unsigned long long *p_call;
     const float *T0, *bias_l, *b_pred, *b_out;
-    unsigned char *xbuf;  // exchange buffers, resident_buf(kind, cls).bytes per team
+    unsigned char *xbuf;  // exchange buffers, resident_buf(kind, bf, cls).bytes per team
     unsigned *form;       // one word per work-group, zero at launch: the XCD it runs on
     unsigned *abort_flag;
     int *status;
@@ -126,15 +126,44 @@ struct ResidentParams {
     int count_rows;       // prediction steps are counted per utterance (Algorithm 1) instead of per team
 };
 
+// The joint's operand z as it travels: [tile of 16 samples][wave][piece][lane], as the waves' matrix instructions take it.  Of a block of 32
+// k's (a half block of 16) a lane has the eight (four) from 8 * (lane / 16) (4 * ...) on of sample lane % 16: fp32 in two pieces (one) of
+// 16 bytes, bf16 in one (in half of one).
+RNNT_HD constexpr unsigned res_z_wave(bool bf, int cls)
+{
+    return (unsigned)(bf ? res_halves(cls) / 2 * 1024 + res_halves(cls) % 2 * 512 : res_halves(cls) * 1024);
+}
+RNNT_HD constexpr unsigned res_z_slot(bool bf, int cls) { return kResSamples / 16 * kResWaves * res_z_wave(bf, cls); }
+// Place of the four values from 4 * k4 on of sample s
+RNNT_HD constexpr unsigned res_z_at(bool bf, int cls, int k4, int s)
+{
+    const int full = res_halves(cls) / 2, per = res_halves(cls) * 4, wave = k4 / per, in = k4 % per;
+    const unsigned at = (unsigned)(s / 16 * kResWaves + wave) * res_z_wave(bf, cls);
+    if (in < full * 8) {
+        const unsigned lane = (unsigned)(in % 8 / 2 * 16 + s % 16);
+        return bf ? at + (unsigned)(in / 8) * 1024u + lane * 16u + (unsigned)(in % 2) * 8u : at + (unsigned)(in / 8 * 2 + in % 2) * 1024u + lane * 16u;
+    }
+    const unsigned lane = (unsigned)((in - full * 8) * 16 + s % 16);
+    return bf ? at + (unsigned)full * 1024u + lane * 8u : at + (unsigned)full * 2048u + lane * 16u;
+}
+// The first group of four values in the 16 bytes at `at` of a slot (bf16: the 16 bytes hold two, of one sample or of two)
+RNNT_HD constexpr int res_z_k4(bool bf, int cls, unsigned at)
+{
+    const unsigned full = (unsigned)res_halves(cls) / 2u, in = at % res_z_wave(bf, cls), first = at / res_z_wave(bf, cls) % kResWaves * (unsigned)res_halves(cls) * 4u;
+    const unsigned piece = in / 1024u, g = in / 256u % 4u;
+    if (piece < full * (bf ? 1u : 2u)) return (int)(first + (bf ? piece * 8u + 2u * g : piece / 2u * 8u + 2u * g + piece % 2u));
+    return (int)(first + full * 8u + (bf ? in % 1024u / 128u : g));
+}
+
 // Byte offsets of a team's exchange buffers, every vector in kResSlots slots.
 // hr, pre: kResident2Pair; pre: [layer][slot][quarter of K][rank][wave of the cells][lane]
-struct ResidentBuf { unsigned h[2], q, key, dur, lse, hr[2], pre, bytes; };
-RNNT_HD constexpr ResidentBuf resident_buf(int kind, int cls)
+struct ResidentBuf { unsigned h[2], z, key, dur, lse, hr[2], pre, bytes; };
+RNNT_HD constexpr ResidentBuf resident_buf(int kind, bool bf, int cls)
 {
     const unsigned vec = kResSlots * (unsigned)(kResRows * res_width(cls)) * 4u;
     const unsigned recs = kResSlots * kResSamples * (unsigned)res_team(cls);
     ResidentBuf b{};
-    b.h[0] = 0; b.h[1] = vec; b.q = 2 * vec; b.key = 3 * vec;
+    b.h[0] = 0; b.h[1] = vec; b.z = 2 * vec; b.key = b.z + kResSlots * res_z_slot(bf, cls);
     b.dur = b.key + recs * 8u;
     b.lse = b.dur + kResSlots * kResSamples * kMaxDur * 4u;
     b.hr[0] = b.hr[1] = b.pre = b.bytes = b.lse + recs * 4u;
@@ -155,32 +184,34 @@ RNNT_HD constexpr int res_main_regs(int kind, bool bf, int cls)
     return (kind == kResident2 ? 3 : 1) * res_lstm_regs(bf, cls) + res_pred_regs(bf, cls) + res_joint_regs(bf, cls);
 }
 
-// LDS layout in bytes (dynamic part).  p: frames of the joint step's samples.  part: the joint step's partial sums;
+// LDS layout in bytes (dynamic part).  p: the work-group's columns of the frames of the joint step's samples, 16 bytes for every lane of the
+// waves that form the operand, z_at: their places of it.  part: the joint step's partial sums;
 // before it, in their place, those of the input stage (ih).  proj: partial sums of the projection (read after
 // the work-group's last barrier before the joint step).  rec0, rec: those of the first and of the top layer's
 // recurrent stage, kept till the next prediction step.
-// q: every wave's eighth of q, rows of res_q_row floats (zeros beyond the joint width).  tail: the tail column (see output()),
+// other: the partner's weights of the output layer (two tiles of samples).  tail: the tail columns (see output()),
 // tpart: its partial sums.  state: cell state and recurrent pre-activations [layer][field][wave][lane] where they are
 // not in registers.  scale: powers of two of the team's list (fp32).  touch: for words that are loaded for their
 // lines only.
 // nmt: tiles of 16 samples.  Helpers: their own, from 0 on.
-struct ResidentLds { int p, part, ih, rec0, proj, rec, q, tail, tpart, state, scale, touch, bytes; };
+struct ResidentLds { int p, z_at, part, ih, rec0, proj, rec, other, tail, tpart, state, scale, touch, bytes; };
 constexpr int kResSumRow = 36;            // floats per row of partial sums: of the joint step, of the projection
 constexpr int kResStageRow = 80;          // and of the LSTM stages
-RNNT_HD constexpr int res_q_row(int cls) { return res_row(cls) / 8 + 4; }
-RNNT_HD constexpr ResidentLds resident_lds(int kind, int cls, int nmt)
+constexpr int kResAlone = 81 * 1024;      // at least: more than half of a compute unit's, which so has one work-group, however few registers that takes
+RNNT_HD constexpr ResidentLds resident_lds(int kind, bool bf, int cls, int nmt)
 {
     ResidentLds l{};
     const int stage = kResWaves * kResRows * kResStageRow * 4, sums = kResWaves * 16 * nmt * kResSumRow * 4;
     l.p = 0;
-    l.part = l.ih = 16 * nmt * res_row(cls) * 4;
+    l.z_at = l.p + 3 * 64 * 16;
+    l.part = l.ih = l.z_at + 3 * 64 * 4;
     int at = l.ih + (kind == kResident1 ? 0 : stage);
     if (at < l.part + sums) at = l.part + sums;
     l.proj = at; at += kResWaves * kResRows * kResSumRow * 4;
     if (kind == kResident2) { l.rec0 = at; at += stage; }
     l.rec = at; at += kind == kResident2Pair ? 0 : stage;
-    l.q = at; at += kResWaves * kResRows * res_q_row(cls) * 4;
-    l.tail = at; at += (kind == kResident2 ? 2 : res_halves(cls) == 1 ? 4 : 3) * res_row(cls) * 2;
+    l.other = at; at += nmt == 2 ? kResWaves * res_joint_regs(bf, cls) * 256 : 0;
+    l.tail = at; at += (bf ? nmt + 1 : res_whole(bf, cls) ? 2 * nmt + 2 : 2 * nmt + 1) * res_row(cls) * 2;
     l.tpart = at; at += kResWaves * 2 * 16 * 4;
     l.state = at; at += kind == kResident2Pair ? 6 * 5 * 64 * 4 : 0;
     l.scale = at; at += kind == kResident2 ? 0 : kResList * 4;
@@ -188,11 +219,12 @@ RNNT_HD constexpr ResidentLds resident_lds(int kind, int cls, int nmt)
     const int help = 2048 + 2 * (kResServed / 2) * res_help_blocks(cls) * 1024;
     if (kind == kResident2Pair && at < help) at = help;
     l.bytes = (at + 15) & ~15;
+    if (l.bytes < kResAlone) l.bytes = kResAlone;
     return l;
 }
 constexpr int kResCtl = 5376;             // bytes kept for the control block and votes
-static_assert(resident_lds(kResident1, 0, 2).bytes + kResCtl <= 160 * 1024 && resident_lds(kResident2, 0, 2).bytes + kResCtl <= 160 * 1024 &&
-              resident_lds(kResident2Pair, 0, 2).bytes + kResCtl <= 160 * 1024, "the largest layouts and the control block fit the LDS");
+static_assert(resident_lds(kResident1, false, 0, 2).bytes + kResCtl <= 160 * 1024 && resident_lds(kResident2, true, 0, 2).bytes + kResCtl <= 160 * 1024 &&
+              resident_lds(kResident2Pair, false, 0, 2).bytes + kResCtl <= 160 * 1024, "the largest layouts and the control block fit the LDS");
 
 // The model's matrices on the device (rows as in the model), and where their packed forms go: register images of the
 // teams' and the helpers' work-groups, [rank][wave][runs of registers, see res_place]; tail columns; what sums are multiplied by; the

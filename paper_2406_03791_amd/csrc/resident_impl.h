@@ -14,9 +14,17 @@
 // Work split inside a team of `ts` work-groups: LSTM units, projection columns and output columns
 // in contiguous ranges.  Every dense stage is the same: K in eighths over the waves, tiles of 16 outputs
 // (the gates of four units, or columns) by 16 columns of the operand on v_mfma 16x16x32, and the waves' partial sums
-// meet in LDS.  Columns of the LSTM stages and the projection are the team's utterances, which a wave receives
-// straight into the operand's registers (Operand); those of the joint output are samples, whose operand relu(P + q)
-// is formed on the way from LDS to the matrix instruction.
+// meet in LDS.  Columns of the LSTM stages and the projection are the team's utterances, those of the joint output are samples.
+// A wave receives its eighth of an operand straight into registers (Operand; the joint's: ask_z).
+//
+// The joint's operand z = relu(P + q) is formed once in the team: every work-group has its own columns of the projection, adds
+// those of the samples' frames (80 bytes a sample) and hands z on in q's place.  Formed from q by every work-group for itself it took
+// nine vector instructions for two values and two LDS reads, 32 times over, and the samples' whole frames in LDS, 80 KB.  What
+// bounds the hand-over is the size: a compute unit takes 8 KB in 0.11 us (32 of them the same 8 KB of an XCD's L2), 16 fp32 samples of
+// 640 in 0.94 us where q of four utterances takes 0.75.  So 32 samples go to a work-group as one tile of 16, for its own
+// and its partner's columns (`half`): as two tiles, for its own columns alone, they took longer than q did (32 utterances 1208 us with
+// q, 1249, and 1160 with half; partners' weights in the frames' place in LDS).  Against q handed on: 32 utterances (three draws) 1083, 1318, 1359 us and
+// 1037, 1264, 1303, bfloat16 mode 850, 925, 925 and 777, 846, 843, 128 utterances 3967 and 3808, one 281 and 278, the small model 344 and 320.
 //
 // fp32 values run on the 16-bit matrix instructions as two fp16 parts each, weights and vectors alike: 23 bits,
 // all four products (the joint of the widest class: three, see there), fp32 sums.  On the fp32 instructions a step's stages were
@@ -79,7 +87,7 @@ struct RRows {
     static constexpr int kPlaces = 8;
     static_assert(kResRows <= kPlaces, "a place for every row");
     RRow s[kPlaces];
-    int b[kPlaces], m[kPlaces];       // utterance; place of frame t among the row's samples, a ring (0 when they are dealt anew)
+    int b[kPlaces];                   // utterance
     int since[kPlaces], next;         // t some steps ago; first utterance of the list that no row has had
 };
 
@@ -94,10 +102,10 @@ struct RCtl {
     int list_len[kResList];
     // this work-group's slices of the biases: second layer [unit][gate], projection, output and tail column; and of
     // what sums are multiplied by (fp32): the same and [layer][unit][gate] of the recurrent matrices
-    float b1[kResUnits * 4], bp[20];
-    float s1[kResUnits * 4], sp[20], sh[2][kResUnits * 4];
-    float2 bo[16], so[16];
-    float bt, st;
+    float b1[kResUnits * 4], s1[kResUnits * 4], sh[2][kResUnits * 4];
+    __align__(16) float bp[24], sp[24];
+    float2 bo[2][16], so[2][16];      // with two tiles of samples: of this work-group and its partner, the even rank first
+    float bt[2], st[2];
     float scale[kResRows];            // fp32: of the utterances in work, see joint_scale
 };
 __shared__ RCtl rc;
@@ -173,6 +181,13 @@ struct RCtx {
     int polls;
 };
 
+// The mark, in a register only where it is stored: constants of two and four words took six registers for the whole loop.
+__device__ __forceinline__ unsigned mark_here()
+{
+    unsigned m;
+    asm volatile("v_mov_b32 %0, -1" : "=v"(m));
+    return m;
+}
 // A word for the team, and the mark into the slot that everyone has read (byte offsets `now` and `old` of
 // the slots): stores that stay in the XCD's L2, or go through to the memory side (sc1).
 __device__ __forceinline__ void put(const RCtx &x, unsigned off, unsigned now, unsigned old, unsigned v)
@@ -187,7 +202,8 @@ __device__ __forceinline__ void put(const RCtx &x, unsigned off, unsigned now, u
 }
 __device__ __forceinline__ void put2(const RCtx &x, unsigned off, unsigned now, unsigned old, r2u v)
 {
-    const r2u mark = {kMark, kMark};
+    const unsigned m = mark_here();
+    const r2u mark = {m, m};
     if (x.local) {
         __builtin_amdgcn_raw_buffer_store_b64(v, x.buf, (int)off, (int)now, 0);
         __builtin_amdgcn_raw_buffer_store_b64(mark, x.buf, (int)off, (int)old, 0);
@@ -203,7 +219,8 @@ __device__ __forceinline__ void put_mark(const RCtx &x, unsigned off, unsigned o
 }
 __device__ __forceinline__ void put_mark2(const RCtx &x, unsigned off, unsigned old)
 {
-    const r2u mark = {kMark, kMark};
+    const unsigned m = mark_here();
+    const r2u mark = {m, m};
     if (x.local) __builtin_amdgcn_raw_buffer_store_b64(mark, x.buf, (int)off, (int)old, 0);
     else __builtin_amdgcn_raw_buffer_store_b64(mark, x.buf, (int)off, (int)old, 16);
 }
@@ -215,6 +232,10 @@ __device__ __forceinline__ void put_far(const RCtx &x, unsigned off, unsigned im
 __device__ __forceinline__ r4u get4(const RCtx &x, unsigned off, unsigned imm)
 {
     return __builtin_bit_cast(r4u, __builtin_amdgcn_raw_buffer_load_b128(x.buf, (int)off, (int)imm, 16));
+}
+__device__ __forceinline__ r2u get2(const RCtx &x, unsigned off, unsigned imm)
+{
+    return __builtin_bit_cast(r2u, __builtin_amdgcn_raw_buffer_load_b64(x.buf, (int)off, (int)imm, 16));
 }
 __device__ __forceinline__ unsigned get1(const RCtx &x, unsigned off, unsigned imm)
 {
@@ -553,41 +574,6 @@ __device__ __forceinline__ void res_finish_row(int b, int cnt)
     if (a->done) __hip_atomic_store(a->done + b, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Loads row `row` of the projected frames into sample s's place in LDS, straight from memory.  The
-// 16-byte piece k4 goes to position (k4 with its low four bits xored with s), so that sixteen samples'
-// pieces of the same k sit in different banks.  (The instruction's offset counts on both sides.)
-template <int CLS>
-__device__ __forceinline__ void load_frame(const ResidentParams &p, const RCtx &x, unsigned lds_p, int row, int s)
-{
-    constexpr int ROW = res_row(CLS);
-    const int lane = lane_id(), j4 = p.J >> 2, k4 = lane ^ (s & 15);
-    const char *src = reinterpret_cast<const char *>(p.P + (long long)row * p.J);
-    const unsigned m = (unsigned)__builtin_amdgcn_readfirstlane((int)(lds_p + (unsigned)(s * ROW * 4)));
-    // A row that fills its place (no joint layer does in the middle class): all of it, with no branch around a load.  The last load takes half
-    // a wave, with all of its lanes on before and after: which waves load which samples goes by wave, so they are.  (m0 is
-    // reserved: the compiler keeps nothing in it.)
-    if constexpr (ROW == res_width(CLS)) if (j4 == ROW / 4) {
-        const unsigned off = (unsigned)k4 * 16u;
-        static_assert(ROW % 256 == 128, "whole waves, and a half one");
-        if constexpr (ROW / 256 == 2)
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\tglobal_load_lds_dwordx4 %0, %2 offset:1024\n\t"
-                         "s_mov_b32 exec_hi, 0\n\tglobal_load_lds_dwordx4 %0, %2 offset:2048\n\ts_mov_b32 exec_hi, -1" :: "v"(off), "s"(m), "s"(src) : "memory");
-        else {
-            static_assert(ROW / 256 == 0 || ROW / 256 == 2, "written out for these");
-            asm volatile("s_mov_b32 m0, %1\n\ts_mov_b32 exec_hi, 0\n\tglobal_load_lds_dwordx4 %0, %2\n\ts_mov_b32 exec_hi, -1" :: "v"(off), "s"(m), "s"(src) : "memory");
-        }
-        return;
-    }
-    static_for<0, (ROW / 4 + 63) / 64>([&](auto u_) {
-        constexpr int u = decltype(u_)::value;
-        const char *from = src;
-        const unsigned to = m, off = (unsigned)k4 * 16u;
-        if (((u + 1) * 64 <= ROW / 4 || lane < ROW / 4 - u * 64) && u * 64 + k4 < j4)
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 offset:%3"
-                         :: "v"(off), "s"(to), "s"(from), "n"(u * 1024) : "memory");
-    });
-}
-
 __device__ __forceinline__ int from_lane(int v, int lane) { return __builtin_amdgcn_ds_bpermute(lane << 2, v); }
 
 // KIND: ResidentKind; BF: bfloat16 mode; CLS: size class; NMT: tiles of 16 samples of a joint step
@@ -604,9 +590,13 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     typedef Operand<BF, CLS, R> Op;
     constexpr bool HALVES = PAIR && NMT == 2;     // steps with one tile of samples as well, see after the loop
     constexpr int NREC = PAIR ? 0 : NL;          // recurrent matrices the chain's work-groups hold
-    constexpr ResidentBuf bo = resident_buf(KIND, CLS);
-    constexpr ResidentLds lo = resident_lds(KIND, CLS, NMT);
+    constexpr ResidentBuf bo = resident_buf(KIND, BF, CLS);
+    constexpr ResidentLds lo = resident_lds(KIND, BF, CLS, NMT);
     constexpr unsigned VROW = W * 4u, VSLOT = R * VROW;                      // h and q rows
+    constexpr unsigned ZSLOT = res_z_slot(BF, CLS), ZWAVE = res_z_wave(BF, CLS);   // the joint's operand
+    constexpr int JREGS = res_joint_regs(BF, CLS);
+    constexpr int ZS = 16 * NMT;                 // samples of the longest joint step
+    constexpr int kFormers = 3;                  // see publish_z
     constexpr unsigned KSLOT = kResSamples * TS * 8u, DSLOT = kResSamples * kMaxDur * 4u;
     constexpr unsigned QSLOT = TS * 5u * 64u * 4u, PSLOT = kResQuarters * QSLOT;         // pre-activations: a quarter of K, all
 
@@ -647,7 +637,15 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             __builtin_amdgcn_raw_buffer_store_b128(mark, x.buf, (int)o, 0, 16);
     };
     if (!helper) {
-        put_marks(0u, bo.pre);
+        put_marks(0u, bo.z);
+        put_marks(bo.key, bo.pre);
+        // (of the operand beyond the joint width, which nobody sends: zeros)
+        const int j4 = p.J >> 2;
+        for (unsigned o = ((unsigned)x.rank * kResThreads + (unsigned)tid0) * 16u; o < kResSlots * ZSLOT; o += TS * kResThreads * 16u) {
+            const int k4 = res_z_k4(BF, CLS, o % ZSLOT);
+            const unsigned a = k4 < j4 ? kMark : 0u, b = BF && (o % ZWAVE) < (unsigned)NF * 1024u ? (k4 + 1 < j4 ? kMark : 0u) : a;
+            __builtin_amdgcn_raw_buffer_store_b128((r4u){a, a, b, b}, x.buf, (int)(bo.z + o), 0, 16);
+        }
     } else {
         bool any = false;
         for (int i = 0; i < kResServed; ++i)
@@ -668,7 +666,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     if (tid0 < kResRows) rc.scale[tid0] = 1.f;
     if (lane0 < kResRows) {
         RRows &w = rc.rows[x.wave];
-        w.s[lane0] = RRow{0, 0, 0, 0}; w.b[lane0] = w.m[lane0] = w.since[lane0] = w.next = 0;
+        w.s[lane0] = RRow{0, 0, 0, 0}; w.b[lane0] = w.since[lane0] = w.next = 0;
     }
     for (int i = tid0 * 16; i < lo.bytes; i += kResThreads * 16) *reinterpret_cast<r4u *>(lds + i) = (r4u){0, 0, 0, 0};
     // the marks have to be in memory before this work-group says that it is there
@@ -883,9 +881,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // two layers).  With the weights asked for before all that, the same call took 0.6 % longer.
     // fp32: what the joint's operands of an utterance are multiplied by, see joint_scale
     float *list_scale = reinterpret_cast<float *>(lds + lo.scale);
-    // (the lengths, in the frames' place)
-    static_assert(kResList * (CLS == 0 ? 8 : CLS == 1 ? 16 : 32) * 4 <= 32 * ROW * 4, "the lengths of a launch fit the places of 32 frames");
-    int *lengths = reinterpret_cast<int *>(lds + lo.p);
+    // (the lengths, in the place of the joint step's sums)
+    static_assert(kResList * (CLS == 0 ? 8 : CLS == 1 ? 16 : 32) * 4 <= kResWaves * 16 * NMT * kResSumRow * 4, "the lengths of a launch fit there");
+    int *lengths = reinterpret_cast<int *>(lds + lo.part);
     for (int b = tid0; b < p.B; b += kResThreads) {
         const int raw = p.enc_len[b];
         if (raw < 0 || raw > p.T) rc.st_clamped = 1;
@@ -893,19 +891,16 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     }
     const int u0 = x.rank * p.pl.units, nu = max(0, min(p.pl.units, p.H - u0));
     const int g0 = x.rank * p.pl.jgroups, njg = max(0, min(p.pl.jgroups, (p.J >> 2) - g0));
-    // A column of the tail: with two tiles of samples for those of one, if there are ranks enough, so that the others wait for half
-    // of what it takes beside the 32 columns of every work-group (0.45 us a step of two tiles; bfloat16 mode 0.39.  32
-    // utterances 1366 us with all samples in one work-group, 1345 with two, bfloat16 mode 867 and 844).
-    const bool share = NMT == 2 && p.pl.n_tail * 2 <= TS;
-    const int tcol = p.pl.nout_m + (share ? x.rank >> 1 : x.rank);
-    const bool has_tail = tcol < p.pl.nout_m + p.pl.n_tail;
-    const unsigned tails = !has_tail ? 0u : share ? 1u << (x.rank & 1) : 3u;      // the tiles, a bit each
-    auto tail_for = [&](int tile) { return NMT == 1 ? has_tail : (tails >> tile & 1u) != 0u; };
-    const int n_tok = min(p.VT, p.pl.nout_m) - x.rank * 32;      // token columns of this work-group's tiles
-    const bool dur_cols = p.tdt && p.VT < p.pl.nout_m && x.rank * 32 + 32 > p.VT;      // they hold duration columns
+    // A joint step of two tiles of samples is shared out by columns and samples: the work-groups of even and the next odd rank have both
+    // their columns, the even one for the first tile, the odd one for the second (`half`), so that what a work-group receives
+    // of the operand is one tile.  Its partner's weights of the output layer are in LDS.  A column of the tail goes with the rank's others.
+    const int half = NMT == 2 ? x.rank & 1 : 0;
+    const int tcol0 = p.pl.nout_m + x.rank - half, n_tails = max(0, min(NMT, p.pl.nout_m + p.pl.n_tail - tcol0));
     {
         const int at = tid0;
-        const bool gate = at < nu * 4, col = at < njg * 4, out = at < 32 && x.rank * 32 + at < p.pl.nout_m;
+        const bool gate = at < nu * 4, col = at < njg * 4;
+        const int ocol = (x.rank - half) * 32 + at;
+        const bool out = at < 32 * NMT && ocol < p.pl.nout_m;
         float b1 = 0.f, s1 = 0.f, sh[NL] = {}, bp = 0.f, sp = 0.f, bo_ = 0.f, so_ = 0.f, bt = 0.f, st = 0.f;
         if (gate) {
             if (NL > 1) { b1 = p.bias_l[((long long)p.H + u0) * 4 + at]; s1 = p.s_ih[u0 * 4 + at]; }
@@ -913,27 +908,29 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             for (int l = 0; l < NREC; ++l) sh[l] = p.s_hh[l][u0 * 4 + at];
         }
         if (col) { bp = p.b_pred[g0 * 4 + at]; sp = p.s_pred[g0 * 4 + at]; }
-        if (out) { bo_ = p.b_out[x.rank * 32 + at]; so_ = p.s_out[x.rank * 32 + at]; }
-        if (at == 0 && has_tail) { bt = p.b_out[tcol]; st = p.s_out[tcol]; }
+        if (out) { bo_ = p.b_out[ocol]; so_ = p.s_out[ocol]; }
+        if (at < n_tails) { bt = p.b_out[tcol0 + at]; st = p.s_out[tcol0 + at]; }
         if (at < kResUnits * 4) {
             rc.b1[at] = b1; rc.s1[at] = s1;
 #pragma unroll
             for (int l = 0; l < NREC; ++l) rc.sh[l][at] = sh[l];
         }
-        if (at < 20) { rc.bp[at] = bp; rc.sp[at] = sp; }
-        if (at < 32) { reinterpret_cast<float *>(rc.bo)[at] = bo_; reinterpret_cast<float *>(rc.so)[at] = so_; }
-        if (at == 0) { rc.bt = bt; rc.st = st; }
+        if (at < 24) { rc.bp[at] = bp; rc.sp[at] = sp; }
+        if (at < 3 * 64) reinterpret_cast<unsigned *>(lds + lo.z_at)[at] = res_z_at(BF, CLS, g0 + at / ZS, at % ZS);
+        if (at < 32 * NMT) { reinterpret_cast<float *>(rc.bo)[at] = bo_; reinterpret_cast<float *>(rc.so)[at] = so_; }
+        if (at < NMT) { rc.bt[at] = bt; rc.st[at] = st; }
     }
-    if (has_tail)
-        for (int i = tid0; i < ROW; i += kResThreads) {
-            const float w = p.w_tail[(long long)(tcol - p.pl.nout_m) * ROW + i];
-            // (rows of 16-bit values: high parts, low parts, zeros; or bf16 values, zeros; or rows of fp32 values, zeros)
-            unsigned short *row = reinterpret_cast<unsigned short *>(lds + lo.tail);
-            unsigned high = __float_as_uint(w) >> 16, low = 0;
-            if (!BF) f16_parts(w, 0.f, high, low);
-            if (WHOLE) reinterpret_cast<float *>(row)[i] = w;
-            else { row[i] = (unsigned short)high; row[ROW + i] = (unsigned short)low; }
-        }
+    for (int i = tid0; i < n_tails * ROW; i += kResThreads) {
+        const int k = i / ROW;
+        const float w = p.w_tail[(long long)(tcol0 - p.pl.nout_m) * ROW + i];
+        // (rows of 16-bit values: high parts, low parts, for either column, zeros; or bf16 values; or rows of fp32 values)
+        unsigned short *row = reinterpret_cast<unsigned short *>(lds + lo.tail);
+        unsigned high = __float_as_uint(w) >> 16, low = 0;
+        if (!BF) f16_parts(w, 0.f, high, low);
+        if (WHOLE) reinterpret_cast<float *>(row)[i] = w;
+        else if (BF) row[i] = (unsigned short)high;
+        else { row[i + k * ROW] = (unsigned short)high; row[i + (k + 1) * ROW] = (unsigned short)low; }
+    }
     __syncthreads();
     // utterances of the team: ranked by length (longest first, ties by index), dealt in serpentine
     // order; empty ones are complete from the start
@@ -950,7 +947,6 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         }
     }
     __syncthreads();
-    for (int b = tid0; b < p.B; b += kResThreads) lengths[b] = 0;
     if constexpr (!BF && !WHOLE) {
         // sixteen lanes to an utterance of the list
         static_assert(kTopParts == 16, "a word for each of sixteen lanes");
@@ -972,6 +968,16 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         if (NL > 1) { load_regs<KIND == kResident2>(w_ih, src, first, lane0); first += LREGS; }
         load_regs<KIND == kResident2>(w_pr, src, first, lane0); first += res_pred_regs(BF, CLS);
         load_regs<KIND == kResident2>(w_ou, src, first, lane0);
+        if constexpr (NMT == 2) {
+            // the partner's, for the same wave
+            static_assert(JREGS % 4 == 0, "whole groups of four registers");
+            const float *from = p.w + ((long long)((x.rank ^ 1) * kResWaves + x.wave) * res_main_regs(KIND, BF, CLS) + first) * 64 + lane0 * 4;
+            const unsigned to = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)(lds + lo.other) + (unsigned)x.wave * (JREGS * 256u);
+#pragma unroll
+            for (int i = 0; i < JREGS / 4; ++i)
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(from + i * 256), "s"(__builtin_amdgcn_readfirstlane((int)(to + i * 1024u))) : "memory");
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
 #pragma unroll
         for (int l = 0; l < NREC; ++l) keep_regs(w_hh[l]);
         if (NL > 1) keep_regs(w_ih);
@@ -991,8 +997,6 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         return l;
     };
     // (joint output: a wave takes every eighth step of K for both column tiles)
-    constexpr int QS = res_q_row(CLS);               // floats per row of a wave's eighth of q
-    float *lq = reinterpret_cast<float *>(lds + lo.q) + x.wave * (R * QS);
     const unsigned lds_p = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)(lds + lo.p);
     float *part = reinterpret_cast<float *>(lds + lo.part);          // joint sums, see there
     float *tpart = reinterpret_cast<float *>(lds + lo.tpart);        // [wave][tile][16]
@@ -1026,8 +1030,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // of the projected frames, -1 for none.
     int last = p.blank, pidx = -1;
     // What a lane needs of the loop control's tables, packed (a register each would be one too many): rows of the
-    // samples lane % 16, 16 + lane % 16, four times the wave plus lane / 16, and lane % 32 (2 bits each, at 0, 14, 16 and 28);
-    // bytes to the word of a row of T0 that its cell takes (2 .. 13); the place of sample lane % 32 among its row's
+    // samples lane / 2, four times the wave plus lane / 16 (of the work-group's tile), and lane (2 bits each, at 0, 16 and 28);
+    // bytes to the word of a row of T0 that its cell takes (2 .. 13); the place of sample `lane` among its row's
     // (5 bits, at 18); its own row's first sample (5, at 23); kTake and kFresh.
     int lane_const = kFresh;
     // Rows that take part in the joint step (one bit in four, as in LEADS), and the frames of each: the samples are dealt
@@ -1051,41 +1055,54 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             if (of >> (r * LR) & 1u) { rows_of |= (unsigned)r << at; at += 2; }
         auto turn_of = [&](int s) { return (s >= la ? 1 : 0) + (s >= 2 * la ? 1 : 0) + (s >= 3 * la ? 1 : 0); };
         auto row_of = [&](int s) { return (int)(rows_of >> (turn_of(s) * 2) & 3u); };
-        const int s = lane & (kResSamples - 1);
+        const int s = lane & (ZS - 1);
         const Place l = place_of(lane);
         const int first = __builtin_popcount(of & ((1u << (lane & 12)) - 1u)) * la;
-        lane_const = row_of(s & 15) | l.gu * 16 + l.j * 4 | row_of(16 + (s & 15)) << 14 | row_of((x.wave * 4 + (lane >> 4)) & 31) << 16 |
+        lane_const = row_of(lane / 2 & (ZS - 1)) | l.gu * 16 + l.j * 4 | row_of(((x.wave * 4 + (lane >> 4)) & 15) + (decltype(nt_)::value == 2 ? half * 16 : 0)) << 16 |
                      ((s - turn_of(s) * la) & 31) << 18 | (first & 31) << 23 | row_of(s) << 28 | (lane_const & (kTake | kFresh));
     };
     std::integral_constant<int, NMT> all_tiles;
-    // Samples of the next joint step: `la` frames of every row in work, each in a place of the row's that it keeps
-    // until the row has passed it (m: the place of the row's frame t, the next ones follow in a ring).  fresh: the samples to load.
-    unsigned long long fresh = 0;
-    auto set_up_samples = [&](int lane, int t, int m, int b, int len) {
+    // Samples of the next joint step: the next `la` frames of every row in work.
+    auto set_up_samples = [&](int lane, int t, int b, int len) {
         const int from = (lane_const >> 28 & 3) * (LR * 4);                         // (bytes: LR lanes per row)
-        const int base = __builtin_amdgcn_ds_bpermute(from, b * p.T + t);
-        const int info = __builtin_amdgcn_ds_bpermute(from, max(0, min(len - t, la)) | m << 8);
-        int off = (lane_const >> 18 & 31) - (info >> 8);
-        if (off < 0) off += la;
-        const int was = pidx;
-        pidx = (lane < part_samples() && off < (info & 255)) ? base + off : -1;
-        fresh = __ballot(pidx >= 0 && pidx != was);
-        n_samples += __popcll(__ballot(pidx >= 0));
+        const int base = __builtin_amdgcn_ds_bpermute(from, b * p.T + t), left = __builtin_amdgcn_ds_bpermute(from, len - t);
+        const int off = lane_const >> 18 & 31;
+        pidx = ((lane & (ZS - 1)) < part_samples() && off < left) ? base + off : -1;
+        n_samples += __popcll(__ballot(pidx >= 0 && lane < ZS));
     };
-    // Loads the samples' frames that are new, of samples `from`, `from` + `step` and so on; `of`: the same ones as bits.  The
-    // waves that do it beside the cells are the last to look for the hidden vector, so an instruction here is one of the
-    // step: with a branch around every load and a look at every sample 32 utterances took 1331, 1357 and 1177 us (three
-    // draws), with neither 1309, 1335 and 1155, TDT 988, 968, 987 and 962, 943, 958.  (One tile, where a wave has few to look at:
-    // over the bits 536 us for one utterance, over the samples 527.)
-    auto load_frames = [&](unsigned of, int from, int step) {
-        if constexpr (NMT == 1) {
-            for (int s = from; s < part_samples(); s += step)
-                if (fresh >> s & 1) load_frame<CLS>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
-        } else {
-            for (unsigned m = (unsigned)fresh & of; m != 0u; m &= m - 1u) {
-                const int s = __builtin_ctz(m);
-                load_frame<CLS>(p, x, lds_p, __builtin_amdgcn_readlane(pidx, s), s);
-            }
+    // Frames of the joint's operand: four columns of sample lane % ZS to LDS, [four columns][sample].
+    auto load_frames = [&](int cg, bool mine) {
+        const unsigned to = (unsigned)__builtin_amdgcn_readfirstlane((int)(lds_p + (unsigned)(cg * ZS) * 16u));
+        const int at = cg + lane_id() / ZS;
+        if (mine && pidx >= 0 && at < njg)
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(p.P + (long long)pidx * p.J + (g0 + at) * 4), "s"(to) : "memory");
+    };
+    // Two columns of a sample for a lane, four columns of 32 samples for a wave (of 16: eight): waves kFormers and after.
+    auto publish_z = [&](auto nt_, unsigned n) {
+        const int lane = lane_id(), s = lane / 2 & (ZS - 1), cg = (x.wave - kFormers) * (32 / ZS) + lane / (2 * ZS), row = lane_const & 3;
+        const float *v = sums_pr + row * kResSumRow + cg * 4 + (lane & 1) * 2;
+        r2f o[kResWaves];
+#pragma unroll
+        for (int w = 0; w < kResWaves; ++w) o[w] = *reinterpret_cast<const r2f *>(v + w * (R * kResSumRow));
+        const r2f frame = *reinterpret_cast<const r2f *>(lds + lo.p + (cg * ZS + s) * 16 + (lane & 1) * 8);
+        const unsigned to = reinterpret_cast<const unsigned *>(lds + lo.z_at)[cg * ZS + s] + (lane & 1) * (BF ? 4u : 8u);
+        const r2f bias = *reinterpret_cast<const r2f *>(rc.bp + cg * 4 + (lane & 1) * 2), by = *reinterpret_cast<const r2f *>(rc.sp + cg * 4 + (lane & 1) * 2);
+        float scale = 1.f;
+        if constexpr (!BF && !WHOLE) scale = rc.scale[row];
+        const r2f sum = ((o[0] + o[1]) + (o[2] + o[3])) + ((o[4] + o[5]) + (o[6] + o[7]));
+        float z[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const float q = BF ? sum[i] + bias[i] : WHOLE ? fmaf(sum[i], by[i], bias[i]) : fmaf(sum[i], by[i], bias[i]) * scale;
+            z[i] = fmaxf(BF || WHOLE ? frame[i] + q : fmaf(frame[i], scale, q), 0.f);
+        }
+        const unsigned now = bo.z + slot_at(n, ZSLOT), old = bo.z + slot_at(n + 2, ZSLOT);
+        if (cg < njg) {
+            if (decltype(nt_)::value < NMT && s >= 16 * decltype(nt_)::value) {
+                if constexpr (BF) put_mark(x, to, old);
+                else put_mark2(x, to, old);
+            } else if constexpr (BF) put(x, to, now, old, bf16_pair(z[0], z[1]));
+            else put2(x, to, now, old, (r2u){__float_as_uint(z[0]), __float_as_uint(z[1])});
         }
     };
     // Rows that want one get the next utterances of the list.  (Control state is by row: every lane works on
@@ -1114,7 +1131,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         any_active = need_pred = m != 0ull;
         row_steps = __popcll(m);
         lay_out(all_tiles, lane0, (unsigned)m);
-        set_up_samples(lane0, 0, 0, b, len);
+        set_up_samples(lane0, 0, b, len);
     }
     // the row of the embedding table (folded into the first layer) that the next prediction step adds
     float t0 = 0.f;
@@ -1158,6 +1175,34 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     constexpr int NS = 16 * NT;
     bool change = false;
     while (ok && any_active && !change) {
+        const unsigned jn = ++n_joint;
+        // A wave's part of the operand, an eighth of K of a tile's samples
+        constexpr int PIECES = BF ? NB : NH;
+        r4u zw[PIECES];
+        auto ask_z = [&]() {
+            const unsigned lane = (unsigned)lane_id(), at = bo.z + slot_at(jn, ZSLOT) + (unsigned)((NT == 2 ? half * kResWaves : 0) + x.wave) * ZWAVE;
+#pragma unroll
+            for (int i = 0; i < PIECES; ++i) {
+                if (BF && i == NF) {
+                    const r2u v = get2(x, lane * 8u, at + i * 1024u);
+                    zw[i] = (r4u){v.x, v.y, 0u, 0u};
+                } else zw[i] = get4(x, lane * 16u, at + i * 1024u);
+            }
+        };
+        // Waits for the words that were asked for; the largest one (they are not negative, so as a float too)
+        auto wait_z = [&]() {
+            unsigned spins = 0, m;
+            for (;;) {
+                m = 0u;
+#pragma unroll
+                for (int i = 0; i < PIECES; ++i) m = max(max(max(zw[i].x, zw[i].y), max(zw[i].z, zw[i].w)), m);
+                if (__ballot(m == kMark) == 0ull) break;
+                if (wait_expired(p, spins)) { rc.ok = 0; break; }
+                ask_z();
+            }
+            x.polls += __builtin_amdgcn_readfirstlane((int)spins);
+            return __uint_as_float(m);
+        };
         if (need_pred) {
             // ---- prediction step -----------------------------------------------------------------
             ++n_pred;
@@ -1225,15 +1270,15 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 if (NMT == 2 && later) {
                     const int lane = lane_id(), r = (int)((unsigned)lane / LR) & (R - 1);
                     const RRow o = rows.s[r];
-                    set_up_samples(lane, o.t, rows.m[r], rows.b[r], o.len);
+                    set_up_samples(lane, o.t, rows.b[r], o.len);
                     later = false;
                 }
                 RES_MARK(1);
                 x1.receive_from(p, x, bo.h[0] + slot_at(n, VSLOT), h4);
             } else {
-                // The frames of the joint step, by the waves that have the least to do here.  A wave's loads return in
+                // The work-group's columns of the joint step's frames, by the waves that have the least to do here.  A wave's loads return in
                 // order, so these waves see the hidden vector when their frames are there: at about the time it comes.
-                load_frames(0x49249249u << (x.wave - 5), x.wave - 5, kResWaves - 5);
+                load_frames((x.wave - 5) * (64 / ZS), true);
                 if constexpr (FRAMES_FIRST) __builtin_amdgcn_s_setprio(0);
                 x1.receive_from(p, x, bo.h[0] + slot_at(n, VSLOT), h4);
                 asm volatile("" :: "v"(t0), "v"(pre[0][0]), "v"(pre[0][1]), "v"(pre[0][2]), "v"(pre[0][3]));
@@ -1294,77 +1339,31 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             RES_MARK(6);
             // prediction-side joint projection
             stage<BF, CLS, R, 2, kResSumRow>(w_pr, x1, sums_pr, x.wave);
-            // this wave's frames are in LDS (what the other waves have stored by now, marks too, their polls for q wait for)
+            // this wave's frames are in LDS (what the other waves have stored by now, marks too, their polls for z wait for)
             if (x.wave >= 5) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            {
-                // LR adjacent threads per value (group of four columns, column, row), R / 2 waves' sums each
-                const int tid = (x.wave * 64 + lane_id()), col = tid >> 4, r = (int)((unsigned)tid / LR) & (R - 1);
-                if (col < njg * 4) {
-                    const float *v = sums_pr + ((tid & (LR - 1)) * (R / 2) * R + r) * kResSumRow + col;
-                    float o = v[0];
-#pragma unroll
-                    for (int i = 1; i < R / 2; ++i) o += v[i * R * kResSumRow];
-                    o = lane_sum<LR>(o);
-                    o = BF ? o + rc.bp[col] : fmaf(o, rc.sp[col], rc.bp[col]);
-                    if constexpr (!BF && !WHOLE) o *= rc.scale[r];
-                    if ((tid & (LR - 1)) == 0 && r < p.slots)
-                        put(x, (unsigned)r * VROW + (unsigned)(g0 * 4 + col) * 4u, bo.q + slot_at(n, VSLOT), bo.q + slot_at(n + 2, VSLOT), word_of(o));
-                }
-            }
+            if (x.wave >= kFormers) publish_z(nt_, jn);
             RES_MARK(7);
-            // (while q is on its way) the recurrent part of the top layer's next step
-            {
-                // the wave's eighth of q, NH * 4 pieces a row
-                constexpr int PW = NH * 4, N = (R * PW + 63) / 64;
-                constexpr bool EARLY = NREC > 0 && NF > 0;
-                constexpr unsigned INV = (65536u + PW - 1u) / PW;         // i / PW for i < 256
-                r4u v[N];
-                const int j4 = p.J >> 2;
-                auto index = [&](int lane, int i) { return (unsigned)min(lane + i * 64, p.slots * PW - 1); };
-                auto places = [&](unsigned (&off)[N], int lane) {
-#pragma unroll
-                    for (int i = 0; i < N; ++i) {
-                        const unsigned at = index(lane, i), r = __umul24(at, INV) >> 16;
-                        off[i] = r * VROW + (unsigned)min(x.wave * PW + (int)(at - r * PW), j4 - 1) * 16u;
-                    }
-                };
-                unsigned off[N];
-                if constexpr (NREC > 0) {
-                    // (Asked for when the work that fills the time is all but done: with the same for the second layer's vector
-                    // above, 32 utterances in the bfloat16 mode take 962 instead of 980 us.  In the narrowest class there is
-                    // less to do and it comes too early: 126.7 instead of 125.8 us for one utterance of 20 frames.)
-                    stage<BF, CLS, R, 5, kResStageRow>(w_hh[NREC - 1], x1, sums_top, x.wave, [&]() {
-                        if (!EARLY) return;
-                        unsigned o[N];
-                        places(o, lane_id());
-                        request<N>(x, o, bo.q + slot_at(n, VSLOT), v);
-                        ordered();
-                    });
-                }
-                RES_MARK(8);
-                const int lane = lane_id();
-                places(off, lane);
-                if constexpr (EARLY) receive_rest<N>(p, x, off, bo.q + slot_at(n, VSLOT), v);
-                else receive<N>(p, x, off, bo.q + slot_at(n, VSLOT), v);
-#pragma unroll
-                for (int i = 0; i < N; ++i) {
-                    const unsigned at = index(lane, i), r = __umul24(at, INV) >> 16;
-                    const float4 o = __builtin_bit_cast(float4, v[i]);
-                    if (x.wave * PW + (int)(at - r * PW) < j4) *reinterpret_cast<float4 *>(lq + r * QS + (at - r * PW) * 4) = o;
-                }
+            // (while z is on its way) the recurrent part of the top layer's next step
+            if constexpr (NREC > 0) {
+                // (The first tile is asked for when the work that fills the time is all but done.)
+                stage<BF, CLS, R, 5, kResStageRow>(w_hh[NREC - 1], x1, sums_top, x.wave, [&]() { ask_z(); ordered(); });
+            } else {
+                ask_z();
             }
+            RES_MARK(8);
             RES_MARK(9);
         } else {
             if constexpr (FRAMES_FIRST) __builtin_amdgcn_s_setprio(0);
-            load_frames(0x01010101u << x.wave, x.wave, kResWaves);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
+            if (x.wave >= kFormers) {
+                load_frames((x.wave - kFormers) * (32 / ZS), lane_id() < 32);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                publish_z(nt_, jn);
+            }
             RES_MARK(10);
+            ask_z();
         }
         // ---- joint step ----------------------------------------------------------------------------
-        ++n_joint;
-        const unsigned jn = n_joint;
         // The frames that come after those of this step are brought to the XCD's L2 meanwhile, a work-group asking for a word of every
         // line of one: the frames' loads of the next step are what the waves without cells wait for.  (Into LDS, where nobody reads them: a
         // register would be waited for.  By the wave that is done first; its next wait, for the keys, is 1.5 us on.)  128 utterances, whose
@@ -1380,135 +1379,144 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" :: "v"(p.P + (long long)row * p.J + k), "s"(to) : "memory");
         }
         {
-            // A wave has an eighth of K for both column tiles, so the operand z = relu(P + q) of a lane's sample is
-            // formed on the way: nobody else needs it.  fp32: every product is that of two fp16 parts of
+            // A wave has an eighth of K for both column tiles.  fp32: every product is that of two fp16 parts of
             // either side (after a power of two of the utterance, see joint_scale; layers of 640: without low times low, which made the joint step 0.1 us longer and
             // the logits' error 2 % smaller), in one sum.  (Products with a low part in sums of their own made the logits' error
             // 1 to 6 % smaller, but twelve registers of the two-layer models' input weights had to be loaded from memory
             // in every step: input stage 1.18 instead of 0.96 us.)
             // (a half block comes first)
-            float scale = 1.f;               // of the lane's sample
             auto block_of = [](int b) { return NH % 2 != 0 ? (b + NB - 1) % NB : b % NB; };
-            auto form = [&](float p_, float q_) { return fmaxf(BF || WHOLE ? p_ + q_ : fmaf(p_, scale, q_), 0.f); };
-            auto relu = [&](float4 p_, float4 q_) { return make_float4(form(p_.x, q_.x), form(p_.y, q_.y), form(p_.z, q_.z), form(p_.w, q_.w)); };
-            // Where the lane's part of sample 16 mt + lane % 16 lies in the wave's eighth: of its frame and of its row's q,
-            // the first four words of block i (the second four: 16 in the address inverted, or added).
-            // Worked out anew for every tile: kept across all of them it takes registers that the weights need.
-            int m16, g, k40, frame0;
-            auto place_lane = [&]() {
-                const int lane = lane_id();
-                m16 = lane & 15; g = lane >> 4;
-                k40 = x.wave * (NH * 4) + 2 * g; frame0 = lo.p + (int)__umul24((unsigned)m16, ROW * 4u);
-            };
-            auto frame_at = [&](int mt, int i) { return frame0 + ((k40 + i * 8 - (i < NF ? 0 : g)) ^ m16) * 16 + mt * 16 * ROW * 4; };
-            auto q_of = [&](int mt) {
-                const unsigned row = (unsigned)lane_const >> (mt ? 14 : 0) & 3u;
-                if constexpr (!BF && !WHOLE) scale = rc.scale[row];
-                return lo.q + (int)__umul24(row, QS * 4u) + x.wave * (R * QS * 4) + g * 32;
-            };
-            auto q_at = [&](int of, int i) { return of + i * 128 - (i < NF ? 0 : g * 16); };
-            auto at = [&](int a) { return *reinterpret_cast<const float4 *>(lds + a); };
             unsigned again = 0;              // samples whose operand has too few bits in parts, or none
-            auto output = [&](auto tails_) {
-                constexpr unsigned TAILS = decltype(tails_)::value;
+            {
+                const float top = wait_z();
+                if constexpr (!BF && !WHOLE) {
+                    const unsigned long long fine = __ballot(top >= kResLeast), small = __ballot(top > 0.f) & ~fine, beyond = __ballot(top > kResMost);
+                    if ((small | beyond) != 0ull) again = unheld(small, fine, beyond);
+                }
+            }
+            RES_MARK(9);
+            // the partner's weights of column tile c
+            auto partner = [&](auto i_, auto part_, int c, int lane) {
+                constexpr int i = decltype(i_)::value, N = i < NF ? 4 : 2;
+                const int reg = res_tile_at(BF, CLS, 2, i, c, decltype(part_)::value);
+                return *reinterpret_cast<const std::conditional_t<N == 4, r4f, r2f> *>(lds + lo.other + x.wave * (JREGS * 256) + reg / 4 * 1024 + lane * 16 + reg % 4 * 4);
+            };
+            // where column tile c's sums go, the work-group's own (0, 1) and its partner's (2, 3)
+            auto sums_at = [&](int c, int lane) {
+                const int side = NT == 2 ? (c < 2 ? half : 1 - half) : 0;
+                return reinterpret_cast<r4f *>(part + ((x.wave * NT + side) * 16 + (lane & 15)) * kResSumRow + (c & 1) * 16 + (lane >> 4) * 4);
+            };
+            constexpr int CT = NT == 2 ? 4 : 2;               // column tiles
+            std::integral_constant<int, 0> high;
+            std::integral_constant<int, 1> low;
+            // the operand as the matrix instructions take it: from a block's first register on, the high parts and then the low ones (else: as it came)
+            auto parts_at = [](int i) { return BF || WHOLE ? i * 4 : i * 8; };
+            unsigned z[PIECES * 4];
+            static_for<0, NB>([&](auto i_) {
+                constexpr int i = decltype(i_)::value, at = parts_at(i), N = i < NF ? 4 : 2;
+                if constexpr (BF || WHOLE) {
+                    z[at] = zw[i].x; z[at + 1] = zw[i].y; z[at + 2] = zw[i].z; z[at + 3] = zw[i].w;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < N; ++e) {
+                        const r4u v = zw[i * 2 + e / 2];
+                        f16_parts(__uint_as_float(e % 2 ? v.z : v.x), __uint_as_float(e % 2 ? v.w : v.y), z[at + e], z[at + N + e]);
+                    }
+                }
+            });
+            auto output = [&](auto tail_) {
+                constexpr bool TAIL = decltype(tail_)::value;
                 const r4f zero = {0.f, 0.f, 0.f, 0.f};
-                r4f big[2], tb;
-                float top = 0.f;
-                float4 pv[2], qv[2];
-                int qo = 0;
-                auto fetch = [&](int b) {
-                    const int mt = b / NB, i = block_of(b % NB);
-                    if (b % NB == 0) { place_lane(); qo = q_of(mt); }
-                    const int pa = frame_at(mt, i), qa = q_at(qo, i);
-                    pv[0] = at(pa); qv[0] = at(qa);
-                    if (i < NF && !(TAILS >> mt & 1u)) { pv[1] = at(pa ^ 16); qv[1] = at(qa + 16); }
-                };
-                fetch(0);
-                static_for<0, NB * NT>([&](auto b_) {
-                    constexpr int b = decltype(b_)::value, mt = b / NB, i = block_of(b % NB);
-                    constexpr bool FULL = i < NF, TAIL = (TAILS >> mt & 1u) != 0u;
-                    if constexpr (b % NB == 0) { big[0] = big[1] = tb = zero; top = 0.f; }
-                    unsigned zh[4], zl[4];
-                    if constexpr (FULL && TAIL) { pv[1] = at(frame_at(mt, i) ^ 16); qv[1] = at(q_at(qo, i) + 16); }      // (registers)
+                // fp32: the work-group's own columns and the tail, then its partner's (registers)
+                constexpr int AT = BF ? CT : 2;
+                static_for<0, CT / AT>([&](auto own_) {
+                    constexpr int c0 = decltype(own_)::value * 2;
+                    r4f big[AT], tb = zero;
 #pragma unroll
-                    for (int j = 0; j < (FULL ? 2 : 1); ++j) {
-                        const float4 z = relu(pv[j], qv[j]);
+                    for (int c = 0; c < AT; ++c) big[c] = zero;
+                    static_for<0, NB>([&](auto b_) {
+                        constexpr int b = decltype(b_)::value, i = block_of(b);
+                        constexpr bool FULL = i < NF;
+                        std::integral_constant<int, i> block;
+                        const unsigned *zh = z + parts_at(i), *zl = zh + (FULL ? 4 : 2);
+                        if constexpr (NH % 2 != 0 && NF > 0 && b == 1) {
+                            // the sums of the half block have to be there
+#pragma unroll
+                            for (int c = 0; c < AT; ++c) there(big[c]);
+                            if (TAIL && c0 == 0) there(tb);
+                        }
+                        ordered();
+                        const int lane = lane_id(), m16 = lane & 15, g = lane >> 4;
                         if constexpr (WHOLE) {
-                            zh[0] = __float_as_uint(z.x); zh[1] = __float_as_uint(z.y); zh[2] = __float_as_uint(z.z); zh[3] = __float_as_uint(z.w);
-                        } else if constexpr (BF) {
-                            zh[j * 2] = bf16_pair(z.x, z.y); zh[j * 2 + 1] = bf16_pair(z.z, z.w);
+#pragma unroll
+                            for (int c = 0; c < 2; ++c) {
+                                r4f w = w_ou.q[c];
+                                if constexpr (c0 != 0) w = *reinterpret_cast<const r4f *>(lds + lo.other + x.wave * (JREGS * 256) + c * 1024 + lane * 16);
+                                big[c] = whole_mfma(w, zh, big[c]);
+                            }
                         } else {
-                            f16_parts(z.x, z.y, zh[j * 2], zl[j * 2]);
-                            f16_parts(z.z, z.w, zh[j * 2 + 1], zl[j * 2 + 1]);
-                            top = fmaxf(fmaxf(z.z, z.w), fmaxf(fmaxf(z.x, z.y), top));
+                            typedef std::conditional_t<FULL, r4f, r2f> Group;
+                            Group wh[AT], wl[AT];
+#pragma unroll
+                            for (int c = 0; c < AT; ++c) {
+                                const bool own = c0 + c < 2;
+                                if (own) wh[c] = weights_of<BF, CLS, 2, i, 0>(w_ou, c0 + c);
+                                else wh[c] = partner(block, high, c0 + c - 2, lane);
+                                if constexpr (!BF) {
+                                    if (own) wl[c] = weights_of<BF, CLS, 2, i, 1>(w_ou, c0 + c);
+                                    else wl[c] = partner(block, low, c0 + c - 2, lane);
+                                }
+                            }
+                            if constexpr (!BF) {
+                                if constexpr (NF < 2) {
+#pragma unroll
+                                    for (int c = 0; c < AT; ++c) big[c] = tile_mfma<BF>(wl[c], zl, big[c]);
+                                }
+#pragma unroll
+                                for (int c = 0; c < AT; ++c) big[c] = tile_mfma<BF>(wh[c], zl, big[c]);
+#pragma unroll
+                                for (int c = 0; c < AT; ++c) big[c] = tile_mfma<BF>(wl[c], zh, big[c]);
+                            }
+#pragma unroll
+                            for (int c = 0; c < AT; ++c) big[c] = tile_mfma<BF>(wh[c], zh, big[c]);
                         }
-                    }
-                    if constexpr (b + 1 < NB * NT) fetch(b + 1);
-                    if constexpr (NH % 2 != 0 && NF > 0 && b % NB == 1) {
-                        // the sums of the half block have to be there
-                        there(big[0]); there(big[1]);
-                        if (TAIL) there(tb);
-                    }
-                    ordered();
-                    if constexpr (!BF && !WHOLE) {
-                        if constexpr (NF < 2) {
-#pragma unroll
-                            for (int c = 0; c < 2; ++c) big[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 1>(w_ou, c), zl, big[c]);
+                        // the tail columns: high and low parts (bfloat16 mode: values) are rows of their own of the
+                        // operand, the others zeros
+                        if constexpr (TAIL && c0 == 0 && WHOLE) {
+                            tb = whole_mfma(*reinterpret_cast<const r4f *>(lds + lo.tail + (min(m16, NMT) * ROW + x.wave * 16 + g * 4) * 4), zh, tb);
+                        } else if constexpr (TAIL && c0 == 0) {
+                            const auto w = *reinterpret_cast<const std::conditional_t<FULL, r4f, r2f> *>(lds + lo.tail + (min(m16, BF ? NMT : 2 * NMT) * ROW + x.wave * (NH * 16) + i * 32 + g * (FULL ? 8 : 4)) * 2);
+                            if constexpr (!BF) tb = tile_mfma<BF>(w, zl, tb);
+                            tb = tile_mfma<BF>(w, zh, tb);
                         }
+                        ordered();
+                    });
+                    const int lane = lane_id();
+                    if (TAIL && c0 == 0 && lane < 16) {
 #pragma unroll
-                        for (int c = 0; c < 2; ++c) big[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 0>(w_ou, c), zl, big[c]);
+                        for (int k = 0; k < NMT; ++k) tpart[(x.wave * 2 + k) * 16 + lane] = BF || WHOLE ? tb[k] : tb[k * 2] + tb[k * 2 + 1];
+                    }
+                    // every wave's sums to LDS, [wave][side][sample][column]
 #pragma unroll
-                        for (int c = 0; c < 2; ++c) big[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 1>(w_ou, c), zh, big[c]);
-                    }
-#pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        if constexpr (WHOLE) big[c] = whole_mfma(w_ou.q[c], zh, big[c]);
-                        else big[c] = tile_mfma<BF>(weights_of<BF, CLS, 2, i, 0>(w_ou, c), zh, big[c]);
-                    }
-                    // the tail column: its high and low parts (bfloat16 mode: its values) are rows of their own of the
-                    // operand, the others zeros
-                    if constexpr (TAIL && WHOLE) {
-                        tb = whole_mfma(*reinterpret_cast<const r4f *>(lds + lo.tail + (min(m16, 1) * ROW + x.wave * 16 + g * 4) * 4), zh, tb);
-                    } else if constexpr (TAIL) {
-                        const auto w = *reinterpret_cast<const std::conditional_t<FULL, r4f, r2f> *>(lds + lo.tail + (min(m16, BF ? 1 : 2) * ROW + x.wave * (NH * 16) + i * 32 + g * (FULL ? 8 : 4)) * 2);
-                        if constexpr (!BF) tb = tile_mfma<BF>(w, zl, tb);
-                        tb = tile_mfma<BF>(w, zh, tb);
-                    }
-                    ordered();
-                    if constexpr (b % NB == NB - 1) {
-                        if constexpr (!BF && !WHOLE) {
-                            const unsigned long long fine = __ballot(top >= kResLeast), small = __ballot(top > 0.f) & ~fine, beyond = __ballot(top > kResMost);
-                            if ((small | beyond) != 0ull) again |= unheld(small, fine, beyond) << (mt * 16);
-                        }
-                        if (TAIL && g == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = BF || WHOLE ? tb[0] : tb[0] + tb[1];
-                        // every wave's sums to LDS, [wave][sample][column]
-#pragma unroll
-                        for (int c = 0; c < 2; ++c)
-                            *reinterpret_cast<r4f *>(part + ((x.wave * NT + mt) * 16 + m16) * kResSumRow + c * 16 + g * 4) = big[c];
-                    }
+                    for (int c = 0; c < AT; ++c) *sums_at(c0 + c, lane) = big[c];
                 });
             };
-            if constexpr (NT == 1) {
-                if (tail_for(0)) output(std::integral_constant<unsigned, 1>());
-                else output(std::integral_constant<unsigned, 0>());
-            } else {
-                if (tails == 0u) output(std::integral_constant<unsigned, 0>());
-                else if (tails == 1u) output(std::integral_constant<unsigned, 1>());
-                else if (tails == 2u) output(std::integral_constant<unsigned, 2>());
-                else output(std::integral_constant<unsigned, 3>());
-            }
+            const bool with_tail = NT == NMT ? n_tails > 0 : half < n_tails;
+            if (with_tail) output(std::true_type());
+            else output(std::false_type());
             if constexpr (!BF && !WHOLE) {
                 // Samples whose operand parts do not hold in the wave's eighth, far below the bound or infinite, are computed once more
-                // as fp32 products (the weights' parts added up again; two tiles of samples 6.5 us).  The lane's e-th value of
+                // as fp32 products (the weights' parts added up again).  The lane's e-th value of
                 // a block times its e-th weight is one 16x16x4 instruction.
                 // (Of the step's own samples: what rows without an utterance, and places without a frame, hold may be of any size.)
-                if (again != 0u) again &= (unsigned)__ballot(pidx >= 0);
+                if (again != 0u) again &= (unsigned)__ballot(pidx >= 0) >> (NT == 2 ? half * 16 : 0);
                 if (again != 0u) {
+                    const int lane = lane_id(), m16 = lane & 15, g = lane >> 4;
+                    const float scale = rc.scale[from_lane(lane_const, (NT == 2 ? half * 16 : 0) + m16) >> 28 & 3], back = inverse_power(scale);
+                    const bool mine = (again >> m16 & 1u) != 0u;
+                    ask_z();
 #pragma unroll 1
-                    for (int mt = 0; mt < NT; ++mt) {
-                        place_lane();
-                        const int qo = q_of(mt);
-                        const float back = inverse_power(scale);
+                    for (int c2 = 0; c2 < CT; c2 += 2) {
                         r4f sum[2], tail = {0.f, 0.f, 0.f, 0.f};
                         sum[0] = sum[1] = tail;
                         static_for<0, NB>([&](auto k_) {
@@ -1517,30 +1525,33 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                             float z[N];
 #pragma unroll
                             for (int j = 0; j < N / 4; ++j) {
-                                const float4 v = relu(at(frame_at(mt, k) ^ (j * 16)), at(q_at(qo, k) + j * 16));
+                                const float4 v = __builtin_bit_cast(float4, zw[k * 2 + j]);
                                 z[j * 4] = v.x * back * scale; z[j * 4 + 1] = v.y * back * scale;        // (infinite where the sum is)
                                 z[j * 4 + 2] = v.z * back * scale; z[j * 4 + 3] = v.w * back * scale;
                             }
 #pragma unroll
                             for (int c = 0; c < 2; ++c) {
                                 auto wh = weights_of<BF, CLS, 2, k, 0>(w_ou, c), wl = weights_of<BF, CLS, 2, k, 1>(w_ou, c);
+                                if (NT == 2 && c2 != 0) { wh = partner(k_, high, c, lane); wl = partner(k_, low, c, lane); }
                                 asm volatile("" : "+v"(wh), "+v"(wl));           // (not added up ahead: that takes registers for the whole loop)
-                                const Halves high = __builtin_bit_cast(Halves, wh), low = __builtin_bit_cast(Halves, wl);
+                                const Halves hi = __builtin_bit_cast(Halves, wh), lw = __builtin_bit_cast(Halves, wl);
 #pragma unroll
-                                for (int e = 0; e < N; ++e) sum[c] = __builtin_amdgcn_mfma_f32_16x16x4f32((float)high[e] + (float)low[e], z[e], sum[c], 0, 0, 0);
+                                for (int e = 0; e < N; ++e) sum[c] = __builtin_amdgcn_mfma_f32_16x16x4f32((float)hi[e] + (float)lw[e], z[e], sum[c], 0, 0, 0);
                                 ordered();
                             }
-                            if (tail_for(mt)) {
-                                const _Float16 *w = reinterpret_cast<const _Float16 *>(lds + lo.tail) + x.wave * (NH * 16) + k * 32 + g * N;
+                            if (with_tail && c2 == 0) {
+                                const _Float16 *w = reinterpret_cast<const _Float16 *>(lds + lo.tail) + min(m16, NMT) * 2 * ROW + x.wave * (NH * 16) + k * 32 + g * N;
 #pragma unroll
-                                for (int e = 0; e < N; ++e) tail = __builtin_amdgcn_mfma_f32_16x16x4f32(m16 == 0 ? (float)w[e] + (float)w[ROW + e] : 0.f, z[e], tail, 0, 0, 0);
+                                for (int e = 0; e < N; ++e) tail = __builtin_amdgcn_mfma_f32_16x16x4f32(m16 < NMT ? (float)w[e] + (float)w[ROW + e] : 0.f, z[e], tail, 0, 0, 0);
                             }
                         });
-                        if ((again >> (mt * 16 + m16) & 1u) != 0u) {
-                            if (tail_for(mt) && g == 0) tpart[(x.wave * 2 + mt) * 16 + m16] = tail[0];
+                        if (mine) {
+                            if (with_tail && c2 == 0 && g == 0) {
 #pragma unroll
-                            for (int c = 0; c < 2; ++c)
-                                *reinterpret_cast<r4f *>(part + ((x.wave * NT + mt) * 16 + m16) * kResSumRow + c * 16 + g * 4) = sum[c];
+                                for (int k = 0; k < NMT; ++k) tpart[(x.wave * 2 + k) * 16 + m16] = tail[k];
+                            }
+#pragma unroll
+                            for (int c = 0; c < 2; ++c) *sums_at(c2 + c, lane) = sum[c];
                         }
                     }
                 }
@@ -1550,17 +1561,22 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             __syncthreads();
             const int tid = (x.wave * 64 + lane_id());
             if (tid < 16 * NT * 16) {
-                const int s = tid >> 4, col = (tid & 15) * 2, gcol = x.rank * 32 + col;
+                // (two tiles: the first four waves the columns of the even rank, the others those of the odd one, as that rank's)
+                const int side = NT == 2 ? x.wave >> 2 : half, rank = x.rank - half + side;
+                const int at = tid >> 4, s = NT == 2 ? half * 16 + (at & 15) : at, col = (tid & 15) * 2, gcol = rank * 32 + col;
+                const int n_tok = min(p.VT, p.pl.nout_m) - rank * 32;        // token columns among them
+                const bool dur_cols = p.tdt && p.VT < p.pl.nout_m && rank * 32 + 32 > p.VT;      // they hold duration columns
+                const int tcol = tcol0 + side;
                 float2 o[kResWaves];
 #pragma unroll
                 for (int w = 0; w < kResWaves; ++w)
-                    o[w] = *reinterpret_cast<const float2 *>(part + (w * NT * 16 + s) * kResSumRow + col);
-                const float2 bias = rc.bo[tid & 15], scale = rc.so[tid & 15];
+                    o[w] = *reinterpret_cast<const float2 *>(part + (w * NT * 16 + at) * kResSumRow + col);
+                const float2 bias = rc.bo[side][tid & 15], scale = rc.so[side][tid & 15];
                 static_assert(kResWaves == 8, "eight lanes add the waves' sums of the tail column");
                 float tw = 0.f, back = 1.f;
                 if constexpr (!BF && !WHOLE) back = inverse_power(rc.scale[lane_const >> 16 & 3]);
-                const bool tail_here = tail_for(x.wave >> 2);          // (a wave has four samples)
-                if (tail_here) tw = tpart[((tid & 7) * 2 + (s >> 4)) * 16 + (s & 15)];
+                const bool tail_here = side < n_tails;
+                if (tail_here) tw = tpart[((tid & 7) * 2 + side) * 16 + (at & 15)];
                 const float l0 = (((o[0].x + o[1].x) + (o[2].x + o[3].x)) + ((o[4].x + o[5].x) + (o[6].x + o[7].x))) * scale.x * back + bias.x;
                 const float l1 = (((o[0].y + o[1].y) + (o[2].y + o[3].y)) + ((o[4].y + o[5].y) + (o[6].y + o[7].y))) * scale.y * back + bias.y;
                 const float m0 = col < n_tok ? l0 : -INFINITY, m1 = col + 1 < n_tok ? l1 : -INFINITY;
@@ -1572,7 +1588,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 int ix = hit ? (m0 == m ? gcol : gcol + 1) : 0x7fffffff;
                 float tail = -INFINITY;
                 if (tail_here) {
-                    tail = lane_sum<8>(tw) * rc.st * back + rc.bt;
+                    tail = lane_sum<8>(tw) * rc.st[side] * back + rc.bt[side];
                     if (tcol >= p.VT) {
                         if ((tid & 15) == 0) {
                             const unsigned d = ((unsigned)s * kMaxDur + (unsigned)(tcol - p.VT)) * 4u;
@@ -1592,7 +1608,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                             put(x, d, bo.dur + slot_at(jn, DSLOT), bo.dur + slot_at(jn + 2, DSLOT), word_of(c ? l1 : l0));
                         }
                 }
-                const unsigned ko = ((unsigned)s * TS + (unsigned)x.rank) * 8u;
+                const unsigned ko = ((unsigned)s * TS + (unsigned)rank) * 8u;
                 if ((tid & 15) == first)
                     put2(x, ko, bo.key + slot_at(jn, KSLOT), bo.key + slot_at(jn + 2, KSLOT), (r2u){word_of(m), (unsigned)ix});
                 if (p.logps) {
@@ -1608,12 +1624,13 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             // the samples that this step does not have: the marks that their words of step jn + 2 need
             const int tid = x.wave * 64 + lane_id(), s = tid >> 4;
             if (s >= NS && s < NS * 2) {
-                const int gcol = x.rank * 32 + (tid & 15) * 2;
+                const int gcol = x.rank * 32 + (tid & 15) * 2, tcol = tcol0 + half;
+                const bool dur_cols = p.tdt && p.VT < p.pl.nout_m && x.rank * 32 + 32 > p.VT;
                 const unsigned ko = ((unsigned)s * TS + (unsigned)x.rank) * 8u, ds = (unsigned)s * kMaxDur * 4u;
                 const bool lead = (tid & 15) == 0;
                 if (lead) put_mark2(x, ko, bo.key + slot_at(jn + 2, KSLOT));
                 if (lead && p.logps) put_mark(x, ko / 2, bo.lse + slot_at(jn + 2, KSLOT / 2));
-                if (lead && tail_for(1) && tcol >= p.VT) put_mark(x, ds + (unsigned)(tcol - p.VT) * 4u, bo.dur + slot_at(jn + 2, DSLOT));
+                if (lead && half < n_tails && tcol >= p.VT) put_mark(x, ds + (unsigned)(tcol - p.VT) * 4u, bo.dur + slot_at(jn + 2, DSLOT));
                 if (dur_cols) {
 #pragma unroll
                     for (int c = 0; c < 2; ++c)
@@ -1699,7 +1716,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         {
             const int lane = lane_id(), r = (int)((unsigned)lane / LR) & (R - 1);
             RRow w = rows.s[r];
-            int b = rows.b[r], m = rows.m[r];
+            int b = rows.b[r];
             // (on its way during the rest: the helpers' results take 0.85 us, and what is left of the step 0.75)
             if (PAIR) load_pre(n_pred, 0, pre[0]);
             __syncthreads();
@@ -1717,32 +1734,26 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             if (!walk) {
                 // a blank moves on by one frame: the first label among the frames the row still has
                 const unsigned labels = (unsigned)__ballot(mine != p.blank);
-                const unsigned at = (labels >> row0) & ((1u << la) - 1u), avail = (unsigned)max(0, min(la, left));     // by place
-                pos = __builtin_ctz(((at >> m) | (at << (la - m))) | (1u << avail));                                  // by frame
+                const unsigned avail = (unsigned)max(0, min(la, left));
+                pos = __builtin_ctz((labels >> row0) | (1u << avail));
                 found = pos < (int)avail;
             } else {
                 // lane = sample: the offset (from the row's frame) that the walk goes to from it, its own for a label
                 // or beyond the row's frames, and the lane of that offset, its own where the walk leaves the step;
                 // then the hops are doubled until every one reaches its end
-                const int ms = from_lane(m, (lane_const >> 28 & 3) * LR), si = lane_const >> 18 & 31;
-                int to = si - ms;
-                if (to < 0) to += la;
+                const int si = lane_const >> 18 & 31;
                 int d = 0;
                 if (mine >= p.V1) d = max(rc.dur[(mine - p.V1) & (kMaxDur - 1)], 1);            // big blank: its span of frames
                 else if (mine == p.blank) d = p.tdt ? min(max(rc.s_d[lane & (kResSamples - 1)], 1), kFarthest) : 1;
                 if (pidx < 0) d = 0;
-                to += d;
-                int at = ms + to;
-                if (at >= la) at -= la;
-                int hop = (d > 0 && to < la ? lane - si + at : lane) << 2;
+                const int to = si + d;
+                int hop = (d > 0 && to < la ? lane + d : lane) << 2;
                 for (int i = 1; i < la; i *= 2) hop = __builtin_amdgcn_ds_bpermute(hop, hop);
-                hop = __builtin_amdgcn_ds_bpermute((row0 + m) << 2, hop);
+                hop = __builtin_amdgcn_ds_bpermute(row0 << 2, hop);
                 pos = __builtin_amdgcn_ds_bpermute(hop, to);
                 found = pos < la && pos < left;
             }
-            int at = m + pos;
-            if (at >= la) at -= la;
-            const int s = max(0, min(row0 + at, kResSamples - 1));
+            const int s = min(row0 + pos, kResSamples - 1);
             const int k = rc.s_k[s];
             if (p.tdt) dval = rc.s_d[s];
             // the label's row of the embedding table is what the next prediction step waits for
@@ -1771,13 +1782,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             w.t += adv;
             const bool ended = left > 0 && adv >= left;
             int action = found && !ended ? kTake : 0;
-            // (where no frame of the step is left, any place will do)
-            m = adv < la ? m + adv : 0;
-            if (m >= la) m -= la;
             if (__ballot(ended) != 0ull) {
                 if (writer && ended) res_finish_row(b, w.cnt);
                 const bool got = refill(lane, ended, b, w.len);
-                if (got) { w.t = w.n = w.cnt = m = 0; action = kFresh; last = p.blank; }
+                if (got) { w.t = w.n = w.cnt = 0; action = kFresh; last = p.blank; }
                 if (lead) rows.b[r] = b;
                 load_t0();
             }
@@ -1802,10 +1810,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             if (next != part_rows && any_active) {
                 // (a row has ended for good, or some go on looking alone: its samples go to the others)
                 lay_out(nt_, lane, next);
-                m = 0;
-                pidx = -1;                // every frame has another place
             }
-            if (lead) { rows.s[r] = w; rows.m[r] = m; }
+            if (lead) rows.s[r] = w;
             if (need_pred) row_steps += n_moved;
             if constexpr (HALVES && NT == NMT) {
                 // every so many steps: have all rows in work gone on by less than one and a half frames a step?
@@ -1821,7 +1827,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             // (32 utterances 1308, 1321, 1151 us with it here, 1291, 1305, 1142 there, bfloat16 mode 836, 941, 892 and 812, 918, 869.
             // One or two rows a team: 530 and 538 us for one utterance, the polls are later there than the words.)
             later = NMT == 2 && need_pred && has_cells && !change;
-            if (!change && !later) set_up_samples(lane, w.t, m, b, w.len);
+            if (!change && !later) set_up_samples(lane, w.t, b, w.len);
         }
         ok = rc.ok != 0;
         RES_MARK(15);
@@ -1843,12 +1849,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             const int lane = lane_id(), r = (int)((unsigned)lane / LR) & (R - 1);
             const RRow w = rows.s[r];
             lay_out(nt_, lane, part_rows);
-            if (lane < 16 && (lane & (LR - 1)) == 0) {
-                rows.m[r] = 0;
-                rows.since[r] = -0x10000000;      // (not after less than kResCalm steps)
-            }
-            pidx = -1;                // every frame has another place
-            set_up_samples(lane, w.t, 0, rows.b[r], w.len);
+            if (lane < 16 && (lane & (LR - 1)) == 0) rows.since[r] = -0x10000000;      // (not after less than kResCalm steps)
+            set_up_samples(lane, w.t, rows.b[r], w.len);
         };
         for (;;) {
             steps(all_tiles);
@@ -1890,7 +1892,7 @@ template <int KIND, bool BF, int CLS, int NMT>
 hipError_t launch_resident_one(const ResidentParams &p, bool plain, hipStream_t stream)
 {
     const void *fn = reinterpret_cast<const void *>(&resident_kernel<KIND, BF, CLS, NMT>);
-    constexpr unsigned lds = (unsigned)resident_lds(KIND, CLS, NMT).bytes;
+    constexpr unsigned lds = (unsigned)resident_lds(KIND, BF, CLS, NMT).bytes;
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     ResidentParams pc = p;

@@ -219,6 +219,30 @@ int main()
         for (unsigned by_default : {kStreamingWait, kResidentWait})
             if (wait_polls(polls, by_default) != polls || wait_polls(-1, by_default) != by_default) { std::printf("wait limit\n"); return 1; }
     // frames that are asked for ahead: the sample's row and the frames of a step, of the launch's rows only
+    // the joint's operand in its exchange buffer: every group of four values of every sample has a place of its own in the slot, and
+    // the inverse finds the group (bfloat16: groups) of 16 bytes
+    for (int cls = 0; cls < kResClasses; ++cls)
+        for (const bool bf : {false, true}) {
+            const unsigned size = res_z_slot(bf, cls), unit = bf ? 8 : 16;
+            std::vector<int> group(size / unit, -1);
+            for (int k4 = 0; k4 < res_row(cls) / 4; ++k4)
+                for (int s = 0; s < kResSamples; ++s) {
+                    const unsigned at = res_z_at(bf, cls, k4, s);
+                    if (at % unit != 0 || at + unit > size || group[at / unit] != -1) {
+                        std::printf("operand place cls %d bf %d group %d sample %d\n", cls, (int)bf, k4, s);
+                        return 1;
+                    }
+                    group[at / unit] = k4;
+                }
+            for (unsigned at = 0; at < size; at += 16) {
+                const int k4 = res_z_k4(bf, cls, at);
+                const bool two = bf && at % res_z_wave(bf, cls) < (unsigned)(res_halves(cls) / 2) * 1024u;
+                if (group[at / unit] != k4 || (bf && group[at / unit + 1] != k4 + (two ? 1 : 0))) {
+                    std::printf("operand group cls %d bf %d at %u\n", cls, (int)bf, at);
+                    return 1;
+                }
+            }
+        }
     if (touch_rows(64, 256, 512) != 0 || touch_rows(27, 500, 640) != 27 * 500 || touch_rows(1, 2147483647, 4) != 2147483647) {
         std::printf("touch rows\n");
         return 1;

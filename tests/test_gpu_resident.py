@@ -496,3 +496,31 @@ def test_a_large_joint_unit_that_nobody_reads(pkg, H, J, V1, L, durations, size)
     eng = pkg.Engine(w.model, w.B, w.T)
     check(pkg, w, w.variant, f"large unit {H}/{J}/{V1}/{L} {durations} {size}", engine=eng, logp=True)
     eng.close()
+
+
+# output layers with a tail of one column, of more columns than there are pairs of work-groups, and of one for each of them; teams of
+# the three size classes
+TAILS = [(128, 128, 257, 1, 32, ()), (128, 128, 264, 1, 32, ()), (124, 128, 254, 1, 32, (0, 1, 2, 3)), (320, 316, 521, 1, 16, ()),
+         (320, 316, 528, 1, 16, ()), (640, 636, 1026, 2, 6, ()), (640, 636, 1056, 2, 6, ()), (640, 640, 1048, 1, 8, (0, 1, 2, 0, 3, 1, 2, 4))]
+
+
+@pytest.mark.parametrize("H,J,V1,L,teams,durations", TAILS)
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("dense", [False, True])
+def test_tails_of_steps_with_two_tiles(pkg, H, J, V1, L, teams, durations, bf16, dense):  # noqa: F811
+    """Three and four rows a team, whose joint steps are shared out over pairs of work-groups: tail columns of either one, equal ones (the
+    lowest index wins), durations among them, and (dense: four labels on every frame) steps of one tile in between."""
+    w = model_inputs(H, J, V1, L, B=3 * (teams if L == 1 or not bf16 else 8) + 2, T=14, seed=H + V1, durations=durations)
+    m, first = w.model, V1 + len(durations) - len(range((V1 + len(durations)) % (32 * {640: 32, 320: 16, 128: 8, 124: 8}[H])))
+    same = [first, first + 3, first + 5] if first + 5 < V1 - 1 else []
+    for i in same[1:]:
+        m.w_out[i], m.b_out[i] = m.w_out[same[0]], m.b_out[same[0]]
+    if same:
+        m.b_out[same] += np.float32(3.0)          # (labels of the tail are found now and then)
+    if dense:
+        m.b_out[m.dims.blank] -= np.float32(4.0)
+    eng = pkg.Engine(m, w.B, w.T, flags=pkg.RNNT_FLAG_BF16_ARITHMETIC if bf16 else 0)
+    _, got, _ = check(pkg, w, w.variant, f"tails {H}/{J}/{V1}/{L} {durations} bf16={bf16} dense={dense}", engine=eng, bf16=bf16, logp=not bf16)
+    labels = np.concatenate(got["tokens"])
+    assert not same or ((labels == same[0]).any() and not np.isin(labels, same[1:]).any())
+    eng.close()
