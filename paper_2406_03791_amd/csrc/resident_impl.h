@@ -1108,6 +1108,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // Rows that want one get the next utterances of the list.  (Control state is by row: every lane works on
     // row lane / LR % R, and the first of LR lanes below 16 stands for its row in ballots.)
     constexpr unsigned long long LEADS = 0x1111ull;
+    bool queued = false;               // utterances of the list wait for a row
     auto refill = [&](int lane, bool want, int &b, int &len) {
         const unsigned long long m = __ballot(want) & LEADS;
         if (m == 0ull) return false;
@@ -1118,6 +1119,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         if constexpr (!BF && !WHOLE)
             if (got) rc.scale[(int)((unsigned)lane / LR) & (R - 1)] = list_scale[at];
         rows.next = next + __popcll(m);
+        queued = __builtin_amdgcn_readfirstlane(rc.n_list) > __builtin_amdgcn_readfirstlane(next) + __popcll(m);
         return got;
     };
     __syncthreads();                  // the list is complete
@@ -1794,18 +1796,20 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             const unsigned moved = (unsigned)__ballot((lane_const & (kTake | kFresh)) != 0) & active;      // rows whose next step has new inputs
             any_active = active != 0u;
             const int n_moved = __builtin_popcount(moved), n_search = __builtin_popcount(active) - n_moved;
-            // The next step is a prediction step if a row has new inputs, unless as many or more are still looking for
-            // their label and the one with the most frames left is among them: then these have the next joint step, and all its samples, to
-            // themselves, at 5 us instead of 8.5 (two-layer fp32 models) or 7.  The rows with labels wait, the team's longest row does not.
-            // 32 utterances 1402, 1383 and 1242 us without this (three draws), 1348, 1367 and 1182 with it, bfloat16 mode 898, 992, 951
-            // and 866, 975, 920, 128 utterances 4664, 4504, 4499 and 4639, 4394, 4376, TDT 1018, 954, 982 and 988, 971, 989.  (Whoever has the most
-            // frames left: bfloat16 mode up to 4 % and the multi-blank model up to 3.5 % slower than without.)
+            // The next step is a prediction step if a row has new inputs, unless half as many or more are still looking for
+            // their label: then these have the next joint step, and all its samples, to themselves, at 4 us instead of 8 (two-layer fp32
+            // models) or 6.5.  But where no utterance waits for a row any more, the row with the most frames left does not wait: it is what
+            // the team's time ends with.  (32 utterances, three draws, with a prediction step at every label 1402, 1383 and 1242 us, against
+            // 1348, 1367 and 1182; as many or more still looking, and the longest never waiting, against half as many and only without
+            // a queue: 1037, 1264, 1303 and 1059, 1245, 1238, bfloat16 mode 777, 846, 843 and 768, 836, 834, 57 with e4m3 weights 644 and 635, 128 utterances
+            // 3807 and 3721.  Whoever has the most frames left: bfloat16 mode up to 4 % and the multi-blank model up to 3.5 % slower than
+            // with a step at every label.)
             int most = w.len - w.t;
             const int rest = most;
             asm("s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
                 "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf" : "+v"(most));
             const unsigned longest = (unsigned)__ballot(rest == most) & active;
-            need_pred = n_moved != 0 && (NT < NMT || n_moved > n_search || (longest & ~moved) == 0u);
+            need_pred = n_moved != 0 && (NT < NMT || n_moved > 2 * n_search || (!queued && (longest & ~moved) == 0u));
             const unsigned next = need_pred || n_moved == 0 ? active : active & ~moved;
             if (next != part_rows && any_active) {
                 // (a row has ended for good, or some go on looking alone: its samples go to the others)
