@@ -62,9 +62,9 @@ constexpr int kStaticLds = 3072;        // kept free for the kernel's static LDS
 // projected frames and the team workspace of one call.  One copy per device, held until the
 // process ends.  In host code this name is only a handle for hipGetSymbolAddress: the address
 // kernels and copies use is the one that call returns (rnnt_engine::scratch).
-// Behind RNNT_NOALLOC_SCRATCH_BYTES there is room for what calls take beyond what they are charged (charged_bytes), 8.3 MB at most;
+// Behind RNNT_NOALLOC_SCRATCH_BYTES there is room for what calls take beyond what they are charged (charged_bytes), 17.1 MB at most;
 // kScratchTop: and for the words on a call's P, which every call finds as the last one left them.
-constexpr size_t kScratchTop = RNNT_NOALLOC_SCRATCH_BYTES + (12u << 20);
+constexpr size_t kScratchTop = RNNT_NOALLOC_SCRATCH_BYTES + (20u << 20);
 static __device__ __align__(256) unsigned char scratch[kScratchTop + top_words(kLaunchRows) * sizeof(TopWord)];
 
 struct DevBuf {
@@ -618,7 +618,7 @@ int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
     // (infinite or undefined weights have no fp16 parts: such a model is left to the other kernel)
     if (found[0]) { e->res.kind = kResidentNone; return RNNT_OK; }
     std::memcpy(&e->res_q_bound, &found[1], sizeof(float));
-    HIP_TRY(e->res_xbuf.alloc((size_t)resident_buf(pl.kind, bf, pl.cls).bytes * pl.n_teams));
+    HIP_TRY(e->res_xbuf.alloc((size_t)resident_buf(pl.kind, bf, pl.cls, kResRows).bytes * pl.n_teams));
     HIP_TRY(e->res_form.alloc((size_t)pl.n_xcd * 32 * sizeof(unsigned)));
     HIP_TRY(e->res_stats.alloc((size_t)pl.n_teams * kStatStride * sizeof(long long)));
     HIP_TRY(hipMemset(e->res_form.p, 0, (size_t)pl.n_xcd * 32 * sizeof(unsigned)));
@@ -630,7 +630,11 @@ int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
 void resident_rows(const ResidentPlan &pl, int nb, int *slots, int *la)
 {
     if (pl.solo) { *slots = 1; *la = kSoloFrames; return; }
-    *slots = std::min(kResRows, (nb + pl.n_teams - 1) / pl.n_teams);
+    // Eight rows a team where every list has eight utterances.  With four and eight, us a call, means of three draws: two-layer fp32 models, six
+    // teams, 32 utterances 1181 and 1204, 42 1393 and 1392, 48 1549 and 1442, 64 1929 and 1679, 128 3721 and 3014, TDT 42 995 and
+    // 998, 48 1087 and 1014, multi-blank 42 760 and 810, 48 868 and 865; bfloat16 mode, eight teams, 56 1152 and 1091, 64 1228 and 1158,
+    // e4m3 TDT 57 635 and 661, 64 670 and 661, 72 770 and 737; one layer 48 1148 and 1078, 64 1416 and 1231; small, 16 teams, 96 563 and 529, 128 683 and 567.
+    *slots = nb >= kResRows * pl.n_teams ? kResRows : std::min(4, (nb + pl.n_teams - 1) / pl.n_teams);
     *la = *slots <= 2 ? 16 / *slots : kResSamples / *slots;
     *la = std::min(*la, 16);
 }
@@ -1217,7 +1221,7 @@ int rnnt_label_looping_decode_noalloc(rnnt_engine *eng, const float *enc_out, co
         size_t off = 0;
         auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
         const size_t o_P = take((size_t)B * T * eng->d.J * sizeof(float));
-        const size_t o_x = take(pl.solo ? 0 : (size_t)resident_buf(pl.kind, pl.bf != 0, pl.cls).bytes * pl.n_teams);
+        const size_t o_x = take(pl.solo ? 0 : (size_t)resident_buf(pl.kind, pl.bf != 0, pl.cls, kResRows).bytes * pl.n_teams);
         const size_t o_f = take((size_t)pl.n_xcd * 32 * sizeof(unsigned));
         const size_t o_s = take((size_t)pl.n_teams * kStatStride * sizeof(long long));
         const size_t o_a = take(sizeof(unsigned)), o_st = take(sizeof(int));

@@ -12,7 +12,7 @@ constexpr int kResThreads = 512;          // eight waves, two per SIMD: 256 regi
 constexpr int kResWaves = 8;
 constexpr int kResUnits = 20;             // LSTM units per work-group at most
 constexpr int kResSlots = 4;              // exchange slots per vector, used in turn
-constexpr int kResRows = 4;               // utterances a team decodes at the same time at most
+constexpr int kResRows = 8;               // utterances a team decodes at the same time at most (4 or 8, see resident_rows)
 constexpr int kResSamples = 32;           // (utterance, frame) pairs per joint step at most
 constexpr int kResCalm = 8;               // joint steps after which a row's frames may be halved, see the loop control
 // Projected frames from which on they are brought to the L2 ahead of the steps that load them: what all XCDs' L2 hold.  (19 utterances of
@@ -158,9 +158,9 @@ RNNT_HD constexpr int res_z_k4(bool bf, int cls, unsigned at)
 // Byte offsets of a team's exchange buffers, every vector in kResSlots slots.
 // hr, pre: kResident2Pair; pre: [layer][slot][quarter of K][rank][wave of the cells][lane]
 struct ResidentBuf { unsigned h[2], z, key, dur, lse, hr[2], pre, bytes; };
-RNNT_HD constexpr ResidentBuf resident_buf(int kind, bool bf, int cls)
+RNNT_HD constexpr ResidentBuf resident_buf(int kind, bool bf, int cls, int rows)
 {
-    const unsigned vec = kResSlots * (unsigned)(kResRows * res_width(cls)) * 4u;
+    const unsigned vec = kResSlots * (unsigned)(rows * res_width(cls)) * 4u;
     const unsigned recs = kResSlots * kResSamples * (unsigned)res_team(cls);
     ResidentBuf b{};
     b.h[0] = 0; b.h[1] = vec; b.z = 2 * vec; b.key = b.z + kResSlots * res_z_slot(bf, cls);
@@ -169,7 +169,7 @@ RNNT_HD constexpr ResidentBuf resident_buf(int kind, bool bf, int cls)
     b.hr[0] = b.hr[1] = b.pre = b.bytes = b.lse + recs * 4u;
     if (kind != kResident2Pair) return b;
     b.hr[1] = b.hr[0] + vec; b.pre = b.hr[1] + vec;
-    b.bytes = b.pre + 2u * kResSlots * kResQuarters * (unsigned)res_team(cls) * 5u * 64u * 4u;
+    b.bytes = b.pre + 2u * kResSlots * kResQuarters * (unsigned)res_team(cls) * 5u * 64u * (unsigned)rows;
     return b;
 }
 
@@ -193,38 +193,39 @@ RNNT_HD constexpr int res_main_regs(int kind, bool bf, int cls)
 // tpart: its partial sums.  state: cell state and recurrent pre-activations [layer][field][wave][lane] where they are
 // not in registers.  scale: powers of two of the team's list (fp32).  touch: for words that are loaded for their
 // lines only.
-// nmt: tiles of 16 samples.  Helpers: their own, from 0 on.
+// nmt: tiles of 16 samples; rows: of a team.  Helpers: their own, from 0 on.
 struct ResidentLds { int p, z_at, part, ih, rec0, proj, rec, other, tail, tpart, state, scale, touch, bytes; };
-constexpr int kResSumRow = 36;            // floats per row of partial sums: of the joint step, of the projection
-constexpr int kResStageRow = 80;          // and of the LSTM stages
+constexpr int kResSumRow = 36;            // floats per row of partial sums: of the joint step
+constexpr int kResProjRow = 20;           // of the projection, as many columns as a work-group has
+RNNT_HD constexpr int res_stage_row(int rows) { return rows == 4 ? 80 : 88; }        // and of the LSTM stages (eight rows in banks of their own)
 constexpr int kResAlone = 81 * 1024;      // at least: more than half of a compute unit's, which so has one work-group, however few registers that takes
-RNNT_HD constexpr ResidentLds resident_lds(int kind, bool bf, int cls, int nmt)
+RNNT_HD constexpr ResidentLds resident_lds(int kind, bool bf, int cls, int nmt, int rows)
 {
     ResidentLds l{};
-    const int stage = kResWaves * kResRows * kResStageRow * 4, sums = kResWaves * 16 * nmt * kResSumRow * 4;
+    const int stage = kResWaves * rows * res_stage_row(rows) * 4, sums = kResWaves * 16 * nmt * kResSumRow * 4;
     l.p = 0;
     l.z_at = l.p + 3 * 64 * 16;
     l.part = l.ih = l.z_at + 3 * 64 * 4;
     int at = l.ih + (kind == kResident1 ? 0 : stage);
     if (at < l.part + sums) at = l.part + sums;
-    l.proj = at; at += kResWaves * kResRows * kResSumRow * 4;
+    l.proj = at; at += kResWaves * rows * kResProjRow * 4;
     if (kind == kResident2) { l.rec0 = at; at += stage; }
     l.rec = at; at += kind == kResident2Pair ? 0 : stage;
     l.other = at; at += nmt == 2 ? kResWaves * res_joint_regs(bf, cls) * 256 : 0;
     l.tail = at; at += (bf ? nmt + 1 : res_whole(bf, cls) ? 2 * nmt + 2 : 2 * nmt + 1) * res_row(cls) * 2;
     l.tpart = at; at += kResWaves * 2 * 16 * 4;
-    l.state = at; at += kind == kResident2Pair ? 6 * 5 * 64 * 4 : 0;
+    l.state = at; at += kind == kResident2Pair ? 2 * (2 + rows / 4) * 5 * 64 * 4 : 0;
     l.scale = at; at += kind == kResident2 ? 0 : kResList * 4;
     l.touch = at; at += kind == kResident2Pair && cls == 0 && nmt == 2 ? 256 : 0;
-    const int help = 2048 + 2 * (kResServed / 2) * res_help_blocks(cls) * 1024;
+    const int help = 2048 + 2 * (kResServed * rows / 8) * res_help_blocks(cls) * 1024;
     if (kind == kResident2Pair && at < help) at = help;
     l.bytes = (at + 15) & ~15;
     if (l.bytes < kResAlone) l.bytes = kResAlone;
     return l;
 }
 constexpr int kResCtl = 5376;             // bytes kept for the control block and votes
-static_assert(resident_lds(kResident1, false, 0, 2).bytes + kResCtl <= 160 * 1024 && resident_lds(kResident2, true, 0, 2).bytes + kResCtl <= 160 * 1024 &&
-              resident_lds(kResident2Pair, false, 0, 2).bytes + kResCtl <= 160 * 1024, "the largest layouts and the control block fit the LDS");
+static_assert(resident_lds(kResident1, false, 0, 2, 8).bytes + kResCtl <= 160 * 1024 && resident_lds(kResident2, true, 0, 2, 8).bytes + kResCtl <= 160 * 1024 &&
+              resident_lds(kResident2Pair, false, 0, 2, 8).bytes + kResCtl <= 160 * 1024, "the largest layouts and the control block fit the LDS");
 
 // The model's matrices on the device (rows as in the model), and where their packed forms go: register images of the
 // teams' and the helpers' work-groups, [rank][wave][runs of registers, see res_place]; tail columns; what sums are multiplied by; the

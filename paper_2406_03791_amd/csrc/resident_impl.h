@@ -17,6 +17,10 @@
 // meet in LDS.  Columns of the LSTM stages and the projection are the team's utterances, those of the joint output are samples.
 // A wave receives its eighth of an operand straight into registers (Operand; the joint's: ask_z).
 //
+// A team decodes four utterances at a time, or eight where its list has as many (resident_rows): two parts of eight rows are the sixteen
+// columns that the matrix instructions of the LSTM stages and the projection have in any case, so a prediction step of eight takes 0.4 us more
+// than one of four; four frames of every row in a joint step where there were eight, but 128 utterances take 400 joint steps instead of 522.
+//
 // The joint's operand z = relu(P + q) is formed once in the team: every work-group has its own columns of the projection, adds
 // those of the samples' frames (80 bytes a sample) and hands z on in q's place.  Formed from q by every work-group for itself it took
 // nine vector instructions for two values and two LDS reads, 32 times over, and the samples' whole frames in LDS, 80 KB.  What
@@ -106,7 +110,7 @@ struct RCtl {
     __align__(16) float bp[24], sp[24];
     float2 bo[2][16], so[2][16];      // with two tiles of samples: of this work-group and its partner, the even rank first
     float bt[2], st[2];
-    float scale[kResRows];            // fp32: of the utterances in work, see joint_scale
+    float scale[RRows::kPlaces];      // fp32: of the utterances in work, see joint_scale
 };
 __shared__ RCtl rc;
 static_assert(sizeof(RCtl) + 256 <= kResCtl, "the control block has its place, and what the compiler keeps for votes of a work-group");
@@ -405,6 +409,7 @@ __device__ __forceinline__ unsigned hidden_word(float h)
 // goes through LDS, and a wave goes on as soon as its own eighth is there.
 template <bool BF, int CLS, int R>
 struct Operand {
+    static_assert(R == 4 || R == 8, "two parts of every row are 8 or 16 columns");
     static constexpr int NH = res_halves(CLS), NF = NH / 2, NB = NF + (NH & 1);
     unsigned z[NH * 2];
     // words of block i for the lane: byte offset in a vector of rows of `W` words; n4 pieces of four words a row, the
@@ -426,7 +431,7 @@ struct Operand {
             const unsigned k0 = __builtin_amdgcn_perm(v[i].y, v[i].x, keep), k1 = __builtin_amdgcn_perm(v[i].w, v[i].z, keep);
             if (i < NF) {
                 const unsigned s0 = __builtin_amdgcn_perm(v[i].y, v[i].x, send), s1 = __builtin_amdgcn_perm(v[i].w, v[i].z, send);
-                constexpr int UP = 0x110 + R, DOWN = 0x100 + R, FIRST = 0x1, SECOND = 0x2;       // banks of four lanes
+                constexpr int UP = 0x110 + R, DOWN = 0x100 + R, FIRST = (1 << (R / 4)) - 1, SECOND = FIRST << (R / 4);       // banks of four lanes
                 z[i * 4] = (unsigned)__builtin_amdgcn_update_dpp((int)k0, (int)s0, UP, 0xf, SECOND, false);
                 z[i * 4 + 1] = (unsigned)__builtin_amdgcn_update_dpp((int)k1, (int)s1, UP, 0xf, SECOND, false);
                 z[i * 4 + 2] = (unsigned)__builtin_amdgcn_update_dpp((int)k0, (int)s0, DOWN, 0xf, FIRST, false);
@@ -494,28 +499,46 @@ __device__ __forceinline__ void stage(const RegW<res_tile_regs(BF, CLS, T)> &w, 
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] += dppf<0x100 + R>(v[i]);
         }
-        if (n < R) *reinterpret_cast<r4f *>(sums + (wave * R + n) * ROW + t * 16 + (lane >> 4) * 4) = v;
+        if (n < R && (t * 16 + 16 <= ROW || t * 16 + (lane >> 4) * 4 < ROW)) *reinterpret_cast<r4f *>(sums + (wave * R + n) * ROW + t * 16 + (lane >> 4) * 4) = v;
     }
 }
 
-// What a lane finishes in the LSTM stages, waves 0 .. 4: gate lane % 4 of unit 4 wave + lane / 16 for row lane / 4 % R.
-// Its sum over the waves:
+// What a lane finishes in the LSTM stages, waves 0 .. 4: of unit 4 wave + lane / 16 and row lane / LR % R (LR = 16 / R lanes a row), gate
+// lane % 4 (four rows), or two gates from 2 * (lane % 2) on (eight rows).
+template <int R> struct RGates {
+    static constexpr int N = R / 4;
+    float g[N];
+};
+// Its sums over the waves:
 template <int R>
-__device__ __forceinline__ float stage_sum(const float *sums, int blk, int lane)
+__device__ __forceinline__ RGates<R> stage_sum(const float *sums, int blk, int lane)
 {
-    const float *s = sums + ((unsigned)lane / 4 & (R - 1)) * kResStageRow + (blk * 4 + ((unsigned)lane >> 4)) * 4 + (lane & 3);
-    float o[kResWaves];
+    constexpr int LR = 16 / R, N = RGates<R>::N, ROW = res_stage_row(R);
+    typedef float Group __attribute__((ext_vector_type(N)));
+    const float *s = sums + ((unsigned)lane / LR & (R - 1)) * ROW + (blk * 4 + ((unsigned)lane >> 4)) * 4 + (lane & (LR - 1)) * N;
+    Group o[kResWaves];
 #pragma unroll
-    for (int w = 0; w < kResWaves; ++w) o[w] = s[w * R * kResStageRow];
-    return ((o[0] + o[1]) + (o[2] + o[3])) + ((o[4] + o[5]) + (o[6] + o[7]));
+    for (int w = 0; w < kResWaves; ++w) o[w] = *reinterpret_cast<const Group *>(s + w * R * ROW);
+    const Group sum = ((o[0] + o[1]) + (o[2] + o[3])) + ((o[4] + o[5]) + (o[6] + o[7]));
+    RGates<R> v;
+    if constexpr (N == 1) v.g[0] = sum[0];
+    else { v.g[0] = sum[0]; v.g[1] = sum[1]; }
+    return v;
 }
 
-// LSTM cell on the four adjacent lanes of a unit and row: lane j holds the pre-activation of gate j of i, f, g, o. Every
-// lane gets the results.
-__device__ __forceinline__ void cell(float pre, int j, float c_old, float &c_new, float &h)
+// LSTM cell on the adjacent lanes of a unit and row: lane j of four holds the pre-activation of gate j of i, f, g, o, or lane j of
+// two those of gates 2 j and 2 j + 1. Every lane gets the results.
+template <int R>
+__device__ __forceinline__ void cell(const RGates<R> &pre, int j, float c_old, float &c_new, float &h)
 {
-    const float act = gate_act(pre, j == 2);
-    const float i_ = dppf<0x00>(act), f_ = dppf<0x55>(act), g_ = dppf<0xAA>(act), o_ = dppf<0xFF>(act);
+    float i_, f_, g_, o_;
+    if constexpr (R == 4) {
+        const float act = gate_act(pre.g[0], j == 2);
+        i_ = dppf<0x00>(act); f_ = dppf<0x55>(act); g_ = dppf<0xAA>(act); o_ = dppf<0xFF>(act);
+    } else {
+        const float a = gate_act(pre.g[0], j == 1), b = gate_act(pre.g[1], false);
+        i_ = dppf<0xA0>(a); f_ = dppf<0xA0>(b); g_ = dppf<0xF5>(a); o_ = dppf<0xF5>(b);          // (lanes 0, 0, 2, 2 and 1, 1, 3, 3)
+    }
     c_new = fmaf(f_, c_old, i_ * g_);
     h = o_ * gate_act(c_new, true);
 }
@@ -576,8 +599,8 @@ __device__ __forceinline__ void res_finish_row(int b, int cnt)
 
 __device__ __forceinline__ int from_lane(int v, int lane) { return __builtin_amdgcn_ds_bpermute(lane << 2, v); }
 
-// KIND: ResidentKind; BF: bfloat16 mode; CLS: size class; NMT: tiles of 16 samples of a joint step
-template <int KIND, bool BF, int CLS, int NMT>
+// KIND: ResidentKind; BF: bfloat16 mode; CLS: size class; NMT: tiles of 16 samples of a joint step; R: rows of a team
+template <int KIND, bool BF, int CLS, int NMT, int R>
 __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const ResidentParams p)
 {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -586,19 +609,20 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     constexpr int W = res_width(CLS), ROW = res_row(CLS), TS = res_team(CLS);
     constexpr int NH = res_halves(CLS), NF = NH / 2, NB = NF + (NH & 1), LREGS = res_lstm_regs(BF, CLS);
     constexpr bool WHOLE = res_whole(BF, CLS);
-    constexpr int R = kResRows, LR = 16 / R;     // rows, lanes per row in the loop control
+    constexpr int LR = 16 / R, GL = R / 4, RB = R == 4 ? 2 : 3;      // lanes per row in the loop control and the cells, gates of such a lane; bits of a row's number
+    constexpr int STAGE_ROW = res_stage_row(R);
     typedef Operand<BF, CLS, R> Op;
     constexpr bool HALVES = PAIR && NMT == 2;     // steps with one tile of samples as well, see after the loop
     constexpr int NREC = PAIR ? 0 : NL;          // recurrent matrices the chain's work-groups hold
-    constexpr ResidentBuf bo = resident_buf(KIND, BF, CLS);
-    constexpr ResidentLds lo = resident_lds(KIND, BF, CLS, NMT);
+    constexpr ResidentBuf bo = resident_buf(KIND, BF, CLS, R);
+    constexpr ResidentLds lo = resident_lds(KIND, BF, CLS, NMT, R);
     constexpr unsigned VROW = W * 4u, VSLOT = R * VROW;                      // h and q rows
     constexpr unsigned ZSLOT = res_z_slot(BF, CLS), ZWAVE = res_z_wave(BF, CLS);   // the joint's operand
     constexpr int JREGS = res_joint_regs(BF, CLS);
     constexpr int ZS = 16 * NMT;                 // samples of the longest joint step
     constexpr int kFormers = 3;                  // see publish_z
     constexpr unsigned KSLOT = kResSamples * TS * 8u, DSLOT = kResSamples * kMaxDur * 4u;
-    constexpr unsigned QSLOT = TS * 5u * 64u * 4u, PSLOT = kResQuarters * QSLOT;         // pre-activations: a quarter of K, all
+    constexpr unsigned QSLOT = TS * 5u * 64u * 4u * GL, PSLOT = kResQuarters * QSLOT;         // pre-activations: a quarter of K, all
 
     RCtx x;
     const int tid0 = threadIdx.x, lane0 = tid0 & 63;         // (for the work before and after the loop)
@@ -653,7 +677,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 x.buf = buffers_of(team + i * pairs); any = true;
                 // (zeros where no unit is: nobody sends these words)
                 for (unsigned o = ((unsigned)x.rank * kResThreads + (unsigned)tid0) * 16u; o < kResSlots * PSLOT; o += TS * kResThreads * 16u) {
-                    const int word = (int)(o / 4u) % (TS * 320), r = word / 320, lu = word % 320 >> 4;
+                    const int word = (int)(o / 4u) % (TS * 320 * GL), r = word / (320 * GL), lu = word % (320 * GL) / (16 * GL);
                     const unsigned v = lu < p.pl.units && r * p.pl.units + lu < p.H ? kMark : 0u;
                     __builtin_amdgcn_raw_buffer_store_b128((r4u){v, v, v, v}, x.buf, (int)(bo.pre + my_layer * kResSlots * PSLOT + o), 0, 16);
                 }
@@ -663,8 +687,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     if (tid0 == 0) { rc.ok = 1; rc.n_list = 0; rc.st_clamped = 0; rc.st_overflow = 0; }
     if (tid0 < kResSamples) { rc.s_k[tid0] = p.blank; rc.s_d[tid0] = 0; }
     if (tid0 < kMaxDur) rc.dur[tid0] = p.durations[tid0];
-    if (tid0 < kResRows) rc.scale[tid0] = 1.f;
-    if (lane0 < kResRows) {
+    if (tid0 < RRows::kPlaces) rc.scale[tid0] = 1.f;
+    if (lane0 < RRows::kPlaces) {
         RRows &w = rc.rows[x.wave];
         w.s[lane0] = RRow{0, 0, 0, 0}; w.b[lane0] = w.since[lane0] = w.next = 0;
     }
@@ -709,7 +733,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     const bool has_cells = x.wave < 5;          // finishes 16 (unit, row) pairs of the LSTM stages, see stage_sum
     // (beyond the buffer for waves without cells, whose loads give zeros: a branch around the loads would make the
     // compiler wait for them where it waits for an older one)
-    unsigned pre_wave = has_cells ? ((unsigned)x.rank * 5u + (unsigned)x.wave) * 256u : 0x80000000u;
+    unsigned pre_wave = has_cells ? ((unsigned)x.rank * 5u + (unsigned)x.wave) * (256u * GL) : 0x80000000u;
     asm volatile("" : "+s"(pre_wave));
     const int h4 = p.H >> 2;
 
@@ -720,8 +744,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         // the next step: 8.5 us a step of 32 utterances now, 9.4 then, of 128 utterances 9.0 and 9.8.  The chain adds the quarters.
         // Twenty tiles of four units, three for the first four waves and two for the others (waves w and w + 4
         // share a SIMD), which need no sums from each other.  The columns of the matrix instructions are the rows of two
-        // teams, in two parts.
-        static_assert(!BF, "two teams' rows in two parts are the sixteen columns");
+        // teams of four rows, in two parts, or of one team of eight.
+        static_assert(!BF, "the rows in two parts are the sixteen columns");
+        constexpr int PER = 8 / R;                // teams of a set of columns
         constexpr int HB = res_help_blocks(CLS), HREGS = res_help_regs(CLS);
         const int quarter = x.rank & 3, first_unit = (x.rank >> 2) * 80, tile0 = x.wave < 4 ? x.wave * 3 : x.wave * 2 + 4;
         const bool third = x.wave < 4;
@@ -733,8 +758,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
 #pragma unroll
         for (int i = 0; i < kResServed; ++i)
             if (serves(i)) { (void)meet(team + i * pairs, false); live |= 1u << i; }
-        // LDS: the scales of the work-group's outputs; twice, for vectors that come and those in work, [two teams][block][lane]
-        constexpr int TWOS = kResServed / 2, AREA = TWOS * HB * 1024, AT = 2048;
+        // LDS: the scales of the work-group's outputs; twice, for vectors that come and those in work, [set of columns][block][lane]
+        constexpr int SETS = kResServed / PER, AREA = SETS * HB * 1024, AT = 2048;
         static_assert(AT + 2 * AREA <= lo.bytes, "the helpers' layout fits");
         for (int i = tid0; i < 320; i += kResThreads)
             reinterpret_cast<float *>(lds)[i] = first_unit * 4 + i < p.H * 4 ? p.s_hh[my_layer][first_unit * 4 + i] : 0.f;
@@ -744,37 +769,38 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         const unsigned apart = (unsigned)pairs * bo.bytes;       // from one team to the next
         const unsigned char *base = p.xbuf + (size_t)team * bo.bytes;
         x.buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(base), 0, (int)((kResServed - 1) * apart + bo.bytes), 0x00020000);
-        // Where the lane's words of block 0 are in a vector, columns 8 .. 15 being the second team, see Operand::offset; and where its
+        // Where the lane's words of block 0 are in a vector, of teams of four rows columns 8 .. 15 being the second, see Operand::offset; and where its
         // results go (beyond the buffer: nowhere)
         const int col = lane0 & 15, g = lane0 >> 4;
-        const unsigned row_at = (my_layer ? bo.hr[1] : bo.hr[0]) + (unsigned)(lane0 & 3) * VROW + (lane0 & 8 ? apart : 0u);
-        const int piece = quarter * (HB * 8) + 2 * g + (col >> 2 & 1);
-        const bool has_words = (lane0 & 3) < p.slots;
+        const unsigned row_at = (my_layer ? bo.hr[1] : bo.hr[0]) + (unsigned)(lane0 & (R - 1)) * VROW + (PER == 2 && (lane0 & 8) ? apart : 0u);
+        const int piece = quarter * (HB * 8) + 2 * g + (col / R & 1);
+        const bool has_words = (lane0 & (R - 1)) < p.slots;
         unsigned to[3];
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
             const int u = first_unit + (tile0 + t) * 4 + g, of = u / p.pl.units, lu = u - of * p.pl.units;
-            to[t] = u < p.H && (col & 4) == 0 ? (((unsigned)of * 5u + (unsigned)(lu >> 2)) * 64u + (unsigned)((lu & 3) * 16 + (col & 3) * 4)) * 4u : 0x80000000u;
+            to[t] = u < p.H && (col & R) == 0 ? (((unsigned)of * 5u + (unsigned)(lu >> 2)) * (64u * GL) + (unsigned)((lu & 3) * (16 * GL) + (col & (R - 1)) * 4)) * 4u : 0x80000000u;
         }
         // bit i: the two bits of the number of team i's next vector, modulo the slots
         unsigned low = ~0u, high = 0;
         auto slot_of = [](unsigned low_, unsigned high_, int i) { return (low_ >> i & 1u) | (high_ >> i & 1u) << 1; };
-        // Loads of (two teams, block) go round the waves, two for each: f(two teams, block)
+        // Loads of (set of columns, block) go round the waves: f(set, block)
+        constexpr unsigned OF_SET = (1u << PER) - 1u;
         auto own = [&](auto f) {
 #pragma unroll
-            for (int i = 0; i < (TWOS * HB + kResWaves - 1) / kResWaves; ++i) {
+            for (int i = 0; i < (SETS * HB + kResWaves - 1) / kResWaves; ++i) {
                 const int at = x.wave + i * kResWaves, q = at / HB;
-                if (at < TWOS * HB && (live >> (q * 2) & 3u) != 0u) f(q, at - q * HB);
+                if (at < SETS * HB && (live >> (q * PER) & OF_SET) != 0u) f(q, at - q * HB);
             }
         };
         unsigned spins = 0, par = 0;
         auto ask = [&]() {
             own([&](int q, int kb) {
-                const unsigned a = slot_of(low, high, q * 2) * VSLOT, b = slot_of(low, high, q * 2 + 1) * VSLOT, of = live >> (q * 2) & 3u;
-                const bool second = (lane_id() & 8) != 0;
+                const unsigned a = slot_of(low, high, q * PER) * VSLOT, b = slot_of(low, high, q * PER + PER - 1) * VSLOT, of = live >> (q * PER) & OF_SET;
+                const bool second = PER == 2 && (lane_id() & 8) != 0;
                 if (has_words && (of & (second ? 2u : 1u)) != 0u)
                     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 sc1"
-                                 :: "v"(row_at + (unsigned)min(piece + kb * 8, h4 - 1) * 16u + (unsigned)(q * 2) * apart + (second ? b : a)),
+                                 :: "v"(row_at + (unsigned)min(piece + kb * 8, h4 - 1) * 16u + (unsigned)(q * PER) * apart + (second ? b : a)),
                                     "s"(area_m0 + par * AREA + (unsigned)((q * HB + kb) * 1024)), "s"(base) : "memory");
             });
         };
@@ -786,15 +812,16 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             else if (stored < 6) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
             else if (stored < 8) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
             else if (stored < 12) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-            else asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+            else if (R == 4 || stored < 24) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
             stored = 0;
             const int area = AT + (int)par * AREA;
             unsigned f = 0;                        // bits 0 ..: words of team i's vector are missing; bits 8 ..: it says stop
             own([&](int q, int kb) {
                 const r4u v = *reinterpret_cast<const r4u *>(lds + area + (q * HB + kb) * 1024 + lane_id() * 16);
                 const unsigned long long m = __ballot(has_words && has_mark(v)), stop = __ballot(v.x == kStop);
-                constexpr unsigned long long FIRST = 0x00ff00ff00ff00ffull;
-                f |= (((m & FIRST) != 0ull ? 1u : 0u) | ((stop & FIRST) != 0ull ? 256u : 0u) | ((m & ~FIRST) != 0ull ? 2u : 0u) | ((stop & ~FIRST) != 0ull ? 512u : 0u)) << (q * 2);
+                constexpr unsigned long long FIRST = PER == 2 ? 0x00ff00ff00ff00ffull : ~0ull;
+                f |= (((m & FIRST) != 0ull ? 1u : 0u) | ((stop & FIRST) != 0ull ? 256u : 0u) | ((m & ~FIRST) != 0ull ? 2u : 0u) | ((stop & ~FIRST) != 0ull ? 512u : 0u)) << (q * PER);
             });
             if (lane_id() == 0) rc.seen[par][x.wave] = f;
             __syncthreads();
@@ -817,22 +844,23 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             while (todo != 0u) {
                 const int one = __builtin_ctz(todo);
                 todo &= todo - 1u;
-                const int two = todo != 0u ? __builtin_ctz(todo) : -1;
-                todo &= todo - (todo != 0u ? 1u : 0u);
+                const int two = PER == 2 && todo != 0u ? __builtin_ctz(todo) : -1;
+                if (PER == 2) todo &= todo - (todo != 0u ? 1u : 0u);
                 const int lane = lane_id(), of = (lane & 8) != 0 && two >= 0 ? two : one;
-                const int at = area + (of >> 1) * (HB * 1024) + ((lane & ~8) | (of & 1) << 3) * 16;
+                const int at = PER == 2 ? area + (of >> 1) * (HB * 1024) + ((lane & ~8) | (of & 1) << 3) * 16 : area + one * (HB * 1024) + lane * 16;
                 unsigned z[HB * 4];
 #pragma unroll
                 for (int kb = 0; kb < HB; ++kb) {
                     const r4u v = *reinterpret_cast<const r4u *>(lds + at + kb * 1024);
-                    const bool other = (lane & 4) != 0;
+                    const bool other = (lane & R) != 0;
                     const unsigned keep = other ? 0x07060302u : 0x05040100u, send = other ? 0x05040100u : 0x07060302u;
                     const unsigned k0 = __builtin_amdgcn_perm(v.y, v.x, keep), k1 = __builtin_amdgcn_perm(v.w, v.z, keep);
                     const unsigned s0 = __builtin_amdgcn_perm(v.y, v.x, send), s1 = __builtin_amdgcn_perm(v.w, v.z, send);
-                    z[kb * 4] = (unsigned)__builtin_amdgcn_update_dpp((int)k0, (int)s0, 0x114, 0xf, 0xa, false);
-                    z[kb * 4 + 1] = (unsigned)__builtin_amdgcn_update_dpp((int)k1, (int)s1, 0x114, 0xf, 0xa, false);
-                    z[kb * 4 + 2] = (unsigned)__builtin_amdgcn_update_dpp((int)k0, (int)s0, 0x104, 0xf, 0x5, false);
-                    z[kb * 4 + 3] = (unsigned)__builtin_amdgcn_update_dpp((int)k1, (int)s1, 0x104, 0xf, 0x5, false);
+                    constexpr int UP = 0x110 + R, DOWN = 0x100 + R, LOWER = R == 4 ? 0x5 : 0x3, UPPER = 0xf ^ LOWER;       // (banks of four lanes)
+                    z[kb * 4] = (unsigned)__builtin_amdgcn_update_dpp((int)k0, (int)s0, UP, 0xf, UPPER, false);
+                    z[kb * 4 + 1] = (unsigned)__builtin_amdgcn_update_dpp((int)k1, (int)s1, UP, 0xf, UPPER, false);
+                    z[kb * 4 + 2] = (unsigned)__builtin_amdgcn_update_dpp((int)k0, (int)s0, DOWN, 0xf, LOWER, false);
+                    z[kb * 4 + 3] = (unsigned)__builtin_amdgcn_update_dpp((int)k1, (int)s1, DOWN, 0xf, LOWER, false);
                 }
                 r4f sum[3];
 #pragma unroll
@@ -848,7 +876,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 if (third) multiply(std::integral_constant<int, 3>());
                 else multiply(std::integral_constant<int, 2>());
                 const unsigned slot1 = slot_of(low0, high0, one), slot2 = two >= 0 ? slot_of(low0, high0, two) : 0u;
-                const bool second = (lane & 8) != 0;
+                const bool second = PER == 2 && (lane & 8) != 0;
                 const unsigned mine = second ? (two >= 0 ? (unsigned)two * apart + slot2 * PSLOT : 0x80000000u) : (unsigned)one * apart + slot1 * PSLOT;
                 const unsigned clear = second ? (two >= 0 ? (unsigned)two * apart + (slot2 ^ 2u) * PSLOT : 0x80000000u) : (unsigned)one * apart + (slot1 ^ 2u) * PSLOT;
 #pragma unroll
@@ -856,7 +884,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     if (t == 2 && !third) break;
                     r4f v = sum[t];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) v[i] += dppf<0x104>(v[i]);
+                    for (int i = 0; i < 4; ++i) v[i] += dppf<0x100 + R>(v[i]);
                     v *= *reinterpret_cast<const r4f *>(lds + ((tile0 + t) * 16 + g * 4) * 4);
                     const r4u o = {word_of(v[0]), word_of(v[1]), word_of(v[2]), word_of(v[3])}, mark = {kMark, kMark, kMark, kMark};
                     // (no lane condition around the stores: every one has to be counted)
@@ -1013,14 +1041,30 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     float *state = reinterpret_cast<float *>(lds + lo.state);
     auto stored = [&]() { return state + x.wave * 64 + lane_id(); };               // (fields 5 * 64 floats apart)
     constexpr int FIELD = 5 * 64;
-    float cs[NL], cc[NL], ps[NL];
-    unsigned pre[NL][kResQuarters];
+    typedef RGates<R> Gates;
+    constexpr int FIELDS = 2 + GL;
+    float cs[NL], cc[NL];
+    Gates ps[NL];
+    unsigned pre[NL][kResQuarters][GL];
+    auto clear_state = [&](int l) {
+        cs[l] = cc[l] = 0.f;
+#pragma unroll
+        for (int e = 0; e < GL; ++e) ps[l].g[e] = 0.f;
+    };
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
-        cs[l] = cc[l] = ps[l] = 0.f;
+        clear_state(l);
 #pragma unroll
-        for (int i = 0; i < kResQuarters; ++i) pre[l][i] = 0u;
+        for (int i = 0; i < kResQuarters; ++i)
+#pragma unroll
+            for (int e = 0; e < GL; ++e) pre[l][i][e] = 0u;
     }
+    auto keep_state = [&](int l) {
+        float *to = stored() + l * FIELDS * FIELD;
+        to[0] = cs[l]; to[FIELD] = cc[l];
+#pragma unroll
+        for (int e = 0; e < GL; ++e) to[(2 + e) * FIELD] = ps[l].g[e];
+    };
     unsigned n_pred = 0, n_joint = 0;
 
     RRows &rows = rc.rows[x.wave];
@@ -1030,9 +1074,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // of the projected frames, -1 for none.
     int last = p.blank, pidx = -1;
     // What a lane needs of the loop control's tables, packed (a register each would be one too many): rows of the
-    // samples lane / 2, four times the wave plus lane / 16 (of the work-group's tile), and lane (2 bits each, at 0, 16 and 28);
-    // bytes to the word of a row of T0 that its cell takes (2 .. 13); the place of sample `lane` among its row's
-    // (5 bits, at 18); its own row's first sample (5, at 23); kTake and kFresh.
+    // samples lane / 2, four times the wave plus lane / 16 (of the work-group's tile), and lane (RB bits each, at 0, 14 and 17);
+    // bytes to the words of a row of T0 that its cell takes (RB .. 13); the place of sample `lane` among its row's
+    // (5 bits, at 20); its own row's first sample (5, at 25); kTake and kFresh.
     int lane_const = kFresh;
     // Rows that take part in the joint step (one bit in four, as in LEADS), and the frames of each: the samples are dealt
     // evenly to the rows with an utterance, so that the last ones of a team's list go on faster when the others have
@@ -1047,26 +1091,32 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         part_rows = of;
         const int n = __builtin_popcount(of);
         // (a byte for every number of rows; label-dense: no more than a team of all rows has, they are not looked at)
-        la = (int)((decltype(nt_)::value == 2 ? 0x080a101fu : NMT == 1 ? 0x04050810u : 0x04050505u) >> (max(n - 1, 0) * 8) & 0xffu);
+        la = (int)((decltype(nt_)::value == 2 ? 0x04040506080a101full : NMT == 1 ? 0x02020203'04050810ull : R == 4 ? 0x04050505ull : 0x0202020304050505ull) >> (max(n - 1, 0) * 8) & 0xffu);
         unsigned rows_of = 0;            // the rows that take part, one after the other, two bits each
         int at = 0;
 #pragma unroll
         for (int r = 0; r < R; ++r)
-            if (of >> (r * LR) & 1u) { rows_of |= (unsigned)r << at; at += 2; }
-        auto turn_of = [&](int s) { return (s >= la ? 1 : 0) + (s >= 2 * la ? 1 : 0) + (s >= 3 * la ? 1 : 0); };
-        auto row_of = [&](int s) { return (int)(rows_of >> (turn_of(s) * 2) & 3u); };
+            if (of >> (r * LR) & 1u) { rows_of |= (unsigned)r << at; at += RB; }
+        // (s / la, rounded down: half a sample from where it changes, so that the reciprocal's last bits say nothing)
+        const float inverse = __builtin_amdgcn_rcpf((float)la);
+        auto turn_of = [&](int s) {
+            if constexpr (R == 4) return (s >= la ? 1 : 0) + (s >= 2 * la ? 1 : 0) + (s >= 3 * la ? 1 : 0);
+            else return (int)(((float)s + 0.5f) * inverse);
+        };
+        auto row_of = [&](int s) { return (int)(rows_of >> (turn_of(s) * RB) & (R - 1)); };
         const int s = lane & (ZS - 1);
         const Place l = place_of(lane);
-        const int first = __builtin_popcount(of & ((1u << (lane & 12)) - 1u)) * la;
-        lane_const = row_of(lane / 2 & (ZS - 1)) | l.gu * 16 + l.j * 4 | row_of(((x.wave * 4 + (lane >> 4)) & 15) + (decltype(nt_)::value == 2 ? half * 16 : 0)) << 16 |
-                     ((s - turn_of(s) * la) & 31) << 18 | (first & 31) << 23 | row_of(s) << 28 | (lane_const & (kTake | kFresh));
+        const int first = __builtin_popcount(of & ((1u << (lane & (16 - LR))) - 1u)) * la;
+        lane_const = row_of(lane / 2 & (ZS - 1)) | l.gu * 16 + l.j * (4 * GL) |
+                     row_of(((x.wave * 4 + (lane >> 4)) & 15) + (decltype(nt_)::value == 2 ? half * 16 : 0)) << 14 | row_of(s) << 17 |
+                     ((s - turn_of(s) * la) & 31) << 20 | (first & 31) << 25 | (lane_const & (kTake | kFresh));
     };
     std::integral_constant<int, NMT> all_tiles;
     // Samples of the next joint step: the next `la` frames of every row in work.
     auto set_up_samples = [&](int lane, int t, int b, int len) {
-        const int from = (lane_const >> 28 & 3) * (LR * 4);                         // (bytes: LR lanes per row)
+        const int from = (lane_const >> 17 & (R - 1)) * (LR * 4);                         // (bytes: LR lanes per row)
         const int base = __builtin_amdgcn_ds_bpermute(from, b * p.T + t), left = __builtin_amdgcn_ds_bpermute(from, len - t);
-        const int off = lane_const >> 18 & 31;
+        const int off = lane_const >> 20 & 31;
         pidx = ((lane & (ZS - 1)) < part_samples() && off < left) ? base + off : -1;
         n_samples += __popcll(__ballot(pidx >= 0 && lane < ZS));
     };
@@ -1079,11 +1129,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     };
     // Two columns of a sample for a lane, four columns of 32 samples for a wave (of 16: eight): waves kFormers and after.
     auto publish_z = [&](auto nt_, unsigned n) {
-        const int lane = lane_id(), s = lane / 2 & (ZS - 1), cg = (x.wave - kFormers) * (32 / ZS) + lane / (2 * ZS), row = lane_const & 3;
-        const float *v = sums_pr + row * kResSumRow + cg * 4 + (lane & 1) * 2;
+        const int lane = lane_id(), s = lane / 2 & (ZS - 1), cg = (x.wave - kFormers) * (32 / ZS) + lane / (2 * ZS), row = lane_const & (R - 1);
+        const float *v = sums_pr + row * kResProjRow + min(cg, kResProjRow / 4 - 1) * 4 + (lane & 1) * 2;
         r2f o[kResWaves];
 #pragma unroll
-        for (int w = 0; w < kResWaves; ++w) o[w] = *reinterpret_cast<const r2f *>(v + w * (R * kResSumRow));
+        for (int w = 0; w < kResWaves; ++w) o[w] = *reinterpret_cast<const r2f *>(v + w * (R * kResProjRow));
         const r2f frame = *reinterpret_cast<const r2f *>(lds + lo.p + (cg * ZS + s) * 16 + (lane & 1) * 8);
         const unsigned to = reinterpret_cast<const unsigned *>(lds + lo.z_at)[cg * ZS + s] + (lane & 1) * (BF ? 4u : 8u);
         const r2f bias = *reinterpret_cast<const r2f *>(rc.bp + cg * 4 + (lane & 1) * 2), by = *reinterpret_cast<const r2f *>(rc.sp + cg * 4 + (lane & 1) * 2);
@@ -1107,7 +1157,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     };
     // Rows that want one get the next utterances of the list.  (Control state is by row: every lane works on
     // row lane / LR % R, and the first of LR lanes below 16 stands for its row in ballots.)
-    constexpr unsigned long long LEADS = 0x1111ull;
+    constexpr unsigned long long LEADS = R == 4 ? 0x1111ull : 0x5555ull;
     bool queued = false;               // utterances of the list wait for a row
     auto refill = [&](int lane, bool want, int &b, int &len) {
         const unsigned long long m = __ballot(want) & LEADS;
@@ -1136,24 +1186,32 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         set_up_samples(lane0, 0, b, len);
     }
     // the row of the embedding table (folded into the first layer) that the next prediction step adds
-    float t0 = 0.f;
+    Gates t0{};
     const unsigned t0_row = (unsigned)p.H * 16u;
     auto load_t0 = [&]() {
-        t0 = 0.f;
+        t0 = Gates{};
         if (has_cells)
-            t0 = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(p.T0) + (__umul24((unsigned)last, t0_row) + ((unsigned)lane_const & 0x3ffcu)));
+            t0 = *reinterpret_cast<const Gates *>(reinterpret_cast<const char *>(p.T0) + (__umul24((unsigned)last, t0_row) + ((unsigned)lane_const & (0x3fffu & ~(R - 1u)))));
     };
     // kResident2Pair: W_hh h of the last step's candidates of a layer as far as it is there
-    auto load_pre = [&](unsigned n, int l, unsigned (&to)[kResQuarters]) {
+    auto load_pre = [&](unsigned n, int l, unsigned (&to)[kResQuarters][GL]) {
         const unsigned slot = bo.pre + slot_at(n, PSLOT) + (unsigned)l * kResSlots * PSLOT;
-        const unsigned o = pre_wave + (unsigned)lane_id() * 4u;
+        const unsigned o = pre_wave + (unsigned)lane_id() * (4u * GL);
 #pragma unroll
-        for (int i = 0; i < kResQuarters; ++i) to[i] = get1(x, o, slot + i * QSLOT);
+        for (int i = 0; i < kResQuarters; ++i) {
+            if constexpr (GL == 1) to[i][0] = get1(x, o, slot + i * QSLOT);
+            else {
+                const r2u v = get2(x, o, slot + i * QSLOT);
+                to[i][0] = v.x; to[i][1] = v.y;
+            }
+        }
     };
-    auto no_pre = [&](const unsigned (&w)[kResQuarters]) {
-        unsigned m = w[0];
+    auto no_pre = [&](const unsigned (&w)[kResQuarters][GL]) {
+        unsigned m = 0u;
 #pragma unroll
-        for (int i = 1; i < kResQuarters; ++i) m = max(m, w[i]);
+        for (int i = 0; i < kResQuarters; ++i)
+#pragma unroll
+            for (int e = 0; e < GL; ++e) m = max(m, w[i][e]);
         return __ballot(m == kMark) != 0ull;
     };
     auto wait_pre = [&](unsigned n, int l) {
@@ -1215,8 +1273,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 const float *from = stored();
 #pragma unroll
                 for (int l = 0; l < NL; ++l) {
-                    cs[l] = cc[l] = ps[l] = 0.f;
-                    if (has_cells) { cs[l] = from[l * 3 * FIELD]; cc[l] = from[(l * 3 + 1) * FIELD]; ps[l] = from[(l * 3 + 2) * FIELD]; }
+                    clear_state(l);
+                    if (has_cells) {
+                        cs[l] = from[l * FIELDS * FIELD]; cc[l] = from[(l * FIELDS + 1) * FIELD];
+#pragma unroll
+                        for (int e = 0; e < GL; ++e) ps[l].g[e] = from[(l * FIELDS + 2 + e) * FIELD];
+                    }
                 }
             }
             // rows that emitted take their candidate state, fresh rows start from zero (kResident2: the second
@@ -1225,18 +1287,28 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             // a stage's sum for the lane, as it is to be used
             auto sum_of = [&](const float *sums, const float *scales) {
                 const int lane = lane_id();
-                const float v = stage_sum<R>(sums, x.wave, lane);
-                return BF ? v : v * scales[(x.wave * 4 + (lane >> 4)) * 4 + (lane & 3)];
+                Gates v = stage_sum<R>(sums, x.wave, lane);
+                if constexpr (!BF) {
+#pragma unroll
+                    for (int e = 0; e < GL; ++e) v.g[e] *= scales[(x.wave * 4 + (lane >> 4)) * 4 + (lane & (LR - 1)) * GL + e];
+                }
+                return v;
             };
             auto commit = [&](int l) {
                 // (Zero for waves without cells, but from a variable: with a constant the compiler waits for the row of T0, and with it
                 // for everything, between the loads of two frames: bfloat16 mode 1035 instead of 962 us for 32 utterances.)
-                float pc = __uint_as_float(pre[l][0]);
-                if constexpr (PAIR) pc = (pc + __uint_as_float(pre[l][1])) + (__uint_as_float(pre[l][2]) + __uint_as_float(pre[l][3]));
-                else if (has_cells) pc = sum_of(l == NL - 1 ? sums_top : sums_rec0, rc.sh[l]);
+                Gates pc;
+#pragma unroll
+                for (int e = 0; e < GL; ++e) {
+                    pc.g[e] = __uint_as_float(pre[l][0][e]);
+                    if constexpr (PAIR) pc.g[e] = (pc.g[e] + __uint_as_float(pre[l][1][e])) + (__uint_as_float(pre[l][2][e]) + __uint_as_float(pre[l][3][e]));
+                }
+                if constexpr (!PAIR)
+                    if (has_cells) pc = sum_of(l == NL - 1 ? sums_top : sums_rec0, rc.sh[l]);
                 const bool take = lane_const & kTake, fresh_row = lane_const & kFresh;       // (bits: as a chain of comparisons it became branches)
                 cs[l] = take ? cc[l] : cs[l]; cs[l] = fresh_row ? 0.f : cs[l];
-                ps[l] = take ? pc : ps[l]; ps[l] = fresh_row ? 0.f : ps[l];
+#pragma unroll
+                for (int e = 0; e < GL; ++e) { ps[l].g[e] = take ? pc.g[e] : ps[l].g[e]; ps[l].g[e] = fresh_row ? 0.f : ps[l].g[e]; }
             };
             // publishes the lane's hidden value of a layer and clears the slot of two steps ago
             unsigned word = 0;
@@ -1265,9 +1337,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 commit(0);
                 const Place l = place_of(lane_id());
                 float h;
-                cell(ps[0] + t0, l.j, cs[0], cc[0], h);
+                Gates in;
+#pragma unroll
+                for (int e = 0; e < GL; ++e) in.g[e] = ps[0].g[e] + t0.g[e];
+                cell<R>(in, l.j, cs[0], cc[0], h);
                 publish_h(0, l, h);
-                if constexpr (PAIR) { float *to = stored(); to[0] = cs[0]; to[FIELD] = cc[0]; to[2 * FIELD] = ps[0]; }
+                if constexpr (PAIR) keep_state(0);
                 if constexpr (NREC > 1) commit(1);
                 if (NMT == 2 && later) {
                     const int lane = lane_id(), r = (int)((unsigned)lane / LR) & (R - 1);
@@ -1283,15 +1358,19 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 load_frames((x.wave - 5) * (64 / ZS), true);
                 if constexpr (FRAMES_FIRST) __builtin_amdgcn_s_setprio(0);
                 x1.receive_from(p, x, bo.h[0] + slot_at(n, VSLOT), h4);
-                asm volatile("" :: "v"(t0), "v"(pre[0][0]), "v"(pre[0][1]), "v"(pre[0][2]), "v"(pre[0][3]));
+#pragma unroll
+                for (int e = 0; e < GL; ++e)
+                    asm volatile("" :: "v"(t0.g[e]), "v"(pre[0][0][e]), "v"(pre[0][1][e]), "v"(pre[0][2][e]), "v"(pre[0][3][e]));
             }
             RES_MARK(2);
             if constexpr (NL > 1) {
                 const Op x0 = x1;
                 // (The second layer's results come during the stage.  Asked for at the end of the last step as well, they were there
-                // sooner, but no step was shorter: with one utterance 6.83 against 6.78 us.)
-                if (PAIR) { load_pre(n - 1, NL - 1, pre[NL - 1]); forward_h(0); }
-                stage<BF, CLS, R, 5, kResStageRow>(w_ih, x0, sums_ih, x.wave);
+                // sooner, but no step was shorter: with one utterance 6.83 against 6.78 us.  Eight rows: twice as many registers, and four of weights
+                // were read back in every step; asked for behind the stage, 128 utterances 3048 and 3014 us.)
+                if (PAIR) { if (R == 4) load_pre(n - 1, NL - 1, pre[NL - 1]); forward_h(0); }
+                stage<BF, CLS, R, 5, STAGE_ROW>(w_ih, x0, sums_ih, x.wave);
+                if (PAIR && R == 8) load_pre(n - 1, NL - 1, pre[NL - 1]);
                 __syncthreads();
                 RES_MARK(3);
                 if constexpr (PAIR) {
@@ -1301,9 +1380,12 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 if (has_cells) {
                     const Place l = place_of(lane_id());
                     float h;
-                    cell(sum_of(sums_ih, rc.s1) + (ps[1] + rc.b1[l.lu * 4 + l.j]), l.j, cs[1], cc[1], h);
+                    Gates in = sum_of(sums_ih, rc.s1);
+#pragma unroll
+                    for (int e = 0; e < GL; ++e) in.g[e] += ps[1].g[e] + rc.b1[l.lu * 4 + l.j * GL + e];
+                    cell<R>(in, l.j, cs[1], cc[1], h);
                     publish_h(1, l, h);
-                    if constexpr (PAIR) { float *to = stored() + 3 * FIELD; to[0] = cs[1]; to[FIELD] = cc[1]; to[2 * FIELD] = ps[1]; }
+                    if constexpr (PAIR) keep_state(1);
                 }
                 RES_MARK(4);
                 // (while the hand-over is on its way) the recurrent part of the next step's first layer
@@ -1313,7 +1395,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
 #pragma unroll
                         for (int i = 0; i < NB; ++i) off[i] = Op::offset(i, x.wave, lane, h4);
                     };
-                    stage<BF, CLS, R, 5, kResStageRow>(w_hh[0], x0, sums_rec0, x.wave, [&]() {
+                    stage<BF, CLS, R, 5, STAGE_ROW>(w_hh[0], x0, sums_rec0, x.wave, [&]() {
                         unsigned off[NB];
                         const int lane = lane_id();
                         places(off, lane);
@@ -1340,7 +1422,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             }
             RES_MARK(6);
             // prediction-side joint projection
-            stage<BF, CLS, R, 2, kResSumRow>(w_pr, x1, sums_pr, x.wave);
+            stage<BF, CLS, R, 2, kResProjRow>(w_pr, x1, sums_pr, x.wave);
             // this wave's frames are in LDS (what the other waves have stored by now, marks too, their polls for z wait for)
             if (x.wave >= 5) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
@@ -1349,7 +1431,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             // (while z is on its way) the recurrent part of the top layer's next step
             if constexpr (NREC > 0) {
                 // (The first tile is asked for when the work that fills the time is all but done.)
-                stage<BF, CLS, R, 5, kResStageRow>(w_hh[NREC - 1], x1, sums_top, x.wave, [&]() { ask_z(); ordered(); });
+                stage<BF, CLS, R, 5, STAGE_ROW>(w_hh[NREC - 1], x1, sums_top, x.wave, [&]() { ask_z(); ordered(); });
             } else {
                 ask_z();
             }
@@ -1514,7 +1596,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 if (again != 0u) again &= (unsigned)__ballot(pidx >= 0) >> (NT == 2 ? half * 16 : 0);
                 if (again != 0u) {
                     const int lane = lane_id(), m16 = lane & 15, g = lane >> 4;
-                    const float scale = rc.scale[from_lane(lane_const, (NT == 2 ? half * 16 : 0) + m16) >> 28 & 3], back = inverse_power(scale);
+                    const float scale = rc.scale[from_lane(lane_const, (NT == 2 ? half * 16 : 0) + m16) >> 17 & (R - 1)], back = inverse_power(scale);
                     const bool mine = (again >> m16 & 1u) != 0u;
                     ask_z();
 #pragma unroll 1
@@ -1576,7 +1658,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 const float2 bias = rc.bo[side][tid & 15], scale = rc.so[side][tid & 15];
                 static_assert(kResWaves == 8, "eight lanes add the waves' sums of the tail column");
                 float tw = 0.f, back = 1.f;
-                if constexpr (!BF && !WHOLE) back = inverse_power(rc.scale[lane_const >> 16 & 3]);
+                if constexpr (!BF && !WHOLE) back = inverse_power(rc.scale[lane_const >> 14 & (R - 1)]);
                 const bool tail_here = side < n_tails;
                 if (tail_here) tw = tpart[((tid & 7) * 2 + side) * 16 + (at & 15)];
                 const float l0 = (((o[0].x + o[1].x) + (o[2].x + o[3].x)) + ((o[4].x + o[5].x) + (o[6].x + o[7].x))) * scale.x * back + bias.x;
@@ -1724,9 +1806,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             __syncthreads();
             RES_MARK(14);
             if (FRAMES_FIRST && !has_cells) __builtin_amdgcn_s_setprio(2);
-            const int mine = rc.s_k[lane & (kResSamples - 1)], row0 = lane_const >> 23 & 31;
+            const int mine = rc.s_k[lane & (kResSamples - 1)], row0 = lane_const >> 25 & 31;
             // (a row that does not take part has nothing left for now)
-            const bool in = (part_rows >> (lane & 12) & 1u) != 0u;
+            const bool in = (part_rows >> (lane & (16 - LR)) & 1u) != 0u;
             const int left = in ? w.len - w.t : 0;
             const bool lead = lane < 16 && (lane & (LR - 1)) == 0;     // stands for its row
             const bool writer = x.rank == 0 && x.wave == kResWaves - 1 && lead;
@@ -1743,7 +1825,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 // lane = sample: the offset (from the row's frame) that the walk goes to from it, its own for a label
                 // or beyond the row's frames, and the lane of that offset, its own where the walk leaves the step;
                 // then the hops are doubled until every one reaches its end
-                const int si = lane_const >> 18 & 31;
+                const int si = lane_const >> 20 & 31;
                 int d = 0;
                 if (mine >= p.V1) d = max(rc.dur[(mine - p.V1) & (kMaxDur - 1)], 1);            // big blank: its span of frames
                 else if (mine == p.blank) d = p.tdt ? min(max(rc.s_d[lane & (kResSamples - 1)], 1), kFarthest) : 1;
@@ -1806,6 +1888,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             // with a step at every label.)
             int most = w.len - w.t;
             const int rest = most;
+            if constexpr (R == 8) asm("s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_ror:2 row_mask:0xf bank_mask:0xf" : "+v"(most));
             asm("s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
                 "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf" : "+v"(most));
             const unsigned longest = (unsigned)__ballot(rest == most) & active;
@@ -1892,11 +1975,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     }
 }
 
-template <int KIND, bool BF, int CLS, int NMT>
+template <int KIND, bool BF, int CLS, int NMT, int R>
 hipError_t launch_resident_one(const ResidentParams &p, bool plain, hipStream_t stream)
 {
-    const void *fn = reinterpret_cast<const void *>(&resident_kernel<KIND, BF, CLS, NMT>);
-    constexpr unsigned lds = (unsigned)resident_lds(KIND, BF, CLS, NMT).bytes;
+    const void *fn = reinterpret_cast<const void *>(&resident_kernel<KIND, BF, CLS, NMT, R>);
+    constexpr unsigned lds = (unsigned)resident_lds(KIND, BF, CLS, NMT, R).bytes;
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     ResidentParams pc = p;

@@ -524,3 +524,34 @@ def test_tails_of_steps_with_two_tiles(pkg, H, J, V1, L, teams, durations, bf16,
     labels = np.concatenate(got["tokens"])
     assert not same or ((labels == same[0]).any() and not np.isin(labels, same[1:]).any())
     eng.close()
+
+
+# (bfloat16 mode: no layers of 640.  Its margin, 2e-2, is about twice what a step of bfloat16, 2^-8 of a value, makes of logits of up to 3
+# at a time; those of 332 reach 9 with these inputs, those of 640 reach 19.)
+EIGHT = [(64, 68, 60, 1, False, 32), (128, 128, 257, 2, True, 32), (316, 320, 529, 1, False, 8), (320, 316, 500, 1, True, 16),
+         (100, 128, 250, 2, False, 24), (324, 332, 1040, 2, False, 6), (324, 332, 1040, 2, True, 8), (640, 636, 1025, 1, False, 8)]
+
+
+@pytest.mark.parametrize("H,J,V1,L,bf16,teams", EIGHT)
+@pytest.mark.parametrize("extra", [{}, dict(durations=(0, 1, 3, 9)), dict(big_blanks=(2, 7))])
+@pytest.mark.parametrize("more", [0, 3])
+def test_eight_rows_a_team(pkg, H, J, V1, L, bf16, teams, extra, more):  # noqa: F811
+    """Lists of eight utterances and of a few more, which take over a row: stretches of labels on every frame (two-layer fp32 models: steps of one
+    tile), stretches with a label every few frames up to one more than a last row's step holds, utterances that end one after the
+    other, and (fp32) a large one, whose neighbours' operands are computed once more."""
+    w = model_inputs(H, J, V1, L, B=8 * teams + more, T=67, seed=H + more, F=(J + 15) // 16 * 16, **extra)
+    want = 60.0 * np.maximum(w.model.w_out[w.model.dims.blank].astype(np.float64), 0.0) - w.model.b_enc
+    blank = np.linalg.lstsq(w.model.w_enc.astype(np.float64), want, rcond=None)[0].astype(np.float32)
+    g = np.random.default_rng(w.B)
+    gap = np.array([1, 2, 4, 5, 6, 8, 31, 32])[g.integers(0, 8, (w.B, 67))].cumsum(1)
+    label = (gap[:, :, None] == np.arange(67)[None, None, :] + 1).any(1)
+    label[g.random(w.B) < 0.4, :25] = True
+    x = np.where(label[:, :, None], w.enc_out, blank[None, None]).astype(np.float32)
+    if not bf16:
+        x[3] *= np.float32(1e9)
+    length = np.sort(g.integers(1, 68, w.B))[::-1].astype(np.int32)
+    w = dataclasses.replace(w, enc_out=x, enc_len=length)
+    eng = pkg.Engine(w.model, w.B, w.T, flags=pkg.RNNT_FLAG_BF16_ARITHMETIC if bf16 else 0)
+    _, _, stats = check(pkg, w, w.variant, f"eight rows {H}/{J}/{V1}/{L} {extra} bf16={bf16} {more}", engine=eng, bf16=bf16, logp=not bf16)
+    assert stats["n_teams"] == teams and stats["lookahead"] == 4
+    eng.close()
