@@ -337,7 +337,7 @@ __device__ __forceinline__ float lane_sum(float v)
 }
 
 // Matrix instruction on a block of a wave's share of K: `w` and `z` from the registers of that block on, four
-// of either (32 k's), two for a half block.  A matrix instruction that adds to what one of the other kind right
+// of either (32 k's), two for a half block (bfloat16 mode).  A matrix instruction that adds to what one of the other kind right
 // before it leaves gives wrong sums (the compiler places no wait between them): where a sum takes both kinds, the
 // half block comes first and a wait after it, of 32 cycles or for a read of the sum (there; ordered: nothing moves
 // across), or it is two sums.
@@ -370,6 +370,13 @@ __device__ __forceinline__ auto weights_of(const RegW<N> &w, int t)
     if constexpr (KB < res_halves(CLS) / 2) return w.q[at / 4];
     else return at / 4 == N / 4 ? w.rest : (at % 4 ? w.q[at / 4].zw : w.q[at / 4].xy);
 }
+
+// fp32: both parts of the half block's weights, the high ones first, as the one instruction takes them that multiplies both: the
+// operand's sixteen k's twice.  (A half block's own instruction takes as long as a whole block's, one for each part, and waits between the
+// two kinds: 32 utterances 1185 us, 1169 with this, one layer 899 and 880, the small model 278 and 271, 128 utterances 3017 and 2997.  Logits are as
+// far from 64 bits, within 0.4 %.)
+template <int CLS, int T, int N>
+__device__ __forceinline__ r4f both_parts(const RegW<N> &w, int t) { return w.q[res_tile_at(false, CLS, T, res_halves(CLS) / 2, t, 0) / 4]; }
 
 __device__ __forceinline__ void ordered() { __builtin_amdgcn_sched_barrier(0); }
 
@@ -461,7 +468,7 @@ template <bool BF, int CLS, int R, int T, int ROW, class F = Nothing>
 __device__ __forceinline__ void stage(const RegW<res_tile_regs(BF, CLS, T)> &w, const Operand<BF, CLS, R> &x, float *sums, int wave, F behind = F())
 {
     constexpr int NH = res_halves(CLS), NF = NH / 2;
-    constexpr bool MIXED = NF > 0 && NH % 2 != 0, APART = MIXED && T < 4;
+    constexpr bool MIXED = BF && NF > 0 && NH % 2 != 0, APART = MIXED && T < 4;
     r4f sum[T], half[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) sum[t] = half[t] = (r4f){0.f, 0.f, 0.f, 0.f};
@@ -476,8 +483,7 @@ __device__ __forceinline__ void stage(const RegW<res_tile_regs(BF, CLS, T)> &w, 
     std::integral_constant<int, NF> last;
     std::integral_constant<int, 0> high;
     std::integral_constant<int, 1> low;
-    if constexpr (NH % 2 != 0) {
-        if constexpr (!BF) block(last, low);
+    if constexpr (BF && NH % 2 != 0) {
         block(last, high);
         if constexpr (MIXED && !APART) {
             ordered();
@@ -487,7 +493,14 @@ __device__ __forceinline__ void stage(const RegW<res_tile_regs(BF, CLS, T)> &w, 
             ordered();
         }
     }
-    if constexpr (!BF) static_for<0, NF>([&](auto kb_) { block(kb_, low); });
+    if constexpr (!BF) {
+        static_for<0, NF>([&](auto kb_) { block(kb_, low); });
+        if constexpr (NH % 2 != 0) {
+            const unsigned z[4] = {x.z[NF * 4], x.z[NF * 4 + 1], x.z[NF * 4], x.z[NF * 4 + 1]};
+#pragma unroll
+            for (int t = 0; t < T; ++t) sum[t] = tile_mfma<BF>(both_parts<CLS, T>(w, t), z, sum[t]);
+        }
+    }
     static_for<0, NF>([&](auto kb_) { block(kb_, high); });
     behind();
     const int lane = lane_id(), n = lane & 15;
@@ -1523,7 +1536,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                         constexpr bool FULL = i < NF;
                         std::integral_constant<int, i> block;
                         const unsigned *zh = z + parts_at(i), *zl = zh + (FULL ? 4 : 2);
-                        if constexpr (NH % 2 != 0 && NF > 0 && b == 1) {
+                        if constexpr (BF && NH % 2 != 0 && NF > 0 && b == 1) {
                             // the sums of the half block have to be there
 #pragma unroll
                             for (int c = 0; c < AT; ++c) there(big[c]);
@@ -1531,7 +1544,20 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                         }
                         ordered();
                         const int lane = lane_id(), m16 = lane & 15, g = lane >> 4;
-                        if constexpr (WHOLE) {
+                        constexpr bool BOTH = !BF && !WHOLE && !FULL;          // see both_parts
+                        const unsigned zhh[4] = {zh[0], zh[1], zh[0], zh[1]}, zll[4] = {zl[0], zl[1], zl[0], zl[1]}, zhl[4] = {zh[0], zh[1], zl[0], zl[1]};
+                        if constexpr (BOTH) {
+                            r4f w[AT];
+#pragma unroll
+                            for (int c = 0; c < AT; ++c) {
+                                if (c0 == 0) w[c] = both_parts<CLS, 2>(w_ou, c);
+                                else w[c] = *reinterpret_cast<const r4f *>(lds + lo.other + x.wave * (JREGS * 256) + res_tile_at(BF, CLS, 2, i, c, 0) / 4 * 1024 + lane * 16);
+                            }
+#pragma unroll
+                            for (int c = 0; c < AT; ++c) big[c] = tile_mfma<BF>(w[c], zll, big[c]);
+#pragma unroll
+                            for (int c = 0; c < AT; ++c) big[c] = tile_mfma<BF>(w[c], zhh, big[c]);
+                        } else if constexpr (WHOLE) {
 #pragma unroll
                             for (int c = 0; c < 2; ++c) {
                                 r4f w = w_ou.q[c];
@@ -1570,8 +1596,11 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                             tb = whole_mfma(*reinterpret_cast<const r4f *>(lds + lo.tail + (min(m16, NMT) * ROW + x.wave * 16 + g * 4) * 4), zh, tb);
                         } else if constexpr (TAIL && c0 == 0) {
                             const auto w = *reinterpret_cast<const std::conditional_t<FULL, r4f, r2f> *>(lds + lo.tail + (min(m16, BF ? NMT : 2 * NMT) * ROW + x.wave * (NH * 16) + i * 32 + g * (FULL ? 8 : 4)) * 2);
-                            if constexpr (!BF) tb = tile_mfma<BF>(w, zl, tb);
-                            tb = tile_mfma<BF>(w, zh, tb);
+                            if constexpr (BOTH) tb = tile_mfma<BF>((r4f){w.x, w.y, w.x, w.y}, zhl, tb);
+                            else {
+                                if constexpr (!BF) tb = tile_mfma<BF>(w, zl, tb);
+                                tb = tile_mfma<BF>(w, zh, tb);
+                            }
                         }
                         ordered();
                     });
