@@ -1055,6 +1055,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     auto stored = [&]() { return state + x.wave * 64 + lane_id(); };               // (fields 5 * 64 floats apart)
     constexpr int FIELD = 5 * 64;
     typedef RGates<R> Gates;
+    Gates first_sum{};
     constexpr int FIELDS = 2 + GL;
     float cs[NL], cc[NL];
     Gates ps[NL];
@@ -1248,6 +1249,16 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     constexpr int NS = 16 * NT;
     bool change = false;
     while (ok && any_active && !change) {
+        // a stage's sum for the lane, as it is to be used
+        auto sum_of = [&](const float *sums, const float *scales) {
+            const int lane = lane_id();
+            Gates v = stage_sum<R>(sums, x.wave, lane);
+            if constexpr (!BF) {
+#pragma unroll
+                for (int e = 0; e < GL; ++e) v.g[e] *= scales[(x.wave * 4 + (lane >> 4)) * 4 + (lane & (LR - 1)) * GL + e];
+            }
+            return v;
+        };
         const unsigned jn = ++n_joint;
         // A wave's part of the operand, an eighth of K of a tile's samples
         constexpr int PIECES = BF ? NB : NH;
@@ -1297,16 +1308,6 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             // rows that emitted take their candidate state, fresh rows start from zero (kResident2: the second
             // layer's while the first one's vector is on its way; kResident2Pair: not before its own cell, the helpers
             // have till then)
-            // a stage's sum for the lane, as it is to be used
-            auto sum_of = [&](const float *sums, const float *scales) {
-                const int lane = lane_id();
-                Gates v = stage_sum<R>(sums, x.wave, lane);
-                if constexpr (!BF) {
-#pragma unroll
-                    for (int e = 0; e < GL; ++e) v.g[e] *= scales[(x.wave * 4 + (lane >> 4)) * 4 + (lane & (LR - 1)) * GL + e];
-                }
-                return v;
-            };
             auto commit = [&](int l) {
                 // (Zero for waves without cells, but from a variable: with a constant the compiler waits for the row of T0, and with it
                 // for everything, between the loads of two frames: bfloat16 mode 1035 instead of 962 us for 32 utterances.)
@@ -1317,7 +1318,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     if constexpr (PAIR) pc.g[e] = (pc.g[e] + __uint_as_float(pre[l][1][e])) + (__uint_as_float(pre[l][2][e]) + __uint_as_float(pre[l][3][e]));
                 }
                 if constexpr (!PAIR)
-                    if (has_cells) pc = sum_of(l == NL - 1 ? sums_top : sums_rec0, rc.sh[l]);
+                    if (has_cells) pc = NL == 1 ? first_sum : sum_of(l == 0 ? sums_rec0 : sums_top, rc.sh[l]);
                 const bool take = lane_const & kTake, fresh_row = lane_const & kFresh;       // (bits: as a chain of comparisons it became branches)
                 cs[l] = take ? cc[l] : cs[l]; cs[l] = fresh_row ? 0.f : cs[l];
 #pragma unroll
@@ -1753,6 +1754,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             }
         }
         RES_MARK(12);
+        // One layer: what the next prediction step's cells add to the row of T0, while the keys travel (one layer of 640, 32 utterances 870 us and 854
+        // with it, 8 571 and 559, the small model 271 and 266.  Two layers in bfloat16 have no register for it; through LDS: no gain.)
+        if constexpr (NL == 1)
+            if (need_pred && has_cells) first_sum = sum_of(sums_top, rc.sh[0]);
         // ---- argmax over the team: TS / 2 adjacent lanes per sample, two candidates per lane --------
         {
             const int tid = (x.wave * 64 + lane_id()), lane = tid & 63;
