@@ -151,7 +151,9 @@ inline int in_launch_order(hipStream_t stream, F enqueue)
     if (dev >= kDevices || capture != hipStreamCaptureStatusNone) return enqueue(false);
     LaunchOrder &d = launch_order(dev);
     std::lock_guard<std::mutex> lock(d.m);
-    if (!d.last && !ok(hipEventCreateWithFlags(&d.last, hipEventDisableTiming), "hipEventCreate")) return rc;
+    // (The event only keeps kernels of this device apart, which fence for themselves: without its own fence for the host and other devices a
+    // call of one utterance takes 1.7 us less, the smallest model's 67.2 us and 65.6.)
+    if (!d.last && !ok(hipEventCreateWithFlags(&d.last, hipEventDisableTiming | hipEventDisableSystemFence), "hipEventCreate")) return rc;
     if (d.used && !ok(hipStreamWaitEvent(stream, d.last, 0), "hipStreamWaitEvent")) return rc;
     const int done = enqueue(true);
     // (also after a failed launch: kernels of the call may be under way)
