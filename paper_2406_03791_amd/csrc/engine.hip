@@ -586,11 +586,12 @@ int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
     const ResidentPlan &pl = e->res;
     const bool bf = pl.bf != 0;
     if (pl.solo) {
-        const size_t groups = (size_t)solo_parts(solo_tiles(e->NOUT)) * 256;
+        const int VT = e->multi_blank ? e->NOUT : d.V1;
+        const size_t groups = (size_t)solo_parts(e->NOUT, VT) * 256;
         HIP_TRY(e->res_w.alloc(groups * sizeof(float4) + sizeof(unsigned)));
         unsigned *check = reinterpret_cast<unsigned *>(e->res_w.as<float4>() + groups), found = 0;
         HIP_TRY(hipMemset(check, 0, sizeof found));
-        HIP_TRY(pack_solo(d.w_hh[0], d.w_pred, d.w_out, d.H, d.J, e->NOUT, e->res_w.as<float4>(), check, nullptr));
+        HIP_TRY(pack_solo(d.w_hh[0], d.w_pred, d.w_out, d.H, d.J, e->NOUT, VT, e->res_w.as<float4>(), check, nullptr));
         HIP_TRY(hipMemcpy(&found, check, sizeof found, hipMemcpyDeviceToHost));
         if (found) { e->res.kind = kResidentNone; return RNNT_OK; }       // (as below)
         HIP_TRY(e->res_stats.alloc((size_t)pl.n_teams * kStatStride * sizeof(long long)));

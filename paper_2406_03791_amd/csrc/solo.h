@@ -15,10 +15,14 @@ inline bool solo_holds(int H, int J, int L, int NOUT, bool bf)
 {
     return !bf && L == 1 && H <= kSoloWidth && J <= kSoloWidth && NOUT <= kSoloOutputs;
 }
-RNNT_HD constexpr int solo_tiles(int NOUT) { return NOUT <= 32 ? 2 : 4; }        // of 16 outputs
+// A single token behind the tiles of 16 that the others fill (sixteen or 32 labels and a blank, no durations) is not worth a tile of
+// its own: its products are four multiply-adds a lane beside the matrix instructions (17 outputs, a call of 20 frames and 45 steps:
+// 64.1 us with two tiles, 60.7 with one and the output behind it).
+RNNT_HD constexpr bool solo_last(int NOUT, int VT) { return VT == NOUT && (NOUT == 17 || NOUT == 33); }
+RNNT_HD constexpr int solo_tiles(int NOUT, int VT) { return solo_last(NOUT, VT) ? NOUT / 16 : NOUT <= 32 ? 2 : 4; }        // of 16 outputs
 // Weights as the threads take them, four values each, [part][thread of 256]: sixteen parts of the recurrent
-// matrix, four of the projection, a tile of outputs each.
-RNNT_HD constexpr int solo_parts(int tiles) { return 16 + 4 + tiles; }
+// matrix, four of the projection, a tile of outputs each, and the output behind the tiles.
+RNNT_HD constexpr int solo_parts(int NOUT, int VT) { return 16 + 4 + solo_tiles(NOUT, VT) + (solo_last(NOUT, VT) ? 1 : 0); }
 
 struct SoloParams {
     int H, J, V1, VT, D, blank, NOUT, tdt;
@@ -35,8 +39,8 @@ struct SoloParams {
     int n_records;
 };
 
-// w: solo_parts(solo_tiles(NOUT)) * 256 groups of four; *check, zero before: raised if a weight is not finite
-hipError_t pack_solo(const float *w_hh, const float *w_pred, const float *w_out, int H, int J, int NOUT, float4 *w, unsigned *check, hipStream_t stream);
+// VT: token outputs, as in calls.  w: solo_parts(NOUT, VT) * 256 groups of four; *check, zero before: raised if a weight is not finite
+hipError_t pack_solo(const float *w_hh, const float *w_pred, const float *w_out, int H, int J, int NOUT, int VT, float4 *w, unsigned *check, hipStream_t stream);
 hipError_t launch_solo(const SoloParams &p, bool plain, hipStream_t stream);
 
 }  // namespace rnnt

@@ -3,15 +3,16 @@
 // One work-group per utterance, and nothing goes from one work-group to another.  Spread over the eight work-groups of a
 // team of the resident kernel, as every model of one layer was, a model of 64 units and 17 outputs spent its steps on hand-overs:
 // three of 0.4 to 0.5 us and the latency around them, 3.5 us a step; here vectors go through LDS, and a step takes
-// 1.3 us (a call of one utterance of 20 frames 157 and 64 us, and as long for 256 of them).  Emitted logits are 2.1e-8 from 64 bits, rms,
+// 1.07 us (a call of one utterance of 20 frames 157 and 60 us, and 69 for 128 of them).  Emitted logits are 2.1e-8 from 64 bits, rms,
 // as they were.
 //
 // Bound by latency: a chain of cell, projection, joint, sums over the waves and argmax, with three barriers.  What can be off the chain
 // is: waves 0 .. 3 run projection, joint and argmax, waves 4 .. 7 (which share their SIMDs) hold the recurrent matrix, compute
 // W_hh h for the next label beside that and then have the cells' pre-activations in their registers.  The loop control is
 // uniform: every wave takes the same decisions from the same sixteen results.  (Projection behind a barrier of its own, outputs
-// written by a wave that has cells, and one instance for all models: 1.6 us a step.)  A quarter of a step is the chain of
-// 16x16x4 matrix instructions, the rest LDS latency (eight times 100 cycles and more), barriers and two gate functions.
+// written by a wave that has cells, and one instance for all models: 1.6 us a step.)  A tile's four matrix
+// instructions and the reads of their sums are 0.075 us of a step, the rest is LDS latency (six times 100 cycles and more), barriers
+// and two gate functions.
 // All products are fp32 instructions: plain multiply-adds for one vector, 16x16x4 matrix instructions for the sixteen
 // frames of a joint step, K in quarters over the waves.
 #include <type_traits>
@@ -26,7 +27,7 @@ namespace {
 typedef float s4f __attribute__((ext_vector_type(4)));
 
 // The value at place `e` of group `i`, or 0
-__device__ __forceinline__ float solo_weight(const float *w_hh, const float *w_pred, const float *w_out, int H, int J, int NOUT, int i, int e)
+__device__ __forceinline__ float solo_weight(const float *w_hh, const float *w_pred, const float *w_out, int H, int J, int NOUT, int tiles, int i, int e)
 {
     const int part = i >> 8, t = i & 255;
     if (part < 16) {              // gate t % 4 of unit t / 4
@@ -37,12 +38,12 @@ __device__ __forceinline__ float solo_weight(const float *w_hh, const float *w_p
         const int j = t >> 2, k = (t & 3) * 16 + (part - 16) * 4 + e;
         return j < J && k < H ? w_pred[(long long)j * H + k] : 0.f;
     }
-    const int o = (part - 20) * 16 + (t & 15), k = (t >> 6) * 16 + (t >> 4 & 3) * 4 + e;
+    const int o = (part - 20) * 16 + (part - 20 < tiles ? t & 15 : 0), k = (t >> 6) * 16 + (t >> 4 & 3) * 4 + e;
     return o < NOUT && k < J ? w_out[(long long)o * J + k] : 0.f;
 }
 
 __global__ void __launch_bounds__(256) pack_solo_kernel(const float *__restrict__ w_hh, const float *__restrict__ w_pred, const float *__restrict__ w_out, int H, int J, int NOUT,
-                                                        int n, float4 *__restrict__ w, unsigned *check)
+                                                        int tiles, int n, float4 *__restrict__ w, unsigned *check)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
@@ -50,7 +51,7 @@ __global__ void __launch_bounds__(256) pack_solo_kernel(const float *__restrict_
     bool finite = true;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        v[e] = solo_weight(w_hh, w_pred, w_out, H, J, NOUT, i, e);
+        v[e] = solo_weight(w_hh, w_pred, w_out, H, J, NOUT, tiles, i, e);
         finite = finite && fabsf(v[e]) < INFINITY;
     }
     w[i] = make_float4(v[0], v[1], v[2], v[3]);
@@ -77,26 +78,51 @@ __device__ __forceinline__ float sum16(float v)
     return v + solo_dpp<0x140>(v);
 }
 
-// LDS, in floats: a ring of 2 * kSoloChunk frames, T0, the waves' partial sums [wave][frame][outputs], h, q, and the
+// acc[i / 4][i % 4] += w[i / 4][i % 4] * (x of lane FIRST + i of the sixteen), i = 0 .. 7: broadcast and multiply-add in one
+// instruction, which the compiler does not make of the two
+template <int FIRST>
+__device__ __forceinline__ void fma_row8(const s4f *w, float x, s4f *acc)
+{
+    float a[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a[i] = acc[i / 4][i % 4];
+#define FMA_ROW(i, wi, lane) "v_fmac_f32_dpp %" #i ", %16, %" #wi " row_newbcast:" #lane " row_mask:0xf bank_mask:0xf\n\t"
+#define FMA_ROWS(l0, l1, l2, l3, l4, l5, l6, l7)                                                                                    \
+    asm("s_nop 1\n\t" FMA_ROW(0, 8, l0) FMA_ROW(1, 9, l1) FMA_ROW(2, 10, l2) FMA_ROW(3, 11, l3)                                     \
+        FMA_ROW(4, 12, l4) FMA_ROW(5, 13, l5) FMA_ROW(6, 14, l6) FMA_ROW(7, 15, l7)                                                \
+        : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3]), "+&v"(a[4]), "+&v"(a[5]), "+&v"(a[6]), "+&v"(a[7])                           \
+        : "v"(w[0][0]), "v"(w[0][1]), "v"(w[0][2]), "v"(w[0][3]), "v"(w[1][0]), "v"(w[1][1]), "v"(w[1][2]), "v"(w[1][3]), "v"(x))
+    static_assert(FIRST == 0 || FIRST == 8, "half of sixteen lanes");
+    if constexpr (FIRST == 0) FMA_ROWS(0, 1, 2, 3, 4, 5, 6, 7);
+    else FMA_ROWS(8, 9, 10, 11, 12, 13, 14, 15);
+#undef FMA_ROWS
+#undef FMA_ROW
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i / 4][i % 4] = a[i];
+}
+
+// LDS, in floats: a ring of 2 * kSoloChunk frames, T0, the waves' partial sums [wave][frame][outputs], those of an output beyond the
+// tiles [frame][wave][lane / 16] (rows of 20: sixteen frames' rows in banks of their own), h, and the
 // results of the frames (label, duration, logit, log-probability), and the table of durations
-struct SoloLds { int frames, t0, part, h, q, res, dur, total; };
+constexpr int kSoloLastRow = 20;
+struct SoloLds { int frames, t0, part, last, h, res, dur, total; };
 RNNT_HD constexpr SoloLds solo_lds(int V1, int tiles)
 {
     SoloLds l{};
     l.frames = 0;
     l.t0 = 2 * kSoloChunk * kSoloWidth;
     l.part = l.t0 + V1 * 4 * kSoloWidth;
-    l.h = l.part + 4 * kSoloFrames * (tiles * 16 + 4);
-    l.q = l.h + kSoloWidth;
-    l.res = l.q + kSoloWidth;
+    l.last = l.part + 4 * kSoloFrames * (tiles * 16 + 4);
+    l.h = l.last + kSoloFrames * kSoloLastRow;
+    l.res = l.h + kSoloWidth;
     l.dur = l.res + 4 * kSoloFrames;
     l.total = l.dur + kMaxDur;
     return l;
 }
 static_assert(solo_lds(kSoloOutputs, 4).total * 4 <= 160 * 1024, "the largest model fits the LDS");
 
-// WALK: TDT and multi-blank models, where not every blank moves on by one frame
-template <int TILES, bool WALK>
+// TILES: of 16 outputs; LAST: and one more behind them; WALK: TDT and multi-blank models, where not every blank moves on by one frame
+template <int TILES, bool LAST, bool WALK>
 __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
 {
     extern __shared__ __align__(16) float lds[];
@@ -104,6 +130,7 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
     const SoloLds lo = solo_lds(p.V1, TILES);
     const int tid = threadIdx.x, lane = tid & 63, t256 = tid & 255, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool chain = wave < 4;
+    if (chain) __builtin_amdgcn_s_setprio(2);        // (0.4 to 0.9 % of a call: the SIMD's other wave is ready early enough)
     if (blockIdx.x == 0) {
         if (tid == 0) p.stats[kStatDecodeStart] = wall_clock64();
         for (int i = gridDim.x + tid; i < p.n_records; i += kSoloThreads)
@@ -114,7 +141,7 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         w[i] = (s4f){0.f, 0.f, 0.f, 0.f};
-        if (!chain || i < 4 + TILES) w[i] = reinterpret_cast<const s4f *>(p.w)[(chain ? 16 + i : i) * 256 + t256];
+        if (!chain || i < 4 + TILES + LAST) w[i] = reinterpret_cast<const s4f *>(p.w)[(chain ? 16 + i : i) * 256 + t256];
         asm volatile("" : "+v"(w[i]));
     }
     for (int i = tid; i < 2 * kSoloChunk * W; i += kSoloThreads) lds[lo.frames + i] = 0.f;       // (beyond the joint width it stays so)
@@ -122,12 +149,14 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
         const int v = i / (4 * W), at = i - v * (4 * W);
         lds[lo.t0 + i] = at < p.H * 4 ? p.T0[(long long)v * p.H * 4 + at] : 0.f;
     }
-    if (tid < W) lds[lo.h + tid] = lds[lo.q + tid] = 0.f;
+    if (tid < W) lds[lo.h + tid] = 0.f;
     const float b_pred = (t256 >> 2) < p.J ? p.b_pred[t256 >> 2] : 0.f;
     float b_out[TILES];
 #pragma unroll
     for (int c = 0; c < TILES; ++c) b_out[c] = (tid & 15) * TILES + c < p.NOUT ? p.b_out[(tid & 15) * TILES + c] : 0.f;
-    float *part = lds + lo.part, *hv = lds + lo.h, *qv = lds + lo.q;
+    const float b_last = LAST ? p.b_out[TILES * 16] : 0.f;
+    float *part = lds + lo.part, *hv = lds + lo.h;
+    s4f q = {0.f, 0.f, 0.f, 0.f};                // of the lane's k's of a joint step
     int *res = reinterpret_cast<int *>(lds + lo.res), *res_d = res + 2 * NF;        // label and logit, duration
     float *res_lp = lds + lo.res + 3 * NF;
     int *durations = reinterpret_cast<int *>(lds + lo.dur);
@@ -158,18 +187,24 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
         auto frames_there = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
         int t = 0, n = 0, cnt = 0, last = p.blank, have = 1;
         bool need = true, pending = false;
-        float c = 0.f, pre = 0.f;
+        float c = 0.f, pre = 0.f, t0 = lds[lo.t0 + last * (4 * W) + t256];
         __syncthreads();              // (nobody reads the last utterance's frames any more)
         load_chunk(0);
         load_chunk(1);
         frames_there();
         __syncthreads();
         while (t < len) {
+            // the lane's part of frame t + lane % 16
+            auto frame_values = [&]() {
+                const int f = (t + (lane & 15)) & (2 * kSoloChunk - 1), k4 = wave * 4 + (lane >> 4);
+                return *reinterpret_cast<const s4f *>(lds + lo.frames + f * W + ((k4 ^ f) & 15) * 4);
+            };
+            s4f pv = {0.f, 0.f, 0.f, 0.f};
             if (need) {
                 ++n_pred;
                 if (!chain) {
                     // the cell: lanes of a unit hold the gates i, f, g, o
-                    const float act = gate_act(pre + lds[lo.t0 + last * (4 * W) + t256], (lane & 3) == 2);
+                    const float act = gate_act(pre + t0, (lane & 3) == 2);
                     const float i_ = solo_dpp<0x00>(act), f_ = solo_dpp<0x55>(act), g_ = solo_dpp<0xAA>(act), o_ = solo_dpp<0xFF>(act);
                     c = fmaf(f_, c, i_ * g_);
                     const float h = o_ * gate_act(c, true);
@@ -178,6 +213,7 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
                 if (pending) { frames_there(); pending = false; }
                 __syncthreads();
                 if (chain) {
+                    pv = frame_values();
                     // projection: four lanes per output, a quarter of K each
                     s4f acc;
 #pragma unroll
@@ -189,23 +225,29 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
                     }
                     float o = (acc[0] + acc[1]) + (acc[2] + acc[3]);
                     o += solo_dpp<0xB1>(o); o += solo_dpp<0x4E>(o);
-                    // (the sixteen values that this wave's part of the joint step needs: no barrier)
-                    if ((lane & 3) == 0) qv[t256 >> 2] = o + b_pred;
+                    // The sixteen values are those that this wave's part of the joint step needs, four of them in every sixteen lanes that
+                    // need those: broadcasts inside the sixteen (through LDS, and with T0's value read where the cell needs it, 0.03 us a step
+                    // more).
+                    o += b_pred;
+                    q = (s4f){solo_dpp<0x150>(o), solo_dpp<0x154>(o), solo_dpp<0x158>(o), solo_dpp<0x15c>(o)};
+                    asm volatile("" : "+v"(pv));
                 }
-            } else if (pending) {
-                frames_there();
-                pending = false;
-                __syncthreads();
+            } else {
+                if (pending) {
+                    frames_there();
+                    pending = false;
+                    __syncthreads();
+                }
+                if (chain) pv = frame_values();
             }
             // joint step: frames t .. t + 15, a quarter of K per wave
             ++n_joint;
             const int left = len - t;
             n_samples += min(left, NF);
             if (chain) {
-                const int m16 = lane & 15, g = lane >> 4, f = (t + m16) & (2 * kSoloChunk - 1), k4 = wave * 4 + g;
-                const s4f pv = *reinterpret_cast<const s4f *>(lds + lo.frames + f * W + ((k4 ^ f) & 15) * 4);
-                const s4f q = *reinterpret_cast<const s4f *>(qv + k4 * 4);
+                const int m16 = lane & 15, g = lane >> 4;
                 s4f sum[TILES];
+                float last_sum = 0.f;
 #pragma unroll
                 for (int o = 0; o < TILES; ++o) sum[o] = (s4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -213,19 +255,23 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
                     const float z = fmaxf(pv[e] + q[e], 0.f);
 #pragma unroll
                     for (int o = 0; o < TILES; ++o) sum[o] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[4 + o][e], z, sum[o], 0, 0, 0);
+                    if (LAST) last_sum = fmaf(w[4 + TILES][e], z, last_sum);
                 }
+                if (LAST) lds[lo.last + m16 * kSoloLastRow + wave * 4 + g] = last_sum;
 #pragma unroll
                 for (int o = 0; o < TILES; ++o) *reinterpret_cast<s4f *>(part + (wave * NF + m16) * PS + o * 16 + g * 4) = sum[o];
             } else if (need) {
-                // W_hh h, in eight sums
-                const s4f *h4 = reinterpret_cast<const s4f *>(hv);
+                // W_hh h, in eight sums: a lane reads four of h's values and has the others from its fifteen neighbours (all 64 values read
+                // by every lane keep the LDS from the projection's reads: 0.5 to 0.8 % of a call, with the frames' read moved up)
+                float x[4];
                 s4f acc[2];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[i] = hv[i * 16 + (lane & 15)];
                 acc[0] = acc[1] = (s4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const s4f x = h4[i];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[i & 1][e] = fmaf(w[i][e], x[e], acc[i & 1][e]);
+                for (int i = 0; i < 4; ++i) {
+                    fma_row8<0>(w + i * 4, x[i], acc);
+                    fma_row8<8>(w + i * 4 + 2, x[i], acc);
                 }
                 const s4f a = acc[0] + acc[1];
                 pre = (a[0] + a[1]) + (a[2] + a[3]);
@@ -244,14 +290,21 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
                     v[i] = ((o[0][i] + o[1][i]) + (o[2][i] + o[3][i])) + b_out[i];
                     mine = fmaxf(mine, first + i < p.VT ? v[i] : -INFINITY);
                 }
+                const float last_v = LAST ? sum16(lds[lo.last + s * kSoloLastRow + l]) + b_last : -INFINITY;
                 // the lowest of equal outputs (none: they are all NaN, and a frame with nothing else is a blank)
                 int k = -1;
 #pragma unroll
                 for (int i = TILES - 1; i >= 0; --i) k = first + i < p.VT && v[i] == mine ? first + i : k;
-                const float m = max16(mine);
+                float m = max16(mine);
                 const unsigned hit = (unsigned)(__ballot(mine == m && k >= 0) >> (lane & 48)) & 0xffffu;
                 const int lead = hit ? __builtin_ctz(hit) : 0;
-                if (l == lead) *reinterpret_cast<int2 *>(res + s * 2) = make_int2(hit ? k : p.blank, __float_as_int(m + 0.0f));
+                int best = hit ? k : p.blank;
+                if (LAST) {
+                    const bool above = last_v > m || (hit == 0u && last_v == m);
+                    best = above ? TILES * 16 : best;
+                    m = above ? last_v : m;
+                }
+                if (l == lead) *reinterpret_cast<int2 *>(res + s * 2) = make_int2(best, __float_as_int(m + 0.0f));
                 if (tdt) {
                     float dm = -INFINITY;
 #pragma unroll
@@ -270,6 +323,7 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
 #pragma unroll
                     for (int i = 0; i < TILES; ++i) e += first + i < p.VT && v[i] > -INFINITY ? expf(v[i] - m) : 0.f;
                     e = sum16(e);
+                    if (LAST) e += last_v > -INFINITY ? expf(last_v - m) : 0.f;
                     if (l == 0) res_lp[s] = -logf(e);
                 }
             }
@@ -296,6 +350,8 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
             if (found) {
                 const int k = __builtin_amdgcn_readlane(mine, pos), d = tdt ? __builtin_amdgcn_readlane(dur, pos) : 0;
                 last = k;
+                // (asked for here, it is there when the rest of the loop control is done)
+                t0 = lds[lo.t0 + last * (4 * W) + t256];
                 if (writer) {
                     if (cnt < p.cap) {
                         const long long o = (long long)b * p.cap + cnt;
@@ -333,10 +389,10 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
     }
 }
 
-template <int TILES, bool WALK>
+template <int TILES, bool LAST, bool WALK>
 hipError_t launch_tiles(const SoloParams &p, bool plain, hipStream_t stream)
 {
-    const void *fn = reinterpret_cast<const void *>(&solo_kernel<TILES, WALK>);
+    const void *fn = reinterpret_cast<const void *>(&solo_kernel<TILES, LAST, WALK>);
     const unsigned lds = (unsigned)solo_lds(p.V1, TILES).total * 4u;
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(solo_lds(kSoloOutputs, TILES).total * 4));
     if (e != hipSuccess) return e;
@@ -349,10 +405,10 @@ hipError_t launch_tiles(const SoloParams &p, bool plain, hipStream_t stream)
 
 }  // namespace
 
-hipError_t pack_solo(const float *w_hh, const float *w_pred, const float *w_out, int H, int J, int NOUT, float4 *w, unsigned *check, hipStream_t stream)
+hipError_t pack_solo(const float *w_hh, const float *w_pred, const float *w_out, int H, int J, int NOUT, int VT, float4 *w, unsigned *check, hipStream_t stream)
 {
-    const int n = solo_parts(solo_tiles(NOUT)) * 256;
-    hipLaunchKernelGGL(pack_solo_kernel, dim3((unsigned)(n / 256)), dim3(256), 0, stream, w_hh, w_pred, w_out, H, J, NOUT, n, w, check);
+    const int n = solo_parts(NOUT, VT) * 256;
+    hipLaunchKernelGGL(pack_solo_kernel, dim3((unsigned)(n / 256)), dim3(256), 0, stream, w_hh, w_pred, w_out, H, J, NOUT, solo_tiles(NOUT, VT), n, w, check);
     return hipGetLastError();
 }
 
@@ -362,8 +418,16 @@ hipError_t launch_solo(const SoloParams &p, bool plain, hipStream_t stream)
     if (p.H < 1 || p.H > kSoloWidth || p.J < 1 || p.J > kSoloWidth || p.J % 4 != 0 || p.NOUT > kSoloOutputs || p.V1 > p.NOUT || p.B < 1 || p.n_records < 1)
         return hipErrorInvalidValue;
     const bool walk = p.tdt || p.VT != p.V1;
-    if (solo_tiles(p.NOUT) == 2) return walk ? launch_tiles<2, true>(p, plain, stream) : launch_tiles<2, false>(p, plain, stream);
-    return walk ? launch_tiles<4, true>(p, plain, stream) : launch_tiles<4, false>(p, plain, stream);
+    auto launch = [&](auto tiles, auto last) {
+        return walk ? launch_tiles<decltype(tiles)::value, decltype(last)::value, true>(p, plain, stream)
+                    : launch_tiles<decltype(tiles)::value, decltype(last)::value, false>(p, plain, stream);
+    };
+    typedef std::integral_constant<int, 1> One;
+    typedef std::integral_constant<int, 2> Two;
+    typedef std::integral_constant<int, 4> Four;
+    const int tiles = solo_tiles(p.NOUT, p.VT);
+    if (solo_last(p.NOUT, p.VT)) return tiles == 1 ? launch(One(), std::true_type()) : launch(Two(), std::true_type());
+    return tiles == 2 ? launch(Two(), std::false_type()) : launch(Four(), std::false_type());
 }
 
 }  // namespace rnnt

@@ -34,6 +34,29 @@ def test_shapes_and_decoders(pkg, H, J, V1, extra):  # noqa: F811
         eng.close()
 
 
+@pytest.mark.parametrize("V1,extra", [(17, {}), (33, {}), (13, dict(big_blanks=(2, 70, 300, 5))), (29, dict(big_blanks=(2, 70, 300, 5)))])
+def test_an_output_behind_the_tiles(pkg, V1, extra):  # noqa: F811
+    """The 17th or 33rd output, a blank, beside outputs of the tiles: as large as one of them it loses, as the higher number; one bit
+    above it wins.  (Rows of zeros: these outputs are their biases, exactly.)"""
+    w = model_inputs(64, 64, V1, 1, B=5, T=40, seed=V1, **extra)
+    check(pkg, w, w.variant, f"behind the tiles {V1} {extra}", logp=True)
+    last = w.model.w_out.shape[0] - 1
+    assert last in (16, 32)
+    for row in (0, 7, last - 5):
+        w.model.w_out[[row, last]] = 0.0
+        w.model.b_out[[row, last]] = np.float32(500.0)
+        for above in (False, True):
+            w.model.b_out[last] = np.nextafter(np.float32(500.0), np.float32(np.inf)) if above else np.float32(500.0)
+            eng = pkg.Engine(w.model, w.B, w.T)
+            out = eng.decode(w.variant, torch.from_numpy(w.enc_out).cuda(), torch.from_numpy(w.enc_len.astype(np.int32)).cuda(), 2)
+            assert eng.stats()["team_size"] == 1
+            n = out["tok_len"].cpu().numpy()
+            assert np.array_equal(n, 0 * w.enc_len if above else 2 * w.enc_len)
+            assert all((out["tokens"][b, :k] == row).all() for b, k in enumerate(n))
+            eng.close()
+        w.model.b_out[row] = -500.0
+
+
 @pytest.mark.parametrize("T", [63, 64, 65, 127, 128, 129, 400])
 @pytest.mark.parametrize("extra", [{}, dict(durations=(0, 1, 49, 64, 128)), dict(big_blanks=(15, 16, 17, 65))])
 def test_frames_in_the_ring(pkg, T, extra):  # noqa: F811
