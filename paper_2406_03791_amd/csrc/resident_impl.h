@@ -1526,8 +1526,23 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 constexpr bool TAIL = decltype(tail_)::value;
                 const r4f zero = {0.f, 0.f, 0.f, 0.f};
                 // fp32: the work-group's own columns and the tail, then its partner's (registers)
-                constexpr int AT = BF ? CT : 2;
-                static_for<0, CT / AT>([&](auto own_) {
+                constexpr int AT = BF ? CT : 2, AHEAD = 2, BEYOND = 2;
+                constexpr bool APART = NT == 2 && !BF && !WHOLE;
+                // The partner's weights, sixteen bytes a lane, in the order of their use: the half block's of both column tiles, then high and low
+                // part of a block's first tile, of its second.  Two reads, then four, are on their way while what is there is used (all of a block
+                // asked for when it was its turn, every block waited for the LDS: 32 utterances 1173 us and 1163 now, TDT 829 and 819, one layer 871 and
+                // 852, 128 utterances 2996 and 2985; three throughout 1168, 822, 855, 2966; three and five: registers spilled).
+                constexpr int HALF = NH % 2 * 2, GROUPS = APART ? HALF + NF * 4 : 0;
+                r4f pw[GROUPS + 1];
+                unsigned from = 0;
+                auto ask_weights = [&](auto lo_, auto hi_) {
+                    static_for<decltype(lo_)::value, decltype(hi_)::value>([&](auto q_) {
+                        constexpr int q = decltype(q_)::value, f = q - HALF;
+                        constexpr int reg = f < 0 ? res_tile_at(BF, CLS, 2, NF, q, 0) : res_tile_at(BF, CLS, 2, f / 4, f / 2 % 2, f % 2);
+                        pw[q] = *reinterpret_cast<const r4f *>(lds + from + (unsigned)(reg / 4 * 1024));
+                    });
+                };
+                static_for<0, APART ? 1 : CT / AT>([&](auto own_) {
                     constexpr int c0 = decltype(own_)::value * 2;
                     r4f big[AT], tb = zero;
 #pragma unroll
@@ -1550,10 +1565,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                         if constexpr (BOTH) {
                             r4f w[AT];
 #pragma unroll
-                            for (int c = 0; c < AT; ++c) {
-                                if (c0 == 0) w[c] = both_parts<CLS, 2>(w_ou, c);
-                                else w[c] = *reinterpret_cast<const r4f *>(lds + lo.other + x.wave * (JREGS * 256) + res_tile_at(BF, CLS, 2, i, c, 0) / 4 * 1024 + lane * 16);
-                            }
+                            for (int c = 0; c < AT; ++c) w[c] = both_parts<CLS, 2>(w_ou, c);
 #pragma unroll
                             for (int c = 0; c < AT; ++c) big[c] = tile_mfma<BF>(w[c], zll, big[c]);
 #pragma unroll
@@ -1614,6 +1626,39 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
 #pragma unroll
                     for (int c = 0; c < AT; ++c) *sums_at(c0 + c, lane) = big[c];
                 });
+                if constexpr (APART) {
+                    // groups asked for when `n` have been used
+                    constexpr auto asked = [](int n) { return n + AHEAD + (n >= HALF ? BEYOND : 0) < GROUPS ? n + AHEAD + (n >= HALF ? BEYOND : 0) : GROUPS; };
+                    from = (unsigned)(lo.other + x.wave * (JREGS * 256) + lane_id() * 16);
+                    ordered();
+                    ask_weights(std::integral_constant<int, 0>(), std::integral_constant<int, asked(0)>());
+                    ordered();
+                    r4f big[2] = {zero, zero};
+                    static_for<0, HALF>([&](auto c_) {
+                        constexpr int c = decltype(c_)::value;
+                        const unsigned *zh = z + parts_at(NF), *zl = zh + 2;
+                        const unsigned zhh[4] = {zh[0], zh[1], zh[0], zh[1]}, zll[4] = {zl[0], zl[1], zl[0], zl[1]};
+                        big[c] = tile_mfma<BF>(pw[c], zll, big[c]);
+                        big[c] = tile_mfma<BF>(pw[c], zhh, big[c]);
+                        ordered();
+                        ask_weights(std::integral_constant<int, asked(c)>(), std::integral_constant<int, asked(c + 1)>());
+                        ordered();
+                    });
+                    static_for<0, NF * 2>([&](auto u_) {
+                        constexpr int u = decltype(u_)::value, c = u % 2, q = HALF + u * 2;
+                        const unsigned *zh = z + parts_at(u / 2), *zl = zh + 4;
+                        if constexpr (NF < 2) big[c] = tile_mfma<BF>(pw[q + 1], zl, big[c]);
+                        big[c] = tile_mfma<BF>(pw[q], zl, big[c]);
+                        big[c] = tile_mfma<BF>(pw[q + 1], zh, big[c]);
+                        big[c] = tile_mfma<BF>(pw[q], zh, big[c]);
+                        ordered();
+                        ask_weights(std::integral_constant<int, asked(q)>(), std::integral_constant<int, asked(q + 2)>());
+                        ordered();
+                    });
+                    const int lane = lane_id();
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) *sums_at(2 + c, lane) = big[c];
+                }
             };
             const bool with_tail = NT == NMT ? n_tails > 0 : half < n_tails;
             if (with_tail) output(std::true_type());
