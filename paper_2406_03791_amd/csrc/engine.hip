@@ -178,7 +178,7 @@ struct rnnt_engine {
     std::vector<Used> last_used;
     bool last_resident = false;     // the last call ran in the resident kernel
     Workspace last_ws;      // where the last call kept its status word
-    int last_B = 0;
+    int last_B = 0, last_T = 0;
     void *scratch = nullptr;   // device address of the library's static scratch array on the engine's device
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};   // before projection, before decode, after
     bool timed = false;
@@ -627,15 +627,21 @@ int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
     return RNNT_OK;
 }
 
-// Utterances a team decodes at a time for a launch of nb, and frames of each and joint step while there are as many.
-void resident_rows(const ResidentPlan &pl, int nb, int *slots, int *la)
+// Utterances a team decodes at a time for a launch of nb of T frames, and frames of each and joint step while there are as many.
+void resident_rows(const ResidentPlan &pl, int nb, int T, int *slots, int *la)
 {
     if (pl.solo) { *slots = 1; *la = kSoloFrames; return; }
     // Eight rows a team where every list has eight utterances.  With four and eight, us a call, means of three draws: two-layer fp32 models, six
     // teams, 32 utterances 1181 and 1204, 42 1393 and 1392, 48 1549 and 1442, 64 1929 and 1679, 128 3721 and 3014, TDT 42 995 and
     // 998, 48 1087 and 1014, multi-blank 42 760 and 810, 48 868 and 865; bfloat16 mode, eight teams, 56 1152 and 1091, 64 1228 and 1158,
     // e4m3 TDT 57 635 and 661, 64 670 and 661, 72 770 and 737; one layer 48 1148 and 1078, 64 1416 and 1231; small, 16 teams, 96 563 and 529, 128 683 and 567.
-    *slots = nb >= kResRows * pl.n_teams ? kResRows : std::min(4, (nb + pl.n_teams - 1) / pl.n_teams);
+    // Of short utterances the last ones of a list are most of a call, and a joint step that has four frames of every row comes too early for
+    // a label: lists of a few hundred frames stay with four rows.  Means of ten draws, utterances x frames: two-layer fp32 models 48 x 20 172 and
+    // 187, 73 x 31 242 and 239, 56 x 60 326 and 331, 64 x 60 387 and 358, TDT 143 and 155, 201 and 206, (99 x 22) 234 and 227, 287 and 291, multi-blank
+    // 50 x 20 180 and 201, 73 x 31 267 and 274, 56 x 100 530 and 476; bfloat16 mode 64 x 20 155 and 159, 64 x 30 188 and 193, e4m3 72 x 60
+    // 232 and 233; one layer 64 x 20 158 and 160, 72 x 60 319 and 285, small 128 x 30 159 and 149.
+    const bool long_lists = (long long)nb * T >= (long long)pl.n_teams * (pl.kind == kResident1 ? 200 : 400);
+    *slots = nb >= kResRows * pl.n_teams && long_lists ? kResRows : std::min(4, (nb + pl.n_teams - 1) / pl.n_teams);
     *la = *slots <= 2 ? 16 / *slots : kResSamples / *slots;
     *la = std::min(*la, 16);
 }
@@ -654,7 +660,7 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
     ci.p_top = res_whole(pl.bf != 0, pl.cls) ? nullptr : ws.top;
     HIP_TRY(launch_encoder_projection(enc_out, enc_len, enc_weights(e), ws.P, B, T, d.F, d.J,
                                       is_bf16_arith(e->wt), ci, stream));
-    e->last_B = B; e->last_used.clear(); e->last_ws = ws; e->last_resident = true;
+    e->last_B = B; e->last_T = T; e->last_used.clear(); e->last_ws = ws; e->last_resident = true;
     if (pl.solo) {
         SoloParams p{};
         p.H = d.H; p.J = d.J; p.V1 = d.V1; p.NOUT = e->NOUT; p.blank = d.blank;
@@ -690,7 +696,7 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
             for (int i = 0; i < kMaxDur; ++i) p.durations[i] = e->durations[i];
             p.B = nb; p.T = T; p.S = S; p.cap = cap;
             int la;
-            resident_rows(pl, nb, &p.slots, &la);
+            resident_rows(pl, nb, T, &p.slots, &la);
             p.spin_limit = wait_polls(e->wait_limit, kResidentWait);
             p.touch_rows = touch_rows(nb, T, d.J);
             p.pl = pl;
@@ -1327,7 +1333,7 @@ int rnnt_engine_stats(rnnt_engine *eng, rnnt_stats *out)
             out->max_joint_steps = std::max<int64_t>(out->max_joint_steps, s[kStatJoint]);
         }
         int slots, la;
-        resident_rows(pl, std::min(eng->last_B, kResList * pl.n_teams), &slots, &la);
+        resident_rows(pl, std::min(eng->last_B, kResList * pl.n_teams), eng->last_T, &slots, &la);
         out->n_teams = pl.n_teams;
         out->team_size = pl.solo ? 1 : res_team(pl.cls);
         out->joint_groups = 1;
