@@ -675,8 +675,10 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
         p.done = e->done; p.status = ws.status; p.stats = ws.stats; p.n_records = pl.n_teams;
         // (Its work-groups wait for nobody, but while they run another decode's would get a part of the device, and wait.  One utterance of 20 frames
         // 53.4 us in no order, 56.6 in this one.)
-        const int rc = in_launch_order(stream, [&](bool plain) -> int {
-            HIP_TRY(launch_solo(p, (plain && !e->coop_launch) || e->plain_launch, stream));
+        const int rc = in_launch_order(stream, [&](LaunchTurn &turn) -> int {
+            const bool plain = (turn.plain && !e->coop_launch) || e->plain_launch;
+            HIP_TRY(launch_solo(p, plain, stream, turn.end));
+            turn.ended = plain && turn.end;
             return RNNT_OK;
         });
         if (rc) return rc;
@@ -684,7 +686,8 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
         return RNNT_OK;
     }
     const int launch_rows = kResList * pl.n_teams;
-    const int rc = in_launch_order(stream, [&](bool plain) -> int {
+    const int rc = in_launch_order(stream, [&](LaunchTurn &turn) -> int {
+        const bool plain = (turn.plain && !e->coop_launch) || e->plain_launch;
         for (int off = 0; off < B; off += launch_rows) {
             const int nb = std::min(launch_rows, B - off);
             if (off > 0) HIP_TRY(launch_reset_resident(ws.form, pl.n_xcd * 32, ws.abort_flag, stream));
@@ -719,8 +722,9 @@ int run_resident(rnnt_engine *e, int variant, const float *enc_out, const int32_
             p.form = ws.form; p.abort_flag = ws.abort_flag; p.status = ws.status; p.stats = ws.stats;
             p.zero_stats = off == 0;
             p.count_rows = variant == kFrameLooping;
-            HIP_TRY(launch_resident(p, p.slots <= 2 ? 1 : 2, (plain && !e->coop_launch) || e->plain_launch, stream));
+            HIP_TRY(launch_resident(p, p.slots <= 2 ? 1 : 2, plain, stream, off + nb == B ? turn.end : nullptr));
         }
+        turn.ended = plain && turn.end;
         return RNNT_OK;
     });
     if (rc) return rc;
@@ -808,7 +812,7 @@ int run_decode(rnnt_engine *e, int variant, const float *enc_out, const int32_t 
         p.done = e->done ? e->done + off : nullptr;
         // the status word is the engine's (or the static workspace's) for all layouts; the
         // step counts are kept per layout and start at zero in a layout's first launch
-        const int rc = in_launch_order(stream, [&](bool) -> int {
+        const int rc = in_launch_order(stream, [&](LaunchTurn &) -> int {
             HIP_TRY(launch_decode(p, off == 0, first_in_layout, stream));
             return RNNT_OK;
         });

@@ -273,7 +273,7 @@ int rnnt_probe_exchange(int32_t team_size, int32_t len, int32_t tagged, double *
         PROBE_TRY(hipMemset(a.ctr, 0, (size_t)a.n_teams * 32 * sizeof(unsigned)));
         PROBE_TRY(hipMemset(a.abort_flag, 0, sizeof(unsigned)));
         void *args[] = {&a};
-        const int rc = rnnt::in_launch_order(nullptr, [&](bool) -> int {
+        const int rc = rnnt::in_launch_order(nullptr, [&](rnnt::LaunchTurn &) -> int {
             PROBE_TRY(hipEventRecord(t.a, nullptr));
             PROBE_TRY(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(exchange_kernel), dim3(n_wg), dim3(kT),
                                                  args, 0, nullptr));

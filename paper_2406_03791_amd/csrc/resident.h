@@ -236,6 +236,7 @@ struct ResidentImages { float *w, *w_help, *w_tail, *s_out, *s_pred, *s_ih, *s_h
 hipError_t pack_resident(const ResidentPlan &pl, const ResidentWeights &rw, const ResidentImages &im, hipStream_t stream);
 
 // nmt: tiles of 16 samples a joint step has, 1 (up to two utterances at a time per team) or 2
-hipError_t launch_resident(const ResidentParams &p, int nmt, bool plain, hipStream_t stream);
+// end: an event for the kernel's own completion, or null (plain launches)
+hipError_t launch_resident(const ResidentParams &p, int nmt, bool plain, hipStream_t stream, hipEvent_t end);
 
 }  // namespace rnnt

@@ -2059,7 +2059,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
 }
 
 template <int KIND, bool BF, int CLS, int NMT, int R>
-hipError_t launch_resident_one(const ResidentParams &p, bool plain, hipStream_t stream)
+hipError_t launch_resident_one(const ResidentParams &p, bool plain, hipStream_t stream, hipEvent_t end)
 {
     const void *fn = reinterpret_cast<const void *>(&resident_kernel<KIND, BF, CLS, NMT, R>);
     constexpr unsigned lds = (unsigned)resident_lds(KIND, BF, CLS, NMT, R).bytes;
@@ -2068,7 +2068,7 @@ hipError_t launch_resident_one(const ResidentParams &p, bool plain, hipStream_t 
     ResidentParams pc = p;
     void *args[] = {&pc};
     const dim3 grid(p.pl.n_xcd * 32), block(kResThreads);
-    if (plain) return hipLaunchKernel(fn, grid, block, args, lds, stream);
+    if (plain) return launch_ending(fn, grid, block, args, lds, stream, end);
     return hipLaunchCooperativeKernel(fn, grid, block, args, lds, stream);
 }
 

@@ -41,6 +41,6 @@ struct SoloParams {
 
 // VT: token outputs, as in calls.  w: solo_parts(NOUT, VT) * 256 groups of four; *check, zero before: raised if a weight is not finite
 hipError_t pack_solo(const float *w_hh, const float *w_pred, const float *w_out, int H, int J, int NOUT, int VT, float4 *w, unsigned *check, hipStream_t stream);
-hipError_t launch_solo(const SoloParams &p, bool plain, hipStream_t stream);
+hipError_t launch_solo(const SoloParams &p, bool plain, hipStream_t stream, hipEvent_t end);
 
 }  // namespace rnnt

@@ -390,7 +390,7 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
 }
 
 template <int TILES, bool LAST, bool WALK>
-hipError_t launch_tiles(const SoloParams &p, bool plain, hipStream_t stream)
+hipError_t launch_tiles(const SoloParams &p, bool plain, hipStream_t stream, hipEvent_t end)
 {
     const void *fn = reinterpret_cast<const void *>(&solo_kernel<TILES, LAST, WALK>);
     const unsigned lds = (unsigned)solo_lds(p.V1, TILES).total * 4u;
@@ -399,7 +399,7 @@ hipError_t launch_tiles(const SoloParams &p, bool plain, hipStream_t stream)
     SoloParams pc = p;
     void *args[] = {&pc};
     const dim3 grid((unsigned)(p.B < p.n_records ? p.B : p.n_records)), block(kSoloThreads);
-    if (plain) return hipLaunchKernel(fn, grid, block, args, lds, stream);
+    if (plain) return launch_ending(fn, grid, block, args, lds, stream, end);
     return hipLaunchCooperativeKernel(fn, grid, block, args, lds, stream);
 }
 
@@ -412,15 +412,15 @@ hipError_t pack_solo(const float *w_hh, const float *w_pred, const float *w_out,
     return hipGetLastError();
 }
 
-hipError_t launch_solo(const SoloParams &p, bool plain, hipStream_t stream)
+hipError_t launch_solo(const SoloParams &p, bool plain, hipStream_t stream, hipEvent_t end)
 {
     // what the kernel is laid out for
     if (p.H < 1 || p.H > kSoloWidth || p.J < 1 || p.J > kSoloWidth || p.J % 4 != 0 || p.NOUT > kSoloOutputs || p.V1 > p.NOUT || p.B < 1 || p.n_records < 1)
         return hipErrorInvalidValue;
     const bool walk = p.tdt || p.VT != p.V1;
     auto launch = [&](auto tiles, auto last) {
-        return walk ? launch_tiles<decltype(tiles)::value, decltype(last)::value, true>(p, plain, stream)
-                    : launch_tiles<decltype(tiles)::value, decltype(last)::value, false>(p, plain, stream);
+        return walk ? launch_tiles<decltype(tiles)::value, decltype(last)::value, true>(p, plain, stream, end)
+                    : launch_tiles<decltype(tiles)::value, decltype(last)::value, false>(p, plain, stream, end);
     };
     typedef std::integral_constant<int, 1> One;
     typedef std::integral_constant<int, 2> Two;
