@@ -187,8 +187,8 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
         auto frames_there = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
         int t = 0, n = 0, cnt = 0, last = p.blank, have = 1;
         bool need = true, pending = false;
+        __syncthreads();              // (nobody reads the last utterance's frames any more, and T0 is there)
         float c = 0.f, pre = 0.f, t0 = lds[lo.t0 + last * (4 * W) + t256];
-        __syncthreads();              // (nobody reads the last utterance's frames any more)
         load_chunk(0);
         load_chunk(1);
         frames_there();
