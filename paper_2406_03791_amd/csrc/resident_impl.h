@@ -612,8 +612,9 @@ __device__ __forceinline__ void res_finish_row(int b, int cnt)
 
 __device__ __forceinline__ int from_lane(int v, int lane) { return __builtin_amdgcn_ds_bpermute(lane << 2, v); }
 
-// KIND: ResidentKind; BF: bfloat16 mode; CLS: size class; NMT: tiles of 16 samples of a joint step; R: rows of a team
-template <int KIND, bool BF, int CLS, int NMT, int R>
+// KIND: ResidentKind; BF: bfloat16 mode; CLS: size class; NMT: tiles of 16 samples of a joint step; R: rows of a team; ONE: no team has
+// more than one utterance
+template <int KIND, bool BF, int CLS, int NMT, int R, bool ONE>
 __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const ResidentParams p)
 {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -622,6 +623,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     constexpr int W = res_width(CLS), ROW = res_row(CLS), TS = res_team(CLS);
     constexpr int NH = res_halves(CLS), NF = NH / 2, NB = NF + (NH & 1), LREGS = res_lstm_regs(BF, CLS);
     constexpr bool WHOLE = res_whole(BF, CLS);
+    static_assert(!ONE || (NMT == 1 && R == 4), "sixteen frames of the one utterance");
     constexpr int LR = 16 / R, GL = R / 4, RB = R == 4 ? 2 : 3;      // lanes per row in the loop control and the cells, gates of such a lane; bits of a row's number
     constexpr int STAGE_ROW = res_stage_row(R);
     typedef Operand<BF, CLS, R> Op;
@@ -1188,6 +1190,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     };
     __syncthreads();                  // the list is complete
     bool any_active, need_pred, later = false;
+    RRow only{};                      // ONE: the row, and its utterance
+    int only_b = 0;
     {
         int b = 0, len = 0;
         const int r = (int)((unsigned)lane0 / LR) & (R - 1);
@@ -1198,6 +1202,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         row_steps = __popcll(m);
         lay_out(all_tiles, lane0, (unsigned)m);
         set_up_samples(lane0, 0, b, len);
+        if constexpr (ONE) { only.len = __builtin_amdgcn_readfirstlane(len); only_b = __builtin_amdgcn_readfirstlane(b); }
     }
     // the row of the embedding table (folded into the first layer) that the next prediction step adds
     Gates t0{};
@@ -1293,7 +1298,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             const unsigned n = n_pred;
             if (PAIR && n > 1) wait_pre(n - 1, 0);
             RES_MARK(0);
-            if constexpr (PAIR) {
+            if constexpr (PAIR && !ONE) {
                 const float *from = stored();
 #pragma unroll
                 for (int l = 0; l < NL; ++l) {
@@ -1319,6 +1324,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 }
                 if constexpr (!PAIR)
                     if (has_cells) pc = NL == 1 ? first_sum : sum_of(l == 0 ? sums_rec0 : sums_top, rc.sh[l]);
+                if constexpr (ONE && PAIR) {
+                    // (it emitted, or nothing would be predicted: all that the cell keeps is its last candidate, in a register: one utterance 326 and 320 us.
+                    // Models whose weights leave more room, which kept it there before, took up to 0.9 % longer.)
+                    cs[l] = cc[l];
+#pragma unroll
+                    for (int e = 0; e < GL; ++e) ps[l].g[e] = n > 1 ? pc.g[e] : 0.f;
+                    return;
+                }
                 const bool take = lane_const & kTake, fresh_row = lane_const & kFresh;       // (bits: as a chain of comparisons it became branches)
                 cs[l] = take ? cc[l] : cs[l]; cs[l] = fresh_row ? 0.f : cs[l];
 #pragma unroll
@@ -1356,7 +1369,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 for (int e = 0; e < GL; ++e) in.g[e] = ps[0].g[e] + t0.g[e];
                 cell<R>(in, l.j, cs[0], cc[0], h);
                 publish_h(0, l, h);
-                if constexpr (PAIR) keep_state(0);
+                if constexpr (PAIR && !ONE) keep_state(0);
                 if constexpr (NREC > 1) commit(1);
                 if (NMT == 2 && later) {
                     const int lane = lane_id(), r = (int)((unsigned)lane / LR) & (R - 1);
@@ -1403,7 +1416,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     for (int e = 0; e < GL; ++e) in.g[e] += ps[1].g[e] + rc.b1[l.lu * 4 + l.j * GL + e];
                     cell<R>(in, l.j, cs[1], cc[1], h);
                     publish_h(1, l, h);
-                    if constexpr (PAIR) keep_state(1);
+                    if constexpr (PAIR && !ONE) keep_state(1);
                 }
                 RES_MARK(4);
                 // (while the hand-over is on its way) the recurrent part of the next step's first layer
@@ -1879,6 +1892,63 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             }
             RES_MARK(13);
         }
+        // ---- loop control of one utterance: the same, with everything but the results of the frames uniform -------------------
+        // (Tables of rows, their places in a step and the choice of those that wait are nothing to one row.  us a call: one utterance 341 and 326, five with
+        // log-probabilities 229 and 222, small model, eight, 263 and 244, multi-blank, four, 308 and 292, bfloat16 mode, eight, 161 and 152.)
+        if constexpr (ONE) {
+            const int lane = lane_id(), at = lane & 15;
+            if (PAIR) load_pre(n_pred, 0, pre[0]);           // (as below)
+            __syncthreads();
+            RES_MARK(14);
+            if (FRAMES_FIRST && !has_cells) __builtin_amdgcn_s_setprio(2);
+            const int mine = rc.s_k[at], left = only.len - only.t, avail = min(16, left);
+            int pos = 0, dval = 0;
+            bool found = false;
+            if (!(p.tdt || p.VT != p.V1)) {
+                pos = __builtin_ctz(((unsigned)__ballot(mine != p.blank) & 0xffffu) | 1u << avail);
+                found = pos < avail;
+            } else {
+                // where the walk goes to from every frame, then frame by frame
+                int d = 0;
+                if (mine >= p.V1) d = max(rc.dur[(mine - p.V1) & (kMaxDur - 1)], 1);            // big blank: its span of frames
+                else if (mine == p.blank) d = p.tdt ? min(max(rc.s_d[at], 1), kFarthest) : 1;
+                const unsigned labels = (unsigned)__ballot(d == 0);
+                while (pos < avail && !(found = (labels >> pos & 1u) != 0u)) pos += __builtin_amdgcn_readlane(d, pos);
+            }
+            const bool writer = x.rank == 0 && x.wave == kResWaves - 1 && lane == 0;
+            int adv = pos;
+            if (adv > 0) only.n = 0;
+            if (found) last = __builtin_amdgcn_readlane(mine, pos);
+            load_t0();
+            if (found) {
+                if (p.tdt) dval = __builtin_amdgcn_readfirstlane(rc.s_d[pos]);
+                if (writer) {
+                    const Args a = args_again();
+                    if (only.cnt < a->cap) {
+                        const long long o = (long long)only_b * a->cap + only.cnt;
+                        a->tokens[o] = last;
+                        if (a->frames) a->frames[o] = only.t + pos;
+                        if (a->logits) a->logits[o] = rc.s_v[pos];
+                        if (a->logps) a->logps[o] = rc.s_lp[pos];
+                        if (a->durs) a->durs[o] = dval;
+                    } else {
+                        rc.st_overflow = 1;
+                    }
+                }
+                ++only.cnt;
+                if (p.tdt && dval > 0) { adv += min(dval, kFarthest); only.n = 0; }
+                else if (++only.n == p.S) { ++adv; only.n = 0; }
+            }
+            any_active = adv < left;
+            only.t += adv;
+            if (!any_active && writer) res_finish_row(only_b, only.cnt);
+            need_pred = found && any_active;
+            lane_const = (lane_const & ~(kTake | kFresh)) | (need_pred ? kTake : 0);
+            const int now = min(16, only.len - only.t);
+            pidx = at < now ? only_b * p.T + only.t + at : -1;
+            if (any_active) n_samples += now;
+            if (need_pred) ++row_steps;
+        } else
         // ---- loop control: every wave for itself, lane = row (outputs: the last wave, which has the least to do next) ------
         {
             const int lane = lane_id(), r = (int)((unsigned)lane / LR) & (R - 1);
@@ -2058,10 +2128,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     }
 }
 
-template <int KIND, bool BF, int CLS, int NMT, int R>
+template <int KIND, bool BF, int CLS, int NMT, int R, bool ONE = false>
 hipError_t launch_resident_one(const ResidentParams &p, bool plain, hipStream_t stream, hipEvent_t end)
 {
-    const void *fn = reinterpret_cast<const void *>(&resident_kernel<KIND, BF, CLS, NMT, R>);
+    const void *fn = reinterpret_cast<const void *>(&resident_kernel<KIND, BF, CLS, NMT, R, ONE>);
     constexpr unsigned lds = (unsigned)resident_lds(KIND, BF, CLS, NMT, R).bytes;
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;

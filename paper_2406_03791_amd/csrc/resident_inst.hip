@@ -14,6 +14,7 @@ hipError_t RNNT_CAT(launch_resident_, RNNT_RES_KIND, _, RNNT_RES_BF, _, RNNT_RES
 {
     if (p.slots > 4) return launch_resident_one<RNNT_RES_KIND, RNNT_RES_BF != 0, RNNT_RES_CLS, 2, 8>(p, plain, stream, end);
     if (nmt == 2) return launch_resident_one<RNNT_RES_KIND, RNNT_RES_BF != 0, RNNT_RES_CLS, 2, 4>(p, plain, stream, end);
+    if (p.slots == 1) return launch_resident_one<RNNT_RES_KIND, RNNT_RES_BF != 0, RNNT_RES_CLS, 1, 4, true>(p, plain, stream, end);
     return launch_resident_one<RNNT_RES_KIND, RNNT_RES_BF != 0, RNNT_RES_CLS, 1, 4>(p, plain, stream, end);
 }
 }  // namespace rnnt

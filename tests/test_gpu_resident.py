@@ -555,3 +555,34 @@ def test_eight_rows_a_team(pkg, H, J, V1, L, bf16, teams, extra, more):  # noqa:
     _, _, stats = check(pkg, w, w.variant, f"eight rows {H}/{J}/{V1}/{L} {extra} bf16={bf16} {more}", engine=eng, bf16=bf16, logp=not bf16)
     assert stats["n_teams"] == teams and stats["lookahead"] == 4
     eng.close()
+
+
+# (teams of the three size classes, as in EIGHT)
+ONE = [(64, 68, 60, 1, False, 32), (128, 128, 257, 2, True, 32), (316, 320, 529, 1, False, 8), (320, 316, 500, 1, True, 16), (100, 128, 250, 2, False, 24),
+       (324, 332, 1040, 2, False, 6), (324, 332, 1040, 2, True, 8), (640, 636, 1025, 1, False, 8)]
+
+
+@pytest.mark.parametrize("H,J,V1,L,bf16,teams", ONE)
+@pytest.mark.parametrize("extra", [{}, dict(durations=(0, 1, 3, 90)), dict(big_blanks=(2, 17, 70))])
+@pytest.mark.parametrize("full", [False, True])
+def test_one_utterance_a_team(pkg, H, J, V1, L, bf16, teams, extra, full):  # noqa: F811
+    """One utterance, and as many as there are teams: labels that follow each other on a frame, at the first, last and one more than the last
+    frame of a step, and none for several steps; empty utterances and such of a frame; jumps within a step and over several."""
+    w = model_inputs(H, J, V1, L, B=teams if full else 1, T=131, seed=H + full, F=(J + 15) // 16 * 16, **extra)
+    want = 60.0 * np.maximum(w.model.w_out[w.model.dims.blank].astype(np.float64), 0.0) - w.model.b_enc
+    blank = np.linalg.lstsq(w.model.w_enc.astype(np.float64), want, rcond=None)[0].astype(np.float32)
+    g = np.random.default_rng(w.B)
+    gap = np.array([1, 2, 15, 16, 17, 33, 49])[g.integers(0, 7, (w.B, 131))].cumsum(1)
+    label = (gap[:, :, None] == np.arange(131)[None, None, :] + 1).any(1)
+    label[::3, 40:60] = True
+    x = np.where(label[:, :, None], w.enc_out, blank[None, None]).astype(np.float32)
+    length = np.sort(g.integers(60, 132, w.B))[::-1].astype(np.int32)
+    if full:
+        length[-1], length[-2] = 0, 1
+        if not bf16:
+            x[3] *= np.float32(1e9)
+    w = dataclasses.replace(w, enc_out=x, enc_len=length)
+    eng = pkg.Engine(w.model, w.B, w.T, flags=pkg.RNNT_FLAG_BF16_ARITHMETIC if bf16 else 0)
+    _, _, stats = check(pkg, w, w.variant, f"one a team {H}/{J}/{V1}/{L} {extra} bf16={bf16} {full}", engine=eng, bf16=bf16, logp=not bf16)
+    assert stats["n_teams"] == teams and stats["lookahead"] == 16
+    eng.close()
