@@ -586,3 +586,16 @@ def test_one_utterance_a_team(pkg, H, J, V1, L, bf16, teams, extra, full):  # no
     _, _, stats = check(pkg, w, w.variant, f"one a team {H}/{J}/{V1}/{L} {extra} bf16={bf16} {full}", engine=eng, bf16=bf16, logp=not bf16)
     assert stats["n_teams"] == teams and stats["lookahead"] == 16
     eng.close()
+
+
+# (the folded embedding table: tiles of 64 labels and 16 units, 32 values of the embedding at a time)
+@pytest.mark.parametrize("H,J,V1,E", [(64, 60, 65, 1), (68, 64, 64, 31), (60, 128, 63, 32), (316, 320, 129, 33), (644, 640, 40, 65), (20, 72, 191, 96)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_folded_embedding_table(pkg, H, J, V1, E, bf16):  # noqa: F811
+    dims = synth.ModelDims(F=32, E=E, H=H, L=1, J=J, V1=V1)
+    model = synth.make_model(dims, H + V1, weight_range=0.15, emb_gain=4.0, pred_gain=3.0, blank_bias=1.5)
+    x, ln = synth.make_inputs(E, 40, 30, dims.F, 0, 30)
+    w = synth.Workload(f"folded table {H}/{V1}/{E}", "label", model, x, ln, 4)
+    eng = pkg.Engine(model, w.B, w.T, flags=pkg.RNNT_FLAG_BF16_ARITHMETIC if bf16 else 0)
+    check(pkg, w, "label", w.name, engine=eng, bf16=bf16, logp=True)
+    eng.close()
