@@ -28,8 +28,8 @@ HBM_PEAK_GBS = 8000.0
 # with register-resident weights, which runs the models measured here, and of the streaming one (--streaming).
 PHASES = ["pred: helpers' results", "pred: layer-0 cell, published", "pred: layer-0 vector received", "pred: input stage of layer 1",
           "pred: layer-1 cell, published", "pred: recurrent stage of layer 0", "pred: layer-1 vector received",
-          "pred: projection stage, q published", "pred: recurrent stage of the top layer", "pred: q received",
-          "joint: frames there (work-group barrier)", "joint: output stage", "joint: sums, argmax published", "joint: keys received",
+          "pred: projection stage, operand published", "pred: recurrent stage of the top layer", "joint: operand received",
+          "joint: operand published (no new label)", "joint: output stage", "joint: sums, argmax published", "joint: keys received",
           "joint: result shared (work-group barrier)", "control: hops, labels emitted, next samples"]
 STREAMING_PHASES = ["pred: stage-0 input filled (general)", "pred: recurrent stage of all layers",
                     "pred: layer-0 cell and store", "pred: barrier (general)",

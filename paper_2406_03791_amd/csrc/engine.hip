@@ -640,6 +640,8 @@ void resident_rows(const ResidentPlan &pl, int nb, int T, int *slots, int *la)
     // 187, 73 x 31 242 and 239, 56 x 60 326 and 331, 64 x 60 387 and 358, TDT 143 and 155, 201 and 206, (99 x 22) 234 and 227, 287 and 291, multi-blank
     // 50 x 20 180 and 201, 73 x 31 267 and 274, 56 x 100 530 and 476; bfloat16 mode 64 x 20 155 and 159, 64 x 30 188 and 193, e4m3 72 x 60
     // 232 and 233; one layer 64 x 20 158 and 160, 72 x 60 319 and 285, small 128 x 30 159 and 149.
+    // (What loses by eight rows is a batch whose time is that of one utterance, which the host cannot see: one with ten labels on each of 200 frames among 127 of
+    // blanks 13.9 and 16.0 ms.  Where all are like that, 87.9 and 52.9.)
     const bool long_lists = (long long)nb * T >= (long long)pl.n_teams * (pl.kind == kResident1 ? 200 : 400);
     *slots = nb >= kResRows * pl.n_teams && long_lists ? kResRows : std::min(4, (nb + pl.n_teams - 1) / pl.n_teams);
     *la = *slots <= 2 ? 16 / *slots : kResSamples / *slots;

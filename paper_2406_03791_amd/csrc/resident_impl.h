@@ -8,8 +8,8 @@
 // of work-groups sits inside one XCD, so its hand-overs go through that XCD's L2: a store that stays
 // in the L2 and a load that passes by the L1 hand 640 floats to 32 work-groups in 0.70 us, where
 // stores and loads through the memory side take 1.3 us (4 x 640 floats: 0.88 against 1.4 us).
-// 32 utterances of a two-layer model of 640 units: 4.35 ms in the kernel that streams its weights, 1.26 here, one of 500
-// frames 1.63 and 0.44.
+// 32 utterances of a two-layer model of 640 units: 4.35 ms in the kernel that streams its weights, 1.14 here, one of 500
+// frames 1.63 and 0.41.
 //
 // Work split inside a team of `ts` work-groups: LSTM units, projection columns and output columns
 // in contiguous ranges.  Every dense stage is the same: K in eighths over the waves, tiles of 16 outputs

@@ -3,7 +3,7 @@
 // One work-group per utterance, and nothing goes from one work-group to another.  Spread over the eight work-groups of a
 // team of the resident kernel, as every model of one layer was, a model of 64 units and 17 outputs spent its steps on hand-overs:
 // three of 0.4 to 0.5 us and the latency around them, 3.5 us a step; here vectors go through LDS, and a step takes
-// 1.07 us (a call of one utterance of 20 frames 157 and 60 us, and 69 for 128 of them).  Emitted logits are 2.1e-8 from 64 bits, rms,
+// 1.07 us (a call of one utterance of 20 frames 157 and 55 us).  Emitted logits are 2.1e-8 from 64 bits, rms,
 // as they were.
 //
 // Bound by latency: a chain of cell, projection, joint, sums over the waves and argmax, with three barriers.  What can be off the chain
