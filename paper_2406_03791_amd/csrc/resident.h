@@ -155,6 +155,21 @@ RNNT_HD constexpr int res_z_k4(bool bf, int cls, unsigned at)
     return (int)(first + full * 8u + (bf ? in % 1024u / 128u : g));
 }
 
+// Frames of each of n rows in a joint step of nt tiles of samples (nmt: of the instance; rows: of a team): dealt evenly, 31 for one row of two
+// tiles, so that shifts of a word by 0 to 31 do.  (Label-dense steps, one tile of two: no more than a team of all rows has, they are not looked at.)
+RNNT_HD constexpr int res_frames(int nt, int nmt, int rows, int n)
+{
+    const int at = n - 1;
+    return (int)((nt == 2 ? 0x04040506080a101full : nmt == 1 ? 0x02020203'04050810ull : rows == 4 ? 0x04050505ull : 0x0202020304050505ull) >> ((at < 0 ? 0 : at) * 8) & 0xffu);
+}
+// The place among those rows that sample s is of: s / la, rounded down half a sample from where it changes, so that the last bits of
+// inverse, 1 / la, say nothing.  Beyond the rows' samples it is the last place there can be: the word of rows has bits for no more.
+RNNT_HD constexpr int res_turn(int s, float inverse, int rows)
+{
+    const int turn = (int)(((float)s + 0.5f) * inverse);
+    return turn < rows ? turn : rows - 1;
+}
+
 // Byte offsets of a team's exchange buffers, every vector in kResSlots slots.
 // hr, pre: kResident2Pair; pre: [layer][slot][quarter of K][rank][wave of the cells][lane]
 struct ResidentBuf { unsigned h[2], z, key, dur, lse, hr[2], pre, bytes; };
@@ -223,7 +238,7 @@ RNNT_HD constexpr ResidentLds resident_lds(int kind, bool bf, int cls, int nmt, 
     if (l.bytes < kResAlone) l.bytes = kResAlone;
     return l;
 }
-constexpr int kResCtl = 5376;             // bytes kept for the control block and votes
+constexpr int kResCtl = 5504;             // bytes kept for the control block and votes
 static_assert(resident_lds(kResident1, false, 0, 2, 8).bytes + kResCtl <= 160 * 1024 && resident_lds(kResident2, true, 0, 2, 8).bytes + kResCtl <= 160 * 1024 &&
               resident_lds(kResident2Pair, false, 0, 2, 8).bytes + kResCtl <= 160 * 1024, "the largest layouts and the control block fit the LDS");
 

@@ -95,6 +95,10 @@ struct RRows {
     int since[kPlaces], next;         // t some steps ago; first utterance of the list that no row has had
 };
 
+// Columns that the waves forming the joint's operand have lanes for, in steps of one tile: a work-group has 20 at most, and these lanes read what
+// they do not send (limited to the 20, the index took a register that the weights need).
+constexpr int kResFormed = 40;
+
 struct RCtl {
     RRows rows[kResWaves];
     int s_k[kResSamples], s_d[kResSamples];        // results of a joint step
@@ -107,7 +111,7 @@ struct RCtl {
     // this work-group's slices of the biases: second layer [unit][gate], projection, output and tail column; and of
     // what sums are multiplied by (fp32): the same and [layer][unit][gate] of the recurrent matrices
     float b1[kResUnits * 4], s1[kResUnits * 4], sh[2][kResUnits * 4];
-    __align__(16) float bp[24], sp[24];
+    __align__(16) float bp[kResFormed], sp[kResFormed];
     float2 bo[2][16], so[2][16];      // with two tiles of samples: of this work-group and its partner, the even rank first
     float bt[2], st[2];
     float scale[RRows::kPlaces];      // fp32: of the utterances in work, see joint_scale
@@ -958,7 +962,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
 #pragma unroll
             for (int l = 0; l < NREC; ++l) rc.sh[l][at] = sh[l];
         }
-        if (at < 24) { rc.bp[at] = bp; rc.sp[at] = sp; }
+        if (at < kResFormed) { rc.bp[at] = bp; rc.sp[at] = sp; }
         if (at < 3 * 64) reinterpret_cast<unsigned *>(lds + lo.z_at)[at] = res_z_at(BF, CLS, g0 + at / ZS, at % ZS);
         if (at < 32 * NMT) { reinterpret_cast<float *>(rc.bo)[at] = bo_; reinterpret_cast<float *>(rc.so)[at] = so_; }
         if (at < NMT) { rc.bt[at] = bt; rc.st[at] = st; }
@@ -1095,8 +1099,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // (5 bits, at 20); its own row's first sample (5, at 25); kTake and kFresh.
     int lane_const = kFresh;
     // Rows that take part in the joint step (one bit in four, as in LEADS), and the frames of each: the samples are dealt
-    // evenly to the rows with an utterance, so that the last ones of a team's list go on faster when the others have
-    // ended.  (One row of 32 samples: 31, which shifts of a word by 0 to 31 do for.)  With eight frames a row whatever
+    // evenly to the rows with an utterance (res_frames), so that the last ones of a team's list go on faster when the others have
+    // ended.  With eight frames a row whatever
     // its neighbours do, 32 utterances on six teams took 178, 170 and 151 joint steps instead of 161, 160 and 139 (three
     // draws; 1544, 1450 and 1348 us instead of 1470, 1412 and 1283), 19 of a multi-blank model 105, 89 and 69 instead of
     // 85, 76 and 54 (846, 760 and 602 us instead of 757, 711 and 520).
@@ -1106,18 +1110,16 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     auto lay_out = [&](auto nt_, int lane, unsigned of) {
         part_rows = of;
         const int n = __builtin_popcount(of);
-        // (a byte for every number of rows; label-dense: no more than a team of all rows has, they are not looked at)
-        la = (int)((decltype(nt_)::value == 2 ? 0x04040506080a101full : NMT == 1 ? 0x02020203'04050810ull : R == 4 ? 0x04050505ull : 0x0202020304050505ull) >> (max(n - 1, 0) * 8) & 0xffu);
-        unsigned rows_of = 0;            // the rows that take part, one after the other, two bits each
+        la = res_frames(decltype(nt_)::value, NMT, R, n);
+        unsigned rows_of = 0;            // the rows that take part, one after the other, RB bits each
         int at = 0;
 #pragma unroll
         for (int r = 0; r < R; ++r)
             if (of >> (r * LR) & 1u) { rows_of |= (unsigned)r << at; at += RB; }
-        // (s / la, rounded down: half a sample from where it changes, so that the reciprocal's last bits say nothing)
         const float inverse = __builtin_amdgcn_rcpf((float)la);
         auto turn_of = [&](int s) {
             if constexpr (R == 4) return (s >= la ? 1 : 0) + (s >= 2 * la ? 1 : 0) + (s >= 3 * la ? 1 : 0);
-            else return (int)(((float)s + 0.5f) * inverse);
+            else return res_turn(s, inverse, R);
         };
         auto row_of = [&](int s) { return (int)(rows_of >> (turn_of(s) * RB) & (R - 1)); };
         const int s = lane & (ZS - 1);
@@ -1146,6 +1148,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // Two columns of a sample for a lane, four columns of 32 samples for a wave (of 16: eight): waves kFormers and after.
     auto publish_z = [&](auto nt_, unsigned n) {
         const int lane = lane_id(), s = lane / 2 & (ZS - 1), cg = (x.wave - kFormers) * (32 / ZS) + lane / (2 * ZS), row = lane_const & (R - 1);
+        static_assert((kResWaves - kFormers) * (32 / ZS) * 4 <= kResFormed, "the tables have a place for every lane");
         const float *v = sums_pr + row * kResProjRow + min(cg, kResProjRow / 4 - 1) * 4 + (lane & 1) * 2;
         r2f o[kResWaves];
 #pragma unroll

@@ -5,7 +5,9 @@
 // do and checks that every (col, k) of the matrix turns up exactly once, at the place the
 // plan says, and that everything else is zero.  Also checks e4m3_bits on all 256 codes, the
 // row-scaled e4m3 and block-scaled e2m1 forms (exponent rules, rounding, packed codes), the split of the joint
-// output stage into an MFMA part and tail columns, and which rows of the projected frames are asked for ahead.
+// output stage into an MFMA part and tail columns, the samples of a joint step and the places of its operand, and which rows of the projected
+// frames are asked for ahead.
+#include <array>
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -218,7 +220,20 @@ int main()
     for (unsigned polls : {0u, 1u, kStreamingWait, kResidentWait, 0xffffffffu})
         for (unsigned by_default : {kStreamingWait, kResidentWait})
             if (wait_polls(polls, by_default) != polls || wait_polls(-1, by_default) != by_default) { std::printf("wait limit\n"); return 1; }
-    // frames that are asked for ahead: the sample's row and the frames of a step, of the launch's rows only
+    // samples of a joint step: the rows' places, and shifts of a word by RB bits a place for every sample, also beyond the rows'
+    for (const auto &[nt, nmt, rows] : {std::array{2, 2, 8}, std::array{1, 2, 8}, std::array{2, 2, 4}, std::array{1, 2, 4}, std::array{1, 1, 4}})
+        for (int n = 0; n <= rows; ++n) {
+            const int la = res_frames(nt, nmt, rows, n), bits = rows == 4 ? 2 : 3;
+            unsigned of = 0;
+            for (int i = 0; i < rows; ++i) of |= (unsigned)i << (i * bits);
+            if (la < 1 || n * la > 16 * nt) { std::printf("frames %d tiles of %d, %d of %d rows\n", nt, nmt, n, rows); return 1; }
+            for (const float inverse : {std::nextafter(1.f / la, 0.f), 1.f / la, std::nextafter(1.f / la, 2.f)})
+                for (int s = 0; s < kResSamples; ++s) {
+                    const int turn = res_turn(s, inverse, rows);
+                    if ((int)(of >> (turn * bits) & (unsigned)(rows - 1)) != (s < n * la ? s / la : turn)) { std::printf("sample %d of %d rows\n", s, n); return 1; }
+                    ++checked;
+                }
+        }
     // the joint's operand in its exchange buffer: every group of four values of every sample has a place of its own in the slot, and
     // the inverse finds the group (bfloat16: groups) of 16 bytes
     for (int cls = 0; cls < kResClasses; ++cls)
@@ -243,6 +258,7 @@ int main()
                 }
             }
         }
+    // frames that are asked for ahead: the sample's row and the frames of a step, of the launch's rows only
     if (touch_rows(64, 256, 512) != 0 || touch_rows(27, 500, 640) != 27 * 500 || touch_rows(1, 2147483647, 4) != 2147483647) {
         std::printf("touch rows\n");
         return 1;
