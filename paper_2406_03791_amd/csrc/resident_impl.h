@@ -375,10 +375,15 @@ __device__ __forceinline__ auto weights_of(const RegW<N> &w, int t)
     else return at / 4 == N / 4 ? w.rest : (at % 4 ? w.q[at / 4].zw : w.q[at / 4].xy);
 }
 
-// fp32: both parts of the half block's weights, the high ones first, as the one instruction takes them that multiplies both: the
+// fp32: both parts of the half block's weights, the high ones first, as one instruction takes them that multiplies both: the
 // operand's sixteen k's twice.  (A half block's own instruction takes as long as a whole block's, one for each part, and waits between the
-// two kinds: 32 utterances 1185 us, 1169 with this, one layer 899 and 880, the small model 278 and 271, 128 utterances 3017 and 2997.  Logits are as
-// far from 64 bits, within 0.4 %.)
+// two kinds: 32 utterances 1185 us, 1169 with this, one layer 899 and 880, the small model 278 and 271, 128 utterances 3017 and 2997.)
+// An instruction aligns its products with the largest of them, so the small ones lose bits beside large ones.  In the joint step the products
+// with one low part have an instruction of their own, and low times low, which is nothing, goes with high times high.  In the projection of the
+// classes with no more than one whole block beside the half one, low and high parts of the weights have an instruction each, by zeros in
+// the other's place (stage, TWO).  Logits from 64 bits, against half blocks with instructions of their own, means of 60 to 80 models: layers of 320
+// +0.24 % (+-0.07) with low beside high parts in all stages, +0.01 % (+-0.07) as it is (eight utterances 0.9 % longer; the recurrent stage in two as well -0.10 %,
+// 1.8 % longer), layers of 128 +0.50 and -0.38 % (+-0.2), of 640 +0.02 and -0.01 % (+-0.05).
 template <int CLS, int T, int N>
 __device__ __forceinline__ r4f both_parts(const RegW<N> &w, int t) { return w.q[res_tile_at(false, CLS, T, res_halves(CLS) / 2, t, 0) / 4]; }
 
@@ -500,9 +505,15 @@ __device__ __forceinline__ void stage(const RegW<res_tile_regs(BF, CLS, T)> &w, 
     if constexpr (!BF) {
         static_for<0, NF>([&](auto kb_) { block(kb_, low); });
         if constexpr (NH % 2 != 0) {
-            const unsigned z[4] = {x.z[NF * 4], x.z[NF * 4 + 1], x.z[NF * 4], x.z[NF * 4 + 1]};
+            constexpr bool TWO = NF < 2 && T == 2;
+            const unsigned z0 = x.z[NF * 4], z1 = x.z[NF * 4 + 1];
+            const unsigned low_only[4] = {0u, 0u, z0, z1}, high_only[4] = {z0, z1, 0u, 0u}, both[4] = {z0, z1, z0, z1};
+            if constexpr (TWO) {
 #pragma unroll
-            for (int t = 0; t < T; ++t) sum[t] = tile_mfma<BF>(both_parts<CLS, T>(w, t), z, sum[t]);
+                for (int t = 0; t < T; ++t) sum[t] = tile_mfma<BF>(both_parts<CLS, T>(w, t), low_only, sum[t]);
+            }
+#pragma unroll
+            for (int t = 0; t < T; ++t) sum[t] = tile_mfma<BF>(both_parts<CLS, T>(w, t), TWO ? high_only : both, sum[t]);
         }
     }
     static_for<0, NF>([&](auto kb_) { block(kb_, high); });
@@ -1581,15 +1592,15 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                         ordered();
                         const int lane = lane_id(), m16 = lane & 15, g = lane >> 4;
                         constexpr bool BOTH = !BF && !WHOLE && !FULL;          // see both_parts
-                        const unsigned zhh[4] = {zh[0], zh[1], zh[0], zh[1]}, zll[4] = {zl[0], zl[1], zl[0], zl[1]}, zhl[4] = {zh[0], zh[1], zl[0], zl[1]};
+                        const unsigned zlh[4] = {zl[0], zl[1], zh[0], zh[1]}, zhl[4] = {zh[0], zh[1], zl[0], zl[1]};
                         if constexpr (BOTH) {
                             r4f w[AT];
 #pragma unroll
                             for (int c = 0; c < AT; ++c) w[c] = both_parts<CLS, 2>(w_ou, c);
 #pragma unroll
-                            for (int c = 0; c < AT; ++c) big[c] = tile_mfma<BF>(w[c], zll, big[c]);
+                            for (int c = 0; c < AT; ++c) big[c] = tile_mfma<BF>(w[c], zlh, big[c]);
 #pragma unroll
-                            for (int c = 0; c < AT; ++c) big[c] = tile_mfma<BF>(w[c], zhh, big[c]);
+                            for (int c = 0; c < AT; ++c) big[c] = tile_mfma<BF>(w[c], zhl, big[c]);
                         } else if constexpr (WHOLE) {
 #pragma unroll
                             for (int c = 0; c < 2; ++c) {
@@ -1657,9 +1668,9 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     static_for<0, HALF>([&](auto c_) {
                         constexpr int c = decltype(c_)::value;
                         const unsigned *zh = z + parts_at(NF), *zl = zh + 2;
-                        const unsigned zhh[4] = {zh[0], zh[1], zh[0], zh[1]}, zll[4] = {zl[0], zl[1], zl[0], zl[1]};
-                        big[c] = tile_mfma<BF>(pw[c], zll, big[c]);
-                        big[c] = tile_mfma<BF>(pw[c], zhh, big[c]);
+                        const unsigned zlh[4] = {zl[0], zl[1], zh[0], zh[1]}, zhl[4] = {zh[0], zh[1], zl[0], zl[1]};
+                        big[c] = tile_mfma<BF>(pw[c], zlh, big[c]);
+                        big[c] = tile_mfma<BF>(pw[c], zhl, big[c]);
                         ordered();
                         ask_weights(std::integral_constant<int, asked(c)>(), std::integral_constant<int, asked(c + 1)>());
                         ordered();

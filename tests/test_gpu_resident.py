@@ -588,6 +588,56 @@ def test_one_utterance_a_team(pkg, H, J, V1, L, bf16, teams, extra, full):  # no
     eng.close()
 
 
+def logits_in_64_bits(model, enc, tokens, frames, count):
+    """Of every label that a decode emitted, after the labels before it."""
+    import torch
+    a = {k: torch.from_numpy(np.ascontiguousarray(v)).cuda().double() for k, v in model.arrays().items()}
+    d, B = model.dims, enc.shape[0]
+    h = [torch.zeros(B, d.H, dtype=torch.float64, device="cuda") for _ in range(d.L)]
+    c, last, out = [v.clone() for v in h], torch.full((B,), d.blank, device="cuda"), []
+    for i in range(int(count.max())):
+        x = a["emb"][last]
+        for l in range(d.L):
+            g = (x @ a[f"w_ih{l}"].t() + a[f"b_ih{l}"] + h[l] @ a[f"w_hh{l}"].t() + a[f"b_hh{l}"]).chunk(4, 1)
+            c[l] = torch.sigmoid(g[1]) * c[l] + torch.sigmoid(g[0]) * torch.tanh(g[2])
+            x = h[l] = torch.sigmoid(g[3]) * torch.tanh(c[l])
+        k, t = tokens[:, i].long().clamp(min=0), frames[:, i].long().clamp(min=0)
+        z = torch.relu(enc[torch.arange(B, device="cuda"), t].double() @ a["w_enc"].t() + a["b_enc"] + x @ a["w_pred"].t() + a["b_pred"])
+        out.append((z * a["w_out"][k]).sum(1) + a["b_out"][k])
+        last = torch.where(i < count, k, last)
+    return torch.stack(out, 1)
+
+
+# rms over 48 models of what is left where high and low parts of a half block's weights have instructions of their own.  (The same on every run;
+# 0.1 % above it is half of what the parts in one instruction cost layers of 320.)
+@pytest.mark.parametrize("H,L,bias,rms", [(128, 1, 1.2, 1.10742e-7), (320, 1, 2.0, 2.25439e-7), (320, 2, 2.0, 2.04635e-7)])
+def test_half_blocks_are_as_close_to_64_bits_as_whole_ones(pkg, H, L, bias, rms):  # noqa: F811
+    """Models with the structure of a trained transducer: a label's embedding opposes its output row, and cell and projection pass that on."""
+    import torch
+    dims, n, square = synth.ModelDims(F=256, E=H, H=H, L=L, J=H, V1=257), 0, 0.0
+    for seed in range(48):
+        r = np.random.default_rng(seed)
+        model = synth.make_model(dims, 0)
+        for v in model.arrays().values():
+            v[...] = (r.random(v.shape, dtype=np.float32) - np.float32(0.5)) * np.float32(0.2)
+        model.emb[:-1] -= np.float32(5.0) * model.w_out[:-1]
+        for l in range(L):
+            model.w_ih[l][2 * H:3 * H] += np.float32(2.0) * np.eye(H, dtype=np.float32)
+        model.w_pred[...] += np.float32(5.0) * np.eye(H, dtype=np.float32)
+        model.b_out[-1] += np.float32(bias)
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        enc = torch.randn((128, 200, dims.F), generator=g, device="cuda")
+        eng = pkg.Engine(model, 128, 200)
+        out = eng.decode("label", enc, torch.full((128,), 200, dtype=torch.int32, device="cuda"), 10)
+        want = logits_in_64_bits(model, enc, out["tokens"], out["frames"], out["tok_len"])
+        there = torch.arange(want.shape[1], device="cuda") < out["tok_len"][:, None]
+        off = (out["logits"][:, :want.shape[1]].double() - want)[there]
+        n, square = n + off.numel(), square + float((off * off).sum())
+        eng.close()
+    print(f"{H}/{L}: {n} labels, rms {np.sqrt(square / n):.5e}", flush=True)
+    assert n > 200000 and np.sqrt(square / n) <= 1.001 * rms
+
+
 # (the folded embedding table: tiles of 64 labels and 16 units, 32 values of the embedding at a time)
 @pytest.mark.parametrize("H,J,V1,E", [(64, 60, 65, 1), (68, 64, 64, 31), (60, 128, 63, 32), (316, 320, 129, 33), (644, 640, 40, 65), (20, 72, 191, 96)])
 @pytest.mark.parametrize("bf16", [False, True])
