@@ -155,6 +155,16 @@ RNNT_HD constexpr int res_z_k4(bool bf, int cls, unsigned at)
     return (int)(first + full * 8u + (bf ? in % 1024u / 128u : g));
 }
 
+// Lanes that load a vector of hidden values, a bit each: columns 0 .. 2 * rows - 1 of sixteen (column n is of row n % rows, see Operand) of the rows in
+// `active`, whose bits are 16 / rows apart: a copy of somebody else's words, or words of a row that has ended, would travel for nothing.
+RNNT_HD constexpr unsigned long long res_takers(int rows, unsigned active)
+{
+    unsigned m = active;              // to a bit a row
+    if (rows == 4) m = (m | m >> 3 | m >> 6 | m >> 9) & 0xfu;
+    else { m = (m | m >> 1) & 0x3333u; m = (m | m >> 2) & 0x0f0fu; m = (m | m >> 4) & 0xffu; }
+    return (m | m << rows) * 0x0001000100010001ull;
+}
+
 // Frames of each of n rows in a joint step of nt tiles of samples (nmt: of the instance; rows: of a team): dealt evenly, 31 for one row of two
 // tiles, so that shifts of a word by 0 to 31 do.  (Label-dense steps, one tile of two: no more than a team of all rows has, they are not looked at.)
 RNNT_HD constexpr int res_frames(int nt, int nmt, int rows, int n)

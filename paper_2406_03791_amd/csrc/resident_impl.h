@@ -436,8 +436,6 @@ struct Operand {
         const int k4 = wave * (NH * 4) + i * 8 + (i < NF ? 2 * g + other : g);
         return (unsigned)(row * (res_width(CLS) * 4)) + (unsigned)min(k4, n4 - 1) * 16u;
     }
-    // the lanes that load: a copy of somebody else's words would travel for nothing
-    static __device__ __forceinline__ bool takes(int lane, int slots) { return (lane & 15) < 2 * R && (lane & (R - 1)) < slots; }
     __device__ __forceinline__ void set(const r4u (&v)[NB], int lane)
     {
         const bool other = ((lane & 15) / R) & 1;
@@ -457,14 +455,14 @@ struct Operand {
             }
         }
     }
-    __device__ __forceinline__ void receive_from(const ResidentParams &p, RCtx &x, unsigned base, int n4)
+    __device__ __forceinline__ void receive_from(const ResidentParams &p, RCtx &x, unsigned base, int n4, unsigned long long take)       // take: res_takers
     {
         unsigned off[NB];
         r4u v[NB];
         const int lane = lane_id();
 #pragma unroll
         for (int i = 0; i < NB; ++i) off[i] = offset(i, x.wave, lane, n4);
-        receive<NB>(p, x, off, base, v, takes(lane, p.slots));
+        receive<NB>(p, x, off, base, v, __builtin_amdgcn_inverse_ballot_w64(take));
         set(v, lane);
     }
 };
@@ -1116,6 +1114,13 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     // draws; 1544, 1450 and 1348 us instead of 1470, 1412 and 1283), 19 of a multi-blank model 105, 89 and 69 instead of
     // 85, 76 and 54 (846, 760 and 602 us instead of 757, 711 and 520).
     unsigned part_rows = 0;
+    // Rows with an utterance, and the lanes that take their hidden values (res_takers): a row that has ended without another utterance never
+    // gets one, so its words stay where they are.  They are what eight rows cost a team where most have ended: one utterance of 2000 labels among
+    // 127 blank ones 16.0 ms with all rows' words, 14.2 without those of ended rows (four rows, all words 14.1), among 255 16.8 and 15.0 (14.5), bfloat16
+    // mode 14.2 and 12.1 (12.8), 19 utterances of a multi-blank model 633 and 615 us.  As a test of every lane's bit at every poll, and ended rows' words
+    // not sent either, up to 1 % longer in calls of 9 to 24 utterances.
+    unsigned active_rows = 0;
+    unsigned long long takers = 0;
     int la = 0;
     auto part_samples = [&]() { return __builtin_popcount(part_rows) * la; };
     auto lay_out = [&](auto nt_, int lane, unsigned of) {
@@ -1213,6 +1218,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
         if (got) { rows.b[r] = b; rows.s[r].len = len; }
         const unsigned long long m = __ballot(got) & LEADS;
         any_active = need_pred = m != 0ull;
+        active_rows = (unsigned)m; takers = res_takers(R, active_rows);
         row_steps = __popcll(m);
         lay_out(all_tiles, lane0, (unsigned)m);
         set_up_samples(lane0, 0, b, len);
@@ -1279,6 +1285,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             return v;
         };
         const unsigned jn = ++n_joint;
+        const unsigned long long take = ONE ? res_takers(R, 1u) : takers;
         // A wave's part of the operand, an eighth of K of a tile's samples
         constexpr int PIECES = BF ? NB : NH;
         r4u zw[PIECES];
@@ -1392,13 +1399,13 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     later = false;
                 }
                 RES_MARK(1);
-                x1.receive_from(p, x, bo.h[0] + slot_at(n, VSLOT), h4);
+                x1.receive_from(p, x, bo.h[0] + slot_at(n, VSLOT), h4, take);
             } else {
                 // The work-group's columns of the joint step's frames, by the waves that have the least to do here.  A wave's loads return in
                 // order, so these waves see the hidden vector when their frames are there: at about the time it comes.
                 load_frames((x.wave - 5) * (64 / ZS), true);
                 if constexpr (FRAMES_FIRST) __builtin_amdgcn_s_setprio(0);
-                x1.receive_from(p, x, bo.h[0] + slot_at(n, VSLOT), h4);
+                x1.receive_from(p, x, bo.h[0] + slot_at(n, VSLOT), h4, take);
 #pragma unroll
                 for (int e = 0; e < GL; ++e)
                     asm volatile("" :: "v"(t0.g[e]), "v"(pre[0][0][e]), "v"(pre[0][1][e]), "v"(pre[0][2][e]), "v"(pre[0][3][e]));
@@ -1444,14 +1451,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                         unsigned off[NB];
                         const int lane = lane_id();
                         places(off, lane);
-                        request<NB>(x, off, bo.h[1] + slot_at(n, VSLOT), v, Op::takes(lane, p.slots));
+                        request<NB>(x, off, bo.h[1] + slot_at(n, VSLOT), v, __builtin_amdgcn_inverse_ballot_w64(take));
                         ordered();
                     });
                     RES_MARK(5);
                     unsigned off[NB];
                     const int lane = lane_id();
                     places(off, lane);
-                    receive_rest<NB>(p, x, off, bo.h[1] + slot_at(n, VSLOT), v, Op::takes(lane, p.slots));
+                    receive_rest<NB>(p, x, off, bo.h[1] + slot_at(n, VSLOT), v, __builtin_amdgcn_inverse_ballot_w64(take));
                     x1.set(v, lane);
                 } else {
                     RES_MARK(5);
@@ -1461,7 +1468,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     // Narrower classes, calls of 1 to 96 utterances of 320 or 128 units, 65 to 170 us: 48 of 320 units 1.2 % shorter with it, the others
                     // within 0.4 %.  Pauses before the other polls: no gain, there is work in between.)
                     __builtin_amdgcn_s_sleep(5);
-                    x1.receive_from(p, x, bo.h[1] + slot_at(n, VSLOT), h4);
+                    x1.receive_from(p, x, bo.h[1] + slot_at(n, VSLOT), h4, take);
                     if (PAIR) forward_h(1);
                 }
             }
@@ -2044,6 +2051,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             const unsigned active = (unsigned)(__ballot(w.t < w.len) & LEADS);
             const unsigned moved = (unsigned)__ballot((lane_const & (kTake | kFresh)) != 0) & active;      // rows whose next step has new inputs
             any_active = active != 0u;
+            if (active != active_rows) { active_rows = active; takers = res_takers(R, active); }
             const int n_moved = __builtin_popcount(moved), n_search = __builtin_popcount(active) - n_moved;
             // The next step is a prediction step if a row has new inputs, unless half as many or more are still looking for
             // their label: then these have the next joint step, and all its samples, to themselves, at 4 us instead of 8 (two-layer fp32

@@ -220,6 +220,17 @@ int main()
     for (unsigned polls : {0u, 1u, kStreamingWait, kResidentWait, 0xffffffffu})
         for (unsigned by_default : {kStreamingWait, kResidentWait})
             if (wait_polls(polls, by_default) != polls || wait_polls(-1, by_default) != by_default) { std::printf("wait limit\n"); return 1; }
+    // lanes that load hidden values: those of the rows with an utterance, every set of them
+    for (const int rows : {4, 8})
+        for (unsigned set = 0; set < 1u << rows; ++set) {
+            unsigned active = 0;
+            for (int r = 0; r < rows; ++r) active |= (set >> r & 1u) << (r * 16 / rows);
+            for (int lane = 0; lane < 64; ++lane)
+                if ((res_takers(rows, active) >> lane & 1u) != ((lane & 15) < 2 * rows ? set >> (lane & (rows - 1)) & 1u : 0u)) {
+                    std::printf("lane %d of %d rows, %x active\n", lane, rows, set);
+                    return 1;
+                }
+        }
     // samples of a joint step: the rows' places, and shifts of a word by RB bits a place for every sample, also beyond the rows'
     for (const auto &[nt, nmt, rows] : {std::array{2, 2, 8}, std::array{1, 2, 8}, std::array{2, 2, 4}, std::array{1, 2, 4}, std::array{1, 1, 4}})
         for (int n = 0; n <= rows; ++n) {
