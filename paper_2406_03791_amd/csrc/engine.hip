@@ -636,13 +636,19 @@ void resident_rows(const ResidentPlan &pl, int nb, int T, int *slots, int *la)
     // 998, 48 1087 and 1014, multi-blank 42 760 and 810, 48 868 and 865; bfloat16 mode, eight teams, 56 1152 and 1091, 64 1228 and 1158,
     // e4m3 TDT 57 635 and 661, 64 670 and 661, 72 770 and 737; one layer 48 1148 and 1078, 64 1416 and 1231; small, 16 teams, 96 563 and 529, 128 683 and 567.
     // Of short utterances the last ones of a list are most of a call, and a joint step that has four frames of every row comes too early for
-    // a label: lists of a few hundred frames stay with four rows.  Means of ten draws, utterances x frames: two-layer fp32 models 48 x 20 172 and
-    // 187, 73 x 31 242 and 239, 56 x 60 326 and 331, 64 x 60 387 and 358, TDT 143 and 155, 201 and 206, (99 x 22) 234 and 227, 287 and 291, multi-blank
-    // 50 x 20 180 and 201, 73 x 31 267 and 274, 56 x 100 530 and 476; bfloat16 mode 64 x 20 155 and 159, 64 x 30 188 and 193, e4m3 72 x 60
-    // 232 and 233; one layer 64 x 20 158 and 160, 72 x 60 319 and 285, small 128 x 30 159 and 149.
-    // (What loses by eight rows is a batch whose time is that of one utterance, which the host cannot see: one with ten labels on each of 200 frames among 127 of
-    // blanks 13.9 and 16.0 ms.  Where all are like that, 87.9 and 52.9.)
-    const bool long_lists = (long long)nb * T >= (long long)pl.n_teams * (pl.kind == kResident1 ? 200 : 400);
+    // a label: lists of a few hundred frames stay with four rows.  Four rows and eight, us a call with lists of 8 and, behind the semicolon, of 11 utterances of T/3 to
+    // T frames, means of eight draws ([T times a list's utterances]): two-layer fp32 models of 640 units [240] 223 and 240, [360] 273 and 288, [560] 381 and 375; [330] 258 and
+    // 270, [495] 335 and 327; TDT [240] 140 and 148, [360] 190 and 180; [330] 163 and 164; multi-blank [240] 173 and 187, [360] 235 and 235; bfloat16 mode [360] 226 and 238,
+    // [560] 297 and 287; [330] 222 and 228, [495] 285 and 263, TDT with e4m3 weights [360] 146 and 148, [560] 182 and 180; two layers of 320 [360] 243 and 254, [560] 336 and
+    // 320; [330] 231 and 229, [495] 310 and 288, bfloat16 mode [360] 204 and 206, [560] 282 and 273; [330] 189 and 192, [495] 255 and 234; two layers of 128 [200] 159 and 170, [240] 176 and
+    // 173; [220] 168 and 163, bfloat16 mode [160] 118 and 117, [240] 157 and 147.  One layer: 640 units [160] 155 and 151; [220] 174 and 162, bfloat16 mode [160] 116 and 116;
+    // [330] 156 and 149, 320 units [160] 134 and 137, [240] 152 and 150; [220] 157 and 157, bfloat16 mode [160] 108 and 107, 128 units [80] 99 and 99, [160] 128 and 123, bfloat16 mode
+    // [160] 112 and 105.
+    // (T is what a call's frames are padded to, the lengths are on the device.  What loses by eight rows is short utterances in long rows, 48 to 66 of 10 to 30 frames in a
+    // T of hundreds the most, 3 to 9 %, 5 to 17 us.  With a launch of either kind, of which the device lets one end at once, every such call is 3 us longer, and 20 in
+    // a capture; with both loops in one kernel weights are spilled, and the calls take up to 2.3 % longer.  And a batch whose time is that of one utterance: one
+    // of 2000 labels on 200 frames among 127 of blanks 14.1 and 14.2 ms, among 255 14.5 and 15.1.  Where all are like that, 88 and 53.)
+    const bool long_lists = (long long)nb * T >= (long long)pl.n_teams * (pl.kind == kResident1 ? 200 : pl.cls == 2 ? 240 : 400);
     *slots = nb >= kResRows * pl.n_teams && long_lists ? kResRows : std::min(4, (nb + pl.n_teams - 1) / pl.n_teams);
     *la = *slots <= 2 ? 16 / *slots : kResSamples / *slots;
     *la = std::min(*la, 16);
