@@ -527,9 +527,10 @@ def test_tails_of_steps_with_two_tiles(pkg, H, J, V1, L, teams, durations, bf16,
 
 
 # (bfloat16 mode: no layers of 640.  Its margin, 2e-2, is about twice what a step of bfloat16, 2^-8 of a value, makes of logits of up to 3
-# at a time; those of 332 reach 9 with these inputs, those of 640 reach 19.)
+# at a time; those of 332 reach 9 with these inputs, those of 640 reach 19.)  Every kind and precision in every size class.
 EIGHT = [(64, 68, 60, 1, False, 32), (128, 128, 257, 2, True, 32), (316, 320, 529, 1, False, 8), (320, 316, 500, 1, True, 16),
-         (100, 128, 250, 2, False, 24), (324, 332, 1040, 2, False, 6), (324, 332, 1040, 2, True, 8), (640, 636, 1025, 1, False, 8)]
+         (100, 128, 250, 2, False, 24), (324, 332, 1040, 2, False, 6), (324, 332, 1040, 2, True, 8), (640, 636, 1025, 1, False, 8),
+         (324, 332, 1040, 1, True, 8), (128, 124, 257, 1, True, 32), (320, 316, 500, 2, True, 16), (316, 320, 500, 2, False, 12)]
 
 
 @pytest.mark.parametrize("H,J,V1,L,bf16,teams", EIGHT)
@@ -557,12 +558,19 @@ def test_eight_rows_a_team(pkg, H, J, V1, L, bf16, teams, extra, more):  # noqa:
     eng.close()
 
 
-# (teams of the three size classes, as in EIGHT)
-ONE = [(64, 68, 60, 1, False, 32), (128, 128, 257, 2, True, 32), (316, 320, 529, 1, False, 8), (320, 316, 500, 1, True, 16), (100, 128, 250, 2, False, 24),
-       (324, 332, 1040, 2, False, 6), (324, 332, 1040, 2, True, 8), (640, 636, 1025, 1, False, 8)]
+# frames of a list (padded ones, as the host counts) from which on eight rows are worth it
+@pytest.mark.parametrize("H,J,V1,L,bf16,teams,frames", [(64, 68, 60, 1, False, 32, 200), (324, 332, 1040, 1, True, 8, 200), (100, 128, 250, 2, False, 24, 240),
+                                                        (128, 128, 257, 2, True, 32, 240), (320, 320, 500, 2, False, 12, 400), (324, 332, 1040, 2, True, 8, 400)])
+def test_short_lists_stay_with_four_rows(pkg, H, J, V1, L, bf16, teams, frames):  # noqa: F811
+    for T in (frames // 8 - 1, frames // 8):
+        w = model_inputs(H, J, V1, L, B=8 * teams, T=T, seed=H + T)
+        eng = pkg.Engine(w.model, w.B, w.T, flags=pkg.RNNT_FLAG_BF16_ARITHMETIC if bf16 else 0)
+        _, _, stats = check(pkg, w, "label", f"short lists {H}/{J}/{V1}/{L} bf16={bf16} {T}", engine=eng, bf16=bf16, logp=not bf16)
+        assert stats["n_teams"] == teams and stats["lookahead"] == (4 if 8 * T >= frames else 8)
+        eng.close()
 
 
-@pytest.mark.parametrize("H,J,V1,L,bf16,teams", ONE)
+@pytest.mark.parametrize("H,J,V1,L,bf16,teams", EIGHT)
 @pytest.mark.parametrize("extra", [{}, dict(durations=(0, 1, 3, 90)), dict(big_blanks=(2, 17, 70))])
 @pytest.mark.parametrize("full", [False, True])
 def test_one_utterance_a_team(pkg, H, J, V1, L, bf16, teams, extra, full):  # noqa: F811
