@@ -15,11 +15,12 @@ inline bool solo_holds(int H, int J, int L, int NOUT, bool bf)
 {
     return !bf && L == 1 && H <= kSoloWidth && J <= kSoloWidth && NOUT <= kSoloOutputs;
 }
-// A single token behind the tiles of 16 that the others fill (sixteen or 32 labels and a blank, no durations) is not worth a tile of
-// its own: its products are four multiply-adds a lane beside the matrix instructions (17 outputs, a call of 20 frames and 45 steps:
-// 64.1 us with two tiles, 60.7 with one and the output behind it).
-RNNT_HD constexpr bool solo_last(int NOUT, int VT) { return VT == NOUT && (NOUT == 17 || NOUT == 33); }
-RNNT_HD constexpr int solo_tiles(int NOUT, int VT) { return solo_last(NOUT, VT) ? NOUT / 16 : NOUT <= 32 ? 2 : 4; }        // of 16 outputs
+// Tiles of 16 outputs, as many as it takes, but for a single token behind full ones (labels and a blank, no durations behind it): its products are
+// four multiply-adds a lane beside the matrix instructions instead of a tile of its own (17 outputs, a call of 20 frames and 45 steps:
+// 64.1 us with two tiles, 60.7 with one and the output behind it).  As many as it takes: 128 utterances of 16 outputs 27.7 us with two tiles, 26.1 with one, of
+// 48 outputs 42.9 with four and 40.5 with three, of 49 31.2 with four, 30.3 with three and one output.
+RNNT_HD constexpr bool solo_last(int NOUT, int VT) { return VT == NOUT && NOUT > 16 && NOUT % 16 == 1; }
+RNNT_HD constexpr int solo_tiles(int NOUT, int VT) { return (NOUT - (solo_last(NOUT, VT) ? 1 : 0) + 15) / 16; }
 // Weights as the threads take them, four values each, [part][thread of 256]: sixteen parts of the recurrent
 // matrix, four of the projection, a tile of outputs each, and the output behind the tiles.
 RNNT_HD constexpr int solo_parts(int NOUT, int VT) { return 16 + 4 + solo_tiles(NOUT, VT) + (solo_last(NOUT, VT) ? 1 : 0); }

@@ -292,7 +292,7 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
             __syncthreads();
             if (chain) {
                 // sixteen lanes per frame, TILES outputs each
-                typedef float Outs __attribute__((ext_vector_type(TILES)));
+                struct __align__(TILES % 2 ? 4 : 4 * TILES) Outs { float of[TILES]; };
                 const int s = t256 >> 4, l = lane & 15, first = l * TILES;
                 Outs o[4];
 #pragma unroll
@@ -300,7 +300,7 @@ __global__ void __launch_bounds__(kSoloThreads) solo_kernel(const SoloParams p)
                 float v[TILES], mine = -INFINITY;
 #pragma unroll
                 for (int i = 0; i < TILES; ++i) {
-                    v[i] = ((o[0][i] + o[1][i]) + (o[2][i] + o[3][i])) + b_out[i];
+                    v[i] = ((o[0].of[i] + o[1].of[i]) + (o[2].of[i] + o[3].of[i])) + b_out[i];
                     mine = fmaxf(mine, first + i < p.VT ? v[i] : -INFINITY);
                 }
                 const float last_v = LAST ? sum16(lds[lo.last + s * kSoloLastRow + l]) + b_last : -INFINITY;
@@ -435,12 +435,17 @@ hipError_t launch_solo(const SoloParams &p, bool plain, hipStream_t stream, hipE
         return walk ? launch_tiles<decltype(tiles)::value, decltype(last)::value, true>(p, plain, stream, end)
                     : launch_tiles<decltype(tiles)::value, decltype(last)::value, false>(p, plain, stream, end);
     };
-    typedef std::integral_constant<int, 1> One;
-    typedef std::integral_constant<int, 2> Two;
-    typedef std::integral_constant<int, 4> Four;
+    std::integral_constant<int, 1> one;
+    std::integral_constant<int, 2> two;
+    std::integral_constant<int, 3> three;
     const int tiles = solo_tiles(p.NOUT, p.VT);
-    if (solo_last(p.NOUT, p.VT)) return tiles == 1 ? launch(One(), std::true_type()) : launch(Two(), std::true_type());
-    return tiles == 2 ? launch(Two(), std::false_type()) : launch(Four(), std::false_type());
+    if (solo_last(p.NOUT, p.VT)) return tiles == 1 ? launch(one, std::true_type()) : tiles == 2 ? launch(two, std::true_type()) : launch(three, std::true_type());
+    switch (tiles) {
+    case 1: return launch(one, std::false_type());
+    case 2: return launch(two, std::false_type());
+    case 3: return launch(three, std::false_type());
+    default: return launch(std::integral_constant<int, 4>(), std::false_type());
+    }
 }
 
 }  // namespace rnnt

@@ -5,8 +5,8 @@
 // do and checks that every (col, k) of the matrix turns up exactly once, at the place the
 // plan says, and that everything else is zero.  Also checks e4m3_bits on all 256 codes, the
 // row-scaled e4m3 and block-scaled e2m1 forms (exponent rules, rounding, packed codes), the split of the joint
-// output stage into an MFMA part and tail columns, the samples of a joint step and the places of its operand, and which rows of the projected
-// frames are asked for ahead.
+// output stage into an MFMA part and tail columns, the samples of a joint step and the places of its operand, the tiles
+// of the smallest models, and which rows of the projected frames are asked for ahead.
 #include <array>
 #include <cstdio>
 #include <cstdlib>
@@ -14,6 +14,7 @@
 
 #include "pack.h"
 #include "resident.h"
+#include "solo.h"
 
 using namespace rnnt;
 
@@ -220,6 +221,17 @@ int main()
     for (unsigned polls : {0u, 1u, kStreamingWait, kResidentWait, 0xffffffffu})
         for (unsigned by_default : {kStreamingWait, kResidentWait})
             if (wait_polls(polls, by_default) != polls || wait_polls(-1, by_default) != by_default) { std::printf("wait limit\n"); return 1; }
+    // outputs of the smallest models: no tile without one, and one behind the tiles only where a tile of its own would be for it alone
+    for (int n = 1; n <= kSoloOutputs; ++n)
+        for (int tokens = std::max(1, n - kMaxDur); tokens <= n; ++tokens) {
+            const int tiles = solo_tiles(n, tokens), last = solo_last(n, tokens) ? 1 : 0;
+            if (tiles < 1 || tiles > 4 || tiles * 16 + last < n || (tiles - 1) * 16 + last >= n || last != (n > 16 && n % 16 == 1 && tokens == n) ||
+                solo_parts(n, tokens) != 20 + tiles + last || (last && n != tiles * 16 + 1)) {
+                std::printf("tiles of %d outputs, %d tokens\n", n, tokens);
+                return 1;
+            }
+            ++checked;
+        }
     // lanes that load hidden values: those of the rows with an utterance, every set of them
     for (const int rows : {4, 8})
         for (unsigned set = 0; set < 1u << rows; ++set) {
