@@ -22,12 +22,6 @@ struct StageDev {
     long long rank_stride; // float4 elements per rank
 };
 
-// Slots of the per-team statistics record.  The first team's also keeps the times of a call in the
-// resident kernel (100 MHz clock), written by the kernels: three events on the stream cost 9 us a call.
-enum { kStatPred = 0, kStatJoint = 1, kStatSamples = 2, kStatPolls = 3, kStatCounters = 4,
-       kStatCallStart = 4, kStatDecodeStart = 5, kStatDecodeEnd = 6, kStatCount = 8,
-       kStatProf = 24, kStatStride = kStatCount + kStatProf };
-
 struct DecodeParams {
     int F, E, H, L, J, V1, D, blank, NOUT;
     int VT;                 // output columns of the token distribution: V1, plus the big blanks of a multi-blank model

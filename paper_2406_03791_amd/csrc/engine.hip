@@ -62,9 +62,9 @@ constexpr int kStaticLds = 3072;        // kept free for the kernel's static LDS
 // projected frames and the team workspace of one call.  One copy per device, held until the
 // process ends.  In host code this name is only a handle for hipGetSymbolAddress: the address
 // kernels and copies use is the one that call returns (rnnt_engine::scratch).
-// Behind RNNT_NOALLOC_SCRATCH_BYTES there is room for what calls take beyond what they are charged (charged_bytes), 17.1 MB at most;
-// kScratchTop: and for the words on a call's P, which every call finds as the last one left them.
-constexpr size_t kScratchTop = RNNT_NOALLOC_SCRATCH_BYTES + (20u << 20);
+// Behind RNNT_NOALLOC_SCRATCH_BYTES there is room for what calls take beyond what they are charged (charged_bytes), kScratchBeyond;
+// at kScratchTop: and for the words on a call's P, which every call finds as the last one left them.
+constexpr size_t kScratchTop = RNNT_NOALLOC_SCRATCH_BYTES + kScratchBeyond;
 static __device__ __align__(256) unsigned char scratch[kScratchTop + top_words(kLaunchRows) * sizeof(TopWord)];
 
 struct DevBuf {
@@ -558,19 +558,6 @@ EncWeights enc_weights(const rnnt_engine *e)
 }
 
 // ---- resident decode kernel ---------------------------------------------------------------
-// What a call of the entry point that allocates nothing is charged of RNNT_NOALLOC_SCRATCH_BYTES, for P and its workspace.  Which
-// calls are refused is part of the interface, so this stays as it was when every kind had buffers of two recurrent
-// vectors and one sum a unit, two-layer fp32 models five teams where they have six, and the smallest models teams as well.
-size_t charged_bytes(const ResidentPlan &pl, size_t p_bytes)
-{
-    auto sized = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
-    const size_t w = res_width(pl.cls), ts = res_team(pl.cls);
-    const size_t chain = kResSlots * (5 * 4 * w * 4 + kResSamples * (ts * 12 + kMaxDur * 4)), sums = 2 * kResSlots * ts * 5 * 64 * 4;
-    const size_t teams = pl.solo ? pl.n_teams / res_team(pl.cls) : pl.kind == kResident2Pair ? pl.n_teams - pl.n_teams / 6 : pl.n_teams;
-    return sized(p_bytes) + sized((chain + sums) * teams) + sized((size_t)pl.n_xcd * 32 * sizeof(unsigned)) +
-           sized(teams * kStatStride * sizeof(long long)) + sized(sizeof(unsigned)) + sized(sizeof(int));
-}
-
 Workspace resident_workspace(const rnnt_engine *e)
 {
     Workspace w;
@@ -619,7 +606,7 @@ int make_resident(rnnt_engine *e, const rnnt_model_desc &d)
     // (infinite or undefined weights have no fp16 parts: such a model is left to the other kernel)
     if (found[0]) { e->res.kind = kResidentNone; return RNNT_OK; }
     std::memcpy(&e->res_q_bound, &found[1], sizeof(float));
-    HIP_TRY(e->res_xbuf.alloc((size_t)resident_buf(pl.kind, bf, pl.cls, kResRows).bytes * pl.n_teams));
+    HIP_TRY(e->res_xbuf.alloc(exchange_bytes(pl, e->max_B)));
     HIP_TRY(e->res_form.alloc((size_t)pl.n_xcd * 32 * sizeof(unsigned)));
     HIP_TRY(e->res_stats.alloc((size_t)pl.n_teams * kStatStride * sizeof(long long)));
     HIP_TRY(hipMemset(e->res_form.p, 0, (size_t)pl.n_xcd * 32 * sizeof(unsigned)));
@@ -1237,22 +1224,17 @@ int rnnt_label_looping_decode_noalloc(rnnt_engine *eng, const float *enc_out, co
     if (!eng->use_streaming) {
         if (B > kLaunchRows) return RNNT_ERR_SCRATCH;
         const ResidentPlan &pl = eng->res;
-        size_t off = 0;
-        auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
-        const size_t o_P = take((size_t)B * T * eng->d.J * sizeof(float));
-        const size_t o_x = take(pl.solo ? 0 : (size_t)resident_buf(pl.kind, pl.bf != 0, pl.cls, kResRows).bytes * pl.n_teams);
-        const size_t o_f = take((size_t)pl.n_xcd * 32 * sizeof(unsigned));
-        const size_t o_s = take((size_t)pl.n_teams * kStatStride * sizeof(long long));
-        const size_t o_a = take(sizeof(unsigned)), o_st = take(sizeof(int));
-        if (charged_bytes(pl, (size_t)B * T * eng->d.J * sizeof(float)) > RNNT_NOALLOC_SCRATCH_BYTES || off > kScratchTop) return RNNT_ERR_SCRATCH;
+        const size_t p_bytes = (size_t)B * T * eng->d.J * sizeof(float);
+        const NoallocLayout at = noalloc_layout(pl, p_bytes, B);
+        if (charged_bytes(pl, p_bytes) > RNNT_NOALLOC_SCRATCH_BYTES || at.bytes > kScratchTop) return RNNT_ERR_SCRATCH;
         unsigned char *base = static_cast<unsigned char *>(eng->scratch);
         Workspace ws;
-        ws.P = reinterpret_cast<float *>(base + o_P);
-        ws.xbuf = base + o_x;
-        ws.form = reinterpret_cast<unsigned *>(base + o_f);
-        ws.stats = reinterpret_cast<long long *>(base + o_s);
-        ws.abort_flag = reinterpret_cast<unsigned *>(base + o_a);
-        ws.status = reinterpret_cast<int *>(base + o_st);
+        ws.P = reinterpret_cast<float *>(base + at.P);
+        ws.xbuf = base + at.xbuf;
+        ws.form = reinterpret_cast<unsigned *>(base + at.form);
+        ws.stats = reinterpret_cast<long long *>(base + at.stats);
+        ws.abort_flag = reinterpret_cast<unsigned *>(base + at.abort_flag);
+        ws.status = reinterpret_cast<int *>(base + at.status);
         ws.top = reinterpret_cast<TopWord *>(base + kScratchTop);
         return run_decode(eng, kLabelLooping, enc_out, enc_len, B, T, max_symbols, tokens_out, tok_len_out, cap, frames_out,
                           logit_out, nullptr, static_cast<hipStream_t>(stream), &ws);

@@ -18,6 +18,12 @@
 
 namespace rnnt {
 
+// Slots of the per-team statistics record.  The first team's also keeps the times of a call in the
+// resident kernel (100 MHz clock), written by the kernels: three events on the stream cost 9 us a call.
+enum { kStatPred = 0, kStatJoint = 1, kStatSamples = 2, kStatPolls = 3, kStatCounters = 4,
+       kStatCallStart = 4, kStatDecodeStart = 5, kStatDecodeEnd = 6, kStatCount = 8,
+       kStatProf = 24, kStatStride = kStatCount + kStatProf };
+
 constexpr int kThreads = 512;        // threads per work-group (8 wavefronts, 2 per SIMD)
 constexpr int kWaves = kThreads / 64;
 constexpr int kBlocksPerWg = kWaves * 16;   // 4-lane MFMA blocks per work-group

@@ -1,4 +1,4 @@
-// Host side of the resident decode kernel: which models fit it.  No device code and no HIP calls.
+// Host side of the resident decode kernel: which models fit it, and the memory of a call.  No device code and no HIP calls.
 #pragma once
 #include <algorithm>
 
@@ -31,6 +31,42 @@ inline ResidentPlan plan_resident(int H, int J, int L, int NOUT, bool bf, int n_
         return pl;
     }
     return pl;
+}
+
+// The teams' exchange buffers for calls of up to B utterances.  Teams have eight rows only where every list has eight utterances (resident_rows), and their
+// buffers are up to twice those of four: an engine of two layers of 640 in fp32 for one utterance keeps 11 MB of them, for 48 and more 20.
+inline size_t exchange_bytes(const ResidentPlan &pl, int B)
+{
+    if (pl.solo) return 0;
+    return (size_t)resident_buf(pl.kind, pl.bf != 0, pl.cls, B >= kResRows * pl.n_teams ? kResRows : 4).bytes * pl.n_teams;
+}
+
+// What a call of the entry point that allocates nothing is charged of RNNT_NOALLOC_SCRATCH_BYTES, for P and its workspace.  Which
+// calls are refused is part of the interface, so this stays as it was when every kind had buffers of two recurrent
+// vectors and one sum a unit, two-layer fp32 models five teams where they have six, and the smallest models teams as well.
+inline size_t sized(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+inline size_t charged_bytes(const ResidentPlan &pl, size_t p_bytes)
+{
+    const size_t w = res_width(pl.cls), ts = res_team(pl.cls);
+    const size_t chain = kResSlots * (5 * 4 * w * 4 + kResSamples * (ts * 12 + kMaxDur * 4)), sums = 2 * kResSlots * ts * 5 * 64 * 4;
+    const size_t teams = pl.solo ? pl.n_teams / res_team(pl.cls) : pl.kind == kResident2Pair ? pl.n_teams - pl.n_teams / 6 : pl.n_teams;
+    return sized(p_bytes) + sized((chain + sums) * teams) + sized((size_t)pl.n_xcd * 32 * sizeof(unsigned)) +
+           sized(teams * kStatStride * sizeof(long long)) + sized(sizeof(unsigned)) + sized(sizeof(int));
+}
+// Where it has them, every part 256-byte aligned.  Behind what is charged there is room for kScratchBeyond bytes more.
+constexpr size_t kScratchBeyond = 20u << 20;
+struct NoallocLayout { size_t P, xbuf, form, stats, abort_flag, status, bytes; };
+inline NoallocLayout noalloc_layout(const ResidentPlan &pl, size_t p_bytes, int B)
+{
+    NoallocLayout l{};
+    auto take = [&](size_t bytes) { const size_t at = l.bytes; l.bytes += sized(bytes); return at; };
+    l.P = take(p_bytes);
+    l.xbuf = take(exchange_bytes(pl, B));
+    l.form = take((size_t)pl.n_xcd * 32 * sizeof(unsigned));
+    l.stats = take((size_t)pl.n_teams * kStatStride * sizeof(long long));
+    l.abort_flag = take(sizeof(unsigned));
+    l.status = take(sizeof(int));
+    return l;
 }
 
 }  // namespace rnnt

@@ -6,7 +6,7 @@
 // plan says, and that everything else is zero.  Also checks e4m3_bits on all 256 codes, the
 // row-scaled e4m3 and block-scaled e2m1 forms (exponent rules, rounding, packed codes), the split of the joint
 // output stage into an MFMA part and tail columns, the samples of a joint step and the places of its operand, the tiles
-// of the smallest models, and which rows of the projected frames are asked for ahead.
+// of the smallest models, the memory of calls, and which rows of the projected frames are asked for ahead.
 #include <array>
 #include <cstdio>
 #include <cstdlib>
@@ -14,6 +14,7 @@
 
 #include "pack.h"
 #include "resident.h"
+#include "resident_pack.h"
 #include "solo.h"
 
 using namespace rnnt;
@@ -221,6 +222,27 @@ int main()
     for (unsigned polls : {0u, 1u, kStreamingWait, kResidentWait, 0xffffffffu})
         for (unsigned by_default : {kStreamingWait, kResidentWait})
             if (wait_polls(polls, by_default) != polls || wait_polls(-1, by_default) != by_default) { std::printf("wait limit\n"); return 1; }
+    // memory of calls: an engine keeps buffers of eight rows only if it is for as many utterances, and whatever plan and batch, what a call takes beyond
+    // what it is charged has its place (calls of up to 128 utterances)
+    size_t beyond = 0, one = 0, many = 0;
+    for (const int n_cu : {32, 64, 128, 224, 256})
+        for (const bool bf : {false, true})
+            for (int L = 1; L <= 2; ++L)
+                for (const int width : {4, 64, 68, 128, 132, 320, 324, 640})
+                    for (const int outputs : {17, 256, 1025}) {
+                        const ResidentPlan pl = plan_resident(width, width, L, outputs, bf, n_cu);
+                        if (pl.kind == kResidentNone) continue;
+                        const size_t four = pl.solo ? 0 : (size_t)resident_buf(pl.kind, bf, pl.cls, 4).bytes * pl.n_teams;
+                        for (int B = 1; B <= 128; ++B) {
+                            const NoallocLayout l = noalloc_layout(pl, 0, B);
+                            const size_t charged = charged_bytes(pl, 0), exchange = exchange_bytes(pl, B);
+                            if (l.bytes > charged) beyond = std::max(beyond, l.bytes - charged);
+                            if (B < 8 * pl.n_teams ? exchange != four : exchange < four || (!pl.solo && exchange == four)) { std::printf("exchange %d\n", B); return 1; }
+                            ++checked;
+                        }
+                        if (n_cu == 256 && width == 640 && L == 2 && !bf) { one = exchange_bytes(pl, 1); many = exchange_bytes(pl, 128); }
+                    }
+    if (beyond > kScratchBeyond || beyond < kScratchBeyond * 3 / 4 || one > (11u << 20) || many > (20u << 20)) { std::printf("scratch %zu, %zu, %zu\n", beyond, one, many); return 1; }
     // outputs of the smallest models: no tile without one, and one behind the tiles only where a tile of its own would be for it alone
     for (int n = 1; n <= kSoloOutputs; ++n)
         for (int tokens = std::max(1, n - kMaxDur); tokens <= n; ++tokens) {
