@@ -323,8 +323,9 @@ int rnnt_quantize_blocks_e2m1(const float *w, int64_t rows, int64_t cols, float 
  * the device (fewer joint groups, then more teams, then fewer) before it
  * refuses.
  * Device memory of an engine: the projected frames (max_B * max_T * J floats)
- * and a packed copy of the weights and a few megabytes of workspace, 40 MB
- * for the Parakeet shape in fp32; of the streaming kernel one copy per team
+ * and a packed copy of the weights, tables and workspace, 63 MB for the
+ * Parakeet shape in fp32 and 72 MB from 48 utterances on (more rows are in
+ * work at a time then); of the streaming kernel one copy per team
  * layout (up to eleven, see rnnt_engine_configure), about 0.4 GB.
  * Synchronous.  *out is set only on success.
  */
@@ -380,7 +381,7 @@ int rnnt_label_looping_decode(rnnt_engine *eng, const float *enc_out, const int3
  * workspace but from one array that the library holds as a static device
  * object on every device it runs on, until the process ends:
  * RNNT_NOALLOC_SCRATCH_BYTES bytes that calls are measured against, and some
- * 8 MiB more that the library keeps for itself.  The entry point calls no
+ * 20 MiB more that the library keeps for itself.  The entry point calls no
  * hipMalloc, hipFree or other allocating routine; the engine (its packed
  * weights) is created beforehand.  A call that is charged more (roughly
  * B * T * J * 4 bytes plus 9 MiB at the Parakeet shape), or one of more than
