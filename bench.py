@@ -27,10 +27,10 @@ HBM_PEAK_GBS = 8000.0
 # Phase timers of a profile build (rnnt_engine_phase_timers), in the order of their slots: of the kernel
 # with register-resident weights, which runs the models measured here, and of the streaming one (--streaming).
 PHASES = ["pred: helpers' results", "pred: layer-0 cell, published", "pred: layer-0 vector received", "pred: input stage of layer 1",
-          "pred: layer-1 cell, published", "pred: recurrent stage of layer 0", "pred: layer-1 vector received",
+          "pred: helpers' results of layer 1", "pred: layer-1 cell, published", "pred: recurrent stage of layer 0", "pred: layer-1 vector received",
           "pred: projection stage, operand published", "pred: recurrent stage of the top layer", "joint: operand received",
-          "joint: operand published (no new label)", "joint: output stage", "joint: sums, argmax published", "joint: keys received",
-          "joint: result shared (work-group barrier)", "control: hops, labels emitted, next samples"]
+          "joint: operand published (no new label)", "joint: output stage", "joint: work-group barrier behind it", "joint: sums, argmax published",
+          "joint: keys received", "joint: result shared (work-group barrier)", "control: hops, labels emitted, next samples"]
 STREAMING_PHASES = ["pred: stage-0 input filled (general)", "pred: recurrent stage of all layers",
                     "pred: layer-0 cell and store", "pred: barrier (general)",
                     "pred: hidden vectors of the layer below received", "pred: input stage of a layer",

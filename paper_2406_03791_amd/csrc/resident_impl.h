@@ -19,7 +19,8 @@
 //
 // A team decodes four utterances at a time, or eight where its list has as many (resident_rows): two parts of eight rows are the sixteen
 // columns that the matrix instructions of the LSTM stages and the projection have in any case, so a prediction step of eight takes 0.4 us more
-// than one of four; four frames of every row in a joint step where there were eight, but 128 utterances take 400 joint steps instead of 522.
+// than one of four; four frames of every row in a joint step where there were eight, but the longest of six teams of 128 utterances takes 433 joint steps instead
+// of 567 (200 to 500 frames, the sweep's draw).
 //
 // The joint's operand z = relu(P + q) is formed once in the team: every work-group has its own columns of the projection, adds
 // those of the samples' frames (80 bytes a sample) and hands z on in q's place.  Formed from q by every work-group for itself it took
@@ -573,7 +574,7 @@ __device__ __forceinline__ void cell(const RGates<R> &pre, int j, float c_old, f
 constexpr int kTake = 1 << 30, kFresh = (int)(1u << 31);
 
 // fp32: the power of two that takes the bound max P + max q of an utterance to 2^14 .. 2^15, which its operands of the
-// joint step, and its q as it travels, are multiplied by.  (Of infinite values of P the finite ones count.)
+// joint step, as they travel, are multiplied by.  (Of infinite values of P the finite ones count.)
 __device__ __forceinline__ float joint_scale(TopWord top, float q_bound)
 {
     const float bound = fminf(__uint_as_float((unsigned)top << 16) + q_bound, kResHuge);
@@ -644,7 +645,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
     constexpr int NREC = PAIR ? 0 : NL;          // recurrent matrices the chain's work-groups hold
     constexpr ResidentBuf bo = resident_buf(KIND, BF, CLS, R);
     constexpr ResidentLds lo = resident_lds(KIND, BF, CLS, NMT, R);
-    constexpr unsigned VROW = W * 4u, VSLOT = R * VROW;                      // h and q rows
+    constexpr unsigned VROW = W * 4u, VSLOT = R * VROW;                      // rows of hidden values
     constexpr unsigned ZSLOT = res_z_slot(BF, CLS), ZWAVE = res_z_wave(BF, CLS);   // the joint's operand
     constexpr int JREGS = res_joint_regs(BF, CLS);
     constexpr int ZS = 16 * NMT;                 // samples of the longest joint step
@@ -1369,7 +1370,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             // order, so polls behind these stores wait for the memory side to take them (label looping of 32 utterances 1470 us with the
             // stores before the polls, 1374 us now, together with the polls apart, below).
             // (No condition around the stores, or what was loaded before them would be waited for together with them.  They are done, the
-            // marks among them, when the wave's next polls are: of the second layer's vector, or of q.)
+            // marks among them, when the wave's next polls are: of the second layer's vector, or of the joint's operand, wait_z.)
             auto forward_h = [&](int layer) {
                 const Place l = place_of(lane_id());
                 const unsigned o = has_cells && l.ok ? (unsigned)l.row * VROW + (unsigned)(u0 + l.lu) * 4u : 0x80000000u;
@@ -1427,6 +1428,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 RES_MARK(3);
                 if constexpr (PAIR) {
                     if (n > 1) wait_pre(n - 1, NL - 1);
+                    RES_MARK(4);
                     commit(NL - 1);
                 }
                 if (has_cells) {
@@ -1439,7 +1441,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     publish_h(1, l, h);
                     if constexpr (PAIR && !ONE) keep_state(1);
                 }
-                RES_MARK(4);
+                RES_MARK(5);
                 // (while the hand-over is on its way) the recurrent part of the next step's first layer
                 if constexpr (NREC > 1) {
                     r4u v[NB];
@@ -1454,14 +1456,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                         request<NB>(x, off, bo.h[1] + slot_at(n, VSLOT), v, __builtin_amdgcn_inverse_ballot_w64(take));
                         ordered();
                     });
-                    RES_MARK(5);
+                    RES_MARK(6);
                     unsigned off[NB];
                     const int lane = lane_id();
                     places(off, lane);
                     receive_rest<NB>(p, x, off, bo.h[1] + slot_at(n, VSLOT), v, __builtin_amdgcn_inverse_ballot_w64(take));
                     x1.set(v, lane);
                 } else {
-                    RES_MARK(5);
+                    RES_MARK(6);
                     // A poll that comes too early is repeated after 0.25 us, and slows down what it waits for: the first one
                     // 320 cycles on.  (32 utterances 1292, 1316 and 1144 us without the pause, three draws, 1266, 1285, 1120 with 128
                     // cycles, 1263, 1281, 1115 with 192, 1256, 1277, 1108 with 320, 1267, 1285, 1116 with 448; one utterance 525, 522, 521, 522, 522.
@@ -1472,14 +1474,14 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     if (PAIR) forward_h(1);
                 }
             }
-            RES_MARK(6);
+            RES_MARK(7);
             // prediction-side joint projection
             stage<BF, CLS, R, 2, kResProjRow>(w_pr, x1, sums_pr, x.wave);
             // this wave's frames are in LDS (what the other waves have stored by now, marks too, their polls for z wait for)
             if (x.wave >= 5) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
             if (x.wave >= kFormers) publish_z(nt_, jn);
-            RES_MARK(7);
+            RES_MARK(8);
             // (while z is on its way) the recurrent part of the top layer's next step
             if constexpr (NREC > 0) {
                 // (The first tile is asked for when the work that fills the time is all but done.)
@@ -1487,8 +1489,8 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             } else {
                 ask_z();
             }
-            RES_MARK(8);
             RES_MARK(9);
+            RES_MARK(10);
         } else {
             if constexpr (FRAMES_FIRST) __builtin_amdgcn_s_setprio(0);
             if (x.wave >= kFormers) {
@@ -1496,7 +1498,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 publish_z(nt_, jn);
             }
-            RES_MARK(10);
+            RES_MARK(11);
             ask_z();
         }
         // ---- joint step ----------------------------------------------------------------------------
@@ -1530,7 +1532,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     if ((small | beyond) != 0ull) again = unheld(small, fine, beyond);
                 }
             }
-            RES_MARK(9);
+            RES_MARK(10);
             // the partner's weights of column tile c
             auto partner = [&](auto i_, auto part_, int c, int lane) {
                 constexpr int i = decltype(i_)::value, N = i < NF ? 4 : 2;
@@ -1753,9 +1755,10 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     }
                 }
             }
-            RES_MARK(11);
+            RES_MARK(12);
             // sixteen lanes per sample, two columns each
             __syncthreads();
+            RES_MARK(13);
             const int tid = (x.wave * 64 + lane_id());
             if (tid < 16 * NT * 16) {
                 // (two tiles: the first four waves the columns of the even rank, the others those of the odd one, as that rank's)
@@ -1836,7 +1839,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                 }
             }
         }
-        RES_MARK(12);
+        RES_MARK(14);
         // One layer: what the next prediction step's cells add to the row of T0, while the keys travel (one layer of 640, 32 utterances 870 us and 854
         // with it, 8 571 and 559, the small model 271 and 266.  Two layers in bfloat16 have no register for it; through LDS: no gain.)
         if constexpr (NL == 1)
@@ -1911,7 +1914,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
                     if (p.logps) rc.s_lp[s] = lp2;
                 }
             }
-            RES_MARK(13);
+            RES_MARK(15);
         }
         // ---- loop control of one utterance: the same, with everything but the results of the frames uniform -------------------
         // (Tables of rows, their places in a step and the choice of those that wait are nothing to one row.  us a call: one utterance 341 and 326, five with
@@ -1920,7 +1923,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             const int lane = lane_id(), at = lane & 15;
             if (PAIR) load_pre(n_pred, 0, pre[0]);           // (as below)
             __syncthreads();
-            RES_MARK(14);
+            RES_MARK(16);
             if (FRAMES_FIRST && !has_cells) __builtin_amdgcn_s_setprio(2);
             const int mine = rc.s_k[at], left = only.len - only.t, avail = min(16, left);
             int pos = 0, dval = 0;
@@ -1978,7 +1981,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             // (on its way during the rest: the helpers' results take 0.85 us, and what is left of the step 0.75)
             if (PAIR) load_pre(n_pred, 0, pre[0]);
             __syncthreads();
-            RES_MARK(14);
+            RES_MARK(16);
             if (FRAMES_FIRST && !has_cells) __builtin_amdgcn_s_setprio(2);
             const int mine = rc.s_k[lane & (kResSamples - 1)], row0 = lane_const >> 25 & 31;
             // (a row that does not take part has nothing left for now)
@@ -2092,7 +2095,7 @@ __global__ void __launch_bounds__(kResThreads, 1) resident_kernel(const Resident
             if (!change && !later) set_up_samples(lane, w.t, b, w.len);
         }
         ok = rc.ok != 0;
-        RES_MARK(15);
+        RES_MARK(17);
     }
     };
     if constexpr (!HALVES) {
